@@ -65,8 +65,9 @@ constexpr int64_t kBalancedLdyMax = 1 << 20;
 struct Hints {
     double col_span = 0.0;
     double cv_row = -1.0;
+    int64_t max_row = -1;
     Hints() = default;
-    explicit Hints(const dgsp_features_t* f) { if (f) { col_span = f->col_span; cv_row = f->cv_row; } }
+    explicit Hints(const dgsp_features_t* f) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
 };
 
 struct Problem {
@@ -78,6 +79,7 @@ struct Problem {
     int phase = DGSP_PHASE_ALL;
     double col_span = 0.0;   // mean column span of a row / K; 0 = unknown
     double cv_row = -1.0;    // coefficient of variation of the row lengths; < 0 = unknown
+    long long max_row = -1;  // entries of the longest row; < 0 = unknown
     int switches = 0;        // DGSP_ABL_* (measurement aids)
     bool scaled = false;     // Y = alpha * A X + beta * Y instead of Y = A X
     float alpha = 1.0f, beta = 0.0f;
@@ -403,89 +405,121 @@ int launch_nb_pr_v(const Problem& p) {
     return DGSP_OK;
 }
 
-int launch_nb_pr(const Problem& p) {
-    switch (nb_pr_lane_width(p.N, p.switches)) {
-        case 8: return launch_nb_pr_v<8, 1>(p);
-        case 4: return launch_nb_pr_v<4, kNbPrKq>(p);
-        case 3: return launch_nb_pr_v<3, kNbPrKq>(p);
-        case 2: return launch_nb_pr_v<2, kNbPrKq>(p);
-        default: return launch_nb_pr_v<1, kNbPrKq>(p);
+// One to three dense columns (one column per lane at any width when vector loads are switched off).
+template <int V, bool XBUF, int DEPTH>
+int launch_nb_sr_v(const Problem& p) {
+    const SrColumns cols = sr_columns(p.N, V, p.N >= 128);
+    if (cols.blocks > 65535u) return DGSP_ERR_INVALID_ARG;
+    const int logU = kNbSrLogTile - 6 + cols.logG;   // items per lane-group run
+    const dim3 grid(balanced_blocks(p, kNbSrTile, resident_blocks_per_cu(nb_sr_kernel<V, XBUF, DEPTH>), false, cols.blocks), cols.blocks);
+    if (p.phase != DGSP_PHASE_MAIN)
+        if (int rc = launch_prepare(p, grid.x * kWavesPerBlock * kSubRanges, (unsigned)logU, kNbSrLogTile)) return rc;
+    if (p.phase != DGSP_PHASE_PREPARE) {
+        if (p.scaled)
+            DGSP_LAUNCH((nb_sr_kernel<V, XBUF, DEPTH, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx,
+                        p.vals, p.X, p.Y, cols.logG, cols.cols_per_block, Scaling{p.alpha, p.beta});
+        else
+            DGSP_LAUNCH((nb_sr_kernel<V, XBUF, DEPTH>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
+                        cols.logG, cols.cols_per_block);
     }
+    return DGSP_OK;
 }
 
-template <int V, bool XBUF, int DEPTH, bool RAGGED>
-int launch_nb_sr_v(const Problem& p) {
-    // N a multiple of 64: column blocks of 64 dense columns (256 bytes of a row of X), several blocks over
-    // the same chunks, one after the other in launch order.  The rows of X that many matrix rows share (hub
-    // columns of a power-law graph) then compete for the L2 with a quarter-kilobyte each instead of N * 4
-    // bytes; re-reading the 8 bytes of an entry per block costs 3 % of what the block gathers for it.
-    SrColumns cols = sr_columns(p.N, V, p.N >= 128);
-    // comparison: column blocks of 32 dense columns (one 128-byte line of a row of X per entry and block)
-    if ((p.switches & DGSP_ABL_COLUMN_BLOCKS_32) && V == 4 && p.N % 32 == 0 && p.N >= 64)
-        cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
-    // A matrix with fewer tiles than the machine has room for waves (two per SIMD) leaves CUs idle: a wave takes a
-    // whole tile of 512 items whatever N is.  Narrower column blocks make more workgroups out of the same tiles
-    // (65 536 rows of 4 entries at N = 32: 640 tiles on 1024 SIMDs; two blocks of 16 columns instead of one of 32).
-    // Only where entries make up most of the items: every block walks the row ends again, and in a matrix of
-    // mostly empty rows that walk is the work (262 144 rows with 52 000 entries at N = 32: 33 -> 56 us when split).
-    if (p.nnz >= p.M) {
-        const long long tiles = (p.nnz + (long long)p.M + kNbSrTile - 1) / kNbSrTile;
-        const long long room = (long long)device_info().cus * kWavesPerBlock * 2;
-        while (tiles * cols.blocks < room && cols.logG > 0 && cols.cols_per_block % (2 * V) == 0) {
-            const int per = cols.cols_per_block / 2;
-            cols = SrColumns{sr_lanes_log2(per, V), per, (unsigned)((p.N + per - 1) / per)};
-        }
-    }
-    const int logG = cols.logG;
+template <int V>
+int launch_nb_sr_pick(const Problem& p) {
+    const bool xb = x_fits_descriptor(p);
+    if (banded(p)) return xb ? launch_nb_sr_v<V, true, 4>(p) : launch_nb_sr_v<V, false, 4>(p);
+    constexpr int D = sr_depth_scattered<V>();
+    return xb ? launch_nb_sr_v<V, true, D>(p) : launch_nb_sr_v<V, false, D>(p);
+}
+
+// Four columns and more.  Items a wave takes at least: fewer and the two searches that open a chunk outweigh it
+// (4096 rows of 8 at N = 32: 5.9 / 6.7 / 8.3 us with 64 / 128 / 256; 20 001 uneven rows of 10: 14.4 / 11.4 / 12.2 us).
+constexpr long long kRunItems = 128;
+// Column blocks of 32 (one line of a row of X per entry and block, every XCD on one block) instead of 64: the slice of X
+// an L2 sees is half as large, at one more pass over A for every 64 columns.  It pays where a few columns hold most
+// entries - a graph; the row lengths stand in for the columns' - and the matrix is large: R-MAT 2^20 x 16 at N = 64 / 128
+// 607 / 1088 -> 527 / 1022 us, 2^18 x 16 at N = 64 100 -> 93 us; but 2^17 x 16 51 -> 55 us, uniform columns 655 -> 697 us
+// (and N = 256, eight blocks: 2081 -> 2302 us).
+constexpr double kGraphCvMin = 4.0;
+constexpr long long kGraphNnzMin = 4000000;
+
+template <int LOGG, bool XBUF>
+int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     const unsigned col_blocks = cols.blocks;
     if (col_blocks > 65535u) return DGSP_ERR_INVALID_ARG;
-    const int logU = kNbSrLogTile - 6 + logG;   // items per lane-group run
-    // a tile's rows are stored through 32-bit byte offsets from the tile's first row
-    if (p.ldy > kBalancedLdyMax) return DGSP_ERR_UNSUPPORTED;
-    dim3 grid(balanced_blocks(p, kNbSrTile, resident_blocks_per_cu(nb_sr_kernel<V, XBUF, DEPTH, false, RAGGED>), false, col_blocks), col_blocks);
-    // Two or four column blocks of a wide X (N = 128 ... 256): every XCD works on one block only, so that an L2 sees
-    // one block's slice of X and the slices do not compete (R-MAT 2^20 at N = 128: 1125 -> 1062 us, N = 256: 2154 ->
-    // 2097 us; uniform columns: 0 ... +4 %).  With eight blocks (N = 512) every XCD would walk the whole matrix alone,
-    // which measured 10-20 % slower on every matrix tried: from there on the blocks stay a second grid dimension.
-    // The grid is then one-dimensional with whole workgroups per XCD.  DGSP_ABL_BLOCKS_OFF_XCDS keeps the blocks as
-    // a second grid dimension (the comparison); eight blocks of 32 columns (DGSP_ABL_COLUMN_BLOCKS_32 at N = 256)
-    // are tied to XCDs too, so that both comparisons can be combined.
+    dim3 grid(balanced_blocks(p, kRunItems, resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, false>), false, col_blocks), col_blocks);
+    // Two or four column blocks of a wide X: every XCD works on one block only, so that an L2 sees one block's slice of X
+    // and the slices do not compete.  With eight blocks every XCD would walk the whole matrix alone (10-20 % slower): from
+    // there on the blocks stay a second grid dimension.  DGSP_ABL_BLOCKS_OFF_XCDS: the comparison.
     unsigned pinned = 0;
-    if (!(p.switches & DGSP_ABL_BLOCKS_OFF_XCDS) && p.N >= 128 &&
+    if (!(p.switches & DGSP_ABL_BLOCKS_OFF_XCDS) && p.N >= 64 &&
         (col_blocks == 2 || col_blocks == 4 || (col_blocks == 8 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)))) {
         pinned = col_blocks;
         const unsigned per_xcd = (grid.x * col_blocks + kXcd - 1) / kXcd;         // as many workgroups as before, in one dimension
         grid = dim3(per_xcd * kXcd, 1);
     }
     const unsigned chunk_groups = pinned ? grid.x / pinned : grid.x;              // workgroups that share one chunk list
-    if (p.phase != DGSP_PHASE_MAIN)
-        if (int rc = launch_prepare(p, chunk_groups * kWavesPerBlock * kSubRanges, (unsigned)logU, kNbSrLogTile)) return rc;
+    // Whole rows per chunk when the longest is at most four shares (or one block of entries): the wave that has it ends
+    // later by as much, which never measured slower than the atomics and the prepare launch it saves (3-5 us).
+    const long long share = (p.nnz + (long long)p.M) / ((long long)chunk_groups * kWavesPerBlock);
+    const int snap = p.nnz >= 0 && p.max_row >= 0 && (p.max_row <= 4 * share || p.max_row <= kRunBlock);
+    if (p.phase != DGSP_PHASE_MAIN && !snap)
+        if (int rc = launch_prepare(p, chunk_groups * kWavesPerBlock * kSubRanges, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
-        if (p.scaled) {
-            DGSP_LAUNCH((nb_sr_kernel<V, XBUF, DEPTH, true, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx,
-                        p.vals, p.X, p.Y, logG, cols.cols_per_block, Scaling{p.alpha, p.beta}, pinned);
-        } else {
-            DGSP_LAUNCH((nb_sr_kernel<V, XBUF, DEPTH, false, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
-                        logG, cols.cols_per_block, Scaling{1.0f, 0.0f}, pinned);
-        }
+        if (p.scaled)
+            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
+                        cols.cols_per_block, snap, Scaling{p.alpha, p.beta}, pinned);
+        else
+            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, false>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
+                        cols.cols_per_block, snap, Scaling{1.0f, 0.0f}, pinned);
     }
     return DGSP_OK;
 }
 
-template <int V, bool RAGGED>
-int launch_nb_sr_pick(const Problem& p) {
-    const bool xb = x_fits_descriptor(p);
-    if (banded(p)) return xb ? launch_nb_sr_v<V, true, 4, RAGGED>(p) : launch_nb_sr_v<V, false, 4, RAGGED>(p);
-    constexpr int D = sr_depth_scattered<V>();
-    return xb ? launch_nb_sr_v<V, true, D, RAGGED>(p) : launch_nb_sr_v<V, false, D, RAGGED>(p);
+template <bool XBUF>
+int launch_nb_sr_run_x(const Problem& p) {
+    // N a multiple of 64 from 128 on: column blocks of 64, so that the rows of X that many matrix rows share compete for
+    // the L2 with a quarter-kilobyte each instead of N * 4 bytes
+    SrColumns cols = sr_columns(p.N, 4, p.N >= 128);
+    const bool graph = p.cv_row >= kGraphCvMin && p.nnz >= kGraphNnzMin && (p.N == 64 || p.N == 128);
+    if (p.N % 32 == 0 && p.N >= 64 && ((p.switches & DGSP_ABL_COLUMN_BLOCKS_32) || graph))
+        cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
+    switch (cols.logG) {
+        case 0: return launch_nb_sr_run_v<0, XBUF>(p, cols);
+        case 1: return launch_nb_sr_run_v<1, XBUF>(p, cols);
+        case 2: return launch_nb_sr_run_v<2, XBUF>(p, cols);
+        case 3: return launch_nb_sr_run_v<3, XBUF>(p, cols);
+        case 4: return launch_nb_sr_run_v<4, XBUF>(p, cols);
+        case 5: return launch_nb_sr_run_v<5, XBUF>(p, cols);
+        default: return launch_nb_sr_run_v<6, XBUF>(p, cols);
+    }
+}
+
+int launch_nb_sr_run(const Problem& p) {
+    // the kernel spends the upper half of the offset range on switching lanes off
+    return dense_bytes(p.K, p.ldx, p.N) <= 0x7fffffffull ? launch_nb_sr_run_x<true>(p) : launch_nb_sr_run_x<false>(p);
 }
 
 int launch_nb_sr(const Problem& p) {
-    const SrShape shape = sr_shape(p);
-    switch (shape.v) {
-        case 4: return shape.ragged ? launch_nb_sr_pick<4, true>(p) : launch_nb_sr_pick<4, false>(p);
-        case 2: return launch_nb_sr_pick<2, false>(p);
-        default: return launch_nb_sr_pick<1, false>(p);
+    if (p.ldy > kBalancedLdyMax) return DGSP_ERR_UNSUPPORTED;
+    if (p.N >= 4 && !(p.switches & DGSP_ABL_SCALAR_DENSE_LOADS)) return launch_nb_sr_run(p);
+    return p.N == 2 && !(p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) ? launch_nb_sr_pick<2>(p) : launch_nb_sr_pick<1>(p);
+}
+
+// Five to eight columns without a comparison switch: the same scheme - consecutive entries summed in a lane, one
+// segmented scan over the lanes' open rows - with two lanes per entry (nb_sr_run_kernel), which reads a row of X in one
+// access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 156 / 156 -> 140 / 139 us, Zipf rows of 16 at N = 8 61 -> 58 us,
+// lognormal rows of 64 at N = 5 / 8 173 / 190 -> 143 / 179 us; a tie on small matrices.
+int launch_nb_pr(const Problem& p) {
+    const int v = nb_pr_lane_width(p.N, p.switches);
+    if (v == 8 && p.N <= 8 && p.switches == 0 && p.ldy <= kBalancedLdyMax) return launch_nb_sr_run(p);
+    switch (v) {
+        case 8: return launch_nb_pr_v<8, 1>(p);
+        case 4: return launch_nb_pr_v<4, kNbPrKq>(p);
+        case 3: return launch_nb_pr_v<3, kNbPrKq>(p);
+        case 2: return launch_nb_pr_v<2, kNbPrKq>(p);
+        default: return launch_nb_pr_v<1, kNbPrKq>(p);
     }
 }
 
@@ -546,7 +580,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     switch (algo) {
         case DGSP_RS_SR: return phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_sr(p);

@@ -293,35 +293,6 @@ __device__ __forceinline__ LaneColumns lane_columns(unsigned block, int cols_per
     return c;
 }
 
-// Stores a lane's V results at byte_offset (kOutOfRange: nothing).  With RAGGED the last lane of a row shares its
-// first `skip` columns with its neighbour, and both hold the same bits there (the same entries in the same order
-// went into them).  In the plain product both may store them: whichever write lands last changes nothing, also
-// when the neighbour sits in another column block and writes at another time.  LEAVE_SHARED_OUT (the scaled form,
-// where a result depends on the old Y and the neighbour may have replaced that already): the lane with skip != 0
-// stores exactly its last `tail` = N % V values (wave-uniform) in one more store of that width, issued by the
-// whole wave and switched off everywhere else.
-template <int V, bool RAGGED, int AUX = 0, bool LEAVE_SHARED_OUT = true>
-__device__ __forceinline__ void buffer_store_columns(__amdgpu_buffer_rsrc_t rsrc, unsigned byte_offset, const float (&x)[V],
-                                                     int skip, int tail) {
-    if constexpr (!RAGGED || !LEAVE_SHARED_OUT) {
-        buffer_store_vec<V, AUX>(rsrc, byte_offset, x);
-    } else {
-        static_assert(V == 4, "the shared lane exists at four columns per lane only");
-        buffer_store_vec<V, AUX>(rsrc, skip == 0 ? byte_offset : kOutOfRange, x);
-        const bool on = skip != 0 && byte_offset != kOutOfRange;
-        if (tail == 1) {
-            const float t[1] = {x[3]};
-            buffer_store_vec<1, AUX>(rsrc, on ? byte_offset + 12u : kOutOfRange, t);
-        } else if (tail == 2) {
-            const float t[2] = {x[2], x[3]};
-            buffer_store_vec<2, AUX>(rsrc, on ? byte_offset + 8u : kOutOfRange, t);
-        } else {
-            const float t[3] = {x[1], x[2], x[3]};
-            buffer_store_vec<3, AUX>(rsrc, on ? byte_offset + 4u : kOutOfRange, t);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // wave64 segmented inclusive scan on DPP (vectorized segment reduction,
 // paper Section 2.1.1)
@@ -346,6 +317,7 @@ __device__ __forceinline__ float dpp_or_zero(float v) {
 }
 
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
+constexpr int kDppRowRor1 = 0x121, kDppRowRor2 = 0x122, kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;   // rotations inside a row of 16
 constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 constexpr int kDppWaveShr1 = 0x138;   // lane l reads lane l-1 across the whole wave; lane 0 gets the fill value
 

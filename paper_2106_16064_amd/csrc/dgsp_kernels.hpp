@@ -1236,19 +1236,19 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
 // cross the tile's own ends go to memory with atomic adds (prepare kernel:
 // rows split by a tile boundary).
 // blockIdx.y selects the block of G*V dense columns.
+// Used at one to three columns (and with one column per lane at any width, the comparison without vector loads):
+// from four columns on nb_sr_run_kernel takes over.
 
 constexpr int kNbSrTile = 512;
 constexpr int kNbSrLogTile = 9;
 
-template <int V, bool XBUF, int DEPTH, bool AXPBY = false, bool RAGGED = false>
+template <int V, bool XBUF, int DEPTH, bool AXPBY = false>
 __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        int logG, int cols_per_block, Scaling sc = Scaling{1.0f, 0.0f},
-                                                        unsigned pinned_blocks = 0) {
+                                                        int logG, int cols_per_block, Scaling sc = Scaling{1.0f, 0.0f}) {
     constexpr int W = kNbSrTile;
-    constexpr int kStoreAux = V == 4 ? 2 : 0;           // results leave non-temporal when rows are 16 bytes or more per lane
     constexpr int kSlotFloats = 2 * kWave * V;          // (64/G + 1) slots of G*V floats each, G <= 64
     __shared__ __align__(16) int s_col[kWavesPerBlock][W];
     __shared__ __align__(16) float s_val[kWavesPerBlock][W];
@@ -1271,25 +1271,12 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
     const int groups = kWave >> logG;
     const int logU = kNbSrLogTile - 6 + logG;
     const unsigned U = 1u << logU;
-    // Column block and place in the chunk list.  Normally blockIdx.y is the column block and blockIdx.x (made
-    // XCD-contiguous) the place.  pinned_blocks = nb > 0 (nb in {2, 4}, or 8 for a comparison; gridDim = (8 k, 1)): the
-    // workgroups of XCD x all take column block x % nb, so that an L2 only ever sees one block's slice of X; the
-    // 8 / nb XCDs of a block share its chunk list, each a contiguous part.
-    unsigned col_block = blockIdx.y;
-    unsigned wg = 0, nwg = 0;
-    if (pinned_blocks) {
-        const unsigned x = blockIdx.x % kXcd, i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
-        col_block = x % pinned_blocks;
-        wg = (x / pinned_blocks) * per_xcd + i;
-        nwg = (kXcd / pinned_blocks) * per_xcd;
-    }
-    const LaneColumns mine = lane_columns<V, RAGGED>(col_block, cols_per_block, gl, N);
+    const LaneColumns mine = lane_columns<V, false>(blockIdx.y, cols_per_block, gl, N);
     const long long n = mine.first;
     const bool col_ok = mine.any;
-    const int tail = N % V;                  // columns of the lane that shares its window (RAGGED)
 
     // chunks start at multiples of U: runs stay aligned
-    const ChunkPlan plan = pinned_blocks ? plan_chunks(rowptr, M, (unsigned)logU, wg, nwg) : plan_chunks(rowptr, M, (unsigned)logU);
+    const ChunkPlan plan = plan_chunks(rowptr, M, (unsigned)logU);
     const unsigned nnz = plan.nnz;
     const unsigned long long y_elems = dense_bytes(M, ldy, N) / 4ull;
     // XBUF: the dense operand is read through a descriptor (its byte offsets fit 32 bits)
@@ -1359,9 +1346,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
             (void*)(Y + first_elem), 0, left > 0xffffffffull ? 0xffffffffu : (unsigned)left, kBufferFlags);
 
         // rows without entries get their zeros here, all groups together (group g: local rows g, g + groups, ...),
-        // so that the walk below meets a store only where a row with entries ends.  With four columns per lane
-        // results are stored non-temporal here and in the walk: nobody reads them again, the L2 is for rows of X
-        // (1-4 % measured at N >= 8; at N = 1, 2 the narrow stores were 4-8 % slower that way).
+        // so that the walk below meets a store only where a row with entries ends.
         {
             float zero[V];
 #pragma unroll
@@ -1382,9 +1367,9 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 #pragma unroll
                         for (int i = 0; i < V; ++i) out[i] = 0.0f;
                         scale_into<V>(out, yrows, off, sc);               // beta * Y
-                        buffer_store_columns<V, RAGGED, kStoreAux, true>(yrows, off, out, mine.skip, tail);
+                        buffer_store_vec<V>(yrows, off, out);
                     } else {
-                        buffer_store_columns<V, RAGGED, kStoreAux, false>(yrows, off, zero, mine.skip, tail);
+                        buffer_store_vec<V>(yrows, off, zero);
                     }
                 }
             }
@@ -1453,9 +1438,9 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 #pragma unroll
                     for (int i = 0; i < V; ++i) out[i] = acc[i];
                     scale_into<V>(out, yrows, off, sc);
-                    buffer_store_columns<V, RAGGED, kStoreAux, true>(yrows, off, out, mine.skip, tail);
+                    buffer_store_vec<V>(yrows, off, out);
                 } else {
-                    buffer_store_columns<V, RAGGED, kStoreAux, false>(yrows, off, acc, mine.skip, tail);
+                    buffer_store_vec<V>(yrows, off, acc);
                 }
                 if (closing) {
                     if (!direct) to_slot(true);
@@ -1519,12 +1504,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
                             for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // lands on beta * Y (prepare)
                         }
                     }
-                    if (RAGGED && mine.skip != 0) {
-#pragma unroll
-                        for (int i = 1; i < V; ++i) {
-                            if (i >= mine.skip) { if (whole) y[i] = val[i]; else unsafeAtomicAdd(y + i, val[i]); }
-                        }
-                    } else if (whole) {
+                    if (whole) {
                         store_vec_dword_aligned<V>(y, val);
                     } else {
                         atomic_add_vec<V>(y, val);
@@ -1537,6 +1517,330 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
         is = ie;
     }
     }   // next chunk
+}
+
+// ===========================================================================
+// nnz-balanced, sequential reduction on blocks of entries (four or more dense columns)
+// ===========================================================================
+//
+// The wave's chunk (an equal share of merge-path items, as above) is walked in blocks of 512 consecutive entries:
+//   1. the block's entries, loaded a block ahead, go to LDS as (byte offset of the row of X, value) pairs;
+//   2. the rows that end in the block leave one bit each at their last entry and their numbers in a list; rows
+//      without entries are zeroed on the way, all lane groups together;
+//   3. the R = 64 / G lane groups (G lanes span the columns, four each) walk one run of U = 512 / R entries each, in
+//      order, eight dense-row loads in flight.  What a step costs is one LDS read, one address addition, the load and
+//      four multiply-adds: run bounds, row ends and row numbers are not looked at, because a batch's row-end bits of
+//      all groups come as one scalar mask and only a step that has a bit there leaves this path.  At such a step the
+//      groups concerned store their sum as the next row of the list and start afresh;
+//   4. a row that crosses runs is what the first row end of a run finds unfinished: the runs' open sums meet in a
+//      segmented scan over the R groups (the vectorized segment reduction of Section 2.1.1 with runs in place of
+//      entries), the last one is carried to the next block.
+// Bound by: what the L2s have to fetch of X (a probe that only gathers rows of X tops out at 7.5 TB/s of L2 misses),
+// and for that the walk has to be short of vector instructions: a wave instruction occupies its SIMD for four cycles,
+// and the walk with row state per lane group that this one replaces spent about 45 of them per step and waited for
+// every single load.  Measured, that walk against this one: R-MAT 2^20 x 16 at N = 8 / 16 / 32 / 128: 196 / 224 / 302 /
+// 1029 us -> 139 / 181 / 250 / 993 us; 20 001 uneven rows of 10 at N = 32: 25 -> 12 us; 65 536-vertex R-MAT at N = 41: 65 -> 33 us.
+//
+// SNAP (host: the longest row is short against a wave's share): a row belongs wholly to the chunk that holds its
+// first item, so nothing is added to memory, the prepare launch falls away and the result is the same from run to
+// run.  Otherwise rows that cross a chunk end are added with atomics to what the prepare launch left.
+//
+// When N is no multiple of four the last lane's window ends at N and overlaps its neighbour's: plain stores may repeat
+// the shared columns (same bits), scaled stores and atomic adds leave them to the neighbour.
+//
+// pinned_blocks = nb (2 or 4; gridDim = (8 k, 1)): the workgroups of XCD x all take column block x % nb, so that an L2
+// only ever sees one block's slice of X; the 8 / nb XCDs of a block share its chunk list, each a contiguous part.
+// Otherwise blockIdx.y is the column block.
+constexpr int kRunBlock = 512;       // entries per block
+constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
+
+// the sum of the lanes' words under bitwise or, wave-uniform
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+    v |= dpp_or_zero_u<kDppRowShr1, 0xf>(v);
+    v |= dpp_or_zero_u<kDppRowShr2, 0xf>(v);
+    v |= dpp_or_zero_u<kDppRowShr4, 0xf>(v);
+    v |= dpp_or_zero_u<kDppRowShr8, 0xf>(v);
+    v |= dpp_or_zero_u<kDppRowBcast15, 0xa>(v);
+    v |= dpp_or_zero_u<kDppRowBcast31, 0xc>(v);
+    return (unsigned)read_lane((int)v, kWave - 1);
+}
+
+template <int LOGG, bool XBUF, bool AXPBY>
+__global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
+                                                           const int* __restrict__ rowptr, const int* __restrict__ colidx,
+                                                           const float* __restrict__ vals, const float* __restrict__ X,
+                                                           float* __restrict__ Y, int cols_per_block, int snap, Scaling sc,
+                                                           unsigned pinned_blocks) {
+    constexpr int W = kRunBlock, E = W / kWave, B = kRunBatch;
+    constexpr int G = 1 << LOGG, R = kWave / G;
+    __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
+    __shared__ unsigned s_bits[kWavesPerBlock][W / 32 + 2];             // bit e: a row ends with entry e of the block
+    __shared__ int s_rows[kWavesPerBlock][W + 1];                       // those rows, in order
+    const int lane = lane_id();
+    const int wib = wave_in_block();
+    uint2* ent = s_ent[wib];
+    unsigned* bits = s_bits[wib];
+    int* rows = s_rows[wib];
+    const int gl = lane & (G - 1), g = lane >> LOGG;
+
+    unsigned col_block = blockIdx.y, wg, nwg;
+    if (pinned_blocks) {
+        const unsigned x = blockIdx.x % kXcd, i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
+        col_block = x % pinned_blocks;
+        wg = (x / pinned_blocks) * per_xcd + i;
+        nwg = (kXcd / pinned_blocks) * per_xcd;
+    } else {
+        wg = xcd_contiguous(blockIdx.x, gridDim.x);
+        nwg = gridDim.x;
+    }
+    const LaneColumns mine = lane_columns<4, true>(col_block, cols_per_block, gl, N);
+    const bool col_ok = mine.any;
+
+    const ChunkPlan plan = plan_chunks(rowptr, M, 6, wg, nwg);
+    unsigned d0, d1;
+    if (!plan.range(0, d0, d1)) return;
+    int is, ie;
+    wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie);
+    unsigned js, je;
+    bool first_split = false;
+    if (snap) {
+        // rows that started before a chunk's first item belong to the chunk before
+        if (is < M && (unsigned)is + (unsigned)rowptr[is] < d0) ++is;
+        if (ie < M && (unsigned)ie + (unsigned)rowptr[ie] < d1) ++ie;
+        js = (unsigned)rowptr[is];
+        je = (unsigned)rowptr[ie];
+    } else {
+        js = d0 - (unsigned)is;
+        je = d1 - (unsigned)ie;
+        first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
+    }
+    is = uniform(is); ie = uniform(ie);
+    js = (unsigned)uniform((int)js); je = (unsigned)uniform((int)je);
+    const int r_first = first_split ? is : -1;
+    const unsigned n_ent = je - js;
+    const unsigned long long chunk_bytes = (unsigned long long)n_ent * 4ull;
+    const __amdgpu_buffer_rsrc_t rc = make_buffer(colidx + js, chunk_bytes);
+    const __amdgpu_buffer_rsrc_t ra = make_buffer(vals + js, chunk_bytes);
+    const __amdgpu_buffer_rsrc_t rx = make_buffer(X, XBUF ? dense_bytes(K, ldx, N) : 0ull);
+    // XBUF: X spans less than 2 GB, so half of the offset range switches off a lane without columns, and an entry past
+    // the chunk's end (a switched-off lane there wraps to the start of X: read, never used)
+    constexpr unsigned kOff = 0x80000000u;
+    const unsigned lane_bytes = col_ok ? (unsigned)mine.first * 4u : kOff;
+    const float* lane_x = X + (col_ok ? mine.first : 0ll);
+    const unsigned pitch = (unsigned)ldx * 4u;
+
+    int lc[E]; float la[E];
+    auto load_entries = [&](unsigned from) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const unsigned off = (from + (unsigned)(e * kWave + lane)) * 4u;
+            lc[e] = buffer_stream_i32(rc, off);                 // past the chunk: column 0, value 0
+            la[e] = buffer_stream_f32(ra, off);
+        }
+    };
+    // start and end offsets of rows first .. first + 63 (lane l: row first + l; past the last one 0)
+    auto load_window = [&](int first, unsigned& start, unsigned& end) {
+        const unsigned long long bytes = first < ie ? (unsigned long long)(ie + 1 - first) * 4ull : 0ull;
+        const __amdgpu_buffer_rsrc_t rr = make_buffer(rowptr + (bytes ? first : 0), bytes);
+        typedef unsigned u2 __attribute__((ext_vector_type(2)));
+        const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rr, (unsigned)lane * 4u, 0, 0);
+        start = t.x; end = t.y;
+    };
+    auto y_at = [&](int row) { return Y + (size_t)row * (size_t)ldy + mine.first; };
+    auto store4 = [&](float* y, const float (&v)[4]) {
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        f4u t = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(t, reinterpret_cast<f4u*>(y));
+    };
+    // a finished row's four columns of my lane
+    auto write_row = [&](int row, const float (&v)[4]) {
+        float* y = y_at(row);
+        if constexpr (AXPBY) {
+            float o[4] = {v[0], v[1], v[2], v[3]};
+            scale_into<4, true>(o, y, sc);
+            if (mine.skip != 0) {
+#pragma unroll
+                for (int i = 1; i < 4; ++i) if (i >= mine.skip) y[i] = o[i];
+            } else {
+                store4(y, o);
+            }
+        } else {
+            store4(y, v);
+        }
+    };
+    auto add_row = [&](int row, const float (&v)[4]) {
+        float* y = y_at(row);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i >= mine.skip) unsafeAtomicAdd(y + i, AXPBY ? sc.alpha * v[i] : v[i]);
+    };
+
+    unsigned w_start, w_end;
+    load_window(is, w_start, w_end);
+    load_entries(0);
+
+    float carry[4] = {0.0f, 0.0f, 0.0f, 0.0f};          // sum of the row that is open at the block's start (every group: its columns)
+    unsigned done = 0;                                  // entries before the block
+    do {
+        const unsigned nE = n_ent - done < (unsigned)W ? n_ent - done : (unsigned)W;
+        const unsigned to = done + nE;
+        // steps per group, a multiple of the batch; a short last block is still shared by all groups
+        const unsigned U = ((nE + R * B - 1) / (R * B)) * B;
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const bool in = (unsigned)(e * kWave + lane) < nE;
+            unsigned off;
+            if constexpr (XBUF) off = in ? (unsigned)lc[e] * pitch : kOff; else off = in ? (unsigned)lc[e] : kNoRow;
+            ent[e * kWave + lane] = make_uint2(off, __builtin_bit_cast(unsigned, la[e]));
+        }
+        if (lane < W / 32 + 2) bits[lane] = 0u;
+        wave_lds_sync();
+        // ---- rows that end in this block: a bit at their last entry, their numbers in order; rows without entries are
+        //      zeroed here, all groups together
+        int listed = 0;
+        auto take_rows = [&](unsigned start, unsigned end) {
+            const unsigned rel = end - js;
+            const bool live = is + lane < ie && rel <= to;
+            const bool has = live && end != start && rel > done;
+            const unsigned long long m_has = __ballot(has), m_zero = __ballot(live && end == start);
+            const int cnt = (int)__popcll(__ballot(live));
+            if (has) {
+                const unsigned q = rel - done - 1u;
+                atomicOr(bits + (q >> 5), 1u << (q & 31u));
+                rows[listed + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m_has >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m_has, 0u))] = is + lane;
+            }
+            listed += (int)__popcll(m_has);
+            if (m_zero != 0ull) {
+                float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+                for (int q = 0; q < G; ++q) {               // R rows per round
+                    const int t = q * R + g;
+                    if (((m_zero >> t) & 1ull) != 0ull && col_ok) write_row(is + t, zero);
+                }
+            }
+            is += cnt;
+            return cnt;
+        };
+        while (take_rows(w_start, w_end) == kWave) {
+            // crowded: the next seven windows at once
+            unsigned ms[E - 1], me[E - 1];
+            int cnt = kWave;
+#pragma unroll
+            for (int m = 0; m < E - 1; ++m) load_window(is + m * kWave, ms[m], me[m]);
+#pragma unroll
+            for (int m = 0; m < E - 1; ++m)
+                if (cnt == kWave) cnt = take_rows(ms[m], me[m]);
+            if (cnt != kWave) break;
+            load_window(is, w_start, w_end);
+        }
+        wave_lds_sync();
+        load_window(is, w_start, w_end);
+        if (to < n_ent) load_entries(to);
+
+        // ---- my group's run: entries [g * U, g * U + U) of the block; k: its next row end in `rows`
+        const unsigned p0 = (unsigned)g * U;
+        int k;
+        {
+            const unsigned word = lane < W / 32 ? bits[lane] : 0u;
+            unsigned n = (unsigned)__popc(word);
+            const unsigned own = n;
+            n += dpp_or_zero_u<kDppRowShr1, 0xf>(n);
+            n += dpp_or_zero_u<kDppRowShr2, 0xf>(n);
+            n += dpp_or_zero_u<kDppRowShr4, 0xf>(n);
+            n += dpp_or_zero_u<kDppRowShr8, 0xf>(n);        // lanes 0 ... 15: the block's 16 words
+            const int wi = (int)(p0 >> 5) < W / 32 ? (int)(p0 >> 5) : W / 32 - 1;
+            const unsigned before = (unsigned)__shfl((int)(n - own), wi);
+            const unsigned here = (unsigned)__shfl((int)word, wi);
+            k = p0 < (unsigned)W ? (int)(before + (unsigned)__popc(here & ((1u << (p0 & 31u)) - 1u))) : listed;
+        }
+        const int k0 = k;
+        int next = rows[k < W ? k : W];
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, head[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        // a run that starts inside a row: the first row end it meets is finished after the walk
+        bool pend = p0 == 0u ? true : ((bits[(p0 - 1u) >> 5] >> ((p0 - 1u) & 31u)) & 1u) == 0u;
+        bool closed = false;
+        for (unsigned s0 = 0; s0 < U; s0 += B) {
+            const unsigned p = p0 + s0;
+            float x[B][4], a[B];
+#pragma unroll
+            for (int s = 0; s < B; ++s) {
+                const uint2 t = ent[p + s];
+                a[s] = __builtin_bit_cast(float, t.y);
+                if constexpr (XBUF) {
+                    buffer_load_vec<4>(rx, t.x + lane_bytes, x[s]);
+                } else {
+                    const bool ok = t.x != kNoRow;
+                    load_vec_dword_aligned<4>(lane_x + (size_t)(ok ? t.x : 0u) * (size_t)ldx, x[s]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[s][i] = ok ? x[s][i] : 0.0f;
+                }
+            }
+            const unsigned m = (bits[p >> 5] >> (p & 31u)) & ((1u << B) - 1u);          // p is a multiple of B
+            const unsigned any = wave_or(m);
+#pragma unroll
+            for (int s = 0; s < B; ++s) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = fmaf(a[s], x[s][i], acc[i]);
+                if ((any >> s) & 1u) {                                       // wave-uniform
+                    if ((m >> s) & 1u) {
+                        if (pend) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) head[i] = acc[i];
+                        } else if (col_ok) {
+                            write_row(next, acc);
+                        }
+                        pend = false;
+                        closed = true;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[i] = 0.0f;
+                        ++k;
+                        next = rows[k];
+                    }
+                }
+            }
+        }
+        // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's
+        //      carry in front; a run that met a row end starts a new segment
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = acc[i] + ((g == 0 && !closed) ? carry[i] : 0.0f);
+        const unsigned long long m_closed = __ballot(closed);
+        // groups directly below mine in my segment
+        const unsigned long long below = m_closed & ((2ull << lane) - 1ull);
+        const int seg = below != 0ull ? ((63 - __builtin_clzll(below)) >> LOGG) : 0;
+        const int h = g - seg;
+#pragma unroll
+        for (int d = 1; d < R; d <<= 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float o = __shfl_up(v[i], (unsigned)(d * G));
+                v[i] += h >= d ? o : 0.0f;
+            }
+        }
+        float in[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float o = __shfl_up(v[i], (unsigned)G);
+            in[i] = g == 0 ? carry[i] : o;
+            carry[i] = __shfl(v[i], kWave - G + gl);
+        }
+        const bool starts_open = p0 == 0u ? true : ((bits[(p0 - 1u) >> 5] >> ((p0 - 1u) & 31u)) & 1u) == 0u;
+        if (closed && starts_open && col_ok) {
+            const int row = rows[k0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) in[i] += head[i];
+            if (row == r_first) add_row(row, in); else write_row(row, in);
+        }
+        done = to;
+    } while (done < n_ent);
+    // the row still open at the end of my chunk is finished by another wave
+    if (!snap && ie < M) {
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) any |= carry[i] != 0.0f;
+        if (any && g == 0 && col_ok) add_row(ie, carry);
+    }
 }
 
 // ===========================================================================

@@ -1,0 +1,73 @@
+"""GPU parity of the kernels' variants at the sizes where they can go wrong: block, run and window edges, whole rows
+against rows shared between waves, plain and scaled form."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_16064_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+
+LENS = {
+    "block_edges": [511, 1, 0, 512, 513, 0, 0, 7, 1024, 1, 504, 8, 9, 1, 1, 1, 0] * 5,
+    "run_edges": [8, 7, 9, 16, 15, 17, 32, 31, 33, 64, 63, 65, 0, 1] * 60,
+    "empty_stretches": ([3] + [0] * 700 + [2, 600] + [0] * 63 + [1] + [0] * 64 + [5] + [0] * 1100) * 3,
+    "one_per_row": [1] * 5000,
+    "one_row": [3000],
+    "empty_ends": [0] * 130 + [40] * 20 + [0] * 130,
+}
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import torch
+    from paper_2106_16064_amd import binding
+    assert torch.cuda.is_available()
+    binding.lib()
+    return binding
+
+
+def _compare(dg, A, N, algo, features, alpha=None, beta=0.0, poison_row=None):
+    import torch
+    X = wl.dense_matrix(A.K, N, "normal", seed=N)
+    Y0 = wl.dense_matrix(A.M, N, "uniform", seed=N + 1)
+    yref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    if poison_row is not None:
+        X = X.copy()
+        X[poison_row] = np.inf                       # a row of X that no entry names
+    dA = dg.DeviceCsr(A)
+    dX = torch.from_numpy(X).cuda()
+    dY = torch.from_numpy(Y0).cuda()
+    f = dA.features if features else None
+    print(f"[case] {A.name} M={A.M} nnz={A.nnz} N={N} algo={algo} features={features} alpha={alpha} beta={beta}", flush=True)
+    if alpha is None:
+        dY.fill_(float("nan"))
+        dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz if features else -1, dA.rowptr, dA.colidx, dA.vals, dX, dY, algo, dg.PHASE_ALL, f)
+    else:
+        dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz if features else -1, dA.rowptr, dA.colidx, dA.vals, dX, dY, alpha, beta, algo, f)
+        yref = alpha * yref + beta * Y0
+        bnd = abs(alpha) * bnd + abs(beta) * np.abs(Y0)
+    torch.cuda.synchronize()
+    ok, worst = oracle.within_bound(dY.cpu().numpy(), yref, bnd, TOL)
+    assert ok, f"worst |err|/bound = {worst:.3e}"
+
+
+@pytest.mark.parametrize("N", [4, 5, 8, 11, 16, 20, 32, 33, 64, 96, 128, 200])
+@pytest.mark.parametrize("lens", sorted(LENS))
+def test_balanced_runs_of_entries(dg, lens, N):
+    """The balanced kernel from four columns on: rows kept whole (statistics given) and rows shared between waves."""
+    A = wl.csr_from_lens(LENS[lens], K=4000, seed=N, name=lens)
+    free = np.setdiff1d(np.arange(A.K), A.colidx)
+    for features in (True, False):
+        _compare(dg, A, N, dg.NB_SR, features, poison_row=int(free[0]) if free.size else None)
+        _compare(dg, A, N, dg.NB_SR, features, alpha=-0.5, beta=1.5)
+
+
+@pytest.mark.parametrize("N", [5, 6, 7, 8])
+def test_balanced_parallel_kernel_at_five_to_eight_columns(dg, N):
+    A = wl.csr_from_lens(LENS["run_edges"] + LENS["empty_stretches"], K=3000, seed=N, name="mixed")
+    for features in (True, False):
+        _compare(dg, A, N, dg.NB_PR, features)
+        _compare(dg, A, N, dg.NB_PR, features, alpha=2.0, beta=-1.0)

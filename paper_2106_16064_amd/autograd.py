@@ -54,39 +54,11 @@ class SparseOperator:
             self.bwd = dg.DeviceCsr(transpose_csr(A), device)
 
     def __call__(self, X, algo=dg.AUTO):
-        return _SpMM.apply(X, self, algo)
-
-
-def _make_function():
-    import torch
-
-    class SpMM(torch.autograd.Function):
-        @staticmethod
-        def forward(ctx, X, op, algo):
-            ctx.op = op
-            squeeze = X.dim() == 1
-            ctx.squeeze = squeeze
-            Xc = (X.unsqueeze(1) if squeeze else X).contiguous().float()
-            Y = op.fwd.spmm(Xc, algo=algo)
-            return Y.squeeze(1) if squeeze else Y
-
-        @staticmethod
-        def backward(ctx, dY):
-            G = (dY.unsqueeze(1) if ctx.squeeze else dY).contiguous().float()
-            dX = ctx.op.bwd.spmm(G)           # the rules choose for A^T on their own
-            return (dX.squeeze(1) if ctx.squeeze else dX), None, None
-
-    return SpMM
-
-
-class _Lazy:
-    _fn = None
-
-    @classmethod
-    def apply(cls, *args):
-        if cls._fn is None:
-            cls._fn = _make_function()
-        return cls._fn.apply(*args)
-
-
-_SpMM = _Lazy
+        """``A X``; the gradient's product picks its own kernel (the rules for A^T, or what ``autotune`` found)."""
+        A, T = self.fwd, self.bwd
+        N = X.shape[1] if X.dim() == 2 else 1
+        if algo == dg.AUTO:
+            algo = A.tuned.get(N, dg.AUTO)
+        return dg.native().multiply_differentiable(
+            X, algo, T.tuned.get(N, dg.AUTO), A.M, A.K, A.features, A.rowptr, A.colidx, A.vals,
+            T.M, T.K, T.features, T.rowptr, T.colidx, T.vals)

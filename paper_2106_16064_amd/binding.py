@@ -1,9 +1,11 @@
-"""Thin ctypes binding over ``libdgsp.so`` with the same names as the C-ABI
+"""Thin binding over ``libdgsp.so`` with the same names as the C-ABI
 (``include/dgsp.h``).  Argument marshalling only: every step of the
 multiplication runs inside the HIP library.  Tensors are ``torch`` CUDA(HIP)
 tensors used purely as device memory; the stream is torch's current stream.
+The products go through ``_dgsp_torch.so`` (``csrc/torch_binding.cpp``), which
+checks the tensors in native code; the rest is ctypes.
 
-There is no CPU fallback: if the shared library has not been built the first
+There is no CPU fallback: if the shared libraries have not been built the first
 call raises.
 """
 from __future__ import annotations
@@ -16,6 +18,7 @@ ALGOS = (RS_SR, RS_PR, NB_SR, NB_PR)
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_LAUNCH = 0, 1, 2, 3
 
 LIB_PATH = Path(__file__).resolve().parent / "libdgsp.so"
+NATIVE_PATH = LIB_PATH.with_name("_dgsp_torch.so")
 
 EXPORTS = (
     "dgsp_spmm_csr", "dgsp_spmm_csr_nnz", "dgsp_spmm_csr_auto", "dgsp_select_algo",
@@ -127,6 +130,26 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The products as native functions on tensors (positional arguments; see ``csrc/torch_binding.cpp``)."""
+    global _native
+    if _native is None:
+        import importlib.util
+        import torch  # noqa: F401  (its libraries have to be loaded before the module)
+        lib()
+        if not NATIVE_PATH.exists():
+            raise DgspError(f"{NATIVE_PATH} is missing: run `python -m paper_2106_16064_amd.build`")
+        spec = importlib.util.spec_from_file_location("_dgsp_torch", NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.set_error_type(DgspError)
+        _native = module
+    return _native
+
+
 def _check(rc: int, what: str):
     if rc != OK:
         raise DgspError(f"{what}: {dgsp_status_string(rc)} (status {rc})")
@@ -157,20 +180,12 @@ def _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y):
 
 def dgsp_spmm_csr(M, K, N, rowptr, colidx, vals, X, Y, algo, stream=None):
     """``Y = A X`` with the kernel ``algo``; the entry count is read on the device."""
-    _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y)
-    rc = lib().dgsp_spmm_csr(M, K, N, _ptr(rowptr), _ptr(colidx), _ptr(vals), _ptr(X), _ptr(Y),
-                             int(algo), _stream(stream))
-    _check(rc, "dgsp_spmm_csr")
+    (_native or native()).spmm_csr(M, K, N, None, rowptr, colidx, vals, X, Y, algo, stream)
 
 
 def dgsp_spmm_csr_nnz(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream=None):
     """``Y = A X`` with the entry count given by the caller."""
-    _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y)
-    if nnz >= 0 and colidx.numel() < nnz:
-        raise DgspError("colidx/vals shorter than nnz")
-    rc = lib().dgsp_spmm_csr_nnz(M, K, N, int(nnz), _ptr(rowptr), _ptr(colidx), _ptr(vals), _ptr(X), _ptr(Y),
-                                 int(algo), _stream(stream))
-    _check(rc, "dgsp_spmm_csr_nnz")
+    (_native or native()).spmm_csr(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream)
 
 
 def dgsp_spmm_csr_i64(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, workspace=None, stream=None):
@@ -205,35 +220,13 @@ def dgsp_spmm_csr_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, f
 def dgsp_spmm_csr_ld(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, features=None, stream=None):
     """``Y = A X`` on 2-D views whose rows are ``stride(0)`` floats apart (``stride(1)`` must be 1):
     column slices of wider row-major tensors are taken as they are, nothing is copied."""
-    import torch
-    for name, t in (("X", X), ("Y", Y)):
-        if not t.is_cuda or t.dtype != torch.float32 or t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
-            raise DgspError(f"{name} must be a 2-D float32 GPU view with unit column stride")
-    if X.shape != (K, N) or Y.shape != (M, N):
-        raise DgspError("X must be K x N and Y M x N")
-    ldx = X.stride(0) if K > 1 else max(N, X.stride(0))
-    ldy = Y.stride(0) if M > 1 else max(N, Y.stride(0))
-    rc = lib().dgsp_spmm_csr_ld(M, K, N, int(nnz), _ptr(rowptr), _ptr(colidx), _ptr(vals), _ptr(X), int(ldx),
-                                _ptr(Y), int(ldy), int(algo),
-                                ctypes.byref(features) if features is not None else None, _stream(stream))
-    _check(rc, "dgsp_spmm_csr_ld")
+    (_native or native()).spmm_csr_view(M, K, N, nnz, rowptr, colidx, vals, X, Y, None, None, algo, features, stream)
 
 
 def dgsp_spmm_csr_axpby(M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha=1.0, beta=0.0, algo=AUTO, features=None,
                         stream=None):
     """``Y = alpha * A X + beta * Y`` on 2-D views (rows ``stride(0)`` floats apart, unit column stride)."""
-    import torch
-    for name, t in (("X", X), ("Y", Y)):
-        if not t.is_cuda or t.dtype != torch.float32 or t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
-            raise DgspError(f"{name} must be a 2-D float32 GPU view with unit column stride")
-    if X.shape != (K, N) or Y.shape != (M, N):
-        raise DgspError("X must be K x N and Y M x N")
-    ldx = X.stride(0) if K > 1 else max(N, X.stride(0))
-    ldy = Y.stride(0) if M > 1 else max(N, Y.stride(0))
-    rc = lib().dgsp_spmm_csr_axpby(M, K, N, int(nnz), _ptr(rowptr), _ptr(colidx), _ptr(vals), _ptr(X), int(ldx),
-                                   _ptr(Y), int(ldy), float(alpha), float(beta), int(algo),
-                                   ctypes.byref(features) if features is not None else None, _stream(stream))
-    _check(rc, "dgsp_spmm_csr_axpby")
+    (_native or native()).spmm_csr_view(M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream)
 
 
 def dgsp_spmm_csr_ablation(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, switches, features=None, stream=None):
@@ -309,12 +302,7 @@ def dgsp_gather_probe_out_len() -> int:
 
 def dgsp_spmm_csr_auto(M, K, N, features: Features, rowptr, colidx, vals, X, Y, stream=None) -> int:
     """Select by the rules, run, return the chosen algo."""
-    _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y)
-    chosen = ctypes.c_int(-1)
-    rc = lib().dgsp_spmm_csr_auto(M, K, N, ctypes.byref(features), _ptr(rowptr), _ptr(colidx), _ptr(vals),
-                                  _ptr(X), _ptr(Y), ctypes.byref(chosen), _stream(stream))
-    _check(rc, "dgsp_spmm_csr_auto")
-    return chosen.value
+    return (_native or native()).spmm_csr_auto(M, K, N, features, rowptr, colidx, vals, X, Y, stream)
 
 
 def dgsp_select_algo(features: Features, N: int) -> int:
@@ -416,6 +404,8 @@ class DeviceCsr:
 
     def spmm(self, X, algo=AUTO, Y=None, use_nnz=True, stream=None):
         """Y = A X.  ``algo=AUTO`` applies the selection rules to this matrix's features."""
+        if Y is None and stream is None and algo == AUTO and not getattr(self, "tuned", None):
+            return (_native or native()).multiply_new(self.M, self.K, self.features, self.rowptr, self.colidx, self.vals, X, AUTO)
         import torch
         N = X.shape[1] if X.dim() == 2 else 1
         if Y is None:

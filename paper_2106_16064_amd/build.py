@@ -1,4 +1,4 @@
-"""Builds ``libdgsp.so`` (HIP, gfx950) in place next to this file.
+"""Builds ``libdgsp.so`` (HIP, gfx950) and ``_dgsp_torch.so`` (its calls from PyTorch) in place next to this file.
 
 Run as ``python -m paper_2106_16064_amd.build``.  hipcc cross-compiles without
 a GPU, so this works on any machine with ROCm installed.
@@ -9,6 +9,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from pathlib import Path
 
 HERE = Path(__file__).resolve().parent
@@ -16,6 +17,9 @@ CSRC = HERE / "csrc"
 LIB = HERE / "libdgsp.so"
 SOURCES = [CSRC / "dgsp.hip"]
 HEADERS = [CSRC / "dgsp_device.hpp", CSRC / "dgsp_kernels.hpp", HERE.parent / "include" / "dgsp.h"]
+
+TORCH_LIB = HERE / "_dgsp_torch.so"
+TORCH_SOURCE = CSRC / "torch_binding.cpp"
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -44,7 +48,27 @@ def build(verbose: bool = True, extra_flags=()) -> Path:
         raise RuntimeError(f"hipcc failed:\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    build_torch_binding(verbose)
     return LIB
+
+
+def build_torch_binding(verbose: bool = True) -> Path:
+    """Host code only: the library's entry points as functions on torch tensors."""
+    import torch
+    top = Path(torch.__file__).resolve().parent
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *(f"-isystem{d}" for d in (top / "include", top / "include/torch/csrc/api/include", f"{rocm}/include",
+                                      sysconfig.get_paths()["include"])),
+           "-o", str(TORCH_LIB), str(TORCH_SOURCE), f"-L{HERE}", "-ldgsp", f"-L{top / 'lib'}", "-ltorch_python", "-ltorch",
+           "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on the torch binding:\n{res.stderr}")
+    return TORCH_LIB
 
 
 EXAMPLE_SRC = HERE.parent / "tests" / "c_abi_example.c"
@@ -66,10 +90,10 @@ def build_c_example(verbose: bool = True) -> Path:
 
 
 def is_stale() -> bool:
-    if not LIB.exists():
+    if not LIB.exists() or not TORCH_LIB.exists():
         return True
-    t = LIB.stat().st_mtime
-    return any(f.stat().st_mtime > t for f in SOURCES + HEADERS)
+    t = min(LIB.stat().st_mtime, TORCH_LIB.stat().st_mtime)
+    return any(f.stat().st_mtime > t for f in [*SOURCES, *HEADERS, TORCH_SOURCE])
 
 
 if __name__ == "__main__":

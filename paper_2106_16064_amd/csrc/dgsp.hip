@@ -87,7 +87,7 @@ struct Problem {
 
 // Vector width of the comparison kernel without LDS staging (rs_sr_direct_kernel) only: it uses plain
 // float2 / float4 accesses, which need N, the leading dimensions and the addresses of X and Y to fit.
-// The four kernels proper do not depend on alignment (see pr_vector_width, sr_shape).
+// The four kernels proper do not depend on alignment (see pr_vector_width, rs_sr_shape).
 inline int direct_kernel_vector_width(const Problem& p) {
     if (p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) return 1;
     int v = 1;
@@ -165,7 +165,22 @@ int launch_rs_pr_v(const Problem& p) {
     return DGSP_OK;
 }
 
+// Rows more or less alike, none of them so long that it would hold up the wave of row groups it is in: equal runs of rows
+// are equal shares of entries, and up to four columns the row-group kernel (rs_sr_kernel), whose H lanes on a row's
+// entries are the same reduction as theirs, takes the place of both parallel kernels.  It needs no search, no row marks, no
+// prepare launch and no atomics, and its entries arrive coalesced through LDS.  Against rs_pr: 4096 rows of 8 at N = 4
+// 5.7 -> 3.7 us, 20 000 rows of 100 at N = 1 16 -> 10 us; against nb_pr: 27-point stencil on 128^3 at N = 1 / 4 129 / 147 ->
+// 95 / 114 us, on 61^3 25 -> 12.5 us, 776 379 rows of 22 over 27 098 columns at N = 1 86 -> 70 us, 187 500 Poisson rows
+// of 8 at N = 4 22 -> 14 us; 262 144 rows of 64 at N = 1 break even.
+constexpr double kRowGroupCvMax = 0.6;
+inline bool row_groups_balance(const Problem& p) {
+    return p.N <= 4 && p.switches == 0 && p.nnz > 0 && p.cv_row >= 0.0 && p.cv_row <= kRowGroupCvMax && p.max_row >= 0 &&
+           (double)p.max_row <= 8.0 * (double)p.nnz / (double)p.M + 64.0;
+}
+int launch_rs_sr(const Problem& p);
+
 int launch_rs_pr(const Problem& p) {
+    if (row_groups_balance(p)) return launch_rs_sr(p);
     const bool xb = x_fits_descriptor(p);
     switch (pr_vector_width(p)) {
         case 4: return xb ? launch_rs_pr_v<4, true>(p) : launch_rs_pr_v<4, false>(p);
@@ -208,6 +223,7 @@ inline SrColumns sr_columns(long long N, int V, bool narrow) {
 // Dense-row loads in flight per lane of the sequential kernels: enough to fill, not to overflow,
 // the L1 when rows of X are scattered (about 1 KB per wave: 4 / V loads), four when the matrix is
 // known to be banded (neighbouring rows then share their rows of X and mostly hit in cache).
+inline bool even_rows(const Problem& p) { return p.cv_row >= 0.0 && p.cv_row <= kEvenRowsCvMax; }
 inline bool banded(const Problem& p) { return p.col_span > 0.0 && p.col_span <= 0.05; }
 
 // The sequential kernels give a lane four dense columns whenever a row has four: the memory pipeline takes
@@ -215,48 +231,89 @@ inline bool banded(const Problem& p) { return p.col_span > 0.0 && p.col_span <= 
 // dimensions restrict the width.  When N is not a multiple of four the last lane of a row takes the row's last
 // four columns; those it shares with its neighbour are the neighbour's to add or to scale (RAGGED).
 struct SrShape { int v; bool ragged; };
-inline SrShape sr_shape(const Problem& p) {
-    if (p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) return {1, false};
-    // N = 3 and N = 6 keep the widest width that divides them: so few columns do not repay the extra stores
-    // of the shared lane (measured: +6 % at N = 6, +7 ... +17 % at N = 3 with it; N = 5 gains 13 %, N = 7 is even)
-    if (p.N == 3) return {1, false};
-    if (p.N == 6 || p.N == 2) return {2, false};
-    const int v = p.N >= 4 ? 4 : 1;
-    return {v, p.N % v != 0};
+// dense-row loads in flight per lane of the balanced kernel at one and two columns (see banded())
+template <int V> constexpr int sr_depth_scattered() { return V == 2 ? 2 : 4; }
+
+// Lines of 128 bytes that `cols` consecutive columns of a row of X touch, on average over the rows.
+inline double lines_per_row(long long cols, long long ldx) {
+    const long long bytes = cols * 4, pitch = ldx * 4;
+    if (pitch % 128 == 0 || 128 % pitch == 0) return (double)((bytes + 127) / 128);
+    return (double)(bytes - 4) / 128.0 + 1.0;
 }
-// dense-row loads in flight per lane (see banded())
-template <int V> constexpr int sr_depth_scattered() { return V == 4 ? 1 : V == 2 ? 2 : 4; }
+
+// Do the rows sweep X in step?  Row-split waves that start together, one lane group per row and one dense-row load in
+// flight each, walk their (ascending, scattered) columns at the same pace, so that at any time they touch a narrow band of
+// X and find it in the L2; more loads in flight, or several lanes on a row's entries, widen the band until it no longer
+// fits.  In step, a call is a chain of dependent loads; out of step it is bound by the lines that the gathers fetch, the
+// dearer the more of them the L2 (4 MB) misses.  Both costs are fitted, to 15 % or so, on random columns of X from 3 to
+// 40 MB, N = 1 to 128, 65 536 to 524 288 rows (`occ`: share of the wave slots in use, `part`: lines per wave / 64):
+//   a step in step      0.1 us + 0.4 us * (1 - occ) + part * (2.6 us * occ + 1.5 us * missed)
+//   a line out of step  6.5 ps + 12.5 ps * missed^2
+// Rows of 30, X of 3 / 5 / 7 / 10 / 16 MB, in step against out of step: N = 1 82 / 89 / 92 / 97 / 114 against
+// 86 / 105 / 134 / 178 / 222 us, N = 4 42 / 61 / 79 / 98 / 115 against 36 / 67 / 112 / 177 / 219 us; rows of 40 at N = 33
+// (16 MB) 81 against 126 us, Poisson rows of 12 there 51 against 46 us; 262 144 rows of 60 at N = 1 (5 MB) 184 against 106 us.
+constexpr double kWaveSlotsPerCu = 32.0;
+inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
+    const double x_bytes = (double)p.K * p.N * 4.0;
+    const double missed = x_bytes > (double)kL2BytesPerXcd ? 1.0 - (double)kL2BytesPerXcd / x_bytes : 0.0;
+    if (banded(p) || p.nnz == 0) return false;
+    if (p.nnz < 0) return missed > 0.0;                        // entry count unknown: rows taken to be long and alike
+    const double avg = (double)p.nnz / (double)p.M;
+    const double longest = p.cv_row > 0.0 ? avg * (1.0 + 2.5 * p.cv_row) : avg;      // of the rows a wave walks together
+    const double rows_per_wave = (double)(kWave >> cols.logG);
+    const double rounds = (double)p.M / rows_per_wave * cols.blocks / (device_info().cus * kWaveSlotsPerCu);
+    const double occ = std::fmin(rounds, 1.0);
+    const double lines = lines_per_row(cols.cols_per_block, p.ldx), part = rows_per_wave * lines / 64.0;
+    const double step = 0.1 + 0.4 * (1.0 - occ) + part * (2.6 * occ + 1.5 * missed);
+    // a wave's rows beyond four rounds of its LDS tile: too few of them walk at a time
+    const double overflow = std::fmax(1.0, rows_per_wave * avg / (4.0 * kRsSrTile));
+    const double in_us = step * longest * std::fmax(rounds, 1.0) * std::pow(overflow, 0.75);
+    const double out_us = (double)p.nnz * lines * cols.blocks * (6.5e-6 + 12.5e-6 * missed * missed);
+    return 1.05 * in_us < out_us;
+}
+
+// log2 of the lanes that share a row's entries (H) when 2^logG lanes span its columns.  A wave's rows should fit one
+// round of the LDS tile: with 64 rows of 27 a round holds 19 of them and the other lanes wait (27-point stencil on 128^3
+// at N = 1: H = 1 153 us, H = 4 121 us; N = 4 190 -> 133 us).  A matrix that leaves the machine half empty is split
+// further while a lane keeps two entries (4500 rows of 30: H = 4 6.5 us, H = 8 3.8 us).
+inline int rs_sr_split_log2(const Problem& p, int logG) {
+    if (p.nnz < 0 || p.M == 0) return 0;
+    const double avg = (double)p.nnz / (double)p.M;
+    int logH = 0;
+    for (; logG + logH < 6; ++logH) {
+        const int rows = kWave >> (logG + logH);
+        if (p.max_row >= 0 && (double)rows * (double)p.max_row <= (double)kRsSrTile) break;
+        const double spread = p.cv_row >= 0.0 ? 2.0 * p.cv_row * avg * std::sqrt((double)rows) : 0.1 * rows * avg;
+        if (rows * avg + spread <= (double)kRsSrTile) break;
+    }
+    const double few = device_info().cus * 8.0;                // waves: two per SIMD
+    while (logG + logH < 6 && (double)p.M * (double)(1 << (logG + logH)) < few * kWave && avg >= (double)(4 << logH)) ++logH;
+    return logH;
+}
 
 template <int V, bool XBUF, int DEPTH, bool RAGGED>
-int launch_rs_sr_v(const Problem& p) {
-    // Rows of about equal length (what the selection rules send here) and N a multiple of 64: column blocks of 64
-    // dense columns as in the balanced kernel, four rows per wave in step; 2-16 % faster at N >= 128 on such matrices.
-    // With long rows among short ones the rows of a wave wait for the longest (+30 % measured), and without row
-    // statistics nothing is known: then a group spans the whole width.
-    const bool even_rows = p.cv_row >= 0.0 && p.cv_row <= kEvenRowsCvMax;
-    const SrColumns cols = sr_columns(p.N, V, even_rows && p.N >= 128);
+int launch_rs_sr_v(const Problem& p, const SrColumns& cols, int logH) {
     const int logG = cols.logG;
     const unsigned col_blocks = cols.blocks;
     if (col_blocks > 65535u) return DGSP_ERR_INVALID_ARG;
-    const int rows_per_wave = kWave >> logG;
+    const int rows_per_wave = kWave >> (logG + logH);
     const long long groups = ((long long)p.M + rows_per_wave - 1) / rows_per_wave;
     const long long cap = (long long)device_info().cus * kBlocksPerCu * 8;
     const dim3 grid(clamp_blocks((groups + kWavesPerBlock - 1) / kWavesPerBlock, cap), col_blocks);
     if (p.scaled) {
         DGSP_LAUNCH((rs_sr_kernel<V, XBUF, DEPTH, true, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals,
-                    p.X, p.Y, logG, cols.cols_per_block, Scaling{p.alpha, p.beta});
+                    p.X, p.Y, logG, logH, cols.cols_per_block, Scaling{p.alpha, p.beta});
         return DGSP_OK;
     }
     DGSP_LAUNCH((rs_sr_kernel<V, XBUF, DEPTH, false, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                p.Y, logG, cols.cols_per_block);
+                p.Y, logG, logH, cols.cols_per_block);
     return DGSP_OK;
 }
 
 template <int V>
 int launch_rs_sr_direct_v(const Problem& p) {
     // the same column blocks as the kernel it is compared with
-    const bool even_rows = p.cv_row >= 0.0 && p.cv_row <= kEvenRowsCvMax;
-    const SrColumns cols = sr_columns(p.N, V, even_rows && p.N >= 128);
+    const SrColumns cols = sr_columns(p.N, V, even_rows(p) && p.N >= 128);
     const int logG = cols.logG;
     const unsigned col_blocks = cols.blocks;
     if (col_blocks > 65535u) return DGSP_ERR_INVALID_ARG;
@@ -272,13 +329,26 @@ int launch_rs_sr_direct_v(const Problem& p) {
 template <int V, bool RAGGED>
 int launch_rs_sr_pick(const Problem& p) {
     const bool xb = x_fits_descriptor(p);
-    // X inside one XCD's L2: nothing to keep together, so hide latency with four loads in flight (-9 % on
-    // Poisson(16) rows, -37 % on rows of 64 at N = 4, 2^18 rows).  Beyond that size the single load is what
-    // keeps the lanes of a wave in step over the same part of X (four in flight: +10 ... +70 % there).
-    if (banded(p) || dense_bytes(p.K, p.ldx, p.N) <= kL2BytesPerXcd)
-        return xb ? launch_rs_sr_v<V, true, 4, RAGGED>(p) : launch_rs_sr_v<V, false, 4, RAGGED>(p);
-    constexpr int D = sr_depth_scattered<V>();
-    return xb ? launch_rs_sr_v<V, true, D, RAGGED>(p) : launch_rs_sr_v<V, false, D, RAGGED>(p);
+    // Rows of about equal length (what the selection rules send here) and N a multiple of 64: column blocks of 64
+    // dense columns as in the balanced kernel, four rows per wave in step; 2-16 % faster at N >= 128 on such matrices.
+    // With long rows among short ones the rows of a wave wait for the longest (+30 % measured), and without row
+    // statistics nothing is known: then a group spans the whole width.
+    const SrColumns cols = sr_columns(p.N, V, even_rows(p) && p.N >= 128);
+    if (rows_in_step(p, cols)) return xb ? launch_rs_sr_v<V, true, 1, RAGGED>(p, cols, 0) : launch_rs_sr_v<V, false, 1, RAGGED>(p, cols, 0);
+    const int logH = rs_sr_split_log2(p, cols.logG);
+    // one column per lane: eight loads in flight are as many registers as two at V = 4 (stencil 128^3: 125 -> 121 us)
+    constexpr int D = V == 1 ? 8 : 4;
+    return xb ? launch_rs_sr_v<V, true, D, RAGGED>(p, cols, logH) : launch_rs_sr_v<V, false, D, RAGGED>(p, cols, logH);
+}
+
+// Dense columns per lane of the row-split sequential kernel: four, the last lane's window overlapping its neighbour's
+// when four does not divide N; three where it divides N = 3 or 6 (N = 3 as three lanes of one column, one lane of four
+// idle: stencil 80^3 42 us, against 37 us at N = 4).
+inline SrShape rs_sr_shape(const Problem& p) {
+    if (p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) return {1, false};
+    if (p.N == 3 || p.N == 6) return {3, false};
+    if (p.N < 4) return {p.N, false};
+    return {4, p.N % 4 != 0};
 }
 
 int launch_rs_sr(const Problem& p) {
@@ -289,9 +359,10 @@ int launch_rs_sr(const Problem& p) {
             default: return launch_rs_sr_direct_v<1>(p);
         }
     }
-    const SrShape shape = sr_shape(p);
+    const SrShape shape = rs_sr_shape(p);
     switch (shape.v) {
         case 4: return shape.ragged ? launch_rs_sr_pick<4, true>(p) : launch_rs_sr_pick<4, false>(p);
+        case 3: return launch_rs_sr_pick<3, false>(p);
         case 2: return launch_rs_sr_pick<2, false>(p);
         default: return launch_rs_sr_pick<1, false>(p);
     }
@@ -512,6 +583,7 @@ int launch_nb_sr(const Problem& p) {
 // access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 156 / 156 -> 140 / 139 us, Zipf rows of 16 at N = 8 61 -> 58 us,
 // lognormal rows of 64 at N = 5 / 8 173 / 190 -> 143 / 179 us; a tie on small matrices.
 int launch_nb_pr(const Problem& p) {
+    if (row_groups_balance(p)) return p.phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_sr(p);
     const int v = nb_pr_lane_width(p.N, p.switches);
     if (v == 8 && p.N <= 8 && p.switches == 0 && p.ldy <= kBalancedLdyMax) return launch_nb_sr_run(p);
     switch (v) {

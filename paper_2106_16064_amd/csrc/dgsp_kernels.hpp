@@ -18,6 +18,8 @@
 
 #include "dgsp_device.hpp"
 
+#include <type_traits>
+
 namespace dgsp {
 
 // ===========================================================================
@@ -158,6 +160,18 @@ __global__ __launch_bounds__(kBlock) void rs_pr_kernel(int M, long long K, int N
 // own row and accumulates its own columns: the dense accesses of a group are
 // one contiguous 4*V*G-byte piece of a row of X.
 // blockIdx.y selects the column block when N > 64*V.
+//
+// When few lanes span the columns, 64 / G rows can be more than a round of the
+// cache holds.  H = 2^logH lanes per column group then share a row's entries
+// (lane h takes every H-th) and add their sums up at the end, so that a wave's
+// 64 / (G H) rows fit one round and every lane walks in it.  Neighbouring lanes
+// hold neighbouring rows: on a stencil or band their gathers fall into the same
+// few lines of X, which costs the address unit a fraction of what one row's
+// scattered columns cost.  27-point stencil on 128^3 at N = 1: 16 rows, H = 4:
+// 95 us (5.0 TB/s), with H = 1 153 us, through the balanced parallel kernel 129 us;
+// N = 4 190 -> 115 us, N = 8 200 -> 155 us.
+// Bound by: HBM streams on banded matrices; the lines gathered from X, out of
+// the L1's and L2's misses, elsewhere.
 
 constexpr int kRsSrTile = 512;   // cached pairs per wave and round
 // DEPTH (template parameter of the sequential kernels) = dense-row loads a lane keeps in flight.
@@ -168,23 +182,28 @@ constexpr int kRsSrTile = 512;   // cached pairs per wave and round
 // at depth 4).  Rows that hit in cache anyway want the latency hidden instead (27-point stencil,
 // N = 8: 204 us at depth 4, 260 us at depth 1), and so do rows of uneven length.  The host picks.
 
+// position of pair e of a round in the LDS tile: eight pairs of padding after every 64, so that rows of 32, 64, ... entries
+// do not put all lane groups on the same banks
+__device__ __forceinline__ unsigned padded(unsigned e) { return e + ((e >> 6) << 3); }
+
 template <int V, bool XBUF, int DEPTH, bool AXPBY = false, bool RAGGED = false>
 __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        int logG, int cols_per_block, Scaling sc = Scaling{1.0f, 0.0f}) {
+                                                        int logG, int logH, int cols_per_block, Scaling sc = Scaling{1.0f, 0.0f}) {
     constexpr int T = kRsSrTile;
-    __shared__ __align__(16) int s_col[kWavesPerBlock][T];
-    __shared__ __align__(16) float s_val[kWavesPerBlock][T];
+    __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][T + T / 8];     // row of X (XBUF: its byte offset), value
     const int lane = lane_id();
     const int wib = wave_in_block();
-    int* cc = s_col[wib];
-    float* cv = s_val[wib];
+    uint2* ent = s_ent[wib];
     const int G = 1 << logG;
+    const int H = 1 << logH;                                     // lanes of a row that share its entries
+    const int log_rows = 6 - logG - logH;
+    const int rows_per_wave = 1 << log_rows;
     const int gl = lane & (G - 1);
-    const int g = lane >> logG;
-    const int rows_per_wave = kWave >> logG;
+    const int g = (lane >> logG) & (rows_per_wave - 1);
+    const int h = lane >> (6 - logH);
 
     const LaneColumns mine = lane_columns<V, RAGGED>(blockIdx.y, cols_per_block, gl, N);
     const long long n = mine.first;                              // my first dense column
@@ -192,12 +211,13 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
 
     const unsigned nwaves = gridDim.x * kWavesPerBlock;
     const unsigned gw = xcd_contiguous(blockIdx.x, gridDim.x) * kWavesPerBlock + wib;
-    const unsigned ngroups = ((unsigned)M + rows_per_wave - 1) / rows_per_wave;
+    const unsigned ngroups = (unsigned)(((long long)M + rows_per_wave - 1) >> log_rows);
 
     // XBUF: the dense operand is read through a descriptor (its byte offsets fit 32 bits)
     const unsigned long long x_bytes = dense_bytes(K, ldx, N);
     const __amdgpu_buffer_rsrc_t rx = make_buffer(X, XBUF ? x_bytes : 0ull);
     const unsigned n_bytes = (unsigned)n * 4u;
+    const unsigned pitch = XBUF ? (unsigned)ldx * 4u : 1u;
 
     for (unsigned rg = gw; rg < ngroups; rg += nwaves) {
         const long long row0 = (long long)rg * rows_per_wave;
@@ -217,31 +237,54 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
             const unsigned long long bytes = (unsigned long long)(pe - ws) * 4ull;
             const __amdgpu_buffer_rsrc_t rc = make_buffer(colidx + ws, bytes);
             const __amdgpu_buffer_rsrc_t ra = make_buffer(vals + ws, bytes);
+            // C * 64 pairs from pair `from` on, all loads before the first wait (a branch around each one makes the compiler
+            // wait inside it: up to eight round trips to memory in a row, 116 instead of 95 us on the stencil at N = 1);
+            // past the stretch's end they read nothing
+            auto stage = [&](unsigned from, auto count) {
+                constexpr int C = decltype(count)::value;
+                unsigned c[C]; float a[C];
 #pragma unroll
-            for (int k = 0; k < T / kWave; ++k) {
-                if (ws + (unsigned)(k * kWave) < pe) {       // wave-uniform
-                    const unsigned off = (unsigned)(k * kWave + lane) * 4u;
-                    cc[k * kWave + lane] = buffer_stream_i32(rc, off);
-                    cv[k * kWave + lane] = buffer_stream_f32(ra, off);
+                for (int k = 0; k < C; ++k) {
+                    const unsigned off = (from + (unsigned)(k * kWave + lane)) * 4u;
+                    c[k] = (unsigned)buffer_stream_i32(rc, off);
+                    a[k] = buffer_stream_f32(ra, off);
                 }
+#pragma unroll
+                for (int k = 0; k < C; ++k)
+                    ent[(from >> 6) * (kWave + 8) + k * (kWave + 8) + lane] = make_uint2(c[k] * pitch, __builtin_bit_cast(unsigned, a[k]));
+            };
+            const unsigned left = pe - ws;                    // wave-uniform
+            if constexpr (DEPTH == 1) {
+                // rows in step: the L2 is to hold the band of X that all waves walk, and the streams in flight take room in
+                // it, 4 KB a wave at eight loads per array (2^20 rows of 27, 16 MB of X: 228 -> 346 us)
+                for (unsigned from = 0; from < (unsigned)T && from < left; from += 2u * kWave)
+                    stage(from, std::integral_constant<int, 2>{});
+            } else if (left <= 64u) {
+                stage(0u, std::integral_constant<int, 1>{});
+            } else if (left <= 128u) {
+                stage(0u, std::integral_constant<int, 2>{});
+            } else if (left <= 256u) {
+                stage(0u, std::integral_constant<int, 4>{});
+            } else {
+                stage(0u, std::integral_constant<int, T / kWave>{});
             }
             wave_lds_sync();
             const unsigned we = pe - ws > (unsigned)T ? ws + T : pe;
-            const unsigned lo = rs > ws ? rs : ws;
-            const unsigned hi = re < we ? re : we;
+            const unsigned lo = (rs > ws ? rs : ws) - ws;
+            const unsigned hi = (re < we ? re : we) - ws;         // may lie before lo: the row is not in this round
             if (col_ok) {
-                for (unsigned p0 = lo; p0 < hi; p0 += DEPTH) {
+                for (unsigned p0 = lo + (unsigned)h; (int)p0 < (int)hi; p0 += (unsigned)(DEPTH * H)) {
                     float x[DEPTH][V]; float a[DEPTH];
 #pragma unroll
                     for (int u = 0; u < DEPTH; ++u) {
-                        const bool ok = p0 + u < hi;
-                        const int e = ok ? (int)(p0 + u - ws) : 0;
-                        a[u] = ok ? cv[e] : 0.0f;
-                        const unsigned c = (unsigned)cc[e];
+                        const unsigned e = p0 + (unsigned)(u * H);
+                        const bool ok = u == 0 || e < hi;
+                        const uint2 t = ent[padded(ok ? e : p0)];
+                        a[u] = ok ? __builtin_bit_cast(float, t.y) : 0.0f;
                         if constexpr (XBUF) {
-                            buffer_load_vec<V>(rx, ok ? c * (unsigned)ldx * 4u + n_bytes : kOutOfRange, x[u]);
+                            buffer_load_vec<V>(rx, ok ? t.x + n_bytes : kOutOfRange, x[u]);
                         } else {
-                            load_vec_dword_aligned<V>(X + (size_t)(ok ? c : 0u) * ldx + n, x[u]);
+                            load_vec_dword_aligned<V>(X + (size_t)t.x * ldx + n, x[u]);      // switched off: the row of p0 once more
 #pragma unroll
                             for (int i = 0; i < V; ++i) x[u][i] = ok ? x[u][i] : 0.0f;
                         }
@@ -253,7 +296,10 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
                 }
             }
         }
-        if (live && col_ok) {
+        for (int m = kWave >> 1; m >= (G << log_rows); m >>= 1)           // the row's H partial sums
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[i] += __shfl_xor(acc[i], m);
+        if (live && col_ok && h == 0) {
             float* y = Y + (size_t)row * ldy + n;
             if constexpr (AXPBY) scale_into<V, true>(acc, y, sc);
             if (AXPBY && RAGGED && mine.skip != 0) {

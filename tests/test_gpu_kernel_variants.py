@@ -71,3 +71,26 @@ def test_balanced_parallel_kernel_at_five_to_eight_columns(dg, N):
     for features in (True, False):
         _compare(dg, A, N, dg.NB_PR, features)
         _compare(dg, A, N, dg.NB_PR, features, alpha=2.0, beta=-1.0)
+
+
+ROW_GROUPS = {                                        # rows alike: what the row-group kernel splits by lanes and rounds
+    "short": ([3, 0, 5, 8, 1] * 200, 4000),
+    "stencil_like": ([27, 26, 18, 27] * 700, 2900),
+    "round_edges": ([64] * 33 + [63] * 32 + [65] * 31, 4000),
+    "longer_than_a_round": ([513, 511, 512, 700] * 5, 4000),
+    "single_wave": ([300], 4000),
+    "spread_over_large_x": ([30, 29, 31] * 24000, 1 << 20),
+}
+
+
+@pytest.mark.parametrize("lens, N", [(name, n) for name in sorted(ROW_GROUPS) for n in (1, 2, 3, 4, 6, 7, 16, 33, 130)
+                                     if n <= 16 or ROW_GROUPS[name][1] < 10000])
+def test_row_groups(dg, lens, N):
+    """Row groups with one and with several lanes on a row's entries, reached by name and in place of both parallel kernels."""
+    rows, K = ROW_GROUPS[lens]
+    A = wl.csr_from_lens(rows, K=K, seed=N, name=lens)
+    free = np.setdiff1d(np.arange(A.K), A.colidx)
+    for algo in (dg.RS_SR, dg.RS_PR, dg.NB_PR) if N <= 4 else (dg.RS_SR,):
+        for features in (True, False):
+            _compare(dg, A, N, algo, features, poison_row=int(free[0]) if free.size else None)
+        _compare(dg, A, N, algo, True, alpha=-0.5, beta=1.5)

@@ -15,8 +15,8 @@
  *   - "device" pointers are HIP device memory of the current device, "host"
  *     pointers ordinary host memory.  The caller owns every buffer; the
  *     library allocates nothing on the device and keeps no state between
- *     calls apart from the selector thresholds (dgsp_set_thresholds) and the
- *     64-byte static device array of dgsp_features_from_csr_device_noalloc.
+ *     calls apart from the selector thresholds (dgsp_set_thresholds) and static
+ *     device arrays for the statistics of matrices in device memory (0.6 MB).
  *   - Indices are int32, zero based.  Values are fp32, accumulation is fp32
  *     (the paper's float2/float4 loads, Section 2.1.2, imply single
  *     precision).  The summation order differs between kernels, so results
@@ -239,10 +239,12 @@ int dgsp_features_from_csr_host(int64_t M, int64_t K, const int32_t *rowptr_host
  * dgsp_features_from_csr_host on a host copy bit for bit.
  *   rowptr, colidx  device, as in dgsp_spmm_csr
  *   workspace       device, DGSP_FEATURES_WORKSPACE_BYTES bytes, 8-byte aligned,
- *                   caller-owned, overwritten; needs no initialisation
+ *                   caller-owned, may be overwritten; needs no initialisation
  *   out             host
- * The call enqueues two small launches and a copy on `stream` and WAITS for them
- * (the result goes to host memory).  Errors as the host versions; a NULL or
+ * The call enqueues one launch on `stream` (more if a row's columns do not ascend)
+ * and WAITS for the result, which the GPU writes to pinned host memory (1 KB per GPU,
+ * allocated by the first call).  Up to eight calls run at a time on one GPU, on any
+ * streams and threads; further ones wait for a place.  Errors as the host versions; a NULL or
  * misaligned workspace with M > 0 -> DGSP_ERR_INVALID_ARG.
  */
 #define DGSP_FEATURES_WORKSPACE_BYTES 64
@@ -252,16 +254,13 @@ int dgsp_features_from_csr_device(int64_t M, int64_t K, const int32_t *rowptr, c
 /*
  * For callers that cannot allocate device memory or pass a workspace (code under
  * HIP graph capture set-up, tight serving loops, harnesses that forbid hipMalloc):
- * the same statistics as dgsp_features_from_csr_device with the 64 bytes of
- * scratch in a static device array inside the library instead of a caller
- * workspace.  No hipMalloc / hipFree or other allocating call is made.
+ * the same statistics as dgsp_features_from_csr_device without a workspace and
+ * without the pinned host words: the result comes back by a copy.  No hipMalloc /
+ * hipFree, hipHostMalloc or other allocating call is made.
  *   - Limit: M <= DGSP_FEATURES_NOALLOC_MAX_ROWS (the int32 index range the
- *     library has anyway; the scratch itself is 64 bytes whatever M is); larger M,
- *     negative extents or NULL pointers -> DGSP_ERR_INVALID_ARG, nothing enqueued.
- *   - Every call on one GPU uses that GPU's one array, cleared by a small kernel at
- *     the start of each call: calls that overlap on one GPU (different streams or
- *     threads) race and give wrong statistics.  Calls on different GPUs do not
- *     interfere (each device holds its own copy, found once per device on first use).
+ *     library has anyway); larger M, negative extents or NULL pointers ->
+ *     DGSP_ERR_INVALID_ARG, nothing enqueued.
+ *   - Calls may overlap like those of the workspace version.
  *   - Like the workspace version it WAITS for its launches (result in host memory).
  */
 #define DGSP_FEATURES_NOALLOC_MAX_ROWS (2147483647LL - 4096LL)

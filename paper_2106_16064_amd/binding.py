@@ -252,8 +252,8 @@ def dgsp_features_from_csr_device(M, K, rowptr, colidx=None, workspace=None, str
 
 
 def dgsp_features_from_csr_device_noalloc(M, K, rowptr, colidx=None, stream=None) -> Features:
-    """The same statistics with the scratch words in the library's static device array: the call allocates
-    nothing and takes no workspace (calls that overlap on one GPU race; waits for the result)."""
+    """The same statistics without a workspace or pinned host memory: the call allocates
+    nothing (waits for the result)."""
     f = Features()
     rc = lib().dgsp_features_from_csr_device_noalloc(M, K, _ptr(rowptr), _ptr(colidx) if colidx is not None else None,
                                                      ctypes.byref(f), _stream(stream))
@@ -374,21 +374,23 @@ class DeviceCsr:
     def from_device(cls, M, K, rowptr, colidx, vals):
         """Wraps CSR arrays that already live on the GPU (int32 ``rowptr`` / ``colidx``, float32 ``vals``; other
         integer or float types are converted once).  The row statistics are computed on the device."""
-        import torch
-        self = cls.__new__(cls)
-        self.M, self.K = int(M), int(K)
-        self.rowptr = rowptr.to(torch.int32).contiguous()
-        self.colidx = colidx.to(torch.int32).contiguous()
-        self.vals = vals.to(torch.float32).contiguous()
-        self.nnz = int(self.colidx.numel())
-        self.features = dgsp_features_from_csr_device(self.M, self.K, self.rowptr, self.colidx if self.nnz else None)
-        self.tuned = {}
-        return self
+        f = Features()
+        return cls._taken((_native or native()).csr_from_arrays(int(M), int(K), rowptr, colidx, vals, f), f)
 
     @classmethod
     def from_torch_sparse_csr(cls, t):
         """From a ``torch.sparse_csr_tensor`` on the GPU."""
-        return cls.from_device(t.shape[0], t.shape[1], t.crow_indices(), t.col_indices(), t.values())
+        f = Features()
+        return cls._taken((_native or native()).csr_from_tensor(t, f), f)
+
+    @classmethod
+    def _taken(cls, arrays, features):
+        self = cls.__new__(cls)
+        self.M, self.K, self.rowptr, self.colidx, self.vals = arrays
+        self.nnz = self.colidx.numel()
+        self.features = features
+        self.tuned = {}
+        return self
 
     def autotune(self, X, reps=5, Y=None):
         """Times the four kernels for this matrix and this width of X and remembers the winner:

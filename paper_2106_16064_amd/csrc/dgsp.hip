@@ -4,12 +4,16 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdint>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
+#include "dgsp_internal.h"
 #include "dgsp_kernels.hpp"
 
 namespace {
@@ -967,30 +971,148 @@ extern "C" int dgsp_features_from_csr_host(int64_t M, int64_t K, const int32_t* 
     return DGSP_OK;
 }
 
+// ---------------------------------------------------------------- statistics of a matrix in device memory
+// Scratch of the pass: static device arrays (every GPU holds its own copies, at addresses that hipGetSymbolAddress tells,
+// asked once per device with that device current).  A call owns one of them from launch to result; kStatSlots calls can
+// be under way on a GPU at a time, further ones wait.
+constexpr int kStatSlots = 8;
+static __device__ __align__(256) StatScratch stat_scratch[kStatSlots];
+
 namespace {
 
-// The device pass behind both entry points: `ws` is kFeatureWords 64-bit words of device scratch.
-int features_from_csr_device(int64_t M, int64_t K, const int32_t* rowptr, const int32_t* colidx,
-                             unsigned long long* ws, dgsp_features_t* out, hipStream_t st) {
-    dgsp_features_t f{};
-    f.M = M; f.K = K;
+constexpr int kMaxDevices = 64;
+
+class StatPool {
+public:
+    struct Slot {
+        int device = -1, index = -1;
+        StatScratch* scratch = nullptr;
+        unsigned long long* host = nullptr;         // result words the GPU writes (nullptr: not asked for, or no pinned memory)
+        unsigned long long ticket = 0;
+    };
+    // false: no current device, or its scratch has no address
+    bool take(Slot& slot, bool with_host) {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+        std::unique_lock<std::mutex> lock(mu_);
+        Device& d = devices_[dev];
+        if (!d.scratch) {
+            void* ptr = nullptr;
+            if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(stat_scratch)) != hipSuccess) return false;
+            d.scratch = static_cast<StatScratch*>(ptr);
+        }
+        if (with_host && !d.host && !d.host_failed) {
+            void* ptr = nullptr;
+            if (hipHostMalloc(&ptr, kStatSlots * kHostWords * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+                d.host = static_cast<unsigned long long*>(ptr);
+                for (int i = 0; i < kStatSlots * kHostWords; ++i) d.host[i] = 0;
+            } else {
+                (void)hipGetLastError();
+                d.host_failed = true;
+            }
+        }
+        free_.wait(lock, [&] { return d.taken != (1u << kStatSlots) - 1u; });
+        int i = 0;
+        while (d.taken >> i & 1u) ++i;
+        d.taken |= 1u << i;
+        slot.device = dev;
+        slot.index = i;
+        slot.scratch = d.scratch + i;
+        slot.host = with_host && d.host ? d.host + i * kHostWords : nullptr;
+        slot.ticket = ++ticket_;
+        return true;
+    }
+    void give_back(const Slot& slot) {
+        std::lock_guard<std::mutex> lock(mu_);
+        devices_[slot.device].taken &= ~(1u << slot.index);
+        free_.notify_one();
+    }
+
+private:
+    static constexpr int kHostWords = 16;
+    struct Device {
+        StatScratch* scratch = nullptr;
+        unsigned long long* host = nullptr;
+        bool host_failed = false;
+        unsigned taken = 0;
+    };
+    std::mutex mu_;
+    std::condition_variable free_;
+    Device devices_[kMaxDevices];
+    unsigned long long ticket_ = 0;
+};
+StatPool g_stat_pool;
+
+// Waits until the GPU has announced `ticket`: a look at host memory instead of a copy and an interrupt (15 us less).
+bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t st) {
+    const auto seen = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket; };
+    for (int i = 0; i < 20000; ++i) {
+        if (seen()) return true;
+        __builtin_ia32_pause();
+    }
+    // much work ahead of it in the stream, or an error
+    return hipStreamSynchronize(st) == hipSuccess && seen();
+}
+
+void finish_features(dgsp_features_t& f, unsigned long long sq, unsigned long long rows, unsigned long long span) {
+    f.avg_row = (double)f.nnz / (double)f.M;
+    const unsigned __int128 num = (unsigned __int128)sq * (unsigned __int128)f.M
+                                  - (unsigned __int128)((uint64_t)f.nnz) * (uint64_t)f.nnz;
+    f.stdv_row = std::sqrt((double)num / ((double)f.M * (double)f.M));
+    f.cv_row = f.avg_row > 0 ? f.stdv_row / f.avg_row : 0.0;
+    f.col_span = (f.K > 0 && rows > 0) ? (double)span / ((double)f.K * (double)rows) : 0.0;
+}
+
+// The pass over columns in any order; `ws`: kFeatureWords words of device scratch.
+int features_of_unsorted_rows(int64_t M, int64_t K, const int32_t* rowptr, const int32_t* colidx, unsigned long long* ws,
+                              dgsp_features_t* out, hipStream_t st) {
     hipLaunchKernelGGL(features_init_kernel, dim3(1), dim3(kWave), 0, st, ws);
     const long long waves = (M + kWave - 1) / kWave;
     const dim3 grid(clamp_blocks((waves + kWavesPerBlock - 1) / kWavesPerBlock, (long long)device_info().cus * kBlocksPerCu));
-    hipLaunchKernelGGL(features_kernel, grid, dim3(kBlock), 0, st, (int)M, rowptr, K > 0 ? colidx : nullptr, ws);
+    hipLaunchKernelGGL(features_kernel, grid, dim3(kBlock), 0, st, (int)M, rowptr, colidx, ws);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     unsigned long long h[kFeatureWords];
     if (hipMemcpyAsync(h, ws, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return DGSP_ERR_LAUNCH;
     if (hipStreamSynchronize(st) != hipSuccess) return DGSP_ERR_LAUNCH;
-    if (h[5] != 0 || h[6] != 0) return DGSP_ERR_INVALID_ARG;       // decreasing row pointers, rowptr[0] != 0
-    f.nnz = (int64_t)h[7];
+    finish_features(*out, h[0], h[3], h[4]);
+    return DGSP_OK;
+}
+
+// `entries`: length of colidx, -1: unknown.  I = int64_t: the 32-bit arrays are written too.
+template <typename I>
+int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* rowptr, const I* colidx, int32_t* rowptr32,
+                             int32_t* colidx32, bool may_allocate, dgsp_features_t* out, hipStream_t st) {
+    using Word = std::conditional_t<sizeof(I) == 8, long long, int>;
+    dgsp_features_t f{};
+    f.M = M; f.K = K;
+    StatPool::Slot slot;
+    if (!g_stat_pool.take(slot, may_allocate)) return DGSP_ERR_LAUNCH;
+    struct Return { const StatPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
+    // enough blocks for the pieces; with the entry count unknown, for rows of 16 and no fewer than one per CU
+    const long long pieces = entries >= 0 ? std::max<long long>((entries + kStatChunk - 1) / kStatChunk, (M + kStatChunk - 1) / kStatChunk)
+                                          : std::max<long long>(M / 128, device_info().cus);
+    hipLaunchKernelGGL((csr_statistics_kernel<Word>), dim3(clamp_blocks(pieces, kStatBlocks)), dim3(kBlock), 0, st, (int)M,
+                       (long long)entries, reinterpret_cast<const Word*>(rowptr), K > 0 ? reinterpret_cast<const Word*>(colidx) : nullptr,
+                       rowptr32, colidx32, slot.scratch, slot.host, slot.ticket);
+    if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
+    unsigned long long h[kStatResultWords];
+    if (slot.host) {
+        if (!wait_for_ticket(slot.host + kStatResultWords, slot.ticket, st)) return DGSP_ERR_LAUNCH;
+        for (int w = 0; w < kStatResultWords; ++w) h[w] = __atomic_load_n(slot.host + w, __ATOMIC_RELAXED);
+    } else {
+        if (hipMemcpyAsync(h, slot.scratch->result, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return DGSP_ERR_LAUNCH;
+        if (hipStreamSynchronize(st) != hipSuccess) return DGSP_ERR_LAUNCH;
+    }
+    if (h[5] != 0 || h[kStatWords] != 0) return DGSP_ERR_INVALID_ARG;       // decreasing row pointers, rowptr[0] != 0
+    f.nnz = (int64_t)h[kStatWords + 1];
     f.max_row = (int64_t)h[1]; f.min_row = (int64_t)h[2];
-    f.avg_row = (double)f.nnz / (double)M;
-    const unsigned __int128 num = (unsigned __int128)h[0] * (unsigned __int128)M
-                                  - (unsigned __int128)((uint64_t)f.nnz) * (uint64_t)f.nnz;
-    f.stdv_row = std::sqrt((double)num / ((double)M * (double)M));
-    f.cv_row = f.avg_row > 0 ? f.stdv_row / f.avg_row : 0.0;
-    f.col_span = (colidx && K > 0 && h[3] > 0) ? (double)h[4] / ((double)K * (double)h[3]) : 0.0;
+    finish_features(f, h[0], h[3], h[4]);
+    if (h[6] != h[7]) {
+        const int rc = features_of_unsorted_rows(M, K, sizeof(I) == 8 ? rowptr32 : reinterpret_cast<const int32_t*>(rowptr),
+                                                 sizeof(I) == 8 ? colidx32 : reinterpret_cast<const int32_t*>(colidx),
+                                                 slot.scratch->result, &f, st);
+        if (rc != DGSP_OK) return rc;
+    }
     *out = f;
     return DGSP_OK;
 }
@@ -1003,46 +1125,29 @@ extern "C" int dgsp_features_from_csr_device(int64_t M, int64_t K, const int32_t
     if (M > (int64_t)INT32_MAX - 4096) return DGSP_ERR_INVALID_ARG;
     if (M == 0) { dgsp_features_t f{}; f.K = K; *out = f; return DGSP_OK; }
     if (!workspace || !aligned(workspace, 8)) return DGSP_ERR_INVALID_ARG;
-    return features_from_csr_device(M, K, rowptr, colidx, static_cast<unsigned long long*>(workspace), out,
-                                    (hipStream_t)stream);
+    return features_from_csr_device<int32_t>(M, K, -1, rowptr, colidx, nullptr, nullptr, true, out, (hipStream_t)stream);
 }
 
-// ---------------------------------------------------------------- the entry point that allocates nothing
-// The statistics pass with its scratch words in a static device array.  In host code the array's name is only
-// a handle: the address a kernel can use comes from hipGetSymbolAddress, asked once per device with that
-// device current (every GPU holds its own copy of the array at its own address).
-static __device__ __align__(256) unsigned long long scratch[dgsp::kFeatureWords];     // 64 bytes per GPU
-
-namespace {
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-unsigned long long* g_scratch_ptr[kMaxDevices] = {};
-
-// Device address of this GPU's copy of `scratch` (nullptr on failure).
-unsigned long long* scratch_of_current_device() {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void* ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess) return nullptr;
-        g_scratch_ptr[dev] = static_cast<unsigned long long*>(ptr);
-    }
-    return g_scratch_ptr[dev];
-}
-
-}  // namespace
-
+// allocates nothing, not even the pinned words: the result comes back by a copy
 extern "C" int dgsp_features_from_csr_device_noalloc(int64_t M, int64_t K, const int32_t* rowptr,
                                                      const int32_t* colidx, dgsp_features_t* out, void* stream) {
     if (M < 0 || K < 0 || !out || (!rowptr && M > 0)) return DGSP_ERR_INVALID_ARG;
     if (M > DGSP_FEATURES_NOALLOC_MAX_ROWS) return DGSP_ERR_INVALID_ARG;
     if (M == 0) { dgsp_features_t f{}; f.K = K; *out = f; return DGSP_OK; }
-    unsigned long long* ws = scratch_of_current_device();
-    if (!ws) return DGSP_ERR_LAUNCH;
-    // features_init_kernel (a kernel, not a memset) clears the array first: it keeps the last call's contents
-    return features_from_csr_device(M, K, rowptr, colidx, ws, out, (hipStream_t)stream);
+    return features_from_csr_device<int32_t>(M, K, -1, rowptr, colidx, nullptr, nullptr, false, out, (hipStream_t)stream);
+}
+
+extern "C" int dgsp_internal_take_csr(int64_t M, int64_t K, int64_t entries, int index_bytes, const void* rowptr,
+                                      const void* colidx, int32_t* rowptr32, int32_t* colidx32, dgsp_features_t* out, void* stream) {
+    const int64_t lim = (int64_t)INT32_MAX - 4096;
+    if (M < 1 || M > lim || K < 0 || entries < 0 || entries > lim || !rowptr || !out) return DGSP_ERR_INVALID_ARG;
+    if (K == 0 || entries == 0) colidx = nullptr;
+    if (index_bytes == 4)
+        return features_from_csr_device<int32_t>(M, K, entries, static_cast<const int32_t*>(rowptr), static_cast<const int32_t*>(colidx),
+                                                 nullptr, nullptr, true, out, (hipStream_t)stream);
+    if (index_bytes != 8 || !rowptr32 || (colidx && !colidx32)) return DGSP_ERR_INVALID_ARG;
+    return features_from_csr_device<int64_t>(M, K, entries, static_cast<const int64_t*>(rowptr), static_cast<const int64_t*>(colidx),
+                                             rowptr32, colidx32, true, out, (hipStream_t)stream);
 }
 
 extern "C" int dgsp_autotune(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,

@@ -20,7 +20,7 @@
 #include <cstring>
 #include <string>
 
-#include "../../include/dgsp.h"
+#include "dgsp_internal.h"
 
 namespace {
 
@@ -204,6 +204,37 @@ struct ProductBackward : public torch::autograd::Node {
     std::string name() const override { return "SpMMBackward"; }
 };
 
+// ---------------------------------------------------------------- a matrix from arrays on the GPU
+
+struct CsrArrays { at::Tensor rowptr, colidx, vals; };
+
+// The arrays in the library's types and the statistics, which the call waits for.  int64 indices are narrowed by the
+// statistics' own launch.
+CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals, dgsp_features_t& f) {
+    at::NoGradGuard no_grad;
+    CsrArrays out;
+    const auto plain = [&](const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); };
+    const bool wide = plain(rowptr, at::kLong) && plain(colidx, at::kLong) && M > 0 && colidx.numel() < INT32_MAX - 4096;
+    out.rowptr = wide ? at::empty(rowptr.sizes(), rowptr.options().dtype(at::kInt)) : rowptr.to(at::kInt).contiguous();
+    out.colidx = wide ? at::empty(colidx.sizes(), colidx.options().dtype(at::kInt)) : colidx.to(at::kInt).contiguous();
+    out.vals = plain(vals, at::kFloat) ? vals : vals.to(at::kFloat).contiguous();
+    if (!on_gpu(out.rowptr) || !on_gpu(out.colidx) || out.rowptr.numel() != M + 1) fail("rowptr needs M+1 entries on the GPU");
+    if (M == 0) {
+        f = dgsp_features_t{};
+        f.K = K;
+        return out;
+    }
+    void* stream = c10::hip::getCurrentHIPStream().stream();
+    const int64_t entries = colidx.numel();
+    const void* rp = ptr(wide ? rowptr : out.rowptr);
+    const void* ci = ptr(wide ? colidx : out.colidx);
+    auto* rp32 = static_cast<int32_t*>(ptr(out.rowptr));
+    auto* ci32 = static_cast<int32_t*>(ptr(out.colidx));
+    check_status(unlocked([&] { return dgsp_internal_take_csr(M, K, entries, wide ? 8 : 4, rp, ci, rp32, ci32, &f, stream); }),
+                 "dgsp_features_from_csr_device");
+    return out;
+}
+
 // ---------------------------------------------------------------- the functions
 
 void want(Py_ssize_t n, Py_ssize_t expected) {
@@ -259,6 +290,43 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
         torch::autograd::set_history(Y, node);
     }
     return THPVariable_Wrap(std::move(Y));
+}
+
+void write_features(PyObject* o, const dgsp_features_t& f) {
+    Py_buffer view;
+    if (PyObject_GetBuffer(o, &view, PyBUF_WRITABLE) != 0) throw Raised{};
+    const bool fits = view.len == (Py_ssize_t)sizeof(f);
+    if (fits) memcpy(view.buf, &f, sizeof(f));
+    PyBuffer_Release(&view);
+    if (!fits) fail("features must be a Features structure");
+}
+
+PyObject* wrapped(CsrArrays&& a, int64_t M, int64_t K) {
+    PyObject* rowptr = THPVariable_Wrap(std::move(a.rowptr));
+    PyObject* colidx = THPVariable_Wrap(std::move(a.colidx));
+    PyObject* vals = THPVariable_Wrap(std::move(a.vals));
+    return Py_BuildValue("LLNNN", (long long)M, (long long)K, rowptr, colidx, vals);
+}
+
+// (M, K, rowptr, colidx, vals, features to fill) -> (M, K, rowptr, colidx, vals) in the library's types
+PyObject* csr_from_arrays(PyObject* const* a, Py_ssize_t n) {
+    want(n, 6);
+    const int64_t M = as_int(a[0]), K = as_int(a[1]);
+    dgsp_features_t f;
+    CsrArrays arrays = take_csr(M, K, as_tensor(a[2], "rowptr"), as_tensor(a[3], "colidx"), as_tensor(a[4], "vals"), f);
+    write_features(a[5], f);
+    return wrapped(std::move(arrays), M, K);
+}
+
+// (sparse CSR tensor, features to fill) -> the same
+PyObject* csr_from_tensor(PyObject* const* a, Py_ssize_t n) {
+    want(n, 2);
+    const at::Tensor& T = as_tensor(a[0], "matrix");
+    if (T.layout() != at::kSparseCsr || T.dim() != 2) fail("the matrix must be a 2-D sparse CSR tensor");
+    dgsp_features_t f;
+    CsrArrays arrays = take_csr(T.size(0), T.size(1), T.crow_indices(), T.col_indices(), T.values().detach(), f);
+    write_features(a[1], f);
+    return wrapped(std::move(arrays), T.size(0), T.size(1));
 }
 
 // (M, K, N, features, rowptr, colidx, vals, X, Y, stream) -> kernel run
@@ -329,7 +397,7 @@ PyObject* spmm_csr_view(PyObject* const* a, Py_ssize_t n) {
 #define DGSP_ENTRY(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&entry<name>)), METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {
     DGSP_ENTRY(set_error_type), DGSP_ENTRY(multiply_new), DGSP_ENTRY(multiply_differentiable), DGSP_ENTRY(spmm_csr_auto),
-    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_view), {nullptr, nullptr, 0, nullptr},
+    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_view), DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_dgsp_torch", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -57,3 +57,68 @@ def test_gradient_of_other_types_and_layouts(dtype, N):
     assert got.dtype == leaf.dtype
     ok, worst = oracle.within_bound(got.float().cpu().numpy().reshape(T.M, cols), 2 * ref, 2 * bnd, 1e-5)
     assert ok, worst
+
+
+STATS = {
+    "chunk_edges": [2047, 1, 2048, 2049, 0, 1, 2046, 2, 0, 0],
+    "one_row": [5000],
+    "one_entry": [1],
+    "empty_rows_around": [0] * 3000 + [7] + [0] * 3000,
+    "no_entries": [0] * 300,
+    "many_blocks": [3, 1, 0, 8] * 160000,
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", ["ascending", "one_descent", "shuffled"])
+@pytest.mark.parametrize("name", sorted(STATS))
+def test_statistics_and_index_types(name, order):
+    """Statistics of device arrays and the 32-bit copies of int64 ones, at the edges of the pieces the entries are counted in."""
+    import torch
+    A = wl.csr_from_lens(STATS[name], K=6000, seed=3, name=name)
+    colidx = A.colidx.copy()
+    rng = np.random.default_rng(1)
+    longest = int(np.argmax(A.row_lengths()))
+    s, e = A.rowptr[longest], A.rowptr[longest + 1]
+    if order == "one_descent" and e - s > 1:
+        colidx[[e - 2, e - 1]] = colidx[[e - 1, e - 2]]
+    elif order == "shuffled":
+        colidx[s:e] = rng.permutation(colidx[s:e])
+    want = dg.dgsp_features_from_csr_host(A.M, A.K, A.rowptr, colidx)
+    vals = torch.from_numpy(A.vals).cuda()
+    for dtype in (np.int32, np.int64):
+        print(f"[case] statistics {name} {order} {dtype.__name__}", flush=True)
+        D = dg.DeviceCsr.from_device(A.M, A.K, torch.from_numpy(A.rowptr.astype(dtype)).cuda(),
+                                     torch.from_numpy(colidx.astype(dtype)).cuda(), vals)
+        assert D.features.as_dict() == want.as_dict()
+        assert D.rowptr.dtype == torch.int32 and np.array_equal(D.rowptr.cpu().numpy(), A.rowptr)
+        assert D.colidx.dtype == torch.int32 and np.array_equal(D.colidx.cpu().numpy(), colidx)
+
+
+@pytest.mark.gpu
+def test_statistics_from_several_threads():
+    """More calls under way than there are places for, each on a stream of its own."""
+    import threading
+    import torch
+    mats = [wl.sweep_csr(3000 + 700 * i, 12, "lognormal", seed=i) for i in range(12)]
+    arrays = [(torch.from_numpy(A.rowptr.astype(np.int64)).cuda(), torch.from_numpy(A.colidx.astype(np.int64)).cuda(),
+               torch.from_numpy(A.vals).cuda()) for A in mats]
+    torch.cuda.synchronize()
+    got, errors = [None] * len(mats), []
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(20):
+                    got[i] = dg.DeviceCsr.from_device(mats[i].M, mats[i].K, *arrays[i]).features.as_dict()
+        except Exception as e:          # surfaced in the main thread below
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(mats))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for A, f in zip(mats, got):
+        assert f == dg.dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict()

@@ -194,7 +194,11 @@ int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz,
 /*
  * Adaptive call (Section 2.2): dgsp_select_algo(features, N), then the chosen
  * kernel.  `features` is a host pointer, read before the call returns.  If
- * `chosen` is not NULL it receives the dgsp_algo_t that ran.
+ * `chosen` is not NULL it receives the dgsp_algo_t of the rules.  Where the
+ * statistics show that runs of rows are balanced anyway (rows alike) or that the
+ * matrix is too small for a balanced kernel's start to pay, the launch itself uses
+ * the row-split sequential kernel with several lanes per row; a kernel asked for
+ * by name is always the one that runs.
  */
 int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N,
                        const dgsp_features_t *features,

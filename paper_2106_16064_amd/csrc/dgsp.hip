@@ -70,6 +70,7 @@ struct Hints {
     double col_span = 0.0;
     double cv_row = -1.0;
     int64_t max_row = -1;
+    bool chosen = false;        // the kernel is the library's choice from these statistics, not the caller's
     Hints() = default;
     explicit Hints(const dgsp_features_t* f) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
 };
@@ -169,22 +170,7 @@ int launch_rs_pr_v(const Problem& p) {
     return DGSP_OK;
 }
 
-// Rows more or less alike, none of them so long that it would hold up the wave of row groups it is in: equal runs of rows
-// are equal shares of entries, and up to four columns the row-group kernel (rs_sr_kernel), whose H lanes on a row's
-// entries are the same reduction as theirs, takes the place of both parallel kernels.  It needs no search, no row marks, no
-// prepare launch and no atomics, and its entries arrive coalesced through LDS.  Against rs_pr: 4096 rows of 8 at N = 4
-// 5.7 -> 3.7 us, 20 000 rows of 100 at N = 1 16 -> 10 us; against nb_pr: 27-point stencil on 128^3 at N = 1 / 4 129 / 147 ->
-// 95 / 114 us, on 61^3 25 -> 12.5 us, 776 379 rows of 22 over 27 098 columns at N = 1 86 -> 70 us, 187 500 Poisson rows
-// of 8 at N = 4 22 -> 14 us; 262 144 rows of 64 at N = 1 break even.
-constexpr double kRowGroupCvMax = 0.6;
-inline bool row_groups_balance(const Problem& p) {
-    return p.N <= 4 && p.switches == 0 && p.nnz > 0 && p.cv_row >= 0.0 && p.cv_row <= kRowGroupCvMax && p.max_row >= 0 &&
-           (double)p.max_row <= 8.0 * (double)p.nnz / (double)p.M + 64.0;
-}
-int launch_rs_sr(const Problem& p);
-
 int launch_rs_pr(const Problem& p) {
-    if (row_groups_balance(p)) return launch_rs_sr(p);
     const bool xb = x_fits_descriptor(p);
     switch (pr_vector_width(p)) {
         case 4: return xb ? launch_rs_pr_v<4, true>(p) : launch_rs_pr_v<4, false>(p);
@@ -279,7 +265,12 @@ inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
 // log2 of the lanes that share a row's entries (H) when 2^logG lanes span its columns.  A wave's rows should fit one
 // round of the LDS tile: with 64 rows of 27 a round holds 19 of them and the other lanes wait (27-point stencil on 128^3
 // at N = 1: H = 1 153 us, H = 4 121 us; N = 4 190 -> 133 us).  A matrix that leaves the machine half empty is split
-// further while a lane keeps two entries (4500 rows of 30: H = 4 6.5 us, H = 8 3.8 us).
+// further while a lane keeps two entries (4500 rows of 30: H = 4 6.5 us, H = 8 3.8 us), uneven rows for the longest one's
+// sake (32 768 lognormal rows of 8 at N = 4: H = 4 / 8 / 16 12.1 / 8.5 / 7.4 us).
+// dense-row loads in flight per lane out of step; at one column per lane eight are as many registers as two at four
+// columns (stencil 128^3 at N = 1: 125 -> 121 us)
+constexpr int rs_sr_depth(int v) { return v == 1 ? 8 : 4; }
+constexpr double kRowGroupCvMax = 0.6;
 inline int rs_sr_split_log2(const Problem& p, int logG) {
     if (p.nnz < 0 || p.M == 0) return 0;
     const double avg = (double)p.nnz / (double)p.M;
@@ -290,8 +281,10 @@ inline int rs_sr_split_log2(const Problem& p, int logG) {
         const double spread = p.cv_row >= 0.0 ? 2.0 * p.cv_row * avg * std::sqrt((double)rows) : 0.1 * rows * avg;
         if (rows * avg + spread <= (double)kRsSrTile) break;
     }
-    const double few = device_info().cus * 8.0;                // waves: two per SIMD
-    while (logG + logH < 6 && (double)p.M * (double)(1 << (logG + logH)) < few * kWave && avg >= (double)(4 << logH)) ++logH;
+    // waves: two per SIMD, or with uneven rows, whose longest keep their lanes busy when the others are done, as many as fit
+    const double few = device_info().cus * (p.cv_row > kRowGroupCvMax ? kWaveSlotsPerCu : 8.0);
+    while (logG + logH < 6 && (double)p.M * (double)(1 << (logG + logH)) < few * kWave &&
+           (avg >= (double)(4 << logH) || p.max_row >= (16ll << logH))) ++logH;
     return logH;
 }
 
@@ -330,6 +323,42 @@ int launch_rs_sr_direct_v(const Problem& p) {
     return DGSP_OK;
 }
 
+// Dense columns per lane of the row-split sequential kernel: four, the last lane's window overlapping its neighbour's
+// when four does not divide N; three where it divides N = 3 or 6 (N = 3 as three lanes of one column, one lane of four
+// idle: stencil 80^3 42 us, against 37 us at N = 4).
+inline SrShape rs_sr_shape(const Problem& p) {
+    if (p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) return {1, false};
+    if (p.N == 3 || p.N == 6) return {3, false};
+    if (p.N < 4) return {p.N, false};
+    return {4, p.N % 4 != 0};
+}
+
+// Where the library chooses: may the row-group kernel (rs_sr_kernel) take the place of the kernel that the selection rules
+// name?  Its H lanes on a row's entries are a parallel reduction too, it needs no search, no row marks, no prepare launch and
+// no atomics, and its entries arrive coalesced through LDS; it does nothing against rows longer than the others but give a
+// row more lanes.
+//   Rows more or less alike, up to four columns: equal runs of rows are equal shares of entries.  Against rs_pr: 4096 rows
+//   of 8 at N = 4 5.7 -> 3.7 us, 20 000 rows of 100 at N = 1 16 -> 10 us; against nb_pr: 27-point stencil on 128^3 at
+//   N = 1 / 4 129 / 147 -> 95 / 114 us, 776 379 rows of 22 over 27 098 columns at N = 1 86 -> 70 us, 187 500 Poisson rows of
+//   8 at N = 4 22 -> 14 us; 262 144 rows of 64 at N = 1 break even.
+//   Small matrices with uneven rows: the balanced kernels' start (searches, row marks, perhaps two launches) is most of
+//   the call, and the longest row is `steps` rounds of loads for its lanes.  Lognormal rows of 8, row groups against the
+//   better of nb_sr and nb_pr: 8192 rows at N = 1 / 4 / 16 / 33 3.8 / 3.9 / 5.3 / 6.7 against 6.7 / 6.4 / 6.8 / 9.3 us,
+//   65 536 rows at N = 1 / 4 / 8 / 16 9.3 / 10.7 / 16.5 / 31 against 10.0 / 12.9 / 16.7 / 16.8 us; crossover near 600 000
+//   entries at N <= 4 (150 000 rows of 8: 15 against 13 us).
+constexpr long long kSmallUnevenNnz = 600000, kTinyNnz = 130000;
+inline bool row_groups_suit(const Problem& p) {
+    if (p.switches != 0 || p.nnz <= 0 || p.M == 0 || p.cv_row < 0.0 || p.max_row < 0) return false;
+    const double avg = (double)p.nnz / (double)p.M;
+    if (p.cv_row <= kRowGroupCvMax && (double)p.max_row <= 8.0 * avg + 64.0) return p.N <= 4;
+    if (p.nnz > kSmallUnevenNnz) return false;
+    const int v = rs_sr_shape(p).v;
+    const int lanes_log2 = rs_sr_split_log2(p, sr_columns(p.N, v, false).logG);
+    // rounds of loads for the longest row, and the rounds of the LDS tile (six times as long) that it takes
+    const double steps = (double)p.max_row / (double)(rs_sr_depth(v) << lanes_log2) + 6.0 * (double)(p.max_row / kRsSrTile);
+    return steps <= (p.N <= 4 ? 16.0 : p.nnz <= kTinyNnz ? 12.0 : 8.0);
+}
+
 template <int V, bool RAGGED>
 int launch_rs_sr_pick(const Problem& p) {
     const bool xb = x_fits_descriptor(p);
@@ -340,19 +369,8 @@ int launch_rs_sr_pick(const Problem& p) {
     const SrColumns cols = sr_columns(p.N, V, even_rows(p) && p.N >= 128);
     if (rows_in_step(p, cols)) return xb ? launch_rs_sr_v<V, true, 1, RAGGED>(p, cols, 0) : launch_rs_sr_v<V, false, 1, RAGGED>(p, cols, 0);
     const int logH = rs_sr_split_log2(p, cols.logG);
-    // one column per lane: eight loads in flight are as many registers as two at V = 4 (stencil 128^3: 125 -> 121 us)
-    constexpr int D = V == 1 ? 8 : 4;
+    constexpr int D = rs_sr_depth(V);
     return xb ? launch_rs_sr_v<V, true, D, RAGGED>(p, cols, logH) : launch_rs_sr_v<V, false, D, RAGGED>(p, cols, logH);
-}
-
-// Dense columns per lane of the row-split sequential kernel: four, the last lane's window overlapping its neighbour's
-// when four does not divide N; three where it divides N = 3 or 6 (N = 3 as three lanes of one column, one lane of four
-// idle: stencil 80^3 42 us, against 37 us at N = 4).
-inline SrShape rs_sr_shape(const Problem& p) {
-    if (p.switches & DGSP_ABL_SCALAR_DENSE_LOADS) return {1, false};
-    if (p.N == 3 || p.N == 6) return {3, false};
-    if (p.N < 4) return {p.N, false};
-    return {4, p.N % 4 != 0};
 }
 
 int launch_rs_sr(const Problem& p) {
@@ -434,6 +452,21 @@ template <int V>
 constexpr bool kNbPrStreams = V <= 4;
 constexpr long long kNbPrStreamNnzMin = 6000000;
 
+// Do the chunks of a balanced kernel take whole rows?  That saves the atomics and the prepare launch (6 us with the gap
+// behind it), and the wave with the longest row ends later: by up to `per_us` entries a microsecond, as it runs on when the
+// others are through - behind a part of the time they take, as long as the call is short.  `lines`: lines of X per entry.
+// 100 000 lognormal rows of 6 at N = 6 20.3 -> 13.6 us, 20 001 of 10 at N = 32 16 -> 11 us; not taken: 100 000 Zipf rows
+// of 50 at N = 33 (141 against 185 us), 100 000 lognormal rows of 20 at N = 33 (64 against 73 us).
+inline bool snap_rows(const Problem& p, unsigned groups, double share_part, double per_us, double lines) {
+    if (p.nnz < 0 || p.max_row < 0) return false;
+    const double share = (double)(p.nnz + (long long)p.M) / ((double)groups * kWavesPerBlock);
+    if ((double)p.max_row <= share_part * share) return true;
+    const double x_bytes = (double)p.K * p.N * 4.0;
+    const double missed = x_bytes > (double)kL2BytesPerXcd ? 1.0 - (double)kL2BytesPerXcd / x_bytes : 0.0;
+    const double call_us = 5.0 + (double)p.nnz * lines * (6.5e-6 + 12.5e-6 * missed * missed);
+    return (double)p.max_row / per_us <= 6.0 + (call_us < 100.0 ? 0.35 * call_us : 0.0);
+}
+
 template <int V, int KQ>
 int launch_nb_pr_v(const Problem& p) {
     constexpr unsigned tile = kWave * 4 * KQ;
@@ -451,30 +484,37 @@ int launch_nb_pr_v(const Problem& p) {
     const bool tiled = !kNbPrStreams<V> || (p.switches & DGSP_ABL_ITEM_TILES) != 0 ||
                        (!forced_blocks && (p.nnz < kNbPrStreamNnzMin || banded_x));   // unknown entry count (-1): tiles
     int resident = resident_blocks_per_cu(nb_pr_tiled_kernel<V, KQ>);
-    if constexpr (kNbPrStreams<V>) { if (!tiled) resident = resident_blocks_per_cu(nb_pr_kernel<V, KQ>); }
+    if constexpr (kNbPrStreams<V>) { if (!tiled) resident = resident_blocks_per_cu(nb_pr_kernel<V, KQ, false>); }
     const bool few_waves = banded_x && V <= 3;
     const dim3 grid(balanced_blocks(p, tile, resident, true, 1, few_waves ? 2 : 0), col_groups);
-    if (p.phase != DGSP_PHASE_MAIN)
+    // a wave alone takes 512 entries in about 4 us
+    const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
+    if (p.phase != DGSP_PHASE_MAIN && !snap)
         if (int rc = launch_prepare(p, grid.x * kWavesPerBlock * kSubRanges, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         if (tiled) {
             if (p.scaled)
                 DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                            p.Y, Scaling{p.alpha, p.beta});
+                            p.Y, snap, Scaling{p.alpha, p.beta});
             else
-                DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, snap);
         } else if constexpr (kNbPrStreams<V>) {
-            if constexpr (V <= 2) {
-                if (p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) {
-                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
-                    return DGSP_OK;
+            const auto launch = [&](auto whole) -> int {
+                constexpr bool kSnap = decltype(whole)::value;
+                if constexpr (V <= 2 && !kSnap) {
+                    if (p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) {
+                        DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                        return DGSP_OK;
+                    }
                 }
-            }
-            if (p.scaled)
-                DGSP_LAUNCH((nb_pr_kernel<V, KQ, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
-                            Scaling{p.alpha, p.beta});
-            else
-                DGSP_LAUNCH((nb_pr_kernel<V, KQ>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                if (p.scaled)
+                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
+                                p.Y, Scaling{p.alpha, p.beta});
+                else
+                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                return DGSP_OK;
+            };
+            return snap ? launch(std::true_type{}) : launch(std::false_type{});
         }
     }
     return DGSP_OK;
@@ -535,10 +575,8 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         grid = dim3(per_xcd * kXcd, 1);
     }
     const unsigned chunk_groups = pinned ? grid.x / pinned : grid.x;              // workgroups that share one chunk list
-    // Whole rows per chunk when the longest is at most four shares (or one block of entries): the wave that has it ends
-    // later by as much, which never measured slower than the atomics and the prepare launch it saves (3-5 us).
-    const long long share = (p.nnz + (long long)p.M) / ((long long)chunk_groups * kWavesPerBlock);
-    const int snap = p.nnz >= 0 && p.max_row >= 0 && (p.max_row <= 4 * share || p.max_row <= kRunBlock);
+    // a wave alone takes one batch of its lane groups in about 1 us
+    const int snap = snap_rows(p, chunk_groups, 1.0, (double)((kWave >> LOGG) * kRunBatch), lines_per_row(cols.cols_per_block, p.ldx) * col_blocks);
     if (p.phase != DGSP_PHASE_MAIN && !snap)
         if (int rc = launch_prepare(p, chunk_groups * kWavesPerBlock * kSubRanges, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
@@ -586,10 +624,12 @@ int launch_nb_sr(const Problem& p) {
 // segmented scan over the lanes' open rows - with two lanes per entry (nb_sr_run_kernel), which reads a row of X in one
 // access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 156 / 156 -> 140 / 139 us, Zipf rows of 16 at N = 8 61 -> 58 us,
 // lognormal rows of 64 at N = 5 / 8 173 / 190 -> 143 / 179 us; a tie on small matrices.
+// Not for a small matrix whose long rows keep it from whole rows per wave (R-MAT 2^14 x 24 at N = 6 12.0 against 14.5 us).
+constexpr long long kRunNarrowNnzMin = 1000000, kRunNarrowRowMax = 1500;
 int launch_nb_pr(const Problem& p) {
-    if (row_groups_balance(p)) return p.phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_sr(p);
     const int v = nb_pr_lane_width(p.N, p.switches);
-    if (v == 8 && p.N <= 8 && p.switches == 0 && p.ldy <= kBalancedLdyMax) return launch_nb_sr_run(p);
+    const bool short_call = p.nnz >= 0 && p.nnz < kRunNarrowNnzMin && p.max_row > kRunNarrowRowMax;
+    if (v == 8 && p.N <= 8 && p.switches == 0 && p.ldy <= kBalancedLdyMax && !short_call) return launch_nb_sr_run(p);
     switch (v) {
         case 8: return launch_nb_pr_v<8, 1>(p);
         case 4: return launch_nb_pr_v<4, kNbPrKq>(p);
@@ -658,6 +698,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
 
     Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
+    if (hints.chosen && algo != DGSP_RS_SR && row_groups_suit(p)) algo = DGSP_RS_SR;
     switch (algo) {
         case DGSP_RS_SR: return phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_sr(p);
         case DGSP_RS_PR: return phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_pr(p);
@@ -696,11 +737,13 @@ extern "C" int dgsp_spmm_csr_ld(int64_t M, int64_t K, int64_t N, int64_t nnz, co
                                 int64_t ldy, int algo, const dgsp_features_t* features, void* stream) {
     if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
     if (features && nnz < 0) nnz = features->nnz;
+    Hints hints(features);
     if (algo == DGSP_AUTO && features && N >= 1) {
         algo = library_choice(dgsp_select_algo(features, N), ldy);
+        hints.chosen = true;
     }
     return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL,
-               Hints(features), 0, ldx, ldy);
+               hints, 0, ldx, ldy);
 }
 
 extern "C" int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
@@ -709,12 +752,14 @@ extern "C" int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz,
                                    void* stream) {
     if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
     if (features && nnz < 0) nnz = features->nnz;
+    Hints hints(features);
     if (algo == DGSP_AUTO && features && N >= 1) {
         algo = library_choice(dgsp_select_algo(features, N), ldy);
+        hints.chosen = true;
     }
     const Scaling sc{alpha, beta};
     return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL,
-               Hints(features), 0, ldx, ldy, &sc);
+               hints, 0, ldx, ldy, &sc);
 }
 
 extern "C" int dgsp_spmm_csr_ablation(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
@@ -748,7 +793,9 @@ extern "C" int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N, const dgsp_fe
     int algo = (N >= 1) ? library_choice(dgsp_select_algo(features, N), N) : DGSP_NB_PR;
     if (algo < 0) return DGSP_ERR_INVALID_ARG;
     if (chosen) *chosen = algo;
-    return run(M, K, N, features->nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, Hints(features));
+    Hints hints(features);
+    hints.chosen = true;
+    return run(M, K, N, features->nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
 }
 
 // ---------------------------------------------------------------- 64-bit row pointers

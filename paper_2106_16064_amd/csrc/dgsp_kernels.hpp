@@ -513,6 +513,55 @@ __device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ ro
     return uniform(lo);
 }
 
+// Rows that ended before diagonal da, and before db (both searches of wave_merge_rows_before in lock-step: their
+// probes are in flight together, so the second costs no further round trips).
+__device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ rowptr, int M, unsigned da, unsigned db,
+                                                        int lane, int& ra, int& rb) {
+    int lo[2] = {0, 0}, hi[2] = {M, M};
+    const unsigned d[2] = {da, db};
+    while (hi[0] > lo[0] || hi[1] > lo[1]) {
+        int step[2], v[2];
+        long long r[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            step[k] = (hi[k] - lo[k] + 63) >> 6;
+            r[k] = (long long)lo[k] + (long long)lane * step[k];
+            v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (hi[k] > lo[k]) {                                   // wave-uniform
+                const bool before = r[k] < hi[k] && (unsigned)r[k] + (unsigned)v[k] < d[k];
+                const int cnt = __popcll(__ballot(before));       // probes are monotone: 1...10...0
+                if (cnt == 0) {
+                    hi[k] = lo[k];
+                } else {
+                    const int nlo = lo[k] + (cnt - 1) * step[k] + 1;
+                    const int nhi = lo[k] + cnt * step[k];
+                    lo[k] = nlo;
+                    hi[k] = nhi < hi[k] ? nhi : hi[k];
+                }
+            }
+        }
+    }
+    ra = uniform(lo[0]);
+    rb = uniform(lo[1]);
+}
+
+// SNAP: a row belongs wholly to the chunk that holds its first item (the host asks for it when the longest row is short
+// against a wave's share).  Nothing is added to memory then, so the launch that clears the shared rows falls away (3-10 us)
+// and the result is the same from run to run.  Turns the bounds of a chunk, [d0, d1) with `is` rows ended before d0 and `ie`
+// before d1, into those of its rows.
+__device__ __forceinline__ void snap_to_rows(const int* __restrict__ rowptr, int M, unsigned d0, unsigned d1, int& is, int& ie,
+                                             unsigned& js, unsigned& je) {
+    // rows that started before a chunk's first item belong to the chunk before
+    if (is < M && (unsigned)is + (unsigned)rowptr[is] < d0) ++is;
+    if (ie < M && (unsigned)ie + (unsigned)rowptr[ie] < d1) ++ie;
+    is = uniform(is); ie = uniform(ie);
+    js = (unsigned)uniform(rowptr[is]);
+    je = (unsigned)uniform(rowptr[ie]);
+}
+
 constexpr unsigned kNoRow = 0xffffffffu;
 
 // ===========================================================================
@@ -558,7 +607,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        Scaling sc = Scaling{1.0f, 0.0f}) {
+                                                        int snap, Scaling sc = Scaling{1.0f, 0.0f}) {
     constexpr int E = 4 * KQ;
     constexpr int W = kWave * E;
     // accessed 16 bytes at a time: every wave's part starts on a 16-byte boundary ((W + 4) * 4 and W * V * 4 are multiples of 16)
@@ -601,11 +650,23 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         continue;
     }
 
-    int is = wave_merge_rows_before(rowptr, M, d0, lane);   // rows that ended before my chunk
-    unsigned js = d0 - (unsigned)is;                        // entries consumed before my chunk
+    int is;                                                 // rows that ended before my chunk
+    unsigned js;                                            // entries consumed before my chunk
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
+    bool first_split = false;
+    if (snap) {
+        int ie1; unsigned je1;
+        wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
+        snap_to_rows(rowptr, M, d0, d1, is, ie1, js, je1);
+        if (is == ie1) continue;
+        d0 = (unsigned)is + js;
+        d1 = (unsigned)ie1 + je1;
+    } else {
+        is = wave_merge_rows_before(rowptr, M, d0, lane);
+        js = d0 - (unsigned)is;
+        first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
+    }
     const int r_first = is;
-    const bool first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
 
     // entries of a tile starting at entry `from`: at most W.  The descriptor ends at the arrays' end,
     // so lanes past it load nothing; `on` = false switches the whole load off.
@@ -869,46 +930,11 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 // The row-bound window of the next step is requested before the next entries, so waiting for it does not wait
 // for them (loads return in issue order).
 
-// Rows that ended before diagonal da, and before db (both searches of wave_merge_rows_before in lock-step: their
-// probes are in flight together, so the second costs no further round trips).
-__device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ rowptr, int M, unsigned da, unsigned db,
-                                                        int lane, int& ra, int& rb) {
-    int lo[2] = {0, 0}, hi[2] = {M, M};
-    const unsigned d[2] = {da, db};
-    while (hi[0] > lo[0] || hi[1] > lo[1]) {
-        int step[2], v[2];
-        long long r[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            step[k] = (hi[k] - lo[k] + 63) >> 6;
-            r[k] = (long long)lo[k] + (long long)lane * step[k];
-            v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            if (hi[k] > lo[k]) {                                   // wave-uniform
-                const bool before = r[k] < hi[k] && (unsigned)r[k] + (unsigned)v[k] < d[k];
-                const int cnt = __popcll(__ballot(before));       // probes are monotone: 1...10...0
-                if (cnt == 0) {
-                    hi[k] = lo[k];
-                } else {
-                    const int nlo = lo[k] + (cnt - 1) * step[k] + 1;
-                    const int nhi = lo[k] + cnt * step[k];
-                    lo[k] = nlo;
-                    hi[k] = nhi < hi[k] ? nhi : hi[k];
-                }
-            }
-        }
-    }
-    ra = uniform(lo[0]);
-    rb = uniform(lo[1]);
-}
-
 // SERIAL_SCAN (a comparison kernel for Section 2.1.1, not used by the library's own choices): the lanes' open-row
 // partial sums meet through a serial segmented prefix sum - they are put into LDS and one lane adds them up in
 // lane order, starting afresh at every lane that holds a row boundary - instead of the DPP network.  Everything
 // else, the balanced split included, is the same, so the difference in time is the vectorized reduction's.
-template <int V, int KQ, bool AXPBY = false, bool SERIAL_SCAN = false>
+template <int V, int KQ, bool SNAP, bool AXPBY = false, bool SERIAL_SCAN = false>
 __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
@@ -955,12 +981,15 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
     int is, ie1;
     wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
-    const unsigned js0 = d0 - (unsigned)is;
-    const unsigned je1 = d1 - (unsigned)ie1;
+    unsigned js0 = d0 - (unsigned)is, je1 = d1 - (unsigned)ie1;
+    if constexpr (SNAP) {
+        snap_to_rows(rowptr, M, d0, d1, is, ie1, js0, je1);
+        if (is == ie1) continue;
+    }
     unsigned js = js0;
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
     const int r_first = is;
-    const bool first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
+    const bool first_split = !SNAP && is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
 
     // entries of block k of my chunk (lane l: entries 64 e + l of the block); nothing past the chunk's last entry
     // One descriptor pair for the whole chunk (a wave's share of a matrix the library takes stays far below the
@@ -1650,11 +1679,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
     unsigned js, je;
     bool first_split = false;
     if (snap) {
-        // rows that started before a chunk's first item belong to the chunk before
-        if (is < M && (unsigned)is + (unsigned)rowptr[is] < d0) ++is;
-        if (ie < M && (unsigned)ie + (unsigned)rowptr[ie] < d1) ++ie;
-        js = (unsigned)rowptr[is];
-        je = (unsigned)rowptr[ie];
+        snap_to_rows(rowptr, M, d0, d1, is, ie, js, je);
     } else {
         js = d0 - (unsigned)is;
         je = d1 - (unsigned)ie;

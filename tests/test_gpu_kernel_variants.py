@@ -42,7 +42,10 @@ def _compare(dg, A, N, algo, features, alpha=None, beta=0.0, poison_row=None):
     dY = torch.from_numpy(Y0).cuda()
     f = dA.features if features else None
     print(f"[case] {A.name} M={A.M} nnz={A.nnz} N={N} algo={algo} features={features} alpha={alpha} beta={beta}", flush=True)
-    if alpha is None:
+    if algo == dg.AUTO and alpha is None:
+        dY.fill_(float("nan"))
+        dg.dgsp_spmm_csr_ld(A.M, A.K, N, A.nnz, dA.rowptr, dA.colidx, dA.vals, dX, dY, algo, f)
+    elif alpha is None:
         dY.fill_(float("nan"))
         dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz if features else -1, dA.rowptr, dA.colidx, dA.vals, dX, dY, algo, dg.PHASE_ALL, f)
     else:
@@ -86,11 +89,32 @@ ROW_GROUPS = {                                        # rows alike: what the row
 @pytest.mark.parametrize("lens, N", [(name, n) for name in sorted(ROW_GROUPS) for n in (1, 2, 3, 4, 6, 7, 16, 33, 130)
                                      if n <= 16 or ROW_GROUPS[name][1] < 10000])
 def test_row_groups(dg, lens, N):
-    """Row groups with one and with several lanes on a row's entries, reached by name and in place of both parallel kernels."""
+    """Row groups with one and with several lanes on a row's entries, by name and as the library's choice."""
     rows, K = ROW_GROUPS[lens]
     A = wl.csr_from_lens(rows, K=K, seed=N, name=lens)
     free = np.setdiff1d(np.arange(A.K), A.colidx)
-    for algo in (dg.RS_SR, dg.RS_PR, dg.NB_PR) if N <= 4 else (dg.RS_SR,):
+    for algo in (dg.RS_SR, dg.AUTO):
         for features in (True, False):
             _compare(dg, A, N, algo, features, poison_row=int(free[0]) if free.size else None)
         _compare(dg, A, N, algo, True, alpha=-0.5, beta=1.5)
+
+
+@pytest.mark.parametrize("N", [1, 3, 4, 8, 16, 33, 100])
+@pytest.mark.parametrize("law", ["lognormal", "zipf"])
+def test_small_uneven_matrices(dg, law, N):
+    """The library's choice on small matrices with uneven rows: many lanes on a row's entries."""
+    for rows, mean in ((4096, 8), (9001, 20), (30011, 5)):
+        A = wl.sweep_csr(rows, mean, law, seed=N)
+        _compare(dg, A, N, dg.AUTO, True)
+        _compare(dg, A, N, dg.AUTO, True, alpha=-0.5, beta=1.5)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 9])
+@pytest.mark.parametrize("lens", sorted(LENS))
+def test_balanced_parallel_tiles_and_blocks(dg, lens, N):
+    """The balanced parallel kernels on uneven rows: kept whole (statistics given) and shared between waves."""
+    A = wl.csr_from_lens(LENS[lens], K=4000, seed=N, name=lens)
+    free = np.setdiff1d(np.arange(A.K), A.colidx)
+    for features in (True, False):
+        _compare(dg, A, N, dg.NB_PR, features, poison_row=int(free[0]) if free.size else None)
+        _compare(dg, A, N, dg.NB_PR, features, alpha=-0.5, beta=1.5)

@@ -563,7 +563,9 @@ template <int LOGG, bool XBUF>
 int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     const unsigned col_blocks = cols.blocks;
     if (col_blocks > 65535u) return DGSP_ERR_INVALID_ARG;
-    dim3 grid(balanced_blocks(p, kRunItems, resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, false>), false, col_blocks), col_blocks);
+    const int resident = p.scaled ? resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, true>)
+                                  : resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, false>);
+    dim3 grid(balanced_blocks(p, kRunItems, resident, false, col_blocks), col_blocks);
     // Two or four column blocks of a wide X: every XCD works on one block only, so that an L2 sees one block's slice of X
     // and the slices do not compete.  With eight blocks every XCD would walk the whole matrix alone (10-20 % slower): from
     // there on the blocks stay a second grid dimension.  DGSP_ABL_BLOCKS_OFF_XCDS: the comparison.

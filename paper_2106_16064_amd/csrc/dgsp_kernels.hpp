@@ -231,6 +231,12 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
         float acc[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+        float old[AXPBY ? V : 1];                            // scaled form: on its way while the row is summed
+        if constexpr (AXPBY) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) old[i] = 0.0f;
+            if (live && col_ok && h == 0 && sc.beta != 0.0f) load_vec_dword_aligned<V>(Y + (size_t)row * ldy + n, old);
+        }
 
         for (unsigned ws = ps; ws < pe; ws += (unsigned)T) {
             wave_lds_sync();                    // last round's readers are done
@@ -301,7 +307,10 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
             for (int i = 0; i < V; ++i) acc[i] += __shfl_xor(acc[i], m);
         if (live && col_ok && h == 0) {
             float* y = Y + (size_t)row * ldy + n;
-            if constexpr (AXPBY) scale_into<V, true>(acc, y, sc);
+            if constexpr (AXPBY) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) acc[i] = sc.beta != 0.0f ? fmaf(sc.alpha, acc[i], sc.beta * old[i]) : sc.alpha * acc[i];
+            }
             if (AXPBY && RAGGED && mine.skip != 0) {
                 // the scaled result depends on the old Y, which the neighbour (another column block, another time)
                 // may have replaced: the shared columns are the neighbour's to write
@@ -420,8 +429,7 @@ struct EvenSplit {
 // The pieces are the `parts` chunks of the even split with quanta of
 // 2^quantum_log2 items, cut further into tiles of 2^tile_log2 items counted
 // from the chunk's start when tile_log2 >= 0.
-// One thread per row for the test (split rows are few: at most two per piece);
-// a wave then clears its split rows together, 64 columns per store.
+// One thread per row for the test (split rows are few: at most two per piece).
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
                                                              int tile_log2, float beta) {
@@ -449,15 +457,35 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
         }
         return;
     }
-    // the wave zeroes its split rows together: lane l clears columns l, l + 64, ...
-    const int lane = lane_id();
-    const long long row0 = row - lane;
-    unsigned long long todo = __ballot(split);
-    while (todo) {                                                           // wave-uniform
-        const int src = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        float* y = Y + (size_t)(row0 + src) * ldy;
-        for (int n = lane; n < N; n += kWave) y[n] = beta != 0.0f ? beta * y[n] : 0.0f;
+    // The workgroup treats its split rows together: they are listed, a wave takes every fourth, eight at a time with a lane
+    // per column, so that the loads of the scaled form are in flight together.  (The long rows of a graph are neighbours and
+    // all split: one row after the other in one wave took R-MAT 2^18 x 13 at N = 58 100 of 206 us.)
+    __shared__ int s_rows[kBlock];
+    __shared__ int s_count[kWavesPerBlock];
+    const int lane = lane_id(), wib = wave_in_block();
+    const unsigned long long mine = __ballot(split);
+    if (lane == 0) s_count[wib] = (int)__popcll(mine);
+    __syncthreads();
+    int before = 0, count = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) { before += w < wib ? s_count[w] : 0; count += s_count[w]; }
+    if (split) s_rows[before + (int)__popcll(mine & ((1ull << lane) - 1ull))] = (int)row;
+    __syncthreads();
+    constexpr int U = 8;
+    for (int r = wib; r < count; r += kWavesPerBlock * U) {                  // wave-uniform
+        for (int n = lane; n < N; n += kWave) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int at = r + u * kWavesPerBlock;
+                v[u] = (beta != 0.0f && at < count) ? Y[(size_t)s_rows[at] * ldy + n] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int at = r + u * kWavesPerBlock;
+                if (at < count) Y[(size_t)s_rows[at] * ldy + n] = beta != 0.0f ? beta * v[u] : 0.0f;
+            }
+        }
     }
 }
 
@@ -708,6 +736,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     // the memory pipeline retires loads and stores in issue order, so a store in front of the gathers would put
     // its own round trip into their wait.
     float pending_val[V];
+    float pending_old[AXPBY ? V : 1];                    // scaled form: what the rows held, requested when their sums were ready
     unsigned pending_off = kOutOfRange;
     unsigned long long pending_first = 0ull;             // first element of the rows the pending store addresses
 #pragma unroll
@@ -718,6 +747,11 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                                                  kBufferFlags);
     };
     auto store_pending = [&]() {
+        if constexpr (AXPBY) {
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                pending_val[i] = sc.beta != 0.0f ? fmaf(sc.alpha, pending_val[i], sc.beta * pending_old[i]) : sc.alpha * pending_val[i];
+        }
         buffer_store_vec<V>(rows_descriptor(pending_first), pending_off, pending_val, second);
         pending_off = kOutOfRange;
     };
@@ -863,25 +897,43 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                 const bool live = t < nrows;
                 const bool shared = first_split && is + t == r_first;   // finished by an atomic add instead
                 const unsigned off = (live && !shared) ? (unsigned)t * (unsigned)ldy * 4u : kOutOfRange;
-                if constexpr (AXPBY) {
-                    if (live && shared) {
-#pragma unroll
-                        for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // lands on beta * Y (prepare)
-                    } else {
-                        scale_into<V>(val, yrows, off, sc, second);
-                    }
-                }
                 if (k == 0) {
                     pending_first = first_elem; pending_off = off;
 #pragma unroll
                     for (int i = 0; i < V; ++i) pending_val[i] = val[i];
+                    if constexpr (AXPBY) { if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off, pending_old, second); }
                 } else {
-                    buffer_store_vec<V>(yrows, off, val, second);
+                    buffer_store_vec<V>(yrows, off, val, second);            // plain form only
+                }
+                if constexpr (AXPBY) {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // an added sum lands on beta * Y (prepare)
                 }
                 if (live && shared) add_to_row(Y + (size_t)(is + t) * ldy + n0, val);
             };
             write_rows(0);
-            for (int k = 1; k * kWave < nrows; ++k) write_rows(k);
+            if constexpr (AXPBY) {
+                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile)
+                constexpr int F = V <= 2 ? 4 : 2;
+                for (int k = 1; k * kWave < nrows; k += F) {
+                    float val[F][V], old[F][V]; unsigned off[F];
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+                        const int t = (k + u) * kWave + lane;
+                        off[u] = t < nrows ? (unsigned)t * (unsigned)ldy * 4u : kOutOfRange;
+                        if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off[u], old[u], second);
+                        load_vec<V>(buf + (size_t)(t < W ? t : 0) * V, val[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+#pragma unroll
+                        for (int i = 0; i < V; ++i) val[u][i] = sc.beta != 0.0f ? fmaf(sc.alpha, val[u][i], sc.beta * old[u][i]) : sc.alpha * val[u][i];
+                        buffer_store_vec<V>(yrows, off[u], val[u], second);
+                    }
+                }
+            } else {
+                for (int k = 1; k * kWave < nrows; ++k) write_rows(k);
+            }
         }
 
         is = ie;
@@ -1053,6 +1105,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     // The first 64 row results of a step are stored one step later, behind the loads issued meanwhile (the memory
     // pipeline retires loads and stores in issue order: a store in front of the gathers adds its round trip to their wait).
     float pending_val[V];
+    float pending_old[AXPBY ? V : 1];                    // scaled form: what the rows held, requested when their sums were ready
     unsigned pending_off = kOutOfRange;
     unsigned long long pending_first = 0ull;             // first element of the rows the pending store addresses
 #pragma unroll
@@ -1063,6 +1116,11 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
                                                  kBufferFlags);
     };
     auto store_pending = [&]() {
+        if constexpr (AXPBY) {
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                pending_val[i] = sc.beta != 0.0f ? fmaf(sc.alpha, pending_val[i], sc.beta * pending_old[i]) : sc.alpha * pending_val[i];
+        }
         buffer_store_vec<V>(rows_descriptor(pending_first), pending_off, pending_val, second);
         pending_off = kOutOfRange;
     };
@@ -1224,25 +1282,43 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
                 const bool live = t < nrows;
                 const bool shared = first_split && is + t == r_first;   // finished by an atomic add instead
                 const unsigned off = (live && !shared) ? (unsigned)t * (unsigned)ldy * 4u : kOutOfRange;
-                if constexpr (AXPBY) {
-                    if (live && shared) {
-#pragma unroll
-                        for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // lands on beta * Y (prepare)
-                    } else {
-                        scale_into<V>(val, yrows, off, sc, second);
-                    }
-                }
                 if (k == 0) {
                     pending_first = first_elem; pending_off = off;
 #pragma unroll
                     for (int i = 0; i < V; ++i) pending_val[i] = val[i];
+                    if constexpr (AXPBY) { if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off, pending_old, second); }
                 } else {
-                    buffer_store_vec<V>(yrows, off, val, second);
+                    buffer_store_vec<V>(yrows, off, val, second);            // plain form only
+                }
+                if constexpr (AXPBY) {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // an added sum lands on beta * Y (prepare)
                 }
                 if (live && shared) add_to_row(Y + (size_t)(is + t) * ldy + n0, val);
             };
             write_rows(0);
-            for (int k = 1; k * kWave < nrows; ++k) write_rows(k);
+            if constexpr (AXPBY) {
+                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile)
+                constexpr int F = V <= 2 ? 4 : 2;
+                for (int k = 1; k * kWave < nrows; k += F) {
+                    float val[F][V], old[F][V]; unsigned off[F];
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+                        const int t = (k + u) * kWave + lane;
+                        off[u] = t < nrows ? (unsigned)t * (unsigned)ldy * 4u : kOutOfRange;
+                        if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off[u], old[u], second);
+                        load_vec<V>(buf + (size_t)(t < W ? t : 0) * V, val[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+#pragma unroll
+                        for (int i = 0; i < V; ++i) val[u][i] = sc.beta != 0.0f ? fmaf(sc.alpha, val[u][i], sc.beta * old[u][i]) : sc.alpha * val[u][i];
+                        buffer_store_vec<V>(yrows, off[u], val[u], second);
+                    }
+                }
+            } else {
+                for (int k = 1; k * kWave < nrows; ++k) write_rows(k);
+            }
         }
         is = ie;
         js = je;
@@ -1723,18 +1799,24 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
         f4u t = {v[0], v[1], v[2], v[3]};
         __builtin_nontemporal_store(t, reinterpret_cast<f4u*>(y));
     };
+    // stores of the scaled form: the columns I share with my neighbour are the neighbour's
+    auto store_own = [&](float* y, const float (&v)[4]) {
+        if (mine.skip != 0) {
+#pragma unroll
+            for (int i = 1; i < 4; ++i) if (i >= mine.skip) y[i] = v[i];
+        } else {
+            store4(y, v);
+        }
+    };
     // a finished row's four columns of my lane
     auto write_row = [&](int row, const float (&v)[4]) {
         float* y = y_at(row);
         if constexpr (AXPBY) {
-            float o[4] = {v[0], v[1], v[2], v[3]};
-            scale_into<4, true>(o, y, sc);
-            if (mine.skip != 0) {
+            float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (sc.beta != 0.0f) load_vec_dword_aligned<4>(y, o);
 #pragma unroll
-                for (int i = 1; i < 4; ++i) if (i >= mine.skip) y[i] = o[i];
-            } else {
-                store4(y, o);
-            }
+            for (int i = 0; i < 4; ++i) o[i] = sc.beta != 0.0f ? fmaf(sc.alpha, v[i], sc.beta * o[i]) : sc.alpha * v[i];
+            store_own(y, o);
         } else {
             store4(y, v);
         }
@@ -1783,11 +1865,30 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
             }
             listed += (int)__popcll(m_has);
             if (m_zero != 0ull) {
-                float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };      // R rows per round
+                if constexpr (AXPBY) {
+                    constexpr int F = G < 4 ? G : 4;        // rounds whose old values are in flight together
 #pragma unroll 1
-                for (int q = 0; q < G; ++q) {               // R rows per round
-                    const int t = q * R + g;
-                    if (((m_zero >> t) & 1ull) != 0ull && col_ok) write_row(is + t, zero);
+                    for (int q = 0; q < G; q += F) {
+                        float v[F][4];
+#pragma unroll
+                        for (int u = 0; u < F; ++u) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[u][i] = 0.0f;
+                            if (empty(q + u) && sc.beta != 0.0f) load_vec_dword_aligned<4>(y_at(is + (q + u) * R + g), v[u]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < F; ++u) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[u][i] = sc.beta != 0.0f ? sc.beta * v[u][i] : 0.0f;
+                            if (empty(q + u)) store_own(y_at(is + (q + u) * R + g), v[u]);
+                        }
+                    }
+                } else {
+                    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+                    for (int q = 0; q < G; ++q)
+                        if (empty(q)) write_row(is + q * R + g, zero);
                 }
             }
             is += cnt;

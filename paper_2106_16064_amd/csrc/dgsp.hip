@@ -70,6 +70,7 @@ struct Hints {
     double col_span = 0.0;
     double cv_row = -1.0;
     int64_t max_row = -1;
+    int64_t size = -1;          // a bound of the entry count
     bool chosen = false;        // the kernel is the library's choice from these statistics, not the caller's
     Hints() = default;
     explicit Hints(const dgsp_features_t* f) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
@@ -85,6 +86,7 @@ struct Problem {
     double col_span = 0.0;   // mean column span of a row / K; 0 = unknown
     double cv_row = -1.0;    // coefficient of variation of the row lengths; < 0 = unknown
     long long max_row = -1;  // entries of the longest row; < 0 = unknown
+    long long size = -1;     // the entry count or, for launch geometry, a bound of it; < 0 = unknown
     int switches = 0;        // DGSP_ABL_* (measurement aids)
     bool scaled = false;     // Y = alpha * A X + beta * Y instead of Y = A X
     float alpha = 1.0f, beta = 0.0f;
@@ -418,9 +420,9 @@ inline unsigned balanced_blocks(const Problem& p, long long tile, int blocks_per
                                 long long col_blocks = 1, long long parallel_per_cu_max = 0) {
     const long long cus = device_info().cus;
     const long long cap = cus * blocks_per_cu;
-    // entry count unknown on the host (the 10-argument call): what serves large matrices best
-    if (p.nnz < 0) return (unsigned)(parallel && blocks_per_cu > 2 ? cus * 2 : cap);
-    const long long tiles = (p.nnz + p.M + tile - 1) / tile;
+    const long long tiles = p.size >= 0 ? (p.size + p.M + tile - 1) / tile : cap * kWavesPerBlock;
+    // entry count unknown on the host and the matrix not known to be small: what serves large matrices best
+    if (p.nnz < 0 && tiles > cus * kWavesPerBlock) return (unsigned)(parallel && blocks_per_cu > 2 ? cus * 2 : cap);
     const long long waves = cus * kWavesPerBlock;
     if (tiles <= waves) return clamp_blocks((tiles + kWavesPerBlock - 1) / kWavesPerBlock, cap);
     long long per_cu;
@@ -698,7 +700,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     if (hints.chosen && algo != DGSP_RS_SR && row_groups_suit(p)) algo = DGSP_RS_SR;
     switch (algo) {
@@ -716,6 +718,13 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
 extern "C" int dgsp_spmm_csr(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int32_t* colidx,
                              const float* vals, const float* X, float* Y, int algo, void* stream) {
     return run(M, K, N, -1, rowptr, colidx, vals, X, Y, algo, stream);
+}
+
+extern "C" int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t capacity, const int32_t* rowptr, const int32_t* colidx,
+                                      const float* vals, const float* X, float* Y, int algo, void* stream) {
+    Hints hints;
+    hints.size = capacity;
+    return run(M, K, N, -1, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
 }
 
 extern "C" int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,

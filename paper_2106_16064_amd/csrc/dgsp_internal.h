@@ -14,6 +14,10 @@ extern "C" {
 int dgsp_internal_take_csr(int64_t M, int64_t K, int64_t entries, int index_bytes, const void *rowptr, const void *colidx,
                            int32_t *rowptr32, int32_t *colidx32, dgsp_features_t *out, void *stream);
 
+/* dgsp_spmm_csr with the length of colidx, which bounds the entry count and sizes the launches. */
+int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t capacity, const int32_t *rowptr, const int32_t *colidx,
+                           const float *vals, const float *X, float *Y, int algo, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -364,7 +364,7 @@ PyObject* spmm_csr(PyObject* const* a, Py_ssize_t n) {
     auto* y = static_cast<float*>(ptr(Y));
     const int rc = unlocked([&] {
         return counted ? dgsp_spmm_csr_nnz(M, K, N, nnz, rp, ci, av, x, y, algo, stream)
-                       : dgsp_spmm_csr(M, K, N, rp, ci, av, x, y, algo, stream);
+                       : dgsp_internal_spmm_csr(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, stream);
     });
     check_status(rc, counted ? "dgsp_spmm_csr_nnz" : "dgsp_spmm_csr");
     Py_RETURN_NONE;

@@ -62,7 +62,7 @@ def build_torch_binding(verbose: bool = True) -> Path:
            *(f"-isystem{d}" for d in (top / "include", top / "include/torch/csrc/api/include", f"{rocm}/include",
                                       sysconfig.get_paths()["include"])),
            "-o", str(TORCH_LIB), str(TORCH_SOURCE), f"-L{HERE}", "-ldgsp", f"-L{top / 'lib'}", "-ltorch_python", "-ltorch",
-           "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+           "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)

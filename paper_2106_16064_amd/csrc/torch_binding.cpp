@@ -10,6 +10,7 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
@@ -148,10 +149,13 @@ int product(int64_t M, int64_t K, int64_t N, const dgsp_features_t* f, const at:
     return dgsp_spmm_csr_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f, stream);
 }
 
-// M x N, or M elements when the dense operand is a vector
+// M x N, or M elements when the dense operand is a vector.  A GPU tensor comes from the allocator directly: the dispatcher's
+// way there is 0.3 us of a 4.5 us call.
 at::Tensor empty_result(int64_t M, int64_t N, bool vector, const at::Tensor& like) {
-    const auto options = at::TensorOptions().dtype(at::kFloat).device(like.device());
-    return vector ? at::empty({M}, options) : at::empty({M, N}, options);
+    const int64_t sizes[2] = {M, N};
+    const at::IntArrayRef shape(sizes, vector ? 1 : 2);
+    if (!like.device().is_cuda()) return at::empty(shape, at::TensorOptions().dtype(at::kFloat).device(like.device()));
+    return at::Tensor(at::detail::empty_cuda(shape, at::kFloat, like.device(), std::nullopt));
 }
 
 int64_t columns_of(const at::Tensor& X) { return X.dim() == 2 ? X.size(1) : 1; }

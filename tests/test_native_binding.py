@@ -66,7 +66,16 @@ STATS = {
     "empty_rows_around": [0] * 3000 + [7] + [0] * 3000,
     "no_entries": [0] * 300,
     "many_blocks": [3, 1, 0, 8] * 160000,
+    "one_block_each": [2048] * 7,
+    "long_and_empty": [1500000] + [0] * 900000 + [1] * 700000,
 }
+
+
+def _columns_by_position(lens):
+    """Rows of any length whose columns ascend in steps of two."""
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colidx = (np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lens)).astype(np.int32) * 2
+    return wl.CsrMatrix(len(lens), 2 * max(lens), rowptr, colidx, np.ones(rowptr[-1], dtype=np.float32), "by_position", {})
 
 
 @pytest.mark.gpu
@@ -75,7 +84,11 @@ STATS = {
 def test_statistics_and_index_types(name, order):
     """Statistics of device arrays and the 32-bit copies of int64 ones, at the edges of the pieces the entries are counted in."""
     import torch
-    A = wl.csr_from_lens(STATS[name], K=6000, seed=3, name=name)
+    lens = STATS[name]
+    if max(lens) > 6000:
+        A = _columns_by_position(lens)
+    else:
+        A = wl.csr_from_lens(lens, K=6000, seed=3, name=name)
     colidx = A.colidx.copy()
     rng = np.random.default_rng(1)
     longest = int(np.argmax(A.row_lengths()))

@@ -298,6 +298,14 @@ def measure_cell(name, n, steps, warmup, full_parity=False):
                             lambda i: rot.phase(i, chosen, dg.PHASE_MAIN), rot.copies, batches,
                             max(1, warmup // rot.copies))
     ev_ms = sum(ev) / len(ev)
+    timed_as = sel
+    if ms_cold < 0.95 * ev_ms:
+        # the adaptive call ran row groups (rs_sr, one launch) in place of the kernel the rules name: that launch is timed
+        none = dg.PHASE_PREPARE
+        ev = time_event_batches(lambda i: rot.phase(i, dg.RS_SR, none), lambda i: rot.phase(i, dg.RS_SR, dg.PHASE_MAIN),
+                                rot.copies, batches, max(1, warmup // rot.copies))
+        ev_ms = sum(ev) / len(ev)
+        timed_as = dg.dgsp_algo_name(dg.RS_SR)
     floors = floor_probes(rot)
     rot.step(0, dg.AUTO)
     torch.cuda.synchronize()
@@ -311,7 +319,7 @@ def measure_cell(name, n, steps, warmup, full_parity=False):
         parity = sampled_parity(A, X, Y)
     bytes_alg = algorithmic_bytes(A, n)
     achieved = bytes_alg / (ev_ms * 1e-3) / 1e9
-    traffic, source = MEASURED_TRAFFIC.get(f"{sel}/{name}/N{n}", (None, None))
+    traffic, source = MEASURED_TRAFFIC.get(f"{timed_as}/{name}/N{n}", (None, None))
     cell = {
         "workload": label, "M": A.M, "K": A.K, "nnz": A.nnz, "N": n, "buffer_rotation": rot.copies,
         "selected_kernel": sel, "ms_per_step": ms_cold,
@@ -320,7 +328,7 @@ def measure_cell(name, n, steps, warmup, full_parity=False):
         "pct_hbm_peak": 100.0 * bytes_alg / (ms_cold * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
-                     "kernel": f"dgsp::{sel}_kernel (main launch alone; HIP events on the launch stream around "
+                     "kernel": f"dgsp::{timed_as}_kernel (main launch alone; HIP events on the launch stream around "
                                f"{len(ev)} batches of {rot.copies} back-to-back launches, one per buffer set)",
                      "algorithmic_bytes": bytes_alg, "launch_ms": ev_ms, "floors_ms": floors},
         "parity": parity,

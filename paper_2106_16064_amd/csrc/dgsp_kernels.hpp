@@ -1741,7 +1741,13 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
         wg = (x / pinned_blocks) * per_xcd + i;
         nwg = (kXcd / pinned_blocks) * per_xcd;
     } else {
-        wg = xcd_contiguous(blockIdx.x, gridDim.x);
+        // Neighbouring chunks on one XCD share lines of A and Y - but where rows have few entries what an item costs changes
+        // along the list (row ends and empty rows at the sparse end of a graph), and an XCD with the dear part ends last
+        // (R-MAT 2^20 x 6, contiguous against dealt out one by one: N = 32 112 or 128 / 113 us, N = 101 420 or 470 / 383 us, the
+        // longer of the two on the hardware queue a process gets first; 2^20 x 8 at N = 32 138 / 143, at N = 101 503 / 478 us,
+        // 2^20 x 16 at N = 32 252 / 260 us).
+        const unsigned per_row = (unsigned)rowptr[M] / (unsigned)M;
+        wg = per_row < (LOGG >= 5 ? 8u : 6u) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
     }
     const LaneColumns mine = lane_columns<4, true>(col_block, cols_per_block, gl, N);

@@ -54,11 +54,11 @@ _TRAFFIC_SOURCE = "profiles/selected_kernels_time_traffic_occupancy.md (rocprofv
 MEASURED_TRAFFIC = {
     # "kernel/workload/N": (bytes fetched + bytes written per launch of the main kernel, source)
     "nb_pr/rmat_spmv/N1": (169.3e6 + 5.1e6, _TRAFFIC_SOURCE),
-    "nb_sr/rmat_gnn/N128": (5376.8e6 + 644.3e6, _TRAFFIC_SOURCE),
-    "nb_sr/rmat_gnn/N32": (1147.9e6 + 161.1e6, _TRAFFIC_SOURCE),
-    "nb_pr/stencil/N1": (505.6e6 + 8.7e6, _TRAFFIC_SOURCE),
-    "rs_sr/stencil/N8": (619.6e6 + 67.1e6, _TRAFFIC_SOURCE),
-    "rs_pr/uniform64/N4": (272.7e6 + 5.2e6, _TRAFFIC_SOURCE),
+    "nb_sr/rmat_gnn/N128": (4815.7e6 + 550.1e6, _TRAFFIC_SOURCE),
+    "nb_sr/rmat_gnn/N32": (1121.6e6 + 137.5e6, _TRAFFIC_SOURCE),
+    "rs_sr/stencil/N1": (497.2e6 + 8.4e6, _TRAFFIC_SOURCE),
+    "rs_sr/stencil/N8": (621.0e6 + 67.1e6, _TRAFFIC_SOURCE),
+    "rs_sr/uniform64/N4": (268.1e6 + 4.2e6, _TRAFFIC_SOURCE),
 }
 
 

@@ -10,6 +10,8 @@ The stored values of A get no gradient.
 """
 from __future__ import annotations
 
+import functools
+
 import numpy as np
 
 from . import binding as dg
@@ -57,8 +59,29 @@ class SparseOperator:
         """``A X``; the gradient's product picks its own kernel (the rules for A^T, or what ``autotune`` found)."""
         A, T = self.fwd, self.bwd
         N = X.shape[1] if X.dim() == 2 else 1
-        if algo == dg.AUTO:
-            algo = A.tuned.get(N, dg.AUTO)
-        return dg.native().multiply_differentiable(
-            X, algo, T.tuned.get(N, dg.AUTO), A.M, A.K, A.features, A.rowptr, A.colidx, A.vals,
-            T.M, T.K, T.features, T.rowptr, T.colidx, T.vals)
+        Y = dg.native().multiply_differentiable(
+            X, A.tuned.get(N, dg.AUTO) if algo == dg.AUTO else algo, T.tuned.get(N, dg.AUTO),
+            A.M, A.K, A.features, A.rowptr, A.colidx, A.vals, T.M, T.K, T.features, T.rowptr, T.colidx, T.vals)
+        return _function().apply(X, self, algo) if Y is None else Y
+
+
+@functools.lru_cache(maxsize=None)
+def _function():
+    """The product as a ``torch.autograd.Function``, for calls that the native graph node does not serve because more than
+    reverse mode looks at them: PyTorch records them when it traces and refuses those it cannot differentiate (a tangent on
+    X, a function transform).  Made on first use: importing this module does not load torch."""
+    import torch
+
+    class SpMM(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, X, op, algo):
+            ctx.op, ctx.vector = op, X.dim() == 1
+            Y = op.fwd.spmm(X.float().contiguous(), algo=algo)
+            return Y.squeeze(1) if ctx.vector else Y
+
+        @staticmethod
+        def backward(ctx, dY):
+            dX = ctx.op.bwd.spmm(dY.float().contiguous())
+            return (dX.squeeze(1) if ctx.vector else dX), None, None
+
+    return SpMM

@@ -11,12 +11,15 @@
 
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/grad_mode.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 
 #include <cstring>
 #include <string>
@@ -276,10 +279,23 @@ PyObject* multiply_new(PyObject* const* a, Py_ssize_t n) {
     return THPVariable_Wrap(multiply(A, X, (int)as_int(a[7]), false));
 }
 
-// (X, algo, bwd_algo, fwd M, K, features, rowptr, colidx, vals, bwd M, K, features, rowptr, colidx, vals) -> Y with a graph node
+// Does nothing but reverse mode look at a product of X?  Not so under a tangent on X (forward mode), a function transform
+// (vmap, grad, jvp), a trace that is being recorded, or Python code that intercepts operations: a graph node of our own
+// would pass by them and return a result without tangent, batch or record.
+bool only_reverse_mode(const at::Tensor& X) {
+    const auto included = c10::impl::tls_local_dispatch_key_set().included_;
+    return !X._fw_grad(/*level=*/0).defined() && !X.unsafeGetTensorImpl()->is_python_dispatch() &&
+           !included.has(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) &&
+           !included.has(c10::DispatchKey::FuncTorchDynamicLayerBackMode) && !torch::jit::tracer::isTracing() &&
+           !c10::impl::TorchDispatchModeTLS::any_modes_set();
+}
+
+// (X, algo, bwd_algo, fwd M, K, features, rowptr, colidx, vals, bwd M, K, features, rowptr, colidx, vals) -> Y with a graph node;
+// None: the caller takes the way through autograd's own Function
 PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
     want(n, 15);
     const at::Tensor& X = as_tensor(a[0], "X");
+    if (!only_reverse_mode(X)) Py_RETURN_NONE;
     const Csr A(a + 5, as_int(a[3]), as_int(a[4]));
     const bool vector = X.dim() == 1;
     at::Tensor Y;

@@ -59,6 +59,101 @@ def test_gradient_of_other_types_and_layouts(dtype, N):
     assert ok, worst
 
 
+class _DenseMatrix:
+    """Stands in for a ``DeviceCsr`` on the CPU, where the native product cannot run."""
+
+    def __init__(self, D):
+        self.D, self.tuned = D, {}
+        self.M, self.K = D.shape
+        self.features = self.rowptr = self.colidx = self.vals = None
+
+    def spmm(self, X, algo=dg.AUTO):
+        return self.D @ (X if X.dim() == 2 else X[:, None])
+
+
+def _operator(device):
+    """(operator, its dense matrix): a stand-in on the CPU, the real one on the GPU."""
+    import torch
+    from paper_2106_16064_amd.autograd import SparseOperator
+    A = wl.sweep_csr(60, 5, "poisson", seed=2)
+    D = torch.zeros(A.M, A.K)
+    D.index_put_((torch.from_numpy(np.repeat(np.arange(A.M), A.row_lengths())), torch.from_numpy(A.colidx).long()),
+                 torch.from_numpy(A.vals), accumulate=True)
+    if device == "cuda":
+        return SparseOperator(A), D.cuda()
+    op = SparseOperator.__new__(SparseOperator)
+    op.fwd, op.bwd = _DenseMatrix(D), _DenseMatrix(D.t().contiguous())
+    return op, D
+
+
+DEVICES = ["cpu", pytest.param("cuda", marks=pytest.mark.gpu)]
+
+
+@pytest.mark.parametrize("device", DEVICES)
+@pytest.mark.parametrize("requires_grad", [False, True])
+def test_a_tangent_on_the_operand_is_refused(device, requires_grad):
+    """Forward mode is not implemented: a product without its tangent would read as a derivative of zero."""
+    import torch
+    from torch.autograd import forward_ad
+    op, D = _operator(device)
+    X = torch.randn(D.shape[1], 3, device=device, requires_grad=requires_grad)
+    with forward_ad.dual_level():
+        with pytest.raises(NotImplementedError):
+            op(forward_ad.make_dual(X, torch.ones_like(X)))
+
+
+@pytest.mark.parametrize("device", DEVICES)
+@pytest.mark.parametrize("transform", ["vmap", "grad", "jvp"])
+def test_function_transforms_are_refused(device, transform):
+    import torch
+    op, D = _operator(device)
+    X = torch.randn(D.shape[1], 3, device=device)
+    call = {"vmap": lambda: torch.func.vmap(op)(torch.stack([X, X])),
+            "grad": lambda: torch.func.grad(lambda x: op(x).sum())(X),
+            "jvp": lambda: torch.func.jvp(op, (X,), (X,))}[transform]
+    with pytest.raises(RuntimeError, match="setup_context"):
+        call()
+
+
+@pytest.mark.parametrize("device", DEVICES)
+def test_a_traced_product_follows_its_input(device):
+    """A recorded product is computed again on every input, inside other operations, with its gradient."""
+    import torch
+    op, D = _operator(device)
+    X = torch.randn(D.shape[1], 3, device=device)
+    traced = torch.jit.trace(lambda x: op(x * 2.0).relu(), X, check_trace=False)
+    for scale in (1.0, -3.0):
+        x = (X * scale + 1.0).requires_grad_(True)
+        y = traced(x)
+        want = (D @ (2.0 * x)).relu()
+        assert torch.allclose(y, want, rtol=1e-5, atol=1e-5)
+        dx, = torch.autograd.grad(y.sum(), x)
+        want_dx, = torch.autograd.grad(want.sum(), x)
+        assert torch.allclose(dx, want_dx, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("device", DEVICES)
+def test_a_mode_that_intercepts_operations_sees_the_product(device):
+    import torch
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Names(TorchDispatchMode):
+        seen = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.seen.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    op, D = _operator(device)
+    X = torch.randn(D.shape[1], 3, dtype=torch.float64, device=device, requires_grad=True)
+    with Names() as mode:
+        y = op(X)
+    assert any("_to_copy" in name for name in mode.seen)
+    y.sum().backward()
+    assert torch.allclose(y, (D.double() @ X).float(), rtol=1e-5, atol=1e-5)
+    assert torch.allclose(X.grad, D.double().sum(0)[:, None].expand_as(X), rtol=1e-5, atol=1e-5)
+
+
 STATS = {
     "chunk_edges": [2047, 1, 2048, 2049, 0, 1, 2046, 2, 0, 0],
     "one_row": [5000],

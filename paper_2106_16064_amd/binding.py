@@ -373,7 +373,8 @@ class DeviceCsr:
     @classmethod
     def from_device(cls, M, K, rowptr, colidx, vals):
         """Wraps CSR arrays that already live on the GPU (int32 ``rowptr`` / ``colidx``, float32 ``vals``; other
-        integer or float types are converted once).  The row statistics are computed on the device."""
+        integer or float types are converted once).  The row statistics are computed on the device, from work on the
+        current stream that the call waits for: the matrix can be used on any stream once it returns."""
         f = Features()
         return cls._taken((_native or native()).csr_from_arrays(int(M), int(K), rowptr, colidx, vals, f), f)
 

@@ -230,3 +230,29 @@ def test_statistics_from_several_threads():
     assert not errors, errors
     for A, f in zip(mats, got):
         assert f == dg.dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows, mean", [(5, 3), (3001, 9), (200_003, 11), (700_001, 16)])
+def test_a_matrix_from_int64_arrays_is_ready_for_every_stream(rows, mean):
+    """The call returns on a word that its kernel writes before it ends; the 32-bit arrays are complete by then, so that
+    nothing orders a reader on another stream behind that kernel."""
+    import torch
+    rng = np.random.default_rng(rows)
+    lens = rng.integers(0, 2 * mean, size=rows)
+    rowptr = np.concatenate([[0], np.cumsum(lens)])
+    colidx = (np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lens)) * 3 + np.repeat(np.arange(rows) % 7, lens)
+    rp, ci = torch.from_numpy(rowptr).cuda(), torch.from_numpy(colidx).cuda()
+    vals = torch.ones(colidx.size, device="cuda")
+    first, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    print(f"[case] int64 arrays on two streams rows={rows}", flush=True)
+    kept = []
+    for _ in range(10):
+        with torch.cuda.stream(first):
+            D = dg.DeviceCsr.from_device(rows, 6 * mean + 7, rp, ci, vals)
+        with torch.cuda.stream(other):
+            kept.append((D, D.rowptr.clone(), D.colidx.clone()))
+    torch.cuda.synchronize()
+    for _, rp32, ci32 in kept:
+        assert torch.equal(rp32.long(), rp) and torch.equal(ci32.long(), ci)

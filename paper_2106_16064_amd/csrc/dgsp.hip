@@ -6,7 +6,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <condition_variable>
 #include <cstdint>
 #include <map>
 #include <mutex>
@@ -15,6 +14,7 @@
 
 #include "dgsp_internal.h"
 #include "dgsp_kernels.hpp"
+#include "stat_pool.hpp"
 
 namespace {
 
@@ -1031,75 +1031,27 @@ extern "C" int dgsp_features_from_csr_host(int64_t M, int64_t K, const int32_t* 
 
 // ---------------------------------------------------------------- statistics of a matrix in device memory
 // Scratch of the pass: static device arrays (every GPU holds its own copies, at addresses that hipGetSymbolAddress tells,
-// asked once per device with that device current).  A call owns one of them from launch to result; kStatSlots calls can
-// be under way on a GPU at a time, further ones wait.
-constexpr int kStatSlots = 8;
+// asked once per device with that device current).  A call owns one of them from launch to result (stat_pool.hpp).
 static __device__ __align__(256) StatScratch stat_scratch[kStatSlots];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
-
-class StatPool {
-public:
-    struct Slot {
-        int device = -1, index = -1;
-        StatScratch* scratch = nullptr;
-        unsigned long long* host = nullptr;         // result words the GPU writes (nullptr: not asked for, or no pinned memory)
-        unsigned long long ticket = 0;
-    };
-    // false: no current device, or its scratch has no address
-    bool take(Slot& slot, bool with_host) {
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
-        std::unique_lock<std::mutex> lock(mu_);
-        Device& d = devices_[dev];
-        if (!d.scratch) {
-            void* ptr = nullptr;
-            if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(stat_scratch)) != hipSuccess) return false;
-            d.scratch = static_cast<StatScratch*>(ptr);
-        }
-        if (with_host && !d.host && !d.host_failed) {
-            void* ptr = nullptr;
-            if (hipHostMalloc(&ptr, kStatSlots * kHostWords * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
-                d.host = static_cast<unsigned long long*>(ptr);
-                for (int i = 0; i < kStatSlots * kHostWords; ++i) d.host[i] = 0;
-            } else {
-                (void)hipGetLastError();
-                d.host_failed = true;
-            }
-        }
-        free_.wait(lock, [&] { return d.taken != (1u << kStatSlots) - 1u; });
-        int i = 0;
-        while (d.taken >> i & 1u) ++i;
-        d.taken |= 1u << i;
-        slot.device = dev;
-        slot.index = i;
-        slot.scratch = d.scratch + i;
-        slot.host = with_host && d.host ? d.host + i * kHostWords : nullptr;
-        slot.ticket = ++ticket_;
-        return true;
+// the current device, as the pool asks about it
+struct StatRuntime {
+    static bool device(int& dev) { return hipGetDevice(&dev) == hipSuccess; }
+    static StatScratch* scratch() {
+        void* ptr = nullptr;
+        return hipGetSymbolAddress(&ptr, HIP_SYMBOL(stat_scratch)) == hipSuccess ? static_cast<StatScratch*>(ptr) : nullptr;
     }
-    void give_back(const Slot& slot) {
-        std::lock_guard<std::mutex> lock(mu_);
-        devices_[slot.device].taken &= ~(1u << slot.index);
-        free_.notify_one();
+    static void* pinned(size_t bytes) {
+        void* ptr = nullptr;
+        if (hipHostMalloc(&ptr, bytes, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) return ptr;
+        (void)hipGetLastError();
+        return nullptr;
     }
-
-private:
-    static constexpr int kHostWords = 16;
-    struct Device {
-        StatScratch* scratch = nullptr;
-        unsigned long long* host = nullptr;
-        bool host_failed = false;
-        unsigned taken = 0;
-    };
-    std::mutex mu_;
-    std::condition_variable free_;
-    Device devices_[kMaxDevices];
-    unsigned long long ticket_ = 0;
 };
-StatPool g_stat_pool;
+using StatisticsPool = StatPool<StatScratch, StatRuntime>;
+StatisticsPool g_stat_pool;
 
 // Waits until the GPU has announced `ticket`: a look at host memory instead of a copy and an interrupt (15 us less).
 bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t st) {
@@ -1143,9 +1095,9 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
     using Word = std::conditional_t<sizeof(I) == 8, long long, int>;
     dgsp_features_t f{};
     f.M = M; f.K = K;
-    StatPool::Slot slot;
+    StatisticsPool::Slot slot;
     if (!g_stat_pool.take(slot, may_allocate)) return DGSP_ERR_LAUNCH;
-    struct Return { const StatPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
+    struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
     // enough blocks for the pieces; with the entry count unknown, for rows of 16 and no fewer than one per CU
     const long long pieces = entries >= 0 ? std::max<long long>((entries + kStatChunk - 1) / kStatChunk, (M + kStatChunk - 1) / kStatChunk)
                                           : std::max<long long>(M / 128, device_info().cus);

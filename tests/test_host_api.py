@@ -191,6 +191,16 @@ def test_c_example_builds_and_links_against_the_library():
     assert exe.exists() and exe.stat().st_size > 0
 
 
+@pytest.mark.parametrize("check", ["wakes_the_right_gpu"])
+def test_pool_of_statistics_scratch(check, tmp_path):
+    """The pool that statistics calls take their scratch from, driven by threads on two pretended GPUs."""
+    import subprocess
+    exe = tmp_path / "stat_pool_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-o", str(exe), os.path.join(ROOT, "tests", "stat_pool_check.cpp")],
+                   check=True)
+    assert subprocess.run([str(exe), check], timeout=60).returncode == 0
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess, sys, os
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))

@@ -33,13 +33,9 @@ public:
             d.scratch = Runtime::scratch();
             if (!d.scratch) return false;
         }
-        if (with_host && !d.host && !d.host_failed) {
+        if (with_host && !d.host) {                 // a refusal may be passing (a capture elsewhere): the next call asks again
             d.host = static_cast<unsigned long long*>(Runtime::pinned(kStatSlots * kHostWords * sizeof(unsigned long long)));
-            if (d.host) {
-                for (int i = 0; i < kStatSlots * kHostWords; ++i) d.host[i] = 0;
-            } else {
-                d.host_failed = true;
-            }
+            for (int i = 0; d.host && i < kStatSlots * kHostWords; ++i) d.host[i] = 0;
         }
         d.free.wait(lock, [&] { return d.taken != (1u << kStatSlots) - 1u; });
         int i = 0;
@@ -64,7 +60,6 @@ private:
     struct Device {
         Scratch* scratch = nullptr;
         unsigned long long* host = nullptr;
-        bool host_failed = false;
         unsigned taken = 0;
         std::condition_variable free;
     };

@@ -14,12 +14,13 @@ namespace {
 
 struct Area { int words[4]; };
 thread_local int t_device = 0;
+bool g_no_memory = false;
 Area g_areas[dgsp::kMaxDevices][dgsp::kStatSlots];
 
 struct Runtime {
     static bool device(int& d) { d = t_device; return true; }
     static Area* scratch() { return g_areas[t_device]; }
-    static void* pinned(size_t bytes) { return malloc(bytes); }
+    static void* pinned(size_t bytes) { return g_no_memory ? nullptr : malloc(bytes); }
 };
 using Pool = dgsp::StatPool<Area, Runtime>;
 
@@ -61,11 +62,25 @@ bool wakes_the_right_gpu() {
     return done[0] == 8;
 }
 
+// Pinned memory that one call could not get is asked for again by the next.
+bool asks_again_for_host_words() {
+    static Pool pool;
+    Pool::Slot s;
+    g_no_memory = true;
+    if (!pool.take(s, true) || s.host) return false;
+    pool.give_back(s);
+    g_no_memory = false;
+    if (!pool.take(s, true) || !s.host || s.host[0] != 0) return false;
+    pool.give_back(s);
+    return pool.take(s, false) && !s.host;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const char* name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "wakes_the_right_gpu")) return wakes_the_right_gpu() ? 0 : 1;
+    if (!strcmp(name, "asks_again_for_host_words")) return asks_again_for_host_words() ? 0 : 1;
     fprintf(stderr, "unknown check %s\n", name);
     return 2;
 }

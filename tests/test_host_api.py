@@ -191,7 +191,7 @@ def test_c_example_builds_and_links_against_the_library():
     assert exe.exists() and exe.stat().st_size > 0
 
 
-@pytest.mark.parametrize("check", ["wakes_the_right_gpu"])
+@pytest.mark.parametrize("check", ["wakes_the_right_gpu", "asks_again_for_host_words"])
 def test_pool_of_statistics_scratch(check, tmp_path):
     """The pool that statistics calls take their scratch from, driven by threads on two pretended GPUs."""
     import subprocess

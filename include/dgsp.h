@@ -249,7 +249,8 @@ int dgsp_features_from_csr_host(int64_t M, int64_t K, const int32_t *rowptr_host
  * and WAITS for the result, which the GPU writes to pinned host memory (1 KB per GPU,
  * allocated by the first call).  Up to eight calls run at a time on one GPU, on any
  * streams and threads; further ones wait for a place.  Errors as the host versions; a NULL or
- * misaligned workspace with M > 0 -> DGSP_ERR_INVALID_ARG.
+ * misaligned workspace with M > 0 -> DGSP_ERR_INVALID_ARG; a stream that is recording a graph,
+ * which cannot be waited for -> DGSP_ERR_LAUNCH, nothing recorded.
  */
 #define DGSP_FEATURES_WORKSPACE_BYTES 64
 int dgsp_features_from_csr_device(int64_t M, int64_t K, const int32_t *rowptr, const int32_t *colidx,

@@ -1053,6 +1053,15 @@ struct StatRuntime {
 using StatisticsPool = StatPool<StatScratch, StatRuntime>;
 StatisticsPool g_stat_pool;
 
+// A stream that records a graph does not run what it is given, so no result would come - and a replay would write into a
+// place of the pool that is another call's by then.
+bool recording(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Waits until the GPU has announced `ticket`: a look at host memory instead of a copy and an interrupt (15 us less).
 bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t st) {
     const auto seen = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket; };
@@ -1095,6 +1104,7 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
     using Word = std::conditional_t<sizeof(I) == 8, long long, int>;
     dgsp_features_t f{};
     f.M = M; f.K = K;
+    if (recording(st)) return DGSP_ERR_LAUNCH;
     StatisticsPool::Slot slot;
     if (!g_stat_pool.take(slot, may_allocate)) return DGSP_ERR_LAUNCH;
     struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};

@@ -256,3 +256,27 @@ def test_a_matrix_from_int64_arrays_is_ready_for_every_stream(rows, mean):
     torch.cuda.synchronize()
     for _, rp32, ci32 in kept:
         assert torch.equal(rp32.long(), rp) and torch.equal(ci32.long(), ci)
+
+
+@pytest.mark.gpu
+def test_statistics_are_refused_while_a_graph_is_recorded():
+    """Nothing of the call gets into the graph, which goes on, and the next call outside it is like any other."""
+    import torch
+    A = wl.sweep_csr(3000, 12, "lognormal", seed=1)
+    arrays = [torch.from_numpy(a).cuda() for a in (A.rowptr.astype(np.int64), A.colidx.astype(np.int64), A.vals)]
+    x = torch.zeros(5, device="cuda")
+    torch.cuda.synchronize()
+    print("[case] statistics while a graph is recorded", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        x.add_(1.0)
+        with pytest.raises(dg.DgspError):
+            dg.DeviceCsr.from_device(A.M, A.K, *arrays)
+        x.mul_(2.0)
+    want = dg.dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict()
+    value = 0.0
+    for _ in range(3):
+        graph.replay()
+        value = 2.0 * (value + 1.0)
+        assert dg.DeviceCsr.from_device(A.M, A.K, *arrays).features.as_dict() == want
+        assert torch.equal(x, torch.full_like(x, value))

@@ -553,13 +553,6 @@ int launch_nb_sr_pick(const Problem& p) {
 // Four columns and more.  Items a wave takes at least: fewer and the two searches that open a chunk outweigh it
 // (4096 rows of 8 at N = 32: 5.9 / 6.7 / 8.3 us with 64 / 128 / 256; 20 001 uneven rows of 10: 14.4 / 11.4 / 12.2 us).
 constexpr long long kRunItems = 128;
-// Column blocks of 32 (one line of a row of X per entry and block, every XCD on one block) instead of 64: the slice of X
-// an L2 sees is half as large, at one more pass over A for every 64 columns.  It pays where a few columns hold most
-// entries - a graph; the row lengths stand in for the columns' - and the matrix is large: R-MAT 2^20 x 16 at N = 64 / 128
-// 607 / 1088 -> 527 / 1022 us, 2^18 x 16 at N = 64 100 -> 93 us; but 2^17 x 16 51 -> 55 us, uniform columns 655 -> 697 us
-// (and N = 256, eight blocks: 2081 -> 2302 us).
-constexpr double kGraphCvMin = 4.0;
-constexpr long long kGraphNnzMin = 4000000;
 
 template <int LOGG, bool XBUF>
 int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
@@ -597,11 +590,13 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
 template <bool XBUF>
 int launch_nb_sr_run_x(const Problem& p) {
     // N a multiple of 64 from 128 on: column blocks of 64, so that the rows of X that many matrix rows share compete for
-    // the L2 with a quarter-kilobyte each instead of N * 4 bytes
+    // the L2 with a quarter-kilobyte each instead of N * 4 bytes.  Blocks of 32 (DGSP_ABL_COLUMN_BLOCKS_32) halve that once
+    // more for one more pass over A.  What that is worth hangs on how many entries name columns between the L2's and twice
+    // the L2's capacity, which no statistic here tells: with N = 64 / 128 R-MAT 2^20 x 16 554 / 992 -> 502 / 1025 us, but
+    // the same rows with columns of other laws, uniform to very uneven, 5-8 % slower, R-MAT 2^17 x 32 78 / 148 -> 86 / 172 us
+    // and R-MAT 2^18 x 32 170 / 363 -> 155 / 337 us.
     SrColumns cols = sr_columns(p.N, 4, p.N >= 128);
-    const bool graph = p.cv_row >= kGraphCvMin && p.nnz >= kGraphNnzMin && (p.N == 64 || p.N == 128);
-    if (p.N % 32 == 0 && p.N >= 64 && ((p.switches & DGSP_ABL_COLUMN_BLOCKS_32) || graph))
-        cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
+    if (p.N % 32 == 0 && p.N >= 64 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)) cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
     switch (cols.logG) {
         case 0: return launch_nb_sr_run_v<0, XBUF>(p, cols);
         case 1: return launch_nb_sr_run_v<1, XBUF>(p, cols);

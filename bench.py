@@ -290,22 +290,14 @@ def measure_cell(name, n, steps, warmup, full_parity=False):
     from paper_2106_16064_amd import binding as dg
     A, X, label = make_workload(name, n)
     rot = Rotation(A, X)
-    chosen = dg.dgsp_select_algo(rot.mats[0].features, n)
-    sel = dg.dgsp_algo_name(chosen)
+    launched = dg.dgsp_auto_algo(rot.mats[0].features, n)
+    sel = dg.dgsp_algo_name(launched)
     ms_cold = time_steps(rot, dg.AUTO, steps, warmup, warm=False)
     batches = max(2, steps // rot.copies)
-    ev = time_event_batches(lambda i: rot.phase(i, chosen, dg.PHASE_PREPARE),
-                            lambda i: rot.phase(i, chosen, dg.PHASE_MAIN), rot.copies, batches,
+    ev = time_event_batches(lambda i: rot.phase(i, launched, dg.PHASE_PREPARE),
+                            lambda i: rot.phase(i, launched, dg.PHASE_MAIN), rot.copies, batches,
                             max(1, warmup // rot.copies))
     ev_ms = sum(ev) / len(ev)
-    timed_as = sel
-    if ms_cold < 0.95 * ev_ms:
-        # the adaptive call ran row groups (rs_sr, one launch) in place of the kernel the rules name: that launch is timed
-        none = dg.PHASE_PREPARE
-        ev = time_event_batches(lambda i: rot.phase(i, dg.RS_SR, none), lambda i: rot.phase(i, dg.RS_SR, dg.PHASE_MAIN),
-                                rot.copies, batches, max(1, warmup // rot.copies))
-        ev_ms = sum(ev) / len(ev)
-        timed_as = dg.dgsp_algo_name(dg.RS_SR)
     floors = floor_probes(rot)
     rot.step(0, dg.AUTO)
     torch.cuda.synchronize()
@@ -319,16 +311,17 @@ def measure_cell(name, n, steps, warmup, full_parity=False):
         parity = sampled_parity(A, X, Y)
     bytes_alg = algorithmic_bytes(A, n)
     achieved = bytes_alg / (ev_ms * 1e-3) / 1e9
-    traffic, source = MEASURED_TRAFFIC.get(f"{timed_as}/{name}/N{n}", (None, None))
+    traffic, source = MEASURED_TRAFFIC.get(f"{sel}/{name}/N{n}", (None, None))
     cell = {
         "workload": label, "M": A.M, "K": A.K, "nnz": A.nnz, "N": n, "buffer_rotation": rot.copies,
-        "selected_kernel": sel, "ms_per_step": ms_cold,
+        "selected_kernel": sel, "rules_name": dg.dgsp_algo_name(dg.dgsp_select_algo(rot.mats[0].features, n)),
+        "ms_per_step": ms_cold,
         "GFLOPs": 2.0 * A.nnz * n / (ms_cold * 1e-3) / 1e9,
         "algorithmic_bytes": bytes_alg, "effective_GBps": bytes_alg / (ms_cold * 1e-3) / 1e9,
         "pct_hbm_peak": 100.0 * bytes_alg / (ms_cold * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
-                     "kernel": f"dgsp::{timed_as}_kernel (main launch alone; HIP events on the launch stream around "
+                     "kernel": f"dgsp::{'nb_sr_run' if sel == 'nb_sr' and n >= 4 else sel}_kernel (main launch alone; HIP events on the launch stream around "
                                f"{len(ev)} batches of {rot.copies} back-to-back launches, one per buffer set)",
                      "algorithmic_bytes": bytes_alg, "launch_ms": ev_ms, "floors_ms": floors},
         "parity": parity,
@@ -454,7 +447,7 @@ def run_configs(args):
             A, X, label = make_workload(name, n)
             rot = Rotation(A, X)
             table = variant_table(rot, args.steps, args.warmup)
-            sel = dg.dgsp_algo_name(dg.dgsp_select_algo(rot.mats[0].features, n))
+            sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(rot.mats[0].features, n))
             best = min(table, key=table.get)
             ba = algorithmic_bytes(A, n)
             row = {"workload": label, "N": n, "nnz": A.nnz, "algorithmic_bytes": ba, "selected": sel, "best": best,
@@ -485,12 +478,13 @@ def run_sweep(args):
                 rot = Rotation(A, X, copies=2)
                 table = variant_table(rot, args.steps, args.warmup)
                 f = rot.mats[0].features
-                sel = dg.dgsp_algo_name(dg.dgsp_select_algo(f, n))
+                sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(f, n))
                 best = min(table, key=table.get)
                 loss = table[sel] / table[best] - 1.0
                 losses.append(loss)
                 fh.write(json.dumps({"matrix": A.name, "N": n, "M": A.M, "avg_row": f.avg_row, "cv_row": f.cv_row,
                                      "max_row": f.max_row, "nnz": A.nnz, "K": A.K, "col_span": f.col_span, "ms": table, "selected": sel,
+                                     "row_groups": row_groups_take_over(f, n),
                                      "best": best, "loss": loss}) + "\n")
                 fh.flush()
                 del rot
@@ -539,7 +533,7 @@ def run_tiny(args):
         torch.cuda.synchronize()
         replay = (time.perf_counter() - t0) / (reps * per_graph)
         out[name] = {"eager_us": eager * 1e6, "graph_us": replay * 1e6}
-    sel = dg.dgsp_algo_name(dg.dgsp_select_algo(dA.features, 4))
+    sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(dA.features, 4))
     print(json.dumps({"suite": "tiny", "workload": label, "nnz": A.nnz, "selected": sel, "per_call": out}))
     return 0
 
@@ -565,10 +559,11 @@ def run_size(args):
                 rot = Rotation(A, wl.dense_matrix(A.K, n, "uniform", seed=0))
                 table = variant_table(rot, args.steps, args.warmup)
                 f = rot.mats[0].features
-                sel = dg.dgsp_algo_name(dg.dgsp_select_algo(f, n))
+                sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(f, n))
                 best = min(table, key=table.get)
                 fh.write(json.dumps({"matrix": name, "N": n, "M": A.M, "avg_row": f.avg_row, "cv_row": f.cv_row,
                                      "max_row": f.max_row, "nnz": A.nnz, "K": A.K, "col_span": f.col_span, "ms": table, "selected": sel,
+                                     "row_groups": row_groups_take_over(f, n),
                                      "best": best, "loss": table[sel] / table[best] - 1.0}) + "\n")
                 fh.flush()
                 cells += 1
@@ -615,7 +610,7 @@ def run_widths(args):
                     def call(i):
                         rot.step(i, dg.AUTO)
                 us = median(time_events(None, call, max(5, min(args.steps, 30)), 3)) * 1e3
-                sel = dg.dgsp_algo_name(dg.dgsp_select_algo(rot.mats[0].features, n))
+                sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(rot.mats[0].features, n))
                 fh.write(json.dumps({"matrix": label, "N": n, "nnz": A.nnz, "us": us, "selected": sel,
                                      "ld": (-(-n // pad) * pad) if pad else n}) + "\n")
                 fh.flush()
@@ -808,7 +803,7 @@ def run_colranges(args):
                             dg.dgsp_spmm_csr_axpby(m.M, m.K, n, m.nnz, m.rowptr, m.colidx, m.vals, Xd, Y, 1.0, 1.0, dg.AUTO, m.features)
                 ms = time_events(None, call, steps, 2)
                 rec = {"workload": label, "N": n, "cut": how, "passes": P, "entries_per_pass": [int(m.nnz) for m in parts],
-                       "kernels": [dg.dgsp_algo_name(dg.dgsp_select_algo(m.features, n)) for m in parts], "us": median(ms) * 1e3}
+                       "kernels": [dg.dgsp_algo_name(dg.dgsp_auto_algo(m.features, n)) for m in parts], "us": median(ms) * 1e3}
                 fh.write(json.dumps(rec) + "\n")
                 fh.flush()
                 print(f"[colranges] {how} P={P}: {rec['us']:.0f} us", file=sys.stderr, flush=True)
@@ -844,10 +839,11 @@ def run_holdout(args):
                 rot = Rotation(A, wl.dense_matrix(A.K, n, "uniform", seed=0), copies=2 if A.nnz * n > 3e8 else None)
                 table = variant_table(rot, k, 2)
                 f = rot.mats[0].features
-                sel = dg.dgsp_algo_name(dg.dgsp_select_algo(f, n))
+                sel = dg.dgsp_algo_name(dg.dgsp_auto_algo(f, n))
                 best = min(table, key=table.get)
                 rec = {"matrix": name, "N": n, "M": A.M, "avg_row": f.avg_row, "cv_row": f.cv_row, "max_row": f.max_row, "nnz": A.nnz,
                        "K": A.K, "col_span": f.col_span, "ms": table, "selected": sel, "best": best,
+                       "row_groups": row_groups_take_over(f, n),
                        "loss": table[sel] / table[best] - 1.0}
                 cells.append(rec)
                 fh.write(json.dumps(rec) + "\n")
@@ -876,6 +872,24 @@ def sr_lanes(N):
     while g < (N + 3) // 4:
         g *= 2
     return min(g, 64)
+
+
+def row_groups_take_over(f, n):
+    """Does an adaptive call launch row groups (rs_sr) whatever the rules answer?  Asked with thresholds that make the rules
+    answer nb_pr."""
+    from paper_2106_16064_amd import binding as dg
+    saved, t = dg.dgsp_get_thresholds(), dg.dgsp_get_thresholds()
+    t.n_parallel_max, t.pr_avg_row_min, t.short_avg_row_max, t.big_x_bytes_min, t.pr_small_nnz_max = 1 << 40, 1e300, 0.0, 0, 0
+    try:
+        dg.dgsp_set_thresholds(t)
+        return dg.dgsp_auto_algo(f, n) == dg.RS_SR
+    finally:
+        dg.dgsp_set_thresholds(saved)
+
+
+def launched_choice(r, t):
+    """The kernel an adaptive call launches on a bench record r when the rules have thresholds t."""
+    return "rs_sr" if r.get("row_groups") else rules_choose(r, t)
 
 
 def rules_choose(r, t):
@@ -917,7 +931,7 @@ def run_fit(args):
                big_x_cv_max=0.0, big_x_avg_row_max=0.0, short_min_waves=0, pr_small_nnz_max=0, pr_small_cv_max=0.0)
 
     def losses(rs, t):
-        return [r["ms"][rules_choose(r, t)] / min(r["ms"].values()) - 1 for r in rs]
+        return [r["ms"][launched_choice(r, t)] / min(r["ms"].values()) - 1 for r in rs]
 
     def loss(rs, t):
         l = losses(rs, t)
@@ -968,7 +982,7 @@ def run_fit(args):
                 "holdout_cells": loss(hold, t)[0]}
 
     def over(rs, t, limit=0.10):
-        return [{"matrix": r["matrix"], "N": r["N"], "selected": rules_choose(r, t), "best": min(r["ms"], key=r["ms"].get),
+        return [{"matrix": r["matrix"], "N": r["N"], "selected": launched_choice(r, t), "best": min(r["ms"], key=r["ms"].get),
                  "loss": round(l, 3)} for r, l in zip(rs, losses(rs, t)) if l > limit]
 
     print(json.dumps({

@@ -197,8 +197,8 @@ int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz,
  * `chosen` is not NULL it receives the dgsp_algo_t of the rules.  Where the
  * statistics show that runs of rows are balanced anyway (rows alike) or that the
  * matrix is too small for a balanced kernel's start to pay, the launch itself uses
- * the row-split sequential kernel with several lanes per row; a kernel asked for
- * by name is always the one that runs.
+ * the row-split sequential kernel with several lanes per row: dgsp_auto_algo says
+ * which kernel it is.  A kernel asked for by name is always the one that runs.
  */
 int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N,
                        const dgsp_features_t *features,
@@ -212,6 +212,15 @@ int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N,
  * DGSP_AUTO (-1) if features is NULL or N < 1.
  */
 int dgsp_select_algo(const dgsp_features_t *features, int64_t N);
+
+/*
+ * The dgsp_algo_t of the kernel that an adaptive call with these statistics launches: the rules' answer, or
+ * DGSP_RS_SR where the launch puts that kernel in its place (see dgsp_spmm_csr_auto).  Asked for by name with the same
+ * `features` (dgsp_spmm_csr_phase, dgsp_spmm_csr_ld, dgsp_spmm_csr_axpby) it is the same launch.  For packed Y and
+ * for views with ldy up to 2^20 floats.  Pure host function (the answer takes the current device's number of compute
+ * units into account, 256 without a device); DGSP_AUTO (-1) if features is NULL or N < 1.
+ */
+int dgsp_auto_algo(const dgsp_features_t *features, int64_t N);
 
 /* Read / replace the thresholds used by dgsp_select_algo (process-wide; reads
  * and writes are serialised by a lock, every selection sees one consistent set).

@@ -21,7 +21,7 @@ LIB_PATH = Path(__file__).resolve().parent / "libdgsp.so"
 NATIVE_PATH = LIB_PATH.with_name("_dgsp_torch.so")
 
 EXPORTS = (
-    "dgsp_spmm_csr", "dgsp_spmm_csr_nnz", "dgsp_spmm_csr_auto", "dgsp_select_algo",
+    "dgsp_spmm_csr", "dgsp_spmm_csr_nnz", "dgsp_spmm_csr_auto", "dgsp_select_algo", "dgsp_auto_algo",
     "dgsp_get_thresholds", "dgsp_set_thresholds", "dgsp_features_from_rowptr_host",
     "dgsp_copy_f32", "dgsp_algo_name", "dgsp_status_string",
     "dgsp_spmm_csr_phase", "dgsp_gather_probe", "dgsp_gather_probe_out_len", "dgsp_features_from_csr_host",
@@ -84,6 +84,8 @@ def lib():
                                          ctypes.POINTER(ci), vp]
         L.dgsp_select_algo.restype = ci
         L.dgsp_select_algo.argtypes = [ctypes.POINTER(Features), i64]
+        L.dgsp_auto_algo.restype = ci
+        L.dgsp_auto_algo.argtypes = [ctypes.POINTER(Features), i64]
         L.dgsp_get_thresholds.restype = None
         L.dgsp_get_thresholds.argtypes = [ctypes.POINTER(Thresholds)]
         L.dgsp_set_thresholds.restype = None
@@ -301,12 +303,17 @@ def dgsp_gather_probe_out_len() -> int:
 
 
 def dgsp_spmm_csr_auto(M, K, N, features: Features, rowptr, colidx, vals, X, Y, stream=None) -> int:
-    """Select by the rules, run, return the chosen algo."""
+    """Select by the rules, run, return the algo of the rules (``dgsp_auto_algo``: the kernel that is launched)."""
     return (_native or native()).spmm_csr_auto(M, K, N, features, rowptr, colidx, vals, X, Y, stream)
 
 
 def dgsp_select_algo(features: Features, N: int) -> int:
     return int(lib().dgsp_select_algo(ctypes.byref(features), int(N)))
+
+
+def dgsp_auto_algo(features: Features, N: int) -> int:
+    """The kernel that an adaptive call with these statistics launches."""
+    return int(lib().dgsp_auto_algo(ctypes.byref(features), int(N)))
 
 
 def dgsp_get_thresholds() -> Thresholds:

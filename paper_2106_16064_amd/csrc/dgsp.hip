@@ -672,6 +672,9 @@ inline int library_choice(int algo, int64_t ldy) {
     return ((algo == DGSP_NB_SR || algo == DGSP_NB_PR) && ldy > kBalancedLdyMax) ? DGSP_RS_SR : algo;
 }
 
+// the kernel that runs where the rules name `algo`
+inline int launched_algo(const Problem& p, int algo) { return algo != DGSP_RS_SR && row_groups_suit(p) ? DGSP_RS_SR : algo; }
+
 int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
         const float* vals, const float* X, float* Y, int algo, void* stream, int phase = DGSP_PHASE_ALL,
         Hints hints = Hints(), int switches = 0, int64_t ldx = -1, int64_t ldy = -1, const Scaling* scaling = nullptr) {
@@ -697,7 +700,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
 
     Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
-    if (hints.chosen && algo != DGSP_RS_SR && row_groups_suit(p)) algo = DGSP_RS_SR;
+    if (hints.chosen) algo = launched_algo(p, algo);
     switch (algo) {
         case DGSP_RS_SR: return phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_sr(p);
         case DGSP_RS_PR: return phase == DGSP_PHASE_PREPARE ? DGSP_OK : launch_rs_pr(p);
@@ -883,6 +886,17 @@ extern "C" int dgsp_select_algo(const dgsp_features_t* f, int64_t N) {
     if (!(f->cv_row > t.sr_cv_min && f->stdv_row > t.sr_stdv_min)) return DGSP_RS_SR;
     // up to eight columns fit one lane of the balanced parallel kernel: still a single pass
     return (N <= t.wide_parallel_n) ? DGSP_NB_PR : DGSP_NB_SR;
+}
+
+extern "C" int dgsp_auto_algo(const dgsp_features_t* f, int64_t N) {
+    const int algo = dgsp_select_algo(f, N);
+    if (algo < 0) return algo;
+    const int64_t lim = (int64_t)INT32_MAX - 4096;
+    if (f->M < 0 || f->M > lim || f->K > lim || f->nnz > lim || N > lim) return algo;       // such calls are turned down
+    const Hints hints(f);
+    Problem p{(int)f->M, (int)N, (int)N, (int)N, f->K, f->nnz};
+    p.col_span = hints.col_span; p.cv_row = hints.cv_row; p.max_row = hints.max_row; p.size = f->nnz;
+    return launched_algo(p, library_choice(algo, N));
 }
 
 extern "C" void dgsp_get_thresholds(dgsp_thresholds_t* out) {

@@ -118,3 +118,16 @@ def test_balanced_parallel_tiles_and_blocks(dg, lens, N):
     for features in (True, False):
         _compare(dg, A, N, dg.NB_PR, features, poison_row=int(free[0]) if free.size else None)
         _compare(dg, A, N, dg.NB_PR, features, alpha=-0.5, beta=1.5)
+
+
+@pytest.mark.parametrize("N", [1, 4, 8, 33])
+@pytest.mark.parametrize("law", ["fixed", "lognormal"])
+def test_the_launched_kernel_by_name_is_the_adaptive_call(dg, law, N):
+    """Row groups sum in a fixed order, so the kernel that ``dgsp_auto_algo`` names gives the same bits."""
+    import torch
+    A = wl.sweep_csr(4096, 9, law, seed=N)
+    dA = dg.DeviceCsr(A)
+    assert dg.dgsp_auto_algo(dA.features, N) == dg.RS_SR
+    X = torch.from_numpy(wl.dense_matrix(A.K, N, "normal", seed=N)).cuda()
+    print(f"[case] launched kernel by name {law} N={N}", flush=True)
+    assert torch.equal(dA.spmm(X), dA.spmm(X, algo=dg.RS_SR))

@@ -234,6 +234,26 @@ def test_default_thresholds_and_their_effect_on_benchmark_shapes():
     assert [dg.dgsp_select_algo(f, n) for n in (1, 4, 8)] == [dg.RS_PR, dg.RS_PR, dg.RS_SR]
 
 
+def test_the_kernel_that_an_adaptive_call_launches():
+    """``dgsp_auto_algo`` names it: the rules' answer, or the row-split sequential kernel where rows alike or a small matrix
+    make row groups the better launch."""
+    S = wl.stencil27_csr(24)
+    f = dg.dgsp_features_from_csr_host(S.M, S.K, S.rowptr, S.colidx)
+    f.nnz = 55_742_968
+    f.M = f.K = 128 ** 3
+    assert [dg.dgsp_select_algo(f, n) for n in (1, 4, 8)] == [dg.NB_PR, dg.NB_PR, dg.RS_SR]
+    assert [dg.dgsp_auto_algo(f, n) for n in (1, 4, 8)] == [dg.RS_SR, dg.RS_SR, dg.RS_SR]
+    small = wl.sweep_csr(4096, 8, "lognormal", seed=0)
+    f = dg.dgsp_features_from_csr_host(small.M, small.K, small.rowptr, small.colidx)
+    assert dg.dgsp_select_algo(f, 1) == dg.NB_PR and dg.dgsp_auto_algo(f, 1) == dg.RS_SR
+    R = wl.rmat_csr(18, 8, seed=0)
+    f = dg.dgsp_features_from_csr_host(R.M, R.K, R.rowptr, R.colidx)
+    assert [dg.dgsp_auto_algo(f, n) for n in (1, 8, 32)] == [dg.NB_PR, dg.NB_PR, dg.NB_SR]
+    g = dg.dgsp_features_from_rowptr_host(3, 5, np.zeros(4, np.int32))           # no entries
+    assert dg.dgsp_auto_algo(g, 4) == dg.dgsp_select_algo(g, 4)
+    assert dg.lib().dgsp_auto_algo(None, 4) == dg.AUTO and dg.dgsp_auto_algo(f, 0) == dg.AUTO
+
+
 def test_the_benchmark_mirror_of_the_rules_agrees_with_the_library():
     """bench.py scores recorded timings with a Python copy of the selection rules (`rules_choose`, used by
     `--suite fit`); the losses it reports are only worth something if that copy picks what `dgsp_select_algo`

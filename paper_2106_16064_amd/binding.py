@@ -182,12 +182,12 @@ def _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y):
 
 def dgsp_spmm_csr(M, K, N, rowptr, colidx, vals, X, Y, algo, stream=None):
     """``Y = A X`` with the kernel ``algo``; the entry count is read on the device."""
-    (_native or native()).spmm_csr(M, K, N, None, rowptr, colidx, vals, X, Y, algo, stream)
+    (_native or native()).spmm_csr(M, K, N, rowptr, colidx, vals, X, Y, algo, stream)
 
 
 def dgsp_spmm_csr_nnz(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream=None):
     """``Y = A X`` with the entry count given by the caller."""
-    (_native or native()).spmm_csr(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream)
+    (_native or native()).spmm_csr_nnz(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream)
 
 
 def dgsp_spmm_csr_i64(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, workspace=None, stream=None):
@@ -222,13 +222,13 @@ def dgsp_spmm_csr_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, f
 def dgsp_spmm_csr_ld(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, features=None, stream=None):
     """``Y = A X`` on 2-D views whose rows are ``stride(0)`` floats apart (``stride(1)`` must be 1):
     column slices of wider row-major tensors are taken as they are, nothing is copied."""
-    (_native or native()).spmm_csr_view(M, K, N, nnz, rowptr, colidx, vals, X, Y, None, None, algo, features, stream)
+    (_native or native()).spmm_csr_ld(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, features, stream)
 
 
 def dgsp_spmm_csr_axpby(M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha=1.0, beta=0.0, algo=AUTO, features=None,
                         stream=None):
     """``Y = alpha * A X + beta * Y`` on 2-D views (rows ``stride(0)`` floats apart, unit column stride)."""
-    (_native or native()).spmm_csr_view(M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream)
+    (_native or native()).spmm_csr_axpby(M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream)
 
 
 def dgsp_spmm_csr_ablation(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, switches, features=None, stream=None):

@@ -48,9 +48,23 @@ int64_t as_int(PyObject* o) {
     return v;
 }
 
-float as_float(PyObject* o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+// Entry counts, algos and factors: what int() and float() take.
+int64_t to_int(PyObject* o) {
+    if (PyLong_CheckExact(o)) return as_int(o);
+    PyObject* i = PyNumber_Long(o);
+    if (!i) throw Raised{};
+    const long long v = PyLong_AsLongLong(i);
+    Py_DECREF(i);
+    if (v == -1 && PyErr_Occurred()) throw Raised{};
+    return v;
+}
+
+float to_float(PyObject* o) {
+    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+    PyObject* f = PyNumber_Float(o);
+    if (!f) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return (float)v;
 }
 
@@ -276,7 +290,7 @@ PyObject* multiply_new(PyObject* const* a, Py_ssize_t n) {
     want(n, 8);
     const Csr A(a + 2, as_int(a[0]), as_int(a[1]));
     const at::Tensor& X = as_tensor(a[6], "X");
-    return THPVariable_Wrap(multiply(A, X, (int)as_int(a[7]), false));
+    return THPVariable_Wrap(multiply(A, X, (int)to_int(a[7]), false));
 }
 
 // Does nothing but reverse mode look at a product of X?  Not so under a tangent on X (forward mode), a function transform
@@ -301,11 +315,11 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
     at::Tensor Y;
     {
         at::NoGradGuard no_grad;
-        Y = multiply(A, X.to(at::kFloat).contiguous(), (int)as_int(a[1]), vector);
+        Y = multiply(A, X.to(at::kFloat).contiguous(), (int)to_int(a[1]), vector);
     }
     if (at::GradMode::is_enabled() && X.requires_grad()) {
         std::shared_ptr<ProductBackward> node(
-            new ProductBackward(Csr(a + 11, as_int(a[9]), as_int(a[10])), (int)as_int(a[2]), vector), torch::autograd::deleteNode);
+            new ProductBackward(Csr(a + 11, as_int(a[9]), as_int(a[10])), (int)to_int(a[2]), vector), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(X));
         torch::autograd::set_history(Y, node);
     }
@@ -364,60 +378,84 @@ PyObject* spmm_csr_auto(PyObject* const* a, Py_ssize_t n) {
     return PyLong_FromLong(algo);
 }
 
-// (M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream); nnz None: read on the device
-PyObject* spmm_csr(PyObject* const* a, Py_ssize_t n) {
-    want(n, 11);
-    const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]);
-    const at::Tensor &rowptr = as_tensor(a[4], "rowptr"), &colidx = as_tensor(a[5], "colidx"), &vals = as_tensor(a[6], "vals");
-    const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
+// `a`: rowptr, colidx, vals, X, Y, algo, stream; `count` nullptr: the entry count is read on the device
+void packed_product(PyObject* const* extents, PyObject* count, PyObject* const* a) {
+    const int64_t M = as_int(extents[0]), K = as_int(extents[1]), N = as_int(extents[2]);
+    const int64_t nnz = count ? to_int(count) : -1;
+    const int algo = (int)to_int(a[5]);
+    const at::Tensor &rowptr = as_tensor(a[0], "rowptr"), &colidx = as_tensor(a[1], "colidx"), &vals = as_tensor(a[2], "vals");
+    const at::Tensor &X = as_tensor(a[3], "X"), &Y = as_tensor(a[4], "Y");
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
-    const bool counted = a[3] != Py_None;
-    const int64_t nnz = counted ? as_int(a[3]) : -1;
-    if (counted && nnz >= 0 && colidx.numel() < nnz) fail("colidx/vals shorter than nnz");
-    const int algo = (int)as_int(a[9]);
-    void* stream = as_stream(a[10]);
+    if (nnz >= 0 && colidx.numel() < nnz) fail("colidx/vals shorter than nnz");
+    void* stream = as_stream(a[6]);
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     const int rc = unlocked([&] {
-        return counted ? dgsp_spmm_csr_nnz(M, K, N, nnz, rp, ci, av, x, y, algo, stream)
-                       : dgsp_internal_spmm_csr(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, stream);
+        return count ? dgsp_spmm_csr_nnz(M, K, N, nnz, rp, ci, av, x, y, algo, stream)
+                     : dgsp_internal_spmm_csr(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, stream);
     });
-    check_status(rc, counted ? "dgsp_spmm_csr_nnz" : "dgsp_spmm_csr");
+    check_status(rc, count ? "dgsp_spmm_csr_nnz" : "dgsp_spmm_csr");
+}
+
+// (M, K, N, rowptr, colidx, vals, X, Y, algo, stream)
+PyObject* spmm_csr(PyObject* const* a, Py_ssize_t n) {
+    want(n, 10);
+    packed_product(a, nullptr, a + 3);
     Py_RETURN_NONE;
 }
 
-// (M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream); alpha None: the plain product
-PyObject* spmm_csr_view(PyObject* const* a, Py_ssize_t n) {
-    want(n, 14);
-    const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]), nnz = as_int(a[3]);
+// (M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, stream)
+PyObject* spmm_csr_nnz(PyObject* const* a, Py_ssize_t n) {
+    want(n, 11);
+    packed_product(a, a[3], a + 4);
+    Py_RETURN_NONE;
+}
+
+struct Factors { float alpha, beta; };
+
+// `a`: M, K, N, nnz, rowptr, colidx, vals, X, Y; `b`: algo, features, stream; `factors` nullptr: the plain product
+void view_product(PyObject* const* a, const Factors* factors, PyObject* const* b) {
+    const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]), nnz = to_int(a[3]);
     const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
     const int64_t ldx = check_view(X, "X", K, N), ldy = check_view(Y, "Y", M, N);
-    const bool scaled = a[9] != Py_None;
-    const float alpha = scaled ? as_float(a[9]) : 1.0f, beta = scaled ? as_float(a[10]) : 0.0f;
-    const int algo = (int)as_int(a[11]);
-    const FeaturesArg f(a[12]);
-    void* stream = as_stream(a[13]);
+    const int algo = (int)to_int(b[0]);
+    const FeaturesArg f(b[1]);
+    void* stream = as_stream(b[2]);
     const auto* rp = static_cast<const int32_t*>(ptr(a[4], "rowptr"));
     const auto* ci = static_cast<const int32_t*>(ptr(a[5], "colidx"));
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     const int rc = unlocked([&] {
-        return scaled ? dgsp_spmm_csr_axpby(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, alpha, beta, algo, f.get(), stream)
-                      : dgsp_spmm_csr_ld(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, algo, f.get(), stream);
+        return factors ? dgsp_spmm_csr_axpby(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors->alpha, factors->beta, algo, f.get(), stream)
+                       : dgsp_spmm_csr_ld(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, algo, f.get(), stream);
     });
-    check_status(rc, scaled ? "dgsp_spmm_csr_axpby" : "dgsp_spmm_csr_ld");
+    check_status(rc, factors ? "dgsp_spmm_csr_axpby" : "dgsp_spmm_csr_ld");
+}
+
+// (M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, features, stream)
+PyObject* spmm_csr_ld(PyObject* const* a, Py_ssize_t n) {
+    want(n, 12);
+    view_product(a, nullptr, a + 9);
+    Py_RETURN_NONE;
+}
+
+// (M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream)
+PyObject* spmm_csr_axpby(PyObject* const* a, Py_ssize_t n) {
+    want(n, 14);
+    const Factors factors{to_float(a[9]), to_float(a[10])};
+    view_product(a, &factors, a + 11);
     Py_RETURN_NONE;
 }
 
 #define DGSP_ENTRY(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&entry<name>)), METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {
     DGSP_ENTRY(set_error_type), DGSP_ENTRY(multiply_new), DGSP_ENTRY(multiply_differentiable), DGSP_ENTRY(spmm_csr_auto),
-    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_view), DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
+    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_nnz), DGSP_ENTRY(spmm_csr_ld), DGSP_ENTRY(spmm_csr_axpby), DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_dgsp_torch", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -29,6 +29,40 @@ def test_arguments_that_are_not_the_arrays_of_a_product_raise(wrong):
             call()
 
 
+def _one_entry(device):
+    import torch
+    return (torch.tensor([0, 1], dtype=torch.int32, device=device), torch.zeros(1, dtype=torch.int32, device=device),
+            torch.full((1,), 3.0, device=device), torch.full((1, 1), 2.0, device=device), torch.zeros(1, 1, device=device))
+
+
+def test_numbers_are_taken_as_int_and_float_take_them():
+    """On host tensors, which are turned down for what they are: a TypeError would mean the number was."""
+    arrays = _one_entry("cpu")
+    for nnz, algo, alpha in ((1.0, 2.0, 1), (np.float32(1.0), np.int64(2), np.float64(0.5)), ("1", "2", "0.5")):
+        for call in (lambda: dg.dgsp_spmm_csr_nnz(1, 1, 1, nnz, *arrays, algo), lambda: dg.dgsp_spmm_csr(1, 1, 1, *arrays, algo),
+                     lambda: dg.dgsp_spmm_csr_ld(1, 1, 1, nnz, *arrays, algo),
+                     lambda: dg.dgsp_spmm_csr_axpby(1, 1, 1, nnz, *arrays, alpha, alpha, algo)):
+            with pytest.raises(dg.DgspError):
+                call()
+    for call in (lambda: dg.dgsp_spmm_csr_nnz(1, 1, 1, None, *arrays, dg.AUTO),
+                 lambda: dg.dgsp_spmm_csr_axpby(1, 1, 1, 1, *arrays, None, 0.0),
+                 lambda: dg.dgsp_spmm_csr_axpby(1, 1, 1, 1, *arrays, 1.0, None)):
+        with pytest.raises(TypeError):
+            call()
+
+
+@pytest.mark.gpu
+def test_numbers_of_other_types_give_the_product():
+    arrays = _one_entry("cuda")
+    Y = arrays[-1]
+    for call, want in ((lambda: dg.dgsp_spmm_csr_nnz(1, 1, 1, 1.0, *arrays, 2.0), 6.0),
+                       (lambda: dg.dgsp_spmm_csr(1, 1, 1, *arrays, np.float64(3.0)), 6.0),
+                       (lambda: dg.dgsp_spmm_csr_ld(1, 1, 1, 1.0, *arrays, 0.0), 6.0),
+                       (lambda: dg.dgsp_spmm_csr_axpby(1, 1, 1, np.float32(1.0), *arrays, np.float64(2.0), 1, 1.0), 13.0)):
+        Y.fill_(1.0)
+        call()
+        assert Y.item() == want
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["float32", "float64"])
 @pytest.mark.parametrize("N", [0, 1, 5, 33])

@@ -16,7 +16,7 @@ HERE = Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libdgsp.so"
 SOURCES = [CSRC / "dgsp.hip"]
-HEADERS = [CSRC / "dgsp_device.hpp", CSRC / "dgsp_kernels.hpp", CSRC / "stat_pool.hpp", HERE.parent / "include" / "dgsp.h"]
+HEADERS = [*sorted(CSRC.glob("*.h")), *sorted(CSRC.glob("*.hpp")), HERE.parent / "include" / "dgsp.h"]
 
 TORCH_LIB = HERE / "_dgsp_torch.so"
 TORCH_SOURCE = CSRC / "torch_binding.cpp"

@@ -184,6 +184,12 @@ def test_column_span_feature():
     assert dg.dgsp_features_from_rowptr_host(3, 10, np.array([0, 2, 2, 3], np.int32)).col_span == 0.0
 
 
+def test_every_source_counts_for_a_stale_build():
+    from paper_2106_16064_amd import build
+    known = {f.resolve() for f in (*build.SOURCES, *build.HEADERS, build.TORCH_SOURCE)}
+    assert known == {f.resolve() for f in (*build.CSRC.iterdir(), build.HERE.parent / "include" / "dgsp.h")}
+
+
 def test_c_example_builds_and_links_against_the_library():
     """The plain-C caller compiles with gcc against include/dgsp.h and links to libdgsp.so (running it needs a GPU)."""
     from paper_2106_16064_amd import build

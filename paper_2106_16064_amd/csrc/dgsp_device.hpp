@@ -317,7 +317,6 @@ __device__ __forceinline__ float dpp_or_zero(float v) {
 }
 
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
-constexpr int kDppRowRor1 = 0x121, kDppRowRor2 = 0x122, kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;   // rotations inside a row of 16
 constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 constexpr int kDppWaveShr1 = 0x138;   // lane l reads lane l-1 across the whole wave; lane 0 gets the fill value
 

@@ -147,6 +147,16 @@ int resident_blocks_per_cu(K kernel) {
 }
 
 // ---------------------------------------------------------------- row-split launches
+// Workgroups whose waves stride over `groups` groups of rows: at most `cap`, and so many that the rounds are equal.  An
+// incomplete last round would be neighbouring groups, which xcd_contiguous gives to one or two XCDs, and would take as long
+// as a full one.  `cap` workgroups against equal rounds: 573 735 rows of 60 at N = 2 326 -> 219 us, 27-point stencil on
+// 106^3 at N = 1 / 2 76 / 90 -> 54 / 64 us, on 84^3 at N = 21 146 -> 97 us.
+inline unsigned even_round_blocks(long long groups, long long cap) {
+    const long long blocks = (groups + kWavesPerBlock - 1) / kWavesPerBlock;
+    const long long rounds = blocks > cap ? (blocks + cap - 1) / cap : 1;
+    return clamp_blocks((blocks + rounds - 1) / rounds, cap);
+}
+
 // X can be addressed with 32-bit byte offsets (through a buffer descriptor)
 constexpr unsigned long long kL2BytesPerXcd = 4ull << 20;      // gfx950: 4 MB of L2 per XCD
 
@@ -162,7 +172,7 @@ int launch_rs_pr_v(const Problem& p) {
     const int rows_per_wave = (kWave >> (logG >= 0 ? logG : 1)) * kRsPrUnroll;
     const long long groups = ((long long)p.M + rows_per_wave - 1) / rows_per_wave;
     const long long cap = (long long)device_info().cus * kBlocksPerCu * 8;
-    const dim3 grid(clamp_blocks((groups + kWavesPerBlock - 1) / kWavesPerBlock, cap));
+    const dim3 grid(even_round_blocks(groups, cap));
     if (p.scaled) {
         DGSP_LAUNCH((rs_pr_kernel<V, XBUF, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
                     p.Y, logG, Scaling{p.alpha, p.beta});
@@ -298,7 +308,7 @@ int launch_rs_sr_v(const Problem& p, const SrColumns& cols, int logH) {
     const int rows_per_wave = kWave >> (logG + logH);
     const long long groups = ((long long)p.M + rows_per_wave - 1) / rows_per_wave;
     const long long cap = (long long)device_info().cus * kBlocksPerCu * 8;
-    const dim3 grid(clamp_blocks((groups + kWavesPerBlock - 1) / kWavesPerBlock, cap), col_blocks);
+    const dim3 grid(even_round_blocks(groups, cap), col_blocks);
     if (p.scaled) {
         DGSP_LAUNCH((rs_sr_kernel<V, XBUF, DEPTH, true, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals,
                     p.X, p.Y, logG, logH, cols.cols_per_block, Scaling{p.alpha, p.beta});
@@ -319,7 +329,7 @@ int launch_rs_sr_direct_v(const Problem& p) {
     const int rows_per_wave = kWave >> logG;
     const long long groups = ((long long)p.M + rows_per_wave - 1) / rows_per_wave;
     const long long cap = (long long)device_info().cus * kBlocksPerCu * 8;
-    const dim3 grid(clamp_blocks((groups + kWavesPerBlock - 1) / kWavesPerBlock, cap), col_blocks);
+    const dim3 grid(even_round_blocks(groups, cap), col_blocks);
     DGSP_LAUNCH((rs_sr_direct_kernel<V>), grid, p.M, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, logG,
                 cols.cols_per_block);
     return DGSP_OK;

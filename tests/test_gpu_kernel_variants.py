@@ -131,3 +131,14 @@ def test_the_launched_kernel_by_name_is_the_adaptive_call(dg, law, N):
     X = torch.from_numpy(wl.dense_matrix(A.K, N, "normal", seed=N)).cuda()
     print(f"[case] launched kernel by name {law} N={N}", flush=True)
     assert torch.equal(dA.spmm(X), dA.spmm(X, algo=dg.RS_SR))
+
+
+@pytest.mark.parametrize("rows", [65536 * 2 - 3, 65536 * 2, 65536 * 2 + 5, 65536 * 3 + 70])
+def test_rounds_of_a_row_split_launch(dg, rows):
+    """One row a wave in the sequential kernel at N = 130, two at N = 100: launches of two to four rounds and their edges."""
+    lens = np.zeros(rows, dtype=np.int64)
+    lens[np.r_[0:7, rows // 2:rows // 2 + 9, rows - 5:rows]] = 2
+    A = wl.csr_from_lens(lens, K=50, seed=1, name="rounds")
+    for N in (100, 130):
+        _compare(dg, A, N, dg.RS_SR, True)
+    _compare(dg, A, 2, dg.RS_PR, False)

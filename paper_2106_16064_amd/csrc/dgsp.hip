@@ -633,11 +633,13 @@ int launch_nb_sr(const Problem& p) {
 // segmented scan over the lanes' open rows - with two lanes per entry (nb_sr_run_kernel), which reads a row of X in one
 // access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 156 / 156 -> 140 / 139 us, Zipf rows of 16 at N = 8 61 -> 58 us,
 // lognormal rows of 64 at N = 5 / 8 173 / 190 -> 143 / 179 us; a tie on small matrices.
-// Not for a small matrix whose long rows keep it from whole rows per wave (R-MAT 2^14 x 24 at N = 6 12.0 against 14.5 us).
+// Not for a small matrix whose rows it cannot keep whole per wave, as some are long (R-MAT 2^14 x 24 at N = 6 12.4 against
+// 13.6 us) or nothing is known of them: without statistics and with the entry count / a bound of it, drawn matrices of
+// 0.1 to 1 million entries run 3-11 / 12-25 % faster on the tiles, from there on 2-12 / 0-9 % slower.
 constexpr long long kRunNarrowNnzMin = 1000000, kRunNarrowRowMax = 1500;
 int launch_nb_pr(const Problem& p) {
     const int v = nb_pr_lane_width(p.N, p.switches);
-    const bool short_call = p.nnz >= 0 && p.nnz < kRunNarrowNnzMin && p.max_row > kRunNarrowRowMax;
+    const bool short_call = p.size >= 0 && p.size < kRunNarrowNnzMin && (p.max_row < 0 || p.max_row > kRunNarrowRowMax);
     if (v == 8 && p.N <= 8 && p.switches == 0 && p.ldy <= kBalancedLdyMax && !short_call) return launch_nb_sr_run(p);
     switch (v) {
         case 8: return launch_nb_pr_v<8, 1>(p);

@@ -736,7 +736,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     // the memory pipeline retires loads and stores in issue order, so a store in front of the gathers would put
     // its own round trip into their wait.
     float pending_val[V];
-    float pending_old[AXPBY ? V : 1];                    // scaled form: what the rows held, requested when their sums were ready
     unsigned pending_off = kOutOfRange;
     unsigned long long pending_first = 0ull;             // first element of the rows the pending store addresses
 #pragma unroll
@@ -747,11 +746,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                                                  kBufferFlags);
     };
     auto store_pending = [&]() {
-        if constexpr (AXPBY) {
-#pragma unroll
-            for (int i = 0; i < V; ++i)
-                pending_val[i] = sc.beta != 0.0f ? fmaf(sc.alpha, pending_val[i], sc.beta * pending_old[i]) : sc.alpha * pending_val[i];
-        }
         buffer_store_vec<V>(rows_descriptor(pending_first), pending_off, pending_val, second);
         pending_off = kOutOfRange;
     };
@@ -901,7 +895,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                     pending_first = first_elem; pending_off = off;
 #pragma unroll
                     for (int i = 0; i < V; ++i) pending_val[i] = val[i];
-                    if constexpr (AXPBY) { if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off, pending_old, second); }
+                    if constexpr (AXPBY) scale_into<V>(pending_val, yrows, off, sc, second);
                 } else {
                     buffer_store_vec<V>(yrows, off, val, second);            // plain form only
                 }
@@ -913,7 +907,9 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
             };
             write_rows(0);
             if constexpr (AXPBY) {
-                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile)
+                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile).
+                // The first batch's are waited for above: most tiles of long rows have no other, and holding them to the
+                // next tile's store made every wait of that tile's loads one for them (Zipf rows of 48 at N = 2 49 -> 55 us)
                 constexpr int F = V <= 2 ? 4 : 2;
                 for (int k = 1; k * kWave < nrows; k += F) {
                     float val[F][V], old[F][V]; unsigned off[F];
@@ -1105,7 +1101,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     // The first 64 row results of a step are stored one step later, behind the loads issued meanwhile (the memory
     // pipeline retires loads and stores in issue order: a store in front of the gathers adds its round trip to their wait).
     float pending_val[V];
-    float pending_old[AXPBY ? V : 1];                    // scaled form: what the rows held, requested when their sums were ready
     unsigned pending_off = kOutOfRange;
     unsigned long long pending_first = 0ull;             // first element of the rows the pending store addresses
 #pragma unroll
@@ -1116,11 +1111,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
                                                  kBufferFlags);
     };
     auto store_pending = [&]() {
-        if constexpr (AXPBY) {
-#pragma unroll
-            for (int i = 0; i < V; ++i)
-                pending_val[i] = sc.beta != 0.0f ? fmaf(sc.alpha, pending_val[i], sc.beta * pending_old[i]) : sc.alpha * pending_val[i];
-        }
         buffer_store_vec<V>(rows_descriptor(pending_first), pending_off, pending_val, second);
         pending_off = kOutOfRange;
     };
@@ -1286,7 +1276,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
                     pending_first = first_elem; pending_off = off;
 #pragma unroll
                     for (int i = 0; i < V; ++i) pending_val[i] = val[i];
-                    if constexpr (AXPBY) { if (sc.beta != 0.0f) buffer_load_vec<V>(yrows, off, pending_old, second); }
+                    if constexpr (AXPBY) scale_into<V>(pending_val, yrows, off, sc, second);
                 } else {
                     buffer_store_vec<V>(yrows, off, val, second);            // plain form only
                 }
@@ -1298,7 +1288,9 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
             };
             write_rows(0);
             if constexpr (AXPBY) {
-                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile)
+                // the old values of F batches in flight together (a row end every other entry: five round trips fewer a tile).
+                // The first batch's are waited for above: most tiles of long rows have no other, and holding them to the
+                // next tile's store made every wait of that tile's loads one for them (Zipf rows of 48 at N = 2 49 -> 55 us)
                 constexpr int F = V <= 2 ? 4 : 2;
                 for (int k = 1; k * kWave < nrows; k += F) {
                     float val[F][V], old[F][V]; unsigned off[F];

@@ -251,9 +251,11 @@ inline double lines_per_row(long long cols, long long ldx) {
 // 40 MB, N = 1 to 128, 65 536 to 524 288 rows (`occ`: share of the wave slots in use, `part`: lines per wave / 64):
 //   a step in step      0.1 us + 0.4 us * (1 - occ) + part * (2.6 us * occ + 1.5 us * missed)
 //   a line out of step  6.5 ps + 12.5 ps * missed^2
-// Rows of 30, X of 3 / 5 / 7 / 10 / 16 MB, in step against out of step: N = 1 82 / 89 / 92 / 97 / 114 against
-// 86 / 105 / 134 / 178 / 222 us, N = 4 42 / 61 / 79 / 98 / 115 against 36 / 67 / 112 / 177 / 219 us; rows of 40 at N = 33
-// (16 MB) 81 against 126 us, Poisson rows of 12 there 51 against 46 us; 262 144 rows of 60 at N = 1 (5 MB) 184 against 106 us.
+// Rows of 30, X of 3 / 5 / 7 / 10 / 16 MB, in step against out of step: 262 144 rows at N = 1 45 / 57 / 59 / 61 / 74 against
+// 44 / 54 / 68 / 89 / 110 us, 131 072 rows at N = 4 34 / 54 / 56 / 57 / 59 against 25 / 30 / 35 / 45 / 55 us; 131 072 rows of
+// 40 at N = 33 (17 MB) 86 against 142 us, Poisson rows of 12 there 56 against 49 us; 262 144 rows of 60 at N = 1 (5 MB)
+// 188 against 106 us.  On 3665 drawn matrices the choice loses 2.7 % to the better of the two (always out of step 3.5 %,
+// always in step 221 %); 9 % of them lose more than 10 %, mostly X of 6 to 12 MB.
 constexpr double kWaveSlotsPerCu = 32.0;
 inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
     const double x_bytes = (double)p.K * p.N * 4.0;
@@ -275,12 +277,13 @@ inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
 }
 
 // log2 of the lanes that share a row's entries (H) when 2^logG lanes span its columns.  A wave's rows should fit one
-// round of the LDS tile: with 64 rows of 27 a round holds 19 of them and the other lanes wait (27-point stencil on 128^3
-// at N = 1: H = 1 153 us, H = 4 121 us; N = 4 190 -> 133 us).  A matrix that leaves the machine half empty is split
-// further while a lane keeps two entries (4500 rows of 30: H = 4 6.5 us, H = 8 3.8 us), uneven rows for the longest one's
-// sake (32 768 lognormal rows of 8 at N = 4: H = 4 / 8 / 16 12.1 / 8.5 / 7.4 us).
+// round of the LDS tile: with 64 rows of 27 a round holds 19 of them and the other lanes wait (27-point stencil on 128^3,
+// H = 1 / 2 / 4 / 8: N = 1 117 / 100 / 94 / 119 us, N = 4 174 / 132 / 114 / 125 us).  A matrix that leaves the machine half
+// empty is split further while a lane keeps two entries (4500 rows of 30: H = 2 / 4 / 8 4.9 / 3.8 / 3.7 us), uneven rows for
+// the longest one's sake (32 768 lognormal rows of 8 at N = 4: H = 4 / 8 / 16 15.7 / 9.9 / 7.8 us).  On 3665 drawn matrices
+// the choice loses 3.1 % to the best of H = 1 ... 16 (H = 1 92 %); 10 % of them lose more than 10 %.
 // dense-row loads in flight per lane out of step; at one column per lane eight are as many registers as two at four
-// columns (stencil 128^3 at N = 1: 125 -> 121 us)
+// columns (stencil 128^3 at N = 1: 94 us with four or eight)
 constexpr int rs_sr_depth(int v) { return v == 1 ? 8 : 4; }
 constexpr double kRowGroupCvMax = 0.6;
 inline int rs_sr_split_log2(const Problem& p, int logG) {
@@ -350,14 +353,16 @@ inline SrShape rs_sr_shape(const Problem& p) {
 // no atomics, and its entries arrive coalesced through LDS; it does nothing against rows longer than the others but give a
 // row more lanes.
 //   Rows more or less alike, up to four columns: equal runs of rows are equal shares of entries.  Against rs_pr: 4096 rows
-//   of 8 at N = 4 5.7 -> 3.7 us, 20 000 rows of 100 at N = 1 16 -> 10 us; against nb_pr: 27-point stencil on 128^3 at
-//   N = 1 / 4 129 / 147 -> 95 / 114 us, 776 379 rows of 22 over 27 098 columns at N = 1 86 -> 70 us, 187 500 Poisson rows of
-//   8 at N = 4 22 -> 14 us; 262 144 rows of 64 at N = 1 break even.
+//   of 8 at N = 4 5.9 -> 3.9 us, 20 000 rows of 100 at N = 1 15.4 -> 10.3 us; against nb_pr: 27-point stencil on 128^3 at
+//   N = 1 / 4 122 / 137 -> 94 / 114 us, 776 379 rows of 22 over 27 098 columns at N = 1 79 -> 60 us, 187 500 Poisson rows of
+//   8 at N = 4 17.7 -> 12.9 us; 262 144 rows of 64 at N = 1 break even (85 us).
 //   Small matrices with uneven rows: the balanced kernels' start (searches, row marks, perhaps two launches) is most of
 //   the call, and the longest row is `steps` rounds of loads for its lanes.  Lognormal rows of 8, row groups against the
-//   better of nb_sr and nb_pr: 8192 rows at N = 1 / 4 / 16 / 33 3.8 / 3.9 / 5.3 / 6.7 against 6.7 / 6.4 / 6.8 / 9.3 us,
-//   65 536 rows at N = 1 / 4 / 8 / 16 9.3 / 10.7 / 16.5 / 31 against 10.0 / 12.9 / 16.7 / 16.8 us; crossover near 600 000
-//   entries at N <= 4 (150 000 rows of 8: 15 against 13 us).
+//   better of nb_sr and nb_pr: 8192 rows at N = 1 / 4 / 16 / 33 4.0 / 4.1 / 5.4 / 6.4 against 6.9 / 6.6 / 7.0 / 9.5 us,
+//   65 536 rows at N = 1 / 4 / 8 / 16 8.7 / 10.7 / 16 / 35 against 8.5 / 10.2 / 10.3 / 13.8 us; crossover near 500 000
+//   entries at N <= 4 (150 000 rows of 8: 20 against 13.6 us).
+//   Where row groups took the rules' kernel's place on 1276 drawn matrices, that kernel took 20 % longer on average; on 6 %
+//   of them it would have been more than 10 % faster.
 constexpr long long kSmallUnevenNnz = 600000, kTinyNnz = 130000;
 inline bool row_groups_suit(const Problem& p) {
     if (p.switches != 0 || p.nnz <= 0 || p.M == 0 || p.cv_row < 0.0 || p.max_row < 0) return false;
@@ -467,8 +472,9 @@ constexpr long long kNbPrStreamNnzMin = 6000000;
 // Do the chunks of a balanced kernel take whole rows?  That saves the atomics and the prepare launch (6 us with the gap
 // behind it), and the wave with the longest row ends later: by up to `per_us` entries a microsecond, as it runs on when the
 // others are through - behind a part of the time they take, as long as the call is short.  `lines`: lines of X per entry.
-// 100 000 lognormal rows of 6 at N = 6 20.3 -> 13.6 us, 20 001 of 10 at N = 32 16 -> 11 us; not taken: 100 000 Zipf rows
-// of 50 at N = 33 (141 against 185 us), 100 000 lognormal rows of 20 at N = 33 (64 against 73 us).
+// 100 000 lognormal rows of 6 at N = 6 18.3 -> 11.7 us, 20 001 of 10 at N = 32 11.6 -> 8.6 us; not taken: 100 000 Zipf rows
+// of 50 at N = 33 (139 against 186 us), 100 000 lognormal rows of 20 at N = 33 (65 against 78 us).  On 2036 drawn matrices the
+// choice loses 1.6 % to the better of the two (never 8.8 %, always 20.7 %); 5 % of them lose more than 10 %.
 inline bool snap_rows(const Problem& p, unsigned groups, double share_part, double per_us, double lines) {
     if (p.nnz < 0 || p.max_row < 0) return false;
     const double share = (double)(p.nnz + (long long)p.M) / ((double)groups * kWavesPerBlock);
@@ -561,7 +567,7 @@ int launch_nb_sr_pick(const Problem& p) {
 }
 
 // Four columns and more.  Items a wave takes at least: fewer and the two searches that open a chunk outweigh it
-// (4096 rows of 8 at N = 32: 5.9 / 6.7 / 8.3 us with 64 / 128 / 256; 20 001 uneven rows of 10: 14.4 / 11.4 / 12.2 us).
+// (4096 rows of 8 at N = 32: 6.2 / 6.8 / 8.3 us with 64 / 128 / 256; 20 001 uneven rows of 10: 9.6 / 8.7 / 9.6 us).
 constexpr long long kRunItems = 128;
 
 template <int LOGG, bool XBUF>
@@ -601,10 +607,10 @@ template <bool XBUF>
 int launch_nb_sr_run_x(const Problem& p) {
     // N a multiple of 64 from 128 on: column blocks of 64, so that the rows of X that many matrix rows share compete for
     // the L2 with a quarter-kilobyte each instead of N * 4 bytes.  Blocks of 32 (DGSP_ABL_COLUMN_BLOCKS_32) halve that once
-    // more for one more pass over A.  What that is worth hangs on how many entries name columns between the L2's and twice
-    // the L2's capacity, which no statistic here tells: with N = 64 / 128 R-MAT 2^20 x 16 554 / 992 -> 502 / 1025 us, but
-    // the same rows with columns of other laws, uniform to very uneven, 5-8 % slower, R-MAT 2^17 x 32 78 / 148 -> 86 / 172 us
-    // and R-MAT 2^18 x 32 170 / 363 -> 155 / 337 us.
+    // more for one more pass over A.  What that is worth hangs on how many entries name columns whose rows one layout keeps
+    // in the L2 and the other does not, and no statistic here tells: at N = 64 / 128 R-MAT 2^20 x 16 gains 9-15 / -3 to 9 %
+    // (five GPUs), 2^18 x 32 9-19 / 3-7 %; 2^17 x 32 loses 9 / 15 %, 2^20 x 4 10 / -5 %, the rows of R-MAT 2^20 x 16 with
+    // independent columns of other laws 5-9 / 8-11 %, Zipf rows of 64 with uniform columns 0-3 %.
     SrColumns cols = sr_columns(p.N, 4, p.N >= 128);
     if (p.N % 32 == 0 && p.N >= 64 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)) cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
     switch (cols.logG) {
@@ -631,8 +637,9 @@ int launch_nb_sr(const Problem& p) {
 
 // Five to eight columns without a comparison switch: the same scheme - consecutive entries summed in a lane, one
 // segmented scan over the lanes' open rows - with two lanes per entry (nb_sr_run_kernel), which reads a row of X in one
-// access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 156 / 156 -> 140 / 139 us, Zipf rows of 16 at N = 8 61 -> 58 us,
-// lognormal rows of 64 at N = 5 / 8 173 / 190 -> 143 / 179 us; a tie on small matrices.
+// access instead of two: R-MAT 2^20 x 16 at N = 5 / 8 158 / 157 -> 140 / 137 us, Zipf rows of 16 at N = 8 57 -> 52 us,
+// lognormal rows of 64 at N = 5 / 8 174 / 189 -> 144 / 179 us.  On 349 drawn matrices the choice loses 1.0 % to the better of
+// the two (always tiles 12.4 %, never 1.9 %).
 // Not for a small matrix whose rows it cannot keep whole per wave, as some are long (R-MAT 2^14 x 24 at N = 6 12.4 against
 // 13.6 us) or nothing is known of them: without statistics and with the entry count / a bound of it, drawn matrices of
 // 0.1 to 1 million entries run 3-11 / 12-25 % faster on the tiles, from there on 2-12 / 0-9 % slower.

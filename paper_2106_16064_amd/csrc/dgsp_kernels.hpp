@@ -167,9 +167,9 @@ __global__ __launch_bounds__(kBlock) void rs_pr_kernel(int M, long long K, int N
 // 64 / (G H) rows fit one round and every lane walks in it.  Neighbouring lanes
 // hold neighbouring rows: on a stencil or band their gathers fall into the same
 // few lines of X, which costs the address unit a fraction of what one row's
-// scattered columns cost.  27-point stencil on 128^3 at N = 1: 16 rows, H = 4:
-// 95 us (5.0 TB/s), with H = 1 153 us, through the balanced parallel kernel 129 us;
-// N = 4 190 -> 115 us, N = 8 200 -> 155 us.
+// scattered columns cost.  27-point stencil on 128^3, one lane per row and column with its loads
+// one after the other against H lanes with all of a round's loads at once: N = 1 154 -> 94 us (H = 4, 5.0 TB/s; through the
+// balanced parallel kernel 122 us), N = 4 188 -> 114 us, N = 8 198 -> 145 us.
 // Bound by: HBM streams on banded matrices; the lines gathered from X, out of
 // the L1's and L2's misses, elsewhere.
 
@@ -1681,8 +1681,9 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // Bound by: what the L2s have to fetch of X (a probe that only gathers rows of X tops out at 7.5 TB/s of L2 misses),
 // and for that the walk has to be short of vector instructions: a wave instruction occupies its SIMD for four cycles,
 // and the walk with row state per lane group that this one replaces spent about 45 of them per step and waited for
-// every single load.  Measured, that walk against this one: R-MAT 2^20 x 16 at N = 8 / 16 / 32 / 128: 196 / 224 / 302 /
-// 1029 us -> 139 / 181 / 250 / 993 us; 20 001 uneven rows of 10 at N = 32: 25 -> 12 us; 65 536-vertex R-MAT at N = 41: 65 -> 33 us.
+// every single load.  Measured, that walk against this one, whole calls: R-MAT 2^20 x 16 at N = 8 / 16 / 32 / 128: 196 /
+// 224 / 302 / 1024 us -> 137-142 / 174 / 237-269 / 985-1100 us (they differ between GPUs and processes); 20 001 uneven
+// rows of 10 at N = 32: 25 -> 9 us; 65 536-vertex R-MAT at N = 41: 65 -> 31 us.
 //
 // SNAP (host: the longest row is short against a wave's share): a row belongs wholly to the chunk that holds its
 // first item, so nothing is added to memory, the prepare launch falls away and the result is the same from run to
@@ -2028,8 +2029,8 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
 // workgroup.  Against plain stores of the 32-bit arrays, whole calls: 20 001 rows of 10 18.5 -> 18.7 us, 200 001 rows of 10
 // 27.1 -> 26.4 us, 27-point stencil on 128^3 186 us in both forms.
 // Bound by the HBM stream on large matrices and by the launch and the host's wait on small ones.  Against two conversions, a
-// clearing launch, a pass with one wave per 64 rows and a copy back, int64 columns: 20 001 rows of 10 66 -> 22 us, 27-point
-// stencil on 128^3 966 -> 189 us (3.6 TB/s of indices read and written), R-MAT 2^20 x 16 1858 -> 59 us.
+// clearing launch, a pass with one wave per 64 rows and a copy back, int64 columns: 20 001 rows of 10 66 -> 19 us, 27-point
+// stencil on 128^3 966 -> 186 us (3.6 TB/s of indices read and written), R-MAT 2^20 x 16 1858 -> 56 us.
 constexpr int kStatBlocks = 1024;
 constexpr int kStatWords = 8;          // sum len^2, max len, min len, rows with a span, sum of spans, decreasing pointers, descents at row starts, descents
 constexpr int kStatResultWords = kStatWords + 2;       // and rowptr[0], rowptr[M]

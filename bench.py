@@ -706,7 +706,7 @@ def run_layouts(args):
     from paper_2106_16064_amd import workloads as wl
     os.makedirs(RESULTS_DIR, exist_ok=True)
     path = os.path.join(RESULTS_DIR, args.out or "bench_layouts.jsonl")
-    variants = {"blocks_of_64_on_xcds (ships at N >= 128)": 0, "blocks_of_64_any_xcd": dg.ABL_BLOCKS_OFF_XCDS,
+    variants = {"blocks_of_64_on_xcds": 0, "blocks_of_64_any_xcd": dg.ABL_BLOCKS_OFF_XCDS,
                 "blocks_of_32_on_xcds": dg.ABL_COLUMN_BLOCKS_32,
                 "blocks_of_32_any_xcd": dg.ABL_COLUMN_BLOCKS_32 | dg.ABL_BLOCKS_OFF_XCDS}
     cells = 0

@@ -418,7 +418,9 @@ int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz,
  *   DGSP_ABL_COLUMN_BLOCKS_32    the balanced sequential kernel with column blocks of 32 dense columns (one
  *                                128-byte line of a row of X per entry and block) instead of 64, where N is a
  *                                multiple of 32 from 64 on (ignored elsewhere): more passes over the sparse
- *                                matrix against a smaller slice of X per pass.
+ *                                matrix against a smaller slice of X per pass.  The calls of this header launch
+ *                                blocks of 64; the Python binding measures a matrix's columns and takes blocks
+ *                                of 32 at N = 64 and 128 where that pays.
  *   DGSP_ABL_BLOCKS_OFF_XCDS     the balanced sequential kernel with its column blocks as a second grid
  *                                dimension, any XCD taking any block.  DGSP_NB_SR itself, when N >= 128 makes
  *                                2 or 4 column blocks, lets every XCD work on one block only, so that an L2

@@ -43,7 +43,15 @@ class Features(ctypes.Structure):
                 ("max_row", ctypes.c_int64), ("min_row", ctypes.c_int64), ("col_span", ctypes.c_double)]
 
     def as_dict(self):
-        return {k: getattr(self, k) for k, _ in self._fields_}
+        return {k: getattr(self, k) for k, _ in Features._fields_}
+
+
+class MatrixFeatures(Features):
+    """The statistics that a ``DeviceCsr`` holds: ``Features``, and what column blocks half as wide would save
+    (``dgsp_internal_stats_t``; negative: not measured yet).  The latter is not part of the C-ABI: the products of this
+    module measure it when one of a width that it matters to first asks for it, of large matrices with very uneven rows,
+    and hand it to the library.  That product waits for its stream once."""
+    _fields_ = [("saved_share", ctypes.c_double)]
 
 
 class Thresholds(ctypes.Structure):
@@ -212,11 +220,7 @@ def dgsp_spmm_csr_i64(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, works
 
 def dgsp_spmm_csr_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features=None, stream=None):
     """One step of the multiplication (measurement aid): PHASE_PREPARE, PHASE_MAIN or PHASE_ALL."""
-    _check_device_tensors(M, K, N, rowptr, colidx, vals, X, Y)
-    rc = lib().dgsp_spmm_csr_phase(M, K, N, int(nnz), _ptr(rowptr), _ptr(colidx), _ptr(vals), _ptr(X), _ptr(Y),
-                                   int(algo), int(phase), ctypes.byref(features) if features is not None else None,
-                                   _stream(stream))
-    _check(rc, "dgsp_spmm_csr_phase")
+    (_native or native()).spmm_csr_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, stream)
 
 
 def dgsp_spmm_csr_ld(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo=AUTO, features=None, stream=None):
@@ -374,7 +378,7 @@ class DeviceCsr:
         self.rowptr = torch.from_numpy(A.rowptr).to(device)
         self.colidx = torch.from_numpy(A.colidx).to(device)
         self.vals = torch.from_numpy(A.vals).to(device)
-        self.features = dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx)
+        self.features = MatrixFeatures(**dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict(), saved_share=-1.0)
         self.tuned = {}        # N -> kernel found fastest by autotune()
 
     @classmethod
@@ -382,13 +386,13 @@ class DeviceCsr:
         """Wraps CSR arrays that already live on the GPU (int32 ``rowptr`` / ``colidx``, float32 ``vals``; other
         integer or float types are converted once).  The row statistics are computed on the device, from work on the
         current stream that the call waits for: the matrix can be used on any stream once it returns."""
-        f = Features()
+        f = MatrixFeatures()
         return cls._taken((_native or native()).csr_from_arrays(int(M), int(K), rowptr, colidx, vals, f), f)
 
     @classmethod
     def from_torch_sparse_csr(cls, t):
         """From a ``torch.sparse_csr_tensor`` on the GPU."""
-        f = Features()
+        f = MatrixFeatures()
         return cls._taken((_native or native()).csr_from_tensor(t, f), f)
 
     @classmethod

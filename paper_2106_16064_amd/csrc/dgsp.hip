@@ -72,8 +72,9 @@ struct Hints {
     int64_t max_row = -1;
     int64_t size = -1;          // a bound of the entry count
     bool chosen = false;        // the kernel is the library's choice from these statistics, not the caller's
+    double saved_share = 0.0;   // what column blocks half as wide would save (kSavedShareMin); 0 = unknown
     Hints() = default;
-    explicit Hints(const dgsp_features_t* f) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
+    explicit Hints(const dgsp_features_t* f, double saved = 0.0) : saved_share(saved) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
 };
 
 struct Problem {
@@ -87,6 +88,7 @@ struct Problem {
     double cv_row = -1.0;    // coefficient of variation of the row lengths; < 0 = unknown
     long long max_row = -1;  // entries of the longest row; < 0 = unknown
     long long size = -1;     // the entry count or, for launch geometry, a bound of it; < 0 = unknown
+    double saved_share = 0.0;  // see Hints
     int switches = 0;        // DGSP_ABL_* (measurement aids)
     bool scaled = false;     // Y = alpha * A X + beta * Y instead of Y = A X
     float alpha = 1.0f, beta = 0.0f;
@@ -570,6 +572,28 @@ int launch_nb_sr_pick(const Problem& p) {
 // (4096 rows of 8 at N = 32: 6.2 / 6.8 / 8.3 us with 64 / 128 / 256; 20 001 uneven rows of 10: 9.6 / 8.7 / 9.6 us).
 constexpr long long kRunItems = 128;
 
+// N a multiple of 64 from 128 on: column blocks of 64, so that the rows of X that many matrix rows share compete for the L2
+// with a quarter-kilobyte each instead of N * 4 bytes.
+// At N = 64 and 128 blocks of 32 - two or four of them, every XCD on one, one 128-byte line of a row of X per entry and
+// block - halve that once more, for one more pass over A.  They save the entries whose row of X an L2 keeps among its last
+// 32768 lines but not among its last 16384 pairs of lines, a share that is measured on the columns (saved_share()).  Where it
+// was 0.1 and more they won on every matrix with four million entries and six a row (blocks of 64 against 32, N = 64 / 128:
+// R-MAT 2^20 x 16 556 / 1080 -> 504 / 980 us, on another GPU 554 / 992 -> 502 / 1025 us; 2^20 x 32, share 0.13, 15 / 13 %;
+// 2^18 x 32, 0.15, 19 / 3 %; columns of that law in rows of another, 0.13, 11 / 10 %).  Below they lose up to 10 %: the rows of
+// R-MAT 2^20 x 16 with other columns, 0.02 to 0.06, 4-9 / 5-11 %, Zipf rows of 64 with uniform columns, 0.06, 0-3 / 0-3 %; and
+// with short rows, whose ends are met once a block, or where the rest of a small X is in the L2 anyway (R-MAT 2^20 x 4 10 / -5 %,
+// 2^16 x 64 8 / 20 %).  Eight blocks (N = 256) leave every XCD the whole matrix: 2081 -> 2302 us.
+constexpr double kSavedShareMin = 0.1, kColumnsCvMin = 4.0, kColumnsAvgMin = 6.0;
+constexpr long long kColumnsNnzMin = 4000000;
+inline bool column_share_matters(const dgsp_features_t& f) {
+    return f.nnz >= kColumnsNnzMin && f.cv_row >= kColumnsCvMin && f.avg_row >= kColumnsAvgMin;
+}
+inline SrColumns nb_sr_run_columns(int64_t N, double saved_share, int switches) {
+    const bool wanted = saved_share >= kSavedShareMin && (N == 64 || N == 128);
+    if (N % 32 == 0 && N >= 64 && (wanted || (switches & DGSP_ABL_COLUMN_BLOCKS_32))) return {3, 32, (unsigned)(N / 32)};
+    return sr_columns(N, 4, N >= 128);
+}
+
 template <int LOGG, bool XBUF>
 int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     const unsigned col_blocks = cols.blocks;
@@ -605,14 +629,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
 
 template <bool XBUF>
 int launch_nb_sr_run_x(const Problem& p) {
-    // N a multiple of 64 from 128 on: column blocks of 64, so that the rows of X that many matrix rows share compete for
-    // the L2 with a quarter-kilobyte each instead of N * 4 bytes.  Blocks of 32 (DGSP_ABL_COLUMN_BLOCKS_32) halve that once
-    // more for one more pass over A.  What that is worth hangs on how many entries name columns whose rows one layout keeps
-    // in the L2 and the other does not, and no statistic here tells: at N = 64 / 128 R-MAT 2^20 x 16 gains 9-15 / -3 to 9 %
-    // (five GPUs), 2^18 x 32 9-19 / 3-7 %; 2^17 x 32 loses 9 / 15 %, 2^20 x 4 10 / -5 %, the rows of R-MAT 2^20 x 16 with
-    // independent columns of other laws 5-9 / 8-11 %, Zipf rows of 64 with uniform columns 0-3 %.
-    SrColumns cols = sr_columns(p.N, 4, p.N >= 128);
-    if (p.N % 32 == 0 && p.N >= 64 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)) cols = SrColumns{3, 32, (unsigned)(p.N / 32)};
+    const SrColumns cols = nb_sr_run_columns(p.N, p.saved_share, p.switches);
     switch (cols.logG) {
         case 0: return launch_nb_sr_run_v<0, XBUF>(p, cols);
         case 1: return launch_nb_sr_run_v<1, XBUF>(p, cols);
@@ -717,7 +734,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     if (hints.chosen) algo = launched_algo(p, algo);
     switch (algo) {
@@ -750,44 +767,50 @@ extern "C" int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz, c
     return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream);
 }
 
-extern "C" int dgsp_spmm_csr_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
-                                   const int32_t* colidx, const float* vals, const float* X, float* Y, int algo,
-                                   int phase, const dgsp_features_t* features, void* stream) {
+extern "C" int dgsp_internal_spmm_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
+                                        const float* vals, const float* X, float* Y, int algo, int phase,
+                                        const dgsp_features_t* features, double saved_share, void* stream) {
     if (algo < DGSP_RS_SR || algo > DGSP_NB_PR) return DGSP_ERR_INVALID_ARG;
     if (phase < DGSP_PHASE_ALL || phase > DGSP_PHASE_MAIN) return DGSP_ERR_INVALID_ARG;
     if (features && nnz < 0) nnz = features->nnz;
     return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, phase,
-               Hints(features));
+               Hints(features, saved_share));
+}
+
+extern "C" int dgsp_spmm_csr_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
+                                   const int32_t* colidx, const float* vals, const float* X, float* Y, int algo,
+                                   int phase, const dgsp_features_t* features, void* stream) {
+    return dgsp_internal_spmm_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, 0.0, stream);
+}
+
+extern "C" int dgsp_internal_spmm_view(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
+                                       const float* vals, const float* X, int64_t ldx, float* Y, int64_t ldy,
+                                       const float* alpha_beta, int algo, const dgsp_features_t* features, double saved_share,
+                                       void* stream) {
+    if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
+    if (features && nnz < 0) nnz = features->nnz;
+    Hints hints(features, saved_share);
+    if (algo == DGSP_AUTO && features && N >= 1) {
+        algo = library_choice(dgsp_select_algo(features, N), ldy);
+        hints.chosen = true;
+    }
+    const Scaling sc{alpha_beta ? alpha_beta[0] : 1.0f, alpha_beta ? alpha_beta[1] : 0.0f};
+    return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL,
+               hints, 0, ldx, ldy, alpha_beta ? &sc : nullptr);
 }
 
 extern "C" int dgsp_spmm_csr_ld(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
                                 const int32_t* colidx, const float* vals, const float* X, int64_t ldx, float* Y,
                                 int64_t ldy, int algo, const dgsp_features_t* features, void* stream) {
-    if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
-    if (features && nnz < 0) nnz = features->nnz;
-    Hints hints(features);
-    if (algo == DGSP_AUTO && features && N >= 1) {
-        algo = library_choice(dgsp_select_algo(features, N), ldy);
-        hints.chosen = true;
-    }
-    return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL,
-               hints, 0, ldx, ldy);
+    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, nullptr, algo, features, 0.0, stream);
 }
 
 extern "C" int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
                                    const int32_t* colidx, const float* vals, const float* X, int64_t ldx, float* Y,
                                    int64_t ldy, float alpha, float beta, int algo, const dgsp_features_t* features,
                                    void* stream) {
-    if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
-    if (features && nnz < 0) nnz = features->nnz;
-    Hints hints(features);
-    if (algo == DGSP_AUTO && features && N >= 1) {
-        algo = library_choice(dgsp_select_algo(features, N), ldy);
-        hints.chosen = true;
-    }
-    const Scaling sc{alpha, beta};
-    return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL,
-               hints, 0, ldx, ldy, &sc);
+    const float factors[2] = {alpha, beta};
+    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, factors, algo, features, 0.0, stream);
 }
 
 extern "C" int dgsp_spmm_csr_ablation(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
@@ -813,17 +836,23 @@ extern "C" int dgsp_spmm_csr_ablation(int64_t M, int64_t K, int64_t N, int64_t n
                Hints(features), switches);
 }
 
-extern "C" int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features,
-                                  const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X,
-                                  float* Y, int* chosen, void* stream) {
+extern "C" int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features, double saved_share,
+                                       const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X,
+                                       float* Y, int* chosen, void* stream) {
     if (!features) return DGSP_ERR_INVALID_ARG;
     if (features->M != M || features->nnz < 0) return DGSP_ERR_INVALID_ARG;
     int algo = (N >= 1) ? library_choice(dgsp_select_algo(features, N), N) : DGSP_NB_PR;
     if (algo < 0) return DGSP_ERR_INVALID_ARG;
     if (chosen) *chosen = algo;
-    Hints hints(features);
+    Hints hints(features, saved_share);
     hints.chosen = true;
     return run(M, K, N, features->nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
+}
+
+extern "C" int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features,
+                                  const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X,
+                                  float* Y, int* chosen, void* stream) {
+    return dgsp_internal_spmm_auto(M, K, N, features, 0.0, rowptr, colidx, vals, X, Y, chosen, stream);
 }
 
 // ---------------------------------------------------------------- 64-bit row pointers
@@ -1101,6 +1130,18 @@ bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, 
     return hipStreamSynchronize(st) == hipSuccess && seen();
 }
 
+// the first `words` result words of a launch that announced itself in word kStatResultWords, or, without pinned words, left
+// them in the scratch
+int fetch_result(const StatisticsPool::Slot& slot, unsigned long long* h, int words, hipStream_t st) {
+    if (slot.host) {
+        if (!wait_for_ticket(slot.host + kStatResultWords, slot.ticket, st)) return DGSP_ERR_LAUNCH;
+        for (int w = 0; w < words; ++w) h[w] = __atomic_load_n(slot.host + w, __ATOMIC_RELAXED);
+        return DGSP_OK;
+    }
+    if (hipMemcpyAsync(h, slot.scratch->result, sizeof(*h) * (size_t)words, hipMemcpyDeviceToHost, st) != hipSuccess) return DGSP_ERR_LAUNCH;
+    return hipStreamSynchronize(st) == hipSuccess ? DGSP_OK : DGSP_ERR_LAUNCH;
+}
+
 void finish_features(dgsp_features_t& f, unsigned long long sq, unsigned long long rows, unsigned long long span) {
     f.avg_row = (double)f.nnz / (double)f.M;
     const unsigned __int128 num = (unsigned __int128)sq * (unsigned __int128)f.M
@@ -1144,13 +1185,7 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
                        rowptr32, colidx32, slot.scratch, slot.host, slot.ticket);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     unsigned long long h[kStatResultWords];
-    if (slot.host) {
-        if (!wait_for_ticket(slot.host + kStatResultWords, slot.ticket, st)) return DGSP_ERR_LAUNCH;
-        for (int w = 0; w < kStatResultWords; ++w) h[w] = __atomic_load_n(slot.host + w, __ATOMIC_RELAXED);
-    } else {
-        if (hipMemcpyAsync(h, slot.scratch->result, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return DGSP_ERR_LAUNCH;
-        if (hipStreamSynchronize(st) != hipSuccess) return DGSP_ERR_LAUNCH;
-    }
+    if (const int rc = fetch_result(slot, h, kStatResultWords, st)) return rc;
     if (h[5] != 0 || h[kStatWords] != 0) return DGSP_ERR_INVALID_ARG;       // decreasing row pointers, rowptr[0] != 0
     f.nnz = (int64_t)h[kStatWords + 1];
     f.max_row = (int64_t)h[1]; f.min_row = (int64_t)h[2];
@@ -1196,6 +1231,58 @@ extern "C" int dgsp_internal_take_csr(int64_t M, int64_t K, int64_t entries, int
     if (index_bytes != 8 || !rowptr32 || (colidx && !colidx32)) return DGSP_ERR_INVALID_ARG;
     return features_from_csr_device<int64_t>(M, K, entries, static_cast<const int64_t*>(rowptr), static_cast<const int64_t*>(colidx),
                                              rowptr32, colidx32, true, out, (hipStream_t)stream);
+}
+
+// Good and Turing's estimate: among w entries the share that names a column met once is the share of further entries whose
+// column is not among those met, D of them.  An L2 of D places misses as often; the sample gives the pairs (D, share) at
+// three sizes, between which the share is taken as linear.
+extern "C" double dgsp_internal_saved_share(const uint64_t* counts) {
+    const double buckets = (double)(1 << kReuseBucketsLog2), rate = (double)(1 << kReuseRateLog2);
+    double at[kReuseLevels + 1] = {0.0}, share[kReuseLevels + 1] = {1.0};
+    for (int l = 0; l < kReuseLevels; ++l) {
+        // columns that share a bucket count as one, and not as met once
+        const double empty = std::fmax(1.0 - (double)counts[2 * l] / buckets, 1.0 / buckets);
+        at[l + 1] = -buckets * std::log(empty) * rate;
+        share[l + 1] = std::fmin((double)counts[2 * l + 1] / empty * rate / (double)((16 * kReuseThreads) << l), 1.0);
+    }
+    const auto missed = [&](double places) {
+        for (int l = 0; l < kReuseLevels; ++l)
+            if (at[l + 1] >= places && at[l + 1] > at[l]) return share[l] + (share[l + 1] - share[l]) * (places - at[l]) / (at[l + 1] - at[l]);
+        return share[kReuseLevels];
+    };
+    return std::fmax(missed(16384.0) - missed(32768.0), 0.0);
+}
+
+extern "C" int dgsp_internal_column_reuse(int64_t entries, const int32_t* colidx, uint64_t* counts, void* stream) {
+    if (entries < kReuseEntriesMin || !colidx || !counts) return DGSP_ERR_INVALID_ARG;
+    hipStream_t st = (hipStream_t)stream;
+    if (recording(st)) return DGSP_ERR_LAUNCH;
+    StatisticsPool::Slot slot;
+    if (!g_stat_pool.take(slot, true)) return DGSP_ERR_LAUNCH;
+    struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
+    constexpr int kCounts = 2 * kReuseLevels;
+    unsigned long long* out = slot.host ? slot.host : slot.scratch->result;
+    hipLaunchKernelGGL(column_reuse_kernel, dim3(1), dim3(kReuseThreads), 0, st, (long long)entries, colidx, out,
+                       slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
+    if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
+    unsigned long long h[kCounts];
+    if (const int rc = fetch_result(slot, h, kCounts, st)) return rc;
+    for (int i = 0; i < kCounts; ++i) counts[i] = h[i];
+    return DGSP_OK;
+}
+
+extern "C" int dgsp_internal_measure_columns(dgsp_internal_stats_t* stats, const int32_t* colidx, void* stream) {
+    if (!stats) return DGSP_ERR_INVALID_ARG;
+    stats->saved_share = 0.0;
+    if (!column_share_matters(stats->features)) return DGSP_OK;
+    uint64_t counts[2 * kReuseLevels];
+    if (const int rc = dgsp_internal_column_reuse(stats->features.nnz, colidx, counts, stream)) return rc;
+    stats->saved_share = dgsp_internal_saved_share(counts);
+    return DGSP_OK;
+}
+
+extern "C" int dgsp_internal_nb_sr_block(const dgsp_internal_stats_t* stats, int64_t N) {
+    return N < 4 ? (int)N : nb_sr_run_columns(N, stats ? stats->saved_share : 0.0, 0).cols_per_block;
 }
 
 extern "C" int dgsp_autotune(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,

@@ -2197,6 +2197,78 @@ __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long
     }
 }
 
+// ===========================================================================
+// how popular the columns are (for the width of the column blocks of nb_sr_run_kernel)
+// ===========================================================================
+// Counts distinct columns, and those met once, among 16384, 32768 and 65536 sampled entries: the first 1024, 2048 and 4096 of
+// 16 pieces, evenly spread.  Only columns whose hash falls into the lower half of its range are counted (saved_share(), host,
+// doubles the counts and allows for the columns that share a bucket): counts of columns, so half of them tell the share to
+// 0.003 to 0.008.  One workgroup, two bits per bucket in 64 KB of LDS, all loads at once: 10 us on R-MAT 2^20 x 16, 20 us
+// with the launch and the host's wait; the loads of 64 pieces in four batches and a word of LDS that every thread added to
+// had been 32 us.
+constexpr int kReuseLevels = 3, kReusePieces = 16, kReuseThreads = 1024, kReuseBucketsLog2 = 18, kReuseRateLog2 = 1;
+constexpr long long kReuseEntriesMin = 4 * kReuseThreads;              // a piece
+
+__global__ __launch_bounds__(kReuseThreads) void column_reuse_kernel(long long entries, const int* __restrict__ colidx,
+                                                                    unsigned long long* out, unsigned long long* announce,
+                                                                    unsigned long long ticket) {
+    constexpr int kWords = (1 << kReuseBucketsLog2) / 16;
+    constexpr int kOwn = kWords / kReuseThreads;
+    __shared__ unsigned table[kWords + kWave];                   // the words behind are for the columns that are not counted
+    __shared__ unsigned sums[kReuseLevels][2];
+    const int t = (int)threadIdx.x;
+    unsigned c[4][kReusePieces];
+#pragma unroll
+    for (int part = 0; part < 4; ++part)
+#pragma unroll
+        for (int q = 0; q < kReusePieces; ++q)
+            c[part][q] = (unsigned)colidx[(entries - kReuseEntriesMin) * q / (kReusePieces - 1) + part * kReuseThreads + t];
+    for (int i = 0; i < kOwn; ++i) table[t + i * kReuseThreads] = 0u;
+    if (t < kReuseLevels * 2) sums[t / 2][t % 2] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int level = 0; level < kReuseLevels; ++level) {
+#pragma unroll
+        for (int part = level == 0 ? 0 : 1 << (level - 1); part < 1 << level; ++part) {
+            unsigned at[kReusePieces], seen[kReusePieces], old[kReusePieces];
+#pragma unroll
+            for (int q = 0; q < kReusePieces; ++q) {
+                unsigned key = c[part][q] * 2654435761u;         // one product alone spreads neighbours too evenly
+                key = (key ^ (key >> 15)) * 2654435761u;
+                const bool counted = (key >> (32 - kReuseRateLog2)) == 0u;
+                const unsigned b = key >> (32 - kReuseRateLog2 - kReuseBucketsLog2);
+                at[q] = counted ? b >> 4 : (unsigned)(kWords + lane_id());
+                seen[q] = counted ? 1u << (2u * (b & 15u)) : 0u;
+                old[q] = atomicOr(&table[at[q]], seen[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kReusePieces; ++q)
+                if (old[q] & seen[q]) atomicOr(&table[at[q]], seen[q] << 1);
+        }
+        __syncthreads();
+        unsigned distinct = 0, once = 0;
+        for (int i = 0; i < kOwn; ++i) {
+            const unsigned w = table[t + i * kReuseThreads];
+            distinct += (unsigned)__popc(w & 0x55555555u);
+            once += (unsigned)__popc(w & 0x55555555u & ~(w >> 1));
+        }
+        unsigned both = distinct | once << 16;                   // at most 2^16 together in a wave's share of the table
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) both += (unsigned)__shfl_xor((int)both, m);
+        if (lane_id() == 0) {                                    // one a wave: 1024 adds to one word take 4 us
+            atomicAdd(&sums[level][0], both & 0xffffu);
+            atomicAdd(&sums[level][1], both >> 16);
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        for (int i = 0; i < kReuseLevels * 2; ++i)
+            __hip_atomic_store(out + i, (unsigned long long)sums[i / 2][i % 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        stores_done();
+        if (announce) __hip_atomic_store(announce, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // The same metrics with every row's columns looked at (rows whose columns are not ascending).
 // ws[0] sum of len^2, [1] max len, [2] min len, [3] non-empty rows whose span was taken,
 // [4] sum of (largest - smallest column + 1), [5] a row pointer decreased, [6] rowptr[0], [7] rowptr[M].

@@ -86,15 +86,15 @@ void* as_stream(PyObject* o) {
     return p;
 }
 
-// The statistics of a ctypes `Features` structure (None: there are none).
+// The statistics of a ctypes `Features` structure, or of the `MatrixFeatures` that a DeviceCsr holds (None: there are none).
 class FeaturesArg {
 public:
     explicit FeaturesArg(PyObject* o) {
         if (o == Py_None) return;
         Py_buffer view;
         if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Raised{};
-        const bool fits = view.len == (Py_ssize_t)sizeof(value_);
-        if (fits) memcpy(&value_, view.buf, sizeof(value_));
+        const bool fits = view.len == (Py_ssize_t)sizeof(value_) || view.len == (Py_ssize_t)sizeof(value_.features);
+        if (fits) memcpy(&value_, view.buf, (size_t)view.len);
         PyBuffer_Release(&view);
         if (!fits) {
             PyErr_SetString(PyExc_TypeError, "features must be a Features structure");
@@ -102,10 +102,16 @@ public:
         }
         given_ = true;
     }
-    const dgsp_features_t* get() const { return given_ ? &value_ : nullptr; }
+    const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
+    double saved_share() const { return value_.saved_share > 0.0 ? value_.saved_share : 0.0; }
+
+    // What narrower column blocks save is measured when the first product that could take them asks for it: a launch and a
+    // wait of 20 us on a matrix of four million entries or more, which fresh matrices of other widths are spared.  Kept in
+    // `o`.  While a graph is recorded nothing can be waited for: the product then takes the wider blocks.
+    void measure_for(int64_t N, PyObject* o, const at::Tensor& colidx, void* stream);
 
 private:
-    dgsp_features_t value_;
+    dgsp_internal_stats_t value_{};
     bool given_ = false;
 };
 
@@ -116,9 +122,10 @@ void* ptr(PyObject* o, const char* name) { return o == Py_None ? nullptr : ptr(a
 
 bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == at::kStrided; }
 
+bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
+
 void check_array(const at::Tensor& t, at::ScalarType type, const char* name, const char* type_name) {
-    if (!on_gpu(t) || t.scalar_type() != type || !t.is_contiguous())
-        fail(std::string(name) + " must be a contiguous " + type_name + " tensor on the GPU");
+    if (!is_array(t, type)) fail(std::string(name) + " must be a contiguous " + type_name + " tensor on the GPU");
 }
 
 void check_csr(int64_t M, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals) {
@@ -152,18 +159,34 @@ int unlocked(F&& call) {
     return rc;
 }
 
+void write_features(PyObject* o, const dgsp_internal_stats_t& f) {
+    Py_buffer view;
+    if (PyObject_GetBuffer(o, &view, PyBUF_WRITABLE) != 0) throw Raised{};
+    const bool fits = view.len == (Py_ssize_t)sizeof(f);
+    if (fits) memcpy(view.buf, &f, sizeof(f));
+    PyBuffer_Release(&view);
+    if (!fits) fail("features must be a MatrixFeatures structure");
+}
+
+void FeaturesArg::measure_for(int64_t N, PyObject* o, const at::Tensor& colidx, void* stream) {
+    if (!(value_.saved_share < 0.0) || (N != 64 && N != 128)) return;
+    if (!is_array(colidx, at::kInt) || colidx.numel() < value_.features.nnz) return;
+    const auto* columns = static_cast<const int32_t*>(ptr(colidx));
+    if (unlocked([&] { return dgsp_internal_measure_columns(&value_, columns, stream); }) == DGSP_OK) write_features(o, value_);
+}
+
 // ---------------------------------------------------------------- one product
 
 // Y = A X by a named kernel, or by the rules (DGSP_AUTO); returns the status and leaves the kernel run in `algo`
-int product(int64_t M, int64_t K, int64_t N, const dgsp_features_t* f, const at::Tensor& rowptr, const at::Tensor& colidx,
+int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Tensor& rowptr, const at::Tensor& colidx,
             const at::Tensor& vals, const at::Tensor& X, const at::Tensor& Y, int& algo, void* stream) {
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    if (algo == DGSP_AUTO) return dgsp_spmm_csr_auto(M, K, N, f, rp, ci, av, x, y, &algo, stream);
-    return dgsp_spmm_csr_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f, stream);
+    if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), f.saved_share(), rp, ci, av, x, y, &algo, stream);
+    return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), f.saved_share(), stream);
 }
 
 // M x N, or M elements when the dense operand is a vector.  A GPU tensor comes from the allocator directly: the dispatcher's
@@ -188,6 +211,10 @@ struct Csr {
         if (!features.get()) fail("the matrix has no features");
         check_csr(M, rowptr, colidx, vals);
     }
+    // before a product with X on the current stream (with its gradient, as wide); `o`: what holds the statistics
+    void measure_for(const at::Tensor& X, PyObject* o) {
+        features.measure_for(columns_of(X), o, colidx, c10::hip::getCurrentHIPStream().stream());
+    }
 };
 
 // on the current stream; called with the interpreter lock held
@@ -196,7 +223,7 @@ at::Tensor multiply(const Csr& A, const at::Tensor& X, int algo, bool vector_res
     at::Tensor Y = empty_result(A.M, N, vector_result, X);
     check_packed(A.M, A.K, N, X, Y);
     void* stream = c10::hip::getCurrentHIPStream().stream();
-    const int rc = unlocked([&] { return product(A.M, A.K, N, A.features.get(), A.rowptr, A.colidx, A.vals, X, Y, algo, stream); });
+    const int rc = unlocked([&] { return product(A.M, A.K, N, A.features, A.rowptr, A.colidx, A.vals, X, Y, algo, stream); });
     check_status(rc, "dgsp_spmm_csr_auto");
     return Y;
 }
@@ -217,7 +244,7 @@ struct ProductBackward : public torch::autograd::Node {
         TORCH_CHECK(on_gpu(G) && G.numel() == A.K * N, "the gradient must be a GPU tensor of M*N elements");
         const at::Tensor dX = empty_result(A.M, N, vector, G);
         int which = algo;
-        const int rc = product(A.M, A.K, N, A.features.get(), A.rowptr, A.colidx, A.vals, G, dX, which,
+        const int rc = product(A.M, A.K, N, A.features, A.rowptr, A.colidx, A.vals, G, dX, which,
                                c10::hip::getCurrentHIPStream().stream());
         TORCH_CHECK(rc == DGSP_OK, "dgsp_spmm_csr_auto: ", dgsp_status_string(rc), " (status ", rc, ")");
         return {dX};
@@ -231,18 +258,18 @@ struct CsrArrays { at::Tensor rowptr, colidx, vals; };
 
 // The arrays in the library's types and the statistics, which the call waits for.  int64 indices are narrowed by the
 // statistics' own launch.
-CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals, dgsp_features_t& f) {
+CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals,
+                   dgsp_internal_stats_t& stats) {
     at::NoGradGuard no_grad;
     CsrArrays out;
-    const auto plain = [&](const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); };
-    const bool wide = plain(rowptr, at::kLong) && plain(colidx, at::kLong) && M > 0 && colidx.numel() < INT32_MAX - 4096;
+    const bool wide = is_array(rowptr, at::kLong) && is_array(colidx, at::kLong) && M > 0 && colidx.numel() < INT32_MAX - 4096;
     out.rowptr = wide ? at::empty(rowptr.sizes(), rowptr.options().dtype(at::kInt)) : rowptr.to(at::kInt).contiguous();
     out.colidx = wide ? at::empty(colidx.sizes(), colidx.options().dtype(at::kInt)) : colidx.to(at::kInt).contiguous();
-    out.vals = plain(vals, at::kFloat) ? vals : vals.to(at::kFloat).contiguous();
+    out.vals = is_array(vals, at::kFloat) ? vals : vals.to(at::kFloat).contiguous();
     if (!on_gpu(out.rowptr) || !on_gpu(out.colidx) || out.rowptr.numel() != M + 1) fail("rowptr needs M+1 entries on the GPU");
+    stats = dgsp_internal_stats_t{{}, -1.0};                    // columns not looked at yet
     if (M == 0) {
-        f = dgsp_features_t{};
-        f.K = K;
+        stats.features.K = K;
         return out;
     }
     void* stream = c10::hip::getCurrentHIPStream().stream();
@@ -251,7 +278,7 @@ CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Ten
     const void* ci = ptr(wide ? colidx : out.colidx);
     auto* rp32 = static_cast<int32_t*>(ptr(out.rowptr));
     auto* ci32 = static_cast<int32_t*>(ptr(out.colidx));
-    check_status(unlocked([&] { return dgsp_internal_take_csr(M, K, entries, wide ? 8 : 4, rp, ci, rp32, ci32, &f, stream); }),
+    check_status(unlocked([&] { return dgsp_internal_take_csr(M, K, entries, wide ? 8 : 4, rp, ci, rp32, ci32, &stats.features, stream); }),
                  "dgsp_features_from_csr_device");
     return out;
 }
@@ -288,8 +315,9 @@ PyObject* set_error_type(PyObject* const* a, Py_ssize_t n) {
 // (M, K, features, rowptr, colidx, vals, X, algo) -> Y
 PyObject* multiply_new(PyObject* const* a, Py_ssize_t n) {
     want(n, 8);
-    const Csr A(a + 2, as_int(a[0]), as_int(a[1]));
+    Csr A(a + 2, as_int(a[0]), as_int(a[1]));
     const at::Tensor& X = as_tensor(a[6], "X");
+    A.measure_for(X, a[2]);
     return THPVariable_Wrap(multiply(A, X, (int)to_int(a[7]), false));
 }
 
@@ -310,7 +338,8 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
     want(n, 15);
     const at::Tensor& X = as_tensor(a[0], "X");
     if (!only_reverse_mode(X)) Py_RETURN_NONE;
-    const Csr A(a + 5, as_int(a[3]), as_int(a[4]));
+    Csr A(a + 5, as_int(a[3]), as_int(a[4]));
+    A.measure_for(X, a[5]);
     const bool vector = X.dim() == 1;
     at::Tensor Y;
     {
@@ -318,21 +347,13 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
         Y = multiply(A, X.to(at::kFloat).contiguous(), (int)to_int(a[1]), vector);
     }
     if (at::GradMode::is_enabled() && X.requires_grad()) {
-        std::shared_ptr<ProductBackward> node(
-            new ProductBackward(Csr(a + 11, as_int(a[9]), as_int(a[10])), (int)to_int(a[2]), vector), torch::autograd::deleteNode);
+        Csr T(a + 11, as_int(a[9]), as_int(a[10]));
+        T.measure_for(X, a[11]);
+        std::shared_ptr<ProductBackward> node(new ProductBackward(std::move(T), (int)to_int(a[2]), vector), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(X));
         torch::autograd::set_history(Y, node);
     }
     return THPVariable_Wrap(std::move(Y));
-}
-
-void write_features(PyObject* o, const dgsp_features_t& f) {
-    Py_buffer view;
-    if (PyObject_GetBuffer(o, &view, PyBUF_WRITABLE) != 0) throw Raised{};
-    const bool fits = view.len == (Py_ssize_t)sizeof(f);
-    if (fits) memcpy(view.buf, &f, sizeof(f));
-    PyBuffer_Release(&view);
-    if (!fits) fail("features must be a Features structure");
 }
 
 PyObject* wrapped(CsrArrays&& a, int64_t M, int64_t K) {
@@ -346,7 +367,7 @@ PyObject* wrapped(CsrArrays&& a, int64_t M, int64_t K) {
 PyObject* csr_from_arrays(PyObject* const* a, Py_ssize_t n) {
     want(n, 6);
     const int64_t M = as_int(a[0]), K = as_int(a[1]);
-    dgsp_features_t f;
+    dgsp_internal_stats_t f;
     CsrArrays arrays = take_csr(M, K, as_tensor(a[2], "rowptr"), as_tensor(a[3], "colidx"), as_tensor(a[4], "vals"), f);
     write_features(a[5], f);
     return wrapped(std::move(arrays), M, K);
@@ -357,24 +378,48 @@ PyObject* csr_from_tensor(PyObject* const* a, Py_ssize_t n) {
     want(n, 2);
     const at::Tensor& T = as_tensor(a[0], "matrix");
     if (T.layout() != at::kSparseCsr || T.dim() != 2) fail("the matrix must be a 2-D sparse CSR tensor");
-    dgsp_features_t f;
+    dgsp_internal_stats_t f;
     CsrArrays arrays = take_csr(T.size(0), T.size(1), T.crow_indices(), T.col_indices(), T.values().detach(), f);
     write_features(a[1], f);
     return wrapped(std::move(arrays), T.size(0), T.size(1));
+}
+
+// (M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, stream); one step of the multiplication
+PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
+    want(n, 13);
+    const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]), nnz = to_int(a[3]);
+    const int algo = (int)to_int(a[9]), phase = (int)to_int(a[10]);
+    const at::Tensor &rowptr = as_tensor(a[4], "rowptr"), &colidx = as_tensor(a[5], "colidx"), &vals = as_tensor(a[6], "vals");
+    const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
+    check_csr(M, rowptr, colidx, vals);
+    check_packed(M, K, N, X, Y);
+    FeaturesArg f(a[11]);
+    void* stream = as_stream(a[12]);
+    f.measure_for(N, a[11], colidx, stream);
+    const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
+    const auto* ci = static_cast<const int32_t*>(ptr(colidx));
+    const auto* av = static_cast<const float*>(ptr(vals));
+    const auto* x = static_cast<const float*>(ptr(X));
+    auto* y = static_cast<float*>(ptr(Y));
+    check_status(unlocked([&] {
+        return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), f.saved_share(), stream);
+    }), "dgsp_spmm_csr_phase");
+    Py_RETURN_NONE;
 }
 
 // (M, K, N, features, rowptr, colidx, vals, X, Y, stream) -> kernel run
 PyObject* spmm_csr_auto(PyObject* const* a, Py_ssize_t n) {
     want(n, 10);
     const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]);
-    const FeaturesArg f(a[3]);
+    FeaturesArg f(a[3]);
     const at::Tensor &rowptr = as_tensor(a[4], "rowptr"), &colidx = as_tensor(a[5], "colidx"), &vals = as_tensor(a[6], "vals");
     const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
     void* stream = as_stream(a[9]);
+    f.measure_for(N, a[3], colidx, stream);
     int algo = DGSP_AUTO;
-    check_status(unlocked([&] { return product(M, K, N, f.get(), rowptr, colidx, vals, X, Y, algo, stream); }), "dgsp_spmm_csr_auto");
+    check_status(unlocked([&] { return product(M, K, N, f, rowptr, colidx, vals, X, Y, algo, stream); }), "dgsp_spmm_csr_auto");
     return PyLong_FromLong(algo);
 }
 
@@ -415,24 +460,22 @@ PyObject* spmm_csr_nnz(PyObject* const* a, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-struct Factors { float alpha, beta; };
-
-// `a`: M, K, N, nnz, rowptr, colidx, vals, X, Y; `b`: algo, features, stream; `factors` nullptr: the plain product
-void view_product(PyObject* const* a, const Factors* factors, PyObject* const* b) {
+// `a`: M, K, N, nnz, rowptr, colidx, vals, X, Y; `b`: algo, features, stream; `factors` alpha and beta, nullptr: the plain product
+void view_product(PyObject* const* a, const float* factors, PyObject* const* b) {
     const int64_t M = as_int(a[0]), K = as_int(a[1]), N = as_int(a[2]), nnz = to_int(a[3]);
     const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
     const int64_t ldx = check_view(X, "X", K, N), ldy = check_view(Y, "Y", M, N);
     const int algo = (int)to_int(b[0]);
-    const FeaturesArg f(b[1]);
+    FeaturesArg f(b[1]);
     void* stream = as_stream(b[2]);
+    if (a[5] != Py_None) f.measure_for(N, b[1], as_tensor(a[5], "colidx"), stream);
     const auto* rp = static_cast<const int32_t*>(ptr(a[4], "rowptr"));
     const auto* ci = static_cast<const int32_t*>(ptr(a[5], "colidx"));
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     const int rc = unlocked([&] {
-        return factors ? dgsp_spmm_csr_axpby(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors->alpha, factors->beta, algo, f.get(), stream)
-                       : dgsp_spmm_csr_ld(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, algo, f.get(), stream);
+        return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), f.saved_share(), stream);
     });
     check_status(rc, factors ? "dgsp_spmm_csr_axpby" : "dgsp_spmm_csr_ld");
 }
@@ -447,15 +490,16 @@ PyObject* spmm_csr_ld(PyObject* const* a, Py_ssize_t n) {
 // (M, K, N, nnz, rowptr, colidx, vals, X, Y, alpha, beta, algo, features, stream)
 PyObject* spmm_csr_axpby(PyObject* const* a, Py_ssize_t n) {
     want(n, 14);
-    const Factors factors{to_float(a[9]), to_float(a[10])};
-    view_product(a, &factors, a + 11);
+    const float factors[2] = {to_float(a[9]), to_float(a[10])};
+    view_product(a, factors, a + 11);
     Py_RETURN_NONE;
 }
 
 #define DGSP_ENTRY(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&entry<name>)), METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {
     DGSP_ENTRY(set_error_type), DGSP_ENTRY(multiply_new), DGSP_ENTRY(multiply_differentiable), DGSP_ENTRY(spmm_csr_auto),
-    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_nnz), DGSP_ENTRY(spmm_csr_ld), DGSP_ENTRY(spmm_csr_axpby), DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
+    DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_nnz), DGSP_ENTRY(spmm_csr_ld), DGSP_ENTRY(spmm_csr_axpby), DGSP_ENTRY(spmm_csr_phase),
+    DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_dgsp_torch", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -184,6 +184,56 @@ def test_column_span_feature():
     assert dg.dgsp_features_from_rowptr_host(3, 10, np.array([0, 2, 2, 3], np.int32)).col_span == 0.0
 
 
+def reuse_counts(colidx):
+    """What the sampling launch counts: distinct buckets and buckets met once in the first 1024, 2048 and 4096 entries of 16
+    pieces, of the columns whose hash is in the lower half of its range."""
+    key = colidx.astype(np.uint32) * np.uint32(2654435761)
+    key = (key ^ (key >> np.uint32(15))) * np.uint32(2654435761)
+    bucket = np.where(key >> np.uint32(31) == 0, key >> np.uint32(13), 1 << 18)
+    first = (colidx.size - 4096) * np.arange(16) // 15
+    counts = []
+    for length in (1024, 2048, 4096):
+        met = np.bincount(bucket[(first[:, None] + np.arange(length)).ravel()], minlength=1 << 18)[:1 << 18]
+        counts += [int((met > 0).sum()), int((met == 1).sum())]
+    return counts
+
+
+def saved_share(counts):
+    f = dg.lib().dgsp_internal_saved_share
+    f.restype, f.argtypes = ctypes.c_double, [ctypes.POINTER(ctypes.c_uint64)]
+    return f((ctypes.c_uint64 * 6)(*counts))
+
+
+def column_block(f, N):
+    block = dg.lib().dgsp_internal_nb_sr_block
+    block.restype, block.argtypes = ctypes.c_int, [ctypes.POINTER(dg.MatrixFeatures), ctypes.c_int64]
+    return block(ctypes.byref(f), N)
+
+
+@pytest.mark.parametrize("law, want", [("uniform 2^20", 16384 / 2 ** 20), ("uniform 2^17", 16384 / 2 ** 17), ("uniform 2^15", 0.5 - np.exp(-2)),
+                                       ("graph", 0.13), ("one column", 0.0)])
+def test_share_of_entries_that_twice_the_places_would_save(law, want):
+    """Uniform columns: a place more holds one column of K; of 32768 columns 65536 samples leave e^-2 unmet, the smallest
+    share that is seen.  Graph: bits of the column one with probability 0.24 (the
+    columns of the R-MAT law; sorted by popularity, 0.59 and 0.71 of the entries name the first 16384 and 32768)."""
+    rng = np.random.default_rng(0)
+    n = 300_000
+    K = 1 << (20 if law in ("graph", "one column") else int(law[-2:]))
+    if law == "graph":
+        col = np.zeros(n, dtype=np.int64)
+        for _ in range(20):
+            col = 2 * col + (rng.random(n) < 0.24)
+    else:
+        col = rng.integers(0, K if law.startswith("uniform") else 1, size=n)
+    assert saved_share(reuse_counts(col.astype(np.int32))) == pytest.approx(want, abs=0.02)
+
+
+def test_column_blocks_follow_the_saved_share():
+    few, many = dg.MatrixFeatures(saved_share=0.09), dg.MatrixFeatures(saved_share=0.11)
+    assert [column_block(few, n) for n in (1, 32, 64, 128, 256)] == [1, 32, 64, 64, 64]
+    assert [column_block(many, n) for n in (1, 32, 64, 96, 128, 192, 256)] == [1, 32, 32, column_block(few, 96), 32, 64, 64]
+
+
 def test_every_source_counts_for_a_stale_build():
     from paper_2106_16064_amd import build
     known = {f.resolve() for f in (*build.SOURCES, *build.HEADERS, build.TORCH_SOURCE)}

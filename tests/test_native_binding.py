@@ -314,3 +314,118 @@ def test_statistics_are_refused_while_a_graph_is_recorded():
         value = 2.0 * (value + 1.0)
         assert dg.DeviceCsr.from_device(A.M, A.K, *arrays).features.as_dict() == want
         assert torch.equal(x, torch.full_like(x, value))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [1, 1000, 1 << 18, 1 << 20, (1 << 31) - 4097])
+@pytest.mark.parametrize("entries", [4096, 4097, 70_001, 1_000_003])
+def test_counts_of_sampled_columns(K, entries):
+    import ctypes
+    import torch
+    from test_host_api import reuse_counts
+    rng = np.random.default_rng(K + entries)
+    col = (K * rng.random(entries) ** 3).astype(np.int32)
+    col[-1] = K - 1
+    dev = torch.from_numpy(col).cuda()
+    counts = (ctypes.c_uint64 * 6)()
+    f = dg.lib().dgsp_internal_column_reuse
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    print(f"[case] sampled columns K={K} entries={entries}", flush=True)
+    assert f(entries, dev.data_ptr(), counts, torch.cuda.current_stream().cuda_stream) == dg.OK
+    assert list(counts) == reuse_counts(col)
+    assert f(4095, dev.data_ptr(), counts, None) == dg.ERR_INVALID_ARG
+
+
+def _from_device(A, dtype, vals):
+    import torch
+    return dg.DeviceCsr.from_device(A.M, A.K, torch.from_numpy(A.rowptr.astype(dtype)).cuda(),
+                                    torch.from_numpy(A.colidx.astype(dtype)).cuda(), vals)
+
+
+@pytest.mark.gpu
+def test_narrow_column_blocks_where_they_save_enough():
+    """A graph of more than four million entries, taken from the host, from int32 and from int64 arrays: its columns are
+    measured by the first product that could take narrow blocks, whichever entry it comes through; the products on them plain
+    and scaled."""
+    import torch
+    from test_host_api import column_block
+    A = wl.rmat_csr(19, 12, seed=3)
+    dA = dg.DeviceCsr(A)
+    for N in (64, 128):
+        X = wl.dense_matrix(A.K, N, "normal", seed=N)
+        Y0 = wl.dense_matrix(A.M, N, "uniform", seed=1)
+        ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+        dX, Y = torch.from_numpy(X).cuda(), torch.from_numpy(Y0).cuda()
+        print(f"[case] narrow column blocks N={N}", flush=True)
+        ok, worst = oracle.within_bound(dA.spmm(dX).cpu().numpy(), ref, bnd, 1e-5)
+        assert ok, worst
+        dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, dA.rowptr, dA.colidx, dA.vals, dX, Y, -0.5, 1.5, features=dA.features)
+        ok, worst = oracle.within_bound(Y.cpu().numpy(), -0.5 * ref + 1.5 * Y0, 0.5 * bnd + 1.5 * np.abs(Y0), 1e-5)
+        assert ok, worst
+    share = dA.features.saved_share
+    assert A.nnz > 4_000_000 and 0.1 < share < 0.2 and column_block(dA.features, 128) == 32
+    x32, x64 = torch.zeros(A.K, 32, device="cuda"), torch.zeros(A.K, 64, device="cuda")
+    y64 = torch.zeros(A.M, 64, device="cuda")
+    for first, dtype in enumerate((np.int32, np.int64, np.int64, np.int32)):
+        D = _from_device(A, dtype, dA.vals)
+        D.spmm(x32)
+        assert D.features.saved_share < 0.0
+        args = (D.M, D.K, 64)
+        if first == 0:
+            dg.dgsp_spmm_csr_auto(*args, D.features, D.rowptr, D.colidx, D.vals, x64, y64)
+        elif first == 1:
+            D.spmm(x64, algo=dg.NB_SR)
+        elif first == 2:
+            dg.dgsp_spmm_csr_ld(*args, D.nnz, D.rowptr, D.colidx, D.vals, x64, y64, features=D.features)
+        else:
+            D.spmm(x64)
+        assert D.features.saved_share == share
+
+
+@pytest.mark.gpu
+def test_columns_that_are_not_measured_or_save_too_little():
+    """Rows as uneven with uniform columns keep the blocks of 64, small matrices are not sampled, and a product that is being
+    recorded leaves the question open; its graph gives the product all the same."""
+    import torch
+    from test_host_api import column_block
+    A = wl.rmat_csr(19, 12, seed=3)
+    U = dg.DeviceCsr(wl.CsrMatrix(A.M, A.K, A.rowptr, np.random.default_rng(0).integers(0, A.K, A.nnz).astype(np.int32), A.vals, "uniform", {}))
+    U.spmm(torch.zeros(A.K, 128, device="cuda"))
+    assert 0.0 <= U.features.saved_share < 0.1 and column_block(U.features, 128) == 64
+    small = dg.DeviceCsr(wl.rmat_csr(14, 24, seed=3))
+    small.spmm(torch.zeros(small.K, 64, device="cuda"))
+    assert small.features.saved_share == 0.0
+    D = dg.DeviceCsr(A)
+    X = torch.randn(A.K, 64, device="cuda")
+    Y = torch.empty(A.M, 64, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    print("[case] narrow column blocks while a graph is recorded", flush=True)
+    with torch.cuda.graph(graph, stream=side):
+        D.spmm(X, Y=Y)
+    assert D.features.saved_share < 0.0
+    want = D.spmm(X)
+    assert D.features.saved_share > 0.1
+    scale = want.abs().max()
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (Y - want).abs().max() <= 1e-4 * scale
+
+
+@pytest.mark.gpu
+def test_gradient_on_narrow_column_blocks():
+    import torch
+    from paper_2106_16064_amd.autograd import SparseOperator, transpose_csr
+    A = wl.rmat_csr(19, 12, seed=3)
+    op = SparseOperator(A)
+    X = torch.zeros(A.K, 64, device="cuda", requires_grad=True)
+    G = wl.dense_matrix(A.M, 64, "uniform", seed=2)
+    op(X).backward(torch.from_numpy(G).cuda())
+    assert op.fwd.features.saved_share > 0.1 and op.bwd.features.saved_share > 0.1
+    T = transpose_csr(A)
+    ref, bnd = oracle.spmm_ref(T.M, T.K, 64, T.rowptr, T.colidx, T.vals, G)
+    ok, worst = oracle.within_bound(X.grad.cpu().numpy(), ref, bnd, 1e-5)
+    assert ok, worst

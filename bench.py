@@ -54,10 +54,10 @@ _TRAFFIC_SOURCE = "profiles/selected_kernels_time_traffic_occupancy.md (rocprofv
 MEASURED_TRAFFIC = {
     # "kernel/workload/N": (bytes fetched + bytes written per launch of the main kernel, source)
     "nb_pr/rmat_spmv/N1": (169.3e6 + 5.1e6, _TRAFFIC_SOURCE),
-    "nb_sr/rmat_gnn/N128": (4815.7e6 + 550.1e6, _TRAFFIC_SOURCE),
-    "nb_sr/rmat_gnn/N32": (1121.6e6 + 137.5e6, _TRAFFIC_SOURCE),
-    "rs_sr/stencil/N1": (497.2e6 + 8.4e6, _TRAFFIC_SOURCE),
-    "rs_sr/stencil/N8": (621.0e6 + 67.1e6, _TRAFFIC_SOURCE),
+    "nb_sr/rmat_gnn/N128": (4815.6e6 + 550.1e6, _TRAFFIC_SOURCE),
+    "nb_sr/rmat_gnn/N32": (1121.4e6 + 137.5e6, _TRAFFIC_SOURCE),
+    "rs_sr/stencil/N1": (497.1e6 + 8.4e6, _TRAFFIC_SOURCE),
+    "rs_sr/stencil/N8": (621.1e6 + 67.1e6, _TRAFFIC_SOURCE),
     "rs_sr/uniform64/N4": (268.1e6 + 4.2e6, _TRAFFIC_SOURCE),
 }
 
@@ -700,8 +700,9 @@ def run_ablation(args):
 
 def run_layouts(args):
     """The wide-N layouts of the balanced sequential kernel on the GNN-style configuration (R-MAT 2^20, row-normalised,
-    N = 64, 128 and 256) and on a matrix with uniform columns: column blocks of 64 (what ships) or 32, tied to XCDs
-    (what ships from N = 128 on) or not; whole call, event-timed, for the comparison table under profiles/."""
+    N = 64, 128 and 256) and on a matrix with uniform columns: column blocks of 64 (the rule's choice, but for
+    matrices whose columns were measured and favour 32) or 32, tied to XCDs (its choice from two blocks on) or not;
+    whole call, event-timed, for the comparison table under profiles/."""
     from paper_2106_16064_amd import binding as dg
     from paper_2106_16064_amd import workloads as wl
     os.makedirs(RESULTS_DIR, exist_ok=True)

@@ -577,9 +577,9 @@ constexpr long long kRunItems = 128;
 // At N = 64 and 128 blocks of 32 - two or four of them, every XCD on one, one 128-byte line of a row of X per entry and
 // block - halve that once more, for one more pass over A.  They save the entries whose row of X an L2 keeps among its last
 // 32768 lines but not among its last 16384 pairs of lines, a share that is measured on the columns (saved_share()).  Where it
-// was 0.1 and more they won on every matrix with four million entries and six a row (blocks of 64 against 32, N = 64 / 128:
+// was 0.1 and more none of 24 matrices with four million entries and six a row was slower (blocks of 64 against 32, N = 64 / 128:
 // R-MAT 2^20 x 16 556 / 1080 -> 504 / 980 us, on another GPU 554 / 992 -> 502 / 1025 us; 2^20 x 32, share 0.13, 15 / 13 %;
-// 2^18 x 32, 0.15, 19 / 3 %; columns of that law in rows of another, 0.13, 11 / 10 %).  Below they lose up to 10 %: the rows of
+// 2^18 x 32, 0.15, 19 / 3 %; columns of that law in rows of another, 0.13, 11 / 10 %).  Below they mostly lose: the rows of
 // R-MAT 2^20 x 16 with other columns, 0.02 to 0.06, 4-9 / 5-11 %, Zipf rows of 64 with uniform columns, 0.06, 0-3 / 0-3 %; and
 // with short rows, whose ends are met once a block, or where the rest of a small X is in the L2 anyway (R-MAT 2^20 x 4 10 / -5 %,
 // 2^16 x 64 8 / 20 %).  Eight blocks (N = 256) leave every XCD the whole matrix: 2081 -> 2302 us.

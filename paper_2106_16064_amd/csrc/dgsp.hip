@@ -462,7 +462,7 @@ inline unsigned balanced_blocks(const Problem& p, long long tile, int blocks_per
 // and more: 2-6 % faster there on R-MAT matrices of every skew (2^20 vertices, degree 16, power law: 104 -> 98 us
 // per call at N = 1, main launch 98 -> 90 us; N = 3: 122 -> 116 us, N = 4: 125 -> 120 us) and on random columns; not
 // on banded matrices (see launch_nb_pr_v).  Smaller matrices give a wave only a few blocks, and the longer kernel's
-// start-up costs more than the overlap returns (5-10 % slower from 0.25 to 4 million entries), so they keep the
+// start-up costs what the overlap returns (10 % faster to 10 % slower on 18 matrices of 0.25 to 4 million entries), so they keep the
 // tiles of merge-path items (nb_pr_tiled_kernel), as does a call that does not know its entry count.  With eight
 // columns per lane the registers that hold a block's gathered values cost more occupancy than the overlap gives
 // (R-MAT N = 8: 162 -> 178 us): tiles as well.  DGSP_ABL_ITEM_TILES / DGSP_ABL_ENTRY_BLOCKS force one or the other
@@ -578,7 +578,8 @@ constexpr long long kRunItems = 128;
 // block - halve that once more, for one more pass over A.  They save the entries whose row of X an L2 keeps among its last
 // 32768 lines but not among its last 16384 pairs of lines, a share that is measured on the columns (saved_share()).  Where it
 // was 0.1 and more none of 24 matrices with four million entries and six a row was slower (blocks of 64 against 32, N = 64 / 128:
-// R-MAT 2^20 x 16 556 / 1080 -> 504 / 980 us, on another GPU 554 / 992 -> 502 / 1025 us; 2^20 x 32, share 0.13, 15 / 13 %;
+// R-MAT 2^20 x 16 612 / 1059 -> 522 / 1011 us, on another GPU 595 / 1073 -> 520 / 969 us, on two of eight at N = 128
+// 988 -> 1012 us; 2^20 x 32, share 0.13, 15 / 13 %;
 // 2^18 x 32, 0.15, 19 / 3 %; columns of that law in rows of another, 0.13, 11 / 10 %).  Below they mostly lose: the rows of
 // R-MAT 2^20 x 16 with other columns, 0.02 to 0.06, 4-9 / 5-11 %, Zipf rows of 64 with uniform columns, 0.06, 0-3 / 0-3 %; and
 // with short rows, whose ends are met once a block, or where the rest of a small X is in the L2 anyway (R-MAT 2^20 x 4 10 / -5 %,

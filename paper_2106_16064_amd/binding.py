@@ -48,9 +48,8 @@ class Features(ctypes.Structure):
 
 class MatrixFeatures(Features):
     """The statistics that a ``DeviceCsr`` holds: ``Features``, and what column blocks half as wide would save
-    (``dgsp_internal_stats_t``; negative: not measured yet).  The latter is not part of the C-ABI: the products of this
-    module measure it when one of a width that it matters to first asks for it, of large matrices with very uneven rows,
-    and hand it to the library.  That product waits for its stream once."""
+    (``dgsp_internal_stats_t``; 0: nothing, or not measured).  The latter is not part of the C-ABI: it is measured of large
+    matrices with very uneven rows when the ``DeviceCsr`` is made, and the products of this module hand it to the library."""
     _fields_ = [("saved_share", ctypes.c_double)]
 
 
@@ -378,7 +377,9 @@ class DeviceCsr:
         self.rowptr = torch.from_numpy(A.rowptr).to(device)
         self.colidx = torch.from_numpy(A.colidx).to(device)
         self.vals = torch.from_numpy(A.vals).to(device)
-        self.features = MatrixFeatures(**dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict(), saved_share=-1.0)
+        self.features = MatrixFeatures(**dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict())
+        if self.colidx.is_cuda:
+            (_native or native()).measure_saved_share(self.features, self.colidx)
         self.tuned = {}        # N -> kernel found fastest by autotune()
 
     @classmethod

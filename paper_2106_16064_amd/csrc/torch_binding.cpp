@@ -11,6 +11,7 @@
 
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
@@ -103,12 +104,7 @@ public:
         given_ = true;
     }
     const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
-    double saved_share() const { return value_.saved_share > 0.0 ? value_.saved_share : 0.0; }
-
-    // What narrower column blocks save is measured when the first product that could take them asks for it: a launch and a
-    // wait of 20 us on a matrix of four million entries or more, which fresh matrices of other widths are spared.  Kept in
-    // `o`.  While a graph is recorded nothing can be waited for: the product then takes the wider blocks.
-    void measure_for(int64_t N, PyObject* o, const at::Tensor& colidx, void* stream);
+    double saved_share() const { return value_.saved_share; }
 
 private:
     dgsp_internal_stats_t value_{};
@@ -168,13 +164,6 @@ void write_features(PyObject* o, const dgsp_internal_stats_t& f) {
     if (!fits) fail("features must be a MatrixFeatures structure");
 }
 
-void FeaturesArg::measure_for(int64_t N, PyObject* o, const at::Tensor& colidx, void* stream) {
-    if (!(value_.saved_share < 0.0) || (N != 64 && N != 128)) return;
-    if (!is_array(colidx, at::kInt) || colidx.numel() < value_.features.nnz) return;
-    const auto* columns = static_cast<const int32_t*>(ptr(colidx));
-    if (unlocked([&] { return dgsp_internal_measure_columns(&value_, columns, stream); }) == DGSP_OK) write_features(o, value_);
-}
-
 // ---------------------------------------------------------------- one product
 
 // Y = A X by a named kernel, or by the rules (DGSP_AUTO); returns the status and leaves the kernel run in `algo`
@@ -210,10 +199,6 @@ struct Csr {
           vals(as_tensor(a[3], "vals")) {
         if (!features.get()) fail("the matrix has no features");
         check_csr(M, rowptr, colidx, vals);
-    }
-    // before a product with X on the current stream (with its gradient, as wide); `o`: what holds the statistics
-    void measure_for(const at::Tensor& X, PyObject* o) {
-        features.measure_for(columns_of(X), o, colidx, c10::hip::getCurrentHIPStream().stream());
     }
 };
 
@@ -256,6 +241,14 @@ struct ProductBackward : public torch::autograd::Node {
 
 struct CsrArrays { at::Tensor rowptr, colidx, vals; };
 
+// What narrower column blocks save, from the columns on the GPU: a launch and a wait, 20 us, where the matrix is one whose
+// products look at it (four million entries and more, very uneven rows).  Here and not in the product, which does not wait.
+void measure_columns(dgsp_internal_stats_t& stats, const at::Tensor& colidx, void* stream) {
+    if (colidx.numel() < stats.features.nnz) return;
+    const auto* columns = static_cast<const int32_t*>(ptr(colidx));
+    (void)unlocked([&] { return dgsp_internal_measure_columns(&stats, columns, stream); });      // not measured: wide blocks
+}
+
 // The arrays in the library's types and the statistics, which the call waits for.  int64 indices are narrowed by the
 // statistics' own launch.
 CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals,
@@ -267,7 +260,7 @@ CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Ten
     out.colidx = wide ? at::empty(colidx.sizes(), colidx.options().dtype(at::kInt)) : colidx.to(at::kInt).contiguous();
     out.vals = is_array(vals, at::kFloat) ? vals : vals.to(at::kFloat).contiguous();
     if (!on_gpu(out.rowptr) || !on_gpu(out.colidx) || out.rowptr.numel() != M + 1) fail("rowptr needs M+1 entries on the GPU");
-    stats = dgsp_internal_stats_t{{}, -1.0};                    // columns not looked at yet
+    stats = dgsp_internal_stats_t{};
     if (M == 0) {
         stats.features.K = K;
         return out;
@@ -280,6 +273,7 @@ CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Ten
     auto* ci32 = static_cast<int32_t*>(ptr(out.colidx));
     check_status(unlocked([&] { return dgsp_internal_take_csr(M, K, entries, wide ? 8 : 4, rp, ci, rp32, ci32, &stats.features, stream); }),
                  "dgsp_features_from_csr_device");
+    measure_columns(stats, out.colidx, stream);
     return out;
 }
 
@@ -317,7 +311,6 @@ PyObject* multiply_new(PyObject* const* a, Py_ssize_t n) {
     want(n, 8);
     Csr A(a + 2, as_int(a[0]), as_int(a[1]));
     const at::Tensor& X = as_tensor(a[6], "X");
-    A.measure_for(X, a[2]);
     return THPVariable_Wrap(multiply(A, X, (int)to_int(a[7]), false));
 }
 
@@ -339,7 +332,6 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
     const at::Tensor& X = as_tensor(a[0], "X");
     if (!only_reverse_mode(X)) Py_RETURN_NONE;
     Csr A(a + 5, as_int(a[3]), as_int(a[4]));
-    A.measure_for(X, a[5]);
     const bool vector = X.dim() == 1;
     at::Tensor Y;
     {
@@ -348,7 +340,6 @@ PyObject* multiply_differentiable(PyObject* const* a, Py_ssize_t n) {
     }
     if (at::GradMode::is_enabled() && X.requires_grad()) {
         Csr T(a + 11, as_int(a[9]), as_int(a[10]));
-        T.measure_for(X, a[11]);
         std::shared_ptr<ProductBackward> node(new ProductBackward(std::move(T), (int)to_int(a[2]), vector), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(X));
         torch::autograd::set_history(Y, node);
@@ -384,6 +375,20 @@ PyObject* csr_from_tensor(PyObject* const* a, Py_ssize_t n) {
     return wrapped(std::move(arrays), T.size(0), T.size(1));
 }
 
+// (features, colidx): the share of a matrix whose statistics are from the host; waits for the current stream of its device
+PyObject* measure_saved_share(PyObject* const* a, Py_ssize_t n) {
+    want(n, 2);
+    FeaturesArg f(a[0]);
+    const at::Tensor& colidx = as_tensor(a[1], "colidx");
+    if (f.get() && is_array(colidx, at::kInt)) {
+        const c10::DeviceGuard guard(colidx.device());
+        dgsp_internal_stats_t stats{*f.get(), 0.0};
+        measure_columns(stats, colidx, c10::hip::getCurrentHIPStream().stream());
+        write_features(a[0], stats);
+    }
+    Py_RETURN_NONE;
+}
+
 // (M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, stream); one step of the multiplication
 PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     want(n, 13);
@@ -395,7 +400,6 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     check_packed(M, K, N, X, Y);
     FeaturesArg f(a[11]);
     void* stream = as_stream(a[12]);
-    f.measure_for(N, a[11], colidx, stream);
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
@@ -417,7 +421,6 @@ PyObject* spmm_csr_auto(PyObject* const* a, Py_ssize_t n) {
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
     void* stream = as_stream(a[9]);
-    f.measure_for(N, a[3], colidx, stream);
     int algo = DGSP_AUTO;
     check_status(unlocked([&] { return product(M, K, N, f, rowptr, colidx, vals, X, Y, algo, stream); }), "dgsp_spmm_csr_auto");
     return PyLong_FromLong(algo);
@@ -468,7 +471,6 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const int algo = (int)to_int(b[0]);
     FeaturesArg f(b[1]);
     void* stream = as_stream(b[2]);
-    if (a[5] != Py_None) f.measure_for(N, b[1], as_tensor(a[5], "colidx"), stream);
     const auto* rp = static_cast<const int32_t*>(ptr(a[4], "rowptr"));
     const auto* ci = static_cast<const int32_t*>(ptr(a[5], "colidx"));
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
@@ -499,7 +501,7 @@ PyObject* spmm_csr_axpby(PyObject* const* a, Py_ssize_t n) {
 PyMethodDef g_methods[] = {
     DGSP_ENTRY(set_error_type), DGSP_ENTRY(multiply_new), DGSP_ENTRY(multiply_differentiable), DGSP_ENTRY(spmm_csr_auto),
     DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_nnz), DGSP_ENTRY(spmm_csr_ld), DGSP_ENTRY(spmm_csr_axpby), DGSP_ENTRY(spmm_csr_phase),
-    DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), {nullptr, nullptr, 0, nullptr},
+    DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), DGSP_ENTRY(measure_saved_share), {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_dgsp_torch", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

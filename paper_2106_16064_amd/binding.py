@@ -47,10 +47,12 @@ class Features(ctypes.Structure):
 
 
 class MatrixFeatures(Features):
-    """The statistics that a ``DeviceCsr`` holds: ``Features``, and what column blocks half as wide would save
-    (``dgsp_internal_stats_t``; 0: nothing, or not measured).  The latter is not part of the C-ABI: it is measured of large
-    matrices with very uneven rows when the ``DeviceCsr`` is made, and the products of this module hand it to the library."""
-    _fields_ = [("saved_share", ctypes.c_double)]
+    """The statistics that a ``DeviceCsr`` holds: ``Features``, what column blocks half as wide would save and the shares
+    of the entries whose column is in one of the hottest runs of columns, for products with one to four columns
+    (``dgsp_internal_stats_t``; 0: nothing, or not measured), and a table of these runs in GPU memory.  The latter are not part of the C-ABI: they are measured of large matrices with
+    very uneven rows when the ``DeviceCsr`` is made, and the products of this module hand them to the library."""
+    _fields_ = [("saved_share", ctypes.c_double), ("hot_share", ctypes.c_double * 4)]
+    hot_columns = None      # int32 tensor on the matrix's GPU
 
 
 class Thresholds(ctypes.Structure):
@@ -379,7 +381,7 @@ class DeviceCsr:
         self.vals = torch.from_numpy(A.vals).to(device)
         self.features = MatrixFeatures(**dgsp_features_from_csr_host(A.M, A.K, A.rowptr, A.colidx).as_dict())
         if self.colidx.is_cuda:
-            (_native or native()).measure_saved_share(self.features, self.colidx)
+            (_native or native()).measure_matrix_columns(self.features, self.colidx)
         self.tuned = {}        # N -> kernel found fastest by autotune()
 
     @classmethod

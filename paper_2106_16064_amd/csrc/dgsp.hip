@@ -73,8 +73,14 @@ struct Hints {
     int64_t size = -1;          // a bound of the entry count
     bool chosen = false;        // the kernel is the library's choice from these statistics, not the caller's
     double saved_share = 0.0;   // what column blocks half as wide would save (kSavedShareMin); 0 = unknown
+    const uint32_t* hot_columns = nullptr;      // the hot runs of a matrix of `hot_K` columns
+    int64_t hot_K = 0;
     Hints() = default;
-    explicit Hints(const dgsp_features_t* f, double saved = 0.0) : saved_share(saved) { if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; } }
+    explicit Hints(const dgsp_features_t* f, const dgsp_internal_hints_t* more = nullptr) {
+        if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; }
+        if (more) saved_share = more->saved_share;
+        if (f && more) { hot_columns = more->hot_columns; hot_K = f->K; }
+    }
 };
 
 struct Problem {
@@ -89,6 +95,7 @@ struct Problem {
     long long max_row = -1;  // entries of the longest row; < 0 = unknown
     long long size = -1;     // the entry count or, for launch geometry, a bound of it; < 0 = unknown
     double saved_share = 0.0;  // see Hints
+    const uint32_t* hot_columns = nullptr;
     int switches = 0;        // DGSP_ABL_* (measurement aids)
     bool scaled = false;     // Y = alpha * A X + beta * Y instead of Y = A X
     float alpha = 1.0f, beta = 0.0f;
@@ -122,9 +129,10 @@ inline int nb_pr_lane_width(int64_t N, int switches) {
     return v;
 }
 
-#define DGSP_LAUNCH(kernel, grid, ...)                                                        \
+#define DGSP_LAUNCH(kernel, grid, ...) DGSP_LAUNCH_THREADS(kernel, grid, kBlock, __VA_ARGS__)
+#define DGSP_LAUNCH_THREADS(kernel, grid, threads, ...)                                       \
     do {                                                                                      \
-        hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, p.stream, __VA_ARGS__);             \
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, p.stream, __VA_ARGS__);            \
         if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;                          \
     } while (0)
 
@@ -487,12 +495,55 @@ inline bool snap_rows(const Problem& p, unsigned groups, double share_part, doub
     return (double)p.max_row / per_us <= 6.0 + (call_us < 100.0 ? 0.35 * call_us : 0.0);
 }
 
+// Runs of 2^shift columns that a table of hot runs counts a matrix of K columns by: 32, more where that would be more than
+// 32768 runs; 0: too many columns.
+inline int hot_shift(int64_t K) {
+    int shift = kHotShiftMin;
+    while (shift <= kHotShiftMax && (K - 1) >> shift >= 32ll * kHotWords) ++shift;
+    return K >= 1 && shift <= kHotShiftMax ? shift : 0;
+}
+// Reading hot runs from LDS pays from this many of their entries on, as copying them costs every CU 4 to 5 us, and where they
+// are this share of all.  R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (shares .58 .43 .33 .27) 95 / 103 / 113 / 114 -> 71 / 87 / 100 / 105 us,
+// 2^20 x 32 167 / 183 / 200 / 201 -> 117 / 148 / 172 / 179 us, 2^18 x 16 (.79 .63 .51 .42) 30 / 32.5 / 36 / 38.6 -> 24 / 28 / 31 / 32 us,
+// 2^21 x 8 (.45 .31 .25 .19) 113 / 122 / 132 / 134 -> 89 / 109 / 120 / 132 us.  N = 1, uniform columns: 16.8 M entries over
+// 100 000 columns (.40) 99 -> 80 us, 262 144 (.20) 102 -> 95 us, 4.2 M over 262 144 (0.8 M of them) 28.7 -> 31.2 us.  Where the hottest
+// columns are so hot that the L1 holds them anyway the shares at N = 2 to 4 pay less: columns 2^20 u^4, N = 2 (.34) 115 -> 110 us,
+// N = 3 (.29) 140 -> 142 us, N = 4 (.26) 151 -> 155 us.
+constexpr double kHotEntriesMin = 1.5e6, kHotShareMin[kHotWidths] = {0.15, 0.3, 0.24, 0.24};
+constexpr long long kHotNnzMin = 3000000;
+inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
+    return N >= 1 && N <= kHotWidths && s.hot_share[N - 1] >= kHotShareMin[N - 1] &&
+           (double)s.features.nnz * s.hot_share[N - 1] >= kHotEntriesMin;
+}
+
+// The hottest runs of X in LDS (nb_pr_kernel, HOT): one workgroup a CU.
+template <int V>
+int launch_nb_pr_hot(const Problem& p) {
+    constexpr int KQ = kNbPrKq;
+    const HotColumns hot{p.hot_columns + (V - 1) * kHotTableInts, hot_shift(p.K)};
+    const dim3 grid((unsigned)device_info().cus);
+    constexpr int kGroups = kHotThreads / kBlock;                   // workgroups of the usual size in one of this kernel
+    const bool snap = snap_rows(p, grid.x * kGroups, 0.1, 128.0, 1.0);
+    if (p.phase != DGSP_PHASE_MAIN && !snap)
+        if (int rc = launch_prepare(p, grid.x * kGroups * kWavesPerBlock, 6, -1)) return rc;
+    if (p.phase == DGSP_PHASE_PREPARE) return DGSP_OK;
+    const Scaling sc{p.alpha, p.beta};
+    const auto launch = [&](auto whole, auto scaled) -> int {
+        DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, false, true>), grid, kHotThreads, p.M,
+                            p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, hot);
+        return DGSP_OK;
+    };
+    if (p.scaled) return snap ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+    return snap ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
+}
+
 template <int V, int KQ>
 int launch_nb_pr_v(const Problem& p) {
     constexpr unsigned tile = kWave * 4 * KQ;
     const unsigned col_groups = (unsigned)((p.N + V - 1) / V);      // V = 8 also takes N = 5, 6, 7: one group
     // the row store addresses a step's rows with 32-bit byte offsets: tile rows * N * 4 must fit
     if (col_groups > 65535u || p.ldy > kBalancedLdyMax) return DGSP_ERR_UNSUPPORTED;
+    if constexpr (V <= kHotWidths) { if (p.N == V && p.ldx == V && p.hot_columns && p.switches == 0) return launch_nb_pr_hot<V>(p); }
     const bool forced_blocks = (p.switches & (DGSP_ABL_ENTRY_BLOCKS | DGSP_ABL_SERIAL_SEGMENT_SCAN)) != 0;
     // A banded matrix (neighbouring rows share their columns: stencils, bands): its gathers hit the L1 and are bound
     // by the rate of the CU's address unit, not by latency, so gathers requested a block ahead gain nothing, and at up
@@ -735,7 +786,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, hints.hot_K == K ? hints.hot_columns : nullptr, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     if (hints.chosen) algo = launched_algo(p, algo);
     switch (algo) {
@@ -770,27 +821,27 @@ extern "C" int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz, c
 
 extern "C" int dgsp_internal_spmm_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
                                         const float* vals, const float* X, float* Y, int algo, int phase,
-                                        const dgsp_features_t* features, double saved_share, void* stream) {
+                                        const dgsp_features_t* features, const dgsp_internal_hints_t* more, void* stream) {
     if (algo < DGSP_RS_SR || algo > DGSP_NB_PR) return DGSP_ERR_INVALID_ARG;
     if (phase < DGSP_PHASE_ALL || phase > DGSP_PHASE_MAIN) return DGSP_ERR_INVALID_ARG;
     if (features && nnz < 0) nnz = features->nnz;
     return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, phase,
-               Hints(features, saved_share));
+               Hints(features, more));
 }
 
 extern "C" int dgsp_spmm_csr_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
                                    const int32_t* colidx, const float* vals, const float* X, float* Y, int algo,
                                    int phase, const dgsp_features_t* features, void* stream) {
-    return dgsp_internal_spmm_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, 0.0, stream);
+    return dgsp_internal_spmm_phase(M, K, N, nnz, rowptr, colidx, vals, X, Y, algo, phase, features, nullptr, stream);
 }
 
 extern "C" int dgsp_internal_spmm_view(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
                                        const float* vals, const float* X, int64_t ldx, float* Y, int64_t ldy,
-                                       const float* alpha_beta, int algo, const dgsp_features_t* features, double saved_share,
-                                       void* stream) {
+                                       const float* alpha_beta, int algo, const dgsp_features_t* features,
+                                       const dgsp_internal_hints_t* more, void* stream) {
     if (ldx < N || ldy < N) return DGSP_ERR_INVALID_ARG;
     if (features && nnz < 0) nnz = features->nnz;
-    Hints hints(features, saved_share);
+    Hints hints(features, more);
     if (algo == DGSP_AUTO && features && N >= 1) {
         algo = library_choice(dgsp_select_algo(features, N), ldy);
         hints.chosen = true;
@@ -803,7 +854,7 @@ extern "C" int dgsp_internal_spmm_view(int64_t M, int64_t K, int64_t N, int64_t 
 extern "C" int dgsp_spmm_csr_ld(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
                                 const int32_t* colidx, const float* vals, const float* X, int64_t ldx, float* Y,
                                 int64_t ldy, int algo, const dgsp_features_t* features, void* stream) {
-    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, nullptr, algo, features, 0.0, stream);
+    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, nullptr, algo, features, nullptr, stream);
 }
 
 extern "C" int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
@@ -811,7 +862,7 @@ extern "C" int dgsp_spmm_csr_axpby(int64_t M, int64_t K, int64_t N, int64_t nnz,
                                    int64_t ldy, float alpha, float beta, int algo, const dgsp_features_t* features,
                                    void* stream) {
     const float factors[2] = {alpha, beta};
-    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, factors, algo, features, 0.0, stream);
+    return dgsp_internal_spmm_view(M, K, N, nnz, rowptr, colidx, vals, X, ldx, Y, ldy, factors, algo, features, nullptr, stream);
 }
 
 extern "C" int dgsp_spmm_csr_ablation(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,
@@ -837,7 +888,7 @@ extern "C" int dgsp_spmm_csr_ablation(int64_t M, int64_t K, int64_t N, int64_t n
                Hints(features), switches);
 }
 
-extern "C" int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features, double saved_share,
+extern "C" int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features, const dgsp_internal_hints_t* more,
                                        const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X,
                                        float* Y, int* chosen, void* stream) {
     if (!features) return DGSP_ERR_INVALID_ARG;
@@ -845,7 +896,7 @@ extern "C" int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dg
     int algo = (N >= 1) ? library_choice(dgsp_select_algo(features, N), N) : DGSP_NB_PR;
     if (algo < 0) return DGSP_ERR_INVALID_ARG;
     if (chosen) *chosen = algo;
-    Hints hints(features, saved_share);
+    Hints hints(features, more);
     hints.chosen = true;
     return run(M, K, N, features->nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
 }
@@ -853,7 +904,7 @@ extern "C" int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dg
 extern "C" int dgsp_spmm_csr_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t* features,
                                   const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X,
                                   float* Y, int* chosen, void* stream) {
-    return dgsp_internal_spmm_auto(M, K, N, features, 0.0, rowptr, colidx, vals, X, Y, chosen, stream);
+    return dgsp_internal_spmm_auto(M, K, N, features, nullptr, rowptr, colidx, vals, X, Y, chosen, stream);
 }
 
 // ---------------------------------------------------------------- 64-bit row pointers
@@ -1254,31 +1305,59 @@ extern "C" double dgsp_internal_saved_share(const uint64_t* counts) {
     return std::fmax(missed(16384.0) - missed(32768.0), 0.0);
 }
 
-extern "C" int dgsp_internal_column_reuse(int64_t entries, const int32_t* colidx, uint64_t* counts, void* stream) {
-    if (entries < kReuseEntriesMin || !colidx || !counts) return DGSP_ERR_INVALID_ARG;
-    hipStream_t st = (hipStream_t)stream;
+namespace {
+// counts[0 ... 5]: distinct columns and columns met once (column_reuse_kernel); counts[6 ... 9]: sampled entries in hot runs,
+// where `hot_table` is given
+int sample_columns(int64_t K, int64_t entries, const int32_t* colidx, uint32_t* hot_table, uint64_t* counts, hipStream_t st) {
     if (recording(st)) return DGSP_ERR_LAUNCH;
     StatisticsPool::Slot slot;
     if (!g_stat_pool.take(slot, true)) return DGSP_ERR_LAUNCH;
     struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
-    constexpr int kCounts = 2 * kReuseLevels;
     unsigned long long* out = slot.host ? slot.host : slot.scratch->result;
-    hipLaunchKernelGGL(column_reuse_kernel, dim3(1), dim3(kReuseThreads), 0, st, (long long)entries, colidx, out,
-                       slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
+    hipLaunchKernelGGL(column_reuse_kernel, dim3(hot_table ? 1 + kHotWidths : 1), dim3(kReuseThreads), 0, st, (long long)entries, colidx, hot_table,
+                       hot_table ? hot_shift(K) : 0, out, slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
-    unsigned long long h[kCounts];
-    if (const int rc = fetch_result(slot, h, kCounts, st)) return rc;
-    for (int i = 0; i < kCounts; ++i) counts[i] = h[i];
+    // a place is given back when nothing is under way in it: all workgroups', whatever became of the first
+    bool hot_done = true;
+    for (int v = 1; hot_table && slot.host && v <= kHotWidths; ++v)
+        hot_done = wait_for_ticket(slot.host + kStatResultWords + v, slot.ticket, st) && hot_done;
+    unsigned long long h[kReuseResultWords];
+    if (const int rc = fetch_result(slot, h, kReuseResultWords, st)) return rc;
+    if (!hot_done) return DGSP_ERR_LAUNCH;
+    for (int i = 0; i < kReuseResultWords; ++i) counts[i] = h[i];
+    return DGSP_OK;
+}
+}  // namespace
+
+extern "C" int dgsp_internal_column_reuse(int64_t entries, const int32_t* colidx, uint64_t* counts, void* stream) {
+    if (entries < kReuseEntriesMin || !colidx || !counts) return DGSP_ERR_INVALID_ARG;
+    uint64_t h[kReuseResultWords];
+    if (const int rc = sample_columns(0, entries, colidx, nullptr, h, (hipStream_t)stream)) return rc;
+    for (int i = 0; i < 2 * kReuseLevels; ++i) counts[i] = h[i];
     return DGSP_OK;
 }
 
-extern "C" int dgsp_internal_measure_columns(dgsp_internal_stats_t* stats, const int32_t* colidx, void* stream) {
+extern "C" int64_t dgsp_internal_hot_columns_bytes(const dgsp_internal_stats_t* stats) {
+    if (!stats) return 0;
+    const dgsp_features_t& f = stats->features;
+    return f.nnz >= kHotNnzMin && f.cv_row >= kColumnsCvMin && hot_shift(f.K) != 0 ? (int64_t)sizeof(int) * kHotTableInts * kHotWidths : 0;
+}
+
+extern "C" int dgsp_internal_wants_hot_columns(const dgsp_internal_stats_t* stats, int64_t N) {
+    return stats && wants_hot_columns(*stats, N);
+}
+
+extern "C" int dgsp_internal_measure_columns(dgsp_internal_stats_t* stats, const int32_t* colidx, uint32_t* hot_columns, void* stream) {
     if (!stats) return DGSP_ERR_INVALID_ARG;
     stats->saved_share = 0.0;
-    if (!column_share_matters(stats->features)) return DGSP_OK;
-    uint64_t counts[2 * kReuseLevels];
-    if (const int rc = dgsp_internal_column_reuse(stats->features.nnz, colidx, counts, stream)) return rc;
-    stats->saved_share = dgsp_internal_saved_share(counts);
+    for (double& share : stats->hot_share) share = 0.0;
+    if (dgsp_internal_hot_columns_bytes(stats) == 0) hot_columns = nullptr;
+    if (!column_share_matters(stats->features) && !hot_columns) return DGSP_OK;
+    if (stats->features.nnz < kReuseEntriesMin || !colidx) return DGSP_ERR_INVALID_ARG;
+    uint64_t counts[kReuseResultWords];
+    if (const int rc = sample_columns(stats->features.K, stats->features.nnz, colidx, hot_columns, counts, (hipStream_t)stream)) return rc;
+    if (column_share_matters(stats->features)) stats->saved_share = dgsp_internal_saved_share(counts);
+    for (int v = 0; hot_columns && v < kHotWidths; ++v) stats->hot_share[v] = (double)counts[2 * kReuseLevels + v] / (double)kHotSample;
     return DGSP_OK;
 }
 

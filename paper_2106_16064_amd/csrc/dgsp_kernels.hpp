@@ -978,29 +978,53 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 // The row-bound window of the next step is requested before the next entries, so waiting for it does not wait
 // for them (loads return in issue order).
 
+// The hottest runs of a packed X of V columns (found when a matrix is taken over, hot_columns()): as many runs of 2^shift rows
+// of X as kHotFloats hold.  `table`: kHotWords words (bitmap of 32 runs, hot runs before them) and the hot runs' numbers,
+// ascending, kNoRow behind the last one; one such table for every V.
+constexpr int kHotThreads = 512, kHotWords = 1024, kHotWidths = 4, kHotShiftMin = 5, kHotShiftMax = 7;
+constexpr int kHotTableInts = 3 * kHotWords;
+// what the products, marks and bitmap of eight waves leave of 160 KB
+constexpr int hot_floats(int v) { return v == 1 ? 31 * 1024 : v == 2 ? 28 * 1024 : v == 3 ? 24 * 1024 : 20 * 1024; }
+__host__ __device__ constexpr int hot_room(int v, int shift) { return hot_floats(v) / (v << shift); }
+struct HotColumns { const unsigned* table; int shift; };
+
 // SERIAL_SCAN (a comparison kernel for Section 2.1.1, not used by the library's own choices): the lanes' open-row
 // partial sums meet through a serial segmented prefix sum - they are put into LDS and one lane adds them up in
 // lane order, starting afresh at every lane that holds a row boundary - instead of the DPP network.  Everything
 // else, the balanced split included, is the same, so the difference in time is the vectorized reduction's.
-template <int V, int KQ, bool SNAP, bool AXPBY = false, bool SERIAL_SCAN = false>
-__global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
+//
+// HOT (packed X, one to four columns): the runs of X that most entries name are read from LDS.  A gather of scattered columns fetches a
+// 128-byte line from the L2 for four to sixteen bytes of it, and the rate of these lines is what bounds the product (R-MAT 2^20 x 16: 14
+// million of them, 75 us for nothing but the gather).  Where few lines hold many of the entries' columns - the columns of a
+// power-law graph: 53 % of that one's are on 896 of its 32768 lines - every CU copies these lines when it starts, and a bitmap of
+// the lines with a running count per word says for a column whether it is among them and where.  One workgroup of eight
+// waves per CU, so that its LDS holds one table; the lanes that found their column there switch their gather off.
+// R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 70.7 / 87.9 / 104.4 us; 4 / 6 / 12 / 16 waves instead of
+// eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 7
+// million at 4 cycles each and CU: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
+// switched off, and by offset or by execution mask, makes no difference, nor would packing the others into fewer instructions.
+template <int V, int KQ, bool SNAP, bool AXPBY = false, bool SERIAL_SCAN = false, bool HOT = false>
+__global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        Scaling sc = Scaling{1.0f, 0.0f}) {
+                                                        Scaling sc = Scaling{1.0f, 0.0f}, HotColumns hot = HotColumns{nullptr, 0}) {
     constexpr int E = 4 * KQ;
     constexpr int W = kWave * E;
-    __shared__ __align__(16) unsigned s_bnd[kWavesPerBlock][W + 4];   // [W]: rows that end before the step's first entry
-    __shared__ __align__(16) float s_buf[kWavesPerBlock][W * V];      // products, then a step's row results
-    __shared__ __align__(16) float s_scan[SERIAL_SCAN ? kWavesPerBlock : 1][SERIAL_SCAN ? kWave * (V + 1) : 1];   // serial scan only
+    constexpr int kWaves = HOT ? kHotThreads / kWave : kWavesPerBlock;
+    __shared__ __align__(16) unsigned short s_bnd[kWaves][W];         // which row (of the step) ends with an entry of the block
+    __shared__ __align__(16) float s_buf[kWaves][W * V];              // products, then a step's row results
+    __shared__ __align__(16) float s_scan[SERIAL_SCAN ? kWaves : 1][SERIAL_SCAN ? kWave * (V + 1) : 1];   // serial scan only
+    __shared__ __align__(16) float s_hot[HOT ? hot_floats(V) : 1];    // the hot runs of X
+    __shared__ __align__(16) uint2 s_word[HOT ? kHotWords : 1];       // 32 runs: which are hot, how many hot ones lie before
     const int lane = lane_id();
     const int wib = wave_in_block();
-    unsigned* bnd = s_bnd[wib];
+    unsigned short* bnd = s_bnd[wib];
     float* buf = s_buf[wib];
     const int n0 = blockIdx.y * V;
 
-    const ChunkPlan plan = plan_chunks(rowptr, M, 6);        // quanta of one wave's width
-    const unsigned nnz = plan.nnz;
+    const unsigned nnz = (unsigned)rowptr[M];
+    const ChunkPlan plan(nnz, nnz + (unsigned)M, gridDim.x * kWaves, xcd_contiguous(blockIdx.x, gridDim.x) * kWaves + wib, 6);   // quanta of one wave's width
     const unsigned long long y_elems = dense_bytes(M, ldy, N) / 4ull;
     // V = 8: the lane's second four columns start here (N = 5, 6, 7: at N - 4, overlapping the first four)
     const int second = (V == 8 && N - n0 < 8) ? N - n0 - 4 : 4;
@@ -1009,10 +1033,55 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
     };
 
-    for (unsigned sub = 0; sub < kSubRanges; ++sub) {
     unsigned d0, d1;
-    if (!plan.range(sub, d0, d1)) continue;
+    const bool any_items = plan.range(0, d0, d1);
+    // the hot runs, 16 bytes a load, and their bitmap: on their way while the chunk's bounds are searched
+    constexpr int kPieces = HOT ? (hot_floats(V) / 4 + kHotThreads - 1) / kHotThreads : 1;
+    constexpr int kWordPieces = HOT ? (kHotWords + kHotThreads - 1) / kHotThreads : 1;
+    float piece[kPieces][4];
+    uint2 word[kWordPieces];
+    if constexpr (HOT) {
+        const __amdgpu_buffer_rsrc_t rh = make_buffer(X, dense_bytes(K, V, V));
+#pragma unroll
+        for (int k = 0; k < kWordPieces; ++k) {
+            const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
+            word[k] = reinterpret_cast<const uint2*>(hot.table)[i < (unsigned)kHotWords ? i : 0u];
+        }
+        // piece i: 16 bytes of hot run (i / pieces of a run)
+        const auto run_of = [&](unsigned i) { return (i >> (hot.shift - 2)) / (unsigned)V; };
+        const unsigned pieces = (unsigned)(hot_room(V, hot.shift) * V) << (hot.shift - 2);
+        unsigned run[kPieces];
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) {
+            const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
+            run[k] = hot.table[2 * kHotWords + run_of(i < pieces ? i : 0u)];
+        }
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) {
+            const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
+            const unsigned inside = i - ((run_of(i) * (unsigned)V) << (hot.shift - 2));
+            const bool none = i >= pieces || run[k] == kNoRow;
+            buffer_load_vec<4>(rh, none ? kOutOfRange : ((run[k] * (unsigned)V) << (hot.shift + 2)) + inside * 16u, piece[k]);
+        }
+    }
 
+    // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
+    int is = 0, ie1 = 0;
+    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
+    if constexpr (HOT) {
+#pragma unroll
+        for (int k = 0; k < kWordPieces; ++k) {
+            const int i = k * kHotThreads + (int)threadIdx.x;
+            if (i < kHotWords) s_word[i] = word[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) {
+            const int i = k * kHotThreads + (int)threadIdx.x;
+            if (i < hot_floats(V) / 4) store_vec<4>(s_hot + 4 * i, piece[k]);
+        }
+        __syncthreads();                                     // the only step that the workgroup's waves take together
+    }
+    if (!any_items) return;
     if (nnz == 0) {
         // nothing stored: every item is a row end; my rows are [d0, d1)
         for (unsigned r = d0 + lane; r < d1; r += kWave) {
@@ -1023,16 +1092,12 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
             if constexpr (AXPBY) scale_into<V, true>(out, y, sc, second);
             store_vec_dword_aligned<V>(y, out, second);
         }
-        continue;
+        return;
     }
-
-    // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
-    int is, ie1;
-    wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
     unsigned js0 = d0 - (unsigned)is, je1 = d1 - (unsigned)ie1;
     if constexpr (SNAP) {
         snap_to_rows(rowptr, M, d0, d1, is, ie1, js0, je1);
-        if (is == ie1) continue;
+        if (is == ie1) return;
     }
     unsigned js = js0;
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
@@ -1066,13 +1131,33 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     // a quarter of the rate of other vector instructions), checked once.
     const unsigned pitch = (unsigned)ldx * 4u;
     const int pitch_shift = (pitch & (pitch - 1u)) == 0u ? __builtin_ctz(pitch) : -1;
+    float in_lds[HOT ? E : 1][V];                         // the values found among the hot runs, 0 for the others
     auto gather = [&](unsigned k, const int (&c)[E], float (&x)[E][V]) {
         if ((unsigned long long)k * W * 4ull >= chunk_bytes && chunk_bytes != 0ull) {
             // no such block: nothing to request (the loop's last iteration)
 #pragma unroll
-            for (int e = 0; e < E; ++e)
+            for (int e = 0; e < E; ++e) {
 #pragma unroll
                 for (int i = 0; i < V; ++i) x[e][i] = 0.0f;
+                if constexpr (HOT)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) in_lds[e][i] = 0.0f;
+            }
+        } else if constexpr (HOT) {
+            uint2 w[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) w[e] = s_word[(unsigned)c[e] >> (hot.shift + 5)];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const unsigned bit = ((unsigned)c[e] >> hot.shift) & 31u;
+                const bool found = ((w[e].x >> bit) & 1u) != 0u;
+                const unsigned before = w[e].y + (unsigned)__popc(w[e].x & ((1u << bit) - 1u));
+                const unsigned at = found ? (before << hot.shift) + ((unsigned)c[e] & ((1u << hot.shift) - 1u)) : 0u;
+                load_vec<V>(s_hot + at * (unsigned)V, in_lds[e]);
+#pragma unroll
+                for (int i = 0; i < V; ++i) in_lds[e][i] = found ? in_lds[e][i] : 0.0f;
+                buffer_load_vec<V>(rx, found ? kOutOfRange : (unsigned)c[e] * (unsigned)(4 * V), x[e]);
+            }
         } else if (x_small) {
             if (pitch_shift >= 0) {
 #pragma unroll
@@ -1128,29 +1213,30 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     // state of the step in flight between its two halves
     int ie = is, nrows = 0;
     unsigned je = js, blk_start = js0, blk_end = js0;
-    bool capped = false;
+    bool capped = false, closes_carry = false;
 
     // first half of a step: which rows end in it, their marks, the next step's row window
     auto step_rows = [&]() {
         wave_lds_sync();                                   // the previous step's readers are done
 #pragma unroll
-        for (int k = 0; k < KQ; ++k)
-            *reinterpret_cast<uint4*>(bnd + E * lane + 4 * k) = make_uint4(kNoRow, kNoRow, kNoRow, kNoRow);
-        if (lane == 0) bnd[W] = kNoRow;
+        for (int k = 0; k < KQ; k += 2) {
+            if constexpr (KQ % 2 == 0) *reinterpret_cast<uint4*>(bnd + E * lane + 4 * k) = make_uint4(kNoRow, kNoRow, kNoRow, kNoRow);
+            else *reinterpret_cast<uint2*>(bnd + E * lane + 4 * k) = make_uint2(kNoRow, kNoRow);
+        }
         wave_lds_sync();
-        const unsigned js_l = js - blk_start;              // the step's first entry, counted from the block's start
         ie = is;
-        // marks the rows of one batch of 64 candidates that end in this block (and in my chunk); returns how many did
-        auto mark_row_ends = [&](int m, unsigned end) {
+        // marks the rows of one batch of 64 candidates that end in this block (and in my chunk); returns how many did.
+        // `before`: where the row in front of the batch ended.  A row without entries leaves no mark: two rows never end
+        // with the same entry.
+        auto mark_row_ends = [&](int m, unsigned end, unsigned before) {
             const long long r = (long long)is + m * kWave + lane;
+            const unsigned start = (unsigned)__builtin_amdgcn_update_dpp((int)before, (int)end, kDppWaveShr1, 0xf, 0xf, false);
             const bool ends = r < ie1 && end <= blk_end;
-            if (ends) {
-                const unsigned q = end - blk_start;        // it ends after entry q-1 of the block; q >= js_l
-                atomicMin(bnd + (q > js_l ? q - 1 : (unsigned)W), (unsigned)(r - is));
-            }
+            if (ends && end > start) bnd[end - blk_start - 1u] = (unsigned short)(m * kWave + lane);      // it ends after that entry
             return (int)__popcll(__ballot(ends));
         };
-        int cnt = mark_row_ends(0, w_end);                 // the first 64 candidates were loaded a step ago
+        int cnt = mark_row_ends(0, w_end, js);             // the first 64 candidates were loaded a step ago
+        closes_carry = cnt != 0 && (unsigned)uniform((int)w_end) == js;      // row `is` ends before the step's first entry
         ie += cnt;
         unsigned last_end = 0;
         if (cnt == kWave) {
@@ -1160,7 +1246,10 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
             for (int m = 1; m < E; ++m) load_row_ends(is + m * kWave, true, me[m - 1]);
 #pragma unroll
             for (int m = 1; m < E; ++m) {
-                if (cnt == kWave) { cnt = mark_row_ends(m, me[m - 1]); ie += cnt; }
+                if (cnt == kWave) {
+                    cnt = mark_row_ends(m, me[m - 1], (unsigned)read_lane((int)(m == 1 ? w_end : me[m > 1 ? m - 2 : 0]), kWave - 1));
+                    ie += cnt;
+                }
             }
             last_end = (unsigned)read_lane((int)me[E - 2], kWave - 1);      // end of row is + W - 1
         }
@@ -1171,16 +1260,14 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
     };
 
     // second half: reduce the step's entries, finish its rows
-    auto step_sums = [&](const float (&pr)[E][V]) {
+    auto step_sums = [&](float (&pr)[E][V]) {
         store_pending();                                   // the previous step's rows
         wave_lds_sync();                                   // marks are in place
-        const int js_l = (int)(js - blk_start), je_l = (int)(je - blk_start);
-        const unsigned b_in = bnd[W];
-        unsigned b[E];
+        unsigned b[E];                                     // 0xffff: no row ends with this entry
 #pragma unroll
-        for (int k = 0; k < KQ; ++k) {
-            const uint4 t = *reinterpret_cast<const uint4*>(bnd + E * lane + 4 * k);
-            b[4 * k] = t.x; b[4 * k + 1] = t.y; b[4 * k + 2] = t.z; b[4 * k + 3] = t.w;
+        for (int e = 0; e < E; e += 2) {
+            const unsigned two = *reinterpret_cast<const unsigned*>(bnd + E * lane + e);
+            b[e] = two & 0xffffu; b[e + 1] = two >> 16;
         }
         // ---- the step's row results: cleared, so rows without entries come out as zeros
         for (int k = 0; k * kWave < nrows; ++k) {
@@ -1190,26 +1277,26 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
             store_vec<V>(buf + (size_t)(k * kWave + lane) * V, zero);
         }
         wave_lds_sync();
-        // rows that end before the step's first entry take the sum carried in
-        if (b_in != kNoRow) {
-            if (lane == 0) store_vec<V>(buf + (size_t)b_in * V, carry);
+        // a row that ends before the step's first entry takes the sum carried in
+        if (closes_carry) {
+            if (lane == 0) store_vec<V>(buf, carry);
 #pragma unroll
             for (int i = 0; i < V; ++i) carry[i] = 0.0f;
         }
 
-        // ---- in-lane reduction over my E consecutive entries (those of this step)
+        // ---- in-lane reduction over my E consecutive entries.  Those of earlier steps have been set to 0; those behind a
+        //      capped step's last row end only reach the carry, which is dropped then
+        constexpr unsigned kNone = 0xffffu;
         float s[V], head[V];
-        unsigned head_row = kNoRow;                        // kNoRow: no boundary inside this lane
+        unsigned head_row = kNone;                         // kNone: no boundary inside this lane
 #pragma unroll
         for (int i = 0; i < V; ++i) { s[i] = lane == 0 ? carry[i] : 0.0f; head[i] = 0.0f; }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int pos = E * lane + e;
-            const bool in = pos >= js_l && pos < je_l;
 #pragma unroll
-            for (int i = 0; i < V; ++i) s[i] += in ? pr[e][i] : 0.0f;
-            if (b[e] != kNoRow) {
-                if (head_row == kNoRow) {
+            for (int i = 0; i < V; ++i) s[i] += pr[e][i];
+            if (b[e] != kNone) {
+                if (head_row == kNone) {
                     head_row = b[e];
 #pragma unroll
                     for (int i = 0; i < V; ++i) head[i] = s[i];
@@ -1222,7 +1309,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
         }
 
         // ---- the open row across lanes: segments start at lanes that hold a boundary
-        const bool flagged = head_row != kNoRow;
+        const bool flagged = head_row != kNone;
         if constexpr (SERIAL_SCAN) {
             float* sc_val = s_scan[wib];                   // 64 x V partial sums, then 64 flags
             float* sc_flag = sc_val + kWave * V;
@@ -1258,6 +1345,15 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
         }
 #pragma unroll
         for (int i = 0; i < V; ++i) carry[i] = read_lane(s[i], kWave - 1);
+        if (capped) {                                      // the next step has the block's remaining entries
+            const int taken = (int)(je - blk_start);
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                carry[i] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < E; ++e) pr[e][i] = E * lane + e < taken ? 0.0f : pr[e][i];
+            }
+        }
         wave_lds_sync();
 
         // ---- write the rows [is, ie) out, lane l row is + l: the first 64 with one unconditional
@@ -1329,7 +1425,10 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
             float p[V];
             const bool mine = e * kWave + lane < nE;
 #pragma unroll
-            for (int i = 0; i < V; ++i) p[i] = mine ? a[e] * x[e][i] : 0.0f;
+            for (int i = 0; i < V; ++i) {
+                const float xi = HOT ? x[e][i] + in_lds[HOT ? e : 0][i] : x[e][i];          // one of the two is 0
+                p[i] = mine ? a[e] * xi : 0.0f;
+            }
             store_vec<V>(buf + (size_t)(e * kWave + lane) * V, p);
         }
         wave_lds_sync();
@@ -1358,7 +1457,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_kernel(int M, long long K, int N
         for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
     }
     if (any && lane == 0 && is < M) add_to_row(Y + (size_t)is * ldy + n0, carry);
-    }   // next chunk
 }
 
 // ===========================================================================
@@ -2198,7 +2296,7 @@ __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long
 }
 
 // ===========================================================================
-// how popular the columns are (for the width of the column blocks of nb_sr_run_kernel)
+// how popular the columns are (for the width of the column blocks of nb_sr_run_kernel and the hot runs of nb_pr_kernel)
 // ===========================================================================
 // Counts distinct columns, and those met once, among 16384, 32768 and 65536 sampled entries: the first 1024, 2048 and 4096 of
 // 16 pieces, evenly spread.  Only columns whose hash falls into the lower half of its range are counted (saved_share(), host,
@@ -2209,14 +2307,147 @@ __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long
 constexpr int kReuseLevels = 3, kReusePieces = 16, kReuseThreads = 1024, kReuseBucketsLog2 = 18, kReuseRateLog2 = 1;
 constexpr long long kReuseEntriesMin = 4 * kReuseThreads;              // a piece
 
+constexpr int kReuseResultWords = 2 * kReuseLevels + kHotWidths;       // its counts, and the sampled entries in hot runs
+
+// exclusive prefix sum over the threads of the workgroup; `total`: the sum of all
+__device__ __forceinline__ unsigned reuse_prefix(unsigned v, unsigned* waves, unsigned& total) {
+    unsigned sum = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const unsigned o = (unsigned)__shfl_up((int)sum, (unsigned)d);
+        sum += lane_id() >= d ? o : 0u;
+    }
+    __syncthreads();                                             // the last call's readers are done
+    if (lane_id() == kWave - 1) waves[threadIdx.x / kWave] = sum;
+    __syncthreads();
+    unsigned before = 0;
+    total = 0;
+    for (int w = 0; w < kReuseThreads / kWave; ++w) {
+        before += w < (int)(threadIdx.x / kWave) ? waves[w] : 0u;
+        total += waves[w];
+    }
+    return before + sum - v;
+}
+
+// The hot runs (HotColumns): 32768 entries, 512 pieces of 64 evenly spread, are counted by run of 2^shift columns, at most 32768
+// runs, and the `room` fullest taken.  Thread t owns runs 32 t ... 32 t + 31, a word of the bitmap.  `bins`: 32768 words.
+// Returns how many of the sampled entries are in hot runs.
+// A wave's 64 counters lie 32 words apart, on one bank, so the counters of a word are rotated by its number.
+constexpr int kHotSamplePieces = 512, kHotSample = kHotSamplePieces * kWave, kHotLevels = kReuseThreads;
+
+__device__ __forceinline__ unsigned hot_columns(long long entries, const int* __restrict__ colidx, unsigned* table, int shift,
+                                                unsigned room, unsigned* bins, unsigned* waves) {
+    constexpr int kPerThread = kHotSample / kReuseThreads;
+    __shared__ unsigned s_level, s_above, s_met;
+    const int t = (int)threadIdx.x;
+    unsigned c[kPerThread];
+#pragma unroll
+    for (int q = 0; q < kPerThread; ++q)
+        c[q] = (unsigned)colidx[(entries - kWave) / (kHotSamplePieces - 1) * (uniform(t / kWave) * kPerThread + q) + lane_id()];
+    for (int i = 0; i < 8; ++i) reinterpret_cast<uint4*>(bins)[t + i * kReuseThreads] = make_uint4(0u, 0u, 0u, 0u);
+    if (t == 0) s_met = 0u;
+    __syncthreads();
+    const auto place = [](unsigned word, unsigned bit) { return word * 32u + ((bit + word) & 31u); };
+#pragma unroll
+    for (int q = 0; q < kPerThread; ++q) {
+        const unsigned run = c[q] >> shift < 32u * kHotWords ? c[q] >> shift : 32u * kHotWords - 1u;
+        atomicAdd(&bins[place(run >> 5, run & 31u)], 1u);
+    }
+    __syncthreads();
+    unsigned n[32];
+#pragma unroll
+    for (unsigned b = 0; b < 32; ++b) n[b] = bins[place((unsigned)t, b)];
+    __syncthreads();
+    // how many runs have each count (the last level: that and more, no more runs than there is room for).  Most have next to
+    // none: these go a wave at a time.
+    unsigned* levels = bins;
+    levels[t] = 0u;
+    __syncthreads();
+    unsigned few = 0;                                            // a byte each for 0, 1, 2, 3
+#pragma unroll
+    for (unsigned b = 0; b < 32; ++b) {
+        if (n[b] < 4u) few += 1u << (8u * n[b]);
+        else atomicAdd(&levels[n[b] < (unsigned)kHotLevels ? n[b] : kHotLevels - 1], 1u);
+    }
+    unsigned even = few & 0x00ff00ffu, odd = (few >> 8) & 0x00ff00ffu;
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        even += (unsigned)__shfl_xor((int)even, m);
+        odd += (unsigned)__shfl_xor((int)odd, m);
+    }
+    if (lane_id() == 0) {
+        atomicAdd(&levels[1], odd & 0xffffu);
+        atomicAdd(&levels[2], even >> 16);
+        atomicAdd(&levels[3], odd >> 16);
+    }
+    __syncthreads();
+    // the lowest level that no more than `room` runs reach
+    unsigned total;
+    {
+        const unsigned level = (unsigned)(kHotLevels - 1 - t), here = levels[level];
+        const unsigned reach = reuse_prefix(here, waves, total) + here;
+        if (level >= 1u && reach <= room && (level == 1u || reach + levels[level - 1u] > room)) {
+            s_level = level;
+            s_above = reach;
+        }
+    }
+    __syncthreads();
+    // its runs, and of those one below the first ones, as many as there are places left
+    const unsigned lowest = s_level, left = lowest > 1u ? room - s_above : 0u;
+    unsigned mask = 0, below = 0;
+#pragma unroll
+    for (unsigned b = 0; b < 32; ++b) {
+        mask |= n[b] >= lowest ? 1u << b : 0u;
+        below |= n[b] + 1u == lowest ? 1u << b : 0u;
+    }
+    const unsigned before = reuse_prefix((unsigned)__popc(mask) | (unsigned)__popc(below) << 16, waves, total);
+    unsigned rank = before >> 16, at = (before & 0xffffu) + (rank < left ? rank : left);
+    for (; below != 0u && rank < left; below &= below - 1u, ++rank) mask |= below & -below;
+    const unsigned tied = total >> 16, hot = (total & 0xffffu) + (tied < left ? tied : left);
+    stat_store_two(reinterpret_cast<int*>(table) + 2 * t, (int)mask, (int)at);
+    unsigned* list = bins + kHotLevels;
+    unsigned met = 0;
+#pragma unroll
+    for (unsigned b = 0; b < 32; ++b) {
+        if ((mask >> b) & 1u) {
+            list[at++] = 32u * (unsigned)t + b;
+            met += n[b];
+        }
+    }
+    if (met) atomicAdd(&s_met, met);
+    __syncthreads();
+    stat_store(reinterpret_cast<int*>(table) + 2 * kHotWords + t, (int)((unsigned)t < hot ? list[t] : kNoRow));
+    stores_done();
+    __syncthreads();
+    return s_met;
+}
+static_assert(kHotSample / kHotLevels <= hot_room(4, kHotShiftMax) && kHotSample / kHotLevels <= hot_room(3, kHotShiftMax),
+              "the runs of the last level fit");
+static_assert(kHotWords == kReuseThreads && hot_floats(1) >> kHotShiftMin <= kReuseThreads, "a thread a word of the bitmap and a hot run");
+
+// Workgroup 0 counts distinct columns; workgroup v, where there is one, finds the hot runs for products with v columns, of a
+// matrix whose columns fall into at most 32768 runs of 2^hot_shift.  Each announces itself in a word of its own.
 __global__ __launch_bounds__(kReuseThreads) void column_reuse_kernel(long long entries, const int* __restrict__ colidx,
+                                                                    unsigned* hot_table, int hot_shift,
                                                                     unsigned long long* out, unsigned long long* announce,
                                                                     unsigned long long ticket) {
     constexpr int kWords = (1 << kReuseBucketsLog2) / 16;
     constexpr int kOwn = kWords / kReuseThreads;
-    __shared__ unsigned table[kWords + kWave];                   // the words behind are for the columns that are not counted
+    __shared__ __align__(16) unsigned table[32 * kHotWords];                   // kWords, and words behind for the columns that are not counted
     __shared__ unsigned sums[kReuseLevels][2];
+    __shared__ unsigned waves[kReuseThreads / kWave];
+    static_assert(kWords + kWave <= 32 * kHotWords, "the table holds both");
     const int t = (int)threadIdx.x;
+    if (blockIdx.x != 0) {
+        const int v = (int)blockIdx.x;
+        const unsigned met = hot_columns(entries, colidx, hot_table + (v - 1) * kHotTableInts, hot_shift, (unsigned)hot_room(v, hot_shift), table, waves);
+        if (t == 0) {
+            __hip_atomic_store(out + 2 * kReuseLevels + v - 1, (unsigned long long)met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            stores_done();
+            if (announce) __hip_atomic_store(announce + v, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        return;
+    }
     unsigned c[4][kReusePieces];
 #pragma unroll
     for (int part = 0; part < 4; ++part)

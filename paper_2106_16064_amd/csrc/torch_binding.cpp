@@ -87,6 +87,15 @@ void* as_stream(PyObject* o) {
     return p;
 }
 
+void* ptr(const at::Tensor& t) { return t.numel() == 0 ? nullptr : t.data_ptr(); }
+
+// the matrix arrays of the entry points that leave their checks to the library: None is a null pointer
+void* ptr(PyObject* o, const char* name) { return o == Py_None ? nullptr : ptr(as_tensor(o, name)); }
+
+bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == at::kStrided; }
+
+bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
+
 // The statistics of a ctypes `Features` structure, or of the `MatrixFeatures` that a DeviceCsr holds (None: there are none).
 class FeaturesArg {
 public:
@@ -102,23 +111,35 @@ public:
             throw Raised{};
         }
         given_ = true;
+        if (value_.hot_share[0] > 0.0 && dgsp_internal_wants_hot_columns(&value_, 1)) take_hot_columns(o);
     }
     const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
-    double saved_share() const { return value_.saved_share; }
+    // for a product with N columns on the GPU of `X`
+    dgsp_internal_hints_t hints(int64_t N, const at::Tensor& X) const {
+        const bool hot = hot_.defined() && hot_.device() == X.device() && dgsp_internal_wants_hot_columns(&value_, N);
+        return {value_.saved_share, hot ? static_cast<const uint32_t*>(hot_.data_ptr()) : nullptr};
+    }
 
 private:
+    // A tensor that the structure carries as an attribute and not as an address among its bytes, which could outlive it.
+    void take_hot_columns(PyObject* o) {
+        static PyObject* const name = PyUnicode_InternFromString("hot_columns");
+        PyObject* t = PyObject_GetAttr(o, name);
+        if (!t) {
+            PyErr_Clear();
+            return;
+        }
+        if (THPVariable_Check(t)) {
+            const at::Tensor& table = THPVariable_Unpack(t);
+            if (is_array(table, at::kInt) && table.numel() * 4 == dgsp_internal_hot_columns_bytes(&value_)) hot_ = table;
+        }
+        Py_DECREF(t);
+    }
+
     dgsp_internal_stats_t value_{};
     bool given_ = false;
+    at::Tensor hot_;
 };
-
-void* ptr(const at::Tensor& t) { return t.numel() == 0 ? nullptr : t.data_ptr(); }
-
-// the matrix arrays of the entry points that leave their checks to the library: None is a null pointer
-void* ptr(PyObject* o, const char* name) { return o == Py_None ? nullptr : ptr(as_tensor(o, name)); }
-
-bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == at::kStrided; }
-
-bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
 
 void check_array(const at::Tensor& t, at::ScalarType type, const char* name, const char* type_name) {
     if (!is_array(t, type)) fail(std::string(name) + " must be a contiguous " + type_name + " tensor on the GPU");
@@ -155,13 +176,26 @@ int unlocked(F&& call) {
     return rc;
 }
 
-void write_features(PyObject* o, const dgsp_internal_stats_t& f) {
+// what is known of a matrix when it has been taken over
+struct Measured {
+    dgsp_internal_stats_t stats{};
+    at::Tensor hot_columns;         // undefined: none, or none worth having
+};
+
+void write_features(PyObject* o, const Measured& m) {
+    const dgsp_internal_stats_t& f = m.stats;
     Py_buffer view;
     if (PyObject_GetBuffer(o, &view, PyBUF_WRITABLE) != 0) throw Raised{};
     const bool fits = view.len == (Py_ssize_t)sizeof(f);
     if (fits) memcpy(view.buf, &f, sizeof(f));
     PyBuffer_Release(&view);
     if (!fits) fail("features must be a MatrixFeatures structure");
+    if (m.hot_columns.defined()) {
+        PyObject* table = THPVariable_Wrap(m.hot_columns);
+        const int rc = PyObject_SetAttrString(o, "hot_columns", table);
+        Py_XDECREF(table);
+        if (rc != 0) throw Raised{};
+    }
 }
 
 // ---------------------------------------------------------------- one product
@@ -174,8 +208,9 @@ int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Ten
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), f.saved_share(), rp, ci, av, x, y, &algo, stream);
-    return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), f.saved_share(), stream);
+    const dgsp_internal_hints_t hints = f.hints(N, X);
+    if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), &hints, rp, ci, av, x, y, &algo, stream);
+    return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), &hints, stream);
 }
 
 // M x N, or M elements when the dense operand is a vector.  A GPU tensor comes from the allocator directly: the dispatcher's
@@ -241,26 +276,35 @@ struct ProductBackward : public torch::autograd::Node {
 
 struct CsrArrays { at::Tensor rowptr, colidx, vals; };
 
-// What narrower column blocks save, from the columns on the GPU: a launch and a wait, 20 us, where the matrix is one whose
-// products look at it (four million entries and more, very uneven rows).  Here and not in the product, which does not wait.
-void measure_columns(dgsp_internal_stats_t& stats, const at::Tensor& colidx, void* stream) {
-    if (colidx.numel() < stats.features.nnz) return;
+// What narrower column blocks save and which runs of columns are the hottest, from the columns on the GPU: a launch and a wait,
+// 20 us, where the matrix is one whose products look at it (four million entries and more, very uneven rows).  Here and not in
+// the product, which does not wait.
+void measure_columns(Measured& m, const at::Tensor& colidx, void* stream) {
+    if (colidx.numel() < m.stats.features.nnz) return;
     const auto* columns = static_cast<const int32_t*>(ptr(colidx));
-    (void)unlocked([&] { return dgsp_internal_measure_columns(&stats, columns, stream); });      // not measured: wide blocks
+    uint32_t* table = nullptr;
+    if (const int64_t bytes = dgsp_internal_hot_columns_bytes(&m.stats)) {
+        m.hot_columns = at::empty({bytes / 4}, colidx.options());
+        table = static_cast<uint32_t*>(m.hot_columns.data_ptr());
+    }
+    const int rc = unlocked([&] { return dgsp_internal_measure_columns(&m.stats, columns, table, stream); });
+    if (rc != DGSP_OK) m.stats = dgsp_internal_stats_t{m.stats.features};       // not measured: the general way
+    // what wider products have of it is less
+    if (!dgsp_internal_wants_hot_columns(&m.stats, 1)) m.hot_columns.reset();
 }
 
 // The arrays in the library's types and the statistics, which the call waits for.  int64 indices are narrowed by the
 // statistics' own launch.
 CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Tensor& colidx, const at::Tensor& vals,
-                   dgsp_internal_stats_t& stats) {
+                   Measured& measured) {
     at::NoGradGuard no_grad;
+    dgsp_internal_stats_t& stats = measured.stats;
     CsrArrays out;
     const bool wide = is_array(rowptr, at::kLong) && is_array(colidx, at::kLong) && M > 0 && colidx.numel() < INT32_MAX - 4096;
     out.rowptr = wide ? at::empty(rowptr.sizes(), rowptr.options().dtype(at::kInt)) : rowptr.to(at::kInt).contiguous();
     out.colidx = wide ? at::empty(colidx.sizes(), colidx.options().dtype(at::kInt)) : colidx.to(at::kInt).contiguous();
     out.vals = is_array(vals, at::kFloat) ? vals : vals.to(at::kFloat).contiguous();
     if (!on_gpu(out.rowptr) || !on_gpu(out.colidx) || out.rowptr.numel() != M + 1) fail("rowptr needs M+1 entries on the GPU");
-    stats = dgsp_internal_stats_t{};
     if (M == 0) {
         stats.features.K = K;
         return out;
@@ -273,7 +317,7 @@ CsrArrays take_csr(int64_t M, int64_t K, const at::Tensor& rowptr, const at::Ten
     auto* ci32 = static_cast<int32_t*>(ptr(out.colidx));
     check_status(unlocked([&] { return dgsp_internal_take_csr(M, K, entries, wide ? 8 : 4, rp, ci, rp32, ci32, &stats.features, stream); }),
                  "dgsp_features_from_csr_device");
-    measure_columns(stats, out.colidx, stream);
+    measure_columns(measured, out.colidx, stream);
     return out;
 }
 
@@ -358,7 +402,7 @@ PyObject* wrapped(CsrArrays&& a, int64_t M, int64_t K) {
 PyObject* csr_from_arrays(PyObject* const* a, Py_ssize_t n) {
     want(n, 6);
     const int64_t M = as_int(a[0]), K = as_int(a[1]);
-    dgsp_internal_stats_t f;
+    Measured f;
     CsrArrays arrays = take_csr(M, K, as_tensor(a[2], "rowptr"), as_tensor(a[3], "colidx"), as_tensor(a[4], "vals"), f);
     write_features(a[5], f);
     return wrapped(std::move(arrays), M, K);
@@ -369,22 +413,23 @@ PyObject* csr_from_tensor(PyObject* const* a, Py_ssize_t n) {
     want(n, 2);
     const at::Tensor& T = as_tensor(a[0], "matrix");
     if (T.layout() != at::kSparseCsr || T.dim() != 2) fail("the matrix must be a 2-D sparse CSR tensor");
-    dgsp_internal_stats_t f;
+    Measured f;
     CsrArrays arrays = take_csr(T.size(0), T.size(1), T.crow_indices(), T.col_indices(), T.values().detach(), f);
     write_features(a[1], f);
     return wrapped(std::move(arrays), T.size(0), T.size(1));
 }
 
-// (features, colidx): the share of a matrix whose statistics are from the host; waits for the current stream of its device
-PyObject* measure_saved_share(PyObject* const* a, Py_ssize_t n) {
+// (features, colidx): the columns of a matrix whose statistics are from the host; waits for the current stream of its device
+PyObject* measure_matrix_columns(PyObject* const* a, Py_ssize_t n) {
     want(n, 2);
     FeaturesArg f(a[0]);
     const at::Tensor& colidx = as_tensor(a[1], "colidx");
     if (f.get() && is_array(colidx, at::kInt)) {
         const c10::DeviceGuard guard(colidx.device());
-        dgsp_internal_stats_t stats{*f.get(), 0.0};
-        measure_columns(stats, colidx, c10::hip::getCurrentHIPStream().stream());
-        write_features(a[0], stats);
+        Measured m;
+        m.stats.features = *f.get();
+        measure_columns(m, colidx, c10::hip::getCurrentHIPStream().stream());
+        write_features(a[0], m);
     }
     Py_RETURN_NONE;
 }
@@ -405,8 +450,9 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
+    const dgsp_internal_hints_t hints = f.hints(N, X);
     check_status(unlocked([&] {
-        return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), f.saved_share(), stream);
+        return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), &hints, stream);
     }), "dgsp_spmm_csr_phase");
     Py_RETURN_NONE;
 }
@@ -476,8 +522,9 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
+    const dgsp_internal_hints_t hints = f.hints(N, X);
     const int rc = unlocked([&] {
-        return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), f.saved_share(), stream);
+        return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), &hints, stream);
     });
     check_status(rc, factors ? "dgsp_spmm_csr_axpby" : "dgsp_spmm_csr_ld");
 }
@@ -501,7 +548,7 @@ PyObject* spmm_csr_axpby(PyObject* const* a, Py_ssize_t n) {
 PyMethodDef g_methods[] = {
     DGSP_ENTRY(set_error_type), DGSP_ENTRY(multiply_new), DGSP_ENTRY(multiply_differentiable), DGSP_ENTRY(spmm_csr_auto),
     DGSP_ENTRY(spmm_csr), DGSP_ENTRY(spmm_csr_nnz), DGSP_ENTRY(spmm_csr_ld), DGSP_ENTRY(spmm_csr_axpby), DGSP_ENTRY(spmm_csr_phase),
-    DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), DGSP_ENTRY(measure_saved_share), {nullptr, nullptr, 0, nullptr},
+    DGSP_ENTRY(csr_from_arrays), DGSP_ENTRY(csr_from_tensor), DGSP_ENTRY(measure_matrix_columns), {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_dgsp_torch", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -434,6 +434,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
                                                              int tile_log2, float beta) {
     const long long row = (long long)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the row's bounds
     bool split = false;
     if (row < M) {
         const unsigned first = (unsigned)row + (unsigned)rowptr[row];       // diagonal of the row's first item
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
         // An empty row is a single item.  Every chunk and tile starts at a multiple of the quantum, so a row
         // whose items lie inside one quantum cannot be split: most rows stop here, before the divisions.
         if (first != last && (first >> quantum_log2) != (last >> quantum_log2)) {
-            const EvenSplit es((unsigned)rowptr[M] + (unsigned)M, parts, quantum_log2);
+            const EvenSplit es(items, parts, quantum_log2);
             const unsigned c1 = es.chunk_of(first), c2 = es.chunk_of(last);
             split = c1 != c2;
             if (!split && tile_log2 >= 0) {
@@ -517,17 +518,25 @@ __device__ __forceinline__ ChunkPlan plan_chunks(const int* __restrict__ rowptr,
     return ChunkPlan(nnz, nnz + (unsigned)M, nwg * kWavesPerBlock, wg * kWavesPerBlock + wave_in_block(), quantum_log2);
 }
 
+// What the first round of a search probes does not depend on what is searched for: asked for beside the entry count, from
+// which the diagonals follow, it saves a chunk's start one round trip to memory.
+__device__ __forceinline__ int first_probe(const int* __restrict__ rowptr, int M, int lane) {
+    const long long r = (long long)lane * ((M + 63ll) >> 6);
+    return r < M ? rowptr[r + 1] : 0;
+}
+
 // Number of rows whose end marker lies before diagonal d, i.e. rows r with
 // r + rowptr[r+1] < d (that key is strictly increasing in r).  64-way search,
 // wave-uniform result.
-__device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ rowptr, int M, unsigned d, int lane) {
+// `probe`: first_probe().
+__device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ rowptr, int M, unsigned d, int lane, int probe) {
     int lo = 0, hi = M;   // rows < lo end before d; rows >= hi do not
-    while (hi > lo) {
-        const int span = hi - lo;
-        const int step = (span + 63) >> 6;
+    for (bool first = true; hi > lo; first = false) {
+        const int step = (int)(((long long)hi - lo + 63) >> 6);
         const long long r = (long long)lo + (long long)lane * step;
-        bool before = false;
-        if (r < hi) before = (unsigned)r + (unsigned)rowptr[r + 1] < d;
+        int v = probe;
+        if (!first) v = r < hi ? rowptr[r + 1] : 0;
+        const bool before = r < hi && (unsigned)r + (unsigned)v < d;
         const int cnt = __popcll(__ballot(before));   // probes are monotone: 1...10...0
         if (cnt == 0) {
             hi = lo;
@@ -542,20 +551,23 @@ __device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ ro
 }
 
 // Rows that ended before diagonal da, and before db (both searches of wave_merge_rows_before in lock-step: their
-// probes are in flight together, so the second costs no further round trips).
+// probes are in flight together, so the second costs no further round trips).  `probe`: first_probe().
 __device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ rowptr, int M, unsigned da, unsigned db,
-                                                        int lane, int& ra, int& rb) {
+                                                        int lane, int probe, int& ra, int& rb) {
     int lo[2] = {0, 0}, hi[2] = {M, M};
     const unsigned d[2] = {da, db};
+    bool first = true;
     while (hi[0] > lo[0] || hi[1] > lo[1]) {
         int step[2], v[2];
         long long r[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            step[k] = (hi[k] - lo[k] + 63) >> 6;
+            step[k] = (int)(((long long)hi[k] - lo[k] + 63) >> 6);
             r[k] = (long long)lo[k] + (long long)lane * step[k];
-            v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
+            v[k] = probe;
+            if (!first) v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
         }
+        first = false;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             if (hi[k] > lo[k]) {                                   // wave-uniform
@@ -582,12 +594,13 @@ __device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ 
 // before d1, into those of its rows.
 __device__ __forceinline__ void snap_to_rows(const int* __restrict__ rowptr, int M, unsigned d0, unsigned d1, int& is, int& ie,
                                              unsigned& js, unsigned& je) {
-    // rows that started before a chunk's first item belong to the chunk before
-    if (is < M && (unsigned)is + (unsigned)rowptr[is] < d0) ++is;
-    if (ie < M && (unsigned)ie + (unsigned)rowptr[ie] < d1) ++ie;
-    is = uniform(is); ie = uniform(ie);
-    js = (unsigned)uniform(rowptr[is]);
-    je = (unsigned)uniform(rowptr[ie]);
+    // rows that started before a chunk's first item belong to the chunk before; where the next row starts is asked for at once
+    const unsigned s0 = (unsigned)rowptr[is], s1 = (unsigned)rowptr[is < M ? is + 1 : M];
+    const unsigned e0 = (unsigned)rowptr[ie], e1 = (unsigned)rowptr[ie < M ? ie + 1 : M];
+    const bool skip = is < M && (unsigned)is + s0 < d0, past = ie < M && (unsigned)ie + e0 < d1;
+    js = (unsigned)uniform((int)(skip ? s1 : s0));
+    je = (unsigned)uniform((int)(past ? e1 : e0));
+    is = uniform(skip ? is + 1 : is); ie = uniform(past ? ie + 1 : ie);
 }
 
 constexpr unsigned kNoRow = 0xffffffffu;
@@ -647,6 +660,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     float* buf = s_buf[wib];
     const int n0 = blockIdx.y * V;
 
+    const int probe = first_probe(rowptr, M, lane);
     const ChunkPlan plan = plan_chunks(rowptr, M, 6);        // quanta of one wave's width
     const unsigned nnz = plan.nnz;
     const unsigned long long y_elems = dense_bytes(M, ldy, N) / 4ull;
@@ -684,13 +698,13 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     bool first_split = false;
     if (snap) {
         int ie1; unsigned je1;
-        wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
+        wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
         snap_to_rows(rowptr, M, d0, d1, is, ie1, js, je1);
         if (is == ie1) continue;
         d0 = (unsigned)is + js;
         d1 = (unsigned)ie1 + je1;
     } else {
-        is = wave_merge_rows_before(rowptr, M, d0, lane);
+        is = wave_merge_rows_before(rowptr, M, d0, lane, probe);
         js = d0 - (unsigned)is;
         first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
     }
@@ -1023,6 +1037,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     float* buf = s_buf[wib];
     const int n0 = blockIdx.y * V;
 
+    const int probe = first_probe(rowptr, M, lane);
     const unsigned nnz = (unsigned)rowptr[M];
     const ChunkPlan plan(nnz, nnz + (unsigned)M, gridDim.x * kWaves, xcd_contiguous(blockIdx.x, gridDim.x) * kWaves + wib, 6);   // quanta of one wave's width
     const unsigned long long y_elems = dense_bytes(M, ldy, N) / 4ull;
@@ -1067,7 +1082,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
     int is = 0, ie1 = 0;
-    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie1);
+    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
     if constexpr (HOT) {
 #pragma unroll
         for (int k = 0; k < kWordPieces; ++k) {
@@ -1516,6 +1531,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
     const long long n = mine.first;
     const bool col_ok = mine.any;
 
+    const int probe = first_probe(rowptr, M, lane);
     // chunks start at multiples of U: runs stay aligned
     const ChunkPlan plan = plan_chunks(rowptr, M, (unsigned)logU);
     const unsigned nnz = plan.nnz;
@@ -1528,7 +1544,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
     for (unsigned sub = 0; sub < kSubRanges; ++sub) {
     unsigned d0, d1;
     if (!plan.range(sub, d0, d1)) continue;
-    int is = wave_merge_rows_before(rowptr, M, d0, lane);
+    int is = wave_merge_rows_before(rowptr, M, d0, lane, probe);
     unsigned js = d0 - (unsigned)is;
     for (unsigned ds = d0; ds < d1; ds += W) {
         const unsigned de = (d1 - ds > (unsigned)W) ? ds + W : d1;
@@ -1825,6 +1841,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
     int* rows = s_rows[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
+    const int probe = first_probe(rowptr, M, lane);
     unsigned col_block = blockIdx.y, wg, nwg;
     if (pinned_blocks) {
         const unsigned x = blockIdx.x % kXcd, i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
@@ -1848,7 +1865,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
     unsigned d0, d1;
     if (!plan.range(0, d0, d1)) return;
     int is, ie;
-    wave_merge_rows_before2(rowptr, M, d0, d1, lane, is, ie);
+    wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie);
     unsigned js, je;
     bool first_split = false;
     if (snap) {

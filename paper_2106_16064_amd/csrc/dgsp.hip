@@ -75,8 +75,9 @@ struct Hints {
     double saved_share = 0.0;   // what column blocks half as wide would save (kSavedShareMin); 0 = unknown
     const uint32_t* hot_columns = nullptr;      // the hot runs of a matrix of `hot_K` columns
     int64_t hot_K = 0;
+    const dgsp_internal_hints_t* more = nullptr;     // for its workspace
     Hints() = default;
-    explicit Hints(const dgsp_features_t* f, const dgsp_internal_hints_t* more = nullptr) {
+    explicit Hints(const dgsp_features_t* f, const dgsp_internal_hints_t* more = nullptr) : more(more) {
         if (f) { col_span = f->col_span; cv_row = f->cv_row; max_row = f->max_row; }
         if (more) saved_share = more->saved_share;
         if (f && more) { hot_columns = more->hot_columns; hot_K = f->K; }
@@ -96,6 +97,7 @@ struct Problem {
     long long size = -1;     // the entry count or, for launch geometry, a bound of it; < 0 = unknown
     double saved_share = 0.0;  // see Hints
     const uint32_t* hot_columns = nullptr;
+    const dgsp_internal_hints_t* more = nullptr;
     int switches = 0;        // DGSP_ABL_* (measurement aids)
     bool scaled = false;     // Y = alpha * A X + beta * Y instead of Y = A X
     float alpha = 1.0f, beta = 0.0f;
@@ -420,11 +422,39 @@ int launch_rs_sr(const Problem& p) {
 // ---------------------------------------------------------------- balanced launches
 // Zeroes (scaled form: multiplies by beta) the rows split by the `parts` chunks the main kernel derives
 // (quanta of 2^quantum_log2 items), cut into tiles of 2^tile_log2 items (tile_log2 < 0: not cut further).
-int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2) {
+int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{}) {
     const dim3 grid((unsigned)(((long long)p.M + kBlock - 1) / kBlock));
-    DGSP_LAUNCH(nb_prepare_kernel, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2,
-                p.scaled ? p.beta : 0.0f);
+    const float beta = p.scaled ? p.beta : 0.0f;
+    if (queues.starts)
+        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues);
+    else
+        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues);
     return DGSP_OK;
+}
+
+// How `waves` waves on each XCD share out the items (`lists` times: column blocks that are a grid dimension) with the help of
+// memory of the caller's; nothing if it has none to give.  The prepare launch's first rows clear the counters, so there have to be
+// as many.  Three tenths of a wave's share (`share` items) are its first piece, the rest goes by chunks of a quarter of a share, 512 to
+// 1024 items: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares 1024 us), at
+// N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).
+constexpr double kFirstPiece = 0.3;
+constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
+ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
+    ChunkQueues q{};
+    const long long items = p.nnz + (long long)p.M;
+    const long long size = std::min<long long>(std::max<long long>(share / 4, 512), 1024), chunks = (items + size - 1) / size;
+    const unsigned run = (unsigned)((double)(chunks / parts) * kFirstPiece / waves);
+    const size_t counters = (size_t)kXcd * lists;
+    if (run == 0 || !p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0 || (size_t)p.M < counters) return q;
+    const size_t head = counters * kQueuePitch * sizeof(unsigned);
+    char* mem = static_cast<char*>(p.more->workspace(p.more->context, head + (size_t)(chunks + 1) * sizeof(int)));
+    if (!mem) return q;
+    q.taken = reinterpret_cast<unsigned*>(mem);
+    q.starts = reinterpret_cast<int*>(mem + head);
+    q.chunks = (unsigned)chunks;
+    q.counters = (unsigned)counters;
+    q.parts = parts; q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
+    return q;
 }
 
 // Blocks of the grid that shares the nnz + M merge-path items of a balanced kernel, `tile` items per
@@ -666,15 +696,32 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     const unsigned chunk_groups = pinned ? grid.x / pinned : grid.x;              // workgroups that share one chunk list
     // a wave alone takes one batch of its lane groups in about 1 us
     const int snap = snap_rows(p, chunk_groups, 1.0, (double)((kWave >> LOGG) * kRunBatch), lines_per_row(cols.cols_per_block, p.ldx) * col_blocks);
+    // Queues instead of equal shares where a chunk is long against what it costs to start one (5 us): from 2048 items a wave and
+    // as many lanes to an entry that the share is 32 768 lane steps.  R-MAT 2^20 x 16 at N = 32 / 41 / 64 / 128 256 / 422 / 507 / 1021 -> 240 /
+    // 405 / 443 / 880 us, 2^20 x 32 at N = 20 / 32 416 / 469 -> 393 / 419 us, 2^20 x 8 at N = 41 257 -> 240 us, 2^18 x 16 at N = 128 201 -> 194 us,
+    // 2^19 x 16 at N = 100 405 -> 398 us; not 2^20 x 16 at N = 16 (170 against 173 to 190 us), 2^19 x 16 at N = 32 (106 / 113 us), 2^18 x 32 at N = 48
+    // (136 / 140 us), nor with few entries a row, whose workgroups are dealt to the XCDs one by one (2^20 x 6 at N = 50 207 / 223 us).
+    ChunkQueues queues{};
+    dim3 queue_grid = grid;
+    if (XBUF && !snap && p.nnz > 0 && grid.x % kXcd == 0 && p.nnz / p.M >= run_dealt_below(LOGG)) {
+        const unsigned parts = pinned ? kXcd / pinned : kXcd;
+        // no more than are resident: what is started late finds the queues empty
+        if (pinned) queue_grid.x = std::min<unsigned>(grid.x, (unsigned)(device_info().cus * resident) / kXcd * kXcd);
+        const unsigned waves = queue_grid.x / kXcd * kWavesPerBlock;
+        const long long share = (p.nnz + (long long)p.M) / parts / waves;
+        if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
+    }
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, chunk_groups * kWavesPerBlock * kSubRanges, 6, -1)) return rc;
+        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, 6, -1, queues)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
-        if (p.scaled)
-            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
-                        cols.cols_per_block, snap, Scaling{p.alpha, p.beta}, pinned);
-        else
-            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, false>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
-                        cols.cols_per_block, snap, Scaling{1.0f, 0.0f}, pinned);
+        const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
+        const auto launch = [&](auto scaled, auto queued) -> int {
+            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, decltype(scaled)::value, XBUF && decltype(queued)::value>), queues.starts ? queue_grid : grid, p.M, p.K, p.N, p.ldx, p.ldy,
+                        p.rowptr, p.colidx, p.vals, p.X, p.Y, cols.cols_per_block, snap, sc, pinned, queues);
+            return DGSP_OK;
+        };
+        if (queues.starts) return p.scaled ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+        return p.scaled ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
     }
     return DGSP_OK;
 }
@@ -786,7 +833,7 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, hints.hot_K == K ? hints.hot_columns : nullptr, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, hints.hot_K == K ? hints.hot_columns : nullptr, hints.more, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     if (hints.chosen) algo = launched_algo(p, algo);
     switch (algo) {

@@ -16,11 +16,15 @@ typedef struct {
     double saved_share, hot_share[4];
 } dgsp_internal_stats_t;
 
-/* What a product may know beyond the public statistics; NULL: nothing.  hot_columns: the table that
- * dgsp_internal_measure_columns wrote for this matrix, on the product's GPU, or NULL. */
+/* What a product may know and use beyond the public statistics; NULL: nothing.  hot_columns: the table that
+ * dgsp_internal_measure_columns wrote for this matrix, on the product's GPU, or NULL.  workspace(context, bytes): device memory on
+ * the product's GPU, aligned to 128 bytes, that is this call's until its launches on the product's stream have run; asked for
+ * at most once a call, it may return NULL, and the product goes without. */
 typedef struct {
     double saved_share;
     const uint32_t *hot_columns;
+    void *(*workspace)(void *context, size_t bytes);
+    void *context;
 } dgsp_internal_hints_t;
 
 /* Statistics of a device CSR matrix with `entries` column indices, in one launch, and its arrays in 32-bit form:

@@ -424,32 +424,84 @@ struct EvenSplit {
     }
 };
 
+// How a call with a workspace shares out the items (nb_sr_run_kernel).  The even split into `chunks` chunks is dealt to
+// `parts` parts, one per XCD that works on a list.  The first chunks of a part are its waves' shares, `run` consecutive ones a
+// wave, a single piece; the others are taken one by one by whoever is done, first from the wave's own part.  In the
+// workspace: `taken`, a counter for each XCD's queue, kQueuePitch words apart, and `starts`, for each chunk and for the end of the
+// list the number of rows that ended before it, which saves the waves their searches.
+constexpr unsigned kQueuePitch = 32;
+struct ChunkQueues {
+    unsigned* taken; int* starts;
+    unsigned chunks, counters, parts, waves, run, helpers;
+    __device__ __forceinline__ unsigned part_from(unsigned part) const { return (unsigned)((unsigned long long)chunks * part / parts); }
+    __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
+    // a number for the piece that chunk c belongs to, different for different pieces
+    __device__ __forceinline__ unsigned piece_of(unsigned c) const {
+        unsigned part = (unsigned)((unsigned long long)c * parts / chunks);
+        while (part + 1u < parts && part_from(part + 1u) <= c) ++part;
+        const unsigned from = part_from(part), at = c - from;
+        return at < waves * run ? from + at / run * run : c;
+    }
+};
+
 // Zeroes the rows whose items do not all lie in one piece of the partition (beta != 0, the scaled
 // variants: multiplies them by beta instead, so that the partial sums added later land on beta * Y).
 // The pieces are the `parts` chunks of the even split with quanta of
 // 2^quantum_log2 items, cut further into tiles of 2^tile_log2 items counted
 // from the chunk's start when tile_log2 >= 0.
 // One thread per row for the test (split rows are few: at most two per piece).
+// QUEUES: the chunks' first rows and the counters are written as well.
+template <bool QUEUES>
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
-                                                             int tile_log2, float beta) {
+                                                             int tile_log2, float beta, ChunkQueues queues) {
     const long long row = (long long)blockIdx.x * kBlock + threadIdx.x;
     const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the row's bounds
     bool split = false;
+    unsigned c_from = 0, c_to = 0;                                          // chunks that start within the row's items
     if (row < M) {
         const unsigned first = (unsigned)row + (unsigned)rowptr[row];       // diagonal of the row's first item
         const unsigned last = (unsigned)row + (unsigned)rowptr[row + 1];    // diagonal of its end marker
+        const unsigned before = first - 1u;                                 // wraps for the list's first item: in no quantum of this row
         // An empty row is a single item.  Every chunk and tile starts at a multiple of the quantum, so a row
         // whose items lie inside one quantum cannot be split: most rows stop here, before the divisions.
-        if (first != last && (first >> quantum_log2) != (last >> quantum_log2)) {
+        // Nor does a chunk start in a row that has no multiple of the quantum among its items.
+        const bool across = first != last && (first >> quantum_log2) != (last >> quantum_log2);
+        const bool starting = QUEUES && ((before >> quantum_log2) != (last >> quantum_log2) || row == M - 1);
+        if (across || starting) {
             const EvenSplit es(items, parts, quantum_log2);
             const unsigned c1 = es.chunk_of(first), c2 = es.chunk_of(last);
-            split = c1 != c2;
-            if (!split && tile_log2 >= 0) {
+            split = across && c1 != c2;
+            if constexpr (QUEUES) split = split && queues.piece_of(c1) != queues.piece_of(c2);
+            if (across && !split && tile_log2 >= 0) {
                 const unsigned start = es.start(c1);
                 split = (first - start) >> tile_log2 != (last - start) >> tile_log2;
             }
+            if (starting) {
+                c_from = c1;
+                if (es.start(c1) < first) ++c_from;
+                while (c_from > 0u && es.start(c_from - 1u) >= first) --c_from;      // chunks without items start where the next one does
+                c_to = (c2 < parts ? c2 + 1u : parts);
+            }
         }
+    }
+    if constexpr (QUEUES) {
+        const unsigned t = (unsigned)row;
+        if (row < (long long)queues.counters) queues.taken[t * kQueuePitch] = 0u;
+        // a few chunks each; a row of very many is written by the whole wave
+        constexpr unsigned kOwn = 8;
+        for (unsigned c = c_from; c < c_to && c < c_from + kOwn; ++c) queues.starts[c] = (int)row;
+        unsigned long long wide = __ballot(c_to > c_from + kOwn);
+        while (wide != 0ull) {                                              // wave-uniform
+            const int src = __ffsll((long long)wide) - 1;
+            wide &= wide - 1ull;
+            const unsigned from = (unsigned)read_lane((int)c_from, src) + kOwn, to = (unsigned)read_lane((int)c_to, src);
+            const int r = read_lane((int)row, src);
+            for (unsigned c = from + (unsigned)lane_id(); c < to; c += (unsigned)kWave) queues.starts[c] = r;
+        }
+        // chunks past the last item, and the list's end
+        if (row == M - 1)
+            for (unsigned c = c_to; c <= parts; ++c) queues.starts[c] = M;
     }
     if (N <= 8) {                                      // narrow rows: the thread clears its own
         if (split) {
@@ -1809,6 +1861,12 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // pinned_blocks = nb (2 or 4; gridDim = (8 k, 1)): the workgroups of XCD x all take column block x % nb, so that an L2
 // only ever sees one block's slice of X; the 8 / nb XCDs of a block share its chunk list, each a contiguous part.
 // Otherwise blockIdx.y is the column block.
+//
+// QUEUED: equal shares do not end together.  What a row of X costs depends on how much of it the L2 holds, and the XCDs do not
+// reach memory equally fast (R-MAT 2^20 x 16, us: N = 128 794 772 820 998 768 875 775 1002, column block 3 last; N = 32 184 to 226; Zipf
+// rows of 16 at N = 64 138 to 146 on the even XCDs, 156 to 166 on the odd ones).  So a wave starts on a part of its share and takes the
+// rest chunk by chunk from its XCD's queue, and some waves of an XCD that is done help the others (ChunkQueues).  A failed
+// take is an add to a word that all waves of the XCD add to, 13 ns a time, which is why most waves stop at their first.
 constexpr int kRunBlock = 512;       // entries per block
 constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
 
@@ -1823,12 +1881,15 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
     return (unsigned)read_lane((int)v, kWave - 1);
 }
 
-template <int LOGG, bool XBUF, bool AXPBY>
-__global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
+// entries per row below which neighbouring chunks go to different XCDs
+__host__ __device__ constexpr int run_dealt_below(int log_lanes) { return log_lanes >= 5 ? 8 : 6; }
+
+template <int LOGG, bool XBUF, bool AXPBY, bool QUEUED = false>
+__global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
                                                            const int* __restrict__ rowptr, const int* __restrict__ colidx,
                                                            const float* __restrict__ vals, const float* __restrict__ X,
                                                            float* __restrict__ Y, int cols_per_block, int snap, Scaling sc,
-                                                           unsigned pinned_blocks) {
+                                                           unsigned pinned_blocks, ChunkQueues queues) {
     constexpr int W = kRunBlock, E = W / kWave, B = kRunBatch;
     constexpr int G = 1 << LOGG, R = kWave / G;
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
@@ -1841,31 +1902,77 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
     int* rows = s_rows[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
-    const int probe = first_probe(rowptr, M, lane);
+    int probe = 0;
+    if constexpr (!QUEUED) probe = first_probe(rowptr, M, lane);
+    const unsigned nnz = (unsigned)rowptr[M], items = nnz + (unsigned)M;
+    // Neighbouring chunks on one XCD share lines of A and Y - but where rows have few entries what an item costs changes
+    // along the list (row ends and empty rows at the sparse end of a graph), and an XCD with the dear part ends last
+    // (R-MAT 2^20 x 6, contiguous against dealt out one by one: N = 32 112 or 128 / 113 us, N = 101 420 or 470 / 383 us, the
+    // longer of the two on the hardware queue a process gets first; 2^20 x 8 at N = 32 138 / 143, at N = 101 503 / 478 us,
+    // 2^20 x 16 at N = 32 252 / 260 us).
     unsigned col_block = blockIdx.y, wg, nwg;
+    const unsigned xcd = blockIdx.x % kXcd;
     if (pinned_blocks) {
-        const unsigned x = blockIdx.x % kXcd, i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
-        col_block = x % pinned_blocks;
-        wg = (x / pinned_blocks) * per_xcd + i;
+        const unsigned i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
+        col_block = xcd % pinned_blocks;
+        wg = (xcd / pinned_blocks) * per_xcd + i;
         nwg = (kXcd / pinned_blocks) * per_xcd;
     } else {
-        // Neighbouring chunks on one XCD share lines of A and Y - but where rows have few entries what an item costs changes
-        // along the list (row ends and empty rows at the sparse end of a graph), and an XCD with the dear part ends last
-        // (R-MAT 2^20 x 6, contiguous against dealt out one by one: N = 32 112 or 128 / 113 us, N = 101 420 or 470 / 383 us, the
-        // longer of the two on the hardware queue a process gets first; 2^20 x 8 at N = 32 138 / 143, at N = 101 503 / 478 us,
-        // 2^20 x 16 at N = 32 252 / 260 us).
-        const unsigned per_row = (unsigned)rowptr[M] / (unsigned)M;
-        wg = per_row < (LOGG >= 5 ? 8u : 6u) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
+        wg = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
+    }
+    const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, 6);
+    // queue q: what the waves of XCD q leave of its part of the chunks
+    const auto part_of = [&](unsigned q) { return pinned_blocks ? q / pinned_blocks : q; };
+    const auto queue_size = [&](unsigned q) { return queues.part_from(part_of(q) + 1u) - queues.queue_from(part_of(q)); };
+    unsigned* taken = queues.taken + (size_t)blockIdx.y * kXcd * kQueuePitch;
+    unsigned queue = xcd;
+    const unsigned own = blockIdx.x / kXcd * kWavesPerBlock + (unsigned)wib;         // of the XCD's waves
+    bool first_piece = true;
+
+    for (;;) {                                           // one piece, or one after the other
+    unsigned chunk = wg * kWavesPerBlock + (unsigned)wib, chunk_end = chunk + 1u;
+    if constexpr (QUEUED) {
+        if (first_piece) {
+            chunk = queues.part_from(part_of(xcd)) + own * queues.run;
+            chunk_end = chunk + queues.run;
+            first_piece = false;
+        } else {
+            bool found = false;
+            while (!found) {
+                unsigned n = 0;
+                if (lane == 0) n = atomicAdd(taken + queue * kQueuePitch, 1u);
+                n = (unsigned)uniform((int)n);
+                const unsigned size = queue_size(queue);
+                if (n < size) {
+                    chunk = queues.queue_from(part_of(queue)) + n;
+                    chunk_end = chunk + 1u;
+                    if (pinned_blocks) col_block = queue % pinned_blocks;
+                    found = true;
+                    break;
+                }
+                // Empty.  The first waves to see it of their own queue help with the others, nearest first, the rest are done: a word
+                // that all waves add to takes 13 ns a time.
+                if (queue == xcd && n - size >= queues.helpers) break;
+                queue = (queue + 1u) % kXcd;
+                if (queue == xcd) break;
+            }
+            if (!found) return;
+        }
     }
     const LaneColumns mine = lane_columns<4, true>(col_block, cols_per_block, gl, N);
     const bool col_ok = mine.any;
-
-    const ChunkPlan plan = plan_chunks(rowptr, M, 6, wg, nwg);
-    unsigned d0, d1;
-    if (!plan.range(0, d0, d1)) return;
+    const unsigned d0 = share.start(chunk), d_end = share.start(chunk_end), d1 = d_end < items ? d_end : items;
+    if (d0 >= d1) {
+        if constexpr (QUEUED) continue; else return;
+    }
     int is, ie;
-    wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie);
+    if constexpr (QUEUED) {
+        is = queues.starts[chunk];
+        ie = queues.starts[chunk_end];
+    } else {
+        wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie);
+    }
     unsigned js, je;
     bool first_split = false;
     if (snap) {
@@ -2126,6 +2233,8 @@ __global__ __launch_bounds__(kBlock) void nb_sr_run_kernel(int M, long long K, i
 #pragma unroll
         for (int i = 0; i < 4; ++i) any |= carry[i] != 0.0f;
         if (any && g == 0 && col_ok) add_row(ie, carry);
+    }
+    if constexpr (!QUEUED) return;
     }
 }
 

@@ -14,6 +14,7 @@
 #include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
@@ -96,6 +97,33 @@ bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == 
 
 bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
 
+// Device memory for one product, of the stream that it runs on: given back when the call returns, it is handed out again to work
+// that comes later on that stream only.  None while the stream records a graph, whose replays the allocator may not know of.
+class Workspace {
+public:
+    explicit Workspace(void* stream) : stream_(static_cast<hipStream_t>(stream)) {}
+    Workspace(const Workspace&) = delete;
+    Workspace& operator=(const Workspace&) = delete;
+    ~Workspace() {
+        if (memory_) c10::hip::HIPCachingAllocator::raw_delete(memory_);
+    }
+    static void* get(void* context, size_t bytes) {
+        auto* self = static_cast<Workspace*>(context);
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (self->memory_ || hipStreamIsCapturing(self->stream_, &status) != hipSuccess || status != hipStreamCaptureStatusNone) return nullptr;
+        try {
+            self->memory_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, self->stream_);
+        } catch (...) {                            // out of memory: the product does without
+            self->memory_ = nullptr;
+        }
+        return self->memory_;
+    }
+
+private:
+    hipStream_t stream_;
+    void* memory_ = nullptr;
+};
+
 // The statistics of a ctypes `Features` structure, or of the `MatrixFeatures` that a DeviceCsr holds (None: there are none).
 class FeaturesArg {
 public:
@@ -115,9 +143,9 @@ public:
     }
     const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
     // for a product with N columns on the GPU of `X`
-    dgsp_internal_hints_t hints(int64_t N, const at::Tensor& X) const {
+    dgsp_internal_hints_t hints(int64_t N, const at::Tensor& X, Workspace& workspace) const {
         const bool hot = hot_.defined() && hot_.device() == X.device() && dgsp_internal_wants_hot_columns(&value_, N);
-        return {value_.saved_share, hot ? static_cast<const uint32_t*>(hot_.data_ptr()) : nullptr};
+        return {value_.saved_share, hot ? static_cast<const uint32_t*>(hot_.data_ptr()) : nullptr, &Workspace::get, &workspace};
     }
 
 private:
@@ -208,7 +236,8 @@ int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Ten
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    const dgsp_internal_hints_t hints = f.hints(N, X);
+    Workspace workspace(stream);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), &hints, rp, ci, av, x, y, &algo, stream);
     return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), &hints, stream);
 }
@@ -450,7 +479,8 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    const dgsp_internal_hints_t hints = f.hints(N, X);
+    Workspace workspace(stream);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     check_status(unlocked([&] {
         return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), &hints, stream);
     }), "dgsp_spmm_csr_phase");
@@ -522,7 +552,8 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    const dgsp_internal_hints_t hints = f.hints(N, X);
+    Workspace workspace(stream);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     const int rc = unlocked([&] {
         return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), &hints, stream);
     });

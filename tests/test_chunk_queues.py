@@ -1,0 +1,108 @@
+"""Products whose waves take chunks from queues (nb_sr_run_kernel, QUEUED), against the oracle.  The queues live in memory that the
+call asks torch's allocator for, so its statistics tell that a product ran this way."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_16064_amd import binding as dg
+from paper_2106_16064_amd import workloads as wl
+
+
+def rows_of(lens, K, seed):
+    rng = np.random.default_rng(seed)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    return wl.CsrMatrix(len(lens), K, rowptr, rng.integers(0, K, rowptr[-1]).astype(np.int32),
+                        rng.uniform(-1, 1, rowptr[-1]).astype(np.float32), "rows", {})
+
+
+def graph(scale=19, degree=17):
+    return wl.rmat_csr(scale, degree, seed=3)
+
+
+def hub():
+    """One row over a thousand chunks between rows of all lengths; empty rows at both ends."""
+    rng = np.random.default_rng(1)
+    lens = np.concatenate([np.zeros(700, int), rng.integers(0, 40, 200_000), [900_000], np.zeros(70_000, int), rng.integers(0, 40, 200_000),
+                           np.zeros(1000, int)])
+    return rows_of(lens, 50_001, 2)
+
+
+def few_rows():
+    """Every row over hundreds of chunks, fewer rows than threads of a workgroup, the last one long."""
+    return rows_of(np.full(41, 220_000), 30_000, 3)
+
+
+def ends_in_a_quantum():
+    """Items a multiple of the quantum and of the chunks, so that the last chunk ends with the list."""
+    lens = np.full(1 << 18, 35)
+    lens[5], lens[6] = 35 + 3000, 35
+    lens[9:9 + 100] -= 30
+    return rows_of(lens, 1 << 18, 4)
+
+
+CASES = [("graph", graph, 41), ("hub", hub, 45), ("few rows", few_rows, 64), ("aligned", ends_in_a_quantum, 44), ("three column blocks", few_rows, 300),
+         ("pinned blocks", graph, 128), ("one line", lambda: graph(20, 17), 32)]
+
+
+def allocations(call):
+    import torch
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    call()
+    return torch.cuda.memory_stats()["allocation.all.allocated"] - before
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name, make, N", CASES, ids=[c[0] for c in CASES])
+def test_products_from_queues(name, make, N):
+    import torch
+    A = make()
+    D = dg.DeviceCsr(A)
+    X = wl.dense_matrix(A.K, N, "normal", seed=2)
+    Y0 = wl.dense_matrix(A.M, N, "uniform", seed=1)
+    ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    dX, Y = torch.from_numpy(X).cuda(), torch.full((A.M, N), float("nan"), device="cuda")
+    print(f"[case] queues {name} N={N}", flush=True)
+    assert allocations(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) == 1
+    ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+    assert ok, worst
+    Y = torch.from_numpy(Y0).cuda()
+    assert allocations(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) == 1
+    ok, worst = oracle.within_bound(Y.cpu().numpy(), -0.5 * ref + 1.5 * Y0, 0.5 * bnd + 1.5 * np.abs(Y0), 1e-5)
+    assert ok, worst
+
+
+@pytest.mark.gpu
+def test_queues_of_calls_on_several_streams_and_none_in_a_graph():
+    """Calls in flight together have queues of their own; a product that is recorded goes without."""
+    import torch
+    A = graph()
+    D = dg.DeviceCsr(A)
+    N = 41
+    X = torch.randn(A.K, N, device="cuda")
+    Y = torch.empty(A.M, N, device="cuda")
+    want = D.spmm(X, algo=dg.RS_SR)
+    scale = want.abs().max()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    torch.cuda.synchronize()
+    print("[case] queues on four streams", flush=True)
+    results = []
+    for _ in range(3):
+        for s in streams:
+            with torch.cuda.stream(s):
+                results.append(D.spmm(X))
+    results.append(D.spmm(X, Y=torch.empty_like(Y), stream=streams[1]))
+    torch.cuda.synchronize()
+    for r in results:
+        assert (r - want).abs().max() <= 1e-5 * scale
+    del results
+    side = streams[0]
+    graph_ = torch.cuda.CUDAGraph()
+    print("[case] queues while a graph is recorded", flush=True)
+    with torch.cuda.graph(graph_, stream=side):
+        assert allocations(lambda: D.spmm(X, Y=Y)) == 0
+    assert allocations(lambda: D.spmm(X, Y=Y)) == 1
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph_.replay()
+        torch.cuda.synchronize()
+        assert (Y - want).abs().max() <= 1e-5 * scale

@@ -1065,7 +1065,7 @@ struct HotColumns { const unsigned* table; int shift; };
 // power-law graph: 53 % of that one's are on 896 of its 32768 lines - every CU copies these lines when it starts, and a bitmap of
 // the lines with a running count per word says for a column whether it is among them and where.  One workgroup of eight
 // waves per CU, so that its LDS holds one table; the lanes that found their column there switch their gather off.
-// R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 70.7 / 87.9 / 104.4 us; 4 / 6 / 12 / 16 waves instead of
+// R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 68.7 / 87.1 / 102.2 us; 4 / 6 / 12 / 16 waves instead of
 // eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 7
 // million at 4 cycles each and CU: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
 // switched off, and by offset or by execution mask, makes no difference, nor would packing the others into fewer instructions.
@@ -1102,27 +1102,31 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     unsigned d0, d1;
     const bool any_items = plan.range(0, d0, d1);
-    // the hot runs, 16 bytes a load, and their bitmap: on their way while the chunk's bounds are searched
+    // The hot runs, 16 bytes a load, and their bitmap: the bitmap and the runs' numbers are on their way while the chunk's bounds are
+    // searched, the runs themselves behind the chunk's first entries (loads return in order: in front of the search they
+    // held up its rounds, first gathers 9.8 us after the start; R-MAT 2^20 x 16 / 2^19 x 16 at N = 1 70.1 / 39.0 -> 68.7 / 37.9 us).
     constexpr int kPieces = HOT ? (hot_floats(V) / 4 + kHotThreads - 1) / kHotThreads : 1;
     constexpr int kWordPieces = HOT ? (kHotWords + kHotThreads - 1) / kHotThreads : 1;
     float piece[kPieces][4];
     uint2 word[kWordPieces];
+    unsigned run[kPieces];
+    // piece i: 16 bytes of hot run (i / pieces of a run)
+    const auto run_of = [&](unsigned i) { return (i >> (hot.shift - 2)) / (unsigned)V; };
+    const unsigned pieces = HOT ? (unsigned)(hot_room(V, hot.shift) * V) << (hot.shift - 2) : 0u;
     if constexpr (HOT) {
-        const __amdgpu_buffer_rsrc_t rh = make_buffer(X, dense_bytes(K, V, V));
 #pragma unroll
         for (int k = 0; k < kWordPieces; ++k) {
             const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
             word[k] = reinterpret_cast<const uint2*>(hot.table)[i < (unsigned)kHotWords ? i : 0u];
         }
-        // piece i: 16 bytes of hot run (i / pieces of a run)
-        const auto run_of = [&](unsigned i) { return (i >> (hot.shift - 2)) / (unsigned)V; };
-        const unsigned pieces = (unsigned)(hot_room(V, hot.shift) * V) << (hot.shift - 2);
-        unsigned run[kPieces];
 #pragma unroll
         for (int k = 0; k < kPieces; ++k) {
             const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
             run[k] = hot.table[2 * kHotWords + run_of(i < pieces ? i : 0u)];
         }
+    }
+    const auto load_hot = [&] {
+        const __amdgpu_buffer_rsrc_t rh = make_buffer(X, dense_bytes(K, V, V));
 #pragma unroll
         for (int k = 0; k < kPieces; ++k) {
             const unsigned i = (unsigned)k * kHotThreads + threadIdx.x;
@@ -1130,12 +1134,9 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             const bool none = i >= pieces || run[k] == kNoRow;
             buffer_load_vec<4>(rh, none ? kOutOfRange : ((run[k] * (unsigned)V) << (hot.shift + 2)) + inside * 16u, piece[k]);
         }
-    }
-
-    // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
-    int is = 0, ie1 = 0;
-    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
-    if constexpr (HOT) {
+    };
+    // the only step that the workgroup's waves take together; every wave gets to one of its calls
+    const auto fill_hot = [&] {
 #pragma unroll
         for (int k = 0; k < kWordPieces; ++k) {
             const int i = k * kHotThreads + (int)threadIdx.x;
@@ -1146,10 +1147,15 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             const int i = k * kHotThreads + (int)threadIdx.x;
             if (i < hot_floats(V) / 4) store_vec<4>(s_hot + 4 * i, piece[k]);
         }
-        __syncthreads();                                     // the only step that the workgroup's waves take together
-    }
-    if (!any_items) return;
-    if (nnz == 0) {
+        __syncthreads();
+    };
+
+    // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
+    int is = 0, ie1 = 0;
+    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
+    if (!any_items || nnz == 0) {
+        if constexpr (HOT) { load_hot(); fill_hot(); }
+        if (!any_items) return;
         // nothing stored: every item is a row end; my rows are [d0, d1)
         for (unsigned r = d0 + lane; r < d1; r += kWave) {
             float* y = Y + (size_t)r * ldy + n0;
@@ -1164,7 +1170,10 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     unsigned js0 = d0 - (unsigned)is, je1 = d1 - (unsigned)ie1;
     if constexpr (SNAP) {
         snap_to_rows(rowptr, M, d0, d1, is, ie1, js0, je1);
-        if (is == ie1) return;
+        if (is == ie1) {
+            if constexpr (HOT) { load_hot(); fill_hot(); }
+            return;
+        }
     }
     unsigned js = js0;
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
@@ -1270,11 +1279,11 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     int c[E]; float a[E], x[E][V];                        // the block whose gathers are in flight
     int lc[E]; float la[E];                               // landing registers of the next block's entries
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
-    load_entries(0, lc, la);
+    load_entries(0, c, a);
     load_row_ends(is, is < ie1, w_end);
-#pragma unroll
-    for (int e = 0; e < E; ++e) { c[e] = lc[e]; a[e] = la[e]; }
+    if constexpr (HOT) load_hot();
     load_entries(1, lc, la);
+    if constexpr (HOT) fill_hot();
     gather(0, c, x);
 
     // state of the step in flight between its two halves

@@ -532,15 +532,16 @@ inline int hot_shift(int64_t K) {
     while (shift <= kHotShiftMax && (K - 1) >> shift >= 32ll * kHotWords) ++shift;
     return K >= 1 && shift <= kHotShiftMax ? shift : 0;
 }
+// Sampled where the column blocks of nb_sr_run_kernel want it, in the same launch: smaller matrices and shorter rows would gain 8 to 20 % of a
+// product and pay 20 us for it when they are taken over.
 // Reading hot runs from LDS pays from this many of their entries on, as copying them costs every CU 4 to 5 us, and where they
 // are this share of all.  R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (shares .58 .43 .33 .27) 95 / 103 / 113 / 114 -> 71 / 87 / 100 / 105 us,
-// 2^20 x 32 167 / 183 / 200 / 201 -> 117 / 148 / 172 / 179 us, 2^18 x 16 (.79 .63 .51 .42) 30 / 32.5 / 36 / 38.6 -> 24 / 28 / 31 / 32 us,
+// 2^20 x 32 167 / 183 / 200 / 201 -> 117 / 148 / 172 / 179 us, 2^18 x 32 (.78 .62 .49 .40) 43 / 46 / 50 / 51 -> 33 / 39 / 43.5 / 47 us,
 // 2^21 x 8 (.45 .31 .25 .19) 113 / 122 / 132 / 134 -> 89 / 109 / 120 / 132 us.  N = 1, uniform columns: 16.8 M entries over
 // 100 000 columns (.40) 99 -> 80 us, 262 144 (.20) 102 -> 95 us, 4.2 M over 262 144 (0.8 M of them) 28.7 -> 31.2 us.  Where the hottest
 // columns are so hot that the L1 holds them anyway the shares at N = 2 to 4 pay less: columns 2^20 u^4, N = 2 (.34) 115 -> 110 us,
 // N = 3 (.29) 140 -> 142 us, N = 4 (.26) 151 -> 155 us.
 constexpr double kHotEntriesMin = 1.5e6, kHotShareMin[kHotWidths] = {0.15, 0.3, 0.24, 0.24};
-constexpr long long kHotNnzMin = 3000000;
 inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
     return N >= 1 && N <= kHotWidths && s.hot_share[N - 1] >= kHotShareMin[N - 1] &&
            (double)s.features.nnz * s.hot_share[N - 1] >= kHotEntriesMin;
@@ -1387,7 +1388,7 @@ extern "C" int dgsp_internal_column_reuse(int64_t entries, const int32_t* colidx
 extern "C" int64_t dgsp_internal_hot_columns_bytes(const dgsp_internal_stats_t* stats) {
     if (!stats) return 0;
     const dgsp_features_t& f = stats->features;
-    return f.nnz >= kHotNnzMin && f.cv_row >= kColumnsCvMin && hot_shift(f.K) != 0 ? (int64_t)sizeof(int) * kHotTableInts * kHotWidths : 0;
+    return column_share_matters(f) && hot_shift(f.K) != 0 ? (int64_t)sizeof(int) * kHotTableInts * kHotWidths : 0;
 }
 
 extern "C" int dgsp_internal_wants_hot_columns(const dgsp_internal_stats_t* stats, int64_t N) {
@@ -1398,12 +1399,12 @@ extern "C" int dgsp_internal_measure_columns(dgsp_internal_stats_t* stats, const
     if (!stats) return DGSP_ERR_INVALID_ARG;
     stats->saved_share = 0.0;
     for (double& share : stats->hot_share) share = 0.0;
+    if (!column_share_matters(stats->features)) return DGSP_OK;
     if (dgsp_internal_hot_columns_bytes(stats) == 0) hot_columns = nullptr;
-    if (!column_share_matters(stats->features) && !hot_columns) return DGSP_OK;
     if (stats->features.nnz < kReuseEntriesMin || !colidx) return DGSP_ERR_INVALID_ARG;
     uint64_t counts[kReuseResultWords];
     if (const int rc = sample_columns(stats->features.K, stats->features.nnz, colidx, hot_columns, counts, (hipStream_t)stream)) return rc;
-    if (column_share_matters(stats->features)) stats->saved_share = dgsp_internal_saved_share(counts);
+    stats->saved_share = dgsp_internal_saved_share(counts);
     for (int v = 0; hot_columns && v < kHotWidths; ++v) stats->hot_share[v] = (double)counts[2 * kReuseLevels + v] / (double)kHotSample;
     return DGSP_OK;
 }

@@ -1280,9 +1280,14 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
     // enough blocks for the pieces; with the entry count unknown, for rows of 16 and no fewer than one per CU
     const long long pieces = entries >= 0 ? std::max<long long>((entries + kStatChunk - 1) / kStatChunk, (M + kStatChunk - 1) / kStatChunk)
                                           : std::max<long long>(M / 128, device_info().cus);
-    hipLaunchKernelGGL((csr_statistics_kernel<Word>), dim3(clamp_blocks(pieces, kStatBlocks)), dim3(kBlock), 0, st, (int)M,
+    // A small matrix: workgroups of their own for the rows, a row a thread, as long as every workgroup has a CU (20 001 rows of 10, whole
+    // call with one product 30.4 -> 29.3 us, 4096 rows of 8 24.3 -> 22.8 us; 60 000 rows of 8, 470 workgroups, 32.5 -> 33.0 us).
+    const long long entry_blocks = entries > 0 && K > 0 && colidx ? (entries + kStatChunk - 1) / kStatChunk : 0;
+    const long long row_blocks = entry_blocks > 0 ? (M + kBlock - 1) / kBlock : 0;
+    const bool apart = row_blocks > 0 && entry_blocks + row_blocks <= std::min(device_info().cus, kStatBlocks);
+    hipLaunchKernelGGL((csr_statistics_kernel<Word>), dim3(apart ? (unsigned)(entry_blocks + row_blocks) : clamp_blocks(pieces, kStatBlocks)), dim3(kBlock), 0, st, (int)M,
                        (long long)entries, reinterpret_cast<const Word*>(rowptr), K > 0 ? reinterpret_cast<const Word*>(colidx) : nullptr,
-                       rowptr32, colidx32, slot.scratch, slot.host, slot.ticket);
+                       rowptr32, colidx32, slot.scratch, slot.host, slot.ticket, apart ? (unsigned)row_blocks : 0u);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     unsigned long long h[kStatResultWords];
     if (const int rc = fetch_result(slot, h, kStatResultWords, st)) return rc;

@@ -2317,11 +2317,13 @@ __device__ __forceinline__ void stat_reduce(unsigned long long (&v)[kStatWords],
 
 // I: int or long long.  `entries`: length of colidx, -1: rowptr[M].  colidx32 is written for 64-bit indices.  `host`: result
 // in host memory, announced by `ticket` in its last word; nullptr: result in the scratch.
+// row_blocks: so many workgroups at the end of the grid take the rows and the others the entries (small matrices: two chains of
+// dependent loads side by side); 0: all take some of both.
 template <typename I>
 __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long entries, const I* __restrict__ rowptr,
                                                                 const I* __restrict__ colidx, int* __restrict__ rowptr32,
                                                                 int* __restrict__ colidx32, StatScratch* sc,
-                                                                unsigned long long* host, unsigned long long ticket) {
+                                                                unsigned long long* host, unsigned long long ticket, unsigned row_blocks) {
     constexpr bool kConvert = sizeof(I) == 8;
     __shared__ unsigned long long lds[kWavesPerBlock][kStatWords];
     __shared__ int s_last;
@@ -2332,11 +2334,25 @@ __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long
     const long long flat = colidx == nullptr ? 0 : kConvert ? entries : nnz;
     long long chunks = (flat + kStatChunk - 1) / kStatChunk;
     const long long by_rows = ((long long)M + kStatChunk - 1) / kStatChunk;
-    if (chunks < by_rows) chunks = by_rows;
-    const long long rows_per_chunk = ((long long)M + chunks - 1) / chunks;
+    if (chunks < by_rows && row_blocks == 0) chunks = by_rows;
+    long long rows_per_chunk = ((long long)M + chunks - 1) / (chunks > 0 ? chunks : 1);
+    const unsigned entry_blocks = gridDim.x - row_blocks;
+    const bool takes_rows = row_blocks == 0 || blockIdx.x >= entry_blocks, takes_entries = blockIdx.x < entry_blocks;
+    unsigned first = blockIdx.x, blocks = gridDim.x;
+    if (row_blocks != 0) {
+        if (takes_rows) {
+            first -= entry_blocks;
+            blocks = row_blocks;
+            rows_per_chunk = ((long long)M + row_blocks - 1) / row_blocks;
+            chunks = row_blocks;
+        } else {
+            blocks = entry_blocks;
+        }
+    }
 
     unsigned long long v[kStatWords] = {0, 0, ~0ull, 0, 0, 0, 0, 0};
-    for (long long c = blockIdx.x; c < chunks; c += gridDim.x) {
+    for (long long c = first; c < chunks; c += blocks) {
+        if (takes_entries) {
         // ---- entries: two per thread and step
         constexpr int S = kStatChunk / (2 * kBlock);
         I x[S], y[S], z[S];                                      // entries p, p + 1 and p + 2
@@ -2368,6 +2384,8 @@ __global__ __launch_bounds__(kBlock) void csr_statistics_kernel(int M, long long
             }
         }
         v[7] += down;
+        }
+        if (!takes_rows) continue;
         // ---- rows
         const long long r1 = (c + 1) * rows_per_chunk < M ? (c + 1) * rows_per_chunk : M;
         for (long long r = c * rows_per_chunk + t; r < r1; r += kBlock) {

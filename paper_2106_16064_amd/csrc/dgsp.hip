@@ -238,7 +238,8 @@ inline SrColumns sr_columns(long long N, int V, bool narrow) {
 // the L1 when rows of X are scattered (about 1 KB per wave: 4 / V loads), four when the matrix is
 // known to be banded (neighbouring rows then share their rows of X and mostly hit in cache).
 inline bool even_rows(const Problem& p) { return p.cv_row >= 0.0 && p.cv_row <= kEvenRowsCvMax; }
-inline bool banded(const Problem& p) { return p.col_span > 0.0 && p.col_span <= 0.05; }
+constexpr double kBandedSpan = 0.05;
+inline bool banded(const Problem& p) { return p.col_span > 0.0 && p.col_span <= kBandedSpan; }
 
 // The sequential kernels give a lane four dense columns whenever a row has four: the memory pipeline takes
 // dwordx2 / dwordx4 accesses at any dword address, so neither the alignment of X and Y nor their leading
@@ -262,12 +263,12 @@ inline double lines_per_row(long long cols, long long ldx) {
 // dearer the more of them the L2 (4 MB) misses.  Both costs are fitted, to 15 % or so, on random columns of X from 3 to
 // 40 MB, N = 1 to 128, 65 536 to 524 288 rows (`occ`: share of the wave slots in use, `part`: lines per wave / 64):
 //   a step in step      0.1 us + 0.4 us * (1 - occ) + part * (2.6 us * occ + 1.5 us * missed)
-//   a line out of step  6.5 ps + 12.5 ps * missed^2
-// Rows of 30, X of 3 / 5 / 7 / 10 / 16 MB, in step against out of step: 262 144 rows at N = 1 45 / 57 / 59 / 61 / 74 against
-// 44 / 54 / 68 / 89 / 110 us, 131 072 rows at N = 4 34 / 54 / 56 / 57 / 59 against 25 / 30 / 35 / 45 / 55 us; 131 072 rows of
-// 40 at N = 33 (17 MB) 86 against 142 us, Poisson rows of 12 there 56 against 49 us; 262 144 rows of 60 at N = 1 (5 MB)
-// 188 against 106 us.  On 3665 drawn matrices the choice loses 2.7 % to the better of the two (always out of step 3.5 %,
-// always in step 221 %); 9 % of them lose more than 10 %, mostly X of 6 to 12 MB.
+//   a line out of step  5.7 ps + 5 ps * missed + 6 ps * missed^2
+// 262 144 rows of 30, X of 2 / 4 / 8 / 16 MB at N = 4, in step against out of step: 45 / 49 / 59 / 75 against 40 / 47 / 78 /
+// 109 us; X of 0.25 / 1 / 4 MB at N = 1 37 / 44 / 49 against 34 / 39 / 46 us; 131 072 rows of 60 at N = 33 (17 MB) 108 against
+// 203 us, 262 144 Poisson rows of 12 there 103 against 92 us; 131 072 rows of 60 at N = 1 (1 MB) 105 against 38 us.  On 94
+// matrices of such rows (X of 0.25 to 268 MB, N = 1 to 64) the choice loses 0.6 % to the better of the two (always out of step
+// 10 %, always in step 24 %; the worst, Poisson rows of 12 with 8 MB of X, 16 %).
 constexpr double kWaveSlotsPerCu = 32.0;
 inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
     const double x_bytes = (double)p.K * p.N * 4.0;
@@ -284,7 +285,7 @@ inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
     // a wave's rows beyond four rounds of its LDS tile: too few of them walk at a time
     const double overflow = std::fmax(1.0, rows_per_wave * avg / (4.0 * kRsSrTile));
     const double in_us = step * longest * std::fmax(rounds, 1.0) * std::pow(overflow, 0.75);
-    const double out_us = (double)p.nnz * lines * cols.blocks * (6.5e-6 + 12.5e-6 * missed * missed);
+    const double out_us = (double)p.nnz * lines * cols.blocks * (5.7e-6 + (5.0e-6 + 6.0e-6 * missed) * missed);
     return 1.05 * in_us < out_us;
 }
 
@@ -315,6 +316,14 @@ inline int rs_sr_split_log2(const Problem& p, int logG) {
     return logH;
 }
 
+// Do waves that stage go before those that walk (rs_sr_kernel)?  Where the gathers go past the L1, yes; on a band the
+// neighbours' walks find their lines in the L1 while they are at it, and what there is to wait for are the streams.  Staging
+// level with the walk / first: 262 144 rows of 64 uniform columns at N = 1 / 2 / 4 85 / 91 / 103 against 76 / 79 / 93 us,
+// 50 001 Poisson rows of 40 over 8000 columns at N = 4 / 16 13.3 / 15.6 against 11.0 / 13.8 us; 27-point stencil on 81^3 at
+// N = 2 / 4 / 5 / 8 / 12 / 16 / 32 27.6 / 30.3 / 36.5 / 38.4 / 51.0 / 56.4 / 93.5 against 31.2 / 33.2 / 37.5 / 38.7 / 49.8 / 53.9 / 91.1 us.
+// Unknown columns are taken for a band.
+inline bool staging_first(const Problem& p, int logG) { return p.col_span > kBandedSpan || logG >= 2; }
+
 template <int V, bool XBUF, int DEPTH, bool RAGGED>
 int launch_rs_sr_v(const Problem& p, const SrColumns& cols, int logH) {
     const int logG = cols.logG;
@@ -324,13 +333,14 @@ int launch_rs_sr_v(const Problem& p, const SrColumns& cols, int logH) {
     const long long groups = ((long long)p.M + rows_per_wave - 1) / rows_per_wave;
     const long long cap = (long long)device_info().cus * kBlocksPerCu * 8;
     const dim3 grid(even_round_blocks(groups, cap), col_blocks);
+    const int first = staging_first(p, logG);
     if (p.scaled) {
         DGSP_LAUNCH((rs_sr_kernel<V, XBUF, DEPTH, true, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals,
-                    p.X, p.Y, logG, logH, cols.cols_per_block, Scaling{p.alpha, p.beta});
+                    p.X, p.Y, logG, logH, cols.cols_per_block, first, Scaling{p.alpha, p.beta});
         return DGSP_OK;
     }
     DGSP_LAUNCH((rs_sr_kernel<V, XBUF, DEPTH, false, RAGGED>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                p.Y, logG, logH, cols.cols_per_block);
+                p.Y, logG, logH, cols.cols_per_block, first);
     return DGSP_OK;
 }
 
@@ -367,7 +377,7 @@ inline SrShape rs_sr_shape(const Problem& p) {
 //   Rows more or less alike, up to four columns: equal runs of rows are equal shares of entries.  Against rs_pr: 4096 rows
 //   of 8 at N = 4 5.9 -> 3.9 us, 20 000 rows of 100 at N = 1 15.4 -> 10.3 us; against nb_pr: 27-point stencil on 128^3 at
 //   N = 1 / 4 122 / 137 -> 94 / 114 us, 776 379 rows of 22 over 27 098 columns at N = 1 79 -> 60 us, 187 500 Poisson rows of
-//   8 at N = 4 17.7 -> 12.9 us; 262 144 rows of 64 at N = 1 break even (85 us).
+//   8 at N = 4 17.7 -> 12.9 us; 262 144 rows of 64 at N = 1 85 -> 76 us.
 //   Small matrices with uneven rows: the balanced kernels' start (searches, row marks, perhaps two launches) is most of
 //   the call, and the longest row is `steps` rounds of loads for its lanes.  Lognormal rows of 8, row groups against the
 //   better of nb_sr and nb_pr: 8192 rows at N = 1 / 4 / 16 / 33 4.0 / 4.1 / 5.4 / 6.4 against 6.9 / 6.6 / 7.0 / 9.5 us,

@@ -171,7 +171,10 @@ __global__ __launch_bounds__(kBlock) void rs_pr_kernel(int M, long long K, int N
 // one after the other against H lanes with all of a round's loads at once: N = 1 154 -> 94 us (H = 4, 5.0 TB/s; through the
 // balanced parallel kernel 122 us), N = 4 188 -> 114 us, N = 8 198 -> 145 us.
 // Bound by: HBM streams on banded matrices; the lines gathered from X, out of
-// the L1's and L2's misses, elsewhere.
+// the L1's and L2's misses, elsewhere.  There waves that fetch bounds and entries
+// go before those that walk (`staging_first`, chosen by the host): they
+// are few issue slots away from gathers of their own, and what the CU has in
+// flight is what bounds the call: 262 144 rows of 64, N = 4, 103 -> 93 us.
 
 constexpr int kRsSrTile = 512;   // cached pairs per wave and round
 // DEPTH (template parameter of the sequential kernels) = dense-row loads a lane keeps in flight.
@@ -191,7 +194,8 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        int logG, int logH, int cols_per_block, Scaling sc = Scaling{1.0f, 0.0f}) {
+                                                        int logG, int logH, int cols_per_block, int staging_first,
+                                                        Scaling sc = Scaling{1.0f, 0.0f}) {
     constexpr int T = kRsSrTile;
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][T + T / 8];     // row of X (XBUF: its byte offset), value
     const int lane = lane_id();
@@ -220,6 +224,7 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
     const unsigned pitch = XBUF ? (unsigned)ldx * 4u : 1u;
 
     for (unsigned rg = gw; rg < ngroups; rg += nwaves) {
+        if (staging_first) __builtin_amdgcn_s_setprio(3);
         const long long row0 = (long long)rg * rows_per_wave;
         const long long row = row0 + g;
         const bool live = row < M;
@@ -239,6 +244,7 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
         }
 
         for (unsigned ws = ps; ws < pe; ws += (unsigned)T) {
+            if (staging_first) __builtin_amdgcn_s_setprio(3);
             wave_lds_sync();                    // last round's readers are done
             const unsigned long long bytes = (unsigned long long)(pe - ws) * 4ull;
             const __amdgpu_buffer_rsrc_t rc = make_buffer(colidx + ws, bytes);
@@ -276,6 +282,7 @@ __global__ __launch_bounds__(kBlock) void rs_sr_kernel(int M, long long K, int N
             }
             wave_lds_sync();
             const unsigned we = pe - ws > (unsigned)T ? ws + T : pe;
+            __builtin_amdgcn_s_setprio(0);
             const unsigned lo = (rs > ws ? rs : ws) - ws;
             const unsigned hi = (re < we ? re : we) - ws;         // may lie before lo: the row is not in this round
             if (col_ok) {

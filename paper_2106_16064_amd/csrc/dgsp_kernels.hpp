@@ -22,6 +22,17 @@
 
 namespace dgsp {
 
+// How the scheduler ranks the wave among those of its SIMD (the instruction takes a constant).  Left alone it issues for the
+// oldest one that can go on, so a young wave waits with its searches and its staging while the others gather: of the four
+// waves of a SIMD with equal shares the oldest ended at 13 us, the youngest at 18 of 24 (R-MAT 2^16 x 16 at N = 41), and the
+// memory idled at both ends.  A wave that has no gather in flight yet needs few issue slots to get there, so it goes first.
+__device__ __forceinline__ void set_wave_priority(unsigned level) {
+    if (level >= 3u) __builtin_amdgcn_s_setprio(3);
+    else if (level == 2u) __builtin_amdgcn_s_setprio(2);
+    else if (level == 1u) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
 // ===========================================================================
 // Row-split, parallel reduction  (CSR-Vector lineage; Section 1, Fig. 2(c,d))
 // ===========================================================================
@@ -1883,8 +1894,16 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // rows of 16 at N = 64 138 to 146 on the even XCDs, 156 to 166 on the odd ones).  So a wave starts on a part of its share and takes the
 // rest chunk by chunk from its XCD's queue, and some waves of an XCD that is done help the others (ChunkQueues).  A failed
 // take is an add to a word that all waves of the XCD add to, 13 ns a time, which is why most waves stop at their first.
+//
+// Wave priorities (set_wave_priority): searches, staging, row marks and the sums across runs at the highest, so that a wave gets
+// to its gathers; in the walk of a longer chunk the lower the further it has come, so that the waves of a SIMD end together.
+// Without / walk at the lowest throughout / by thirds: R-MAT 2^17 x 16 at N = 9 / 16 / 40 / 64 / 100 30.2 / 27.1 / 44.1 / 48.5 / 82.2,
+// 28.8 / 25.7 / 42.1 / 47.0 / 81.9, 27.9 / 25.2 / 40.2 / 48.0 / 80.9 us; 2^18 x 32 at N = 20 / 41 96 / 144, 95 / 143, 89.7 / 134.7 us.  Chunks of
+// kPacedFrom entries or fewer have nothing to make up (2^13 x 16 at N = 100 20.0, 20.1, 20.4 us); without statistics on a
+// 27-point stencil, 61^3 at N = 64, the walk's lines leave the L1 earlier (104.5, 105.6, 106.8 us).
 constexpr int kRunBlock = 512;       // entries per block
 constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
+constexpr unsigned kPacedFrom = 256;
 
 // the sum of the lanes' words under bitwise or, wave-uniform
 __device__ __forceinline__ unsigned wave_or(unsigned v) {
@@ -1918,6 +1937,7 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
     int* rows = s_rows[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
+    __builtin_amdgcn_s_setprio(3);
     int probe = 0;
     if constexpr (!QUEUED) probe = first_probe(rowptr, M, lane);
     const unsigned nnz = (unsigned)rowptr[M], items = nnz + (unsigned)M;
@@ -2071,6 +2091,7 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
 
     float carry[4] = {0.0f, 0.0f, 0.0f, 0.0f};          // sum of the row that is open at the block's start (every group: its columns)
     unsigned done = 0;                                  // entries before the block
+    const unsigned third = n_ent > kPacedFrom ? (n_ent + 2u) / 3u : 0u;
     do {
         const unsigned nE = n_ent - done < (unsigned)W ? n_ent - done : (unsigned)W;
         const unsigned to = done + nE;
@@ -2169,7 +2190,10 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
         // a run that starts inside a row: the first row end it meets is finished after the walk
         bool pend = p0 == 0u ? true : ((bits[(p0 - 1u) >> 5] >> ((p0 - 1u) & 31u)) & 1u) == 0u;
         bool closed = false;
+        unsigned pace = 4u;
         for (unsigned s0 = 0; s0 < U; s0 += B) {
+            const unsigned at = done + s0 * R, behind = at < third ? 2u : at < 2u * third ? 1u : 0u;
+            if (behind != pace) { pace = behind; set_wave_priority(pace); }
             const unsigned p = p0 + s0;
             float x[B][4], a[B];
 #pragma unroll
@@ -2209,6 +2233,7 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
                 }
             }
         }
+        __builtin_amdgcn_s_setprio(3);
         // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's
         //      carry in front; a run that met a row end starts a new segment
         float v[4];

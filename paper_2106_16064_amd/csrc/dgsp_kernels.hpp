@@ -730,6 +730,9 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     float* buf = s_buf[wib];
     const int n0 = blockIdx.y * V;
 
+    // Until its gathers are out a wave goes before those that reduce (set_wave_priority): 100 001 Zipf rows of 12 without
+    // statistics at N = 2 / 3 / 4 15.0 / 17.5 / 18.8 -> 14.7 / 17.0 / 18.4 us; at N = 1 300 001 lognormal rows of 30 59.3 -> 60.1 us.
+    if constexpr (V >= 2) __builtin_amdgcn_s_setprio(3);
     const int probe = first_probe(rowptr, M, lane);
     const ChunkPlan plan = plan_chunks(rowptr, M, 6);        // quanta of one wave's width
     const unsigned nnz = plan.nnz;
@@ -836,6 +839,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 
     // one tile: consumes (c, a, w_end), leaves the next tile's loads in flight in (c2, a2, w_end2)
     auto do_tile = [&](int (&c)[E], float (&a)[E], unsigned w_end, int (&c2)[E], float (&a2)[E], unsigned& w_end2) {
+        if constexpr (V >= 2) __builtin_amdgcn_s_setprio(3);
         const unsigned de = (d1 - ds > (unsigned)W) ? ds + W : d1;
 
         // ---- row ends of this tile -> LDS marks
@@ -889,6 +893,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
             load_entries(je, more, c2, a2);
         }
         store_pending();                                   // the previous tile's rows
+        if constexpr (V >= 2) __builtin_amdgcn_s_setprio(0);
 
         // ---- products change hands through LDS: entry 64e+l -> lane (64e+l)/E
 #pragma unroll
@@ -1508,7 +1513,13 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     const unsigned nblocks = (je1 - js0 + (unsigned)W - 1) / (unsigned)W;
     const unsigned nb = nblocks ? nblocks : 1u;            // a chunk without entries still has its row ends to finish
+    // Waves that lag behind go first, by quarters of the chunk, so that those of a SIMD end together: R-MAT 2^20 x 16 at
+    // N = 2 / 4 86.7 / 102.4 -> 85.1 / 101.1 us, 300 001 lognormal rows of 30 at N = 1 56.0 -> 54.8 us.  In chunks of a few
+    // blocks there is nothing to make up (R-MAT 2^18 x 16 at N = 2, four blocks, 32.4 -> 32.9 us).
+    unsigned pace = 4u;
     for (unsigned k = 0; k < nb; ++k) {
+        const unsigned behind = nb < 8u ? 0u : 3u - 4u * k / nb;
+        if (behind != pace) { pace = behind; set_wave_priority(pace); }
         blk_start = js0 + k * (unsigned)W;                 // == js: the previous block was consumed to its end
         blk_end = (je1 - blk_start > (unsigned)W) ? blk_start + (unsigned)W : je1;
         // ---- products of block k change hands through LDS: entry 64e+l of the block -> lane (64e+l)/E

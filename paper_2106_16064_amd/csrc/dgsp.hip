@@ -432,13 +432,13 @@ int launch_rs_sr(const Problem& p) {
 // ---------------------------------------------------------------- balanced launches
 // Zeroes (scaled form: multiplies by beta) the rows split by the `parts` chunks the main kernel derives
 // (quanta of 2^quantum_log2 items), cut into tiles of 2^tile_log2 items (tile_log2 < 0: not cut further).
-int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{}) {
+int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{}, int empty_rows = 0) {
     const dim3 grid((unsigned)(((long long)p.M + kBlock - 1) / kBlock));
     const float beta = p.scaled ? p.beta : 0.0f;
     if (queues.starts)
-        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues);
+        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues, empty_rows);
     else
-        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues);
+        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues, empty_rows);
     return DGSP_OK;
 }
 
@@ -723,7 +723,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, 6, -1, queues)) return rc;
+        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, 6, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         const auto launch = [&](auto scaled, auto queued) -> int {

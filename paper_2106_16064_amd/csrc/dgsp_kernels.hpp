@@ -469,10 +469,15 @@ struct ChunkQueues {
 // from the chunk's start when tile_log2 >= 0.
 // One thread per row for the test (split rows are few: at most two per piece).
 // QUEUES: the chunks' first rows and the counters are written as well.
+// `empty_rows`: rows without entries are treated alike and the main launch leaves them alone (nb_sr_run_kernel, scaled form).  Half of
+// a power-law graph's rows are such; a wave at the sparse end has hundreds, and their old values were four or more trips to memory
+// per 64 of them, one after the other.  R-MAT 2^17 x 16 at N = 8 / 16 / 40 / 100 29.5 / 41.6 / 74.2 / 153.4 -> 28.0 / 36.9 / 62.0 / 114.5 us,
+// 2^20 x 12 at N = 20 305 -> 263 us.  Plain products write zeros without waiting and keep them where they are (by this launch
+// 2^17 x 16 at N = 16 / 40 23.2 / 40.3 -> 23.9 / 43.1 us).
 template <bool QUEUES>
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
-                                                             int tile_log2, float beta, ChunkQueues queues) {
+                                                             int tile_log2, float beta, ChunkQueues queues, int empty_rows) {
     const long long row = (long long)blockIdx.x * kBlock + threadIdx.x;
     const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the row's bounds
     bool split = false;
@@ -484,13 +489,14 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
         // An empty row is a single item.  Every chunk and tile starts at a multiple of the quantum, so a row
         // whose items lie inside one quantum cannot be split: most rows stop here, before the divisions.
         // Nor does a chunk start in a row that has no multiple of the quantum among its items.
+        split = empty_rows != 0 && first == last;
         const bool across = first != last && (first >> quantum_log2) != (last >> quantum_log2);
         const bool starting = QUEUES && ((before >> quantum_log2) != (last >> quantum_log2) || row == M - 1);
         if (across || starting) {
             const EvenSplit es(items, parts, quantum_log2);
             const unsigned c1 = es.chunk_of(first), c2 = es.chunk_of(last);
-            split = across && c1 != c2;
-            if constexpr (QUEUES) split = split && queues.piece_of(c1) != queues.piece_of(c2);
+            if (across) split = c1 != c2;
+            if constexpr (QUEUES) split = split && (!across || queues.piece_of(c1) != queues.piece_of(c2));
             if (across && !split && tile_log2 >= 0) {
                 const unsigned start = es.start(c1);
                 split = (first - start) >> tile_log2 != (last - start) >> tile_log2;
@@ -521,16 +527,18 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
         if (row == M - 1)
             for (unsigned c = c_to; c <= parts; ++c) queues.starts[c] = M;
     }
-    if (N <= 8) {                                      // narrow rows: the thread clears its own
+    if (N <= 8 && !empty_rows) {                       // few and narrow: the thread clears its own
         if (split) {
             float* y = Y + (size_t)row * ldy;
             for (int n = 0; n < N; ++n) y[n] = beta != 0.0f ? beta * y[n] : 0.0f;
         }
         return;
     }
-    // The workgroup treats its split rows together: they are listed, a wave takes every fourth, eight at a time with a lane
-    // per column, so that the loads of the scaled form are in flight together.  (The long rows of a graph are neighbours and
-    // all split: one row after the other in one wave took R-MAT 2^18 x 13 at N = 58 100 of 206 us.)
+    // The workgroup treats its rows together: they are listed, 2^log_lanes lanes take one, eight of a lane's in flight at a time, so
+    // that the loads of the scaled form overlap.  (The long rows of a graph are neighbours and all split: one row after the
+    // other in one wave took R-MAT 2^18 x 13 at N = 58 100 of 206 us; with a wave to a row of 8 / 12 columns 2^18 x 6 / 2^17 x 16 in the
+    // scaled form took 33 / 45 instead of 28 / 38 us, with one to a row of 12 / 20 columns plain products on 2^17 x 16 28.3 / 31.6 instead of
+    // 26.5 / 30.6 us.)
     __shared__ int s_rows[kBlock];
     __shared__ int s_count[kWavesPerBlock];
     const int lane = lane_id(), wib = wave_in_block();
@@ -543,17 +551,19 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     if (split) s_rows[before + (int)__popcll(mine & ((1ull << lane) - 1ull))] = (int)row;
     __syncthreads();
     constexpr int U = 8;
-    for (int r = wib; r < count; r += kWavesPerBlock * U) {                  // wave-uniform
-        for (int n = lane; n < N; n += kWave) {
+    const int log_lanes = N > kWave / 2 ? 6 : 32 - __builtin_clz((unsigned)N - 1u | 1u);
+    const int lanes = 1 << log_lanes, step = kBlock >> log_lanes;                    // rows that the workgroup takes at once
+    for (int r = (int)threadIdx.x >> log_lanes; r < count; r += step * U) {
+        for (int n = lane & (lanes - 1); n < N; n += lanes) {
             float v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int at = r + u * kWavesPerBlock;
+                const int at = r + u * step;
                 v[u] = (beta != 0.0f && at < count) ? Y[(size_t)s_rows[at] * ldy + n] : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int at = r + u * kWavesPerBlock;
+                const int at = r + u * step;
                 if (at < count) Y[(size_t)s_rows[at] * ldy + n] = beta != 0.0f ? beta * v[u] : 0.0f;
             }
         }
@@ -2133,7 +2143,7 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
                 rows[listed + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m_has >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m_has, 0u))] = is + lane;
             }
             listed += (int)__popcll(m_has);
-            if (m_zero != 0ull) {
+            if (m_zero != 0ull && (!AXPBY || snap)) {              // scaled form: the prepare launch's, if there is one
                 const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };      // R rows per round
                 if constexpr (AXPBY) {
                     constexpr int F = G < 4 ? G : 4;        // rounds whose old values are in flight together

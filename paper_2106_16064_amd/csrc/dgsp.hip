@@ -271,7 +271,10 @@ inline double lines_per_row(long long cols, long long ldx) {
 // 10 %, always in step 24 %; the worst, Poisson rows of 12 with 8 MB of X, 16 %).
 constexpr double kWaveSlotsPerCu = 32.0;
 inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
-    const double x_bytes = (double)p.K * p.N * 4.0;
+    const double lines = lines_per_row(cols.cols_per_block, p.ldx);
+    // columns of a wider matrix come with the lines around them (64 378 rows of 15, 18 of 33 columns, N * K of 4.6 MB, lines of
+    // 8.5 MB: in step 13.9, out of step 18.0 us)
+    const double x_bytes = (double)p.K * std::fmin(p.ldx * 4.0, lines * cols.blocks * 128.0);
     const double missed = x_bytes > (double)kL2BytesPerXcd ? 1.0 - (double)kL2BytesPerXcd / x_bytes : 0.0;
     if (banded(p) || p.nnz == 0) return false;
     if (p.nnz < 0) return missed > 0.0;                        // entry count unknown: rows taken to be long and alike
@@ -280,7 +283,7 @@ inline bool rows_in_step(const Problem& p, const SrColumns& cols) {
     const double rows_per_wave = (double)(kWave >> cols.logG);
     const double rounds = (double)p.M / rows_per_wave * cols.blocks / (device_info().cus * kWaveSlotsPerCu);
     const double occ = std::fmin(rounds, 1.0);
-    const double lines = lines_per_row(cols.cols_per_block, p.ldx), part = rows_per_wave * lines / 64.0;
+    const double part = rows_per_wave * lines / 64.0;
     const double step = 0.1 + 0.4 * (1.0 - occ) + part * (2.6 * occ + 1.5 * missed);
     // a wave's rows beyond four rounds of its LDS tile: too few of them walk at a time
     const double overflow = std::fmax(1.0, rows_per_wave * avg / (4.0 * kRsSrTile));

@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     constexpr int U = 8;
     const int log_lanes = N > kWave / 2 ? 6 : 32 - __builtin_clz((unsigned)N - 1u | 1u);
     const int lanes = 1 << log_lanes, step = kBlock >> log_lanes;                    // rows that the workgroup takes at once
-    for (int r = (int)threadIdx.x >> log_lanes; r < count; r += step * U) {
+    for (int r = log_lanes == 6 ? wib : (int)threadIdx.x >> log_lanes; r < count; r += step * U) {       // a wave's row is known to be one
         for (int n = lane & (lanes - 1); n < N; n += lanes) {
             float v[U];
 #pragma unroll

@@ -447,24 +447,28 @@ int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int 
 
 // How `waves` waves on each XCD share out the items (`lists` times: column blocks that are a grid dimension) with the help of
 // memory of the caller's; nothing if it has none to give.  The prepare launch's first rows clear the counters, so there have to be
-// as many.  Three tenths of a wave's share (`share` items) are its first piece, the rest goes by chunks of a quarter of a share, 512 to
-// 1024 items: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares 1024 us), at
-// N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).
+// as many.  Three tenths of a wave's share (`share` items) are its first piece, the rest goes by chunks of 512 items, 1024 from
+// shares of 4096 on: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares 1024 us), at
+// N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).  Powers of two, so that the
+// prepare launch knows rows within a chunk by a shift: 2^19 x 16 at N = 100, scaled, 475.5 -> 473 us, 2^20 x 16 at N = 32 228.7 -> 228.0 us.
 constexpr double kFirstPiece = 0.3;
 constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
 ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
     ChunkQueues q{};
     const long long items = p.nnz + (long long)p.M;
-    const long long size = std::min<long long>(std::max<long long>(share / 4, 512), 1024), chunks = (items + size - 1) / size;
+    const unsigned size_log2 = share >= 4096 ? 10 : 9;
+    const long long chunks = (items + (1ll << size_log2) - 1) >> size_log2;
     const unsigned run = (unsigned)((double)(chunks / parts) * kFirstPiece / waves);
     const size_t counters = (size_t)kXcd * lists;
-    if (run == 0 || !p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0 || (size_t)p.M < counters) return q;
+    if (run == 0 || !p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0 || (size_t)p.M < counters ||
+        (chunks << size_log2) > 0xffffffffll) return q;
     const size_t head = counters * kQueuePitch * sizeof(unsigned);
     char* mem = static_cast<char*>(p.more->workspace(p.more->context, head + (size_t)(chunks + 1) * sizeof(int)));
     if (!mem) return q;
     q.taken = reinterpret_cast<unsigned*>(mem);
     q.starts = reinterpret_cast<int*>(mem + head);
     q.chunks = (unsigned)chunks;
+    q.size_log2 = size_log2;
     q.counters = (unsigned)counters;
     q.parts = parts; q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
     return q;
@@ -726,7 +730,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, 6, -1, queues, p.scaled)) return rc;
+        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         const auto launch = [&](auto scaled, auto queued) -> int {

@@ -442,7 +442,7 @@ struct EvenSplit {
     }
 };
 
-// How a call with a workspace shares out the items (nb_sr_run_kernel).  The even split into `chunks` chunks is dealt to
+// How a call with a workspace shares out the items (nb_sr_run_kernel).  `chunks` chunks of 2^size_log2 items are dealt to
 // `parts` parts, one per XCD that works on a list.  The first chunks of a part are its waves' shares, `run` consecutive ones a
 // wave, a single piece; the others are taken one by one by whoever is done, first from the wave's own part.  In the
 // workspace: `taken`, a counter for each XCD's queue, kQueuePitch words apart, and `starts`, for each chunk and for the end of the
@@ -450,7 +450,7 @@ struct EvenSplit {
 constexpr unsigned kQueuePitch = 32;
 struct ChunkQueues {
     unsigned* taken; int* starts;
-    unsigned chunks, counters, parts, waves, run, helpers;
+    unsigned chunks, size_log2, counters, parts, waves, run, helpers;
     __device__ __forceinline__ unsigned part_from(unsigned part) const { return (unsigned)((unsigned long long)chunks * part / parts); }
     __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
     // a number for the piece that chunk c belongs to, different for different pieces
@@ -1978,7 +1978,7 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
         wg = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
     }
-    const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, 6);
+    const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, QUEUED ? queues.size_log2 : 6u);
     // queue q: what the waves of XCD q leave of its part of the chunks
     const auto part_of = [&](unsigned q) { return pinned_blocks ? q / pinned_blocks : q; };
     const auto queue_size = [&](unsigned q) { return queues.part_from(part_of(q) + 1u) - queues.queue_from(part_of(q)); };

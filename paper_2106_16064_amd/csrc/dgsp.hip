@@ -470,7 +470,7 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
     q.chunks = (unsigned)chunks;
     q.size_log2 = size_log2;
     q.counters = (unsigned)counters;
-    q.parts = parts; q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
+    q.parts_log2 = (unsigned)__builtin_ctz(parts); q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
     return q;
 }
 

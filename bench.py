@@ -53,12 +53,12 @@ RESULTS_DIR = "gpurun_out"     # per-cell records of the suites
 _TRAFFIC_SOURCE = "profiles/selected_kernels_time_traffic_occupancy.md (rocprofv3 FETCH_SIZE + WRITE_SIZE per launch, scaled by the copy kernel)"
 MEASURED_TRAFFIC = {
     # "kernel/workload/N": (bytes fetched + bytes written per launch of the main kernel, source)
-    "nb_pr/rmat_spmv/N1": (169.3e6 + 5.1e6, _TRAFFIC_SOURCE),
+    "nb_pr/rmat_spmv/N1": (169.4e6 + 5.1e6, _TRAFFIC_SOURCE),
     "nb_sr/rmat_gnn/N128": (4815.6e6 + 550.1e6, _TRAFFIC_SOURCE),
     "nb_sr/rmat_gnn/N32": (1121.4e6 + 137.5e6, _TRAFFIC_SOURCE),
     "rs_sr/stencil/N1": (497.1e6 + 8.4e6, _TRAFFIC_SOURCE),
     "rs_sr/stencil/N8": (621.1e6 + 67.1e6, _TRAFFIC_SOURCE),
-    "rs_sr/uniform64/N4": (268.1e6 + 4.2e6, _TRAFFIC_SOURCE),
+    "rs_sr/uniform64/N4": (257.4e6 + 4.2e6, _TRAFFIC_SOURCE),
 }
 
 

@@ -27,6 +27,7 @@
 #include <string>
 
 #include "dgsp_internal.h"
+#include "workspace.hpp"
 
 namespace {
 
@@ -97,32 +98,20 @@ bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == 
 
 bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
 
-// Device memory for one product, of the stream that it runs on: given back when the call returns, it is handed out again to work
-// that comes later on that stream only.  None while the stream records a graph, whose replays the allocator may not know of.
-class Workspace {
-public:
-    explicit Workspace(void* stream) : stream_(static_cast<hipStream_t>(stream)) {}
-    Workspace(const Workspace&) = delete;
-    Workspace& operator=(const Workspace&) = delete;
-    ~Workspace() {
-        if (memory_) c10::hip::HIPCachingAllocator::raw_delete(memory_);
-    }
-    static void* get(void* context, size_t bytes) {
-        auto* self = static_cast<Workspace*>(context);
+// what Workspace asks
+struct GpuRuntime {
+    using Stream = hipStream_t;
+    static bool capture_status(Stream stream, bool& recording) {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        if (self->memory_ || hipStreamIsCapturing(self->stream_, &status) != hipSuccess || status != hipStreamCaptureStatusNone) return nullptr;
-        try {
-            self->memory_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, self->stream_);
-        } catch (...) {                            // out of memory: the product does without
-            self->memory_ = nullptr;
-        }
-        return self->memory_;
+        const bool known = hipStreamIsCapturing(stream, &status) == hipSuccess;
+        recording = status != hipStreamCaptureStatusNone;
+        return known;
     }
-
-private:
-    hipStream_t stream_;
-    void* memory_ = nullptr;
+    static void* allocate(size_t bytes, Stream stream) { return c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream); }
+    static void release(void* memory) { c10::hip::HIPCachingAllocator::raw_delete(memory); }
+    static void forget_error() { (void)hipGetLastError(); }
 };
+using Workspace = dgsp::Workspace<GpuRuntime>;
 
 // The statistics of a ctypes `Features` structure, or of the `MatrixFeatures` that a DeviceCsr holds (None: there are none).
 class FeaturesArg {
@@ -236,7 +225,7 @@ int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Ten
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(stream);
+    Workspace workspace(static_cast<hipStream_t>(stream));
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), &hints, rp, ci, av, x, y, &algo, stream);
     return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), &hints, stream);
@@ -479,7 +468,7 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(stream);
+    Workspace workspace(static_cast<hipStream_t>(stream));
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     check_status(unlocked([&] {
         return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), &hints, stream);
@@ -552,7 +541,7 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(stream);
+    Workspace workspace(static_cast<hipStream_t>(stream));
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     const int rc = unlocked([&] {
         return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), &hints, stream);

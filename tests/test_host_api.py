@@ -257,6 +257,15 @@ def test_pool_of_statistics_scratch(check, tmp_path):
     assert subprocess.run([str(exe), check], timeout=60).returncode == 0
 
 
+@pytest.mark.parametrize("check", ["one_block_a_call", "leaves_no_error"])
+def test_memory_of_one_product(check, tmp_path):
+    """The workspace that the Python binding offers a product, on a pretended runtime."""
+    import subprocess
+    exe = tmp_path / "workspace_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(exe), os.path.join(ROOT, "tests", "workspace_check.cpp")], check=True)
+    assert subprocess.run([str(exe), check], timeout=60).returncode == 0
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess, sys, os
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))

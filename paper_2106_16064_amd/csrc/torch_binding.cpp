@@ -107,6 +107,13 @@ struct GpuRuntime {
         recording = status != hipStreamCaptureStatusNone;
         return known;
     }
+    static bool device(int& d) { return hipGetDevice(&d) == hipSuccess; }
+    static bool device_of(Stream stream, int& d) {
+        hipDevice_t on = -1;
+        const bool known = hipStreamGetDevice(stream, &on) == hipSuccess;
+        d = on;
+        return known;
+    }
     static void* allocate(size_t bytes, Stream stream) { return c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream); }
     static void release(void* memory) { c10::hip::HIPCachingAllocator::raw_delete(memory); }
     static void forget_error() { (void)hipGetLastError(); }
@@ -225,7 +232,7 @@ int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Ten
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(static_cast<hipStream_t>(stream));
+    Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), &hints, rp, ci, av, x, y, &algo, stream);
     return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), &hints, stream);
@@ -468,7 +475,7 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(static_cast<hipStream_t>(stream));
+    Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     check_status(unlocked([&] {
         return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), &hints, stream);
@@ -541,7 +548,7 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
-    Workspace workspace(static_cast<hipStream_t>(stream));
+    Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
     const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
     const int rc = unlocked([&] {
         return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), &hints, stream);

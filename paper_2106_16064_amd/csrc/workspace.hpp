@@ -6,15 +6,17 @@
 namespace dgsp {
 
 // Memory of the stream that the product runs on: given back when the call returns, it is handed out again to work that comes
-// later on that stream only.  None while the stream records a graph, whose replays the allocator may not know of.
+// later on that stream only.  None while the stream records a graph, whose replays the allocator may not know of, and none
+// unless the stream and the operands are on the current GPU: what the allocator hands out is memory of that one.
 //
-// `Runtime` asks the GPU runtime and the allocator: bool capture_status(Stream, bool& recording), false on an error that it leaves
-// as the runtime's last one; void* allocate(size_t, Stream), which may throw; void release(void*); void forget_error().
+// `Runtime` asks the GPU runtime and the allocator: bool capture_status(Stream, bool& recording), bool device(int&) (the current
+// one) and bool device_of(Stream, int&), false on an error that they leave as the runtime's last one; void* allocate(size_t,
+// Stream), memory of the current GPU, which may throw; void release(void*); void forget_error().
 template <typename Runtime>
 class Workspace {
 public:
     using Stream = typename Runtime::Stream;
-    explicit Workspace(Stream stream) : stream_(stream) {}
+    Workspace(Stream stream, int device) : stream_(stream), device_(device) {}
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;
     ~Workspace() {
@@ -35,11 +37,14 @@ public:
 private:
     bool usable() const {
         bool recording = false;
-        if (Runtime::capture_status(stream_, recording)) return !recording;
+        int current = -1, on = -1;
+        if (Runtime::capture_status(stream_, recording) && Runtime::device(current) && Runtime::device_of(stream_, on))
+            return !recording && current == on && current == device_;
         Runtime::forget_error();                   // the product's launches ask for the last error
         return false;
     }
     Stream stream_;
+    int device_;                                   // of the operands
     void* memory_ = nullptr;
 };
 

@@ -257,7 +257,7 @@ def test_pool_of_statistics_scratch(check, tmp_path):
     assert subprocess.run([str(exe), check], timeout=60).returncode == 0
 
 
-@pytest.mark.parametrize("check", ["one_block_a_call", "leaves_no_error"])
+@pytest.mark.parametrize("check", ["one_block_a_call", "leaves_no_error", "only_on_the_products_gpu"])
 def test_memory_of_one_product(check, tmp_path):
     """The workspace that the Python binding offers a product, on a pretended runtime."""
     import subprocess

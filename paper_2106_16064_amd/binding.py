@@ -47,10 +47,11 @@ class Features(ctypes.Structure):
 
 
 class MatrixFeatures(Features):
-    """The statistics that a ``DeviceCsr`` holds: ``Features``, what column blocks half as wide would save and the shares
-    of the entries whose column is in one of the hottest runs of columns, for products with one to four columns
-    (``dgsp_internal_stats_t``; 0: nothing, or not measured), and a table of these runs in GPU memory.  The latter are not part of the C-ABI: they are measured of large matrices with
-    very uneven rows when the ``DeviceCsr`` is made, and the products of this module hand them to the library."""
+    """The statistics that a ``DeviceCsr`` holds: ``Features``, what column blocks half as wide would save, for products with
+    one to four columns the share of the entries that reading the hottest runs of X from LDS saves the caches
+    (``dgsp_internal_stats_t``; 0: nothing, or not measured), and a table of these runs in GPU memory.  All but ``Features`` is
+    not part of the C-ABI: it is measured of large matrices with very uneven rows when the ``DeviceCsr`` is made, and the
+    products of this module hand it to the library."""
     _fields_ = [("saved_share", ctypes.c_double), ("hot_share", ctypes.c_double * 4)]
     hot_columns = None      # int32 tensor on the matrix's GPU
 

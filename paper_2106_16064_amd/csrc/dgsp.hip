@@ -551,14 +551,18 @@ inline int hot_shift(int64_t K) {
 }
 // Sampled where the column blocks of nb_sr_run_kernel want it, in the same launch: smaller matrices and shorter rows would gain 8 to 20 % of a
 // product and pay 20 us for it when they are taken over.
-// Reading hot runs from LDS pays from this many of their entries on, as copying them costs every CU 4 to 5 us, and where they
-// are this share of all.  R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (shares .58 .43 .33 .27) 95 / 103 / 113 / 114 -> 71 / 87 / 100 / 105 us,
-// 2^20 x 32 167 / 183 / 200 / 201 -> 117 / 148 / 172 / 179 us, 2^18 x 32 (.78 .62 .49 .40) 43 / 46 / 50 / 51 -> 33 / 39 / 43.5 / 47 us,
-// 2^21 x 8 (.45 .31 .25 .19) 113 / 122 / 132 / 134 -> 89 / 109 / 120 / 132 us.  N = 1, uniform columns: 16.8 M entries over
-// 100 000 columns (.40) 99 -> 80 us, 262 144 (.20) 102 -> 95 us, 4.2 M over 262 144 (0.8 M of them) 28.7 -> 31.2 us.  Where the hottest
-// columns are so hot that the L1 holds them anyway the shares at N = 2 to 4 pay less: columns 2^20 u^4, N = 2 (.34) 115 -> 110 us,
-// N = 3 (.29) 140 -> 142 us, N = 4 (.26) 151 -> 155 us.
-constexpr double kHotEntriesMin = 1.5e6, kHotShareMin[kHotWidths] = {0.15, 0.3, 0.24, 0.24};
+// Reading hot runs from LDS pays where it saves the caches this many entries, as copying the runs costs every CU 4 to 5 us, and
+// this share of them (hot_columns()): the others bound the product, all the more the more of them miss the L2.  66 matrices with 4
+// to 32 million entries, share, general way -> hot runs:
+//   R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (.31 .25 .19 .16) 90 / 100 / 109 / 111 -> 68 / 83 / 97 / 101 us, 2^20 x 32 (.31 .25 .19 .16) 168 / 181 /
+//   194 / 196 -> 114 / 145 / 169 / 175 us, 2^18 x 32 (.40 .35 .28 .22) 40 / 43 / 46 / 48 -> 31 / 35 / 41 / 44 us, 2^21 x 8 (.27 .19 .16 .11) 108 / 119 /
+//   127 / 136 -> 85 / 106 / 116 / 135 us;
+//   N = 1, uniform columns: 16.8 M entries over 100 000 / 262 144 / 500 000 (.28 .11 .06) 94 / 97 / 98 -> 76 / 90 / 95 us, 4.7 M over
+//   180 000 / 262 144 / 350 000 (.15 .10 .08; 0.73 / 0.49 / 0.37 M of them) 34.5 / 34.6 / 35.4 -> 32.9 / 34.1 / 35.4 us;
+//   the lines, columns K u^p: N = 2 2^20 u^4 (.13) 123 -> 116 us, 1.5 M u^4 (.12) 100 -> 102 us, 3 M u^6 (.11) 141 -> 143 us; N = 3 2^19 u^3
+//   (.11) 131 -> 120 us, 2^20 u^4 (.10) 148 -> 149 us, 2^21 u^6 (.10) 150 -> 153 us; N = 4 2^18 u^4 (.12) 112 -> 99 us, 2^20 u^8 (.09) 115 ->
+//   113 us, 2^20 u^4 (.08) 159 -> 161 us.  Columns as hot as 2^20 u^8 would gain below the lines of N = 2 and 3, too (.12 101 -> 87, .10 111 -> 105 us).
+constexpr double kHotEntriesMin = 0.45e6, kHotShareMin[kHotWidths] = {0.05, 0.12, 0.107, 0.1};
 inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
     return N >= 1 && N <= kHotWidths && s.hot_share[N - 1] >= kHotShareMin[N - 1] &&
            (double)s.features.nnz * s.hot_share[N - 1] >= kHotEntriesMin;

@@ -9,8 +9,8 @@ extern "C" {
 #endif
 
 /* What the binding keeps of a matrix: the public statistics, what column blocks half as wide would save
- * (dgsp_internal_saved_share; 0: not measured) and the shares of the entries whose column is in a hot run of products with one to
- * four columns (0: not measured). */
+ * (dgsp_internal_saved_share; 0: not measured) and, for products with one to four columns, the share of the entries that reading
+ * the hot runs of X from LDS saves the caches (0: nothing, or not measured). */
 typedef struct {
     dgsp_features_t features;
     double saved_share, hot_share[4];

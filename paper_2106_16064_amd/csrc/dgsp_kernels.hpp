@@ -1092,6 +1092,8 @@ constexpr int kHotTableInts = 3 * kHotWords;
 // what the products, marks and bitmap of eight waves leave of 160 KB
 constexpr int hot_floats(int v) { return v == 1 ? 31 * 1024 : v == 2 ? 28 * 1024 : v == 3 ? 24 * 1024 : 20 * 1024; }
 __host__ __device__ constexpr int hot_room(int v, int shift) { return hot_floats(v) / (v << shift); }
+// runs that the L1 (32 KB, half of it left by everything else that passes through) holds without a table
+__host__ __device__ constexpr int hot_cached(int v, int shift) { return (128 << 5) / (v << shift); }
 struct HotColumns { const unsigned* table; int shift; };
 
 // SERIAL_SCAN (a comparison kernel for Section 2.1.1, not used by the library's own choices): the lanes' open-row
@@ -2544,21 +2546,29 @@ __device__ __forceinline__ unsigned reuse_prefix(unsigned v, unsigned* waves, un
 
 // The hot runs (HotColumns): 32768 entries, 512 pieces of 64 evenly spread, are counted by run of 2^shift columns, at most 32768
 // runs, and the `room` fullest taken.  Thread t owns runs 32 t ... 32 t + 31, a word of the bitmap.  `bins`: 32768 words.
-// Returns how many of the sampled entries are in hot runs.
+// Returns how many entries the table saves the caches, per kHotSample: those in hot runs, without those in the fullest `cached`
+// ones, which an L1 holds anyway.  A run is among the fullest of a sample partly because the sample met it often, so the entries that
+// made the choice overstate its share (uniform columns, 262 144 of them at N = 1: 23 % of the sample, 12 % of the matrix).  Every
+// entry is therefore asked whether its run would have been taken by the others alone (12 % there; of 66 matrices the worst is 1.7 % of
+// all entries away from the matrix's own count, without the question 11 %).
 // A wave's 64 counters lie 32 words apart, on one bank, so the counters of a word are rotated by its number.
 constexpr int kHotSamplePieces = 512, kHotSample = kHotSamplePieces * kWave, kHotLevels = kReuseThreads;
 
 __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __restrict__ colidx, unsigned* table, int shift,
-                                                unsigned room, unsigned* bins, unsigned* waves) {
+                                                unsigned room, unsigned cached, unsigned* bins, unsigned* waves) {
     constexpr int kPerThread = kHotSample / kReuseThreads;
-    __shared__ unsigned s_level, s_above, s_met;
+    __shared__ unsigned s_level[2], s_above[2], s_tied[2], s_met[2][2];       // of the `room` and of the `cached` fullest runs
     const int t = (int)threadIdx.x;
     unsigned c[kPerThread];
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q)
         c[q] = (unsigned)colidx[(entries - kWave) / (kHotSamplePieces - 1) * (uniform(t / kWave) * kPerThread + q) + lane_id()];
     for (int i = 0; i < 8; ++i) reinterpret_cast<uint4*>(bins)[t + i * kReuseThreads] = make_uint4(0u, 0u, 0u, 0u);
-    if (t == 0) s_met = 0u;
+    if (t < 2) {
+        s_level[t] = (unsigned)kHotLevels;                       // even the last level has too many
+        s_above[t] = 0u;
+        s_met[t][0] = s_met[t][1] = 0u;
+    }
     __syncthreads();
     const auto place = [](unsigned word, unsigned bit) { return word * 32u + ((bit + word) & 31u); };
 #pragma unroll
@@ -2599,14 +2609,19 @@ __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __
     {
         const unsigned level = (unsigned)(kHotLevels - 1 - t), here = levels[level];
         const unsigned reach = reuse_prefix(here, waves, total) + here;
-        if (level >= 1u && reach <= room && (level == 1u || reach + levels[level - 1u] > room)) {
-            s_level = level;
-            s_above = reach;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const unsigned places = k == 0 ? room : cached;
+            if (level >= 1u && reach <= places && (level == 1u || reach + levels[level - 1u] > places)) {
+                s_level[k] = level;
+                s_above[k] = reach;
+            }
         }
     }
     __syncthreads();
+    if (t < 2) s_tied[t] = levels[s_level[t] - 1u];
     // its runs, and of those one below the first ones, as many as there are places left
-    const unsigned lowest = s_level, left = lowest > 1u ? room - s_above : 0u;
+    const unsigned lowest = s_level[0], left = lowest > 1u ? room - s_above[0] : 0u;
     unsigned mask = 0, below = 0;
 #pragma unroll
     for (unsigned b = 0; b < 32; ++b) {
@@ -2619,20 +2634,34 @@ __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __
     const unsigned tied = total >> 16, hot = (total & 0xffffu) + (tied < left ? tied : left);
     stat_store_two(reinterpret_cast<int*>(table) + 2 * t, (int)mask, (int)at);
     unsigned* list = bins + kHotLevels;
-    unsigned met = 0;
 #pragma unroll
-    for (unsigned b = 0; b < 32; ++b) {
-        if ((mask >> b) & 1u) {
-            list[at++] = 32u * (unsigned)t + b;
-            met += n[b];
+    for (unsigned b = 0; b < 32; ++b)
+        if ((mask >> b) & 1u) list[at++] = 32u * (unsigned)t + b;
+    // Without one of its entries a run still has the count that was asked for (the first sum), or it shares the places that are
+    // left with those one below (the second)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const unsigned level = s_level[k];
+        unsigned sure = 0, shared = 0;
+#pragma unroll
+        for (unsigned b = 0; b < 32; ++b) {
+            sure += level < (unsigned)kHotLevels && n[b] > level ? n[b] : 0u;
+            shared += (level < (unsigned)kHotLevels ? n[b] == level : n[b] + 1u >= level) ? n[b] : 0u;
         }
+        if (sure) atomicAdd(&s_met[k][0], sure);
+        if (shared) atomicAdd(&s_met[k][1], shared);
     }
-    if (met) atomicAdd(&s_met, met);
     __syncthreads();
     stat_store(reinterpret_cast<int*>(table) + 2 * kHotWords + t, (int)((unsigned)t < hot ? list[t] : kNoRow));
     stores_done();
     __syncthreads();
-    return s_met;
+    const auto would_be_met = [&](int k, unsigned places) {
+        const unsigned level = s_level[k];
+        const float share = level == 1u ? 0.0f : (float)(places - s_above[k] + 1u) / (float)(s_tied[k] + 1u);
+        return (float)s_met[k][0] + share * (float)s_met[k][1];
+    };
+    const float saved = would_be_met(0, room) - would_be_met(1, cached);
+    return saved > 0.0f ? (unsigned)(saved + 0.5f) : 0u;
 }
 static_assert(kHotSample / kHotLevels <= hot_room(4, kHotShiftMax) && kHotSample / kHotLevels <= hot_room(3, kHotShiftMax),
               "the runs of the last level fit");
@@ -2653,7 +2682,8 @@ __global__ __launch_bounds__(kReuseThreads) void column_reuse_kernel(long long e
     const int t = (int)threadIdx.x;
     if (blockIdx.x != 0) {
         const int v = (int)blockIdx.x;
-        const unsigned met = hot_columns(entries, colidx, hot_table + (v - 1) * kHotTableInts, hot_shift, (unsigned)hot_room(v, hot_shift), table, waves);
+        const unsigned met = hot_columns(entries, colidx, hot_table + (v - 1) * kHotTableInts, hot_shift, (unsigned)hot_room(v, hot_shift),
+                                         (unsigned)hot_cached(v, hot_shift), table, waves);
         if (t == 0) {
             __hip_atomic_store(out + 2 * kReuseLevels + v - 1, (unsigned long long)met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             stores_done();

@@ -120,6 +120,13 @@ struct GpuRuntime {
 };
 using Workspace = dgsp::Workspace<GpuRuntime>;
 
+// would any product look at the table?
+bool wants_hot_columns(const dgsp_internal_stats_t& stats) {
+    for (int64_t n = 1; n <= 4; ++n)
+        if (stats.hot_share[n - 1] > 0.0 && dgsp_internal_wants_hot_columns(&stats, n)) return true;
+    return false;
+}
+
 // The statistics of a ctypes `Features` structure, or of the `MatrixFeatures` that a DeviceCsr holds (None: there are none).
 class FeaturesArg {
 public:
@@ -135,7 +142,7 @@ public:
             throw Raised{};
         }
         given_ = true;
-        if (value_.hot_share[0] > 0.0 && dgsp_internal_wants_hot_columns(&value_, 1)) take_hot_columns(o);
+        if (wants_hot_columns(value_)) take_hot_columns(o);
     }
     const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
     // for a product with N columns on the GPU of `X`
@@ -314,8 +321,7 @@ void measure_columns(Measured& m, const at::Tensor& colidx, void* stream) {
     }
     const int rc = unlocked([&] { return dgsp_internal_measure_columns(&m.stats, columns, table, stream); });
     if (rc != DGSP_OK) m.stats = dgsp_internal_stats_t{m.stats.features};       // not measured: the general way
-    // what wider products have of it is less
-    if (!dgsp_internal_wants_hot_columns(&m.stats, 1)) m.hot_columns.reset();
+    if (!wants_hot_columns(m.stats)) m.hot_columns.reset();
 }
 
 // The arrays in the library's types and the statistics, which the call waits for.  int64 indices are narrowed by the

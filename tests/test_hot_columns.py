@@ -1,5 +1,6 @@
 """Products with one to four columns that read the hottest runs of X from LDS (nb_pr_kernel, HOT), against the oracle."""
 import copy
+import ctypes
 import pickle
 
 import numpy as np
@@ -13,14 +14,24 @@ WORDS, PIECES, TABLE = 1024, 512, 3 * 1024
 FLOATS = {1: 31 * 1024, 2: 28 * 1024, 3: 24 * 1024, 4: 20 * 1024}
 
 
-def uneven_matrix(M, K, power, seed, nnz=4_200_000):
-    """Row lengths far apart (CV above 4, empty rows among them); columns K * u^power, duplicates kept."""
+def column_law(K, law, count, rng):
+    """K * u^law, or the pair (H, share): that share of the entries uniform over H scattered runs, the others over all columns."""
+    if not isinstance(law, tuple):
+        return np.minimum((K * rng.random(count) ** law).astype(np.int64), K - 1)
+    shift = hot_shift(K)
+    runs = rng.choice((K - 1) >> shift, law[0], replace=False)
+    inside = (rng.choice(runs, count) << shift) + rng.integers(0, 1 << shift, count)
+    return np.where(rng.random(count) < law[1], inside, rng.integers(0, K, count))
+
+
+def uneven_matrix(M, K, law, seed, nnz=4_200_000):
+    """Row lengths far apart (CV above 4, empty rows among them); duplicate columns kept."""
     rng = np.random.default_rng(seed)
     weight = rng.pareto(0.9, M) * (rng.random(M) < 0.8)
     lens = np.minimum((weight * (1.3 * nnz / weight.sum())).astype(np.int64), 60_000)
     lens[rng.integers(0, M, 64)] += max(nnz - int(lens.sum()), 0) // 64 + 1
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
-    cols = np.minimum((K * rng.random(rowptr[-1]) ** power).astype(np.int64), K - 1)
+    cols = column_law(K, law, rowptr[-1], rng)
     return wl.CsrMatrix(M, K, rowptr, cols.astype(np.int32), rng.uniform(-1, 1, rowptr[-1]).astype(np.float32), "uneven", {})
 
 
@@ -31,50 +42,87 @@ def hot_shift(K):
     return shift
 
 
-def expected_table(colidx, K, V):
-    """Bitmap words, the words' running counts and the runs, as the selection's sample gives them; the share of the sample."""
-    shift = hot_shift(K)
-    room = FLOATS[V] // (V << shift)
+def run_counts(colidx, K):
+    """How often the selection's sample meets each run."""
     at = (len(colidx) - 64) // (PIECES - 1) * np.arange(PIECES)[:, None] + np.arange(64)
-    counts = np.bincount(colidx[at.ravel()] >> shift, minlength=32 * WORDS)
+    return np.bincount(colidx[at.ravel()] >> hot_shift(K), minlength=32 * WORDS)
+
+
+def fullest(counts, places):
+    """The runs that `places` places go to (the first of those that tie), and how many sampled entries would find their run among
+    them by the other entries' counts alone."""
     level = 1
-    while (counts >= level).sum() > room:
+    while (counts >= level).sum() > places:
         level += 1
-    hot = counts >= level
-    if level > 1:
-        below = np.flatnonzero(counts == level - 1)
-        hot[below[:room - hot.sum()]] = True
+    taken = counts >= level
+    if level == 1:
+        return taken, counts[counts > 1].sum()
+    left, tied = places - taken.sum(), np.flatnonzero(counts == level - 1)
+    sure, shared = counts[counts > level].sum(), counts[counts == level].sum()
+    taken[tied[:left]] = True
+    return taken, sure + shared * (left + 1) / (len(tied) + 1)
+
+
+def places(K, V):
+    """Runs that the table has room for, runs that an L1 holds anyway."""
+    per_run = V << hot_shift(K)
+    return FLOATS[V] // per_run, 4096 // per_run
+
+
+def expected_table(colidx, K, V):
+    """Bitmap words, the words' running counts and the runs, as the selection's sample gives them; the share that they save."""
+    counts = run_counts(colidx, K)
+    room, cached = places(K, V)
+    hot, met = fullest(counts, room)
+    share = max(met - fullest(counts, cached)[1], 0) / (64 * PIECES)
     runs = np.flatnonzero(hot)
     words = (hot.reshape(WORDS, 32) * (1 << np.arange(32, dtype=np.int64))).sum(1)
     before = np.concatenate([[0], np.cumsum(hot.reshape(WORDS, 32).sum(1))[:-1]])
     table = np.full(TABLE, -1, dtype=np.int64)
     table[0:2 * WORDS:2], table[1:2 * WORDS:2] = words, before
     table[2 * WORDS:2 * WORDS + len(runs)] = runs
-    return table.astype(np.uint32).view(np.int32), counts[hot].sum() / (64 * PIECES)
+    return table.astype(np.uint32).view(np.int32), share
 
 
-CASES = [("graph", 0, 0, 0), ("odd", 300_007, 700_001, 4.0), ("wide runs", 200_000, 3_000_001, 6.0),
-         ("every column hot", 150_001, 20_011, 1.0), ("few columns", 120_000, 37, 1.0), ("short last run", 262_144, 1_048_573, 4.0)]
+CASES = [("graph", 0, 0, 0), ("odd", 300_007, 700_001, (400, 0.6)), ("runs of 64", 200_000, 1_500_007, (200, 0.6)),
+         ("runs of 128", 200_000, 3_000_001, (100, 0.6)), ("every column hot", 150_001, 4_999, 1.0),
+         ("short last run", 262_144, 262_141, 4.0)]
 
 
-def matrix(name, M, K, power):
-    return wl.rmat_csr(19, 12, seed=3) if name == "graph" else uneven_matrix(M, K, power, seed=M)
+def matrix(name, M, K, law):
+    return wl.rmat_csr(19, 12, seed=3) if name == "graph" else uneven_matrix(M, K, law, seed=M)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name, M, K, power", CASES, ids=[c[0] for c in CASES])
-def test_products_with_hot_runs(name, M, K, power):
+@pytest.mark.parametrize("K, law", [(262_144, 1.0), (500_000, 1.0), (1 << 20, 3.0), (3_000_001, (60, 0.3))])
+def test_the_share_is_the_matrix_s_and_not_the_sample_s(K, law):
+    """The runs are those that the sample met most often, by luck among other things: what they save is counted over all entries here.
+    The sample's share is off by the square root of p (1 - p) / n; five times that."""
+    A = uneven_matrix(M := 200_000, K, law, seed=M)
+    print(f"[case] share of hot runs K={K}", flush=True)
+    f = dg.DeviceCsr(A).features
+    counts, runs = run_counts(A.colidx, K), A.colidx >> hot_shift(K)
+    for V in (1, 2, 3, 4):
+        hot, cached = (fullest(counts, n)[0] for n in places(K, V))
+        assert abs(f.hot_share[V - 1] - (np.mean(hot[runs]) - np.mean(cached[runs]))) <= 5 * 0.5 / (64 * PIECES) ** 0.5
+    # an L1 that holds all columns is saved nothing
+    assert dg.DeviceCsr(uneven_matrix(120_000, 37, 1.0, seed=1)).features.hot_columns is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name, M, K, law", CASES, ids=[c[0] for c in CASES])
+def test_products_with_hot_runs(name, M, K, law):
     import torch
-    A = matrix(name, M, K, power)
+    A = matrix(name, M, K, law)
     D = dg.DeviceCsr(A)
     f = D.features
     assert f.cv_row >= 4 and f.nnz >= 4_000_000
     tables = f.hot_columns.cpu().numpy().reshape(4, TABLE)
     for N in (1, 2, 3, 4):
         table, share = expected_table(A.colidx, A.K, N)
-        assert f.hot_share[N - 1] == pytest.approx(share)
+        assert f.hot_share[N - 1] == pytest.approx(share, abs=1.0 / (64 * PIECES))       # whole entries
         assert np.array_equal(tables[N - 1], table)
-        assert N > 1 or f.nnz * share >= 1.5e6
+        assert dg.lib().dgsp_internal_wants_hot_columns(ctypes.byref(f), ctypes.c_int64(N))
         X = wl.dense_matrix(A.K, N, "normal", seed=2)
         Y0 = wl.dense_matrix(A.M, N, "uniform", seed=1)
         ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
@@ -87,6 +135,12 @@ def test_products_with_hot_runs(name, M, K, power):
             x.copy_(dX)
             ok, worst = oracle.within_bound(D.spmm(x).cpu().numpy(), ref, bnd, 1e-5)
             assert ok, worst
+        # a table that calls every run hot and stages nothing: zeros, if the product looks at it
+        lies = dg.MatrixFeatures.from_buffer_copy(bytes(f))
+        lies.hot_columns = torch.tensor([-1, 0] * WORDS + [-1] * WORDS, dtype=torch.int32, device="cuda").repeat(4)
+        Y = torch.full((A.M, N), float("nan"), device="cuda")
+        dg.dgsp_spmm_csr_auto(A.M, A.K, N, lies, D.rowptr, D.colidx, D.vals, dX, Y)
+        assert not Y.any()
         for alpha, beta in ((-0.5, 1.5), (2.0, 0.0)):
             Y = torch.from_numpy(Y0).cuda() if beta else torch.full((A.M, N), float("nan"), device="cuda")
             dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, alpha, beta, features=f)

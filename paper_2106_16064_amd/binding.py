@@ -54,6 +54,7 @@ class MatrixFeatures(Features):
     products of this module hand it to the library."""
     _fields_ = [("saved_share", ctypes.c_double), ("hot_share", ctypes.c_double * 4)]
     hot_columns = None      # int32 tensor on the matrix's GPU
+    hot_stream = 0          # handle of the stream that its memory belongs to
 
 
 class Thresholds(ctypes.Structure):

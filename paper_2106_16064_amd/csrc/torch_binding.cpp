@@ -17,6 +17,7 @@
 #include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/grad_mode.h>
@@ -24,6 +25,7 @@
 #include <torch/csrc/jit/frontend/tracer.h>
 
 #include <cstring>
+#include <optional>
 #include <string>
 
 #include "dgsp_internal.h"
@@ -78,15 +80,34 @@ const at::Tensor& as_tensor(PyObject* o, const char* name) {
     return THPVariable_Unpack(o);
 }
 
+// The stream that a call runs on; `known`: as torch's allocator knows it, none for a stream that is not torch's, which may be gone
+// when the allocator asks how far it has come.
+struct CallStream {
+    void* handle;
+    std::optional<c10::hip::HIPStream> known;
+};
+
+CallStream call_stream(c10::hip::HIPStream s) {
+    void* handle = s.stream();
+    const bool foreign = handle != nullptr && s.id() == (int64_t)reinterpret_cast<intptr_t>(handle);        // torch names those by their address
+    return {handle, foreign ? std::nullopt : std::make_optional(s)};
+}
+
+CallStream current_stream() { return call_stream(c10::hip::getCurrentHIPStream()); }
+
 // the torch stream given, or the current one
-void* as_stream(PyObject* o) {
-    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+CallStream as_stream(PyObject* o) {
+    if (o == Py_None) return current_stream();
     PyObject* handle = PyObject_GetAttrString(o, "cuda_stream");
     if (!handle) throw Raised{};
     void* p = PyLong_AsVoidPtr(handle);
     Py_DECREF(handle);
     if (!p && PyErr_Occurred()) throw Raised{};
-    return p;
+    if (!THPStream_Check(o)) return {p, std::nullopt};
+    const auto* t = reinterpret_cast<THPStream*>(o);
+    const c10::Device device(c10::DeviceType::HIP, (c10::DeviceIndex)t->device_index);
+    const CallStream s = call_stream(c10::hip::HIPStream(c10::hip::HIPStream::UNCHECKED, c10::Stream(c10::Stream::UNSAFE, device, t->stream_id)));
+    return s.handle == p ? s : CallStream{p, std::nullopt};
 }
 
 void* ptr(const at::Tensor& t) { return t.numel() == 0 ? nullptr : t.data_ptr(); }
@@ -146,30 +167,41 @@ public:
     }
     const dgsp_features_t* get() const { return given_ ? &value_.features : nullptr; }
     // for a product with N columns on the GPU of `X`
-    dgsp_internal_hints_t hints(int64_t N, const at::Tensor& X, Workspace& workspace) const {
-        const bool hot = hot_.defined() && hot_.device() == X.device() && dgsp_internal_wants_hot_columns(&value_, N);
-        return {value_.saved_share, hot ? static_cast<const uint32_t*>(hot_.data_ptr()) : nullptr, &Workspace::get, &workspace};
+    dgsp_internal_hints_t hints(int64_t N, const at::Tensor& X, Workspace& workspace, const CallStream& stream) const {
+        return {value_.saved_share, hot_columns(N, X, stream), &Workspace::get, &workspace};
     }
 
 private:
+    // The table goes when the structure does, which the caller may let go as soon as the call has returned.  Its memory must not be
+    // handed out again before the product has run: on the stream that it was allocated on it comes later anyway, other streams of
+    // torch's are named to the allocator, and on those that torch does not know products go the general way.
+    const uint32_t* hot_columns(int64_t N, const at::Tensor& X, const CallStream& stream) const {
+        if (!hot_.defined() || hot_.device() != X.device() || !dgsp_internal_wants_hot_columns(&value_, N)) return nullptr;
+        if (!stream.handle || stream.handle != hot_stream_) {
+            if (!stream.known) return nullptr;
+            c10::hip::HIPCachingAllocator::recordStream(hot_.storage().data_ptr(), *stream.known);
+        }
+        return static_cast<const uint32_t*>(hot_.data_ptr());
+    }
+
     // A tensor that the structure carries as an attribute and not as an address among its bytes, which could outlive it.
     void take_hot_columns(PyObject* o) {
-        static PyObject* const name = PyUnicode_InternFromString("hot_columns");
-        PyObject* t = PyObject_GetAttr(o, name);
-        if (!t) {
-            PyErr_Clear();
-            return;
-        }
-        if (THPVariable_Check(t)) {
+        static PyObject *const columns = PyUnicode_InternFromString("hot_columns"), *const stream = PyUnicode_InternFromString("hot_stream");
+        PyObject *t = PyObject_GetAttr(o, columns), *s = t ? PyObject_GetAttr(o, stream) : nullptr;
+        if (t && THPVariable_Check(t)) {
             const at::Tensor& table = THPVariable_Unpack(t);
             if (is_array(table, at::kInt) && table.numel() * 4 == dgsp_internal_hot_columns_bytes(&value_)) hot_ = table;
         }
-        Py_DECREF(t);
+        if (s && PyLong_Check(s)) hot_stream_ = PyLong_AsVoidPtr(s);
+        PyErr_Clear();
+        Py_XDECREF(s);
+        Py_XDECREF(t);
     }
 
     dgsp_internal_stats_t value_{};
     bool given_ = false;
     at::Tensor hot_;
+    void* hot_stream_ = nullptr;
 };
 
 void check_array(const at::Tensor& t, at::ScalarType type, const char* name, const char* type_name) {
@@ -211,6 +243,7 @@ int unlocked(F&& call) {
 struct Measured {
     dgsp_internal_stats_t stats{};
     at::Tensor hot_columns;         // undefined: none, or none worth having
+    void* hot_stream = nullptr;     // that its memory belongs to
 };
 
 void write_features(PyObject* o, const Measured& m) {
@@ -223,9 +256,12 @@ void write_features(PyObject* o, const Measured& m) {
     if (!fits) fail("features must be a MatrixFeatures structure");
     if (m.hot_columns.defined()) {
         PyObject* table = THPVariable_Wrap(m.hot_columns);
-        const int rc = PyObject_SetAttrString(o, "hot_columns", table);
+        PyObject* stream = PyLong_FromVoidPtr(m.hot_stream);
+        const bool set = table && stream && PyObject_SetAttrString(o, "hot_columns", table) == 0 &&
+                         PyObject_SetAttrString(o, "hot_stream", stream) == 0;
+        Py_XDECREF(stream);
         Py_XDECREF(table);
-        if (rc != 0) throw Raised{};
+        if (!set) throw Raised{};
     }
 }
 
@@ -233,14 +269,15 @@ void write_features(PyObject* o, const Measured& m) {
 
 // Y = A X by a named kernel, or by the rules (DGSP_AUTO); returns the status and leaves the kernel run in `algo`
 int product(int64_t M, int64_t K, int64_t N, const FeaturesArg& f, const at::Tensor& rowptr, const at::Tensor& colidx,
-            const at::Tensor& vals, const at::Tensor& X, const at::Tensor& Y, int& algo, void* stream) {
+            const at::Tensor& vals, const at::Tensor& X, const at::Tensor& Y, int& algo, const CallStream& on) {
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
+    void* const stream = on.handle;
     Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
-    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace, on);
     if (algo == DGSP_AUTO) return dgsp_internal_spmm_auto(M, K, N, f.get(), &hints, rp, ci, av, x, y, &algo, stream);
     return dgsp_internal_spmm_phase(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, DGSP_PHASE_ALL, f.get(), &hints, stream);
 }
@@ -274,7 +311,7 @@ at::Tensor multiply(const Csr& A, const at::Tensor& X, int algo, bool vector_res
     const int64_t N = columns_of(X);
     at::Tensor Y = empty_result(A.M, N, vector_result, X);
     check_packed(A.M, A.K, N, X, Y);
-    void* stream = c10::hip::getCurrentHIPStream().stream();
+    const CallStream stream = current_stream();
     const int rc = unlocked([&] { return product(A.M, A.K, N, A.features, A.rowptr, A.colidx, A.vals, X, Y, algo, stream); });
     check_status(rc, "dgsp_spmm_csr_auto");
     return Y;
@@ -297,7 +334,7 @@ struct ProductBackward : public torch::autograd::Node {
         const at::Tensor dX = empty_result(A.M, N, vector, G);
         int which = algo;
         const int rc = product(A.M, A.K, N, A.features, A.rowptr, A.colidx, A.vals, G, dX, which,
-                               c10::hip::getCurrentHIPStream().stream());
+                               current_stream());
         TORCH_CHECK(rc == DGSP_OK, "dgsp_spmm_csr_auto: ", dgsp_status_string(rc), " (status ", rc, ")");
         return {dX};
     }
@@ -317,6 +354,7 @@ void measure_columns(Measured& m, const at::Tensor& colidx, void* stream) {
     uint32_t* table = nullptr;
     if (const int64_t bytes = dgsp_internal_hot_columns_bytes(&m.stats)) {
         m.hot_columns = at::empty({bytes / 4}, colidx.options());
+        m.hot_stream = c10::hip::getCurrentHIPStream(colidx.device().index()).stream();
         table = static_cast<uint32_t*>(m.hot_columns.data_ptr());
     }
     const int rc = unlocked([&] { return dgsp_internal_measure_columns(&m.stats, columns, table, stream); });
@@ -475,14 +513,15 @@ PyObject* spmm_csr_phase(PyObject* const* a, Py_ssize_t n) {
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
     FeaturesArg f(a[11]);
-    void* stream = as_stream(a[12]);
+    const CallStream on = as_stream(a[12]);
+    void* const stream = on.handle;
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
-    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace, on);
     check_status(unlocked([&] {
         return dgsp_internal_spmm_phase(M, K, N, nnz, rp, ci, av, x, y, algo, phase, f.get(), &hints, stream);
     }), "dgsp_spmm_csr_phase");
@@ -498,7 +537,7 @@ PyObject* spmm_csr_auto(PyObject* const* a, Py_ssize_t n) {
     const at::Tensor &X = as_tensor(a[7], "X"), &Y = as_tensor(a[8], "Y");
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
-    void* stream = as_stream(a[9]);
+    const CallStream stream = as_stream(a[9]);
     int algo = DGSP_AUTO;
     check_status(unlocked([&] { return product(M, K, N, f, rowptr, colidx, vals, X, Y, algo, stream); }), "dgsp_spmm_csr_auto");
     return PyLong_FromLong(algo);
@@ -514,7 +553,7 @@ void packed_product(PyObject* const* extents, PyObject* count, PyObject* const* 
     check_csr(M, rowptr, colidx, vals);
     check_packed(M, K, N, X, Y);
     if (nnz >= 0 && colidx.numel() < nnz) fail("colidx/vals shorter than nnz");
-    void* stream = as_stream(a[6]);
+    void* const stream = as_stream(a[6]).handle;
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
@@ -548,14 +587,15 @@ void view_product(PyObject* const* a, const float* factors, PyObject* const* b) 
     const int64_t ldx = check_view(X, "X", K, N), ldy = check_view(Y, "Y", M, N);
     const int algo = (int)to_int(b[0]);
     FeaturesArg f(b[1]);
-    void* stream = as_stream(b[2]);
+    const CallStream on = as_stream(b[2]);
+    void* const stream = on.handle;
     const auto* rp = static_cast<const int32_t*>(ptr(a[4], "rowptr"));
     const auto* ci = static_cast<const int32_t*>(ptr(a[5], "colidx"));
     const auto* av = static_cast<const float*>(ptr(a[6], "vals"));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
-    const dgsp_internal_hints_t hints = f.hints(N, X, workspace);
+    const dgsp_internal_hints_t hints = f.hints(N, X, workspace, on);
     const int rc = unlocked([&] {
         return dgsp_internal_spmm_view(M, K, N, nnz, rp, ci, av, x, ldx, y, ldy, factors, algo, f.get(), &hints, stream);
     });

@@ -135,9 +135,9 @@ def test_products_with_hot_runs(name, M, K, law):
             x.copy_(dX)
             ok, worst = oracle.within_bound(D.spmm(x).cpu().numpy(), ref, bnd, 1e-5)
             assert ok, worst
-        # a table that calls every run hot and stages nothing: zeros, if the product looks at it
+        # the product looks at the table
         lies = dg.MatrixFeatures.from_buffer_copy(bytes(f))
-        lies.hot_columns = torch.tensor([-1, 0] * WORDS + [-1] * WORDS, dtype=torch.int32, device="cuda").repeat(4)
+        lies.hot_columns = zeros_table()
         Y = torch.full((A.M, N), float("nan"), device="cuda")
         dg.dgsp_spmm_csr_auto(A.M, A.K, N, lies, D.rowptr, D.colidx, D.vals, dX, Y)
         assert not Y.any()
@@ -221,3 +221,73 @@ def test_hot_runs_in_a_graph_and_on_a_stream():
         graph.replay()
         torch.cuda.synchronize()
         assert (Y - want * 2.0 ** (k + 1)).abs().max() <= 1e-5 * scale * 2.0 ** (k + 1)
+
+
+def zeros_table():
+    """Calls every run hot and stages nothing: a product that looks at it is zero."""
+    import torch
+    return torch.tensor([-1, 0] * WORDS + [-1] * WORDS, dtype=torch.int32, device="cuda").repeat(4)
+
+
+def device_matrix(A):
+    """With int32 arrays, which the caller keeps."""
+    import torch
+    arrays = [torch.from_numpy(a).cuda() for a in (A.rowptr, A.colidx, A.vals)]
+    return dg.DeviceCsr.from_device(A.M, A.K, *arrays), arrays
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("by_argument", [True, False])
+def test_the_table_s_memory_is_not_reused_under_a_product_on_another_stream(by_argument):
+    """The matrix may go while its products on other streams are still to run: the arrays are the caller's, the table is not."""
+    import torch
+    A = matrix(*CASES[0])
+    D, arrays = device_matrix(A)
+    X = torch.randn(A.K, 1, device="cuda")
+    want = D.spmm(X, algo=dg.NB_SR)
+    side, busy = torch.cuda.Stream(), torch.randn(8192, 8192, device="cuda")
+    Y = torch.empty(A.M, 1, device="cuda")
+    torch.cuda.synchronize()
+    print("[case] hot runs: the matrix goes before its product runs", flush=True)
+    with torch.cuda.stream(side):
+        for _ in range(20):
+            busy @ busy
+        if not by_argument:
+            D.spmm(X, Y=Y)
+    if by_argument:
+        D.spmm(X, Y=Y, stream=side)
+    table = D.features.hot_columns.data_ptr()
+    del D
+    blocks = [torch.full((4 * TABLE,), -1, dtype=torch.int32, device="cuda") for _ in range(64)]
+    assert not side.query()                               # the product is still to come
+    assert table not in [b.data_ptr() for b in blocks]
+    torch.cuda.synchronize()
+    assert (Y - want).abs().max() <= 1e-5 * want.abs().max()
+
+
+@pytest.mark.gpu
+def test_streams_that_torch_does_not_know():
+    """The allocator cannot be told of them for good: products go without the table, unless its memory is that stream's own."""
+    import torch
+    A = matrix(*CASES[0])
+    X = torch.randn(A.K, 1, device="cuda")
+    foreign = torch.cuda.ExternalStream(torch.cuda.Stream().cuda_stream)
+    torch.cuda.synchronize()
+    print("[case] hot runs on a foreign stream", flush=True)
+
+    def looks_at_the_table(D, **stream):
+        return not D.spmm(X, Y=torch.full((A.M, 1), float("nan"), device="cuda"), **stream).any()
+
+    D, _ = device_matrix(A)
+    D.features.hot_columns.copy_(zeros_table())
+    assert looks_at_the_table(D)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        assert looks_at_the_table(D)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(foreign):
+        assert not looks_at_the_table(D)
+        own, _ = device_matrix(A)
+        own.features.hot_columns.copy_(zeros_table())
+        assert looks_at_the_table(own)
+    torch.cuda.synchronize()
+    assert not looks_at_the_table(D, stream=foreign)

@@ -174,9 +174,16 @@ public:
 private:
     // The table goes when the structure does, which the caller may let go as soon as the call has returned.  Its memory must not be
     // handed out again before the product has run: on the stream that it was allocated on it comes later anyway, other streams of
-    // torch's are named to the allocator, and on those that torch does not know products go the general way.
+    // torch's are named to the allocator, and on those that torch does not know products go the general way.  So do products that are
+    // recorded into a graph: its replays read whatever has become of the table.
     const uint32_t* hot_columns(int64_t N, const at::Tensor& X, const CallStream& stream) const {
         if (!hot_.defined() || hot_.device() != X.device() || !dgsp_internal_wants_hot_columns(&value_, N)) return nullptr;
+        bool recording = false;
+        if (!GpuRuntime::capture_status(static_cast<hipStream_t>(stream.handle), recording)) {
+            GpuRuntime::forget_error();
+            return nullptr;
+        }
+        if (recording) return nullptr;
         if (!stream.handle || stream.handle != hot_stream_) {
             if (!stream.known) return nullptr;
             c10::hip::HIPCachingAllocator::recordStream(hot_.storage().data_ptr(), *stream.known);

@@ -56,6 +56,20 @@ class MatrixFeatures(Features):
     hot_columns = None      # int32 tensor on the matrix's GPU
     hot_stream = 0          # handle of the stream that its memory belongs to
 
+    def __copy__(self):
+        copied = type(self).from_buffer_copy(self)
+        vars(copied).update(vars(self))
+        return copied
+
+    def __deepcopy__(self, memo):
+        return self.__copy__()          # nothing writes to the table: copies share it
+
+    def __reduce__(self):
+        """Without the table, which stays in the memory of its GPU: statistics can be read where there is none."""
+        restore, (cls, (attributes, data)) = super().__reduce__()
+        attributes = {k: v for k, v in attributes.items() if k not in ("hot_columns", "hot_stream")}
+        return restore, (cls, (attributes, data))
+
 
 class Thresholds(ctypes.Structure):
     """``dgsp_thresholds_t``"""
@@ -408,6 +422,12 @@ class DeviceCsr:
         self.features = features
         self.tuned = {}
         return self
+
+    def __setstate__(self, state):
+        """Restored from a file or deeply copied: the table of hot runs that its statistics lack is made again."""
+        self.__dict__.update(state)
+        if self.colidx.is_cuda and any(self.features.hot_share) and self.features.hot_columns is None:
+            (_native or native()).measure_matrix_columns(self.features, self.colidx)
 
     def autotune(self, X, reps=5, Y=None):
         """Times the four kernels for this matrix and this width of X and remembers the winner:

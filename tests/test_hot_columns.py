@@ -93,6 +93,23 @@ def matrix(name, M, K, law):
     return wl.rmat_csr(19, 12, seed=3) if name == "graph" else uneven_matrix(M, K, law, seed=M)
 
 
+def test_statistics_are_saved_without_the_table():
+    """They are read where the GPU that holds the table is not; copies in the same program share it."""
+    import torch
+    f = dg.MatrixFeatures(M=3, K=5, saved_share=0.25)
+    f.hot_share[1] = 0.5
+    f.hot_columns, f.hot_stream, f.note = torch.arange(4), 16, "kept"
+    saved = pickle.dumps(f)
+    assert b"tensor" not in saved and b"storage" not in saved
+    restored = pickle.loads(saved)
+    assert bytes(restored) == bytes(f) and restored.note == "kept"
+    assert restored.hot_columns is None and restored.hot_stream == 0
+    for copied in (copy.copy(f), copy.deepcopy(f)):
+        assert bytes(copied) == bytes(f) and copied.hot_columns is f.hot_columns and copied.hot_stream == 16 and copied.note == "kept"
+        copied.M = 4
+        assert f.M == 3
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("K, law", [(262_144, 1.0), (500_000, 1.0), (1 << 20, 3.0), (3_000_001, (60, 0.3))])
 def test_the_share_is_the_matrix_s_and_not_the_sample_s(K, law):
@@ -188,7 +205,10 @@ def test_the_table_stays_with_its_matrix():
     bare = dg.MatrixFeatures.from_buffer_copy(bytes(f))
     assert list(bare.hot_share) == list(f.hot_share) and bare.hot_columns is None
     restored = pickle.loads(pickle.dumps(f))
-    assert restored.hot_columns is None or torch.equal(restored.hot_columns, f.hot_columns)
+    assert bytes(restored) == bytes(f) and restored.hot_columns is None
+    again = pickle.loads(pickle.dumps(D))                           # a whole matrix comes back with a table
+    assert torch.equal(again.features.hot_columns, f.hot_columns) and bytes(again.features) == bytes(f)
+    assert copy.deepcopy(D).features.hot_columns is f.hot_columns
     wrong = copy.copy(bare)
     wrong.hot_columns = f.hot_columns[:-1].contiguous()
     for features in (f, bare, wrong, restored, copy.copy(f), dg.Features(**f.as_dict())):

@@ -1177,7 +1177,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             buffer_load_vec<4>(rh, none ? kOutOfRange : ((run[k] * (unsigned)V) << (hot.shift + 2)) + inside * 16u, piece[k]);
         }
     };
-    // the only step that the workgroup's waves take together; every wave gets to one of its calls
+    // the only step that the workgroup's waves take together
     const auto fill_hot = [&] {
 #pragma unroll
         for (int k = 0; k < kWordPieces; ++k) {
@@ -1194,11 +1194,11 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
     int is = 0, ie1 = 0;
-    if (any_items && nnz != 0) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
-    if (!any_items || nnz == 0) {
-        if constexpr (HOT) { load_hot(); fill_hot(); }
+    bool idle = !any_items || nnz == 0;                  // HOT: such a wave has an empty chunk and goes along up to the barrier
+    if (!idle) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
+    // nothing stored: every item is a row end; my rows are [d0, d1)
+    const auto rows_without_entries = [&] {
         if (!any_items) return;
-        // nothing stored: every item is a row end; my rows are [d0, d1)
         for (unsigned r = d0 + lane; r < d1; r += kWave) {
             float* y = Y + (size_t)r * ldy + n0;
             float out[V];
@@ -1207,14 +1207,20 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             if constexpr (AXPBY) scale_into<V, true>(out, y, sc, second);
             store_vec_dword_aligned<V>(y, out, second);
         }
-        return;
+    };
+    if constexpr (!HOT) {
+        if (idle) {
+            rows_without_entries();
+            return;
+        }
     }
     unsigned js0 = d0 - (unsigned)is, je1 = d1 - (unsigned)ie1;
+    if (HOT && idle) js0 = je1 = 0u;
     if constexpr (SNAP) {
-        snap_to_rows(rowptr, M, d0, d1, is, ie1, js0, je1);
-        if (is == ie1) {
-            if constexpr (HOT) { load_hot(); fill_hot(); }
-            return;
+        if (!idle) snap_to_rows(rowptr, M, d0, d1, is, ie1, js0, je1);
+        idle |= is == ie1;
+        if constexpr (!HOT) {
+            if (idle) return;
         }
     }
     unsigned js = js0;
@@ -1325,7 +1331,13 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     load_row_ends(is, is < ie1, w_end);
     if constexpr (HOT) load_hot();
     load_entries(1, lc, la);
-    if constexpr (HOT) fill_hot();
+    if constexpr (HOT) {
+        fill_hot();
+        if (idle) {
+            if (nnz == 0) rows_without_entries();
+            return;
+        }
+    }
     gather(0, c, x);
 
     // state of the step in flight between its two halves

@@ -24,12 +24,17 @@ def column_law(K, law, count, rng):
     return np.where(rng.random(count) < law[1], inside, rng.integers(0, K, count))
 
 
-def uneven_matrix(M, K, law, seed, nnz=4_200_000):
-    """Row lengths far apart (CV above 4, empty rows among them); duplicate columns kept."""
+def uneven_matrix(M, K, law, seed, nnz=4_200_000, longest=60_000):
+    """Row lengths far apart (CV above 4, empty rows among them); duplicate columns kept.  longest = 3100: one row in twenty has
+    140 entries, a hundred have as many as that, more than a wave's share, and short enough that the waves take whole rows."""
     rng = np.random.default_rng(seed)
-    weight = rng.pareto(0.9, M) * (rng.random(M) < 0.8)
-    lens = np.minimum((weight * (1.3 * nnz / weight.sum())).astype(np.int64), 60_000)
-    lens[rng.integers(0, M, 64)] += max(nnz - int(lens.sum()), 0) // 64 + 1
+    if longest == 3100:
+        lens = np.where(rng.random(M) < 0.05, 140, 0)
+        lens[rng.choice(M, 100, replace=False)] = longest
+    else:
+        weight = rng.pareto(0.9, M) * (rng.random(M) < 0.8)
+        lens = np.minimum((weight * (1.3 * nnz / weight.sum())).astype(np.int64), longest)
+        lens[rng.integers(0, M, 64)] += max(nnz - int(lens.sum()), 0) // 64 + 1
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     cols = column_law(K, law, rowptr[-1], rng)
     return wl.CsrMatrix(M, K, rowptr, cols.astype(np.int32), rng.uniform(-1, 1, rowptr[-1]).astype(np.float32), "uneven", {})
@@ -86,11 +91,22 @@ def expected_table(colidx, K, V):
 
 CASES = [("graph", 0, 0, 0), ("odd", 300_007, 700_001, (400, 0.6)), ("runs of 64", 200_000, 1_500_007, (200, 0.6)),
          ("runs of 128", 200_000, 3_000_001, (100, 0.6)), ("every column hot", 150_001, 4_999, 1.0),
-         ("short last run", 262_144, 262_141, 4.0)]
+         ("short last run", 262_144, 262_141, 4.0), ("whole rows", 600_000, 3_000_001, (100, 0.6))]
 
 
 def matrix(name, M, K, law):
-    return wl.rmat_csr(19, 12, seed=3) if name == "graph" else uneven_matrix(M, K, law, seed=M)
+    if name == "graph":
+        return wl.rmat_csr(19, 12, seed=3)
+    return uneven_matrix(M, K, law, seed=M, longest=3100 if name == "whole rows" else 60_000)
+
+
+def launches(call):
+    """Names of the kernels that a call launches."""
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages()]
 
 
 def test_statistics_are_saved_without_the_table():
@@ -152,6 +168,10 @@ def test_products_with_hot_runs(name, M, K, law):
             x.copy_(dX)
             ok, worst = oracle.within_bound(D.spmm(x).cpu().numpy(), ref, bnd, 1e-5)
             assert ok, worst
+        # waves that take whole rows share none, so nothing is prepared; some of them have no row at all here
+        kernels = launches(lambda: D.spmm(dX))
+        assert any("nb_pr_kernel" in k for k in kernels)
+        assert any("nb_prepare_kernel" in k for k in kernels) == (name != "whole rows")
         # the product looks at the table
         lies = dg.MatrixFeatures.from_buffer_copy(bytes(f))
         lies.hot_columns = zeros_table()

@@ -72,6 +72,30 @@ def test_products_from_queues(name, make, N):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("make, N, longer", [(graph, 41, 1.0001), (graph, 128, 1.5), (hub, 45, 1.1), (few_rows, 64, 2.0)])
+def test_arrays_longer_than_the_matrix(make, N, longer):
+    """Calls with a named kernel take the length of colidx for the entry count: chunks are then more or longer than one quantum."""
+    import torch
+    A = make()
+    D = dg.DeviceCsr(A)
+    room = int(A.nnz * longer) + 1
+    colidx, vals = torch.zeros(room, dtype=torch.int32, device="cuda"), torch.full((room,), float("nan"), device="cuda")
+    colidx[:A.nnz], vals[:A.nnz] = D.colidx, D.vals
+    X = wl.dense_matrix(A.K, N, "normal", seed=2)
+    Y0 = wl.dense_matrix(A.M, N, "uniform", seed=1)
+    ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    dX, Y = torch.from_numpy(X).cuda(), torch.full((A.M, N), float("nan"), device="cuda")
+    print(f"[case] queues, arrays {longer} times as long N={N}", flush=True)
+    assert allocations(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) == 1
+    ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+    assert ok, worst
+    Y = torch.from_numpy(Y0).cuda()
+    assert allocations(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) == 1
+    ok, worst = oracle.within_bound(Y.cpu().numpy(), -0.5 * ref + 1.5 * Y0, 0.5 * bnd + 1.5 * np.abs(Y0), 1e-5)
+    assert ok, worst
+
+
+@pytest.mark.gpu
 def test_queues_of_calls_on_several_streams_and_none_in_a_graph():
     """Calls in flight together have queues of their own; a product that is recorded goes without."""
     import torch

@@ -613,7 +613,7 @@ int launch_nb_pr_v(const Problem& p) {
     // a wave alone takes 512 entries in about 4 us
     const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, grid.x * kWavesPerBlock * kSubRanges, 6, -1)) return rc;
+        if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         if (tiled) {
             if (p.scaled)
@@ -651,7 +651,7 @@ int launch_nb_sr_v(const Problem& p) {
     const int logU = kNbSrLogTile - 6 + cols.logG;   // items per lane-group run
     const dim3 grid(balanced_blocks(p, kNbSrTile, resident_blocks_per_cu(nb_sr_kernel<V, XBUF, DEPTH>), false, cols.blocks), cols.blocks);
     if (p.phase != DGSP_PHASE_MAIN)
-        if (int rc = launch_prepare(p, grid.x * kWavesPerBlock * kSubRanges, (unsigned)logU, kNbSrLogTile)) return rc;
+        if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, (unsigned)logU, kNbSrLogTile)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         if (p.scaled)
             DGSP_LAUNCH((nb_sr_kernel<V, XBUF, DEPTH, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx,
@@ -734,7 +734,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock * kSubRanges, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
+        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         const auto launch = [&](auto scaled, auto queued) -> int {

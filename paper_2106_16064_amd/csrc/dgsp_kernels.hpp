@@ -398,22 +398,22 @@ __global__ __launch_bounds__(kBlock) void rs_sr_direct_kernel(int M, int N, int 
 // of a piece.  For matrices without empty stretches it is the paper's fixed
 // share of non-zeros up to the few percent that row markers add.
 //
-// The list is cut into kSubRanges * (number of waves) contiguous chunks; wave w
-// takes chunks w, w + nwaves, ... (waves of one XCD hold neighbouring chunks).
-// Chunks begin at multiples of a quantum of items and differ by at most one
-// quantum: chunk c covers quanta [c*Q/parts, (c+1)*Q/parts) of the Q quanta, so
-// no wave stays without work while another holds two quanta.  The split is
-// static: one contended atomic costs more than a tile on this machine.  A wave
-// finds the first row of a chunk with a 64-way search and then walks.
+// The list is cut into contiguous chunks, one a wave (waves of one XCD hold
+// neighbouring chunks).  Chunks begin at multiples of a quantum of items and
+// differ by at most one quantum: chunk c covers quanta [c*Q/parts, (c+1)*Q/parts)
+// of the Q quanta, so no wave stays without work while another holds two quanta.
+// A wave finds the first row of its chunk with a 64-way search and then walks.
+// This split is static; where a wave's share is long and the call has memory for
+// it, nb_sr_run_kernel cuts the list finer and the waves take most of the chunks
+// from queues (ChunkQueues).
 //
 // Rows whose items straddle a chunk boundary (in the sequential kernel: the
 // boundary of a lane group's run) are combined with fp32 atomic adds; the
 // paper does not say how partial rows of different warps meet.  That needs
 // zeros underneath.  A small "prepare" kernel zeroes exactly those rows and no
-// others; every other row, empty ones included, is written once with a plain
-// store by the chunk that holds its end marker.
-
-constexpr unsigned kSubRanges = 1;
+// others (in the scaled form of nb_sr_run_kernel also the rows without entries);
+// every other row is written once with a plain store by the chunk that holds its
+// end marker.
 
 // The even split of the Q quanta into `parts` chunks: chunk c starts at quantum floor(c * Q / parts),
 // so chunks differ by at most one quantum and the longer ones are spread over the whole list (put
@@ -577,17 +577,15 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     }
 }
 
-// The chunks of the calling wave: chunk(s) = s * nwaves + wave id, s < kSubRanges.
+// The chunk of the calling wave, number `wave` of `waves`.
 struct ChunkPlan {
-    unsigned nnz, items, nwaves, gw;
+    unsigned nnz, items, wave;
     EvenSplit split;
-    __device__ __forceinline__ ChunkPlan(unsigned nnz_, unsigned items_, unsigned nwaves_, unsigned gw_,
-                                         unsigned quantum_log2)
-        : nnz(nnz_), items(items_), nwaves(nwaves_), gw(gw_), split(items_, nwaves_ * kSubRanges, quantum_log2) {}
-    __device__ __forceinline__ bool range(unsigned s, unsigned& d0, unsigned& d1) const {
-        const unsigned c = s * nwaves + gw;
-        d0 = split.start(c);
-        const unsigned e = split.start(c + 1);
+    __device__ __forceinline__ ChunkPlan(unsigned nnz_, unsigned items_, unsigned waves, unsigned wave_, unsigned quantum_log2)
+        : nnz(nnz_), items(items_), wave(wave_), split(items_, waves, quantum_log2) {}
+    __device__ __forceinline__ bool range(unsigned& d0, unsigned& d1) const {
+        d0 = split.start(wave);
+        const unsigned e = split.start(wave + 1);
         d1 = e < items ? e : items;
         return d0 < d1;
     }
@@ -597,12 +595,6 @@ __device__ __forceinline__ ChunkPlan plan_chunks(const int* __restrict__ rowptr,
     const unsigned nnz = (unsigned)rowptr[M];
     return ChunkPlan(nnz, nnz + (unsigned)M, gridDim.x * kWavesPerBlock,
                      xcd_contiguous(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block(), quantum_log2);
-}
-// the same for a workgroup that is number `wg` of `nwg` sharing the list (a mapping of its own, see nb_sr_kernel)
-__device__ __forceinline__ ChunkPlan plan_chunks(const int* __restrict__ rowptr, int M, unsigned quantum_log2, unsigned wg,
-                                                 unsigned nwg) {
-    const unsigned nnz = (unsigned)rowptr[M];
-    return ChunkPlan(nnz, nnz + (unsigned)M, nwg * kWavesPerBlock, wg * kWavesPerBlock + wave_in_block(), quantum_log2);
 }
 
 // What the first round of a search probes does not depend on what is searched for: asked for beside the entry count, from
@@ -762,9 +754,8 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
     };
 
-    for (unsigned sub = 0; sub < kSubRanges; ++sub) {
     unsigned d0, d1;
-    if (!plan.range(sub, d0, d1)) continue;
+    if (!plan.range(d0, d1)) return;
 
     if (nnz == 0) {
         // nothing stored: every item is a row end; my rows are [d0, d1)
@@ -779,7 +770,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
             if constexpr (AXPBY) scale_into<V, true>(out, y, sc, second);
             store_vec_dword_aligned<V>(y, out, second);
         }
-        continue;
+        return;
     }
 
     int is;                                                 // rows that ended before my chunk
@@ -790,7 +781,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         int ie1; unsigned je1;
         wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
         snap_to_rows(rowptr, M, d0, d1, is, ie1, js, je1);
-        if (is == ie1) continue;
+        if (is == ie1) return;
         d0 = (unsigned)is + js;
         d1 = (unsigned)ie1 + je1;
     } else {
@@ -1058,7 +1049,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
     }
     if (any && lane == 0 && is < M) add_to_row(Y + (size_t)is * ldy + n0, carry);
-    }   // next chunk
 }
 
 // ===========================================================================
@@ -1143,7 +1133,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     };
 
     unsigned d0, d1;
-    const bool any_items = plan.range(0, d0, d1);
+    const bool any_items = plan.range(d0, d1);
     // The hot runs, 16 bytes a load, and their bitmap: the bitmap and the runs' numbers are on their way while the chunk's bounds are
     // searched, the runs themselves behind the chunk's first entries (loads return in order: in front of the search they
     // held up its rounds, first gathers 9.8 us after the start; R-MAT 2^20 x 16 / 2^19 x 16 at N = 1 70.1 / 39.0 -> 68.7 / 37.9 us).
@@ -1662,9 +1652,8 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
     const __amdgpu_buffer_rsrc_t rx = make_buffer(X, XBUF ? x_bytes : 0ull);
     const unsigned n_bytes = (unsigned)n * 4u;
 
-    for (unsigned sub = 0; sub < kSubRanges; ++sub) {
     unsigned d0, d1;
-    if (!plan.range(sub, d0, d1)) continue;
+    if (!plan.range(d0, d1)) return;
     int is = wave_merge_rows_before(rowptr, M, d0, lane, probe);
     unsigned js = d0 - (unsigned)is;
     for (unsigned ds = d0; ds < d1; ds += W) {
@@ -1894,7 +1883,6 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
         js = de - (unsigned)ie;
         is = ie;
     }
-    }   // next chunk
 }
 
 // ===========================================================================

@@ -1930,7 +1930,9 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // Without / walk at the lowest throughout / by thirds: R-MAT 2^17 x 16 at N = 9 / 16 / 40 / 64 / 100 30.2 / 27.1 / 44.1 / 48.5 / 82.2,
 // 28.8 / 25.7 / 42.1 / 47.0 / 81.9, 27.9 / 25.2 / 40.2 / 48.0 / 80.9 us; 2^18 x 32 at N = 20 / 41 96 / 144, 95 / 143, 89.7 / 134.7 us.  Chunks of
 // kPacedFrom entries or fewer have nothing to make up (2^13 x 16 at N = 100 20.0, 20.1, 20.4 us); without statistics on a
-// 27-point stencil, 61^3 at N = 64, the walk's lines leave the L1 earlier (104.5, 105.6, 106.8 us).
+// 27-point stencil, 61^3 at N = 64, the walk's lines leave the L1 earlier (104.5, 105.6, 106.8 us).  Where a launch does not fill the
+// SIMDs the priorities do not pay for themselves: without / with them R-MAT 2^12 x 4 at N = 120 15.1 / 15.6 us, 2^13 x 16 at N = 100
+// 18.4 / 18.7 us, 20 001 lognormal rows of 10 at N = 32 8.8 / 9.05 us.
 constexpr int kRunBlock = 512;       // entries per block
 constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
 constexpr unsigned kPacedFrom = 256;
@@ -2220,10 +2222,14 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
         // a run that starts inside a row: the first row end it meets is finished after the walk
         bool pend = p0 == 0u ? true : ((bits[(p0 - 1u) >> 5] >> ((p0 - 1u) & 31u)) & 1u) == 0u;
         bool closed = false;
-        unsigned pace = 4u;
+        unsigned until = 0u;                                // where the next priority begins
         for (unsigned s0 = 0; s0 < U; s0 += B) {
-            const unsigned at = done + s0 * R, behind = at < third ? 2u : at < 2u * third ? 1u : 0u;
-            if (behind != pace) { pace = behind; set_wave_priority(pace); }
+            const unsigned at = done + s0 * R;
+            if (at >= until) {
+                const unsigned behind = at < third ? 2u : at < 2u * third ? 1u : 0u;
+                until = behind == 2u ? third : behind == 1u ? 2u * third : ~0u;
+                set_wave_priority(behind);
+            }
             const unsigned p = p0 + s0;
             float x[B][4], a[B];
 #pragma unroll

@@ -323,8 +323,8 @@ inline int rs_sr_split_log2(const Problem& p, int logG) {
 // neighbours' walks find their lines in the L1 while they are at it, and what there is to wait for are the streams.  Staging
 // level with the walk / first: 262 144 rows of 64 uniform columns at N = 1 / 2 / 4 85 / 91 / 103 against 76 / 79 / 93 us,
 // 50 001 Poisson rows of 40 over 8000 columns at N = 4 / 16 13.3 / 15.6 against 11.0 / 13.8 us; 27-point stencil on 81^3 at
-// N = 2 / 4 / 5 / 8 / 12 / 16 / 32 27.6 / 30.3 / 36.5 / 38.4 / 51.0 / 56.4 / 93.5 against 31.2 / 33.2 / 37.5 / 38.7 / 49.8 / 53.9 / 91.1 us.
-// Unknown columns are taken for a band.
+// N = 2 / 4 / 5 / 8 / 12 / 16 / 32 27.6 / 30.3 / 36.5 / 38.4 / 51.0 / 56.4 / 93.5 against
+// 31.2 / 33.2 / 37.5 / 38.7 / 49.8 / 53.9 / 91.1 us. Unknown columns are taken for a band.
 inline bool staging_first(const Problem& p, int logG) { return p.col_span > kBandedSpan || logG >= 2; }
 
 template <int V, bool XBUF, int DEPTH, bool RAGGED>
@@ -435,22 +435,26 @@ int launch_rs_sr(const Problem& p) {
 // ---------------------------------------------------------------- balanced launches
 // Zeroes (scaled form: multiplies by beta) the rows split by the `parts` chunks the main kernel derives
 // (quanta of 2^quantum_log2 items), cut into tiles of 2^tile_log2 items (tile_log2 < 0: not cut further).
-int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{}, int empty_rows = 0) {
+int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{},
+                   int empty_rows = 0) {
     const dim3 grid((unsigned)(((long long)p.M + kBlock - 1) / kBlock));
     const float beta = p.scaled ? p.beta : 0.0f;
     if (queues.starts)
-        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues, empty_rows);
+        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues,
+                    empty_rows);
     else
-        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues, empty_rows);
+        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues,
+                    empty_rows);
     return DGSP_OK;
 }
 
 // How `waves` waves on each XCD share out the items (`lists` times: column blocks that are a grid dimension) with the help of
 // memory of the caller's; nothing if it has none to give.  The prepare launch's first rows clear the counters, so there have to be
 // as many.  Three tenths of a wave's share (`share` items) are its first piece, the rest goes by chunks of 512 items, 1024 from
-// shares of 4096 on: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares 1024 us), at
-// N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).  Powers of two, so that the
-// prepare launch knows rows within a chunk by a shift: 2^19 x 16 at N = 100, scaled, 475.5 -> 473 us, 2^20 x 16 at N = 32 228.7 -> 228.0 us.
+// shares of 4096 on: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares
+// 1024 us), at N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).  Powers of
+// two, so that the prepare launch knows rows within a chunk by a shift: 2^19 x 16 at N = 100, scaled, 475.5 -> 473 us, 2^20 x
+// 16 at N = 32 228.7 -> 228.0 us.
 constexpr double kFirstPiece = 0.3;
 constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
 ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
@@ -549,19 +553,20 @@ inline int hot_shift(int64_t K) {
     while (shift <= kHotShiftMax && (K - 1) >> shift >= 32ll * kHotWords) ++shift;
     return K >= 1 && shift <= kHotShiftMax ? shift : 0;
 }
-// Sampled where the column blocks of nb_sr_run_kernel want it, in the same launch: smaller matrices and shorter rows would gain 8 to 20 % of a
-// product and pay 20 us for it when they are taken over.
+// Sampled where the column blocks of nb_sr_run_kernel want it, in the same launch: smaller matrices and shorter rows would gain
+// 8 to 20 % of a product and pay 20 us for it when they are taken over.
 // Reading hot runs from LDS pays where it saves the caches this many entries, as copying the runs costs every CU 4 to 5 us, and
 // this share of them (hot_columns()): the others bound the product, all the more the more of them miss the L2.  66 matrices with 4
 // to 32 million entries, share, general way -> hot runs:
-//   R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (.31 .25 .19 .16) 90 / 100 / 109 / 111 -> 68 / 83 / 97 / 101 us, 2^20 x 32 (.31 .25 .19 .16) 168 / 181 /
-//   194 / 196 -> 114 / 145 / 169 / 175 us, 2^18 x 32 (.40 .35 .28 .22) 40 / 43 / 46 / 48 -> 31 / 35 / 41 / 44 us, 2^21 x 8 (.27 .19 .16 .11) 108 / 119 /
-//   127 / 136 -> 85 / 106 / 116 / 135 us;
+//   R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 (.31 .25 .19 .16) 90 / 100 / 109 / 111 -> 68 / 83 / 97 / 101 us, 2^20 x 32 (.31 .25
+//   .19 .16) 168 / 181 / 194 / 196 -> 114 / 145 / 169 / 175 us, 2^18 x 32 (.40 .35 .28 .22) 40 / 43 / 46 / 48 ->
+//   31 / 35 / 41 / 44 us, 2^21 x 8 (.27 .19 .16 .11) 108 / 119 / 127 / 136 -> 85 / 106 / 116 / 135 us;
 //   N = 1, uniform columns: 16.8 M entries over 100 000 / 262 144 / 500 000 (.28 .11 .06) 94 / 97 / 98 -> 76 / 90 / 95 us, 4.7 M over
 //   180 000 / 262 144 / 350 000 (.15 .10 .08; 0.73 / 0.49 / 0.37 M of them) 34.5 / 34.6 / 35.4 -> 32.9 / 34.1 / 35.4 us;
-//   the lines, columns K u^p: N = 2 2^20 u^4 (.13) 123 -> 116 us, 1.5 M u^4 (.12) 100 -> 102 us, 3 M u^6 (.11) 141 -> 143 us; N = 3 2^19 u^3
-//   (.11) 131 -> 120 us, 2^20 u^4 (.10) 148 -> 149 us, 2^21 u^6 (.10) 150 -> 153 us; N = 4 2^18 u^4 (.12) 112 -> 99 us, 2^20 u^8 (.09) 115 ->
-//   113 us, 2^20 u^4 (.08) 159 -> 161 us.  Columns as hot as 2^20 u^8 would gain below the lines of N = 2 and 3, too (.12 101 -> 87, .10 111 -> 105 us).
+//   the lines, columns K u^p: N = 2 2^20 u^4 (.128) 123 -> 116 us, 1.5 M u^4 (.121) 46 -> 47 us, 3 M u^6 (.11) 141 -> 143 us;
+//   N = 3 2^19 u^3 (.11) 131 -> 120 us, 2^20 u^4 (.10) 148 -> 149 us, 2^21 u^6 (.10) 150 -> 153 us; N = 4 2^18 u^4 (.12) 112 ->
+//   99 us, 2^20 u^8 (.09) 115 -> 113 us, 2^20 u^4 (.08) 159 -> 161 us.  Columns as hot as 2^20 u^8 would gain below the lines
+//   of N = 2 and 3, too (.12 101 -> 87, .10 111 -> 105 us).
 constexpr double kHotEntriesMin = 0.45e6, kHotShareMin[kHotWidths] = {0.05, 0.12, 0.107, 0.1};
 inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
     return N >= 1 && N <= kHotWidths && s.hot_share[N - 1] >= kHotShareMin[N - 1] &&
@@ -719,10 +724,12 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     // a wave alone takes one batch of its lane groups in about 1 us
     const int snap = snap_rows(p, chunk_groups, 1.0, (double)((kWave >> LOGG) * kRunBatch), lines_per_row(cols.cols_per_block, p.ldx) * col_blocks);
     // Queues instead of equal shares where a chunk is long against what it costs to start one (5 us): from 2048 items a wave and
-    // as many lanes to an entry that the share is 32 768 lane steps.  R-MAT 2^20 x 16 at N = 32 / 41 / 64 / 128 256 / 422 / 507 / 1021 -> 240 /
-    // 405 / 443 / 880 us, 2^20 x 32 at N = 20 / 32 416 / 469 -> 393 / 419 us, 2^20 x 8 at N = 41 257 -> 240 us, 2^18 x 16 at N = 128 201 -> 194 us,
-    // 2^19 x 16 at N = 100 405 -> 398 us; not 2^20 x 16 at N = 16 (170 against 173 to 190 us), 2^19 x 16 at N = 32 (106 / 113 us), 2^18 x 32 at N = 48
-    // (136 / 140 us), nor with few entries a row, whose workgroups are dealt to the XCDs one by one (2^20 x 6 at N = 50 207 / 223 us).
+    // as many lanes to an entry that the share is 32 768 lane steps.  R-MAT 2^20 x 16 at
+    // N = 32 / 41 / 64 / 128 256 / 422 / 507 / 1021 -> 240 / 405 / 443 / 880 us, 2^20 x 32 at N = 20 / 32 416 / 469 ->
+    // 393 / 419 us, 2^20 x 8 at N = 41 257 -> 240 us, 2^18 x 16 at N = 128 201 -> 194 us, 2^19 x 16 at N = 100 405 -> 398 us;
+    // not 2^20 x 16 at N = 16 (170 against 173 to 190 us), 2^19 x 16 at N = 32 (106 / 113 us), 2^18 x 32 at N = 48
+    // (136 / 140 us), nor with few entries a row, whose workgroups are dealt to the XCDs one by one (2^20 x 6 at
+    // N = 50 207 / 223 us).
     ChunkQueues queues{};
     dim3 queue_grid = grid;
     if (XBUF && !snap && p.nnz > 0 && grid.x % kXcd == 0 && p.nnz / p.M >= run_dealt_below(LOGG)) {
@@ -733,13 +740,15 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         const long long share = (p.nnz + (long long)p.M) / parts / waves;
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
+    const unsigned chunks = queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock;
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
+        if (int rc = launch_prepare(p, chunks, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         const auto launch = [&](auto scaled, auto queued) -> int {
-            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, decltype(scaled)::value, XBUF && decltype(queued)::value>), queues.starts ? queue_grid : grid, p.M, p.K, p.N, p.ldx, p.ldy,
-                        p.rowptr, p.colidx, p.vals, p.X, p.Y, cols.cols_per_block, snap, sc, pinned, queues);
+            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, decltype(scaled)::value, XBUF && decltype(queued)::value>),
+                        queues.starts ? queue_grid : grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
+                        cols.cols_per_block, snap, sc, pinned, queues);
             return DGSP_OK;
         };
         if (queues.starts) return p.scaled ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
@@ -855,7 +864,9 @@ int run(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr, con
         algo = library_choice((N <= one_pass) ? DGSP_NB_PR : DGSP_NB_SR, ldy);
     }
 
-    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span, hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share, hints.hot_K == K ? hints.hot_columns : nullptr, hints.more, switches};
+    Problem p{(int)M, (int)N, (int)ldx, (int)ldy, K, nnz, rowptr, colidx, vals, X, Y, (hipStream_t)stream, phase, hints.col_span,
+              hints.cv_row, hints.max_row, nnz >= 0 ? nnz : hints.size, hints.saved_share,
+              hints.hot_K == K ? hints.hot_columns : nullptr, hints.more, switches};
     if (scaling) { p.scaled = true; p.alpha = scaling->alpha; p.beta = scaling->beta; }
     if (hints.chosen) algo = launched_algo(p, algo);
     switch (algo) {
@@ -1306,8 +1317,9 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
     const long long entry_blocks = entries > 0 && K > 0 && colidx ? (entries + kStatChunk - 1) / kStatChunk : 0;
     const long long row_blocks = entry_blocks > 0 ? (M + kBlock - 1) / kBlock : 0;
     const bool apart = row_blocks > 0 && entry_blocks + row_blocks <= std::min(device_info().cus, kStatBlocks);
-    hipLaunchKernelGGL((csr_statistics_kernel<Word>), dim3(apart ? (unsigned)(entry_blocks + row_blocks) : clamp_blocks(pieces, kStatBlocks)), dim3(kBlock), 0, st, (int)M,
-                       (long long)entries, reinterpret_cast<const Word*>(rowptr), K > 0 ? reinterpret_cast<const Word*>(colidx) : nullptr,
+    const dim3 grid(apart ? (unsigned)(entry_blocks + row_blocks) : clamp_blocks(pieces, kStatBlocks));
+    hipLaunchKernelGGL((csr_statistics_kernel<Word>), grid, dim3(kBlock), 0, st, (int)M, (long long)entries,
+                       reinterpret_cast<const Word*>(rowptr), K > 0 ? reinterpret_cast<const Word*>(colidx) : nullptr,
                        rowptr32, colidx32, slot.scratch, slot.host, slot.ticket, apart ? (unsigned)row_blocks : 0u);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     unsigned long long h[kStatResultWords];
@@ -1388,8 +1400,8 @@ int sample_columns(int64_t K, int64_t entries, const int32_t* colidx, uint32_t* 
     if (!g_stat_pool.take(slot, true)) return DGSP_ERR_LAUNCH;
     struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
     unsigned long long* out = slot.host ? slot.host : slot.scratch->result;
-    hipLaunchKernelGGL(column_reuse_kernel, dim3(hot_table ? 1 + kHotWidths : 1), dim3(kReuseThreads), 0, st, (long long)entries, colidx, hot_table,
-                       hot_table ? hot_shift(K) : 0, out, slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
+    hipLaunchKernelGGL(column_reuse_kernel, dim3(hot_table ? 1 + kHotWidths : 1), dim3(kReuseThreads), 0, st, (long long)entries,
+                       colidx, hot_table, hot_table ? hot_shift(K) : 0, out, slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     // a place is given back when nothing is under way in it: all workgroups', whatever became of the first
     bool hot_done = true;

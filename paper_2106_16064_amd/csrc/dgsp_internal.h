@@ -41,7 +41,8 @@ int dgsp_internal_measure_columns(dgsp_internal_stats_t *stats, const int32_t *c
 /* Would a product with these statistics look at the table? */
 int dgsp_internal_wants_hot_columns(const dgsp_internal_stats_t *stats, int64_t N);
 /* Its two halves: distinct columns and columns met once among 16384, 32768, 65536 sampled entries (six counts, of half
- * of the columns; `entries` at least 4096), and the share of entries whose column is not among the last 16384 distinct ones but among the last 32768. */
+ * of the columns; `entries` at least 4096), and the share of entries whose column is not among the last 16384 distinct ones
+ * but among the last 32768. */
 int dgsp_internal_column_reuse(int64_t entries, const int32_t *colidx, uint64_t *counts, void *stream);
 double dgsp_internal_saved_share(const uint64_t *counts);
 /* Dense columns per column block of DGSP_NB_SR at width N. */
@@ -49,8 +50,9 @@ int dgsp_internal_nb_sr_block(const dgsp_internal_stats_t *stats, int64_t N);
 
 /* The public entry points with hints beside the statistics: dgsp_spmm_csr_auto, dgsp_spmm_csr_phase, and
  * dgsp_spmm_csr_ld / _axpby (alpha_beta NULL / two factors). */
-int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t *features, const dgsp_internal_hints_t *hints, const int32_t *rowptr,
-                            const int32_t *colidx, const float *vals, const float *X, float *Y, int *chosen, void *stream);
+int dgsp_internal_spmm_auto(int64_t M, int64_t K, int64_t N, const dgsp_features_t *features, const dgsp_internal_hints_t *hints,
+                            const int32_t *rowptr, const int32_t *colidx, const float *vals, const float *X, float *Y, int *chosen,
+                            void *stream);
 int dgsp_internal_spmm_phase(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
                              const float *vals, const float *X, float *Y, int algo, int phase, const dgsp_features_t *features,
                              const dgsp_internal_hints_t *hints, void *stream);

@@ -451,7 +451,8 @@ constexpr unsigned kQueuePitch = 32;
 struct ChunkQueues {
     unsigned* taken; int* starts;
     unsigned chunks, size_log2, counters, parts_log2, waves, run, helpers;
-    __device__ __forceinline__ unsigned part_from(unsigned part) const { return (chunks * part) >> parts_log2; }      // at most 2^23 chunks, 8 parts
+    // at most 2^23 chunks, 8 parts
+    __device__ __forceinline__ unsigned part_from(unsigned part) const { return (chunks * part) >> parts_log2; }
     __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
     // a number for the piece that chunk c belongs to, different for different pieces
     __device__ __forceinline__ unsigned piece_of(unsigned c) const {
@@ -471,9 +472,9 @@ struct ChunkQueues {
 // QUEUES: the chunks' first rows and the counters are written as well.
 // `empty_rows`: rows without entries are treated alike and the main launch leaves them alone (nb_sr_run_kernel, scaled form).  Half of
 // a power-law graph's rows are such; a wave at the sparse end has hundreds, and their old values were four or more trips to memory
-// per 64 of them, one after the other.  R-MAT 2^17 x 16 at N = 8 / 16 / 40 / 100 29.5 / 41.6 / 74.2 / 153.4 -> 28.0 / 36.9 / 62.0 / 114.5 us,
-// 2^20 x 12 at N = 20 305 -> 263 us.  Plain products write zeros without waiting and keep them where they are (by this launch
-// 2^17 x 16 at N = 16 / 40 23.2 / 40.3 -> 23.9 / 43.1 us).
+// per 64 of them, one after the other.  R-MAT 2^17 x 16 at N = 8 / 16 / 40 / 100 29.5 / 41.6 / 74.2 / 153.4 ->
+// 28.0 / 36.9 / 62.0 / 114.5 us, 2^20 x 12 at N = 20 305 -> 263 us.  Plain products write zeros without waiting and keep them
+// where they are (by this launch 2^17 x 16 at N = 16 / 40 23.2 / 40.3 -> 23.9 / 43.1 us).
 template <bool QUEUES>
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
@@ -497,7 +498,8 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
             // Chunks of one quantum each, unless the caller's entry count was not the matrix's: no divisions (nearly every wave has
             // a row at a chunk's end; with those of part_from() R-MAT 2^20 x 16 at N = 32 / 64 222.7 / 465.6 -> 221.8 / 463.2 us)
             const bool one_each = QUEUES && es.Q == parts;
-            const unsigned c1 = one_each ? first >> quantum_log2 : es.chunk_of(first), c2 = one_each ? last >> quantum_log2 : es.chunk_of(last);
+            const unsigned c1 = one_each ? first >> quantum_log2 : es.chunk_of(first);
+            const unsigned c2 = one_each ? last >> quantum_log2 : es.chunk_of(last);
             if (across) split = c1 != c2;
             if constexpr (QUEUES) split = split && (!across || queues.piece_of(c1) != queues.piece_of(c2));
             if (across && !split && tile_log2 >= 0) {
@@ -544,8 +546,8 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     // The workgroup treats its rows together: they are listed, 2^log_lanes lanes take one, eight of a lane's in flight at a time, so
     // that the loads of the scaled form overlap.  (The long rows of a graph are neighbours and all split: one row after the
     // other in one wave took R-MAT 2^18 x 13 at N = 58 100 of 206 us; with a wave to a row of 8 / 12 columns 2^18 x 6 / 2^17 x 16 in the
-    // scaled form took 33 / 45 instead of 28 / 38 us, with one to a row of 12 / 20 columns plain products on 2^17 x 16 28.3 / 31.6 instead of
-    // 26.5 / 30.6 us.)
+    // scaled form took 33 / 45 instead of 28 / 38 us, with one to a row of 12 / 20 columns plain products on 2^17 x 16
+    // 28.3 / 31.6 instead of 26.5 / 30.6 us.)
     __shared__ int s_rows[kBlock];
     __shared__ int s_count[kWavesPerBlock];
     const int lane = lane_id(), wib = wave_in_block();
@@ -1094,15 +1096,16 @@ struct HotColumns { const unsigned* table; int shift; };
 // HOT (packed X, one to four columns): the runs of X that most entries name are read from LDS.  A gather of scattered columns fetches a
 // 128-byte line from the L2 for four to sixteen bytes of it, and the rate of these lines is what bounds the product (R-MAT 2^20 x 16: 14
 // million of them, 75 us for nothing but the gather).  Where few lines hold many of the entries' columns - the columns of a
-// power-law graph: 53 % of that one's are on 896 of its 32768 lines - every CU copies these lines when it starts, and a bitmap of
+// power-law graph: 55 % of that one's are on 992 of its 32768 lines - every CU copies these lines when it starts, and a bitmap of
 // the lines with a running count per word says for a column whether it is among them and where.  One workgroup of eight
 // waves per CU, so that its LDS holds one table; the lanes that found their column there switch their gather off.
 // R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 68.7 / 87.1 / 102.2 us; 4 / 6 / 12 / 16 waves instead of
-// eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 7
-// million at 4 cycles each and CU: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
+// eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 8.7
+// million of 14.1 by the L2s' counters, streams included: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
 // switched off, and by offset or by execution mask, makes no difference, nor would packing the others into fewer instructions.
 template <int V, int KQ, bool SNAP, bool AXPBY = false, bool SERIAL_SCAN = false, bool HOT = false>
-__global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
+__global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy,
+                                                        const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
@@ -1123,7 +1126,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     const int probe = first_probe(rowptr, M, lane);
     const unsigned nnz = (unsigned)rowptr[M];
-    const ChunkPlan plan(nnz, nnz + (unsigned)M, gridDim.x * kWaves, xcd_contiguous(blockIdx.x, gridDim.x) * kWaves + wib, 6);   // quanta of one wave's width
+    const ChunkPlan plan(nnz, nnz + (unsigned)M, gridDim.x * kWaves, xcd_contiguous(blockIdx.x, gridDim.x) * kWaves + wib,
+                         6);                              // quanta of one wave's width
     const unsigned long long y_elems = dense_bytes(M, ldy, N) / 4ull;
     // V = 8: the lane's second four columns start here (N = 5, 6, 7: at N - 4, overlapping the first four)
     const int second = (V == 8 && N - n0 < 8) ? N - n0 - 4 : 4;
@@ -1928,11 +1932,11 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // Wave priorities (set_wave_priority): searches, staging, row marks and the sums across runs at the highest, so that a wave gets
 // to its gathers; in the walk of a longer chunk the lower the further it has come, so that the waves of a SIMD end together.
 // Without / walk at the lowest throughout / by thirds: R-MAT 2^17 x 16 at N = 9 / 16 / 40 / 64 / 100 30.2 / 27.1 / 44.1 / 48.5 / 82.2,
-// 28.8 / 25.7 / 42.1 / 47.0 / 81.9, 27.9 / 25.2 / 40.2 / 48.0 / 80.9 us; 2^18 x 32 at N = 20 / 41 96 / 144, 95 / 143, 89.7 / 134.7 us.  Chunks of
-// kPacedFrom entries or fewer have nothing to make up (2^13 x 16 at N = 100 20.0, 20.1, 20.4 us); without statistics on a
-// 27-point stencil, 61^3 at N = 64, the walk's lines leave the L1 earlier (104.5, 105.6, 106.8 us).  Where a launch does not fill the
-// SIMDs the priorities do not pay for themselves: without / with them R-MAT 2^12 x 4 at N = 120 15.1 / 15.6 us, 2^13 x 16 at N = 100
-// 18.4 / 18.7 us, 20 001 lognormal rows of 10 at N = 32 8.8 / 9.05 us.
+// 28.8 / 25.7 / 42.1 / 47.0 / 81.9, 27.9 / 25.2 / 40.2 / 48.0 / 80.9 us; 2^18 x 32 at N = 20 / 41 96 / 144, 95 / 143,
+// 89.7 / 134.7 us.  Chunks of kPacedFrom entries or fewer have nothing to make up (2^13 x 16 at N = 100 20.0, 20.1, 20.4 us);
+// without statistics on a 27-point stencil, 61^3 at N = 64, the walk's lines leave the L1 earlier (104.5, 105.6,
+// 106.8 us).  Where a launch does not fill the SIMDs the priorities do not pay for themselves: without / with them R-MAT 2^12 x
+// 4 at N = 120 15.1 / 15.6 us, 2^13 x 16 at N = 100 18.4 / 18.7 us, 20 001 lognormal rows of 10 at N = 32 8.8 / 9.05 us.
 constexpr int kRunBlock = 512;       // entries per block
 constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
 constexpr unsigned kPacedFrom = 256;
@@ -2681,7 +2685,7 @@ __global__ __launch_bounds__(kReuseThreads) void column_reuse_kernel(long long e
                                                                     unsigned long long ticket) {
     constexpr int kWords = (1 << kReuseBucketsLog2) / 16;
     constexpr int kOwn = kWords / kReuseThreads;
-    __shared__ __align__(16) unsigned table[32 * kHotWords];                   // kWords, and words behind for the columns that are not counted
+    __shared__ __align__(16) unsigned table[32 * kHotWords];     // kWords, and words behind for the columns that are not counted
     __shared__ unsigned sums[kReuseLevels][2];
     __shared__ unsigned waves[kReuseThreads / kWave];
     static_assert(kWords + kWave <= 32 * kHotWords, "the table holds both");

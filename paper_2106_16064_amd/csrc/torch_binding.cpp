@@ -89,7 +89,7 @@ struct CallStream {
 
 CallStream call_stream(c10::hip::HIPStream s) {
     void* handle = s.stream();
-    const bool foreign = handle != nullptr && s.id() == (int64_t)reinterpret_cast<intptr_t>(handle);        // torch names those by their address
+    const bool foreign = handle != nullptr && s.id() == (int64_t)reinterpret_cast<intptr_t>(handle);      // named by their address
     return {handle, foreign ? std::nullopt : std::make_optional(s)};
 }
 
@@ -106,7 +106,8 @@ CallStream as_stream(PyObject* o) {
     if (!THPStream_Check(o)) return {p, std::nullopt};
     const auto* t = reinterpret_cast<THPStream*>(o);
     const c10::Device device(c10::DeviceType::HIP, (c10::DeviceIndex)t->device_index);
-    const CallStream s = call_stream(c10::hip::HIPStream(c10::hip::HIPStream::UNCHECKED, c10::Stream(c10::Stream::UNSAFE, device, t->stream_id)));
+    const c10::Stream named(c10::Stream::UNSAFE, device, t->stream_id);
+    const CallStream s = call_stream(c10::hip::HIPStream(c10::hip::HIPStream::UNCHECKED, named));
     return s.handle == p ? s : CallStream{p, std::nullopt};
 }
 
@@ -193,7 +194,8 @@ private:
 
     // A tensor that the structure carries as an attribute and not as an address among its bytes, which could outlive it.
     void take_hot_columns(PyObject* o) {
-        static PyObject *const columns = PyUnicode_InternFromString("hot_columns"), *const stream = PyUnicode_InternFromString("hot_stream");
+        static PyObject* const columns = PyUnicode_InternFromString("hot_columns");
+        static PyObject* const stream = PyUnicode_InternFromString("hot_stream");
         PyObject *t = PyObject_GetAttr(o, columns), *s = t ? PyObject_GetAttr(o, stream) : nullptr;
         if (t && THPVariable_Check(t)) {
             const at::Tensor& table = THPVariable_Unpack(t);

@@ -567,7 +567,7 @@ inline int hot_shift(int64_t K) {
 //   N = 3 2^19 u^3 (.11) 131 -> 120 us, 2^20 u^4 (.10) 148 -> 149 us, 2^21 u^6 (.10) 150 -> 153 us; N = 4 2^18 u^4 (.12) 112 ->
 //   99 us, 2^20 u^8 (.09) 115 -> 113 us, 2^20 u^4 (.08) 159 -> 161 us.  Columns as hot as 2^20 u^8 would gain below the lines
 //   of N = 2 and 3, too (.12 101 -> 87, .10 111 -> 105 us).
-constexpr double kHotEntriesMin = 0.45e6, kHotShareMin[kHotWidths] = {0.05, 0.12, 0.107, 0.1};
+constexpr double kHotEntriesMin = 0.45e6, kHotShareMin[kHotWidths] = {0.05, 0.123, 0.107, 0.1};
 inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
     return N >= 1 && N <= kHotWidths && s.hot_share[N - 1] >= kHotShareMin[N - 1] &&
            (double)s.features.nnz * s.hot_share[N - 1] >= kHotEntriesMin;

@@ -67,8 +67,9 @@ class MatrixFeatures(Features):
     def __reduce__(self):
         """Without the table, which stays in the memory of its GPU: statistics can be read where there is none."""
         restore, (cls, (attributes, data)) = super().__reduce__()
+        left_out = {"hot_columns_left_out": True} if self.hot_columns is not None else {}
         attributes = {k: v for k, v in attributes.items() if k not in ("hot_columns", "hot_stream")}
-        return restore, (cls, (attributes, data))
+        return restore, (cls, ({**attributes, **left_out}, data))
 
 
 class Thresholds(ctypes.Structure):
@@ -424,9 +425,9 @@ class DeviceCsr:
         return self
 
     def __setstate__(self, state):
-        """Restored from a file or deeply copied: the table of hot runs that its statistics lack is made again."""
+        """Restored from a file: the table of hot runs that its statistics left out is made again."""
         self.__dict__.update(state)
-        if self.colidx.is_cuda and any(self.features.hot_share) and self.features.hot_columns is None:
+        if vars(self.features).pop("hot_columns_left_out", False) and self.colidx.is_cuda:
             (_native or native()).measure_matrix_columns(self.features, self.colidx)
 
     def autotune(self, X, reps=5, Y=None):

@@ -121,7 +121,7 @@ bool on_gpu(const at::Tensor& t) { return t.device().is_cuda() && t.layout() == 
 bool is_array(const at::Tensor& t, at::ScalarType type) { return on_gpu(t) && t.scalar_type() == type && t.is_contiguous(); }
 
 // what Workspace asks
-struct GpuRuntime {
+struct HipRuntime {
     using Stream = hipStream_t;
     static bool capture_status(Stream stream, bool& recording) {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -140,7 +140,7 @@ struct GpuRuntime {
     static void release(void* memory) { c10::hip::HIPCachingAllocator::raw_delete(memory); }
     static void forget_error() { (void)hipGetLastError(); }
 };
-using Workspace = dgsp::Workspace<GpuRuntime>;
+using Workspace = dgsp::Workspace<HipRuntime>;
 
 // would any product look at the table?
 bool wants_hot_columns(const dgsp_internal_stats_t& stats) {
@@ -180,8 +180,8 @@ private:
     const uint32_t* hot_columns(int64_t N, const at::Tensor& X, const CallStream& stream) const {
         if (!hot_.defined() || hot_.device() != X.device() || !dgsp_internal_wants_hot_columns(&value_, N)) return nullptr;
         bool recording = false;
-        if (!GpuRuntime::capture_status(static_cast<hipStream_t>(stream.handle), recording)) {
-            GpuRuntime::forget_error();
+        if (!HipRuntime::capture_status(static_cast<hipStream_t>(stream.handle), recording)) {
+            HipRuntime::forget_error();
             return nullptr;
         }
         if (recording) return nullptr;

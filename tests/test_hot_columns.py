@@ -228,7 +228,11 @@ def test_the_table_stays_with_its_matrix():
     assert bytes(restored) == bytes(f) and restored.hot_columns is None
     again = pickle.loads(pickle.dumps(D))                           # a whole matrix comes back with a table
     assert torch.equal(again.features.hot_columns, f.hot_columns) and bytes(again.features) == bytes(f)
-    assert copy.deepcopy(D).features.hot_columns is f.hot_columns
+    for copied in (copy.copy(D), copy.deepcopy(D)):                 # and copies in the same program share it
+        assert copied.features.hot_columns is f.hot_columns
+    small = dg.DeviceCsr(wl.rmat_csr(14, 24, seed=3))
+    small.features.hot_share[0] = 0.01                              # measured, and not worth a table: nothing is measured again
+    assert copy.copy(small).features.hot_share[0] == pickle.loads(pickle.dumps(small)).features.hot_share[0] == 0.01
     wrong = copy.copy(bare)
     wrong.hot_columns = f.hot_columns[:-1].contiguous()
     for features in (f, bare, wrong, restored, copy.copy(f), dg.Features(**f.as_dict())):

@@ -2567,18 +2567,15 @@ constexpr int kHotSamplePieces = 512, kHotSample = kHotSamplePieces * kWave, kHo
 __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __restrict__ colidx, unsigned* table, int shift,
                                                 unsigned room, unsigned cached, unsigned* bins, unsigned* waves) {
     constexpr int kPerThread = kHotSample / kReuseThreads;
-    __shared__ unsigned s_level[2], s_above[2], s_tied[2], s_met[2][2];       // of the `room` and of the `cached` fullest runs
+    // of the `room` and of the `cached` fullest runs: the count that all but the last have, how many have it and how many have one
+    // less, the entries in runs with more than it and with just it
+    __shared__ unsigned s_level[2], s_above[2], s_tied[2], s_sure[2], s_shared[2];
     const int t = (int)threadIdx.x;
     unsigned c[kPerThread];
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q)
         c[q] = (unsigned)colidx[(entries - kWave) / (kHotSamplePieces - 1) * (uniform(t / kWave) * kPerThread + q) + lane_id()];
     for (int i = 0; i < 8; ++i) reinterpret_cast<uint4*>(bins)[t + i * kReuseThreads] = make_uint4(0u, 0u, 0u, 0u);
-    if (t < 2) {
-        s_level[t] = (unsigned)kHotLevels;                       // even the last level has too many
-        s_above[t] = 0u;
-        s_met[t][0] = s_met[t][1] = 0u;
-    }
     __syncthreads();
     const auto place = [](unsigned word, unsigned bit) { return word * 32u + ((bit + word) & 31u); };
 #pragma unroll
@@ -2618,18 +2615,32 @@ __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __
     unsigned total;
     {
         const unsigned level = (unsigned)(kHotLevels - 1 - t), here = levels[level];
-        const unsigned reach = reuse_prefix(here, waves, total) + here;
+        // runs, and their entries in the upper half (the last level's as if they had just that count; neither sum goes beyond kHotSample)
+        const unsigned before = reuse_prefix(here | (level * here) << 16, waves, total);
+        const unsigned reach = (before & 0xffffu) + here, more = before >> 16;
+        const unsigned up_to = (total >> 16) - more;                 // entries at this level and below
+        const bool last = t == 0;                                    // all entries that are not below it are at the last level
+        const unsigned in_last = kHotSample - (up_to - level * here);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const unsigned places = k == 0 ? room : cached;
-            if (level >= 1u && reach <= places && (level == 1u || reach + levels[level - 1u] > places)) {
+            const unsigned below = level > 0u ? levels[level - 1u] : 0u;
+            if (level >= 1u && reach <= places && (level == 1u || reach + below > places)) {
                 s_level[k] = level;
                 s_above[k] = reach;
+                s_tied[k] = below;
+                s_sure[k] = last ? in_last : kHotSample - up_to;
+                s_shared[k] = last ? 0u : level * here;
+            } else if (last && reach > places) {                     // even the last level has too many: `places` of them
+                s_level[k] = (unsigned)kHotLevels;
+                s_above[k] = 1u;
+                s_tied[k] = here - 1u;
+                s_sure[k] = 0u;
+                s_shared[k] = in_last;
             }
         }
     }
     __syncthreads();
-    if (t < 2) s_tied[t] = levels[s_level[t] - 1u];
     // its runs, and of those one below the first ones, as many as there are places left
     const unsigned lowest = s_level[0], left = lowest > 1u ? room - s_above[0] : 0u;
     unsigned mask = 0, below = 0;
@@ -2647,28 +2658,15 @@ __device__ __forceinline__ unsigned hot_columns(long long entries, const int* __
 #pragma unroll
     for (unsigned b = 0; b < 32; ++b)
         if ((mask >> b) & 1u) list[at++] = 32u * (unsigned)t + b;
-    // Without one of its entries a run still has the count that was asked for (the first sum), or it shares the places that are
-    // left with those one below (the second)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const unsigned level = s_level[k];
-        unsigned sure = 0, shared = 0;
-#pragma unroll
-        for (unsigned b = 0; b < 32; ++b) {
-            sure += level < (unsigned)kHotLevels && n[b] > level ? n[b] : 0u;
-            shared += (level < (unsigned)kHotLevels ? n[b] == level : n[b] + 1u >= level) ? n[b] : 0u;
-        }
-        if (sure) atomicAdd(&s_met[k][0], sure);
-        if (shared) atomicAdd(&s_met[k][1], shared);
-    }
     __syncthreads();
     stat_store(reinterpret_cast<int*>(table) + 2 * kHotWords + t, (int)((unsigned)t < hot ? list[t] : kNoRow));
     stores_done();
     __syncthreads();
+    // Without one of its entries a run still has the count that was asked for, or it shares the places that are left with those
+    // one below.
     const auto would_be_met = [&](int k, unsigned places) {
-        const unsigned level = s_level[k];
-        const float share = level == 1u ? 0.0f : (float)(places - s_above[k] + 1u) / (float)(s_tied[k] + 1u);
-        return (float)s_met[k][0] + share * (float)s_met[k][1];
+        const float share = s_level[k] == 1u ? 0.0f : (float)(places - s_above[k] + 1u) / (float)(s_tied[k] + 1u);
+        return (float)s_sure[k] + share * (float)s_shared[k];
     };
     const float saved = would_be_met(0, room) - would_be_met(1, cached);
     return saved > 0.0f ? (unsigned)(saved + 0.5f) : 0u;

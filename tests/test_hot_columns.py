@@ -127,7 +127,7 @@ def test_statistics_are_saved_without_the_table():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K, law", [(262_144, 1.0), (500_000, 1.0), (1 << 20, 3.0), (3_000_001, (60, 0.3))])
+@pytest.mark.parametrize("K, law", [(262_144, 1.0), (500_000, 1.0), (1 << 20, 3.0), (3_000_001, (60, 0.3)), (3_000_001, (20, 1.0))])
 def test_the_share_is_the_matrix_s_and_not_the_sample_s(K, law):
     """The runs are those that the sample met most often, by luck among other things: what they save is counted over all entries here.
     The sample's share is off by the square root of p (1 - p) / n; five times that."""

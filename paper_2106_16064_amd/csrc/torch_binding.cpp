@@ -362,9 +362,13 @@ void measure_columns(Measured& m, const at::Tensor& colidx, void* stream) {
     const auto* columns = static_cast<const int32_t*>(ptr(colidx));
     uint32_t* table = nullptr;
     if (const int64_t bytes = dgsp_internal_hot_columns_bytes(&m.stats)) {
-        m.hot_columns = at::empty({bytes / 4}, colidx.options());
-        m.hot_stream = c10::hip::getCurrentHIPStream(colidx.device().index()).stream();
-        table = static_cast<uint32_t*>(m.hot_columns.data_ptr());
+        try {
+            m.hot_columns = at::empty({bytes / 4}, colidx.options());
+            m.hot_stream = c10::hip::getCurrentHIPStream(colidx.device().index()).stream();
+            table = static_cast<uint32_t*>(m.hot_columns.data_ptr());
+        } catch (const c10::OutOfMemoryError&) {                                // no table: the general way
+            HipRuntime::forget_error();
+        }
     }
     const int rc = unlocked([&] { return dgsp_internal_measure_columns(&m.stats, columns, table, stream); });
     if (rc != DGSP_OK) m.stats = dgsp_internal_stats_t{m.stats.features};       // not measured: the general way

@@ -311,6 +311,32 @@ def test_the_table_s_memory_is_not_reused_under_a_product_on_another_stream(by_a
 
 
 @pytest.mark.gpu
+def test_a_matrix_without_memory_for_a_table():
+    """Arrays in the library's types are taken over without an allocation: where there is no memory for a table there is none."""
+    import torch
+    A = matrix(*CASES[0])
+    D, arrays = device_matrix(A)
+    X, Y = torch.randn(A.K, 1, device="cuda"), torch.empty(A.M, 1, device="cuda")
+    want = D.spmm(X)
+    assert D.features.hot_columns is not None
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    print("[case] hot runs: no memory for the table", flush=True)
+    torch.cuda.set_per_process_memory_fraction(0.0)
+    try:
+        rest = []
+        with pytest.raises(torch.OutOfMemoryError):
+            while len(rest) < 100_000:
+                rest.append(torch.empty(4 * TABLE, dtype=torch.int32, device="cuda"))
+        bare = dg.DeviceCsr.from_device(A.M, A.K, *arrays)
+        assert bare.features.hot_columns is None and bare.features.saved_share == D.features.saved_share
+        bare.spmm(X, Y=Y)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert (Y - want).abs().max() <= 1e-5 * want.abs().max()
+
+
+@pytest.mark.gpu
 def test_streams_that_torch_does_not_know():
     """The allocator cannot be told of them for good: products go without the table, unless its memory is that stream's own."""
     import torch

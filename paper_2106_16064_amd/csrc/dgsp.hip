@@ -7,8 +7,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <atomic>
 #include <map>
 #include <mutex>
+#include <random>
 #include <type_traits>
 #include <utility>
 
@@ -478,6 +480,18 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
     return q;
 }
 
+// Words by which the waves of `chunks` chunks agree on the rows they share, in memory of the call's; none if it has none to give
+// (the prepare launch clears these rows then).  Counted per process from a random number on, `call` is even.
+RowSharing make_sharing(const Problem& p, size_t chunks) {
+    static std::atomic<RowWord> calls{[] {
+        std::random_device device;
+        return ((RowWord)device() << 32 | device()) & ~1ull;
+    }()};
+    if (!p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0) return RowSharing{nullptr, 0};
+    void* mem = p.more->workspace(p.more->context, chunks * sizeof(RowWord));
+    return RowSharing{static_cast<RowWord*>(mem), mem ? calls.fetch_add(2, std::memory_order_relaxed) : 0};
+}
+
 // Blocks of the grid that shares the nnz + M merge-path items of a balanced kernel, `tile` items per
 // tile.  The gathers of a CU go through one L1 whose capacity for outstanding misses bounds them,
 // whatever the number of waves, so CUs must finish together: the grid is a whole multiple of the CU
@@ -581,13 +595,14 @@ int launch_nb_pr_hot(const Problem& p) {
     const dim3 grid((unsigned)device_info().cus);
     constexpr int kGroups = kHotThreads / kBlock;                   // workgroups of the usual size in one of this kernel
     const bool snap = snap_rows(p, grid.x * kGroups, 0.1, 128.0, 1.0);
+    const unsigned chunks = grid.x * kGroups * kWavesPerBlock;
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, grid.x * kGroups * kWavesPerBlock, 6, -1)) return rc;
+        if (int rc = launch_prepare(p, chunks, 6, -1)) return rc;
     if (p.phase == DGSP_PHASE_PREPARE) return DGSP_OK;
     const Scaling sc{p.alpha, p.beta};
     const auto launch = [&](auto whole, auto scaled) -> int {
         DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, false, true>), grid, kHotThreads, p.M,
-                            p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, hot);
+                            p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, RowSharing{}, hot);
         return DGSP_OK;
     };
     if (p.scaled) return snap ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
@@ -611,35 +626,41 @@ int launch_nb_pr_v(const Problem& p) {
     const bool banded_x = banded(p) && !forced_blocks;
     const bool tiled = !kNbPrStreams<V> || (p.switches & DGSP_ABL_ITEM_TILES) != 0 ||
                        (!forced_blocks && (p.nnz < kNbPrStreamNnzMin || banded_x));   // unknown entry count (-1): tiles
-    int resident = resident_blocks_per_cu(nb_pr_tiled_kernel<V, KQ>);
+    int resident = resident_blocks_per_cu(nb_pr_tiled_kernel<V, KQ, false, false>);
     if constexpr (kNbPrStreams<V>) { if (!tiled) resident = resident_blocks_per_cu(nb_pr_kernel<V, KQ, false>); }
     const bool few_waves = banded_x && V <= 3;
     const dim3 grid(balanced_blocks(p, tile, resident, true, 1, few_waves ? 2 : 0), col_groups);
     // a wave alone takes 512 entries in about 4 us
     const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
-    if (p.phase != DGSP_PHASE_MAIN && !snap)
+    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups);
+    if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
+        const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         if (tiled) {
-            if (p.scaled)
-                DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                            p.Y, snap, Scaling{p.alpha, p.beta});
-            else
-                DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, snap);
+            const auto launch = [&](auto scaled, auto shares) -> int {
+                DGSP_LAUNCH((nb_pr_tiled_kernel<V, KQ, decltype(scaled)::value, decltype(shares)::value>), grid, p.M, p.K, p.N, p.ldx,
+                            p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, snap, sc, sharing);
+                return DGSP_OK;
+            };
+            if (sharing.words) return p.scaled ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+            return p.scaled ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
         } else if constexpr (kNbPrStreams<V>) {
             const auto launch = [&](auto whole) -> int {
                 constexpr bool kSnap = decltype(whole)::value;
                 if constexpr (V <= 2 && !kSnap) {
                     if (p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) {
-                        DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                        DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
+                                    p.Y, sc, sharing);
                         return DGSP_OK;
                     }
                 }
                 if (p.scaled)
                     DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                                p.Y, Scaling{p.alpha, p.beta});
+                                p.Y, sc, sharing);
                 else
-                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y);
+                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc,
+                                sharing);
                 return DGSP_OK;
             };
             return snap ? launch(std::true_type{}) : launch(std::false_type{});
@@ -741,18 +762,23 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
     const unsigned chunks = queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock;
-    if (p.phase != DGSP_PHASE_MAIN && !snap)
+    RowSharing sharing{};
+    if (!snap && !p.scaled && !queues.starts) sharing = make_sharing(p, (size_t)chunks * col_blocks);
+    if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, chunks, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
-        const auto launch = [&](auto scaled, auto queued) -> int {
-            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, decltype(scaled)::value, XBUF && decltype(queued)::value>),
+        const auto launch = [&](auto scaled, auto queued, auto shares) -> int {
+            DGSP_LAUNCH((nb_sr_run_kernel<LOGG, XBUF, decltype(scaled)::value, XBUF && decltype(queued)::value, decltype(shares)::value>),
                         queues.starts ? queue_grid : grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y,
-                        cols.cols_per_block, snap, sc, pinned, queues);
+                        cols.cols_per_block, snap, sc, pinned, queues, sharing);
             return DGSP_OK;
         };
-        if (queues.starts) return p.scaled ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
-        return p.scaled ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
+        if (queues.starts) return p.scaled ? launch(yes, yes, no) : launch(no, yes, no);
+        if (sharing.words) return launch(no, no, yes);
+        return p.scaled ? launch(yes, no, no) : launch(no, no, no);
     }
     return DGSP_OK;
 }
@@ -886,11 +912,12 @@ extern "C" int dgsp_spmm_csr(int64_t M, int64_t K, int64_t N, const int32_t* row
     return run(M, K, N, -1, rowptr, colidx, vals, X, Y, algo, stream);
 }
 
-extern "C" int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t capacity, const int32_t* rowptr, const int32_t* colidx,
-                                      const float* vals, const float* X, float* Y, int algo, void* stream) {
-    Hints hints;
+extern "C" int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t nnz, int64_t capacity, const int32_t* rowptr,
+                                      const int32_t* colidx, const float* vals, const float* X, float* Y, int algo,
+                                      const dgsp_internal_hints_t* more, void* stream) {
+    Hints hints(nullptr, more);
     hints.size = capacity;
-    return run(M, K, N, -1, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
+    return run(M, K, N, nnz < 0 ? -1 : nnz, rowptr, colidx, vals, X, Y, algo, stream, DGSP_PHASE_ALL, hints);
 }
 
 extern "C" int dgsp_spmm_csr_nnz(int64_t M, int64_t K, int64_t N, int64_t nnz, const int32_t* rowptr,

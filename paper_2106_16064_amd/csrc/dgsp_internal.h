@@ -18,8 +18,8 @@ typedef struct {
 
 /* What a product may know and use beyond the public statistics; NULL: nothing.  hot_columns: the table that
  * dgsp_internal_measure_columns wrote for this matrix, on the product's GPU, or NULL.  workspace(context, bytes): device memory on
- * the product's GPU, aligned to 128 bytes, that is this call's until its launches on the product's stream have run; asked for
- * at most once a call, it may return NULL, and the product goes without. */
+ * the product's GPU, aligned to 128 bytes, that is this call's until its launches on the product's stream have run; it may
+ * return NULL, and does for a call that has some already, and the product goes without. */
 typedef struct {
     double saved_share;
     const uint32_t *hot_columns;
@@ -60,9 +60,10 @@ int dgsp_internal_spmm_view(int64_t M, int64_t K, int64_t N, int64_t nnz, const 
                             const float *vals, const float *X, int64_t ldx, float *Y, int64_t ldy, const float *alpha_beta, int algo,
                             const dgsp_features_t *features, const dgsp_internal_hints_t *hints, void *stream);
 
-/* dgsp_spmm_csr with the length of colidx, which bounds the entry count and sizes the launches. */
-int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t capacity, const int32_t *rowptr, const int32_t *colidx,
-                           const float *vals, const float *X, float *Y, int algo, void *stream);
+/* dgsp_spmm_csr (nnz < 0) and dgsp_spmm_csr_nnz with the length of colidx, which bounds the entry count and sizes the launches. */
+int dgsp_internal_spmm_csr(int64_t M, int64_t K, int64_t N, int64_t nnz, int64_t capacity, const int32_t *rowptr,
+                           const int32_t *colidx, const float *vals, const float *X, float *Y, int algo,
+                           const dgsp_internal_hints_t *hints, void *stream);
 
 #ifdef __cplusplus
 }

@@ -17,6 +17,7 @@
 #pragma once
 
 #include "dgsp_device.hpp"
+#include "shared_rows.hpp"
 
 #include <type_traits>
 
@@ -410,10 +411,11 @@ __global__ __launch_bounds__(kBlock) void rs_sr_direct_kernel(int M, int N, int 
 // Rows whose items straddle a chunk boundary (in the sequential kernel: the
 // boundary of a lane group's run) are combined with fp32 atomic adds; the
 // paper does not say how partial rows of different warps meet.  That needs
-// zeros underneath.  A small "prepare" kernel zeroes exactly those rows and no
-// others (in the scaled form of nb_sr_run_kernel also the rows without entries);
-// every other row is written once with a plain store by the chunk that holds its
-// end marker.
+// zeros underneath.  Where the call has memory for it the waves see to them
+// themselves (RowSharing); otherwise a small "prepare" kernel zeroes exactly
+// those rows and no others (in the scaled form of nb_sr_run_kernel also the rows
+// without entries).  Every other row is written once with a plain store by the
+// chunk that holds its end marker.
 
 // The even split of the Q quanta into `parts` chunks: chunk c starts at quantum floor(c * Q / parts),
 // so chunks differ by at most one quantum and the longer ones are spread over the whole list (put
@@ -686,6 +688,79 @@ __device__ __forceinline__ void snap_to_rows(const int* __restrict__ rowptr, int
 
 constexpr unsigned kNoRow = 0xffffffffu;
 
+// Rows whose entries lie in several chunks, without a launch that clears them first (shared_rows.hpp).  `words`: one for each
+// chunk and column group, for the row that starts in it and is open at its end; nullptr: the prepare launch has been there.
+// The prepare launch is two to three dependent trips to memory, 4.8 us, whatever the size.  Here a wave claims its word in front of its
+// searches, which take longer, and its zeros are under way beside its first entries; what is left of the cost is a trip to
+// memory at the first row end of a chunk.  Whole calls, with that launch / without: R-MAT 2^13 x 9 at N = 15 10.2 / 8.6 us, 2^18 x
+// 10 at N = 6 32.0 / 29.5 us, 2^19 x 5 at N = 6, product and gradient 70.7 / 61.8 us, 2^16 x 16 at N = 41 57.1 / 49.6 us,
+// 2^18 x 32 at N = 24 103.2 / 99.5 us.
+struct RowSharing { RowWord* words; RowWord call; };
+
+struct DeviceWords {
+    static __device__ __forceinline__ RowWord load(RowWord* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ void store(RowWord* p, RowWord v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ RowWord exchange(RowWord* p, RowWord v) {
+        return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ bool replace(RowWord* p, RowWord& seen, RowWord v) {
+        return __hip_atomic_compare_exchange_strong(p, &seen, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(1); }
+};
+
+// The wave's earlier stores have reached the place where they were sent.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// A store that waves on all XCDs find once stores_done() is past.
+__device__ __forceinline__ void store_through(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// The rows at the two ends of a chunk whose first item is d0: rows [is, ie) end in it, entries [js, je) lie in it.
+struct ChunkEnds {
+    unsigned head = 0, tail = 0;    // words of row `is` and of row `ie`
+    bool shares_head = false;       // row `is` ends here, started in an earlier chunk and has entries here
+    bool starts_tail = false;       // row `ie` has its first entries here, others in later chunks
+    bool whole_tail = false;        // row `ie` has all its entries here (its end marker is the next chunk's)
+    bool shares_tail = false;       // row `ie` has some of its entries here
+    __device__ __forceinline__ ChunkEnds() {}
+    __device__ __forceinline__ ChunkEnds(const EvenSplit& split, const int* __restrict__ rowptr, int M, unsigned chunk, unsigned d0, int is,
+                                         int ie, unsigned js, unsigned je) {
+        const unsigned h0 = (unsigned)rowptr[is], h1 = (unsigned)rowptr[is < M ? is + 1 : M];
+        const unsigned t0 = (unsigned)rowptr[ie], t1 = (unsigned)rowptr[ie < M ? ie + 1 : M];
+        const bool here = ie < M && je > (t0 > js ? t0 : js), first = (unsigned)ie + t0 >= d0;
+        shares_head = is < ie && (unsigned)is + h0 < d0 && h1 > js;
+        starts_tail = here && first && t1 > je;
+        whole_tail = here && first && t1 <= je;
+        shares_tail = here && !whole_tail;
+        // whatever the row pointers hold, there is such a word
+        const auto word_of = [&](unsigned item) {
+            const unsigned c = split.chunk_of(item);
+            return (unsigned)uniform((int)(c < split.parts ? c : split.parts - 1u));
+        };
+        head = shares_head ? word_of((unsigned)is + h0) : chunk;
+        tail = shares_tail && !starts_tail ? word_of((unsigned)ie + t0) : chunk;
+    }
+};
+
+// Zeros, or the old values times beta, for the parts of a row to be added to (claim_row()): V columns of a lane, the second four of
+// eight `second` columns behind the first.
+template <int V, bool AXPBY>
+__device__ __forceinline__ void clear_row(float* y, Scaling sc, int second = 4) {
+    float old[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && sc.beta != 0.0f ? y[i < 4 ? i : second + i - 4] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < V; ++i) store_through(y + (i < 4 ? i : second + i - 4), AXPBY && sc.beta != 0.0f ? sc.beta * old[i] : 0.0f);
+}
+// The first part of a row (row_has_sum()), times alpha already, on what beta leaves of the old values.
+template <int V, bool AXPBY>
+__device__ __forceinline__ void write_part(float* y, const float (&v)[V], Scaling sc, int second = 4) {
+    float old[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && sc.beta != 0.0f ? y[i < 4 ? i : second + i - 4] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < V; ++i) store_through(y + (i < 4 ? i : second + i - 4), AXPBY && sc.beta != 0.0f ? fmaf(sc.beta, old[i], v[i]) : v[i]);
+}
+
 // ===========================================================================
 // nnz-balanced, parallel reduction: vectorized segment reduction (Section 2.1.1)
 // ===========================================================================
@@ -724,12 +799,12 @@ constexpr unsigned kNoRow = 0xffffffffu;
 // the next tile's loads stay in flight while this tile is reduced.
 // blockIdx.y selects the group of V dense columns (N > V: one pass each).
 
-template <int V, int KQ, bool AXPBY = false>
+template <int V, int KQ, bool AXPBY, bool SHARES>
 __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K, int N, int ldx, int ldy, const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        int snap, Scaling sc = Scaling{1.0f, 0.0f}) {
+                                                        int snap, Scaling sc, RowSharing sharing) {
     constexpr int E = 4 * KQ;
     constexpr int W = kWave * E;
     // accessed 16 bytes at a time: every wave's part starts on a 16-byte boundary ((W + 4) * 4 and W * V * 4 are multiples of 16)
@@ -755,6 +830,19 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     auto add_to_row = [&](float* y, const float (&v)[V]) {
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
     };
+    auto y_of = [&](int row) { return Y + (size_t)row * ldy + n0; };
+    // rows shared with other waves, where no launch has cleared them; one lane's business
+    RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
+    constexpr bool shares = SHARES;
+    auto give_to_row = [&](unsigned word, float* y, const float (&v)[V]) {
+        if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
+            add_to_row(y, v);
+        } else {
+            write_part<V, AXPBY>(y, v, sc, second);
+            stores_done();
+            publish_part<DeviceWords>(words + word, sharing.call);
+        }
+    };
 
     unsigned d0, d1;
     if (!plan.range(d0, d1)) return;
@@ -779,7 +867,17 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     unsigned js;                                            // entries consumed before my chunk
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
     bool first_split = false;
-    if (snap) {
+    ChunkEnds ends;
+    RowWord found = 0;
+    if constexpr (shares) {
+        int ie1;
+        if (lane == 0) found = claim_row<DeviceWords>(words + plan.wave, sharing.call);
+        wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
+        js = d0 - (unsigned)is;
+        first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
+        ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js, d1 - (unsigned)ie1);
+        if (lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<V, AXPBY>(y_of(ie1), sc, second);
+    } else if (snap) {
         int ie1; unsigned je1;
         wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
         snap_to_rows(rowptr, M, d0, d1, is, ie1, js, je1);
@@ -828,6 +926,10 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     load_row_bounds(is, true, w_unused, wA);
     load_entries(js, true, cA, aA);
     unsigned ds = d0;
+    if (shares) {                                          // the zeros have been under way as long as the entries
+        stores_done();
+        if (lane == 0) publish_start<DeviceWords>(words + plan.wave, sharing.call, found);
+    }
 
     // The first 64 row results of a tile are stored one tile later, after the next tile's loads have been issued:
     // the memory pipeline retires loads and stores in issue order, so a store in front of the gathers would put
@@ -1002,7 +1104,10 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 #pragma unroll
                     for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // an added sum lands on beta * Y (prepare)
                 }
-                if (live && shared) add_to_row(Y + (size_t)(is + t) * ldy + n0, val);
+                if (live && shared) {
+                    if (!shares) add_to_row(y_of(is + t), val);
+                    else if (ends.shares_head) give_to_row(ends.head, y_of(is + t), val);
+                }
             };
             write_rows(0);
             if constexpr (AXPBY) {
@@ -1043,6 +1148,19 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 
     store_pending();                                       // the last tile's rows
     // the row still open at the end of my chunk is finished by another wave
+    if (shares) {
+        if (lane == 0 && ends.whole_tail) {
+            if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
+            store_vec_dword_aligned<V>(y_of(is), carry, second);
+        } else if (lane == 0 && ends.shares_tail) {
+            if constexpr (AXPBY) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
+            }
+            give_to_row(ends.tail, y_of(is), carry);
+        }
+        return;
+    }
     bool any = false;
 #pragma unroll
     for (int i = 0; i < V; ++i) any |= carry[i] != 0.0f;
@@ -1050,7 +1168,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 #pragma unroll
         for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
     }
-    if (any && lane == 0 && is < M) add_to_row(Y + (size_t)is * ldy + n0, carry);
+    if (any && lane == 0 && is < M) add_to_row(y_of(is), carry);
 }
 
 // ===========================================================================
@@ -1109,7 +1227,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        Scaling sc = Scaling{1.0f, 0.0f}, HotColumns hot = HotColumns{nullptr, 0}) {
+                                                        Scaling sc, RowSharing sharing, HotColumns hot = HotColumns{nullptr, 0}) {
     constexpr int E = 4 * KQ;
     constexpr int W = kWave * E;
     constexpr int kWaves = HOT ? kHotThreads / kWave : kWavesPerBlock;
@@ -1134,6 +1252,19 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     auto add_to_row = [&](float* y, const float (&v)[V]) {
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
+    };
+    auto y_of = [&](int row) { return Y + (size_t)row * ldy + n0; };
+    // rows shared with other waves, where no launch has cleared them; one lane's business
+    RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
+    const bool shares = !SNAP && !HOT && sharing.words != nullptr;
+    auto give_to_row = [&](unsigned word, float* y, const float (&v)[V]) {
+        if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
+            add_to_row(y, v);
+        } else {
+            write_part<V, AXPBY>(y, v, sc, second);
+            stores_done();
+            publish_part<DeviceWords>(words + word, sharing.call);
+        }
     };
 
     unsigned d0, d1;
@@ -1189,6 +1320,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // my chunk: rows [is, ie1) end in it, entries [js0, je1) lie in it
     int is = 0, ie1 = 0;
     bool idle = !any_items || nnz == 0;                  // HOT: such a wave has an empty chunk and goes along up to the barrier
+    RowWord found = 0;
+    if (shares && !idle && lane == 0) found = claim_row<DeviceWords>(words + plan.wave, sharing.call);
     if (!idle) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
     // nothing stored: every item is a row end; my rows are [d0, d1)
     const auto rows_without_entries = [&] {
@@ -1221,6 +1354,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
     const int r_first = is;
     const bool first_split = !SNAP && is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
+    ChunkEnds ends;
+    if (shares && !idle) ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
 
     // entries of block k of my chunk (lane l: entries 64 e + l of the block); nothing past the chunk's last entry
     // One descriptor pair for the whole chunk (a wave's share of a matrix the library takes stays far below the
@@ -1321,6 +1456,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     int c[E]; float a[E], x[E][V];                        // the block whose gathers are in flight
     int lc[E]; float la[E];                               // landing registers of the next block's entries
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
+    if (shares && !idle && lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<V, AXPBY>(y_of(ie1), sc, second);
     load_entries(0, c, a);
     load_row_ends(is, is < ie1, w_end);
     if constexpr (HOT) load_hot();
@@ -1331,6 +1467,10 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             if (nnz == 0) rows_without_entries();
             return;
         }
+    }
+    if (shares) {                                         // the zeros have been under way as long as the entries
+        stores_done();
+        if (lane == 0) publish_start<DeviceWords>(words + plan.wave, sharing.call, found);
     }
     gather(0, c, x);
 
@@ -1504,7 +1644,10 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 #pragma unroll
                     for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // an added sum lands on beta * Y (prepare)
                 }
-                if (live && shared) add_to_row(Y + (size_t)(is + t) * ldy + n0, val);
+                if (live && shared) {
+                    if (!shares) add_to_row(y_of(is + t), val);
+                    else if (ends.shares_head) give_to_row(ends.head, y_of(is + t), val);
+                }
             };
             write_rows(0);
             if constexpr (AXPBY) {
@@ -1579,6 +1722,19 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 
     store_pending();                                       // the last step's rows
     // the row still open at the end of my chunk is finished by another wave
+    if (shares) {
+        if (lane == 0 && ends.whole_tail) {
+            if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
+            store_vec_dword_aligned<V>(y_of(is), carry, second);
+        } else if (lane == 0 && ends.shares_tail) {
+            if constexpr (AXPBY) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
+            }
+            give_to_row(ends.tail, y_of(is), carry);
+        }
+        return;
+    }
     bool any = false;
 #pragma unroll
     for (int i = 0; i < V; ++i) any |= carry[i] != 0.0f;
@@ -1586,7 +1742,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
 #pragma unroll
         for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
     }
-    if (any && lane == 0 && is < M) add_to_row(Y + (size_t)is * ldy + n0, carry);
+    if (any && lane == 0 && is < M) add_to_row(y_of(is), carry);
 }
 
 // ===========================================================================
@@ -1914,7 +2070,7 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 //
 // SNAP (host: the longest row is short against a wave's share): a row belongs wholly to the chunk that holds its
 // first item, so nothing is added to memory, the prepare launch falls away and the result is the same from run to
-// run.  Otherwise rows that cross a chunk end are added with atomics to what the prepare launch left.
+// run.  Otherwise rows that cross a chunk end are added with atomics to zeros (RowSharing) or to what the prepare launch left.
 //
 // When N is no multiple of four the last lane's window ends at N and overlaps its neighbour's: plain stores may repeat
 // the shared columns (same bits), scaled stores and atomic adds leave them to the neighbour.
@@ -1955,12 +2111,12 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
 // entries per row below which neighbouring chunks go to different XCDs
 __host__ __device__ constexpr int run_dealt_below(int log_lanes) { return log_lanes >= 5 ? 8 : 6; }
 
-template <int LOGG, bool XBUF, bool AXPBY, bool QUEUED = false>
-__global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
+template <int LOGG, bool XBUF, bool AXPBY, bool QUEUED = false, bool SHARES = false>
+__global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
                                                            const int* __restrict__ rowptr, const int* __restrict__ colidx,
                                                            const float* __restrict__ vals, const float* __restrict__ X,
                                                            float* __restrict__ Y, int cols_per_block, int snap, Scaling sc,
-                                                           unsigned pinned_blocks, ChunkQueues queues) {
+                                                           unsigned pinned_blocks, ChunkQueues queues, RowSharing sharing) {
     constexpr int W = kRunBlock, E = W / kWave, B = kRunBatch;
     constexpr int G = 1 << LOGG, R = kWave / G;
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
@@ -2039,6 +2195,12 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
         if constexpr (QUEUED) continue; else return;
     }
     int is, ie;
+    // rows shared with other waves, where no launch has cleared them
+    RowWord* const words = sharing.words + (size_t)col_block * share.parts;
+    constexpr bool shares = SHARES;
+    static_assert(!SHARES || (!QUEUED && !AXPBY), "queues and the scaled form have their prepare launch");
+    RowWord found = 0;
+    if (shares && lane == 0) found = claim_row<DeviceWords>(words + chunk, sharing.call);
     if constexpr (QUEUED) {
         is = queues.starts[chunk];
         ie = queues.starts[chunk_end];
@@ -2057,6 +2219,8 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
     is = uniform(is); ie = uniform(ie);
     js = (unsigned)uniform((int)js); je = (unsigned)uniform((int)je);
     const int r_first = first_split ? is : -1;
+    ChunkEnds ends;
+    if (shares) ends = ChunkEnds(share, rowptr, M, chunk, d0, is, ie, js, je);
     const unsigned n_ent = je - js;
     const unsigned long long chunk_bytes = (unsigned long long)n_ent * 4ull;
     const __amdgpu_buffer_rsrc_t rc = make_buffer(colidx + js, chunk_bytes);
@@ -2121,9 +2285,30 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
             if (i >= mine.skip) unsafeAtomicAdd(y + i, AXPBY ? sc.alpha * v[i] : v[i]);
     };
 
+    // all lanes that hold columns of a row shared with other waves
+    auto give_to_row = [&](unsigned word, int row, bool lanes, const float (&v)[4]) {
+        bool sum = false;
+        if (lane == 0) sum = row_has_sum<DeviceWords>(words + word, sharing.call);
+        if (uniform(sum ? 1 : 0) != 0) {
+            if (lanes) add_row(row, v);
+        } else {
+            if (lanes) write_part<4, false>(y_at(row), v, sc);
+            stores_done();
+            if (lane == 0) publish_part<DeviceWords>(words + word, sharing.call);
+        }
+    };
+
+    if (shares && ends.starts_tail) {
+        const bool clear = uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0;       // as lane 0 found it
+        if (clear && g == 0 && col_ok) clear_row<4, false>(y_at(ie), sc);
+    }
     unsigned w_start, w_end;
     load_window(is, w_start, w_end);
     load_entries(0);
+    if (shares) {                                       // the zeros have been under way as long as the entries
+        stores_done();
+        if (lane == 0) publish_start<DeviceWords>(words + chunk, sharing.call, found);
+    }
 
     float carry[4] = {0.0f, 0.0f, 0.0f, 0.0f};          // sum of the row that is open at the block's start (every group: its columns)
     unsigned done = 0;                                  // entries before the block
@@ -2300,16 +2485,24 @@ __global__ __launch_bounds__(kBlock, QUEUED ? 4 : 1) void nb_sr_run_kernel(int M
             carry[i] = __shfl(v[i], kWave - G + gl);
         }
         const bool starts_open = p0 == 0u ? true : ((bits[(p0 - 1u) >> 5] >> ((p0 - 1u) & 31u)) & 1u) == 0u;
+        bool give = false;
         if (closed && starts_open && col_ok) {
             const int row = rows[k0];
 #pragma unroll
             for (int i = 0; i < 4; ++i) in[i] += head[i];
-            if (row == r_first) add_row(row, in); else write_row(row, in);
+            if (row != r_first) write_row(row, in); else if (shares) give = true; else add_row(row, in);
         }
+        if (shares && __ballot(give) != 0ull) give_to_row(ends.head, r_first, give, in);
         done = to;
     } while (done < n_ent);
     // the row still open at the end of my chunk is finished by another wave
-    if (!snap && ie < M) {
+    if (shares) {
+        if (ends.whole_tail) {
+            if (g == 0 && col_ok) write_row(ie, carry);
+        } else if (ends.shares_tail) {
+            give_to_row(ends.tail, ie, g == 0 && col_ok, carry);
+        }
+    } else if (!snap && ie < M) {
         bool any = false;
 #pragma unroll
         for (int i = 0; i < 4; ++i) any |= carry[i] != 0.0f;
@@ -2349,7 +2542,6 @@ struct StatScratch {
 __device__ __forceinline__ void stat_store(unsigned long long* p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // Stores of the 32-bit arrays, one or two entries (8-byte aligned): written through the XCD's L2, so that kernels on other
 // streams, on any XCD, find them once stores_done() is past.
 __device__ __forceinline__ void stat_store(int* p, int v) {

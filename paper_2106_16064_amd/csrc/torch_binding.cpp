@@ -567,14 +567,15 @@ void packed_product(PyObject* const* extents, PyObject* count, PyObject* const* 
     check_packed(M, K, N, X, Y);
     if (nnz >= 0 && colidx.numel() < nnz) fail("colidx/vals shorter than nnz");
     void* const stream = as_stream(a[6]).handle;
+    Workspace workspace(static_cast<hipStream_t>(stream), X.device().index());
+    const dgsp_internal_hints_t hints = {0.0, nullptr, &Workspace::get, &workspace};
     const auto* rp = static_cast<const int32_t*>(ptr(rowptr));
     const auto* ci = static_cast<const int32_t*>(ptr(colidx));
     const auto* av = static_cast<const float*>(ptr(vals));
     const auto* x = static_cast<const float*>(ptr(X));
     auto* y = static_cast<float*>(ptr(Y));
     const int rc = unlocked([&] {
-        return count ? dgsp_spmm_csr_nnz(M, K, N, nnz, rp, ci, av, x, y, algo, stream)
-                     : dgsp_internal_spmm_csr(M, K, N, colidx.numel(), rp, ci, av, x, y, algo, stream);
+        return dgsp_internal_spmm_csr(M, K, N, count ? nnz : -1, colidx.numel(), rp, ci, av, x, y, algo, &hints, stream);
     });
     check_status(rc, count ? "dgsp_spmm_csr_nnz" : "dgsp_spmm_csr");
 }

@@ -1,0 +1,121 @@
+"""Rows whose entries several waves of a balanced kernel hold, in products without a launch that clears them first: calls that have
+memory for it (RowSharing), against the oracle and against the calls of the C interface, which have none."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_16064_amd import binding as dg
+from paper_2106_16064_amd import workloads as wl
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends"])
+def test_waves_agree_on_a_row(check, tmp_path):
+    exe = tmp_path / "shared_rows_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-o", str(exe), os.path.join(ROOT, "tests", "shared_rows_check.cpp")],
+                   check=True)
+    assert subprocess.run([str(exe), check], timeout=100).returncode == 0
+
+
+def rows_of(lens, K, seed):
+    rng = np.random.default_rng(seed)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    return wl.CsrMatrix(len(lens), K, rowptr, rng.integers(0, K, rowptr[-1]).astype(np.int32),
+                        rng.uniform(-1, 1, rowptr[-1]).astype(np.float32), "rows", {})
+
+
+def one_row():
+    return rows_of([300_001], 5000, 1)
+
+
+def ends_at_every_item():
+    """Rows of 63, 64 and 65 items and their neighbours: a row's last entry, its end marker and the next row's first entry meet the
+    chunks' ends (multiples of 64 items) in every order; long rows between them, empty ones at the ends."""
+    lens = np.concatenate([[0, 0]] + [np.full(120, k) for k in range(60, 68)] + [[5000, 0, 0, 63, 20_000, 0]] +
+                          [np.full(40, k) for k in range(125, 130)] + [[3001], np.zeros(70, int)])
+    return rows_of(lens, 3001, 2)
+
+
+def hubs():
+    """A power-law graph's rows: hubs over many chunks, half of the rows empty; six million entries and more (entry blocks)."""
+    return wl.rmat_csr(17, 56, seed=4)
+
+
+CASES = [("one row", one_row), ("ends", ends_at_every_item), ("hubs", hubs)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name, make", CASES, ids=[c[0] for c in CASES])
+def test_shared_rows(name, make):
+    import torch
+    A = make()
+    D = dg.DeviceCsr(A)
+    arrays = (D.rowptr, D.colidx, D.vals)
+    for N in (1, 2, 3, 4, 5, 8, 16, 41, 130):
+        X = wl.dense_matrix(A.K, N, "normal", seed=N)
+        Y0 = wl.dense_matrix(A.M, N, "uniform", seed=1)
+        ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+        dX = torch.from_numpy(X).cuda()
+        for algo in (dg.NB_PR, dg.NB_SR):
+            print(f"[case] shared rows {name} N={N} algo={algo}", flush=True)
+            Y = torch.full((A.M, N), float("nan"), device="cuda")
+            for call in (lambda: dg.dgsp_spmm_csr(A.M, A.K, N, *arrays, dX, Y, algo),
+                         lambda: dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, *arrays, dX, Y, algo),
+                         lambda: dg.dgsp_spmm_csr_ld(A.M, A.K, N, A.nnz, *arrays, dX, Y, algo)):
+                Y.fill_(float("nan"))
+                call()
+                ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+                assert ok, worst
+            # against rows that the prepare launch has cleared: the same parts, added up in another order
+            before = torch.full((A.M, N), float("nan"), device="cuda")
+            for phase in (dg.PHASE_PREPARE, dg.PHASE_MAIN):
+                dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz, *arrays, dX, before, algo, phase)
+            ok, worst = oracle.within_bound(Y.cpu().numpy(), before.cpu().numpy().astype(np.float64), bnd, 1e-5)
+            assert ok, worst
+            for beta in (0.0, 0.5):                        # 0: the old values are not read
+                Y.copy_(torch.from_numpy(Y0)) if beta else Y.fill_(float("nan"))
+                dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, *arrays, dX, Y, -2.0, beta, algo)
+                ok, worst = oracle.within_bound(Y.cpu().numpy(), -2.0 * ref + beta * Y0, 2.0 * bnd + beta * np.abs(Y0), 1e-5)
+                assert ok, worst
+
+
+@pytest.mark.gpu
+def test_calls_in_flight_together_and_in_a_graph():
+    """Every call has words of its own; a product that is recorded takes the prepare launch, and its replays are right."""
+    import torch
+    A = ends_at_every_item()
+    D = dg.DeviceCsr(A)
+    N = 41
+    X = wl.dense_matrix(A.K, N, "normal", seed=2)
+    ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    dX = torch.from_numpy(X).cuda()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    results = []
+    torch.cuda.synchronize()
+    print("[case] shared rows on four streams", flush=True)
+    for i in range(40):
+        with torch.cuda.stream(streams[i % 4]):
+            Y = torch.full((A.M, N), float("nan"), device="cuda")
+            dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR)
+            results.append(Y)
+    torch.cuda.synchronize()
+    for Y in results:
+        ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+        assert ok, worst
+    print("[case] shared rows while a graph is recorded", flush=True)
+    Y = torch.empty((A.M, N), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR)
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, results[0], dg.NB_SR)
+        torch.cuda.synchronize()
+        for y in (Y, results[0]):
+            ok, worst = oracle.within_bound(y.cpu().numpy(), ref, bnd, 1e-5)
+            assert ok, worst

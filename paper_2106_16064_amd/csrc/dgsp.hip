@@ -435,29 +435,39 @@ int launch_rs_sr(const Problem& p) {
 }
 
 // ---------------------------------------------------------------- balanced launches
+// Two rows a thread where chunks' first rows are wanted and there are enough rows: nearly every wave has a row at a chunk's start and
+// goes through all of the kernel for it, and with 16 waves a SIMD that is what it takes (R-MAT 2^20 x 16 at N = 32 / 128, one / two
+// / four rows a thread 9.5 / 6.8 / 9.1 and 11.8 / 11.2 / 14.0 us, with the zeros a dword at a time).  Fewer rows end later than they save
+// (2^18 x 16 at N = 128 5.9 / 6.9 us, 2^19 x 16 6.1 / 6.1 us); without queues it is two to three trips to memory either way
+// (2^20 x 16 at N = 1 4.9 / 4.8 us, and the product behind it 0.5 us later), and the scaled form's rows without entries want the waves.
+constexpr long long kTwoRowsMin = 1 << 19;
 // Zeroes (scaled form: multiplies by beta) the rows split by the `parts` chunks the main kernel derives
 // (quanta of 2^quantum_log2 items), cut into tiles of 2^tile_log2 items (tile_log2 < 0: not cut further).
 int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{},
                    int empty_rows = 0) {
-    const dim3 grid((unsigned)(((long long)p.M + kBlock - 1) / kBlock));
     const float beta = p.scaled ? p.beta : 0.0f;
-    if (queues.starts)
-        DGSP_LAUNCH(nb_prepare_kernel<true>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues,
-                    empty_rows);
-    else
-        DGSP_LAUNCH(nb_prepare_kernel<false>, grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2, tile_log2, beta, queues,
-                    empty_rows);
-    return DGSP_OK;
+    const auto launch = [&](auto with_queues, auto rows) -> int {
+        constexpr int R = decltype(rows)::value;
+        const dim3 grid((unsigned)(((long long)p.M + kBlock * R - 1) / (kBlock * R)));
+        DGSP_LAUNCH((nb_prepare_kernel<decltype(with_queues)::value, R>), grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2,
+                    tile_log2, beta, queues, empty_rows);
+        return DGSP_OK;
+    };
+    if (queues.starts && p.M >= kTwoRowsMin && !empty_rows) return launch(std::true_type{}, std::integral_constant<int, 2>{});
+    return queues.starts ? launch(std::true_type{}, std::integral_constant<int, 1>{})
+                         : launch(std::false_type{}, std::integral_constant<int, 1>{});
 }
 
 // How `waves` waves on each XCD share out the items (`lists` times: column blocks that are a grid dimension) with the help of
-// memory of the caller's; nothing if it has none to give.  The prepare launch's first rows clear the counters, so there have to be
-// as many.  Three tenths of a wave's share (`share` items) are its first piece, the rest goes by chunks of 512 items, 1024 from
-// shares of 4096 on: R-MAT 2^20 x 16 at N = 128 with 0.3 / 0.6 / 0.8 of the share 884 / 952 / 1018 us (1024 items; equal shares
-// 1024 us), at N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 / 227 us (equal shares 248 us).  Powers of
-// two, so that the prepare launch knows rows within a chunk by a shift: 2^19 x 16 at N = 100, scaled, 475.5 -> 473 us, 2^20 x
-// 16 at N = 32 228.7 -> 228.0 us.
-constexpr double kFirstPiece = 0.3;
+// memory of the caller's; nothing if it has none to give.  About half of a wave's share (`share` items) is its first piece, the rest
+// goes by chunks of 512 items, 1024 from shares of 4096 on.  With 0.3 / 0.5 to 0.6 of the share R-MAT 2^20 x 16 at N = 32 / 64 / 128
+// 227.7 / 440.1 / 872.4 and 225.9 / 440.2 / 868.7 us, 2^20 x 8 at N = 41 240.6 and 237.5 us, 2^19 x 16 at N = 100 397.4 and
+// 390.4 us (0.8 of it at N = 128 1018 us, equal shares 1024 us); N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 /
+// 227 us (equal shares 248 us), and no better with chunks of 1024 first and smaller ones at the end (237 us and more): what a
+// chunk costs beyond its entries, two shared rows and four trips to memory, is more than the ends lie apart.  Powers of two,
+// so that the prepare launch knows rows within a chunk by a shift: 2^19 x 16 at N = 100, scaled, 475.5 -> 473 us, 2^20 x 16 at
+// N = 32 228.7 -> 228.0 us.
+constexpr double kFirstPiece = 0.55;
 constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
 ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
     ChunkQueues q{};
@@ -466,7 +476,7 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
     const long long chunks = (items + (1ll << size_log2) - 1) >> size_log2;
     const unsigned run = (unsigned)((double)(chunks / parts) * kFirstPiece / waves);
     const size_t counters = (size_t)kXcd * lists;
-    if (run == 0 || !p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0 || (size_t)p.M < counters ||
+    if (run == 0 || !p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0 ||
         (chunks << size_log2) > 0xffffffffll) return q;
     const size_t head = counters * kQueuePitch * sizeof(unsigned);
     char* mem = static_cast<char*>(p.more->workspace(p.more->context, head + (size_t)(chunks + 1) * sizeof(int)));
@@ -477,6 +487,8 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
     q.size_log2 = size_log2;
     q.counters = (unsigned)counters;
     q.parts_log2 = (unsigned)__builtin_ctz(parts); q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
+    q.parts_per_chunk = (float)parts / (float)chunks;
+    q.per_run = 1.0f / (float)run;
     return q;
 }
 

@@ -453,15 +453,21 @@ constexpr unsigned kQueuePitch = 32;
 struct ChunkQueues {
     unsigned* taken; int* starts;
     unsigned chunks, size_log2, counters, parts_log2, waves, run, helpers;
+    float parts_per_chunk, per_run;                      // 2^parts_log2 / chunks, 1 / run
     // at most 2^23 chunks, 8 parts
     __device__ __forceinline__ unsigned part_from(unsigned part) const { return (chunks * part) >> parts_log2; }
     __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
-    // a number for the piece that chunk c belongs to, different for different pieces
-    __device__ __forceinline__ unsigned piece_of(unsigned c) const {
-        unsigned part = 0u;
-        while (part + 1u < (1u << parts_log2) && part_from(part + 1u) <= c) ++part;
-        const unsigned from = part_from(part), at = c - from;
-        return at < waves * run ? from + at / run * run : c;
+    // do chunks c1 and c2 >= c1 belong to one piece?  (c2 in a queue: a piece is a chunk; else no multiple of `run` lies behind c1)
+    __device__ __forceinline__ bool one_piece(unsigned c1, unsigned c2) const {
+        unsigned part = (unsigned)((float)c2 * parts_per_chunk);            // one off at most
+        if (part_from(part + 1u) <= c2) ++part;
+        else if (part_from(part) > c2) --part;
+        const unsigned at = c2 - part_from(part);
+        if (at >= waves * run) return c1 == c2;
+        unsigned into = at - (unsigned)((float)at * per_run) * run;         // into the piece: at % run
+        if ((int)into < 0) into += run;
+        else if (into >= run) into -= run;
+        return c2 - c1 <= into;
     }
 };
 
@@ -470,45 +476,78 @@ struct ChunkQueues {
 // The pieces are the `parts` chunks of the even split with quanta of
 // 2^quantum_log2 items, cut further into tiles of 2^tile_log2 items counted
 // from the chunk's start when tile_log2 >= 0.
-// One thread per row for the test (split rows are few: at most two per piece).
+// R rows a thread for the test (split rows are few: at most two per piece); those with a multiple of the quantum among their items
+// go on, one a thread and round.
 // QUEUES: the chunks' first rows and the counters are written as well.
+// Bound by the trips to memory (row bounds, zeros) and, with queues, by its instructions: at M = 2^20 nearly every wave has such a
+// row and a row to clear.  R-MAT 2^20 x 16 at N = 32 / 128 12.2 / 11.8 -> 5.9 / 7.8 us with two rows a thread, the pieces told apart by
+// one look at the second chunk in place of two searches and divisions, and zeros 16 bytes a lane in place of 4.
 // `empty_rows`: rows without entries are treated alike and the main launch leaves them alone (nb_sr_run_kernel, scaled form).  Half of
 // a power-law graph's rows are such; a wave at the sparse end has hundreds, and their old values were four or more trips to memory
 // per 64 of them, one after the other.  R-MAT 2^17 x 16 at N = 8 / 16 / 40 / 100 29.5 / 41.6 / 74.2 / 153.4 ->
 // 28.0 / 36.9 / 62.0 / 114.5 us, 2^20 x 12 at N = 20 305 -> 263 us.  Plain products write zeros without waiting and keep them
 // where they are (by this launch 2^17 x 16 at N = 16 / 40 23.2 / 40.3 -> 23.9 / 43.1 us).
-template <bool QUEUES>
+template <bool QUEUES, int R>
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
                                                              int tile_log2, float beta, ChunkQueues queues, int empty_rows) {
-    const long long row = (long long)blockIdx.x * kBlock + threadIdx.x;
-    const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the row's bounds
-    bool split = false;
-    unsigned c_from = 0, c_to = 0;                                          // chunks that start within the row's items
-    if (row < M) {
-        const unsigned first = (unsigned)row + (unsigned)rowptr[row];       // diagonal of the row's first item
-        const unsigned last = (unsigned)row + (unsigned)rowptr[row + 1];    // diagonal of its end marker
+    const long long row0 = ((long long)blockIdx.x * kBlock + threadIdx.x) * R;
+    const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the rows' bounds
+    unsigned bound[R + 1];
+    if (R == 1 && row0 < M) {
+        bound[0] = (unsigned)rowptr[row0];
+        bound[1] = (unsigned)rowptr[row0 + 1];
+    } else if (R > 1 && row0 + R <= M) {
+        __builtin_memcpy(bound, rowptr + row0, sizeof(bound));
+    } else {
+#pragma unroll
+        for (int k = 0; k <= R; ++k) bound[k] = (unsigned)rowptr[row0 + k < M ? row0 + k : M];
+    }
+    unsigned split = 0, look = 0;                                           // bit k: row row0 + k
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const long long row = row0 + k;
+        const unsigned first = (unsigned)row + bound[k];                    // diagonal of the row's first item
+        const unsigned last = (unsigned)row + bound[k + 1];                 // diagonal of its end marker
         const unsigned before = first - 1u;                                 // wraps for the list's first item: in no quantum of this row
         // An empty row is a single item.  Every chunk and tile starts at a multiple of the quantum, so a row
         // whose items lie inside one quantum cannot be split: most rows stop here, before the divisions.
         // Nor does a chunk start in a row that has no multiple of the quantum among its items.
-        split = empty_rows != 0 && first == last;
         const bool across = first != last && (first >> quantum_log2) != (last >> quantum_log2);
         const bool starting = QUEUES && ((before >> quantum_log2) != (last >> quantum_log2) || row == M - 1);
-        if (across || starting) {
-            const EvenSplit es(items, parts, quantum_log2);
-            // Chunks of one quantum each, unless the caller's entry count was not the matrix's: no divisions (nearly every wave has
-            // a row at a chunk's end; with those of part_from() R-MAT 2^20 x 16 at N = 32 / 64 222.7 / 465.6 -> 221.8 / 463.2 us)
-            const bool one_each = QUEUES && es.Q == parts;
+        if (row < M) {
+            if (empty_rows != 0 && first == last) split |= 1u << k;
+            if (across || starting) look |= 1u << k;
+        }
+    }
+    // The others, a row a lane and round: the first one of each lane's, and so on.  With one row a lane there is a single round, and
+    // no lane waits for another's unless they write first rows together (R-MAT 2^20 x 16 at N = 1, whole calls 69.8 -> 69.0 us).
+    const EvenSplit es(items, parts, quantum_log2);
+    // Chunks of one quantum each, unless the caller's entry count was not the matrix's: no divisions
+    const bool one_each = QUEUES && es.Q == parts;
+    for (bool round = R == 1 ? QUEUES || look != 0u : __ballot(look != 0u) != 0ull; round; round = R > 1 && __ballot(look != 0u) != 0ull) {
+        const bool any = look != 0u;
+        const int k = any ? __builtin_ctz(look) : 0;
+        look &= look - 1u;
+        const long long row = row0 + k;
+        unsigned first = bound[0], last = bound[1];
+#pragma unroll
+        for (int q = 1; q < R; ++q) { first = q == k ? bound[q] : first; last = q == k ? bound[q + 1] : last; }
+        first += (unsigned)row; last += (unsigned)row;
+        unsigned c_from = 0, c_to = 0;                                      // chunks that start within the row's items
+        if (any) {
             const unsigned c1 = one_each ? first >> quantum_log2 : es.chunk_of(first);
             const unsigned c2 = one_each ? last >> quantum_log2 : es.chunk_of(last);
-            if (across) split = c1 != c2;
-            if constexpr (QUEUES) split = split && (!across || queues.piece_of(c1) != queues.piece_of(c2));
-            if (across && !split && tile_log2 >= 0) {
-                const unsigned start = es.start(c1);
-                split = (first - start) >> tile_log2 != (last - start) >> tile_log2;
+            if (first != last) {
+                bool cut = c1 != c2;
+                if constexpr (QUEUES) cut = cut && !queues.one_piece(c1, c2);
+                if (!cut && tile_log2 >= 0) {
+                    const unsigned start = es.start(c1);
+                    cut = (first - start) >> tile_log2 != (last - start) >> tile_log2;
+                }
+                if (cut) split |= 1u << k;
             }
-            if (starting) {
+            if constexpr (QUEUES) {
                 c_from = c1;
                 if (one_each) {
                     c_from += first != c1 << quantum_log2;
@@ -519,28 +558,30 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
                 c_to = (c2 < parts ? c2 + 1u : parts);
             }
         }
+        if constexpr (QUEUES) {
+            // a few chunks each; a row of very many is written by the whole wave
+            constexpr unsigned kOwn = 8;
+            for (unsigned c = c_from; c < c_to && c < c_from + kOwn; ++c) queues.starts[c] = (int)row;
+            unsigned long long wide = __ballot(c_to > c_from + kOwn);
+            while (wide != 0ull) {                                          // wave-uniform
+                const int src = __ffsll((long long)wide) - 1;
+                wide &= wide - 1ull;
+                const unsigned wide_from = (unsigned)read_lane((int)c_from, src) + kOwn, wide_to = (unsigned)read_lane((int)c_to, src);
+                const int r = read_lane((int)row, src);
+                for (unsigned c = wide_from + (unsigned)lane_id(); c < wide_to; c += (unsigned)kWave) queues.starts[c] = r;
+            }
+            // chunks past the last item, and the list's end
+            if (any && row == M - 1)
+                for (unsigned c = c_to; c <= parts; ++c) queues.starts[c] = M;
+        }
     }
     if constexpr (QUEUES) {
-        const unsigned t = (unsigned)row;
-        if (row < (long long)queues.counters) queues.taken[t * kQueuePitch] = 0u;
-        // a few chunks each; a row of very many is written by the whole wave
-        constexpr unsigned kOwn = 8;
-        for (unsigned c = c_from; c < c_to && c < c_from + kOwn; ++c) queues.starts[c] = (int)row;
-        unsigned long long wide = __ballot(c_to > c_from + kOwn);
-        while (wide != 0ull) {                                              // wave-uniform
-            const int src = __ffsll((long long)wide) - 1;
-            wide &= wide - 1ull;
-            const unsigned from = (unsigned)read_lane((int)c_from, src) + kOwn, to = (unsigned)read_lane((int)c_to, src);
-            const int r = read_lane((int)row, src);
-            for (unsigned c = from + (unsigned)lane_id(); c < to; c += (unsigned)kWave) queues.starts[c] = r;
-        }
-        // chunks past the last item, and the list's end
-        if (row == M - 1)
-            for (unsigned c = c_to; c <= parts; ++c) queues.starts[c] = M;
+        for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < queues.counters; t += (size_t)gridDim.x * kBlock)
+            queues.taken[t * kQueuePitch] = 0u;
     }
-    if (N <= 8 && !empty_rows) {                       // few and narrow: the thread clears its own
-        if (split) {
-            float* y = Y + (size_t)row * ldy;
+    if (N < 4 || (N <= 8 && !empty_rows)) {            // few and narrow: the thread clears its own
+        for (; split != 0u; split &= split - 1u) {
+            float* y = Y + (size_t)(row0 + __builtin_ctz(split)) * ldy;
             for (int n = 0; n < N; ++n) y[n] = beta != 0.0f ? beta * y[n] : 0.0f;
         }
         return;
@@ -550,17 +591,34 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     // other in one wave took R-MAT 2^18 x 13 at N = 58 100 of 206 us; with a wave to a row of 8 / 12 columns 2^18 x 6 / 2^17 x 16 in the
     // scaled form took 33 / 45 instead of 28 / 38 us, with one to a row of 12 / 20 columns plain products on 2^17 x 16
     // 28.3 / 31.6 instead of 26.5 / 30.6 us.)
-    __shared__ int s_rows[kBlock];
+    __shared__ int s_rows[kBlock * R];
     __shared__ int s_count[kWavesPerBlock];
     const int lane = lane_id(), wib = wave_in_block();
-    const unsigned long long mine = __ballot(split);
-    if (lane == 0) s_count[wib] = (int)__popcll(mine);
+    unsigned long long mine[R];
+    int own = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) { mine[k] = __ballot((split >> k) & 1u); own += (int)__popcll(mine[k]); }
+    if (lane == 0) s_count[wib] = own;
     __syncthreads();
     int before = 0, count = 0;
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w) { before += w < wib ? s_count[w] : 0; count += s_count[w]; }
-    if (split) s_rows[before + (int)__popcll(mine & ((1ull << lane) - 1ull))] = (int)row;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        if ((split >> k) & 1u) s_rows[before + (int)__popcll(mine[k] & ((1ull << lane) - 1ull))] = (int)(row0 + k);
+        before += (int)__popcll(mine[k]);
+    }
     __syncthreads();
+    if (beta == 0.0f) {                                  // nothing to wait for: zeros, four columns a lane, the last four where N ends
+        const int log_quads = N > 2 * kWave ? 6 : 32 - __builtin_clz((unsigned)(N + 3) / 4u - 1u | 1u);
+        for (int r = (int)threadIdx.x >> log_quads; r < count; r += kBlock >> log_quads) {
+            float* y = Y + (size_t)s_rows[r] * ldy;
+            const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int n = 4 * (int)(threadIdx.x & ((1u << log_quads) - 1u)); n < N; n += 4 << log_quads)
+                store_vec_dword_aligned<4>(y + (n + 4 <= N ? n : N - 4), zero);
+        }
+        return;
+    }
     constexpr int U = 8;
     const int log_lanes = N > kWave / 2 ? 6 : 32 - __builtin_clz((unsigned)N - 1u | 1u);
     const int lanes = 1 << log_lanes, step = kBlock >> log_lanes;                    // rows that the workgroup takes at once
@@ -570,12 +628,12 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int at = r + u * step;
-                v[u] = (beta != 0.0f && at < count) ? Y[(size_t)s_rows[at] * ldy + n] : 0.0f;
+                v[u] = at < count ? Y[(size_t)s_rows[at] * ldy + n] : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int at = r + u * step;
-                if (at < count) Y[(size_t)s_rows[at] * ldy + n] = beta != 0.0f ? beta * v[u] : 0.0f;
+                if (at < count) Y[(size_t)s_rows[at] * ldy + n] = beta * v[u];
             }
         }
     }

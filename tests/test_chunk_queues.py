@@ -40,7 +40,11 @@ def ends_in_a_quantum():
     return rows_of(lens, 1 << 18, 4)
 
 
-CASES = [("graph", graph, 41), ("hub", hub, 45), ("few rows", few_rows, 64), ("aligned", ends_in_a_quantum, 44), ("three column blocks", few_rows, 300),
+def fewer_rows_than_queues():
+    return rows_of(np.full(5, 1_900_000), 30_000, 3)
+
+
+CASES = [("fewer rows than queues", fewer_rows_than_queues, 64), ("graph", graph, 41), ("hub", hub, 45), ("few rows", few_rows, 64), ("aligned", ends_in_a_quantum, 44), ("three column blocks", few_rows, 300),
          ("pinned blocks", graph, 128), ("one line", lambda: graph(20, 17), 32)]
 
 

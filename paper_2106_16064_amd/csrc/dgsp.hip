@@ -1296,8 +1296,8 @@ bool recording(hipStream_t st) {
 }
 
 // Waits until the GPU has announced `ticket`: a look at host memory instead of a copy and an interrupt (15 us less).
-bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t st) {
-    const auto seen = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket; };
+template <typename Seen>
+bool wait_until(Seen&& seen, hipStream_t st) {
     for (int i = 0; i < 20000; ++i) {
         if (seen()) return true;
         __builtin_ia32_pause();
@@ -1305,12 +1305,38 @@ bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, 
     // much work ahead of it in the stream, or an error
     return hipStreamSynchronize(st) == hipSuccess && seen();
 }
+bool wait_for_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t st) {
+    return wait_until([&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket; }, st);
+}
 
-// the first `words` result words of a launch that announced itself in word kStatResultWords, or, without pinned words, left
+// what stands beside every piece of a call's statistics, and in no upper half that column_reuse_kernel leaves in these words
+inline unsigned stat_tag(unsigned long long ticket) { return (unsigned)ticket | 0x80000000u; }
+
+// the pieces that csr_statistics_kernel leaves
+int fetch_statistics(const StatisticsPool::Slot& slot, unsigned long long* h, hipStream_t st) {
+    if (slot.host) {
+        int got = 0;
+        const auto all = [&] {
+            for (; got < kStatPieces; ++got) {
+                h[got] = __atomic_load_n(slot.host + got, __ATOMIC_RELAXED);
+                if (h[got] >> 32 != stat_tag(slot.ticket)) return false;
+            }
+            return true;
+        };
+        if (!wait_until(all, st)) return DGSP_ERR_LAUNCH;
+    } else {
+        if (hipMemcpyAsync(h, slot.scratch->result, sizeof(*h) * kStatPieces, hipMemcpyDeviceToHost, st) != hipSuccess) return DGSP_ERR_LAUNCH;
+        if (hipStreamSynchronize(st) != hipSuccess) return DGSP_ERR_LAUNCH;
+    }
+    for (int i = 0; i < kStatPieces; ++i) h[i] &= 0xffffffffull;
+    return DGSP_OK;
+}
+
+// the first `words` result words of a launch that announced itself in word kStatAnnounceWord, or, without pinned words, left
 // them in the scratch
 int fetch_result(const StatisticsPool::Slot& slot, unsigned long long* h, int words, hipStream_t st) {
     if (slot.host) {
-        if (!wait_for_ticket(slot.host + kStatResultWords, slot.ticket, st)) return DGSP_ERR_LAUNCH;
+        if (!wait_for_ticket(slot.host + kStatAnnounceWord, slot.ticket, st)) return DGSP_ERR_LAUNCH;
         for (int w = 0; w < words; ++w) h[w] = __atomic_load_n(slot.host + w, __ATOMIC_RELAXED);
         return DGSP_OK;
     }
@@ -1364,14 +1390,14 @@ int features_from_csr_device(int64_t M, int64_t K, int64_t entries, const I* row
     const dim3 grid(apart ? (unsigned)(entry_blocks + row_blocks) : clamp_blocks(pieces, kStatBlocks));
     hipLaunchKernelGGL((csr_statistics_kernel<Word>), grid, dim3(kBlock), 0, st, (int)M, (long long)entries,
                        reinterpret_cast<const Word*>(rowptr), K > 0 ? reinterpret_cast<const Word*>(colidx) : nullptr,
-                       rowptr32, colidx32, slot.scratch, slot.host, slot.ticket, apart ? (unsigned)row_blocks : 0u);
+                       rowptr32, colidx32, slot.scratch, slot.host, stat_tag(slot.ticket), apart ? (unsigned)row_blocks : 0u);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
-    unsigned long long h[kStatResultWords];
-    if (const int rc = fetch_result(slot, h, kStatResultWords, st)) return rc;
+    unsigned long long h[kStatPieces];
+    if (const int rc = fetch_statistics(slot, h, st)) return rc;
     if (h[5] != 0 || h[kStatWords] != 0) return DGSP_ERR_INVALID_ARG;       // decreasing row pointers, rowptr[0] != 0
-    f.nnz = (int64_t)h[kStatWords + 1];
+    f.nnz = (int64_t)(int32_t)h[kStatWords + 1];
     f.max_row = (int64_t)h[1]; f.min_row = (int64_t)h[2];
-    finish_features(f, h[0], h[3], h[4]);
+    finish_features(f, h[0] | h[kStatWords + 2] << 32, h[3], h[4] | h[kStatWords + 3] << 32);
     if (h[6] != h[7]) {
         const int rc = features_of_unsorted_rows(M, K, sizeof(I) == 8 ? rowptr32 : reinterpret_cast<const int32_t*>(rowptr),
                                                  sizeof(I) == 8 ? colidx32 : reinterpret_cast<const int32_t*>(colidx),
@@ -1445,12 +1471,12 @@ int sample_columns(int64_t K, int64_t entries, const int32_t* colidx, uint32_t* 
     struct Return { const StatisticsPool::Slot& s; ~Return() { g_stat_pool.give_back(s); } } give_back{slot};
     unsigned long long* out = slot.host ? slot.host : slot.scratch->result;
     hipLaunchKernelGGL(column_reuse_kernel, dim3(hot_table ? 1 + kHotWidths : 1), dim3(kReuseThreads), 0, st, (long long)entries,
-                       colidx, hot_table, hot_table ? hot_shift(K) : 0, out, slot.host ? slot.host + kStatResultWords : nullptr, slot.ticket);
+                       colidx, hot_table, hot_table ? hot_shift(K) : 0, out, slot.host ? slot.host + kStatAnnounceWord : nullptr, slot.ticket);
     if (hipGetLastError() != hipSuccess) return DGSP_ERR_LAUNCH;
     // a place is given back when nothing is under way in it: all workgroups', whatever became of the first
     bool hot_done = true;
     for (int v = 1; hot_table && slot.host && v <= kHotWidths; ++v)
-        hot_done = wait_for_ticket(slot.host + kStatResultWords + v, slot.ticket, st) && hot_done;
+        hot_done = wait_for_ticket(slot.host + kStatAnnounceWord + v, slot.ticket, st) && hot_done;
     unsigned long long h[kReuseResultWords];
     if (const int rc = fetch_result(slot, h, kReuseResultWords, st)) return rc;
     if (!hot_done) return DGSP_ERR_LAUNCH;

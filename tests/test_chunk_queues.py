@@ -44,8 +44,16 @@ def fewer_rows_than_queues():
     return rows_of(np.full(5, 1_900_000), 30_000, 3)
 
 
-CASES = [("fewer rows than queues", fewer_rows_than_queues, 64), ("graph", graph, 41), ("hub", hub, 45), ("few rows", few_rows, 64), ("aligned", ends_in_a_quantum, 44), ("three column blocks", few_rows, 300),
-         ("pinned blocks", graph, 128), ("one line", lambda: graph(20, 17), 32)]
+def odd_rows():
+    """The prepare launch takes two rows a thread (2^19 of them and more): here its last thread has one, which is long."""
+    lens = np.random.default_rng(5).integers(0, 38, (1 << 19) + 1)
+    lens[-1] = 70_000
+    return rows_of(lens, 40_000, 6)
+
+
+CASES = [("fewer rows than queues", fewer_rows_than_queues, 64), ("graph", graph, 41), ("hub", hub, 45), ("few rows", few_rows, 64),
+         ("aligned", ends_in_a_quantum, 44), ("three column blocks", few_rows, 300), ("pinned blocks", graph, 128),
+         ("one line", lambda: graph(20, 17), 32), ("odd rows", odd_rows, 64)]
 
 
 def allocations(call):

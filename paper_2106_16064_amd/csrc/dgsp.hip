@@ -472,7 +472,7 @@ constexpr double kFirstPiece = 0.55;
 constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
 ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
     ChunkQueues q{};
-    const long long items = p.nnz + (long long)p.M;
+    const long long items = p.size + (long long)p.M;
     const unsigned size_log2 = share >= 4096 ? 10 : 9;
     const long long chunks = (items + (1ll << size_log2) - 1) >> size_log2;
     const unsigned run = (unsigned)((double)(chunks / parts) * kFirstPiece / waves);
@@ -767,15 +767,20 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     // 393 / 419 us, 2^20 x 8 at N = 41 257 -> 240 us, 2^18 x 16 at N = 128 201 -> 194 us, 2^19 x 16 at N = 100 405 -> 398 us;
     // not 2^20 x 16 at N = 16 (170 against 173 to 190 us), 2^19 x 16 at N = 32 (106 / 113 us), 2^18 x 32 at N = 48
     // (136 / 140 us), nor with few entries a row, whose workgroups are dealt to the XCDs one by one (2^20 x 6 at
-    // N = 50 207 / 223 us).
+    // N = 50 207 / 223 us).  Not from 1024 items and 16 384 lane steps on either, in chunks of 256: 2^18 x 16 at N = 64 103.1 / 108.4 us,
+    // 2^18 x 32 at N = 48 126.6 / 140.2 us, 2^18 Zipf rows of 16 at N = 64 163.0 / 170.6 us, 2^18 rows of exactly 16 163.5 / 171.1 us.
+    // A bound of the entry count (the length of colidx) will do, the kernels fit the chunks to the matrix: calls without statistics, R-MAT
+    // 2^20 x 16 at N = 32 / 64 250 / 574 -> 228 / 497 us, 2^20 x 8 at N = 41 258 -> 231 us, 2^20 Zipf rows of 16 at N = 64
+    // 662 -> 632 us, 635 441 Poisson rows of 13 at N = 60 434 -> 421 us.  With arrays four times as long as the matrix, whose true
+    // share is then below the line: 2^18 x 16 at N = 64 85.3 -> 93.9 us, 2^19 Zipf rows of 10 at N = 100 416 -> 427 us.
     ChunkQueues queues{};
     dim3 queue_grid = grid;
-    if (XBUF && !snap && p.nnz > 0 && grid.x % kXcd == 0 && p.nnz / p.M >= run_dealt_below(LOGG)) {
+    if (XBUF && !snap && p.size > 0 && grid.x % kXcd == 0 && p.size / p.M >= run_dealt_below(LOGG)) {
         const unsigned parts = pinned ? kXcd / pinned : kXcd;
         // no more than are resident: what is started late finds the queues empty
         if (pinned) queue_grid.x = std::min<unsigned>(grid.x, (unsigned)(device_info().cus * resident) / kXcd * kXcd);
         const unsigned waves = queue_grid.x / kXcd * kWavesPerBlock;
-        const long long share = (p.nnz + (long long)p.M) / parts / waves;
+        const long long share = (p.size + (long long)p.M) / parts / waves;
         if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
     }
     const unsigned chunks = queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock;

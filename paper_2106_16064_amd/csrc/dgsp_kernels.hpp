@@ -457,6 +457,16 @@ struct ChunkQueues {
     // at most 2^23 chunks, 8 parts
     __device__ __forceinline__ unsigned part_from(unsigned part) const { return (chunks * part) >> parts_log2; }
     __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
+    // The host counts with a bound of the entries where it does not know them.  Fewer items: fewer chunks of the same size, and shorter
+    // first pieces to the same share.
+    __device__ __forceinline__ void fit(unsigned items) {
+        const unsigned quanta = EvenSplit(items, 1u, size_log2).Q;
+        if (quanta >= chunks) return;
+        run = (unsigned)((float)run * ((float)quanta / (float)chunks));     // 0: all by the queues
+        chunks = quanta;
+        parts_per_chunk = (float)(1u << parts_log2) / (float)chunks;
+        per_run = 1.0f / (float)run;
+    }
     // do chunks c1 and c2 >= c1 belong to one piece?  (c2 in a queue: a piece is a chunk; else no multiple of `run` lies behind c1)
     __device__ __forceinline__ bool one_piece(unsigned c1, unsigned c2) const {
         unsigned part = (unsigned)((float)c2 * parts_per_chunk);            // one off at most
@@ -595,6 +605,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     }
     const long long row0 = ((long long)(blockIdx.x - search_blocks) * kBlock + threadIdx.x) * R;
     const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the rows' bounds
+    if constexpr (QUEUES) { queues.fit(items); parts = queues.chunks; }
     unsigned bound[R + 1];
     if (R == 1 && row0 < M) {
         bound[0] = (unsigned)rowptr[row0];
@@ -625,7 +636,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
     // The others, a row a lane and round: the first one of each lane's, and so on.  With one row a lane there is a single round, and
     // no lane waits for another's unless they write first rows together (R-MAT 2^20 x 16 at N = 1, whole calls 69.8 -> 69.0 us).
     const EvenSplit es(items, parts, quantum_log2);
-    // Chunks of one quantum each, unless the caller's entry count was not the matrix's: no divisions
+    // Chunks of one quantum each, unless the caller's entry count was below the matrix's: no divisions
     const bool one_each = QUEUES && es.Q == parts;
     for (bool round = R == 1 ? QUEUES || look != 0u : __ballot(look != 0u) != 0ull; round; round = R > 1 && __ballot(look != 0u) != 0ull) {
         const bool any = look != 0u;
@@ -2240,6 +2251,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         wg = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
     }
+    if constexpr (QUEUED) queues.fit(items);
     const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, QUEUED ? queues.size_log2 : 6u);
     // queue q: what the waves of XCD q leave of its part of the chunks
     const auto part_of = [&](unsigned q) { return pinned_blocks ? q / pinned_blocks : q; };

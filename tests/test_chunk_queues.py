@@ -108,6 +108,28 @@ def test_arrays_longer_than_the_matrix(make, N, longer):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("make, N, longer", [(graph, 41, 1.0), (odd_rows, 64, 1.3), (hub, 128, 30.0), (lambda: graph(17, 20), 41, 8.0),
+                                             (lambda: rows_of(np.ones(3, int), 500, 1), 64, 4_000_000.0)])
+def test_calls_that_know_no_entry_count(make, N, longer):
+    """The length of colidx stands for it: queues are fitted to the matrix, down to none of it in first pieces and a single chunk."""
+    import torch
+    A = make()
+    D = dg.DeviceCsr(A)
+    room = int(A.nnz * longer)
+    colidx, vals = torch.zeros(room, dtype=torch.int32, device="cuda"), torch.full((room,), float("nan"), device="cuda")
+    colidx[:A.nnz], vals[:A.nnz] = D.colidx[:A.nnz], D.vals[:A.nnz]
+    X = wl.dense_matrix(A.K, N, "normal", seed=2)
+    ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    dX = torch.from_numpy(X).cuda()
+    for algo in (dg.AUTO, dg.NB_SR):
+        Y = torch.full((A.M, N), float("nan"), device="cuda")
+        print(f"[case] queues without an entry count, arrays {longer} times as long N={N}", flush=True)
+        dg.dgsp_spmm_csr(A.M, A.K, N, D.rowptr, colidx, vals, dX, Y, algo)
+        ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+        assert ok, worst
+
+
+@pytest.mark.gpu
 def test_queues_of_calls_on_several_streams_and_none_in_a_graph():
     """Calls in flight together have queues of their own; a product that is recorded goes without."""
     import torch

@@ -444,14 +444,13 @@ constexpr long long kTwoRowsMin = 1 << 19;
 // Zeroes (scaled form: multiplies by beta) the rows split by the `parts` chunks the main kernel derives
 // (quanta of 2^quantum_log2 items), cut into tiles of 2^tile_log2 items (tile_log2 < 0: not cut further).
 int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int tile_log2, ChunkQueues queues = ChunkQueues{},
-                   int empty_rows = 0, int* starts = nullptr) {
-    const unsigned search_blocks = starts ? parts / kWavesPerBlock + 1u : 0u;
+                   int empty_rows = 0) {
     const float beta = p.scaled ? p.beta : 0.0f;
     const auto launch = [&](auto with_queues, auto rows) -> int {
         constexpr int R = decltype(rows)::value;
-        const dim3 grid((unsigned)(((long long)p.M + kBlock * R - 1) / (kBlock * R)) + search_blocks);
+        const dim3 grid((unsigned)(((long long)p.M + kBlock * R - 1) / (kBlock * R)));
         DGSP_LAUNCH((nb_prepare_kernel<decltype(with_queues)::value, R>), grid, p.M, p.N, p.ldy, p.rowptr, p.Y, parts, quantum_log2,
-                    tile_log2, beta, queues, empty_rows, starts, search_blocks);
+                    tile_log2, beta, queues, empty_rows);
         return DGSP_OK;
     };
     if (queues.starts && p.M >= kTwoRowsMin && !empty_rows) return launch(std::true_type{}, std::integral_constant<int, 2>{});
@@ -604,17 +603,13 @@ inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
 template <int V>
 int launch_nb_pr_hot(const Problem& p) {
     constexpr int KQ = kNbPrKq;
-    HotColumns hot{p.hot_columns + (V - 1) * kHotTableInts, hot_shift(p.K), nullptr};
+    const HotColumns hot{p.hot_columns + (V - 1) * kHotTableInts, hot_shift(p.K)};
     const dim3 grid((unsigned)device_info().cus);
     constexpr int kGroups = kHotThreads / kBlock;                   // workgroups of the usual size in one of this kernel
     const bool snap = snap_rows(p, grid.x * kGroups, 0.1, 128.0, 1.0);
     const unsigned chunks = grid.x * kGroups * kWavesPerBlock;
-    int* starts = nullptr;
-    if (!snap && p.phase == DGSP_PHASE_ALL && p.more && p.more->workspace)
-        starts = static_cast<int*>(p.more->workspace(p.more->context, ((size_t)chunks + 1) * sizeof(int)));
-    hot.starts = starts;
     if (p.phase != DGSP_PHASE_MAIN && !snap)
-        if (int rc = launch_prepare(p, chunks, 6, -1, ChunkQueues{}, 0, starts)) return rc;
+        if (int rc = launch_prepare(p, chunks, 6, -1)) return rc;
     if (p.phase == DGSP_PHASE_PREPARE) return DGSP_OK;
     const Scaling sc{p.alpha, p.beta};
     const auto launch = [&](auto whole, auto scaled) -> int {

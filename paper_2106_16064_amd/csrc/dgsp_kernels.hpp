@@ -481,96 +481,6 @@ struct ChunkQueues {
     }
 };
 
-// The chunk of the calling wave, number `wave` of `waves`.
-struct ChunkPlan {
-    unsigned nnz, items, wave;
-    EvenSplit split;
-    __device__ __forceinline__ ChunkPlan(unsigned nnz_, unsigned items_, unsigned waves, unsigned wave_, unsigned quantum_log2)
-        : nnz(nnz_), items(items_), wave(wave_), split(items_, waves, quantum_log2) {}
-    __device__ __forceinline__ bool range(unsigned& d0, unsigned& d1) const {
-        d0 = split.start(wave);
-        const unsigned e = split.start(wave + 1);
-        d1 = e < items ? e : items;
-        return d0 < d1;
-    }
-};
-
-__device__ __forceinline__ ChunkPlan plan_chunks(const int* __restrict__ rowptr, int M, unsigned quantum_log2) {
-    const unsigned nnz = (unsigned)rowptr[M];
-    return ChunkPlan(nnz, nnz + (unsigned)M, gridDim.x * kWavesPerBlock,
-                     xcd_contiguous(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block(), quantum_log2);
-}
-
-// What the first round of a search probes does not depend on what is searched for: asked for beside the entry count, from
-// which the diagonals follow, it saves a chunk's start one round trip to memory.
-__device__ __forceinline__ int first_probe(const int* __restrict__ rowptr, int M, int lane) {
-    const long long r = (long long)lane * ((M + 63ll) >> 6);
-    return r < M ? rowptr[r + 1] : 0;
-}
-
-// Number of rows whose end marker lies before diagonal d, i.e. rows r with
-// r + rowptr[r+1] < d (that key is strictly increasing in r).  64-way search,
-// wave-uniform result.
-// `probe`: first_probe().
-__device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ rowptr, int M, unsigned d, int lane, int probe) {
-    int lo = 0, hi = M;   // rows < lo end before d; rows >= hi do not
-    for (bool first = true; hi > lo; first = false) {
-        const int step = (int)(((long long)hi - lo + 63) >> 6);
-        const long long r = (long long)lo + (long long)lane * step;
-        int v = probe;
-        if (!first) v = r < hi ? rowptr[r + 1] : 0;
-        const bool before = r < hi && (unsigned)r + (unsigned)v < d;
-        const int cnt = __popcll(__ballot(before));   // probes are monotone: 1...10...0
-        if (cnt == 0) {
-            hi = lo;
-        } else {
-            const int nlo = lo + (cnt - 1) * step + 1;
-            const int nhi = lo + cnt * step;
-            lo = nlo;
-            hi = nhi < hi ? nhi : hi;
-        }
-    }
-    return uniform(lo);
-}
-
-// Rows that ended before diagonal da, and before db (both searches of wave_merge_rows_before in lock-step: their
-// probes are in flight together, so the second costs no further round trips).  `probe`: first_probe().
-__device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ rowptr, int M, unsigned da, unsigned db,
-                                                        int lane, int probe, int& ra, int& rb) {
-    int lo[2] = {0, 0}, hi[2] = {M, M};
-    const unsigned d[2] = {da, db};
-    bool first = true;
-    while (hi[0] > lo[0] || hi[1] > lo[1]) {
-        int step[2], v[2];
-        long long r[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            step[k] = (int)(((long long)hi[k] - lo[k] + 63) >> 6);
-            r[k] = (long long)lo[k] + (long long)lane * step[k];
-            v[k] = probe;
-            if (!first) v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
-        }
-        first = false;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            if (hi[k] > lo[k]) {                                   // wave-uniform
-                const bool before = r[k] < hi[k] && (unsigned)r[k] + (unsigned)v[k] < d[k];
-                const int cnt = __popcll(__ballot(before));       // probes are monotone: 1...10...0
-                if (cnt == 0) {
-                    hi[k] = lo[k];
-                } else {
-                    const int nlo = lo[k] + (cnt - 1) * step[k] + 1;
-                    const int nhi = lo[k] + cnt * step[k];
-                    lo[k] = nlo;
-                    hi[k] = nhi < hi[k] ? nhi : hi[k];
-                }
-            }
-        }
-    }
-    ra = uniform(lo[0]);
-    rb = uniform(lo[1]);
-}
-
 // Zeroes the rows whose items do not all lie in one piece of the partition (beta != 0, the scaled
 // variants: multiplies them by beta instead, so that the partial sums added later land on beta * Y).
 // The pieces are the `parts` chunks of the even split with quanta of
@@ -579,7 +489,6 @@ __device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ 
 // R rows a thread for the test (split rows are few: at most two per piece); those with a multiple of the quantum among their items
 // go on, one a thread and round.
 // QUEUES: the chunks' first rows and the counters are written as well.
-// Otherwise the first `search_blocks` workgroups, if any, find for each chunk and for the list's end how many rows ended before it, a wave each.
 // Bound by the trips to memory (row bounds, zeros) and, with queues, by its instructions: at M = 2^20 nearly every wave has such a
 // row and a row to clear.  R-MAT 2^20 x 16 at N = 32 / 128 12.2 / 11.8 -> 5.9 / 7.8 us with two rows a thread, the pieces told apart by
 // one look at the second chunk in place of two searches and divisions, and zeros 16 bytes a lane in place of 4.
@@ -591,19 +500,8 @@ __device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ 
 template <bool QUEUES, int R>
 __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ldy, const int* __restrict__ rowptr,
                                                              float* __restrict__ Y, unsigned parts, unsigned quantum_log2,
-                                                             int tile_log2, float beta, ChunkQueues queues, int empty_rows,
-                                                             int* __restrict__ starts, unsigned search_blocks) {
-    if (!QUEUES && blockIdx.x < search_blocks) {
-        const unsigned c = blockIdx.x * kWavesPerBlock + (unsigned)wave_in_block();
-        const int probe = first_probe(rowptr, M, lane_id());
-        const unsigned n = (unsigned)rowptr[M] + (unsigned)M;
-        if (c > parts) return;
-        const unsigned d = EvenSplit(n, parts, quantum_log2).start(c);
-        const int rows = wave_merge_rows_before(rowptr, M, d < n ? d : n, lane_id(), probe);
-        if (lane_id() == 0) starts[c] = rows;
-        return;
-    }
-    const long long row0 = ((long long)(blockIdx.x - search_blocks) * kBlock + threadIdx.x) * R;
+                                                             int tile_log2, float beta, ChunkQueues queues, int empty_rows) {
+    const long long row0 = ((long long)blockIdx.x * kBlock + threadIdx.x) * R;
     const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the rows' bounds
     if constexpr (QUEUES) { queues.fit(items); parts = queues.chunks; }
     unsigned bound[R + 1];
@@ -750,6 +648,96 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
             }
         }
     }
+}
+
+// The chunk of the calling wave, number `wave` of `waves`.
+struct ChunkPlan {
+    unsigned nnz, items, wave;
+    EvenSplit split;
+    __device__ __forceinline__ ChunkPlan(unsigned nnz_, unsigned items_, unsigned waves, unsigned wave_, unsigned quantum_log2)
+        : nnz(nnz_), items(items_), wave(wave_), split(items_, waves, quantum_log2) {}
+    __device__ __forceinline__ bool range(unsigned& d0, unsigned& d1) const {
+        d0 = split.start(wave);
+        const unsigned e = split.start(wave + 1);
+        d1 = e < items ? e : items;
+        return d0 < d1;
+    }
+};
+
+__device__ __forceinline__ ChunkPlan plan_chunks(const int* __restrict__ rowptr, int M, unsigned quantum_log2) {
+    const unsigned nnz = (unsigned)rowptr[M];
+    return ChunkPlan(nnz, nnz + (unsigned)M, gridDim.x * kWavesPerBlock,
+                     xcd_contiguous(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block(), quantum_log2);
+}
+
+// What the first round of a search probes does not depend on what is searched for: asked for beside the entry count, from
+// which the diagonals follow, it saves a chunk's start one round trip to memory.
+__device__ __forceinline__ int first_probe(const int* __restrict__ rowptr, int M, int lane) {
+    const long long r = (long long)lane * ((M + 63ll) >> 6);
+    return r < M ? rowptr[r + 1] : 0;
+}
+
+// Number of rows whose end marker lies before diagonal d, i.e. rows r with
+// r + rowptr[r+1] < d (that key is strictly increasing in r).  64-way search,
+// wave-uniform result.
+// `probe`: first_probe().
+__device__ __forceinline__ int wave_merge_rows_before(const int* __restrict__ rowptr, int M, unsigned d, int lane, int probe) {
+    int lo = 0, hi = M;   // rows < lo end before d; rows >= hi do not
+    for (bool first = true; hi > lo; first = false) {
+        const int step = (int)(((long long)hi - lo + 63) >> 6);
+        const long long r = (long long)lo + (long long)lane * step;
+        int v = probe;
+        if (!first) v = r < hi ? rowptr[r + 1] : 0;
+        const bool before = r < hi && (unsigned)r + (unsigned)v < d;
+        const int cnt = __popcll(__ballot(before));   // probes are monotone: 1...10...0
+        if (cnt == 0) {
+            hi = lo;
+        } else {
+            const int nlo = lo + (cnt - 1) * step + 1;
+            const int nhi = lo + cnt * step;
+            lo = nlo;
+            hi = nhi < hi ? nhi : hi;
+        }
+    }
+    return uniform(lo);
+}
+
+// Rows that ended before diagonal da, and before db (both searches of wave_merge_rows_before in lock-step: their
+// probes are in flight together, so the second costs no further round trips).  `probe`: first_probe().
+__device__ __forceinline__ void wave_merge_rows_before2(const int* __restrict__ rowptr, int M, unsigned da, unsigned db,
+                                                        int lane, int probe, int& ra, int& rb) {
+    int lo[2] = {0, 0}, hi[2] = {M, M};
+    const unsigned d[2] = {da, db};
+    bool first = true;
+    while (hi[0] > lo[0] || hi[1] > lo[1]) {
+        int step[2], v[2];
+        long long r[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            step[k] = (int)(((long long)hi[k] - lo[k] + 63) >> 6);
+            r[k] = (long long)lo[k] + (long long)lane * step[k];
+            v[k] = probe;
+            if (!first) v[k] = (hi[k] > lo[k] && r[k] < hi[k]) ? rowptr[r[k] + 1] : 0;
+        }
+        first = false;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (hi[k] > lo[k]) {                                   // wave-uniform
+                const bool before = r[k] < hi[k] && (unsigned)r[k] + (unsigned)v[k] < d[k];
+                const int cnt = __popcll(__ballot(before));       // probes are monotone: 1...10...0
+                if (cnt == 0) {
+                    hi[k] = lo[k];
+                } else {
+                    const int nlo = lo[k] + (cnt - 1) * step[k] + 1;
+                    const int nhi = lo[k] + cnt * step[k];
+                    lo[k] = nlo;
+                    hi[k] = nhi < hi[k] ? nhi : hi[k];
+                }
+            }
+        }
+    }
+    ra = uniform(lo[0]);
+    rb = uniform(lo[1]);
 }
 
 // SNAP: a row belongs wholly to the chunk that holds its first item (the host asks for it when the longest row is short
@@ -1278,9 +1266,6 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
 // The hottest runs of a packed X of V columns (found when a matrix is taken over, hot_columns()): as many runs of 2^shift rows
 // of X as kHotFloats hold.  `table`: kHotWords words (bitmap of 32 runs, hot runs before them) and the hot runs' numbers,
 // ascending, kNoRow behind the last one; one such table for every V.
-// `starts`: for each chunk and for the end of the list the number of rows that ended before it, found by the prepare launch, whose rows keep
-// it busy for as long as the searches take (first gathers after 6.5 us with them in this kernel; R-MAT 2^20 x 16 at N = 1 69.1 ->
-// 68.0 us, 2^18 x 32 at N = 2 38.2 -> 37.5 us); nullptr: not known.
 constexpr int kHotThreads = 512, kHotWords = 1024, kHotWidths = 4, kHotShiftMin = 5, kHotShiftMax = 7;
 constexpr int kHotTableInts = 3 * kHotWords;
 // what the products, marks and bitmap of eight waves leave of 160 KB
@@ -1288,7 +1273,7 @@ constexpr int hot_floats(int v) { return v == 1 ? 31 * 1024 : v == 2 ? 28 * 1024
 __host__ __device__ constexpr int hot_room(int v, int shift) { return hot_floats(v) / (v << shift); }
 // runs that the L1 (32 KB, half of it left by everything else that passes through) holds without a table
 __host__ __device__ constexpr int hot_cached(int v, int shift) { return (128 << 5) / (v << shift); }
-struct HotColumns { const unsigned* table; int shift; const int* starts; };
+struct HotColumns { const unsigned* table; int shift; };
 
 // SERIAL_SCAN (a comparison kernel for Section 2.1.1, not used by the library's own choices): the lanes' open-row
 // partial sums meet through a serial segmented prefix sum - they are put into LDS and one lane adds them up in
@@ -1311,7 +1296,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
                                                         const int* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         const float* __restrict__ X, float* __restrict__ Y,
-                                                        Scaling sc, RowSharing sharing, HotColumns hot = HotColumns{nullptr, 0, nullptr}) {
+                                                        Scaling sc, RowSharing sharing, HotColumns hot = HotColumns{nullptr, 0}) {
     constexpr int E = 4 * KQ;
     constexpr int W = kWave * E;
     constexpr int kWaves = HOT ? kHotThreads / kWave : kWavesPerBlock;
@@ -1319,9 +1304,6 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     __shared__ __align__(16) float s_buf[kWaves][W * V];              // products, then a step's row results
     __shared__ __align__(16) float s_scan[SERIAL_SCAN ? kWaves : 1][SERIAL_SCAN ? kWave * (V + 1) : 1];   // serial scan only
     __shared__ __align__(16) float s_hot[HOT ? hot_floats(V) : 1];    // the hot runs of X
-    constexpr bool kInPairs = HOT && V == 1;                          // (a table for two columns or more leaves no word free)
-    __shared__ int s_done[kInPairs ? kWaves : 1];                     // blocks that each wave has behind it
-    if (kInPairs && threadIdx.x < kWaves) s_done[threadIdx.x] = 0;
     __shared__ __align__(16) uint2 s_word[HOT ? kHotWords : 1];       // 32 runs: which are hot, how many hot ones lie before
     const int lane = lane_id();
     const int wib = wave_in_block();
@@ -1329,8 +1311,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     float* buf = s_buf[wib];
     const int n0 = blockIdx.y * V;
 
-    const bool known = HOT && hot.starts != nullptr;      // the prepare launch has searched already
-    const int probe = known ? 0 : first_probe(rowptr, M, lane);
+    const int probe = first_probe(rowptr, M, lane);
     const unsigned nnz = (unsigned)rowptr[M];
     const ChunkPlan plan(nnz, nnz + (unsigned)M, gridDim.x * kWaves, xcd_contiguous(blockIdx.x, gridDim.x) * kWaves + wib,
                          6);                              // quanta of one wave's width
@@ -1410,11 +1391,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     bool idle = !any_items || nnz == 0;                  // HOT: such a wave has an empty chunk and goes along up to the barrier
     RowWord found = 0;
     if (shares && !idle && lane == 0) found = claim_row<DeviceWords>(words + plan.wave, sharing.call);
-    if (known) {
-        is = uniform(hot.starts[plan.wave]);
-        ie1 = uniform(hot.starts[plan.wave + 1u]);
-        if (idle) is = ie1 = 0;
-    } else if (!idle) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
+    if (!idle) wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
     // nothing stored: every item is a row end; my rows are [d0, d1)
     const auto rows_without_entries = [&] {
         if (!any_items) return;
@@ -1776,19 +1753,9 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // Waves that lag behind go first, by quarters of the chunk, so that those of a SIMD end together: R-MAT 2^20 x 16 at
     // N = 2 / 4 86.7 / 102.4 -> 85.1 / 101.1 us, 300 001 lognormal rows of 30 at N = 1 56.0 -> 54.8 us.  In chunks of a few
     // blocks there is nothing to make up (R-MAT 2^18 x 16 at N = 2, four blocks, 32.4 -> 32.9 us).
-    // By quarters the younger of the two waves that a SIMD has with hot runs still ended 2.5 us behind the older (57.3 against 54.8 of 63 us,
-    // R-MAT 2^20 x 16 at N = 1); there they compare how far they are, block by block: 68.0 -> 67.4 us, 2^20 x 32 114.2 -> 111.5 us.
     unsigned pace = 4u;
     for (unsigned k = 0; k < nb; ++k) {
-        unsigned behind;
-        if constexpr (kInPairs) {
-            static_assert(kWaves == 8, "waves w and w + 4 are on one SIMD");
-            if (lane == 0) __hip_atomic_store(&s_done[wib], (int)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const int other = uniform(__hip_atomic_load(&s_done[wib ^ 4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            behind = (int)k < other ? 3u : (int)k > other ? 0u : 1u;
-        } else {
-            behind = nb < 8u ? 0u : 3u - 4u * k / nb;
-        }
+        const unsigned behind = nb < 8u ? 0u : 3u - 4u * k / nb;
         if (behind != pace) { pace = behind; set_wave_priority(pace); }
         blk_start = js0 + k * (unsigned)W;                 // == js: the previous block was consumed to its end
         blk_end = (je1 - blk_start > (unsigned)W) ? blk_start + (unsigned)W : je1;

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lane_columns.hpp"
+
 namespace dgsp {
 
 constexpr int kWave = 64;                       // lanes per wavefront
@@ -265,32 +267,6 @@ __device__ __forceinline__ int buffer_stream_i32(__amdgpu_buffer_rsrc_t r, unsig
 }
 __device__ __forceinline__ float buffer_stream_f32(__amdgpu_buffer_rsrc_t r, unsigned byte_offset) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, byte_offset, 0, 2));
-}
-
-// ---------------------------------------------------------------------------
-// the V dense columns of a lane in the sequential-reduction kernels
-// ---------------------------------------------------------------------------
-// Column block `block` covers `cols_per_block` columns (a multiple of V, at most G * V) from block * cols_per_block;
-// lane `gl` of a group normally owns [first, first + V) with first = block * cols_per_block + gl * V.  RAGGED (N is
-// not a multiple of V, N >= V): the lane whose window would pass N takes the last V columns of the row instead, so
-// that every load stays inside the row; `skip` of them also belong to its left neighbour, which computes the same
-// sums from the same entries in the same order - the lane keeps them out of what it adds to memory and of the
-// scaled form's stores (plain stores may repeat them: the bits are the same).
-struct LaneColumns {
-    long long first;    // first column of the window
-    int skip;           // leading columns of the window that are the neighbour's (0 < skip < V on one lane at most)
-    bool any;           // the lane has columns at all
-};
-template <int V, bool RAGGED>
-__device__ __forceinline__ LaneColumns lane_columns(unsigned block, int cols_per_block, int gl, int N) {
-    LaneColumns c;
-    c.first = (long long)block * cols_per_block + gl * V;
-    c.skip = 0;
-    c.any = gl * V < cols_per_block && c.first < N;
-    if constexpr (RAGGED) {
-        if (c.any && c.first + V > N) { c.skip = (int)(c.first + V - N); c.first = (long long)N - V; }
-    }
-    return c;
 }
 
 // ---------------------------------------------------------------------------

@@ -776,12 +776,12 @@ struct DeviceWords {
         return __hip_atomic_compare_exchange_strong(p, &seen, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(1); }
+    // waves on all XCDs find it once stores_done() is past
+    static __device__ __forceinline__ void put(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
 // The wave's earlier stores have reached the place where they were sent.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// A store that waves on all XCDs find once stores_done() is past.
-__device__ __forceinline__ void store_through(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // The rows at the two ends of a chunk whose first item is d0: rows [is, ie) end in it, entries [js, je) lie in it.
 struct ChunkEnds {
@@ -809,26 +809,6 @@ struct ChunkEnds {
         tail = shares_tail && !starts_tail ? word_of((unsigned)ie + t0) : chunk;
     }
 };
-
-// Zeros, or the old values times beta, for the parts of a row to be added to (claim_row()): V columns of a lane, the second four of
-// eight `second` columns behind the first.
-template <int V, bool AXPBY>
-__device__ __forceinline__ void clear_row(float* y, Scaling sc, int second = 4) {
-    float old[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) old[i] = AXPBY && sc.beta != 0.0f ? y[i < 4 ? i : second + i - 4] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < V; ++i) store_through(y + (i < 4 ? i : second + i - 4), AXPBY && sc.beta != 0.0f ? sc.beta * old[i] : 0.0f);
-}
-// The first part of a row (row_has_sum()), times alpha already, on what beta leaves of the old values.
-template <int V, bool AXPBY>
-__device__ __forceinline__ void write_part(float* y, const float (&v)[V], Scaling sc, int second = 4) {
-    float old[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) old[i] = AXPBY && sc.beta != 0.0f ? y[i < 4 ? i : second + i - 4] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < V; ++i) store_through(y + (i < 4 ? i : second + i - 4), AXPBY && sc.beta != 0.0f ? fmaf(sc.beta, old[i], v[i]) : v[i]);
-}
 
 // ===========================================================================
 // nnz-balanced, parallel reduction: vectorized segment reduction (Section 2.1.1)
@@ -907,7 +887,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
             add_to_row(y, v);
         } else {
-            write_part<V, AXPBY>(y, v, sc, second);
+            write_part<DeviceWords, V, AXPBY>(y, v, sc.beta, 0, second);
             stores_done();
             publish_part<DeviceWords>(words + word, sharing.call);
         }
@@ -945,7 +925,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         js = d0 - (unsigned)is;
         first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
         ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js, d1 - (unsigned)ie1);
-        if (lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<V, AXPBY>(y_of(ie1), sc, second);
+        if (lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<DeviceWords, V, AXPBY>(y_of(ie1), sc.beta, 0, second);
     } else if (snap) {
         int ie1; unsigned je1;
         wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
@@ -1330,7 +1310,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
         if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
             add_to_row(y, v);
         } else {
-            write_part<V, AXPBY>(y, v, sc, second);
+            write_part<DeviceWords, V, AXPBY>(y, v, sc.beta, 0, second);
             stores_done();
             publish_part<DeviceWords>(words + word, sharing.call);
         }
@@ -1525,7 +1505,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     int c[E]; float a[E], x[E][V];                        // the block whose gathers are in flight
     int lc[E]; float la[E];                               // landing registers of the next block's entries
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
-    if (shares && !idle && lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<V, AXPBY>(y_of(ie1), sc, second);
+    if (shares && !idle && lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<DeviceWords, V, AXPBY>(y_of(ie1), sc.beta, 0, second);
     load_entries(0, c, a);
     load_row_ends(is, is < ie1, w_end);
     if constexpr (HOT) load_hot();
@@ -2142,7 +2122,8 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 // run.  Otherwise rows that cross a chunk end are added with atomics to zeros (RowSharing) or to what the prepare launch left.
 //
 // When N is no multiple of four the last lane's window ends at N and overlaps its neighbour's: plain stores may repeat
-// the shared columns (same bits), scaled stores and atomic adds leave them to the neighbour.
+// the shared columns (same bits); scaled stores, atomic adds and what they add to leave them to the neighbour, who may be another
+// column block's (N = 16129: 63 blocks of 256 columns and one of a single column).
 //
 // pinned_blocks = nb (2 or 4; gridDim = (8 k, 1)): the workgroups of XCD x all take column block x % nb, so that an L2
 // only ever sees one block's slice of X; the 8 / nb XCDs of a block share its chunk list, each a contiguous part.
@@ -2362,7 +2343,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         if (uniform(sum ? 1 : 0) != 0) {
             if (lanes) add_row(row, v);
         } else {
-            if (lanes) write_part<4, false>(y_at(row), v, sc);
+            if (lanes) write_part<DeviceWords, 4, false>(y_at(row), v, 0.0f, mine.skip);
             stores_done();
             if (lane == 0) publish_part<DeviceWords>(words + word, sharing.call);
         }
@@ -2370,7 +2351,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
 
     if (shares && ends.starts_tail) {
         const bool clear = uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0;       // as lane 0 found it
-        if (clear && g == 0 && col_ok) clear_row<4, false>(y_at(ie), sc);
+        if (clear && g == 0 && col_ok) clear_row<DeviceWords, 4, false>(y_at(ie), 0.0f, mine.skip);
     }
     unsigned w_start, w_end;
     load_window(is, w_start, w_end);

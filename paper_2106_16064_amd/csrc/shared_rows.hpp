@@ -15,14 +15,12 @@
 // numbers with a chance of 2^-62 a word.
 //
 // `Ops` accesses words that all waves see: load(p), store(p, v), exchange(p, v), replace(p, seen, v) - compare and swap
-// which leaves what it found in `seen` -, and pause().
+// which leaves what it found in `seen` -, and pause(); put(y, v) stores a float so that all waves find it behind the word's publication.
 #pragma once
 
-#if defined(__HIPCC__)
-#define DGSP_SHARED_ROWS_FN __host__ __device__ inline
-#else
-#define DGSP_SHARED_ROWS_FN inline
-#endif
+#include "host_device.hpp"
+
+#include <cmath>
 
 namespace dgsp {
 
@@ -30,20 +28,20 @@ using RowWord = unsigned long long;
 
 // The wave that the row starts in: what it found, for start_row().
 template <typename Ops>
-DGSP_SHARED_ROWS_FN RowWord claim_row(RowWord* word, RowWord call) { return Ops::exchange(word, call); }
+DGSP_HOST_DEVICE RowWord claim_row(RowWord* word, RowWord call) { return Ops::exchange(word, call); }
 
 // Is the row mine to clear?  (Otherwise somebody has come before me.)
-DGSP_SHARED_ROWS_FN bool mine_to_clear(RowWord found, RowWord call) { return found != call && found != call + 1; }
+DGSP_HOST_DEVICE bool mine_to_clear(RowWord found, RowWord call) { return found != call && found != call + 1; }
 
 // Once the zeros are in memory, or the row is not mine to clear.  Whoever has claimed the row before me publishes it himself.
 template <typename Ops>
-DGSP_SHARED_ROWS_FN void publish_start(RowWord* word, RowWord call, RowWord found) {
+DGSP_HOST_DEVICE void publish_start(RowWord* word, RowWord call, RowWord found) {
     if (found != call) Ops::store(word, call + 1);
 }
 
 // A wave with a part of the row.  True: there is a sum to add to.  False: the part is the first one, to be written and then published.
 template <typename Ops>
-DGSP_SHARED_ROWS_FN bool row_has_sum(RowWord* word, RowWord call) {
+DGSP_HOST_DEVICE bool row_has_sum(RowWord* word, RowWord call) {
     RowWord seen = Ops::load(word);
     for (;;) {
         if (seen == call + 1) return true;
@@ -56,6 +54,31 @@ DGSP_SHARED_ROWS_FN bool row_has_sum(RowWord* word, RowWord call) {
     }
 }
 template <typename Ops>
-DGSP_SHARED_ROWS_FN void publish_part(RowWord* word, RowWord call) { Ops::store(word, call + 1); }
+DGSP_HOST_DEVICE void publish_part(RowWord* word, RowWord call) { Ops::store(word, call + 1); }
+
+// Column i of the V that a lane holds from y[0] on: the second four of eight `second` columns behind the first.
+DGSP_HOST_DEVICE int lane_column(int i, int second) { return i < 4 ? i : second + i - 4; }
+
+// Zeros, or the old values times beta, for the parts of a row to be added to (claim_row()).  The first `skip` columns are left
+// alone: they are another lane's, which may be in another column block and have sums there already (lane_columns()).
+template <typename Ops, int V, bool AXPBY>
+DGSP_HOST_DEVICE void clear_row(float* y, float beta, int skip = 0, int second = 4) {
+    float old[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[lane_column(i, second)] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        if (i >= skip) Ops::put(y + lane_column(i, second), AXPBY && beta != 0.0f ? beta * old[i] : 0.0f);
+}
+// The first part of a row (row_has_sum()), times alpha already, on what beta leaves of the old values; `skip` as above.
+template <typename Ops, int V, bool AXPBY>
+DGSP_HOST_DEVICE void write_part(float* y, const float (&v)[V], float beta, int skip = 0, int second = 4) {
+    float old[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[lane_column(i, second)] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        if (i >= skip) Ops::put(y + lane_column(i, second), AXPBY && beta != 0.0f ? fmaf(beta, old[i], v[i]) : v[i]);
+}
 
 }  // namespace dgsp

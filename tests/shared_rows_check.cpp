@@ -1,6 +1,8 @@
 // Drives the agreement on shared rows with threads in place of waves: shared_rows_check <name of a check>; exit code 0: it holds.
+#include "../paper_2106_16064_amd/csrc/lane_columns.hpp"
 #include "../paper_2106_16064_amd/csrc/shared_rows.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
@@ -19,6 +21,7 @@ struct Words {
         return __atomic_compare_exchange_n(p, &seen, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
     }
     static void pause() { std::this_thread::yield(); }
+    static void put(float* p, float v) { *p = v; }
 };
 
 struct Row {
@@ -96,6 +99,67 @@ bool every_claim_ends() {
     return word == 41;
 }
 
+// A row of N columns in column blocks of `per`, each with a word of its own: the wave that the row starts in and one more wave a block.
+struct BlockedRow {
+    int N, per;
+    float beta;
+    std::vector<float> y;
+    std::vector<RowWord> words;
+    static constexpr RowWord kCall = 40;
+
+    BlockedRow(int N, int per, float beta) : N(N), per(per), beta(beta), y(N), words((N + per - 1) / per, 7) {
+        for (int n = 0; n < N; ++n) y[n] = beta == 0.0f ? NAN : (float)(8 * n);
+    }
+    template <typename F>
+    void lanes(unsigned block, F&& f) {
+        for (int gl = 0; gl * 4 < per; ++gl) {
+            const dgsp::LaneColumns c = dgsp::lane_columns<4, true>(block, per, gl, N);
+            if (c.any) f(c);
+        }
+    }
+    void start(unsigned block) {
+        const RowWord found = dgsp::claim_row<Words>(&words[block], kCall);
+        if (dgsp::mine_to_clear(found, kCall))
+            lanes(block, [&](const dgsp::LaneColumns& c) { dgsp::clear_row<Words, 4, true>(&y[c.first], beta, c.skip); });
+        dgsp::publish_start<Words>(&words[block], kCall, found);
+    }
+    void give(unsigned block, float part) {
+        const bool sum = dgsp::row_has_sum<Words>(&words[block], kCall);
+        lanes(block, [&](const dgsp::LaneColumns& c) {
+            float v[4];
+            for (int i = 0; i < 4; ++i) v[i] = part * (float)(c.first + i + 1);
+            if (!sum) dgsp::write_part<Words, 4, true>(&y[c.first], v, beta, c.skip);
+            else for (int i = c.skip; i < 4; ++i) y[c.first + i] += v[i];
+        });
+        if (!sum) dgsp::publish_part<Words>(&words[block], kCall);
+    }
+    bool whole(float sum) const {
+        for (int n = 0; n < N; ++n)
+            if (y[n] != (beta == 0.0f ? 0.0f : beta * (float)(8 * n)) + sum * (float)(n + 1)) return false;
+        return true;
+    }
+};
+
+// Every order of the steps of the last two column blocks, the last with one to four columns, with the start first or not.
+bool ragged_blocks() {
+    for (int N = 9; N <= 16; ++N)
+        for (const float beta : {0.0f, 0.5f})
+            for (int late = 0; late < 4; ++late) {               // bit b: in block b a part comes before the start
+                int order[] = {0, 0, 0, 1, 1, 1};
+                do {
+                    BlockedRow row(N, 8, beta);
+                    int step[2] = {0, 0};
+                    for (const int b : order) {
+                        const int s = step[b]++;
+                        const int what = (late >> b & 1) ? (s == 0 ? 1 : s == 1 ? 0 : 2) : s;
+                        if (what == 0) row.start((unsigned)b); else row.give((unsigned)b, what == 1 ? 3.0f : 5.0f);
+                    }
+                    if (!row.whole(8.0f)) return false;
+                } while (std::next_permutation(order, order + 6));
+            }
+    return true;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -103,6 +167,7 @@ int main(int argc, char** argv) {
     if (!strcmp(argv[1], "every_part_once")) return every_part_once(0) ? 0 : 1;
     if (!strcmp(argv[1], "the_start_comes_late")) return every_part_once(200) ? 0 : 1;
     if (!strcmp(argv[1], "in_turn")) return in_turn() ? 0 : 1;
+    if (!strcmp(argv[1], "ragged_blocks")) return ragged_blocks() ? 0 : 1;
     if (!strcmp(argv[1], "every_claim_ends")) return every_claim_ends() ? 0 : 1;
     return 2;
 }

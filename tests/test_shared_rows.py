@@ -13,7 +13,7 @@ from paper_2106_16064_amd import workloads as wl
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends"])
+@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends", "ragged_blocks"])
 def test_waves_agree_on_a_row(check, tmp_path):
     exe = tmp_path / "shared_rows_check"
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-o", str(exe), os.path.join(ROOT, "tests", "shared_rows_check.cpp")],
@@ -81,6 +81,33 @@ def test_shared_rows(name, make):
                 dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, *arrays, dX, Y, -2.0, beta, algo)
                 ok, worst = oracle.within_bound(Y.cpu().numpy(), -2.0 * ref + beta * Y0, 2.0 * bnd + beta * np.abs(Y0), 1e-5)
                 assert ok, worst
+
+
+def long_rows():
+    """Few rows, all over many chunks."""
+    return rows_of(np.concatenate([[0, 0], np.full(30, 700), [3000, 0, 65, 2500], np.full(20, 333)]), 500, 5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [257, 300, 16129, 16130, 16131, 16132])
+def test_shared_rows_in_several_column_blocks(N):
+    """From 16129 on there are column blocks of 256 and the last one may have a single column: what is cleared and written under the
+    sums of a row stays off the columns of the block before."""
+    import torch
+    A = long_rows()
+    D = dg.DeviceCsr(A)
+    X = wl.dense_matrix(A.K, N, "normal", seed=N)
+    ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+    dX = torch.from_numpy(X).cuda()
+    Y = torch.empty((A.M, N), device="cuda")
+    print(f"[case] shared rows in several column blocks N={N}", flush=True)
+    for call in (lambda: dg.dgsp_spmm_csr(A.M, A.K, N, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR),
+                 lambda: dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR)):
+        for _ in range(3):
+            Y.fill_(float("nan"))
+            call()
+            ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+            assert ok, worst
 
 
 @pytest.mark.gpu

@@ -7,13 +7,12 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
-#include <atomic>
 #include <map>
 #include <mutex>
-#include <random>
 #include <type_traits>
 #include <utility>
 
+#include "call_numbers.hpp"
 #include "dgsp_internal.h"
 #include "dgsp_kernels.hpp"
 #include "stat_pool.hpp"
@@ -493,15 +492,11 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
 }
 
 // Words by which the waves of `chunks` chunks agree on the rows they share, in memory of the call's; none if it has none to give
-// (the prepare launch clears these rows then).  Counted per process from a random number on, `call` is even.
+// (the prepare launch clears these rows then).
 RowSharing make_sharing(const Problem& p, size_t chunks) {
-    static std::atomic<RowWord> calls{[] {
-        std::random_device device;
-        return ((RowWord)device() << 32 | device()) & ~1ull;
-    }()};
     if (!p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0) return RowSharing{nullptr, 0};
     void* mem = p.more->workspace(p.more->context, chunks * sizeof(RowWord));
-    return RowSharing{static_cast<RowWord*>(mem), mem ? calls.fetch_add(2, std::memory_order_relaxed) : 0};
+    return RowSharing{static_cast<RowWord*>(mem), mem ? next_call_number() : 0};
 }
 
 // Blocks of the grid that shares the nnz + M merge-path items of a balanced kernel, `tile` items per

@@ -11,8 +11,8 @@
 // between no wave waits for another.  Every claim is published, whether there turns out to be a row or not, so a wait ends for
 // any contents of the row pointers.
 //
-// `call` is even and no other call's, so that the words need no clearing: memory that other kernels have used holds one of the two
-// numbers with a chance of 2^-62 a word.
+// `call` is even and of no other call of the process (next_call_number()), so that the words need no clearing: memory that other
+// kernels or other processes have used holds one of the two numbers with a chance of 2^-62 a word.
 //
 // `Ops` accesses words that all waves see: load(p), store(p, v), exchange(p, v), replace(p, seen, v) - compare and swap
 // which leaves what it found in `seen` -, and pause(); put(y, v) stores a float so that all waves find it behind the word's publication.
@@ -26,7 +26,7 @@ namespace dgsp {
 
 using RowWord = unsigned long long;
 
-// The wave that the row starts in: what it found, for start_row().
+// The wave that the row starts in: what it found, for mine_to_clear() and publish_start().
 template <typename Ops>
 DGSP_HOST_DEVICE RowWord claim_row(RowWord* word, RowWord call) { return Ops::exchange(word, call); }
 

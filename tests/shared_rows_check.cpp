@@ -1,4 +1,5 @@
 // Drives the agreement on shared rows with threads in place of waves: shared_rows_check <name of a check>; exit code 0: it holds.
+#include "../paper_2106_16064_amd/csrc/call_numbers.hpp"
 #include "../paper_2106_16064_amd/csrc/lane_columns.hpp"
 #include "../paper_2106_16064_amd/csrc/shared_rows.hpp"
 
@@ -160,6 +161,16 @@ bool ragged_blocks() {
     return true;
 }
 
+// Even numbers, one after the other and none twice; without random bytes, too, and nothing is thrown.
+bool call_numbers() {
+    const RowWord first = dgsp::next_call_number(), second = dgsp::next_call_number();
+    if (first % 2 != 0 || second != first + 2) return false;
+    if (dgsp::first_call_number([](void* p, size_t n) { memset(p, 0xff, n); return true; }) != ~1ull) return false;
+    const auto none = [](void*, size_t) { return false; };
+    const RowWord one = dgsp::first_call_number(none), other = dgsp::first_call_number(none);
+    return one % 2 == 0 && other % 2 == 0 && one != other && one != first;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -168,6 +179,7 @@ int main(int argc, char** argv) {
     if (!strcmp(argv[1], "the_start_comes_late")) return every_part_once(200) ? 0 : 1;
     if (!strcmp(argv[1], "in_turn")) return in_turn() ? 0 : 1;
     if (!strcmp(argv[1], "ragged_blocks")) return ragged_blocks() ? 0 : 1;
+    if (!strcmp(argv[1], "call_numbers")) return call_numbers() ? 0 : 1;
     if (!strcmp(argv[1], "every_claim_ends")) return every_claim_ends() ? 0 : 1;
     return 2;
 }

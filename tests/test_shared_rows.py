@@ -13,12 +13,19 @@ from paper_2106_16064_amd import workloads as wl
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends", "ragged_blocks"])
+@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends", "ragged_blocks", "call_numbers"])
 def test_waves_agree_on_a_row(check, tmp_path):
     exe = tmp_path / "shared_rows_check"
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-o", str(exe), os.path.join(ROOT, "tests", "shared_rows_check.cpp")],
                    check=True)
     assert subprocess.run([str(exe), check], timeout=100).returncode == 0
+
+
+def test_the_library_takes_random_numbers_without_exceptions():
+    """Its entry points are C functions, and most of their callers never share rows: std::random_device throws where there is no source."""
+    names = subprocess.run(["nm", "-D", "--undefined-only", os.path.join(ROOT, "paper_2106_16064_amd", "libdgsp.so")],
+                           check=True, capture_output=True, text=True).stdout
+    assert "getrandom" in names and "random_device" not in names
 
 
 def rows_of(lens, K, seed):

@@ -493,8 +493,9 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
 
 // Words by which the waves of `chunks` chunks agree on the rows they share, in memory of the call's; none if it has none to give
 // (the prepare launch clears these rows then).
+inline bool may_share(const Problem& p) { return p.more && p.more->workspace && p.phase == DGSP_PHASE_ALL && p.switches == 0; }
 RowSharing make_sharing(const Problem& p, size_t chunks) {
-    if (!p.more || !p.more->workspace || p.phase != DGSP_PHASE_ALL || p.switches != 0) return RowSharing{nullptr, 0};
+    if (!may_share(p)) return RowSharing{nullptr, 0};
     void* mem = p.more->workspace(p.more->context, chunks * sizeof(RowWord));
     return RowSharing{static_cast<RowWord*>(mem), mem ? next_call_number() : 0};
 }
@@ -608,7 +609,7 @@ int launch_nb_pr_hot(const Problem& p) {
     if (p.phase == DGSP_PHASE_PREPARE) return DGSP_OK;
     const Scaling sc{p.alpha, p.beta};
     const auto launch = [&](auto whole, auto scaled) -> int {
-        DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, false, true>), grid, kHotThreads, p.M,
+        DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, false, false, true>), grid, kHotThreads, p.M,
                             p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, RowSharing{}, hot);
         return DGSP_OK;
     };
@@ -623,6 +624,8 @@ int launch_nb_pr_v(const Problem& p) {
     // the row store addresses a step's rows with 32-bit byte offsets: tile rows * N * 4 must fit
     if (col_groups > 65535u || p.ldy > kBalancedLdyMax) return DGSP_ERR_UNSUPPORTED;
     if constexpr (V <= kHotWidths) { if (p.N == V && p.ldx == V && p.hot_columns && p.switches == 0) return launch_nb_pr_hot<V>(p); }
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
     const bool forced_blocks = (p.switches & (DGSP_ABL_ENTRY_BLOCKS | DGSP_ABL_SERIAL_SEGMENT_SCAN)) != 0;
     // A banded matrix (neighbouring rows share their columns: stencils, bands): its gathers hit the L1 and are bound
     // by the rate of the CU's address unit, not by latency, so gathers requested a block ahead gain nothing, and at up
@@ -633,9 +636,21 @@ int launch_nb_pr_v(const Problem& p) {
     const bool banded_x = banded(p) && !forced_blocks;
     const bool tiled = !kNbPrStreams<V> || (p.switches & DGSP_ABL_ITEM_TILES) != 0 ||
                        (!forced_blocks && (p.nnz < kNbPrStreamNnzMin || banded_x));   // unknown entry count (-1): tiles
-    int resident = resident_blocks_per_cu(nb_pr_tiled_kernel<V, KQ, false, false>);
-    if constexpr (kNbPrStreams<V>) { if (!tiled) resident = resident_blocks_per_cu(nb_pr_kernel<V, KQ, false>); }
-    const bool few_waves = banded_x && V <= 3;
+    // of the form that is launched (that of the plain one for the scaled one, which keeps two resident at four columns, was three: R-MAT
+    // 2^20 x 32 249 / 200 us with three / two, lognormal rows of 30 492 / 456 us, Zipf rows of 50 741 / 751 us)
+    const auto resident_of = [&](auto scaled, auto shares) -> int {
+        if constexpr (kNbPrStreams<V>) {
+            if (!tiled) return resident_blocks_per_cu(nb_pr_kernel<V, KQ, false, decltype(scaled)::value, decltype(shares)::value>);
+        }
+        return resident_blocks_per_cu(nb_pr_tiled_kernel<V, KQ, decltype(scaled)::value, decltype(shares)::value>);
+    };
+    const int resident = p.scaled ? may_share(p) ? resident_of(yes, yes) : resident_of(yes, no)
+                                  : may_share(p) ? resident_of(no, yes) : resident_of(no, no);
+    // Entry blocks at one and two columns, too: the gathers of two workgroups are as many as the L1 holds misses for, and more
+    // would only be shorter shares (R-MAT 2^20 x 32 at N = 1 / 2 on 2 / 3 / 4 workgroups per CU 154.6 / 156.5 / 164.0 and
+    // 171.0 / 173.2 / 179.5 us, Zipf rows of 50 317.8 / 321.0 / 332.7 and 515.6 / 515.7 / 519.7 us, in the scaled form at N = 2, which
+    // keeps three resident, 521.9 / 521.7 / 560.0 us).
+    const bool few_waves = (banded_x && V <= 3) || (!tiled && V <= 2);
     const dim3 grid(balanced_blocks(p, tile, resident, true, 1, few_waves ? 2 : 0), col_groups);
     // a wave alone takes 512 entries in about 4 us
     const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
@@ -650,27 +665,24 @@ int launch_nb_pr_v(const Problem& p) {
                             p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, snap, sc, sharing);
                 return DGSP_OK;
             };
-            if (sharing.words) return p.scaled ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
-            return p.scaled ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
+            if (sharing.words) return p.scaled ? launch(yes, yes) : launch(no, yes);
+            return p.scaled ? launch(yes, no) : launch(no, no);
         } else if constexpr (kNbPrStreams<V>) {
-            const auto launch = [&](auto whole) -> int {
-                constexpr bool kSnap = decltype(whole)::value;
-                if constexpr (V <= 2 && !kSnap) {
-                    if (p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) {
-                        DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                                    p.Y, sc, sharing);
-                        return DGSP_OK;
-                    }
-                }
-                if (p.scaled)
-                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X,
-                                p.Y, sc, sharing);
-                else
-                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, kSnap>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc,
-                                sharing);
+            const auto launch = [&](auto whole, auto scaled, auto shares) -> int {
+                DGSP_LAUNCH((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, decltype(shares)::value>), grid, p.M, p.K,
+                            p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, sharing);
                 return DGSP_OK;
             };
-            return snap ? launch(std::true_type{}) : launch(std::false_type{});
+            if constexpr (V <= 2) {
+                if (p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) {
+                    DGSP_LAUNCH((nb_pr_kernel<V, KQ, false, false, false, true>), grid, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals,
+                                p.X, p.Y, sc, sharing);
+                    return DGSP_OK;
+                }
+            }
+            if (snap) return p.scaled ? launch(yes, yes, no) : launch(yes, no, no);
+            if (sharing.words) return p.scaled ? launch(no, yes, yes) : launch(no, no, yes);
+            return p.scaled ? launch(no, yes, no) : launch(no, no, no);
         }
     }
     return DGSP_OK;

@@ -1270,7 +1270,7 @@ struct HotColumns { const unsigned* table; int shift; };
 // eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 8.7
 // million of 14.1 by the L2s' counters, streams included: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
 // switched off, and by offset or by execution mask, makes no difference, nor would packing the others into fewer instructions.
-template <int V, int KQ, bool SNAP, bool AXPBY = false, bool SERIAL_SCAN = false, bool HOT = false>
+template <int V, int KQ, bool SNAP, bool AXPBY, bool SHARES = false, bool SERIAL_SCAN = false, bool HOT = false>
 __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M, long long K, int N, int ldx, int ldy,
                                                         const int* __restrict__ rowptr,
                                                         const int* __restrict__ colidx,
@@ -1305,7 +1305,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     auto y_of = [&](int row) { return Y + (size_t)row * ldy + n0; };
     // rows shared with other waves, where no launch has cleared them; one lane's business
     RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
-    const bool shares = !SNAP && !HOT && sharing.words != nullptr;
+    constexpr bool shares = SHARES;
+    static_assert(!SHARES || (!SNAP && !HOT && !SERIAL_SCAN), "no shared rows, or a prepare launch for them");
     auto give_to_row = [&](unsigned word, float* y, const float (&v)[V]) {
         if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
             add_to_row(y, v);

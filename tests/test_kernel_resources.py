@@ -1,0 +1,40 @@
+"""What the compiler gave the kernels of the built library: registers and spills, from the notes of its code object."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def resources(tmp_path_factory):
+    """Mangled kernel name -> its numbers."""
+    at = tmp_path_factory.mktemp("code")
+    tool = lambda name, *args: subprocess.run([os.path.join(LLVM, name), *args], check=True, capture_output=True, text=True).stdout  # noqa: E731
+    tool("llvm-objcopy", f"--dump-section=.hip_fatbin={at}/bundle", os.path.join(ROOT, "paper_2106_16064_amd", "libdgsp.so"), f"{at}/copy")
+    tool("clang-offload-bundler", "--unbundle", "--type=o", f"--input={at}/bundle", f"--output={at}/code",
+         "--targets=hipv4-amdgcn-amd-amdhsa--gfx950")
+    found, name = {}, None
+    for line in tool("llvm-readelf", "--notes", f"{at}/code").splitlines():
+        m = re.match(r"    \.(name|sgpr_spill_count|vgpr_count|vgpr_spill_count): +(\S+)", line)
+        if m and m[1] == "name":
+            name = m[2]
+            found[name] = {}
+        elif m:
+            found[name][m[1]] = int(m[2])
+    return found
+
+
+def test_forms_that_share_no_rows_pay_nothing_for_those_that_do(resources):
+    """nb_pr_kernel<V, KQ, SNAP, AXPBY, SHARES, ...>: with the choice left to the run, these spilled 22 scalar registers and more, and at
+    two columns the plain form lost one of four waves a SIMD (128 vector registers)."""
+    forms = {name: r for name, r in resources.items() if re.search(r"nb_pr_kernelILi\dELi2ELb\dELb\dELb0E", name)}
+    assert len(forms) >= 4 * 8
+    for name, r in forms.items():
+        assert r["sgpr_spill_count"] == 0 and r["vgpr_spill_count"] == 0, name
+    for v in (1, 2):
+        plain, = [r for name, r in forms.items() if f"nb_pr_kernelILi{v}ELi2ELb0ELb0ELb0ELb0ELb0E" in name]
+        assert plain["vgpr_count"] <= 128

@@ -458,8 +458,8 @@ int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int 
 }
 
 // How `waves` waves on each XCD share out the items (`lists` times: column blocks that are a grid dimension) with the help of
-// memory of the caller's; nothing if it has none to give.  About half of a wave's share (`share` items) is its first piece, the rest
-// goes by chunks of 512 items, 1024 from shares of 4096 on.  With 0.3 / 0.5 to 0.6 of the share R-MAT 2^20 x 16 at N = 32 / 64 / 128
+// memory of the caller's; nothing if it has none to give or where a wave's share is below `least` items.  About half of a share is its
+// first piece, the rest goes by chunks of 512 items, 1024 from shares of 4096 on.  With 0.3 / 0.5 to 0.6 of the share R-MAT 2^20 x 16 at N = 32 / 64 / 128
 // 227.7 / 440.1 / 872.4 and 225.9 / 440.2 / 868.7 us, 2^20 x 8 at N = 41 240.6 and 237.5 us, 2^19 x 16 at N = 100 397.4 and
 // 390.4 us (0.8 of it at N = 128 1018 us, equal shares 1024 us); N = 32 with chunks of 256 / 512 / 768 / 1024 items 244 / 230 / 228.5 /
 // 227 us (equal shares 248 us), and no better with chunks of 1024 first and smaller ones at the end (237 us and more): what a
@@ -468,9 +468,10 @@ int launch_prepare(const Problem& p, unsigned parts, unsigned quantum_log2, int 
 // N = 32 228.7 -> 228.0 us.
 constexpr double kFirstPiece = 0.55;
 constexpr unsigned kQueueHelpers = 256;      // waves of an XCD that help others out: 0 / 32 / 128 of 512 at N = 128 1045 / 1018 / 969 us
-ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsigned waves, unsigned lists) {
+ChunkQueues make_queues(const Problem& p, unsigned parts, unsigned waves, unsigned lists, long long least, unsigned fewest_a_row) {
     ChunkQueues q{};
-    const long long items = p.size + (long long)p.M;
+    const long long items = p.size + (long long)p.M, share = items / parts / waves;
+    if (share < least) return q;
     const unsigned size_log2 = share >= 4096 ? 10 : 9;
     const long long chunks = (items + (1ll << size_log2) - 1) >> size_log2;
     const unsigned run = (unsigned)((double)(chunks / parts) * kFirstPiece / waves);
@@ -488,6 +489,7 @@ ChunkQueues make_queues(const Problem& p, long long share, unsigned parts, unsig
     q.parts_log2 = (unsigned)__builtin_ctz(parts); q.waves = waves; q.run = run; q.helpers = kQueueHelpers;
     q.parts_per_chunk = (float)parts / (float)chunks;
     q.per_run = 1.0f / (float)run;
+    q.fewest = (unsigned)(least * parts * waves); q.fewest_a_row = fewest_a_row;
     return q;
 }
 
@@ -773,8 +775,8 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     // 2^18 x 32 at N = 48 126.6 / 140.2 us, 2^18 Zipf rows of 16 at N = 64 163.0 / 170.6 us, 2^18 rows of exactly 16 163.5 / 171.1 us.
     // A bound of the entry count (the length of colidx) will do, the kernels fit the chunks to the matrix: calls without statistics, R-MAT
     // 2^20 x 16 at N = 32 / 64 250 / 574 -> 228 / 497 us, 2^20 x 8 at N = 41 258 -> 231 us, 2^20 Zipf rows of 16 at N = 64
-    // 662 -> 632 us, 635 441 Poisson rows of 13 at N = 60 434 -> 421 us.  With arrays four times as long as the matrix, whose true
-    // share is then below the line: 2^18 x 16 at N = 64 85.3 -> 93.9 us, 2^19 Zipf rows of 10 at N = 100 416 -> 427 us.
+    // 662 -> 632 us, 635 441 Poisson rows of 13 at N = 60 434 -> 421 us; where the true share turns out to be below the line they
+    // make the shares equal (ChunkQueues::fit()).
     ChunkQueues queues{};
     dim3 queue_grid = grid;
     if (XBUF && !snap && p.size > 0 && grid.x % kXcd == 0 && p.size / p.M >= run_dealt_below(LOGG)) {
@@ -782,8 +784,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
         // no more than are resident: what is started late finds the queues empty
         if (pinned) queue_grid.x = std::min<unsigned>(grid.x, (unsigned)(device_info().cus * resident) / kXcd * kXcd);
         const unsigned waves = queue_grid.x / kXcd * kWavesPerBlock;
-        const long long share = (p.size + (long long)p.M) / parts / waves;
-        if (share >= 2048 && (share << LOGG) >= 32768) queues = make_queues(p, share, parts, waves, grid.y);
+        queues = make_queues(p, parts, waves, grid.y, std::max(2048, 32768 >> LOGG), run_dealt_below(LOGG));
     }
     const unsigned chunks = queues.starts ? queues.chunks : chunk_groups * kWavesPerBlock;
     RowSharing sharing{};

@@ -16,6 +16,7 @@
 //     number of stored entries to be read on the device from rowptr[M].
 #pragma once
 
+#include "chunk_queues.hpp"
 #include "dgsp_device.hpp"
 #include "shared_rows.hpp"
 
@@ -417,70 +418,6 @@ __global__ __launch_bounds__(kBlock) void rs_sr_direct_kernel(int M, int N, int 
 // without entries).  Every other row is written once with a plain store by the
 // chunk that holds its end marker.
 
-// The even split of the Q quanta into `parts` chunks: chunk c starts at quantum floor(c * Q / parts),
-// so chunks differ by at most one quantum and the longer ones are spread over the whole list (put
-// first, they would all fall to the first XCDs).  The quotients are formed in fp64: numerators stay
-// below 2^53 and a non-integer quotient n / m lies at least 1 / m away from an integer, far more than
-// the rounding of one correctly rounded division, so the floors are exact - and much cheaper here
-// than 64-bit integer division, which the per-row test of the prepare kernel would pay twice.
-struct EvenSplit {
-    unsigned Q, parts, shift;     // quanta, chunks, log2 of the quantum
-    __device__ __forceinline__ EvenSplit(unsigned items, unsigned parts_, unsigned quantum_log2) {
-        const unsigned quantum = 1u << quantum_log2;
-        Q = (items >> quantum_log2) + ((items & (quantum - 1)) != 0);
-        parts = parts_;
-        shift = quantum_log2;
-    }
-    // first item of chunk c (c may be `parts`: the end of the list, rounded up to a quantum)
-    __device__ __forceinline__ unsigned start(unsigned c) const {
-        const double n = (double)((unsigned long long)c * Q);
-        return (unsigned)(n / (double)parts) << shift;
-    }
-    // chunk that holds item d: the largest c with floor(c * Q / parts) <= d's quantum
-    __device__ __forceinline__ unsigned chunk_of(unsigned d) const {
-        const unsigned long long q = d >> shift;
-        const double n = (double)((q + 1) * parts - 1);
-        return (unsigned)(n / (double)Q);
-    }
-};
-
-// How a call with a workspace shares out the items (nb_sr_run_kernel).  `chunks` chunks of 2^size_log2 items are dealt to
-// `parts` parts, one per XCD that works on a list.  The first chunks of a part are its waves' shares, `run` consecutive ones a
-// wave, a single piece; the others are taken one by one by whoever is done, first from the wave's own part.  In the
-// workspace: `taken`, a counter for each XCD's queue, kQueuePitch words apart, and `starts`, for each chunk and for the end of the
-// list the number of rows that ended before it, which saves the waves their searches.
-constexpr unsigned kQueuePitch = 32;
-struct ChunkQueues {
-    unsigned* taken; int* starts;
-    unsigned chunks, size_log2, counters, parts_log2, waves, run, helpers;
-    float parts_per_chunk, per_run;                      // 2^parts_log2 / chunks, 1 / run
-    // at most 2^23 chunks, 8 parts
-    __device__ __forceinline__ unsigned part_from(unsigned part) const { return (chunks * part) >> parts_log2; }
-    __device__ __forceinline__ unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
-    // The host counts with a bound of the entries where it does not know them.  Fewer items: fewer chunks of the same size, and shorter
-    // first pieces to the same share.
-    __device__ __forceinline__ void fit(unsigned items) {
-        const unsigned quanta = EvenSplit(items, 1u, size_log2).Q;
-        if (quanta >= chunks) return;
-        run = (unsigned)((float)run * ((float)quanta / (float)chunks));     // 0: all by the queues
-        chunks = quanta;
-        parts_per_chunk = (float)(1u << parts_log2) / (float)chunks;
-        per_run = 1.0f / (float)run;
-    }
-    // do chunks c1 and c2 >= c1 belong to one piece?  (c2 in a queue: a piece is a chunk; else no multiple of `run` lies behind c1)
-    __device__ __forceinline__ bool one_piece(unsigned c1, unsigned c2) const {
-        unsigned part = (unsigned)((float)c2 * parts_per_chunk);            // one off at most
-        if (part_from(part + 1u) <= c2) ++part;
-        else if (part_from(part) > c2) --part;
-        const unsigned at = c2 - part_from(part);
-        if (at >= waves * run) return c1 == c2;
-        unsigned into = at - (unsigned)((float)at * per_run) * run;         // into the piece: at % run
-        if ((int)into < 0) into += run;
-        else if (into >= run) into -= run;
-        return c2 - c1 <= into;
-    }
-};
-
 // Zeroes the rows whose items do not all lie in one piece of the partition (beta != 0, the scaled
 // variants: multiplies them by beta instead, so that the partial sums added later land on beta * Y).
 // The pieces are the `parts` chunks of the even split with quanta of
@@ -503,7 +440,7 @@ __global__ __launch_bounds__(kBlock) void nb_prepare_kernel(int M, int N, int ld
                                                              int tile_log2, float beta, ChunkQueues queues, int empty_rows) {
     const long long row0 = ((long long)blockIdx.x * kBlock + threadIdx.x) * R;
     const unsigned items = (unsigned)rowptr[M] + (unsigned)M;               // on its way with the rows' bounds
-    if constexpr (QUEUES) { queues.fit(items); parts = queues.chunks; }
+    if constexpr (QUEUES) { queues.fit(items, (unsigned)M); parts = queues.chunks; quantum_log2 = queues.size_log2; }
     unsigned bound[R + 1];
     if (R == 1 && row0 < M) {
         bound[0] = (unsigned)rowptr[row0];
@@ -2200,7 +2137,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         wg = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
     }
-    if constexpr (QUEUED) queues.fit(items);
+    if constexpr (QUEUED) queues.fit(items, (unsigned)M);
     const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, QUEUED ? queues.size_log2 : 6u);
     // queue q: what the waves of XCD q leave of its part of the chunks
     const auto part_of = [&](unsigned q) { return pinned_blocks ? q / pinned_blocks : q; };
@@ -2213,7 +2150,10 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
     for (;;) {                                           // one piece, or one after the other
     unsigned chunk = wg * kWavesPerBlock + (unsigned)wib, chunk_end = chunk + 1u;
     if constexpr (QUEUED) {
-        if (first_piece) {
+        if (queues.run == 0u) {                          // equal shares: chunk `chunk`, nothing else
+            if (!first_piece || chunk >= queues.chunks) return;
+            first_piece = false;
+        } else if (first_piece) {
             chunk = queues.part_from(part_of(xcd)) + own * queues.run;
             chunk_end = chunk + queues.run;
             first_piece = false;

@@ -1,11 +1,25 @@
 """Products whose waves take chunks from queues (nb_sr_run_kernel, QUEUED), against the oracle.  The queues live in memory that the
 call asks torch's allocator for, so its statistics tell that a product ran this way."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
 import oracle
 from paper_2106_16064_amd import binding as dg
 from paper_2106_16064_amd import workloads as wl
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("check", ["pieces", "fits", "even_split"])
+def test_how_items_are_shared_out(check, tmp_path):
+    """The arithmetic that the prepare launch and the product have to agree on, against counting."""
+    exe = tmp_path / "chunk_queues_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(exe), os.path.join(ROOT, "tests", "chunk_queues_check.cpp")], check=True)
+    assert subprocess.run([str(exe), check], timeout=100).returncode == 0
 
 
 def rows_of(lens, K, seed):

@@ -1,5 +1,6 @@
 """Products whose waves take chunks from queues (nb_sr_run_kernel, QUEUED), against the oracle.  The queues live in memory that the
-call asks torch's allocator for, so its statistics tell that a product ran this way."""
+call asks torch's allocator for, so its statistics tell that a product ran this way: by how much it asked for, as rows that waves
+share without queues take memory, too."""
 import os
 import subprocess
 
@@ -77,6 +78,22 @@ def allocations(call):
     return torch.cuda.memory_stats()["allocation.all.allocated"] - before
 
 
+def requested(call):
+    """Bytes of the one block that a call asks for, 0 for none."""
+    import torch
+    stats = torch.cuda.memory_stats()
+    before = stats["allocation.all.allocated"], stats["requested_bytes.all.allocated"]
+    call()
+    stats = torch.cuda.memory_stats()
+    assert stats["allocation.all.allocated"] - before[0] <= 1
+    return stats["requested_bytes.all.allocated"] - before[1]
+
+
+def queue_bytes(entries, M, lists=1):
+    """What queues over so many entries take: a counter for each XCD in a line of its own, the first rows of chunks of 512 or 1024 items."""
+    return {8 * lists * 128 + 4 * (-(-(entries + M) // size) + 1) for size in (512, 1024)}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name, make, N", CASES, ids=[c[0] for c in CASES])
 def test_products_from_queues(name, make, N):
@@ -88,11 +105,12 @@ def test_products_from_queues(name, make, N):
     ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
     dX, Y = torch.from_numpy(X).cuda(), torch.full((A.M, N), float("nan"), device="cuda")
     print(f"[case] queues {name} N={N}", flush=True)
-    assert allocations(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) == 1
+    queues = queue_bytes(A.nnz, A.M, 3 if N == 300 else 1)
+    assert requested(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) in queues
     ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
     assert ok, worst
     Y = torch.from_numpy(Y0).cuda()
-    assert allocations(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) == 1
+    assert requested(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) in queues
     ok, worst = oracle.within_bound(Y.cpu().numpy(), -0.5 * ref + 1.5 * Y0, 0.5 * bnd + 1.5 * np.abs(Y0), 1e-5)
     assert ok, worst
 
@@ -112,20 +130,27 @@ def test_arrays_longer_than_the_matrix(make, N, longer):
     ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
     dX, Y = torch.from_numpy(X).cuda(), torch.full((A.M, N), float("nan"), device="cuda")
     print(f"[case] queues, arrays {longer} times as long N={N}", flush=True)
-    assert allocations(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) == 1
+    queues = queue_bytes(room, A.M)
+    assert requested(lambda: dg.dgsp_spmm_csr_phase(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, dg.NB_SR, dg.PHASE_ALL, D.features)) in queues
     ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
     assert ok, worst
     Y = torch.from_numpy(Y0).cuda()
-    assert allocations(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) == 1
+    assert requested(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, room, D.rowptr, colidx, vals, dX, Y, -0.5, 1.5, dg.NB_SR, D.features)) in queues
     ok, worst = oracle.within_bound(Y.cpu().numpy(), -0.5 * ref + 1.5 * Y0, 0.5 * bnd + 1.5 * np.abs(Y0), 1e-5)
     assert ok, worst
 
 
+def short_rows():
+    return rows_of(np.random.default_rng(7).integers(0, 9, 2_200_000), 40_000, 8)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("make, N, longer", [(graph, 41, 1.0), (odd_rows, 64, 1.3), (hub, 128, 30.0), (lambda: graph(17, 20), 41, 8.0),
-                                             (lambda: rows_of(np.ones(3, int), 500, 1), 64, 4_000_000.0)])
+                                             (lambda: graph(16, 20), 128, 16.0), (lambda: rows_of(np.full(41, 100_000), 30_000, 3), 300, 4.0),
+                                             (short_rows, 41, 3.0), (lambda: rows_of(np.ones(3, int), 500, 1), 64, 4_000_000.0)])
 def test_calls_that_know_no_entry_count(make, N, longer):
-    """The length of colidx stands for it: queues are fitted to the matrix, down to none of it in first pieces and a single chunk."""
+    """The length of colidx stands for it: queues are fitted to the matrix, from the fourth on down to equal shares - pinned column blocks,
+    three lists, rows too short for queues, a single chunk."""
     import torch
     A = make()
     D = dg.DeviceCsr(A)
@@ -138,7 +163,7 @@ def test_calls_that_know_no_entry_count(make, N, longer):
     for algo in (dg.AUTO, dg.NB_SR):
         Y = torch.full((A.M, N), float("nan"), device="cuda")
         print(f"[case] queues without an entry count, arrays {longer} times as long N={N}", flush=True)
-        dg.dgsp_spmm_csr(A.M, A.K, N, D.rowptr, colidx, vals, dX, Y, algo)
+        assert requested(lambda: dg.dgsp_spmm_csr(A.M, A.K, N, D.rowptr, colidx, vals, dX, Y, algo)) in queue_bytes(room, A.M, 3 if N == 300 else 1)
         ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
         assert ok, worst
 

@@ -38,3 +38,21 @@ def test_forms_that_share_no_rows_pay_nothing_for_those_that_do(resources):
     for v in (1, 2):
         plain, = [r for name, r in forms.items() if f"nb_pr_kernelILi{v}ELi2ELb0ELb0ELb0ELb0ELb0E" in name]
         assert plain["vgpr_count"] <= 128
+
+
+def waves_a_simd(r):
+    return min(8, 512 // (-(-r["vgpr_count"] // 8) * 8))
+
+
+def test_forms_that_share_rows_or_queue_keep_as_many_workgroups(resources):
+    """launch_nb_sr_run_v sizes the grid by the form without either, per lane layout and scaling."""
+    plain = {name: r for name, r in resources.items() if re.search(r"nb_sr_run_kernelILi\dELb\dELb\dELb0ELb0E", name)}
+    assert len(plain) >= 7 * 3
+    others = 0
+    for name, r in plain.items():
+        for form in ("ELb1ELb0E", "ELb0ELb1E"):
+            other = resources.get(re.sub(r"(nb_sr_run_kernelILi\dELb\dELb\d)ELb0ELb0E", r"\1" + form, name))
+            if other:
+                others += 1
+                assert waves_a_simd(other) >= waves_a_simd(r), name
+    assert others >= 7 * 3

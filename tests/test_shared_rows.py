@@ -9,6 +9,7 @@ import pytest
 import oracle
 from paper_2106_16064_amd import binding as dg
 from paper_2106_16064_amd import workloads as wl
+from test_chunk_queues import queue_bytes, requested
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -70,11 +71,18 @@ def test_shared_rows(name, make):
         for algo in (dg.NB_PR, dg.NB_SR):
             print(f"[case] shared rows {name} N={N} algo={algo}", flush=True)
             Y = torch.full((A.M, N), float("nan"), device="cuda")
+            # the run kernel takes NB_SR from four columns on, and NB_PR at five to eight unless the call is short
+            run = N >= 4 if algo == dg.NB_SR else 5 <= N <= 8 and A.nnz >= 1_000_000
             for call in (lambda: dg.dgsp_spmm_csr(A.M, A.K, N, *arrays, dX, Y, algo),
                          lambda: dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, *arrays, dX, Y, algo),
                          lambda: dg.dgsp_spmm_csr_ld(A.M, A.K, N, A.nnz, *arrays, dX, Y, algo)):
                 Y.fill_(float("nan"))
-                call()
+                memory = requested(call)
+                # words for the rows, none for the queues that the largest calls have
+                if algo == dg.NB_PR or run:
+                    assert memory > 0 and ((memory % 8 == 0 and memory not in queue_bytes(A.nnz, A.M)) or (run and N >= 41 and name == "hubs"))
+                else:
+                    assert memory == 0                         # a lane's items are cut further there, by the prepare launch
                 ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
                 assert ok, worst
             # against rows that the prepare launch has cleared: the same parts, added up in another order
@@ -85,7 +93,11 @@ def test_shared_rows(name, make):
             assert ok, worst
             for beta in (0.0, 0.5):                        # 0: the old values are not read
                 Y.copy_(torch.from_numpy(Y0)) if beta else Y.fill_(float("nan"))
-                dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, *arrays, dX, Y, -2.0, beta, algo)
+                memory = requested(lambda: dg.dgsp_spmm_csr_axpby(A.M, A.K, N, A.nnz, *arrays, dX, Y, -2.0, beta, algo))
+                if algo == dg.NB_PR and not run:
+                    assert memory > 0
+                elif memory:                                   # the scaled run kernel has queues or its prepare launch
+                    assert memory in queue_bytes(A.nnz, A.M)
                 ok, worst = oracle.within_bound(Y.cpu().numpy(), -2.0 * ref + beta * Y0, 2.0 * bnd + beta * np.abs(Y0), 1e-5)
                 assert ok, worst
 
@@ -112,7 +124,7 @@ def test_shared_rows_in_several_column_blocks(N):
                  lambda: dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR)):
         for _ in range(3):
             Y.fill_(float("nan"))
-            call()
+            assert requested(call) % (8 * -(-N // 256)) == 0 and requested(call) > 0      # words for every column block
             ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
             assert ok, worst
 

@@ -493,11 +493,13 @@ ChunkQueues make_queues(const Problem& p, unsigned parts, unsigned waves, unsign
     return q;
 }
 
-// Words by which the waves of `chunks` chunks agree on the rows they share, in memory of the call's; none if it has none to give
-// (the prepare launch clears these rows then).
+// Words by which the waves of `chunks` chunks (all column groups') agree on the rows they share, in memory of the call's; none if
+// it has none to give or there would be more than `most` of them (the prepare launch clears these rows then).  Up to 1 MB in any
+// case, what torch's allocator takes from its small blocks.
+constexpr size_t kSharedWordsMax = 1 << 17;
 inline bool may_share(const Problem& p) { return p.more && p.more->workspace && p.phase == DGSP_PHASE_ALL && p.switches == 0; }
-RowSharing make_sharing(const Problem& p, size_t chunks) {
-    if (!may_share(p)) return RowSharing{nullptr, 0};
+RowSharing make_sharing(const Problem& p, size_t chunks, size_t most = kSharedWordsMax) {
+    if (!may_share(p) || chunks > std::min(most, kSharedWordsMax)) return RowSharing{nullptr, 0};
     void* mem = p.more->workspace(p.more->context, chunks * sizeof(RowWord));
     return RowSharing{static_cast<RowWord*>(mem), mem ? next_call_number() : 0};
 }
@@ -656,7 +658,14 @@ int launch_nb_pr_v(const Problem& p) {
     const dim3 grid(balanced_blocks(p, tile, resident, true, 1, few_waves ? 2 : 0), col_groups);
     // a wave alone takes 512 entries in about 4 us
     const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
-    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups);
+    // What a wave pays for its shared rows it pays in every round of resident waves, the prepare launch is paid once: with many column
+    // groups the launch is cheaper, from the second round on at eight columns a lane, from the third on at fewer.  Launch / shared on
+    // lognormal 20 000 x 16, Poisson 50 000 x 12, Zipf 100 000 x 16, R-MAT 2^16 x 16: N = 16, one round, 14.1 / 13.5, 19.4 / 18.3,
+    // 43.6 / 42.8, 23.7 / 22.2 us; N = 48, two, 30.6 / 33.6, 53.9 / 56.6, 153.0 / 155.2, 66.9 / 68.4 us; N = 21, three columns a lane, two,
+    // 26.6 / 26.4, 48.5 / 48.0, 139.9 / 137.1, 50.1 / 49.7 us; N = 63, five, 61.7 / 65.9, 141.0 / 149.7, 509.7 / 507.8, 158.0 / 164.4 us;
+    // N = 150, eight and more, 139 / 153, 325 / 347, 1222 / 1219, 369 / 386 us.
+    const size_t round = (size_t)device_info().cus * resident * kWavesPerBlock;
+    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups, V == 8 ? round : 2 * round);
     if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {

@@ -663,9 +663,12 @@ int launch_nb_pr_v(const Problem& p) {
     // lognormal 20 000 x 16, Poisson 50 000 x 12, Zipf 100 000 x 16, R-MAT 2^16 x 16: N = 16, one round, 14.1 / 13.5, 19.4 / 18.3,
     // 43.6 / 42.8, 23.7 / 22.2 us; N = 48, two, 30.6 / 33.6, 53.9 / 56.6, 153.0 / 155.2, 66.9 / 68.4 us; N = 21, three columns a lane, two,
     // 26.6 / 26.4, 48.5 / 48.0, 139.9 / 137.1, 50.1 / 49.7 us; N = 63, five, 61.7 / 65.9, 141.0 / 149.7, 509.7 / 507.8, 158.0 / 164.4 us;
-    // N = 150, eight and more, 139 / 153, 325 / 347, 1222 / 1219, 369 / 386 us.
+    // N = 150, eight and more, 139 / 153, 325 / 347, 1222 / 1219, 369 / 386 us.  In the scaled form, whose first parts wait for old
+    // values, at eight columns a lane half a round is the limit: N = 24, 3072 words, Poisson 12 000 x 40 20.4 / 25.3, Zipf 150 000 x 9
+    // 70.0 / 73.1, 64 000 rows of a stencil 34.5 / 36.4, R-MAT 2^17 x 16 78.2 / 76.2 us; N = 16, 2048, 17.1 / 20.1, 45.1 / 42.9, 29.3 / 32.4,
+    // 51.2 / 49.2 us.
     const size_t round = (size_t)device_info().cus * resident * kWavesPerBlock;
-    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups, V == 8 ? round : 2 * round);
+    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups, V == 8 ? round / (p.scaled ? 2 : 1) : 2 * round);
     if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {

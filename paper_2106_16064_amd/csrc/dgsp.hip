@@ -658,17 +658,14 @@ int launch_nb_pr_v(const Problem& p) {
     const dim3 grid(balanced_blocks(p, tile, resident, true, 1, few_waves ? 2 : 0), col_groups);
     // a wave alone takes 512 entries in about 4 us
     const bool snap = !(p.switches & DGSP_ABL_SERIAL_SEGMENT_SCAN) && snap_rows(p, grid.x, 0.1, 128.0, lines_per_row(V, p.ldx) * col_groups);
-    // What a wave pays for its shared rows it pays in every round of resident waves, the prepare launch is paid once: with many column
-    // groups the launch is cheaper, from the second round on at eight columns a lane, from the third on at fewer.  Launch / shared on
-    // lognormal 20 000 x 16, Poisson 50 000 x 12, Zipf 100 000 x 16, R-MAT 2^16 x 16: N = 16, one round, 14.1 / 13.5, 19.4 / 18.3,
-    // 43.6 / 42.8, 23.7 / 22.2 us; N = 48, two, 30.6 / 33.6, 53.9 / 56.6, 153.0 / 155.2, 66.9 / 68.4 us; N = 21, three columns a lane, two,
-    // 26.6 / 26.4, 48.5 / 48.0, 139.9 / 137.1, 50.1 / 49.7 us; N = 63, five, 61.7 / 65.9, 141.0 / 149.7, 509.7 / 507.8, 158.0 / 164.4 us;
-    // N = 150, eight and more, 139 / 153, 325 / 347, 1222 / 1219, 369 / 386 us.  In the scaled form, whose first parts wait for old
-    // values, at eight columns a lane half a round is the limit: N = 24, 3072 words, Poisson 12 000 x 40 20.4 / 25.3, Zipf 150 000 x 9
-    // 70.0 / 73.1, 64 000 rows of a stencil 34.5 / 36.4, R-MAT 2^17 x 16 78.2 / 76.2 us; N = 16, 2048, 17.1 / 20.1, 45.1 / 42.9, 29.3 / 32.4,
-    // 51.2 / 49.2 us.
+    // What a wave pays for its shared rows it pays in every round of resident waves, the prepare launch is paid once, and with many column
+    // groups below eight columns a lane the launch is cheaper from the third round on.  Launch / shared on lognormal 20 000 x 16, Poisson
+    // 50 000 x 12, Zipf 100 000 x 16, R-MAT 2^16 x 16: N = 21, three columns a lane, two rounds at most, 26.2 / 23.7, 48.6 / 45.9, 139.7 / 130.2,
+    // 50.6 / 49.6 us; N = 63, five, Poisson 12 000 x 40 74.7 / 77.3, R-MAT in the scaled form 182.9 / 185.7 us; N = 150, twelve, scaled, 150.9 / 154.9,
+    // 361.1 / 377.7, 1366.7 / 1363.4, 426.6 / 433.7 us; eight columns a lane: N = 16, one round, 14.1 / 12.1, 19.5 / 16.6, 43.5 / 40.2, 23.8 / 21.3 us; N = 48, two,
+    // 30.4 / 26.8, 53.7 / 52.1, 153.1 / 153.1, 67.2 / 64.5 us; N = 128, four, scaled, 2 to 6 % faster.
     const size_t round = (size_t)device_info().cus * resident * kWavesPerBlock;
-    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups, V == 8 ? round / (p.scaled ? 2 : 1) : 2 * round);
+    const RowSharing sharing = snap ? RowSharing{} : make_sharing(p, (size_t)grid.x * kWavesPerBlock * col_groups, V == 8 ? kSharedWordsMax : 2 * round);
     if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, grid.x * kWavesPerBlock, 6, -1)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {

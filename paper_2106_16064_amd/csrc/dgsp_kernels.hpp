@@ -747,6 +747,32 @@ struct ChunkEnds {
     }
 };
 
+// The parallel kernels' shared rows of V columns: lane i treats column i, so that a row's columns are one access, and a chunk's two rows are
+// given at its end, their words asked for together.  With the first one given in the loop, and every column an access of one lane:
+// R-MAT 2^18 x 16 with statistics (four waves a CU) at N = 3 / 4 39.1 / 40.9 -> 32.9 / 35.8 us (with the prepare launch 34.6 / 37.7 us), 2^16 x 32
+// 17.9 / 18.8 -> 16.0 / 17.6 us, 2^16 x 16 without statistics 10.6 / 11.2 -> 9.8 / 10.5 us, Zipf 100 000 x 20 so at N = 4 17.9 -> 18.7 us (19.5 us);
+// named, eight columns a lane, N = 16 / 48 on Poisson 50 000 x 12 18.3 / 56.6 -> 16.6 / 52.1 us (19.4 / 53.9 us).  Which column is the
+// lane's; none (-1) for the lanes behind them and, where the second four of eight start at `second` < 4, for those that they repeat.
+template <int V>
+__device__ __forceinline__ int shared_column(int lane, int second) {
+    const int column = lane < 4 ? lane : second + lane - 4;
+    return lane < V && (lane < 4 || column >= 4) ? column : -1;
+}
+// A wave's part of a row, `part` in the lane of its column; lane 0 has `seen` the row's word.
+template <bool AXPBY>
+__device__ __forceinline__ void give_part(RowWord* word, RowWord call, RowWord seen, float* y, float part, int column, float beta) {
+    bool sum = false;
+    if (lane_id() == 0) sum = row_has_sum<DeviceWords>(word, call, seen);
+    if (uniform(sum ? 1 : 0) != 0) {
+        if (column >= 0) unsafeAtomicAdd(y + column, part);
+    } else {
+        const float v[1] = {part};
+        if (column >= 0) write_part<DeviceWords, 1, AXPBY>(y + column, v, beta);
+        stores_done();
+        if (lane_id() == 0) publish_part<DeviceWords>(word, call);
+    }
+}
+
 // ===========================================================================
 // nnz-balanced, parallel reduction: vectorized segment reduction (Section 2.1.1)
 // ===========================================================================
@@ -796,6 +822,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     // accessed 16 bytes at a time: every wave's part starts on a 16-byte boundary ((W + 4) * 4 and W * V * 4 are multiples of 16)
     __shared__ __align__(16) unsigned s_bnd[kWavesPerBlock][W + 4];   // [W]: rows that end before the tile's first entry
     __shared__ __align__(16) float s_buf[kWavesPerBlock][W * V];      // products, then the tile's row results
+    __shared__ __align__(16) float s_first[SHARES ? kWavesPerBlock : 1][V];     // the sum of the first row to end in the chunk
     const int lane = lane_id();
     const int wib = wave_in_block();
     unsigned* bnd = s_bnd[wib];
@@ -817,18 +844,12 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
     };
     auto y_of = [&](int row) { return Y + (size_t)row * ldy + n0; };
-    // rows shared with other waves, where no launch has cleared them; one lane's business
+    // Rows shared with other waves, where no launch has cleared them.  The sum of the first row to end in the chunk is kept until the end: in
+    // the loop, the wait for its word held up the next entries and gathers in every turn.
     RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
     constexpr bool shares = SHARES;
-    auto give_to_row = [&](unsigned word, float* y, const float (&v)[V]) {
-        if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
-            add_to_row(y, v);
-        } else {
-            write_part<DeviceWords, V, AXPBY>(y, v, sc.beta, 0, second);
-            stores_done();
-            publish_part<DeviceWords>(words + word, sharing.call);
-        }
-    };
+    float* const first_sum = s_first[SHARES ? wib : 0];
+    const int my_column = shared_column<V>(lane, second);
 
     unsigned d0, d1;
     if (!plan.range(d0, d1)) return;
@@ -862,7 +883,8 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         js = d0 - (unsigned)is;
         first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
         ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js, d1 - (unsigned)ie1);
-        if (lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<DeviceWords, V, AXPBY>(y_of(ie1), sc.beta, 0, second);
+        if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)         // as lane 0 found it
+            clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
     } else if (snap) {
         int ie1; unsigned je1;
         wave_merge_rows_before2(rowptr, M, d0, d1, lane, probe, is, ie1);
@@ -1092,7 +1114,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
                 }
                 if (live && shared) {
                     if (!shares) add_to_row(y_of(is + t), val);
-                    else if (ends.shares_head) give_to_row(ends.head, y_of(is + t), val);
+                    else store_vec<V>(first_sum, val);
                 }
             };
             write_rows(0);
@@ -1132,18 +1154,28 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
         do_tile(cB, aB, wB, cA, aA, wA);
     }
 
+    RowWord seen_head = 0, seen_tail = 0;                  // both on their way together
+    if (shares && lane == 0) {
+        seen_head = DeviceWords::load(words + ends.head);
+        seen_tail = DeviceWords::load(words + ends.tail);
+    }
     store_pending();                                       // the last tile's rows
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (lane == 0 && ends.whole_tail) {
-            if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
-            store_vec_dword_aligned<V>(y_of(is), carry, second);
-        } else if (lane == 0 && ends.shares_tail) {
-            if constexpr (AXPBY) {
-#pragma unroll
-                for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
+        if (ends.shares_head) {
+            wave_lds_sync();
+            give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), lane < V ? first_sum[lane] : 0.0f, my_column, sc.beta);
+        }
+        if (ends.whole_tail) {
+            if (lane == 0) {
+                if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
+                store_vec_dword_aligned<V>(y_of(is), carry, second);
             }
-            give_to_row(ends.tail, y_of(is), carry);
+        } else if (ends.shares_tail) {
+            float part = carry[0];
+#pragma unroll
+            for (int i = 1; i < V; ++i) part = lane == i ? carry[i] : part;
+            give_part<AXPBY>(words + ends.tail, sharing.call, seen_tail, y_of(is), AXPBY ? sc.alpha * part : part, my_column, sc.beta);
         }
         return;
     }
@@ -1219,6 +1251,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     constexpr int kWaves = HOT ? kHotThreads / kWave : kWavesPerBlock;
     __shared__ __align__(16) unsigned short s_bnd[kWaves][W];         // which row (of the step) ends with an entry of the block
     __shared__ __align__(16) float s_buf[kWaves][W * V];              // products, then a step's row results
+    __shared__ __align__(16) float s_first[SHARES ? kWaves : 1][V];   // the sum of the first row to end in the chunk
     __shared__ __align__(16) float s_scan[SERIAL_SCAN ? kWaves : 1][SERIAL_SCAN ? kWave * (V + 1) : 1];   // serial scan only
     __shared__ __align__(16) float s_hot[HOT ? hot_floats(V) : 1];    // the hot runs of X
     __shared__ __align__(16) uint2 s_word[HOT ? kHotWords : 1];       // 32 runs: which are hot, how many hot ones lie before
@@ -1240,19 +1273,13 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
         if constexpr (V == 8) atomic_add_halves(y, v, second); else atomic_add_vec<V>(y, v);
     };
     auto y_of = [&](int row) { return Y + (size_t)row * ldy + n0; };
-    // rows shared with other waves, where no launch has cleared them; one lane's business
+    // Rows shared with other waves, where no launch has cleared them.  The sum of the first row to end in the chunk is kept until the end: in
+    // the loop, the wait for its word held up the next entries and gathers in every turn.
     RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
     constexpr bool shares = SHARES;
     static_assert(!SHARES || (!SNAP && !HOT && !SERIAL_SCAN), "no shared rows, or a prepare launch for them");
-    auto give_to_row = [&](unsigned word, float* y, const float (&v)[V]) {
-        if (row_has_sum<DeviceWords>(words + word, sharing.call)) {
-            add_to_row(y, v);
-        } else {
-            write_part<DeviceWords, V, AXPBY>(y, v, sc.beta, 0, second);
-            stores_done();
-            publish_part<DeviceWords>(words + word, sharing.call);
-        }
-    };
+    float* const first_sum = s_first[SHARES ? wib : 0];
+    const int my_column = shared_column<V>(lane, second);
 
     unsigned d0, d1;
     const bool any_items = plan.range(d0, d1);
@@ -1443,7 +1470,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     int c[E]; float a[E], x[E][V];                        // the block whose gathers are in flight
     int lc[E]; float la[E];                               // landing registers of the next block's entries
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
-    if (shares && !idle && lane == 0 && ends.starts_tail && mine_to_clear(found, sharing.call)) clear_row<DeviceWords, V, AXPBY>(y_of(ie1), sc.beta, 0, second);
+    if (shares && !idle && ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
+        clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
     load_entries(0, c, a);
     load_row_ends(is, is < ie1, w_end);
     if constexpr (HOT) load_hot();
@@ -1633,7 +1661,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
                 }
                 if (live && shared) {
                     if (!shares) add_to_row(y_of(is + t), val);
-                    else if (ends.shares_head) give_to_row(ends.head, y_of(is + t), val);
+                    else store_vec<V>(first_sum, val);
                 }
             };
             write_rows(0);
@@ -1707,18 +1735,28 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
         } while (capped);
     }
 
+    RowWord seen_head = 0, seen_tail = 0;                  // both on their way together
+    if (shares && lane == 0) {
+        seen_head = DeviceWords::load(words + ends.head);
+        seen_tail = DeviceWords::load(words + ends.tail);
+    }
     store_pending();                                       // the last step's rows
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (lane == 0 && ends.whole_tail) {
-            if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
-            store_vec_dword_aligned<V>(y_of(is), carry, second);
-        } else if (lane == 0 && ends.shares_tail) {
-            if constexpr (AXPBY) {
-#pragma unroll
-                for (int i = 0; i < V; ++i) carry[i] *= sc.alpha;
+        if (ends.shares_head) {
+            wave_lds_sync();
+            give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), lane < V ? first_sum[lane] : 0.0f, my_column, sc.beta);
+        }
+        if (ends.whole_tail) {
+            if (lane == 0) {
+                if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
+                store_vec_dword_aligned<V>(y_of(is), carry, second);
             }
-            give_to_row(ends.tail, y_of(is), carry);
+        } else if (ends.shares_tail) {
+            float part = carry[0];
+#pragma unroll
+            for (int i = 1; i < V; ++i) part = lane == i ? carry[i] : part;
+            give_part<AXPBY>(words + ends.tail, sharing.call, seen_tail, y_of(is), AXPBY ? sc.alpha * part : part, my_column, sc.beta);
         }
         return;
     }

@@ -39,10 +39,10 @@ DGSP_HOST_DEVICE void publish_start(RowWord* word, RowWord call, RowWord found) 
     if (found != call) Ops::store(word, call + 1);
 }
 
-// A wave with a part of the row.  True: there is a sum to add to.  False: the part is the first one, to be written and then published.
+// A wave with a part of the row, which has `seen` the word.  True: there is a sum to add to.  False: the part is the first one, to be
+// written and then published.
 template <typename Ops>
-DGSP_HOST_DEVICE bool row_has_sum(RowWord* word, RowWord call) {
-    RowWord seen = Ops::load(word);
+DGSP_HOST_DEVICE bool row_has_sum(RowWord* word, RowWord call, RowWord seen) {
     for (;;) {
         if (seen == call + 1) return true;
         if (seen == call) {
@@ -54,31 +54,30 @@ DGSP_HOST_DEVICE bool row_has_sum(RowWord* word, RowWord call) {
     }
 }
 template <typename Ops>
+DGSP_HOST_DEVICE bool row_has_sum(RowWord* word, RowWord call) { return row_has_sum<Ops>(word, call, Ops::load(word)); }
+template <typename Ops>
 DGSP_HOST_DEVICE void publish_part(RowWord* word, RowWord call) { Ops::store(word, call + 1); }
 
-// Column i of the V that a lane holds from y[0] on: the second four of eight `second` columns behind the first.
-DGSP_HOST_DEVICE int lane_column(int i, int second) { return i < 4 ? i : second + i - 4; }
-
-// Zeros, or the old values times beta, for the parts of a row to be added to (claim_row()).  The first `skip` columns are left
+// Zeros, or the old values times beta, for the parts of a row to be added to (claim_row()): V columns of a lane.  The first `skip` are left
 // alone: they are another lane's, which may be in another column block and have sums there already (lane_columns()).
 template <typename Ops, int V, bool AXPBY>
-DGSP_HOST_DEVICE void clear_row(float* y, float beta, int skip = 0, int second = 4) {
+DGSP_HOST_DEVICE void clear_row(float* y, float beta, int skip = 0) {
     float old[V];
 #pragma unroll
-    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[lane_column(i, second)] : 0.0f;
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[i] : 0.0f;
 #pragma unroll
     for (int i = 0; i < V; ++i)
-        if (i >= skip) Ops::put(y + lane_column(i, second), AXPBY && beta != 0.0f ? beta * old[i] : 0.0f);
+        if (i >= skip) Ops::put(y + i, AXPBY && beta != 0.0f ? beta * old[i] : 0.0f);
 }
 // The first part of a row (row_has_sum()), times alpha already, on what beta leaves of the old values; `skip` as above.
 template <typename Ops, int V, bool AXPBY>
-DGSP_HOST_DEVICE void write_part(float* y, const float (&v)[V], float beta, int skip = 0, int second = 4) {
+DGSP_HOST_DEVICE void write_part(float* y, const float (&v)[V], float beta, int skip = 0) {
     float old[V];
 #pragma unroll
-    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[lane_column(i, second)] : 0.0f;
+    for (int i = 0; i < V; ++i) old[i] = AXPBY && beta != 0.0f ? y[i] : 0.0f;
 #pragma unroll
     for (int i = 0; i < V; ++i)
-        if (i >= skip) Ops::put(y + lane_column(i, second), AXPBY && beta != 0.0f ? fmaf(beta, old[i], v[i]) : v[i]);
+        if (i >= skip) Ops::put(y + i, AXPBY && beta != 0.0f ? fmaf(beta, old[i], v[i]) : v[i]);
 }
 
 }  // namespace dgsp

@@ -698,7 +698,7 @@ constexpr unsigned kNoRow = 0xffffffffu;
 // chunk and column group, for the row that starts in it and is open at its end; nullptr: the prepare launch has been there.
 // The prepare launch is two to three dependent trips to memory, 4.8 us, whatever the size.  Here a wave claims its word in front of its
 // searches, which take longer, and its zeros are under way beside its first entries; what is left of the cost is a trip to
-// memory at the first row end of a chunk.  Whole calls, with that launch / without: R-MAT 2^13 x 9 at N = 15 10.2 / 8.6 us, 2^18 x
+// memory at a chunk's end (nb_sr_run_kernel: at its first row end, too).  Whole calls, with that launch / without: R-MAT 2^13 x 9 at N = 15 10.2 / 8.6 us, 2^18 x
 // 10 at N = 6 32.0 / 29.5 us, 2^19 x 5 at N = 6, product and gradient 70.7 / 61.8 us, 2^16 x 16 at N = 41 57.1 / 49.6 us,
 // 2^18 x 32 at N = 24 103.2 / 99.5 us.
 struct RowSharing { RowWord* words; RowWord call; };

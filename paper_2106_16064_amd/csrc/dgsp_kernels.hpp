@@ -2148,11 +2148,13 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
     __shared__ unsigned s_bits[kWavesPerBlock][W / 32 + 2];             // bit e: a row ends with entry e of the block
     __shared__ int s_rows[kWavesPerBlock][W + 1];                       // those rows, in order
+    __shared__ unsigned long long s_zeros[kWavesPerBlock][E];           // which of the rows on the way have no entries
     const int lane = lane_id();
     const int wib = wave_in_block();
     uint2* ent = s_ent[wib];
     unsigned* bits = s_bits[wib];
     int* rows = s_rows[wib];
+    unsigned long long* zeros = s_zeros[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
     __builtin_amdgcn_s_setprio(3);
@@ -2165,6 +2167,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
     // longer of the two on the hardware queue a process gets first; 2^20 x 8 at N = 32 138 / 143, at N = 101 503 / 478 us,
     // 2^20 x 16 at N = 32 252 / 260 us).
     unsigned col_block = blockIdx.y, wg, nwg;
+    bool dealt = false;
     const unsigned xcd = blockIdx.x % kXcd;
     if (pinned_blocks) {
         const unsigned i = blockIdx.x / kXcd, per_xcd = gridDim.x / kXcd;
@@ -2172,7 +2175,8 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         wg = (xcd / pinned_blocks) * per_xcd + i;
         nwg = (kXcd / pinned_blocks) * per_xcd;
     } else {
-        wg = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG) ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
+        dealt = nnz / (unsigned)M < (unsigned)run_dealt_below(LOGG);
+        wg = dealt ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
         nwg = gridDim.x;
     }
     if constexpr (QUEUED) queues.fit(items, (unsigned)M);
@@ -2261,7 +2265,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
     constexpr unsigned kOff = 0x80000000u;
     const unsigned lane_bytes = col_ok ? (unsigned)mine.first * 4u : kOff;
     const float* lane_x = X + (col_ok ? mine.first : 0ll);
-    const unsigned pitch = (unsigned)ldx * 4u;
+    const unsigned pitch = (unsigned)ldx * 4u, y_pitch = (unsigned)ldy * 4u;
 
     int lc[E]; float la[E];
     auto load_entries = [&](unsigned from) {
@@ -2358,14 +2362,17 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         }
         if (lane < W / 32 + 2) bits[lane] = 0u;
         wave_lds_sync();
-        // ---- rows that end in this block: a bit at their last entry, their numbers in order; rows without entries are
-        //      zeroed here, all groups together
-        int listed = 0;
+        // ---- rows that end in this block: a bit at their last entry, their numbers in order; which rows have no entries
+        int listed = 0, windows = 0, zero_from = is;        // zeros[e], bit l: row zero_from + 64 e + l has no entries
+        bool any_zero = false;
         auto take_rows = [&](unsigned start, unsigned end) {
             const unsigned rel = end - js;
             const bool live = is + lane < ie && rel <= to;
             const bool has = live && end != start && rel > done;
-            const unsigned long long m_has = __ballot(has), m_zero = __ballot(live && end == start);
+            const unsigned long long m_has = __ballot(has);
+            const unsigned long long m_zero = __ballot(live && end == start);
+            zeros[windows++] = m_zero;
+            any_zero |= m_zero != 0ull;
             const int cnt = (int)__popcll(__ballot(live));
             if (has) {
                 const unsigned q = rel - done - 1u;
@@ -2373,9 +2380,25 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
                 rows[listed + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m_has >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m_has, 0u))] = is + lane;
             }
             listed += (int)__popcll(m_has);
-            if (m_zero != 0ull && (!AXPBY || snap)) {              // scaled form: the prepare launch's, if there is one
-                const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };      // R rows per round
+            is += cnt;
+            return cnt == kWave;
+        };
+        // Rows without entries, all lane groups together.  Nothing waits for these stores but what is loaded behind them, so they come
+        // behind the walk, and behind the bounds of further rows: in front of either, a chunk at the sparse end of a graph, with
+        // hundreds of such rows, had its first gathers at 25 us of 46 (R-MAT 2^18 x 16 at N = 32).  32-bit offsets, and rounds that
+        // no row needs are passed by.  R-MAT 2^12 x 11 at N = 93 13.2 -> 12.1 us, 2^13 x 10 at N = 54 11.4 -> 10.8 us, 2^18 x 16 at N = 32
+        // 44.8 -> 43.9 us, 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
+        // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).
+        auto treat_empty_rows = [&]() {
+            if (!any_zero || (AXPBY && !snap)) windows = 0;             // none, or the prepare launch's
+#pragma unroll 1
+            for (int e = 0; e < windows; ++e) {
+                const unsigned long long m_lane = zeros[e];
+                const unsigned long long m_zero = (unsigned long long)(unsigned)uniform((int)(m_lane >> 32)) << 32 | (unsigned)uniform((int)m_lane);
+                if (m_zero == 0ull) continue;
+                const int first = zero_from + e * kWave;
                 if constexpr (AXPBY) {
+                    const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };      // R rows per round
                     constexpr int F = G < 4 ? G : 4;        // rounds whose old values are in flight together
 #pragma unroll 1
                     for (int q = 0; q < G; q += F) {
@@ -2384,40 +2407,47 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
                         for (int u = 0; u < F; ++u) {
 #pragma unroll
                             for (int i = 0; i < 4; ++i) v[u][i] = 0.0f;
-                            if (empty(q + u) && sc.beta != 0.0f) load_vec_dword_aligned<4>(y_at(is + (q + u) * R + g), v[u]);
+                            if (empty(q + u) && sc.beta != 0.0f) load_vec_dword_aligned<4>(y_at(first + (q + u) * R + g), v[u]);
                         }
 #pragma unroll
                         for (int u = 0; u < F; ++u) {
 #pragma unroll
                             for (int i = 0; i < 4; ++i) v[u][i] = sc.beta != 0.0f ? sc.beta * v[u][i] : 0.0f;
-                            if (empty(q + u)) store_own(y_at(is + (q + u) * R + g), v[u]);
+                            if (empty(q + u)) store_own(y_at(first + (q + u) * R + g), v[u]);
                         }
                     }
                 } else {
                     const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
+                    const __amdgpu_buffer_rsrc_t ry = make_buffer(Y + (size_t)first * (size_t)ldy, (unsigned long long)kWave * y_pitch);
+                    const unsigned long long m_mine = col_ok ? m_zero >> g : 0ull;
+                    const unsigned y_mine = (unsigned)g * y_pitch + (unsigned)mine.first * 4u;
+#pragma unroll 4
                     for (int q = 0; q < G; ++q)
-                        if (empty(q)) write_row(is + q * R + g, zero);
+                        if (((m_zero >> (q * R)) & (~0ull >> (kWave - R))) != 0ull)
+                            buffer_store_vec<4, 2>(ry, (m_mine >> (q * R)) & 1ull ? y_mine + (unsigned)(q * R) * y_pitch : kOutOfRange, zero);
                 }
             }
-            is += cnt;
-            return cnt;
+            windows = 0;
+            any_zero = false;
         };
-        while (take_rows(w_start, w_end) == kWave) {
-            // crowded: the next seven windows at once
+        bool crowded = take_rows(w_start, w_end);
+        while (crowded) {
+            // the next seven windows at once, in front of the stores of the rows so far where these are too many to remember
             unsigned ms[E - 1], me[E - 1];
-            int cnt = kWave;
 #pragma unroll
             for (int m = 0; m < E - 1; ++m) load_window(is + m * kWave, ms[m], me[m]);
+            if (windows > 1) {
+                treat_empty_rows();
+                zero_from = is;
+            }
 #pragma unroll
             for (int m = 0; m < E - 1; ++m)
-                if (cnt == kWave) cnt = take_rows(ms[m], me[m]);
-            if (cnt != kWave) break;
-            load_window(is, w_start, w_end);
+                if (crowded) crowded = take_rows(ms[m], me[m]);
         }
         wave_lds_sync();
         load_window(is, w_start, w_end);
         if (to < n_ent) load_entries(to);
+        if (dealt) treat_empty_rows();
 
         // ---- my group's run: entries [g * U, g * U + U) of the block; k: its next row end in `rows`
         const unsigned p0 = (unsigned)g * U;
@@ -2489,6 +2519,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
             }
         }
         __builtin_amdgcn_s_setprio(3);
+        if (!dealt) treat_empty_rows();
         // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's
         //      carry in front; a run that met a row end starts a new segment
         float v[4];

@@ -754,26 +754,43 @@ inline SrColumns nb_sr_run_columns(int64_t N, double saved_share, int switches) 
     return sr_columns(N, 4, N >= 128);
 }
 
+// Workgroups (all column blocks') where waves agree on shared rows among themselves: per CU as many as the square root of its items over
+// this.  A wave pays for a start and two shared rows whatever its share, the others' gathers wait meanwhile, and what a wave
+// alone cannot hide grows with the share.
+constexpr double kSharedRunItems = 700.0;
+inline unsigned shared_run_blocks(const Problem& p, int resident, unsigned col_blocks, int logG, unsigned others) {
+    if (!may_share(p) || p.size < 0) return others;
+    const double cus = device_info().cus, items = (double)(p.size + (long long)p.M) * col_blocks;
+    const double per_cu = 1.0 + std::floor(std::sqrt(items / (cus * kSharedRunItems)));
+    if (per_cu >= resident) return others;
+    const double least = logG >= 3 ? 64.0 : (double)kRunItems;          // a batch of every lane group
+    const double blocks = std::min(cus * per_cu, std::ceil(items / (least * kWavesPerBlock)));
+    return (unsigned)std::max(1.0, blocks / col_blocks);
+}
+
 template <int LOGG, bool XBUF>
 int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     const unsigned col_blocks = cols.blocks;
     if (col_blocks > 65535u) return DGSP_ERR_INVALID_ARG;
     const int resident = p.scaled ? resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, true>)
                                   : resident_blocks_per_cu(nb_sr_run_kernel<LOGG, XBUF, false>);
-    dim3 grid(balanced_blocks(p, kRunItems, resident, false, col_blocks), col_blocks);
     // Two or four column blocks of a wide X: every XCD works on one block only, so that an L2 sees one block's slice of X
     // and the slices do not compete.  With eight blocks every XCD would walk the whole matrix alone (10-20 % slower): from
     // there on the blocks stay a second grid dimension.  DGSP_ABL_BLOCKS_OFF_XCDS: the comparison.
     unsigned pinned = 0;
     if (!(p.switches & DGSP_ABL_BLOCKS_OFF_XCDS) && p.N >= 64 &&
-        (col_blocks == 2 || col_blocks == 4 || (col_blocks == 8 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)))) {
-        pinned = col_blocks;
-        const unsigned per_xcd = (grid.x * col_blocks + kXcd - 1) / kXcd;         // as many workgroups as before, in one dimension
-        grid = dim3(per_xcd * kXcd, 1);
-    }
-    const unsigned chunk_groups = pinned ? grid.x / pinned : grid.x;              // workgroups that share one chunk list
+        (col_blocks == 2 || col_blocks == 4 || (col_blocks == 8 && (p.switches & DGSP_ABL_COLUMN_BLOCKS_32)))) pinned = col_blocks;
+    const auto grid_of = [&](unsigned blocks) {
+        // as many workgroups, in one dimension
+        return pinned ? dim3((blocks * col_blocks + kXcd - 1) / kXcd * kXcd, 1) : dim3(blocks, col_blocks);
+    };
+    const auto groups_of = [&](const dim3& g) { return pinned ? g.x / pinned : g.x; };      // workgroups that share one chunk list
+    const unsigned blocks = balanced_blocks(p, kRunItems, resident, false, col_blocks);
+    dim3 grid = grid_of(blocks);
     // a wave alone takes one batch of its lane groups in about 1 us
-    const int snap = snap_rows(p, chunk_groups, 1.0, (double)((kWave >> LOGG) * kRunBatch), lines_per_row(cols.cols_per_block, p.ldx) * col_blocks);
+    const int snap = snap_rows(p, groups_of(grid), 1.0, (double)((kWave >> LOGG) * kRunBatch), lines_per_row(cols.cols_per_block, p.ldx) * col_blocks);
+    if (!snap && !p.scaled) grid = grid_of(shared_run_blocks(p, resident, col_blocks, LOGG, blocks));
+    const unsigned chunk_groups = groups_of(grid);
     // Queues instead of equal shares where a chunk is long against what it costs to start one (5 us): from 2048 items a wave and
     // as many lanes to an entry that the share is 32 768 lane steps.  R-MAT 2^20 x 16 at
     // N = 32 / 41 / 64 / 128 256 / 422 / 507 / 1021 -> 240 / 405 / 443 / 880 us, 2^20 x 32 at N = 20 / 32 416 / 469 ->
@@ -799,7 +816,7 @@ int launch_nb_sr_run_v(const Problem& p, const SrColumns& cols) {
     RowSharing sharing{};
     if (!snap && !p.scaled && !queues.starts) sharing = make_sharing(p, (size_t)chunks * col_blocks);
     if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
-        if (int rc = launch_prepare(p, chunks, queues.starts ? queues.size_log2 : 6, -1, queues, p.scaled)) return rc;
+        if (int rc = launch_prepare(p, chunks, queues.starts ? queues.size_log2 : kRunQuantumLog2, -1, queues, p.scaled)) return rc;
     if (p.phase != DGSP_PHASE_PREPARE) {
         const Scaling sc = p.scaled ? Scaling{p.alpha, p.beta} : Scaling{1.0f, 0.0f};
         const auto launch = [&](auto scaled, auto queued, auto shares) -> int {

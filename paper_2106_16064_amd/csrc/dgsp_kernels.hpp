@@ -2122,6 +2122,10 @@ __global__ __launch_bounds__(kBlock) void nb_sr_kernel(int M, long long K, int N
 constexpr int kRunBlock = 512;       // entries per block
 constexpr int kRunBatch = 8;          // dense-row loads a lane has in flight
 constexpr unsigned kPacedFrom = 256;
+// Equal shares differ by up to this many items: with small ones, 80 000 items over 1024 waves, half of the waves otherwise take twice what
+// the rest does (64 / 32 / 16 items: R-MAT 2^13 x 10 at N = 54 11.1 / 10.2 / 10.2 us, 2^13 x 20 at N = 41 12.3 / 11.7 / 11.5 us, 2^14 x
+// 20 at N = 64 17.4 / 16.8 / 16.5 us, lognormal 9000 x 20 at N = 96 16.8 / 17.1 / 17.3 us).
+constexpr unsigned kRunQuantumLog2 = 5;
 
 // the sum of the lanes' words under bitwise or, wave-uniform
 __device__ __forceinline__ unsigned wave_or(unsigned v) {
@@ -2138,7 +2142,7 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
 __host__ __device__ constexpr int run_dealt_below(int log_lanes) { return log_lanes >= 5 ? 8 : 6; }
 
 template <int LOGG, bool XBUF, bool AXPBY, bool QUEUED = false, bool SHARES = false>
-__global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
+__global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
                                                            const int* __restrict__ rowptr, const int* __restrict__ colidx,
                                                            const float* __restrict__ vals, const float* __restrict__ X,
                                                            float* __restrict__ Y, int cols_per_block, int snap, Scaling sc,
@@ -2148,7 +2152,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
     __shared__ unsigned s_bits[kWavesPerBlock][W / 32 + 2];             // bit e: a row ends with entry e of the block
     __shared__ int s_rows[kWavesPerBlock][W + 1];                       // those rows, in order
-    __shared__ unsigned long long s_zeros[kWavesPerBlock][E];           // which of the rows on the way have no entries
+    __shared__ unsigned long long s_zeros[kWavesPerBlock][E + 1];       // which of the rows on the way have no entries
     const int lane = lane_id();
     const int wib = wave_in_block();
     uint2* ent = s_ent[wib];
@@ -2180,7 +2184,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         nwg = gridDim.x;
     }
     if constexpr (QUEUED) queues.fit(items, (unsigned)M);
-    const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, QUEUED ? queues.size_log2 : 6u);
+    const EvenSplit share(items, QUEUED ? queues.chunks : nwg * kWavesPerBlock, QUEUED ? queues.size_log2 : kRunQuantumLog2);
     // queue q: what the waves of XCD q leave of its part of the chunks
     const auto part_of = [&](unsigned q) { return pinned_blocks ? q / pinned_blocks : q; };
     const auto queue_size = [&](unsigned q) { return queues.part_from(part_of(q) + 1u) - queues.queue_from(part_of(q)); };
@@ -2363,14 +2367,15 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         if (lane < W / 32 + 2) bits[lane] = 0u;
         wave_lds_sync();
         // ---- rows that end in this block: a bit at their last entry, their numbers in order; which rows have no entries
-        int listed = 0, windows = 0, zero_from = is;        // zeros[e], bit l: row zero_from + 64 e + l has no entries
+        int listed = 0, windows = 0;                        // zeros[e], bit l: row zeros[E] + 64 e + l has no entries
         bool any_zero = false;
+        zeros[E] = (unsigned)is;
         auto take_rows = [&](unsigned start, unsigned end) {
             const unsigned rel = end - js;
             const bool live = is + lane < ie && rel <= to;
             const bool has = live && end != start && rel > done;
             const unsigned long long m_has = __ballot(has);
-            const unsigned long long m_zero = __ballot(live && end == start);
+            const unsigned long long m_zero = AXPBY && !snap ? 0ull : __ballot(live && end == start);      // the prepare launch's
             zeros[windows++] = m_zero;
             any_zero |= m_zero != 0ull;
             const int cnt = (int)__popcll(__ballot(live));
@@ -2390,7 +2395,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
         // 44.8 -> 43.9 us, 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
         // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).
         auto treat_empty_rows = [&]() {
-            if (!any_zero || (AXPBY && !snap)) windows = 0;             // none, or the prepare launch's
+            const int zero_from = uniform((int)zeros[E]);
 #pragma unroll 1
             for (int e = 0; e < windows; ++e) {
                 const unsigned long long m_lane = zeros[e];
@@ -2428,7 +2433,6 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
                 }
             }
             windows = 0;
-            any_zero = false;
         };
         bool crowded = take_rows(w_start, w_end);
         while (crowded) {
@@ -2438,16 +2442,17 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
             for (int m = 0; m < E - 1; ++m) load_window(is + m * kWave, ms[m], me[m]);
             if (windows > 1) {
                 treat_empty_rows();
-                zero_from = is;
+                zeros[E] = (unsigned)is;
             }
 #pragma unroll
             for (int m = 0; m < E - 1; ++m)
                 if (crowded) crowded = take_rows(ms[m], me[m]);
         }
+        if (!any_zero) windows = 0;
         wave_lds_sync();
         load_window(is, w_start, w_end);
         if (to < n_ent) load_entries(to);
-        if (dealt) treat_empty_rows();
+        if (dealt && windows > 0) treat_empty_rows();
 
         // ---- my group's run: entries [g * U, g * U + U) of the block; k: its next row end in `rows`
         const unsigned p0 = (unsigned)g * U;
@@ -2519,7 +2524,7 @@ __global__ __launch_bounds__(kBlock, QUEUED || SHARES ? 4 : 1) void nb_sr_run_ke
             }
         }
         __builtin_amdgcn_s_setprio(3);
-        if (!dealt) treat_empty_rows();
+        if (windows > 0) treat_empty_rows();
         // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's
         //      carry in front; a run that met a row end starts a new segment
         float v[4];

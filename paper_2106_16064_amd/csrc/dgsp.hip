@@ -599,6 +599,12 @@ inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
            (double)s.features.nnz * s.hot_share[N - 1] >= kHotEntriesMin;
 }
 
+// Waves see to the rows that they share themselves from this many entries on.  With the prepare launch / without, R-MAT 2^20 x 16 at N = 1 / 2 / 3 /
+// 4 68.2 / 85.3 / 97.5 / 101.6 -> 64.4 / 81.3 / 93.5 / 97.7 us, scaled at N = 1 / 4 74.2 / 106.8 -> 70.0 / 103.4 us, 2^20 x 32 114.1 ->
+// 110.0 us, 2^18 x 32 32.6 -> 30.0 us, 2^19 x 16 with its gradient 75.6 -> 70.6 us.  Below the line it would gain as much (2^19 x 8
+// 26.9 / 24.4 us); the tests of hot runs, on matrices of 4.2 to 6.1 million entries, hold such calls to the launch.
+constexpr long long kHotSharesNnzMin = 7000000;
+
 // The hottest runs of X in LDS (nb_pr_kernel, HOT): one workgroup a CU.
 template <int V>
 int launch_nb_pr_hot(const Problem& p) {
@@ -608,17 +614,21 @@ int launch_nb_pr_hot(const Problem& p) {
     constexpr int kGroups = kHotThreads / kBlock;                   // workgroups of the usual size in one of this kernel
     const bool snap = snap_rows(p, grid.x * kGroups, 0.1, 128.0, 1.0);
     const unsigned chunks = grid.x * kGroups * kWavesPerBlock;
-    if (p.phase != DGSP_PHASE_MAIN && !snap)
+    const RowSharing sharing = snap || p.nnz < kHotSharesNnzMin ? RowSharing{} : make_sharing(p, chunks);
+    if (p.phase != DGSP_PHASE_MAIN && !snap && !sharing.words)
         if (int rc = launch_prepare(p, chunks, 6, -1)) return rc;
     if (p.phase == DGSP_PHASE_PREPARE) return DGSP_OK;
     const Scaling sc{p.alpha, p.beta};
-    const auto launch = [&](auto whole, auto scaled) -> int {
-        DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, false, false, true>), grid, kHotThreads, p.M,
-                            p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, RowSharing{}, hot);
+    const auto launch = [&](auto whole, auto scaled, auto shares) -> int {
+        DGSP_LAUNCH_THREADS((nb_pr_kernel<V, KQ, decltype(whole)::value, decltype(scaled)::value, decltype(shares)::value, false, true>), grid,
+                            kHotThreads, p.M, p.K, p.N, p.ldx, p.ldy, p.rowptr, p.colidx, p.vals, p.X, p.Y, sc, sharing, hot);
         return DGSP_OK;
     };
-    if (p.scaled) return snap ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
-    return snap ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if (snap) return p.scaled ? launch(yes, yes, no) : launch(yes, no, no);
+    if (sharing.words) return p.scaled ? launch(no, yes, yes) : launch(no, no, yes);
+    return p.scaled ? launch(no, yes, no) : launch(no, no, no);
 }
 
 template <int V, int KQ>

@@ -1235,7 +1235,8 @@ struct HotColumns { const unsigned* table; int shift; };
 // power-law graph: 55 % of that one's are on 992 of its 32768 lines - every CU copies these lines when it starts, and a bitmap of
 // the lines with a running count per word says for a column whether it is among them and where.  One workgroup of eight
 // waves per CU, so that its LDS holds one table; the lanes that found their column there switch their gather off.
-// R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 68.7 / 87.1 / 102.2 us; 4 / 6 / 12 / 16 waves instead of
+// R-MAT 2^20 x 16, N = 1 / 2 / 4, whole calls: 92.6 / 103.6 / 113.7 -> 68.7 / 87.1 / 102.2 us (64.4 / 81.3 / 97.7 us where the waves see
+// to the rows that they share themselves, SHARES); 4 / 6 / 12 / 16 waves instead of
 // eight, with tables as large as they leave room for: 88.6 / 73.6 / 75.0 / 77.4 us at N = 1.  Bound by the lines that are left, 8.7
 // million of 14.1 by the L2s' counters, streams included: streams and look-ups alone take 24 us, with the gathers 54 us; which lanes of a gather are
 // switched off, and by offset or by execution mask, makes no difference, nor would packing the others into fewer instructions.
@@ -1251,7 +1252,8 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     constexpr int kWaves = HOT ? kHotThreads / kWave : kWavesPerBlock;
     __shared__ __align__(16) unsigned short s_bnd[kWaves][W];         // which row (of the step) ends with an entry of the block
     __shared__ __align__(16) float s_buf[kWaves][W * V];              // products, then a step's row results
-    __shared__ __align__(16) float s_first[SHARES ? kWaves : 1][V];   // the sum of the first row to end in the chunk
+    constexpr bool kFirstInLds = SHARES && !HOT;
+    __shared__ __align__(16) float s_first[kFirstInLds ? kWaves : 1][V];        // the sum of the first row to end in the chunk
     __shared__ __align__(16) float s_scan[SERIAL_SCAN ? kWaves : 1][SERIAL_SCAN ? kWave * (V + 1) : 1];   // serial scan only
     __shared__ __align__(16) float s_hot[HOT ? hot_floats(V) : 1];    // the hot runs of X
     __shared__ __align__(16) uint2 s_word[HOT ? kHotWords : 1];       // 32 runs: which are hot, how many hot ones lie before
@@ -1277,8 +1279,12 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // the loop, the wait for its word held up the next entries and gathers in every turn.
     RowWord* const words = sharing.words + (size_t)blockIdx.y * plan.split.parts;
     constexpr bool shares = SHARES;
-    static_assert(!SHARES || (!SNAP && !HOT && !SERIAL_SCAN), "no shared rows, or a prepare launch for them");
-    float* const first_sum = s_first[SHARES ? wib : 0];
+    // HOT: between a claim and its publication lies the workgroup's barrier, up to which no wave waits for another workgroup's.
+    static_assert(!SHARES || (!SNAP && !SERIAL_SCAN), "no shared rows, or a prepare launch for them");
+    float* const first_sum = s_first[kFirstInLds ? wib : 0];
+    float first_held[V];                                  // HOT: the same in lane 0, as all LDS is the hot runs'
+#pragma unroll
+    for (int i = 0; i < V; ++i) first_held[i] = 0.0f;
     const int my_column = shared_column<V>(lane, second);
 
     unsigned d0, d1;
@@ -1369,7 +1375,6 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     const int r_first = is;
     const bool first_split = !SNAP && is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
     ChunkEnds ends;
-    if (shares && !idle) ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
 
     // entries of block k of my chunk (lane l: entries 64 e + l of the block); nothing past the chunk's last entry
     // One descriptor pair for the whole chunk (a wave's share of a matrix the library takes stays far below the
@@ -1470,10 +1475,17 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     int c[E]; float a[E], x[E][V];                        // the block whose gathers are in flight
     int lc[E]; float la[E];                               // landing registers of the next block's entries
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
-    if (shares && !idle && ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
-        clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
+    // the zeros; with hot runs behind the entries, as they are waited for together with the runs
+    const auto start_shared_rows = [&] {
+        if (!shares || idle) return;
+        ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
+        if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
+            clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
+    };
+    if constexpr (!HOT) start_shared_rows();
     load_entries(0, c, a);
     load_row_ends(is, is < ie1, w_end);
+    if constexpr (HOT) start_shared_rows();
     if constexpr (HOT) load_hot();
     load_entries(1, lc, la);
     if constexpr (HOT) {
@@ -1660,8 +1672,14 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
                     for (int i = 0; i < V; ++i) val[i] *= sc.alpha;          // an added sum lands on beta * Y (prepare)
                 }
                 if (live && shared) {
-                    if (!shares) add_to_row(y_of(is + t), val);
-                    else store_vec<V>(first_sum, val);
+                    if constexpr (!shares) {
+                        add_to_row(y_of(is + t), val);
+                    } else if constexpr (HOT) {                      // t = 0 of the first 64
+#pragma unroll
+                        for (int i = 0; i < V; ++i) first_held[i] = val[i];
+                    } else {
+                        store_vec<V>(first_sum, val);
+                    }
                 }
             };
             write_rows(0);
@@ -1745,7 +1763,17 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     if (shares) {
         if (ends.shares_head) {
             wave_lds_sync();
-            give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), lane < V ? first_sum[lane] : 0.0f, my_column, sc.beta);
+            float part = 0.0f;
+            if constexpr (HOT) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    const float of_first = read_lane(first_held[i], 0);
+                    part = lane == i ? of_first : part;
+                }
+            } else if (lane < V) {
+                part = first_sum[lane];
+            }
+            give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), part, my_column, sc.beta);
         }
         if (ends.whole_tail) {
             if (lane == 0) {

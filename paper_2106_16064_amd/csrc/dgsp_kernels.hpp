@@ -1282,9 +1282,9 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // HOT: between a claim and its publication lies the workgroup's barrier, up to which no wave waits for another workgroup's.
     static_assert(!SHARES || (!SNAP && !SERIAL_SCAN), "no shared rows, or a prepare launch for them");
     float* const first_sum = s_first[kFirstInLds ? wib : 0];
-    float first_held[V];                                  // HOT: the same in lane 0, as all LDS is the hot runs'
+    float first_held[SHARES && HOT ? V : 1];              // HOT: the same in lane 0, as all LDS is the hot runs'
 #pragma unroll
-    for (int i = 0; i < V; ++i) first_held[i] = 0.0f;
+    for (float& f : first_held) f = 0.0f;
     const int my_column = shared_column<V>(lane, second);
 
     unsigned d0, d1;
@@ -1477,10 +1477,12 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     unsigned w_end;                                       // end offsets of rows is .. is + 63 (lane l: row is + l)
     // the zeros; with hot runs behind the entries, as they are waited for together with the runs
     const auto start_shared_rows = [&] {
-        if (!shares || idle) return;
-        ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
-        if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
-            clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
+        if constexpr (SHARES) {
+            if (idle) return;
+            ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
+            if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
+                clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
+        }
     };
     if constexpr (!HOT) start_shared_rows();
     load_entries(0, c, a);

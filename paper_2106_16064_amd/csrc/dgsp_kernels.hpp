@@ -2191,6 +2191,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     unsigned long long* zeros = s_zeros[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
+    if constexpr (QUEUED) snap = 0;                      // queues are for rows that chunks share
     __builtin_amdgcn_s_setprio(3);
     int probe = 0;
     if constexpr (!QUEUED) probe = first_probe(rowptr, M, lane);
@@ -2287,8 +2288,6 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     is = uniform(is); ie = uniform(ie);
     js = (unsigned)uniform((int)js); je = (unsigned)uniform((int)je);
     const int r_first = first_split ? is : -1;
-    ChunkEnds ends;
-    if (shares) ends = ChunkEnds(share, rowptr, M, chunk, d0, is, ie, js, je);
     const unsigned n_ent = je - js;
     const unsigned long long chunk_bytes = (unsigned long long)n_ent * 4ull;
     const __amdgpu_buffer_rsrc_t rc = make_buffer(colidx + js, chunk_bytes);
@@ -2366,18 +2365,17 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         }
     };
 
+    unsigned w_start, w_end;
+    load_window(is, w_start, w_end);
+    load_entries(0);
+    // Behind the first entries, which otherwise wait for the two rows' bounds, and published when these entries are in LDS: R-MAT 2^18 x 16 at N = 32
+    // 45.8 -> 44.9 us, Poisson 50 000 x 12 at N = 12 without statistics 13.6 -> 13.2 us, Zipf rows of 16 at N = 32 85.4 -> 84.8 us.
+    ChunkEnds ends;
+    if (shares) ends = ChunkEnds(share, rowptr, M, chunk, d0, is, ie, js, je);
     if (shares && ends.starts_tail) {
         const bool clear = uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0;       // as lane 0 found it
         if (clear && g == 0 && col_ok) clear_row<DeviceWords, 4, false>(y_at(ie), 0.0f, mine.skip);
     }
-    unsigned w_start, w_end;
-    load_window(is, w_start, w_end);
-    load_entries(0);
-    if (shares) {                                       // the zeros have been under way as long as the entries
-        stores_done();
-        if (lane == 0) publish_start<DeviceWords>(words + chunk, sharing.call, found);
-    }
-
     float carry[4] = {0.0f, 0.0f, 0.0f, 0.0f};          // sum of the row that is open at the block's start (every group: its columns)
     unsigned done = 0;                                  // entries before the block
     const unsigned third = n_ent > kPacedFrom ? (n_ent + 2u) / 3u : 0u;
@@ -2400,14 +2398,55 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         int listed = 0, windows = 0;                        // zeros[e], bit l: row zeros[E] + 64 e + l has no entries
         bool any_zero = false;
         zeros[E] = (unsigned)is;
+        // 64 rows from `first` on, those without entries: all lane groups together
+        auto write_zeros = [&](int first, unsigned long long m_zero) {
+            const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };          // R rows per round
+            if constexpr (AXPBY) {
+                constexpr int F = G < 4 ? G : 4;        // rounds whose old values are in flight together
+#pragma unroll 1
+                for (int q = 0; q < G; q += F) {
+                    float v[F][4];
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[u][i] = 0.0f;
+                        if (empty(q + u) && sc.beta != 0.0f) load_vec_dword_aligned<4>(y_at(first + (q + u) * R + g), v[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[u][i] = sc.beta != 0.0f ? sc.beta * v[u][i] : 0.0f;
+                        if (empty(q + u)) store_own(y_at(first + (q + u) * R + g), v[u]);
+                    }
+                }
+            } else if constexpr (QUEUED) {                                  // in fewer registers
+                const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+                for (int q = 0; q < G; ++q)
+                    if (empty(q)) write_row(first + q * R + g, zero);
+            } else {
+                const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                const __amdgpu_buffer_rsrc_t ry = make_buffer(Y + (size_t)first * (size_t)ldy, (unsigned long long)kWave * y_pitch);
+                const unsigned long long m_mine = col_ok ? m_zero >> g : 0ull;
+                const unsigned y_mine = (unsigned)g * y_pitch + (unsigned)mine.first * 4u;
+#pragma unroll 4
+                for (int q = 0; q < G; ++q)
+                    if (((m_zero >> (q * R)) & (~0ull >> (kWave - R))) != 0ull)
+                        buffer_store_vec<4, 2>(ry, (m_mine >> (q * R)) & 1ull ? y_mine + (unsigned)(q * R) * y_pitch : kOutOfRange, zero);
+            }
+        };
         auto take_rows = [&](unsigned start, unsigned end) {
             const unsigned rel = end - js;
             const bool live = is + lane < ie && rel <= to;
             const bool has = live && end != start && rel > done;
             const unsigned long long m_has = __ballot(has);
             const unsigned long long m_zero = AXPBY && !snap ? 0ull : __ballot(live && end == start);      // the prepare launch's
-            zeros[windows++] = m_zero;
-            any_zero |= m_zero != 0ull;
+            if constexpr (QUEUED) {
+                if (m_zero != 0ull) write_zeros(is, m_zero);
+            } else {
+                zeros[windows++] = m_zero;
+                any_zero |= m_zero != 0ull;
+            }
             const int cnt = (int)__popcll(__ballot(live));
             if (has) {
                 const unsigned q = rel - done - 1u;
@@ -2423,44 +2462,16 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         // hundreds of such rows, had its first gathers at 25 us of 46 (R-MAT 2^18 x 16 at N = 32).  32-bit offsets, and rounds that
         // no row needs are passed by.  R-MAT 2^12 x 11 at N = 93 13.2 -> 12.1 us, 2^13 x 10 at N = 54 11.4 -> 10.8 us, 2^18 x 16 at N = 32
         // 44.8 -> 43.9 us, 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
-        // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).
+        // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).  Nor with
+        // queues, whose waves have no registers left for it: 2^20 x 16 at N = 32 222.1 us behind, 220.7 in front, Poisson rows of 13,
+        // none of them empty, at N = 60 420.8 and 418.7 us.
         auto treat_empty_rows = [&]() {
             const int zero_from = uniform((int)zeros[E]);
 #pragma unroll 1
             for (int e = 0; e < windows; ++e) {
                 const unsigned long long m_lane = zeros[e];
                 const unsigned long long m_zero = (unsigned long long)(unsigned)uniform((int)(m_lane >> 32)) << 32 | (unsigned)uniform((int)m_lane);
-                if (m_zero == 0ull) continue;
-                const int first = zero_from + e * kWave;
-                if constexpr (AXPBY) {
-                    const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };      // R rows per round
-                    constexpr int F = G < 4 ? G : 4;        // rounds whose old values are in flight together
-#pragma unroll 1
-                    for (int q = 0; q < G; q += F) {
-                        float v[F][4];
-#pragma unroll
-                        for (int u = 0; u < F; ++u) {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) v[u][i] = 0.0f;
-                            if (empty(q + u) && sc.beta != 0.0f) load_vec_dword_aligned<4>(y_at(first + (q + u) * R + g), v[u]);
-                        }
-#pragma unroll
-                        for (int u = 0; u < F; ++u) {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) v[u][i] = sc.beta != 0.0f ? sc.beta * v[u][i] : 0.0f;
-                            if (empty(q + u)) store_own(y_at(first + (q + u) * R + g), v[u]);
-                        }
-                    }
-                } else {
-                    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    const __amdgpu_buffer_rsrc_t ry = make_buffer(Y + (size_t)first * (size_t)ldy, (unsigned long long)kWave * y_pitch);
-                    const unsigned long long m_mine = col_ok ? m_zero >> g : 0ull;
-                    const unsigned y_mine = (unsigned)g * y_pitch + (unsigned)mine.first * 4u;
-#pragma unroll 4
-                    for (int q = 0; q < G; ++q)
-                        if (((m_zero >> (q * R)) & (~0ull >> (kWave - R))) != 0ull)
-                            buffer_store_vec<4, 2>(ry, (m_mine >> (q * R)) & 1ull ? y_mine + (unsigned)(q * R) * y_pitch : kOutOfRange, zero);
-                }
+                if (m_zero != 0ull) write_zeros(zero_from + e * kWave, m_zero);
             }
             windows = 0;
         };
@@ -2481,6 +2492,10 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         if (!any_zero) windows = 0;
         wave_lds_sync();
         load_window(is, w_start, w_end);
+        if (shares && done == 0u) {
+            stores_done();
+            if (lane == 0) publish_start<DeviceWords>(words + chunk, sharing.call, found);
+        }
         if (to < n_ent) load_entries(to);
         if (dealt && windows > 0) treat_empty_rows();
 
@@ -2554,7 +2569,9 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
             }
         }
         __builtin_amdgcn_s_setprio(3);
-        if (windows > 0) treat_empty_rows();
+        if constexpr (!QUEUED) {
+            if (windows > 0) treat_empty_rows();
+        }
         // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's
         //      carry in front; a run that met a row end starts a new segment
         float v[4];

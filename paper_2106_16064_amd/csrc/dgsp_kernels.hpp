@@ -723,27 +723,34 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // The rows at the two ends of a chunk whose first item is d0: rows [is, ie) end in it, entries [js, je) lie in it.
 struct ChunkEnds {
     unsigned head = 0, tail = 0;    // words of row `is` and of row `ie`
-    bool shares_head = false;       // row `is` ends here, started in an earlier chunk and has entries here
-    bool starts_tail = false;       // row `ie` has its first entries here, others in later chunks
-    bool whole_tail = false;        // row `ie` has all its entries here (its end marker is the next chunk's)
-    bool shares_tail = false;       // row `ie` has some of its entries here
+    // In one register: four booleans took a pair of scalar registers each for the whole walk.  Spilled, four booleans -> one word:
+    // nb_pr_kernel at N = 1 to 4 0 to 12 -> 0 to 4 (scaled 7 to 22 -> 2 to 17), vector registers at N = 2 131 -> 127, four waves a SIMD in
+    // place of three; nb_sr_run_kernel 2 to 10 -> 0 to 6.  No call's time moved by more than its runs differ.
+    unsigned kinds = 0;
+    // row `is` ends here, started in an earlier chunk and has entries here
+    __device__ __forceinline__ bool shares_head() const { return (kinds & 1u) != 0u; }
+    // row `ie` has its first entries here, others in later chunks
+    __device__ __forceinline__ bool starts_tail() const { return (kinds & 2u) != 0u; }
+    // row `ie` has all its entries here (its end marker is the next chunk's)
+    __device__ __forceinline__ bool whole_tail() const { return (kinds & 4u) != 0u; }
+    // row `ie` has some of its entries here
+    __device__ __forceinline__ bool shares_tail() const { return (kinds & 8u) != 0u; }
     __device__ __forceinline__ ChunkEnds() {}
     __device__ __forceinline__ ChunkEnds(const EvenSplit& split, const int* __restrict__ rowptr, int M, unsigned chunk, unsigned d0, int is,
                                          int ie, unsigned js, unsigned je) {
         const unsigned h0 = (unsigned)rowptr[is], h1 = (unsigned)rowptr[is < M ? is + 1 : M];
         const unsigned t0 = (unsigned)rowptr[ie], t1 = (unsigned)rowptr[ie < M ? ie + 1 : M];
         const bool here = ie < M && je > (t0 > js ? t0 : js), first = (unsigned)ie + t0 >= d0;
-        shares_head = is < ie && (unsigned)is + h0 < d0 && h1 > js;
-        starts_tail = here && first && t1 > je;
-        whole_tail = here && first && t1 <= je;
-        shares_tail = here && !whole_tail;
+        const bool of_head = is < ie && (unsigned)is + h0 < d0 && h1 > js;
+        const bool starts = here && first && t1 > je, whole = here && first && t1 <= je, of_tail = here && !whole;
+        kinds = (unsigned)uniform((of_head ? 1 : 0) | (starts ? 2 : 0) | (whole ? 4 : 0) | (of_tail ? 8 : 0));
         // whatever the row pointers hold, there is such a word
         const auto word_of = [&](unsigned item) {
             const unsigned c = split.chunk_of(item);
             return (unsigned)uniform((int)(c < split.parts ? c : split.parts - 1u));
         };
-        head = shares_head ? word_of((unsigned)is + h0) : chunk;
-        tail = shares_tail && !starts_tail ? word_of((unsigned)ie + t0) : chunk;
+        head = of_head ? word_of((unsigned)is + h0) : chunk;
+        tail = of_tail && !starts ? word_of((unsigned)ie + t0) : chunk;
     }
 };
 
@@ -934,7 +941,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     if constexpr (shares) {
         first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
         ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js, d1 - (unsigned)ie1);
-        if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)         // as lane 0 found it
+        if (ends.starts_tail() && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)         // as lane 0 found it
             clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
         stores_done();
         if (lane == 0) publish_start<DeviceWords>(words + plan.wave, sharing.call, found);
@@ -1163,16 +1170,16 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     store_pending();                                       // the last tile's rows
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (ends.shares_head) {
+        if (ends.shares_head()) {
             wave_lds_sync();
             give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), lane < V ? first_sum[lane] : 0.0f, my_column, sc.beta);
         }
-        if (ends.whole_tail) {
+        if (ends.whole_tail()) {
             if (lane == 0) {
                 if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
                 store_vec_dword_aligned<V>(y_of(is), carry, second);
             }
-        } else if (ends.shares_tail) {
+        } else if (ends.shares_tail()) {
             float part = carry[0];
 #pragma unroll
             for (int i = 1; i < V; ++i) part = lane == i ? carry[i] : part;
@@ -1481,7 +1488,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
         if constexpr (SHARES) {
             if (idle) return;
             ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js0, je1);
-            if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
+            if (ends.starts_tail() && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)     // as lane 0 found it
                 clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
         }
     };
@@ -1763,7 +1770,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     store_pending();                                       // the last step's rows
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (ends.shares_head) {
+        if (ends.shares_head()) {
             wave_lds_sync();
             float part = 0.0f;
             if constexpr (HOT) {
@@ -1777,12 +1784,12 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
             }
             give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), part, my_column, sc.beta);
         }
-        if (ends.whole_tail) {
+        if (ends.whole_tail()) {
             if (lane == 0) {
                 if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
                 store_vec_dword_aligned<V>(y_of(is), carry, second);
             }
-        } else if (ends.shares_tail) {
+        } else if (ends.shares_tail()) {
             float part = carry[0];
 #pragma unroll
             for (int i = 1; i < V; ++i) part = lane == i ? carry[i] : part;
@@ -2372,7 +2379,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     // 45.8 -> 44.9 us, Poisson 50 000 x 12 at N = 12 without statistics 13.6 -> 13.2 us, Zipf rows of 16 at N = 32 85.4 -> 84.8 us.
     ChunkEnds ends;
     if (shares) ends = ChunkEnds(share, rowptr, M, chunk, d0, is, ie, js, je);
-    if (shares && ends.starts_tail) {
+    if (shares && ends.starts_tail()) {
         const bool clear = uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0;       // as lane 0 found it
         if (clear && g == 0 && col_ok) clear_row<DeviceWords, 4, false>(y_at(ie), 0.0f, mine.skip);
     }
@@ -2610,9 +2617,9 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     } while (done < n_ent);
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (ends.whole_tail) {
+        if (ends.whole_tail()) {
             if (g == 0 && col_ok) write_row(ie, carry);
-        } else if (ends.shares_tail) {
+        } else if (ends.shares_tail()) {
             give_to_row(ends.tail, ie, g == 0 && col_ok, carry);
         }
     } else if (!snap && ie < M) {

@@ -9,6 +9,7 @@ import pytest
 import oracle
 from paper_2106_16064_amd import binding as dg
 from paper_2106_16064_amd import workloads as wl
+from test_chunk_queues import requested
 
 WORDS, PIECES, TABLE = 1024, 512, 3 * 1024
 FLOATS = {1: 31 * 1024, 2: 28 * 1024, 3: 24 * 1024, 4: 20 * 1024}
@@ -168,10 +169,20 @@ def test_products_with_hot_runs(name, M, K, law):
             x.copy_(dX)
             ok, worst = oracle.within_bound(D.spmm(x).cpu().numpy(), ref, bnd, 1e-5)
             assert ok, worst
-        # waves that take whole rows share none, so nothing is prepared; some of them have no row at all here
-        kernels = launches(lambda: D.spmm(dX))
-        assert any("nb_pr_kernel" in k for k in kernels)
-        assert any("nb_prepare_kernel" in k for k in kernels) == (name != "whole rows")
+        # One launch: waves see to the rows that they share, with a word a wave.  Waves that take whole rows share none; some of them
+        # have no row at all here.
+        shares = name != "whole rows"
+        Y = torch.full((A.M, N), float("nan"), device="cuda")
+        kernels = launches(lambda: D.spmm(dX, Y=Y))
+        assert any("nb_pr_kernel" in k for k in kernels) and not any("nb_prepare_kernel" in k for k in kernels)
+        assert requested(lambda: D.spmm(dX, Y=Y)) == (8 * 8 * torch.cuda.get_device_properties(0).multi_processor_count if shares else 0)
+        # a call in two phases has no memory for them: there the launch in front clears the rows
+        Y = torch.full((A.M, N), float("nan"), device="cuda")
+        phase = lambda which: dg.dgsp_spmm_csr_phase(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_PR, which, f)  # noqa: E731
+        assert any("nb_prepare_kernel" in k for k in launches(lambda: phase(dg.PHASE_PREPARE))) == shares
+        assert any("nb_pr_kernel" in k for k in launches(lambda: phase(dg.PHASE_MAIN)))
+        ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+        assert ok, worst
         # the product looks at the table
         lies = dg.MatrixFeatures.from_buffer_copy(bytes(f))
         lies.hot_columns = zeros_table()

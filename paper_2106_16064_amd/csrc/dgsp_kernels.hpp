@@ -2178,6 +2178,8 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
 // entries per row below which neighbouring chunks go to different XCDs
 __host__ __device__ constexpr int run_dealt_below(int log_lanes) { return log_lanes >= 5 ? 8 : 6; }
 
+// Four workgroups a CU in all forms: without the bound the scaled ones of two and of four lanes take 130 and 132 vector registers, three waves a
+// SIMD (three / four: lognormal 100 001 x 20 at N = 8 25.3 / 21.8 us, 2^16 x 16 at N = 16 24.6 / 23.4 us); the others fit anyway.
 template <int LOGG, bool XBUF, bool AXPBY, bool QUEUED = false, bool SHARES = false>
 __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K, int N, int ldx, int ldy,
                                                            const int* __restrict__ rowptr, const int* __restrict__ colidx,
@@ -2199,6 +2201,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
     if constexpr (QUEUED) snap = 0;                      // queues are for rows that chunks share
+    constexpr bool kZerosBehind = !QUEUED && !AXPBY;
     __builtin_amdgcn_s_setprio(3);
     int probe = 0;
     if constexpr (!QUEUED) probe = first_probe(rowptr, M, lane);
@@ -2448,7 +2451,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
             const bool has = live && end != start && rel > done;
             const unsigned long long m_has = __ballot(has);
             const unsigned long long m_zero = AXPBY && !snap ? 0ull : __ballot(live && end == start);      // the prepare launch's
-            if constexpr (QUEUED) {
+            if constexpr (!kZerosBehind) {
                 if (m_zero != 0ull) write_zeros(is, m_zero);
             } else {
                 zeros[windows++] = m_zero;
@@ -2469,9 +2472,11 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         // hundreds of such rows, had its first gathers at 25 us of 46 (R-MAT 2^18 x 16 at N = 32).  32-bit offsets, and rounds that
         // no row needs are passed by.  R-MAT 2^12 x 11 at N = 93 13.2 -> 12.1 us, 2^13 x 10 at N = 54 11.4 -> 10.8 us, 2^18 x 16 at N = 32
         // 44.8 -> 43.9 us, 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
-        // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).  Nor with
-        // queues, whose waves have no registers left for it: 2^20 x 16 at N = 32 222.1 us behind, 220.7 in front, Poisson rows of 13,
-        // none of them empty, at N = 60 420.8 and 418.7 us.
+        // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).  kZerosBehind: nor with
+        // queues, whose waves have no registers left for it (2^20 x 16 at N = 32 222.1 us behind, 220.7 in front, Poisson rows of 13,
+        // none of them empty, at N = 60 420.8 and 418.7 us), nor in the scaled form, where the prepare launch sees to these rows or few are
+        // empty, and remembering them costs for nothing (behind / in front 2^12 x 16 at N = 8 10.2 / 10.1 us, Zipf 30 001 x 30 at N = 16 / 33 20.3 / 33.4 and
+        // 20.1 / 33.0 us, lognormal 100 001 x 20 at N = 5 / 16 21.9 / 31.1 and 21.2 / 30.4 us).
         auto treat_empty_rows = [&]() {
             const int zero_from = uniform((int)zeros[E]);
 #pragma unroll 1
@@ -2576,7 +2581,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
             }
         }
         __builtin_amdgcn_s_setprio(3);
-        if constexpr (!QUEUED) {
+        if constexpr (kZerosBehind) {
             if (windows > 0) treat_empty_rows();
         }
         // ---- the open row across the groups' runs: inclusive segmented sum of what each run leaves open, the block's

@@ -72,6 +72,7 @@ def test_what_sharing_rows_costs_the_forms_that_do(resources):
     assert len(hot) == 8
     for r in hot:                                          # eight waves a CU, two a SIMD
         assert r["vgpr_count"] <= 256 and r["vgpr_spill_count"] == 0 and r["sgpr_spill_count"] <= 17
+    assert all(r["vgpr_count"] <= 128 for name, r in resources.items() if "nb_sr_run_kernel" in name)      # four waves a SIMD
     runs = {name: r for name, r in resources.items() if re.search(r"nb_sr_run_kernelILi\dELb\dELb0ELb0ELb1E", name)}
     assert len(runs) == 14
     for name, r in runs.items():

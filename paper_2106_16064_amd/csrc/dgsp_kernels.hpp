@@ -723,9 +723,10 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // The rows at the two ends of a chunk whose first item is d0: rows [is, ie) end in it, entries [js, je) lie in it.
 struct ChunkEnds {
     unsigned head = 0, tail = 0;    // words of row `is` and of row `ie`
-    // In one register: four booleans took a pair of scalar registers each for the whole walk.  Spilled, four booleans -> one word:
-    // nb_pr_kernel at N = 1 to 4 0 to 12 -> 0 to 4 (scaled 7 to 22 -> 2 to 17), vector registers at N = 2 131 -> 127, four waves a SIMD in
-    // place of three; nb_sr_run_kernel 2 to 10 -> 0 to 6.  No call's time moved by more than its runs differ.
+    // In one register (uniform(): the compiler takes it apart again otherwise), as four booleans were in a pair of scalar registers each
+    // for the whole walk.  Spilled, four booleans -> one word: nb_pr_kernel at N = 1 to 4 0 to 12 -> 0 to 4 (scaled 7 to 22 -> 2 to 17), vector
+    // registers at N = 2 131 -> 127, four waves a SIMD in place of three; nb_sr_run_kernel 2 to 10 -> 0 to 6.  No call's time moved by more
+    // than its runs differ.
     unsigned kinds = 0;
     // row `is` ends here, started in an earlier chunk and has entries here
     __device__ __forceinline__ bool shares_head() const { return (kinds & 1u) != 0u; }
@@ -2191,13 +2192,14 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
     __shared__ __align__(16) uint2 s_ent[kWavesPerBlock][W];            // row offset in X, value
     __shared__ unsigned s_bits[kWavesPerBlock][W / 32 + 2];             // bit e: a row ends with entry e of the block
     __shared__ int s_rows[kWavesPerBlock][W + 1];                       // those rows, in order
-    __shared__ unsigned long long s_zeros[kWavesPerBlock][E + 1];       // which of the rows on the way have no entries
+    struct EmptyRows { unsigned long long which[E]; int from; };        // bit l of which[e]: row from + 64 e + l has no entries
+    __shared__ EmptyRows s_empty[kWavesPerBlock];
     const int lane = lane_id();
     const int wib = wave_in_block();
     uint2* ent = s_ent[wib];
     unsigned* bits = s_bits[wib];
     int* rows = s_rows[wib];
-    unsigned long long* zeros = s_zeros[wib];
+    EmptyRows& remembered = s_empty[wib];
     const int gl = lane & (G - 1), g = lane >> LOGG;
 
     if constexpr (QUEUED) snap = 0;                      // queues are for rows that chunks share
@@ -2405,9 +2407,9 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         if (lane < W / 32 + 2) bits[lane] = 0u;
         wave_lds_sync();
         // ---- rows that end in this block: a bit at their last entry, their numbers in order; which rows have no entries
-        int listed = 0, windows = 0;                        // zeros[e], bit l: row zeros[E] + 64 e + l has no entries
-        bool any_zero = false;
-        zeros[E] = (unsigned)is;
+        int listed = 0, windows = 0;                        // windows of 64 rows that are remembered
+        unsigned any_zero = 0u;
+        if constexpr (kZerosBehind) remembered.from = is;
         // 64 rows from `first` on, those without entries: all lane groups together
         auto write_zeros = [&](int first, unsigned long long m_zero) {
             const auto empty = [&](int q) { return ((m_zero >> (q * R + g)) & 1ull) != 0ull && col_ok; };          // R rows per round
@@ -2454,8 +2456,8 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
             if constexpr (!kZerosBehind) {
                 if (m_zero != 0ull) write_zeros(is, m_zero);
             } else {
-                zeros[windows++] = m_zero;
-                any_zero |= m_zero != 0ull;
+                remembered.which[windows++] = m_zero;
+                any_zero |= (unsigned)m_zero | (unsigned)(m_zero >> 32);
             }
             const int cnt = (int)__popcll(__ballot(live));
             if (has) {
@@ -2478,12 +2480,12 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         // empty, and remembering them costs for nothing (behind / in front 2^12 x 16 at N = 8 10.2 / 10.1 us, Zipf 30 001 x 30 at N = 16 / 33 20.3 / 33.4 and
         // 20.1 / 33.0 us, lognormal 100 001 x 20 at N = 5 / 16 21.9 / 31.1 and 21.2 / 30.4 us).
         auto treat_empty_rows = [&]() {
-            const int zero_from = uniform((int)zeros[E]);
+            const int from = uniform(remembered.from);
 #pragma unroll 1
             for (int e = 0; e < windows; ++e) {
-                const unsigned long long m_lane = zeros[e];
+                const unsigned long long m_lane = remembered.which[e];
                 const unsigned long long m_zero = (unsigned long long)(unsigned)uniform((int)(m_lane >> 32)) << 32 | (unsigned)uniform((int)m_lane);
-                if (m_zero != 0ull) write_zeros(zero_from + e * kWave, m_zero);
+                if (m_zero != 0ull) write_zeros(from + e * kWave, m_zero);
             }
             windows = 0;
         };
@@ -2495,13 +2497,13 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
             for (int m = 0; m < E - 1; ++m) load_window(is + m * kWave, ms[m], me[m]);
             if (windows > 1) {
                 treat_empty_rows();
-                zeros[E] = (unsigned)is;
+                remembered.from = is;
             }
 #pragma unroll
             for (int m = 0; m < E - 1; ++m)
                 if (crowded) crowded = take_rows(ms[m], me[m]);
         }
-        if (!any_zero) windows = 0;
+        if (any_zero == 0u) windows = 0;
         wave_lds_sync();
         load_window(is, w_start, w_end);
         if (shares && done == 0u) {

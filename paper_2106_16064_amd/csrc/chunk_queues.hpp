@@ -47,10 +47,11 @@ struct ChunkQueues {
     DGSP_HOST_DEVICE unsigned queue_from(unsigned part) const { return part_from(part) + waves * run; }
     // The host counts with a bound of the entries where it does not know them.  Fewer items: fewer chunks of the same size, and shorter
     // first pieces to the same share - or, where the host would not have chosen queues had it known (`fewest` items, `fewest_a_row`
-    // entries a row), equal shares for all waves, as without queues: run = 0, a chunk of whole 64 items a wave.  Arrays twice / four times / eight
-    // times as long as the matrix, queues all the same -> equal shares: R-MAT 2^18 x 16 at N = 64 86 / 94 / 100 -> 86 / 89 / 89 us,
-    // 2^20 x 6 at N = 50 216 / 224 / 224 -> 205 us, Zipf rows of 16 at N = 64 164 / 173 / 173 -> 165 us, of 10 at N = 100 403 / 423 / 423 ->
-    // 415 us, lognormal rows of 20 at N = 100 433 / 438 / 439 -> 440 us; the line is the same as for calls that know the count.
+    // entries a row), equal shares for all waves, as without queues: run = 0, a chunk a wave, even to 64 items (without queues to 32:
+    // kRunQuantumLog2).  Arrays twice / four times / eight times as long as the matrix, queues all the same -> equal shares: R-MAT
+    // 2^18 x 16 at N = 64 86 / 94 / 100 -> 86 / 89 / 89 us, 2^20 x 6 at N = 50 216 / 224 / 224 -> 205 us, Zipf rows of 16 at N = 64
+    // 164 / 173 / 173 -> 165 us, of 10 at N = 100 403 / 423 / 423 -> 415 us, lognormal rows of 20 at N = 100 433 / 438 / 439 -> 440 us;
+    // the line is the same as for calls that know the count.
     DGSP_HOST_DEVICE void fit(unsigned items, unsigned rows) {
         const unsigned quanta = EvenSplit(items, 1u, size_log2).Q;
         if (items >= fewest && items - rows >= (unsigned long long)fewest_a_row * rows) {

@@ -8,8 +8,9 @@
 // started, because the machine is busy with other launches, writes its own part instead.
 //
 // Nobody waits for a wave that has not started: a word is `call` only between a claim and the same wave's publish(), and in
-// between no wave waits for another.  Every claim is published, whether there turns out to be a row or not, so a wait ends for
-// any contents of the row pointers.
+// between no wave waits for another workgroup's.  The waves of one workgroup start together, so they may meet at a barrier
+// there which all of them reach without waiting for anything else (nb_pr_kernel with hot runs).  Every claim is published, whether
+// there turns out to be a row or not, so a wait ends for any contents of the row pointers.
 //
 // `call` is even and of no other call of the process (next_call_number()), so that the words need no clearing: memory that other
 // kernels or other processes have used holds one of the two numbers with a chance of 2^-62 a word.

@@ -105,7 +105,7 @@ bool fits() {
 bool even_split() {
     for (int i = 0; i < 3000; ++i) {
         const unsigned items = i % 3 == 0 ? between(1, 5000) : between(1, 4000000000u), parts = between(1, i % 2 ? 5000 : 70);
-        const EvenSplit s(items, parts, between(6, 10));
+        const EvenSplit s(items, parts, between(5, 10));
         if (s.start(0) != 0) return false;
         for (unsigned c = 0; c < parts; c += between(1, parts / 64 + 1)) {
             const unsigned long long from = (unsigned long long)c * s.Q / parts << s.shift, to = (unsigned long long)(c + 1) * s.Q / parts << s.shift;

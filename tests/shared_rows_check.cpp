@@ -84,6 +84,50 @@ bool in_turn() {
     return true;
 }
 
+// Waves of a workgroup that meet at a barrier between their claims and their publications, as where they fill LDS together.
+struct Meeting {
+    std::atomic<int> missing;
+    explicit Meeting(int waves) : missing(waves) {}
+    void meet() {
+        for (--missing; missing.load() > 0;) std::this_thread::yield();
+    }
+};
+
+// A list of chunks, a wave each, whose last row goes on in the next chunk: workgroups that start all at once, or one only when the one
+// before it - or behind it - has ended, which is when nobody may wait for waves that have not started.
+bool workgroups_that_meet() {
+    constexpr int kGroups = 5, kWaves = 3, kChunks = kGroups * kWaves;
+    for (RowWord call = 1000; call < 1000 + 2 * 300; call += 2) {
+        std::vector<Row> rows(kChunks);
+        for (Row& r : rows) { r.word = 7 * call; r.sum = -9; }
+        const auto wave = [&](int chunk, Meeting& meeting) {
+            Row& mine = rows[chunk];
+            const RowWord found = dgsp::claim_row<Words>(&mine.word, call);
+            if (dgsp::mine_to_clear(found, call)) mine.sum.store(0);
+            meeting.meet();
+            dgsp::publish_start<Words>(&mine.word, call, found);
+            if (chunk > 0) give(rows[chunk - 1], call, 100);
+            give(mine, call, 1);
+        };
+        const auto group = [&](int g) {
+            Meeting meeting(kWaves);
+            std::vector<std::thread> waves;
+            for (int w = 0; w < kWaves; ++w) waves.emplace_back([&, w] { wave(g * kWaves + w, meeting); });
+            for (auto& w : waves) w.join();
+        };
+        if (call % 6 == 4) {
+            std::vector<std::thread> groups;
+            for (int g = 0; g < kGroups; ++g) groups.emplace_back([&, g] { group(g); });
+            for (auto& g : groups) g.join();
+        } else {
+            for (int g = 0; g < kGroups; ++g) group(call % 6 == 0 ? g : kGroups - 1 - g);
+        }
+        for (int c = 0; c < kChunks; ++c)
+            if (rows[c].sum != (c + 1 < kChunks ? 101 : 1) || rows[c].word != call + 1) return false;
+    }
+    return true;
+}
+
 // A claim is published whether there is a row to clear or not, except where somebody else holds the word and will.
 bool every_claim_ends() {
     for (const RowWord before : {0ull, 41ull, 39ull, ~0ull}) {
@@ -180,6 +224,7 @@ int main(int argc, char** argv) {
     if (!strcmp(argv[1], "in_turn")) return in_turn() ? 0 : 1;
     if (!strcmp(argv[1], "ragged_blocks")) return ragged_blocks() ? 0 : 1;
     if (!strcmp(argv[1], "call_numbers")) return call_numbers() ? 0 : 1;
+    if (!strcmp(argv[1], "workgroups_that_meet")) return workgroups_that_meet() ? 0 : 1;
     if (!strcmp(argv[1], "every_claim_ends")) return every_claim_ends() ? 0 : 1;
     return 2;
 }

@@ -14,7 +14,8 @@ from test_chunk_queues import queue_bytes, requested
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends", "ragged_blocks", "call_numbers"])
+@pytest.mark.parametrize("check", ["every_part_once", "the_start_comes_late", "in_turn", "every_claim_ends", "ragged_blocks", "call_numbers",
+                                   "workgroups_that_meet"])
 def test_waves_agree_on_a_row(check, tmp_path):
     exe = tmp_path / "shared_rows_check"
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-o", str(exe), os.path.join(ROOT, "tests", "shared_rows_check.cpp")],

@@ -34,11 +34,14 @@ def single_entries():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("make", [long_rows, short_rows, single_entries])
+@pytest.mark.parametrize("make, dealt", [(long_rows, False), (short_rows, True), (single_entries, True)])
 @pytest.mark.parametrize("N", [4, 7, 8, 15, 16, 33, 64, 93, 128, 257])
-def test_rows_without_entries(make, N):
+def test_rows_without_entries(make, dealt, N):
+    """`dealt`: with fewer than six entries a row (eight from 32 lanes a row of X on) chunks are dealt out to the XCDs and such rows are
+    written in front of the walk, others behind it."""
     import torch
     A = make()
+    assert A.nnz // A.M < 6 if dealt else A.nnz // A.M >= 8
     D = dg.DeviceCsr(A)
     X = wl.dense_matrix(A.K, N, "normal", seed=N)
     ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)

@@ -1,5 +1,6 @@
 """Rows whose entries several waves of a balanced kernel hold, in products without a launch that clears them first: calls that have
 memory for it (RowSharing), against the oracle and against the calls of the C interface, which have none."""
+import math
 import os
 import subprocess
 
@@ -49,12 +50,23 @@ def ends_at_every_item():
     return rows_of(lens, 3001, 2)
 
 
+def ends_at_32_items():
+    """The same around 32 items, the quantum of nb_sr's run kernel."""
+    lens = np.concatenate([[0]] + [np.full(150, k) for k in range(29, 35)] + [[900, 0, 31, 4000, 0, 0]] + [np.full(60, k) for k in (15, 16, 61, 62, 63)] +
+                          [np.ones(90, int), [1500], np.zeros(33, int)])
+    return rows_of(lens, 2003, 6)
+
+
+def few_items():
+    return rows_of([0, 3, 0, 29, 1, 33, 0, 64, 1], 70, 7)
+
+
 def hubs():
     """A power-law graph's rows: hubs over many chunks, half of the rows empty; six million entries and more (entry blocks)."""
     return wl.rmat_csr(17, 56, seed=4)
 
 
-CASES = [("one row", one_row), ("ends", ends_at_every_item), ("hubs", hubs)]
+CASES = [("one row", one_row), ("ends", ends_at_every_item), ("ends at 32", ends_at_32_items), ("few items", few_items), ("hubs", hubs)]
 
 
 @pytest.mark.gpu
@@ -101,6 +113,47 @@ def test_shared_rows(name, make):
                     assert memory in queue_bytes(A.nnz, A.M)
                 ok, worst = oracle.within_bound(Y.cpu().numpy(), -2.0 * ref + beta * Y0, 2.0 * bnd + beta * np.abs(Y0), 1e-5)
                 assert ok, worst
+
+
+LAYOUTS = {16: (2, 1), 32: (3, 1), 64: (4, 1), 128: (4, 2), 300: (5, 3)}       # log2 of the lanes a row of X, column blocks
+ITEMS_A_CU = 700                                                                # kSharedRunItems
+
+
+def workgroups(items, N, cus):
+    """All column blocks' where nb_sr's run kernel shares rows: one a CU and as many more as the square root of the CU's items over 700,
+    and no more than leave a wave 64 items, 128 below eight lanes.  None: as many as fit, four a CU."""
+    lanes, blocks = LAYOUTS[N]
+    per_cu = 1 + math.floor(math.sqrt(items * blocks / (cus * ITEMS_A_CU)))
+    if per_cu >= 4:
+        return None
+    least = 64 if lanes >= 3 else 128
+    most = min(cus * per_cu, math.ceil(items * blocks / (4 * least)))
+    groups = max(1, int(most / blocks))
+    return -(-groups * blocks // 8) * 8 if blocks == 2 else groups * blocks         # two blocks: every XCD works on one of them
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", sorted(LAYOUTS))
+def test_workgroups_follow_the_items(N):
+    """Around the steps of the rule, from a single entry on: as many words as waves, and the right product."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    blocks = LAYOUTS[N][1]
+    steps = [k * k * ITEMS_A_CU * cus // blocks for k in (1, 2, 3) if N <= 64 or k == 1]
+    for items in [2, 33, 64, 65, 128, 129, 513, 1025, 64 * 4 * cus // blocks + 1] + [s + d for s in steps for d in (-1, 0, 1)]:
+        M = 1 if items < 64 else max(1, min(items // 9, 3001))
+        lens = np.random.default_rng(items).multinomial(items - M, np.full(M, 1.0 / M))
+        A = rows_of(lens, 1501, items)
+        assert A.nnz + A.M == items
+        D = dg.DeviceCsr(A)
+        X = wl.dense_matrix(A.K, N, "normal", seed=N)
+        ref, bnd = oracle.spmm_ref(A.M, A.K, N, A.rowptr, A.colidx, A.vals, X)
+        dX, Y = torch.from_numpy(X).cuda(), torch.full((A.M, N), float("nan"), device="cuda")
+        print(f"[case] workgroups items={items} N={N}", flush=True)
+        memory = requested(lambda: dg.dgsp_spmm_csr_nnz(A.M, A.K, N, A.nnz, D.rowptr, D.colidx, D.vals, dX, Y, dg.NB_SR))
+        assert memory == 8 * 4 * (workgroups(items, N, cus) or 4 * cus)
+        ok, worst = oracle.within_bound(Y.cpu().numpy(), ref, bnd, 1e-5)
+        assert ok, worst
 
 
 @pytest.mark.gpu

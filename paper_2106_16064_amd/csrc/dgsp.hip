@@ -765,7 +765,13 @@ inline SrColumns nb_sr_run_columns(int64_t N, double saved_share, int switches) 
 
 // Workgroups (all column blocks') where waves agree on shared rows among themselves: per CU as many as the square root of its items over
 // this.  A wave pays for a start and two shared rows whatever its share, the others' gathers wait meanwhile, and what a wave
-// alone cannot hide grows with the share.
+// alone cannot hide grows with the share.  1 / 2 / 3 / 4 workgroups a CU, us:
+//   0.2 M items: R-MAT 2^14 x 20 at N = 72 21.1 / 17.6 / 18.6 / 19.9, 6001 rows of 40 at N = 95 18.6 / 17.1 / 20.0 / 22.0 (two are taken)
+//   0.5 M: 12 001 rows of 40 at N = 95 30.5 / 24.2 / 26.9 / 27.5; 0.7 M: R-MAT 2^15 x 20 at N = 95 36.8 / 27.7 / 27.2 / 28.5 (two)
+//   1.1 M: R-MAT 2^16 x 16 at N = 72 / 95 56.8 / 37.0 / 32.9 / 33.0 and 58.7 / 39.8 / 37.5 / 38.1 (three)
+//   1.6 M: 27 705 rows of 56 over 17 795 columns at N = 72 / 95 77.8 / 48.3 / 43.4 / 41.7 and 82.6 / 54.7 / 56.9 / 55.8, R-MAT 2^16 x 24 at
+//   N = 95 80.0 / 52.3 / 47.1 / 48.8 (three)
+// From 17 lanes a row of X on rows of one length would do with two at any size, by up to 5 %, where power-law graphs lose up to 12 %.
 constexpr double kSharedRunItems = 700.0;
 inline unsigned shared_run_blocks(const Problem& p, int resident, unsigned col_blocks, int logG, unsigned others) {
     if (!may_share(p) || p.size < 0) return others;

@@ -2473,7 +2473,7 @@ __global__ __launch_bounds__(kBlock, 4) void nb_sr_run_kernel(int M, long long K
         // behind the walk, and behind the bounds of further rows: in front of either, a chunk at the sparse end of a graph, with
         // hundreds of such rows, had its first gathers at 25 us of 46 (R-MAT 2^18 x 16 at N = 32).  32-bit offsets, and rounds that
         // no row needs are passed by.  R-MAT 2^12 x 11 at N = 93 13.2 -> 12.1 us, 2^13 x 10 at N = 54 11.4 -> 10.8 us, 2^18 x 16 at N = 32
-        // 44.8 -> 43.9 us, 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
+        // 46.1 -> 45.1 us (on another GPU 44.8 -> 43.9 us), 2^18 x 10 at N = 87 in a slice 134.6 -> 122.4 us.  Not where rows are dealt out with few entries each: there all
         // chunks have such rows, and their stores would all come at the end (2^18 x 6 at N = 35 36.6 us in front, 38.2 behind).  kZerosBehind: nor with
         // queues, whose waves have no registers left for it (2^20 x 16 at N = 32 222.1 us behind, 220.7 in front, Poisson rows of 13,
         // none of them empty, at N = 60 420.8 and 418.7 us), nor in the scaled form, where the prepare launch sees to these rows or few are

@@ -67,7 +67,7 @@ def test_what_sharing_rows_costs_the_forms_that_do(resources):
     assert plain["1"]["vgpr_count"] <= 128 and plain["2"]["vgpr_count"] <= 128 and scaled["1"]["vgpr_count"] <= 128
     for v in "1234":
         assert plain[v]["vgpr_spill_count"] == scaled[v]["vgpr_spill_count"] == 0
-        assert plain[v]["sgpr_spill_count"] <= 4 and scaled[v]["sgpr_spill_count"] <= 17
+        assert plain[v]["sgpr_spill_count"] <= 4 and scaled[v]["sgpr_spill_count"] <= 15
     hot = [r for name, r in resources.items() if re.search(r"nb_pr_kernelILi\dELi2ELb0ELb\dELb1ELb0ELb1E", name)]
     assert len(hot) == 8
     for r in hot:                                          # eight waves a CU, two a SIMD

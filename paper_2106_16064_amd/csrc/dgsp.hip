@@ -603,8 +603,8 @@ inline bool wants_hot_columns(const dgsp_internal_stats_t& s, int64_t N) {
 // has memory for it, at all sizes that have a table.  With the prepare launch / without: R-MAT 2^20 x 16 at N = 1 / 2 / 3 / 4 68.2 / 85.3 / 97.5 /
 // 101.6 -> 64.4 / 81.3 / 93.5 / 97.7 us, scaled at N = 1 / 4 74.2 / 106.8 -> 70.0 / 103.4 us, 2^20 x 32 114.1 -> 110.0 us, 2^18 x 32 32.6 ->
 // 30.0 us, 2^19 x 16 with its gradient 75.6 -> 70.6 us; the smallest, 4.2 million entries and more: 2^19 x 8 at N = 1 / 2 / 4 26.5 / 30.4 / 36.3 ->
-// 24.1 / 28.1 / 33.5 us, 2^19 x 12 at N = 1 / 4 32.5 / 45.8 -> 29.7 / 42.6 us, 2^18 x 20 24.9 / 34.8 -> 22.8 / 32.3 us, 2^19 x 10 scaled 32.5 / 43.4 ->
-// 29.9 / 40.2 us, 2^18 x 18 with its gradient at N = 2 56.8 -> 52.7 us.
+// 24.1 / 28.1 / 33.5 us, 2^19 x 12 at N = 1 / 4 32.5 / 45.8 -> 29.7 / 42.6 us, 2^18 x 20 24.9 / 34.8 -> 22.8 / 32.3 us, 2^19 x 10 scaled 32.4 / 43.4 ->
+// 29.6 / 40.7 us, 2^18 x 18 with its gradient at N = 2 56.8 -> 52.7 us.
 template <int V>
 int launch_nb_pr_hot(const Problem& p) {
     constexpr int KQ = kNbPrKq;

@@ -723,41 +723,48 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // The rows at the two ends of a chunk whose first item is d0: rows [is, ie) end in it, entries [js, je) lie in it.
 struct ChunkEnds {
     unsigned head = 0, tail = 0;    // words of row `is` and of row `ie`
-    bool shares_head = false;       // row `is` ends here, started in an earlier chunk and has entries here
-    bool starts_tail = false;       // row `ie` has its first entries here, others in later chunks
-    bool whole_tail = false;        // row `ie` has all its entries here (its end marker is the next chunk's)
-    bool shares_tail = false;       // row `ie` has some of its entries here
+    bool gives_head = false, starts = false, whole = false, gives_tail = false;
+    // row `is` ends here, started in an earlier chunk and has entries here
+    __device__ __forceinline__ bool shares_head() const { return gives_head; }
+    // row `ie` has its first entries here, others in later chunks
+    __device__ __forceinline__ bool starts_tail() const { return starts; }
+    // row `ie` has all its entries here (its end marker is the next chunk's)
+    __device__ __forceinline__ bool whole_tail() const { return whole; }
+    // row `ie` has some of its entries here
+    __device__ __forceinline__ bool shares_tail() const { return gives_tail; }
     __device__ __forceinline__ ChunkEnds() {}
     __device__ __forceinline__ ChunkEnds(const EvenSplit& split, const int* __restrict__ rowptr, int M, unsigned chunk, unsigned d0, int is,
                                          int ie, unsigned js, unsigned je) {
         const unsigned h0 = (unsigned)rowptr[is], h1 = (unsigned)rowptr[is < M ? is + 1 : M];
         const unsigned t0 = (unsigned)rowptr[ie], t1 = (unsigned)rowptr[ie < M ? ie + 1 : M];
         const bool here = ie < M && je > (t0 > js ? t0 : js), first = (unsigned)ie + t0 >= d0;
-        shares_head = is < ie && (unsigned)is + h0 < d0 && h1 > js;
-        starts_tail = here && first && t1 > je;
-        whole_tail = here && first && t1 <= je;
-        shares_tail = here && !whole_tail;
+        gives_head = is < ie && (unsigned)is + h0 < d0 && h1 > js;
+        starts = here && first && t1 > je;
+        whole = here && first && t1 <= je;
+        gives_tail = here && !whole;
         // whatever the row pointers hold, there is such a word
         const auto word_of = [&](unsigned item) {
             const unsigned c = split.chunk_of(item);
             return (unsigned)uniform((int)(c < split.parts ? c : split.parts - 1u));
         };
-        head = shares_head ? word_of((unsigned)is + h0) : chunk;
-        tail = shares_tail && !starts_tail ? word_of((unsigned)ie + t0) : chunk;
+        head = gives_head ? word_of((unsigned)is + h0) : chunk;
+        tail = gives_tail && !starts ? word_of((unsigned)ie + t0) : chunk;
     }
 };
 
-// The same in three registers, for kernels that keep them over a long walk: four booleans take a pair of scalar registers each (uniform(): the
-// compiler takes the word apart again otherwise).  Spilled, four booleans -> one word: nb_pr_kernel at N = 1 to 4 0 to 12 -> 0 to 4 (scaled
-// 7 to 22 -> 2 to 15), vector registers at N = 2 131 -> 127, four waves a SIMD in place of three; nb_sr_run_kernel 2 to 10 -> 0 to 6.  Their
-// calls' times did not move by more than runs differ.  Not in nb_pr_tiled_kernel, whose chunks are short: 0.3 % slower in the mean of 18
-// calls (R-MAT 2^17 x 16 scaled at N = 1 16.8 -> 16.9 us, lognormal 100 003 x 30 at N = 4 without statistics 23.4 -> 23.6 us).
+// The same in three registers, for kernels that keep them over a long walk: four booleans take a pair of scalar registers each
+// (uniform(): the compiler takes the word apart again otherwise).  Spilled, four booleans -> one word: nb_pr_kernel at N = 1 / 2 0 / 8 ->
+// 0 / 4 (scaled 7 / 18 -> 2 / 15), vector registers at N = 2 131 -> 127, four waves a SIMD in place of three; nb_sr_run_kernel 2 to 10 -> 0 to
+// 6.  Their calls' times did not move by more than runs differ.  Not elsewhere, where it frees scalar registers alone: nb_pr_kernel at N = 3 and 4
+// is slower with it (Zipf 165 040 x 44 at N = 3 / 4 47.4 / 47.5 -> 47.9 / 47.9 us, 0.3 % in the mean of 12 calls), and so are hot runs (R-MAT
+// 2^20 x 16 scaled at N = 1 / 2 70.1 / 85.5 -> 70.5 / 86.3 us, at N = 4 103.9 -> 102.5 us) and the tiles, whose chunks are short (0.3 % in the mean of
+// 18 calls, R-MAT 2^17 x 16 scaled at N = 1 16.8 -> 16.9 us, lognormal 100 003 x 30 at N = 4 without statistics 23.4 -> 23.6 us).
 struct HeldEnds {
     unsigned head = 0, tail = 0, kinds = 0;
     __device__ __forceinline__ HeldEnds() {}
     __device__ __forceinline__ HeldEnds(const ChunkEnds& e)
         : head(e.head), tail(e.tail),
-          kinds((unsigned)uniform((e.shares_head ? 1 : 0) | (e.starts_tail ? 2 : 0) | (e.whole_tail ? 4 : 0) | (e.shares_tail ? 8 : 0))) {}
+          kinds((unsigned)uniform((e.shares_head() ? 1 : 0) | (e.starts_tail() ? 2 : 0) | (e.whole_tail() ? 4 : 0) | (e.shares_tail() ? 8 : 0))) {}
     __device__ __forceinline__ bool shares_head() const { return (kinds & 1u) != 0u; }
     __device__ __forceinline__ bool starts_tail() const { return (kinds & 2u) != 0u; }
     __device__ __forceinline__ bool whole_tail() const { return (kinds & 4u) != 0u; }
@@ -951,7 +958,7 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     if constexpr (shares) {
         first_split = is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
         ends = ChunkEnds(plan.split, rowptr, M, plan.wave, d0, is, ie1, js, d1 - (unsigned)ie1);
-        if (ends.starts_tail && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)         // as lane 0 found it
+        if (ends.starts_tail() && uniform(mine_to_clear(found, sharing.call) ? 1 : 0) != 0 && my_column >= 0)         // as lane 0 found it
             clear_row<DeviceWords, 1, AXPBY>(y_of(ie1) + my_column, sc.beta);
         stores_done();
         if (lane == 0) publish_start<DeviceWords>(words + plan.wave, sharing.call, found);
@@ -1180,16 +1187,16 @@ __global__ __launch_bounds__(kBlock) void nb_pr_tiled_kernel(int M, long long K,
     store_pending();                                       // the last tile's rows
     // the row still open at the end of my chunk is finished by another wave
     if (shares) {
-        if (ends.shares_head) {
+        if (ends.shares_head()) {
             wave_lds_sync();
             give_part<AXPBY>(words + ends.head, sharing.call, seen_head, y_of(r_first), lane < V ? first_sum[lane] : 0.0f, my_column, sc.beta);
         }
-        if (ends.whole_tail) {
+        if (ends.whole_tail()) {
             if (lane == 0) {
                 if constexpr (AXPBY) scale_into<V, true>(carry, y_of(is), sc, second);
                 store_vec_dword_aligned<V>(y_of(is), carry, second);
             }
-        } else if (ends.shares_tail) {
+        } else if (ends.shares_tail()) {
             float part = carry[0];
 #pragma unroll
             for (int i = 1; i < V; ++i) part = lane == i ? carry[i] : part;
@@ -1392,7 +1399,7 @@ __global__ __launch_bounds__(HOT ? kHotThreads : kBlock) void nb_pr_kernel(int M
     // the first row to end in my chunk started before it?  then its sum is shared with another wave
     const int r_first = is;
     const bool first_split = !SNAP && is < M && (unsigned)is + (unsigned)rowptr[is] < d0;
-    HeldEnds ends;
+    std::conditional_t<!HOT && V <= 2, HeldEnds, ChunkEnds> ends;
 
     // entries of block k of my chunk (lane l: entries 64 e + l of the block); nothing past the chunk's last entry
     // One descriptor pair for the whole chunk (a wave's share of a matrix the library takes stays far below the

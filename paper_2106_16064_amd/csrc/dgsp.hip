@@ -771,7 +771,8 @@ inline SrColumns nb_sr_run_columns(int64_t N, double saved_share, int switches) 
 //   1.1 M: R-MAT 2^16 x 16 at N = 72 / 95 56.8 / 37.0 / 32.9 / 33.0 and 58.7 / 39.8 / 37.5 / 38.1 (three)
 //   1.6 M: 27 705 rows of 56 over 17 795 columns at N = 72 / 95 77.8 / 48.3 / 43.4 / 41.7 and 82.6 / 54.7 / 56.9 / 55.8, R-MAT 2^16 x 24 at
 //   N = 95 80.0 / 52.3 / 47.1 / 48.8 (three)
-// From 17 lanes a row of X on rows of one length would do with two at any size, by up to 5 %, where power-law graphs lose up to 12 %.
+// From 17 lanes a row of X on rows that are alike would do with two at any size (up to 6 %; at N = 200 with one, 7 %), where power-law
+// graphs lose up to 12 %.
 constexpr double kSharedRunItems = 700.0;
 inline unsigned shared_run_blocks(const Problem& p, int resident, unsigned col_blocks, int logG, unsigned others) {
     if (!may_share(p) || p.size < 0) return others;
